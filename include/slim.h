@@ -77,7 +77,7 @@ typedef enum {
     SLIM_ERR_ALIGN = -3,      /* a pointer is not 16-byte aligned                     */
     SLIM_ERR_WORKSPACE = -4,  /* workspace missing or smaller than slim_workspace_bytes */
     SLIM_ERR_HIP = -5,        /* a HIP runtime call failed (launch error)             */
-    SLIM_ERR_WAIT = -6        /* slim_workspace_check: a decode call gave up waiting  */
+    SLIM_ERR_WAIT = -6        /* slim_workspace_check: a forward call gave up waiting */
 } slim_status;
 
 /* d_out, d_in and the true adapter rank (0 = layer without adapters). */
@@ -272,8 +272,9 @@ int slim_unpack(const uint8_t *qvals, const uint8_t *meta, slim_shape shape, int
  * the decode kernel advances it on every replay).  No result is carried between calls: one
  * workspace (of the largest size needed) can serve any sequence of layers and
  * token counts.  Two calls that overlap in time need two workspaces.
- * Diagnostics: the one-launch decode kernel waits, inside the kernel, for its own
- * T = X R^T; the wait is bounded.  Should it ever run out (it never should),
+ * Diagnostics: the one-launch decode kernel, and slim_linear_gemm and slim_lowrank
+ * on small batches (up to 512 tokens, where their tiles leave compute units free), wait,
+ * inside the kernel, for their own T = X R^T; the wait is bounded.  Should it ever run out (it never should),
  * the outputs that depend on the missing part are NaN -- a failed call cannot
  * pass for a result -- and word 2 of the workspace is set to 1.
  * slim_workspace_check reads that word back: it synchronizes `stream` (so it is
@@ -343,8 +344,8 @@ int slim_linear_gemv_static(const slim_layer *layer, const slim_half *X, int32_t
  *           roles as two launches (where that geometry fits, else as 0); 2 as -1;
  *           3 a test of the kernel's bounded wait: where the one-launch geometry
  *           fits, only the half of the kernel that waits for T is launched, with
- *           the wait cut to 256 polls, so it gives up: every wavefront still ends
- *           normally, Y is NaN and the workspace's error word is set
+ *           the wait cut to 256 polls, so it gives up (slim_linear_gemm on a small
+ *           batch likewise): every wavefront still ends normally, Y is NaN and the workspace's error word is set
  *           (slim_workspace_check then reports SLIM_ERR_WAIT);
  *   lds_kb  0: plan with the device's LDS; 16..160: with at most this many KiB
  *           (X then streams through the LDS in chunks on small layers too).
@@ -379,14 +380,16 @@ int slim_decode_plan(const slim_layer *layer, int32_t m, int32_t *out);
 int slim_gemm_tile_order(int32_t n, int32_t m, int32_t *out, size_t count);
 
 /*
- * slim_linear_gemm -- prefill-shaped forward, any m >= 1 (meant for m >= 64):
+ * slim_linear_gemm -- prefill-shaped forward, any m >= 1 (meant for m > 16):
  * Y = X W^C + (X L) R of Sec. 3.2 in this header's orientation; by the count of
  * App. "Computation Reduction Analysis" (Eq. 13) the 2:4 mask halves the
  * multiply-adds of the weight term, quantization saves none, and the adapters
  * add 2 m r (n + k).
  * Matrix-core GEMM over the compressed weights with the adapter product
  * T = X R^T (rounded once to fp16) folded in as extra k-steps, row scale
- * applied to the fp32 accumulators, Y rounded once to fp16.
+ * applied to the fp32 accumulators, Y rounded once to fp16.  Small batches
+ * (up to 512 tokens on layers whose tiles leave compute units free) run on
+ * smaller tiles, in one launch together with T where all of it is resident.
  * Requires k % 128 == 0.  Errors as slim_linear_gemv.
  */
 int slim_linear_gemm(const slim_layer *layer, const slim_half *X, int32_t m, slim_half *Y,

@@ -53,7 +53,10 @@ WorkspacePlan plan_workspace(int32_t n, int32_t k, int32_t rank_pad, int32_t m, 
     p.t16_off = p.dec_off + 256 + 2 * round256((size_t)16 * rank_pad * sizeof(float));
     p.dec_bytes = p.t16_off + round256((size_t)4 * 16 * (rank_pad / 4) * 16) - p.dec_off;
     p.t_off = p.dec_off + p.dec_bytes;
-    p.t_bytes = m > 16 ? round256((size_t)m * rank_pad * sizeof(uint16_t)) : 0;
+    // (the small-batch path, up to 512 tokens, keeps T in pieces of 16 bytes per four ranks, whole tiles of 32 tokens and
+    // 64 ranks)
+    const size_t t_pieces = (size_t)tl_rows(m < 512 ? m : 512) * ((rank_pad + 63) / 64 * 64) * 4, t_rows = (size_t)m * rank_pad * sizeof(uint16_t);
+    p.t_bytes = m > 16 ? round256(t_pieces > t_rows ? t_pieces : t_rows) : 0;
     p.acc_off = p.t_off + p.t_bytes;
     p.acc_bytes = m <= 16 ? round256((size_t)plan_decode(n, k, rank_pad, m).slots * m * n * sizeof(float)) : 0;
     p.part_off = p.acc_off + p.acc_bytes;

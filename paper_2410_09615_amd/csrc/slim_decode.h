@@ -47,6 +47,44 @@ __device__ __forceinline__ void packed_half(const UnitRegs &b, const half_t *xh,
     }
 }
 
+// ---- pieces of T = X R^T that travel between workgroups of one launch ----
+// The number that tags a call's pieces.  A launch argument normally; a launch that is being captured into a
+// graph would replay with the same number and take the pieces of the previous replay for its own, so there
+// the number lives in the workspace and a one-thread kernel ahead of the launch advances it on every
+// replay.  The top bit keeps the two kinds apart.
+struct CallEpoch {
+    unsigned number;         // top bit clear, never 0, or
+    const unsigned *where;   // under stream capture: the word of the workspace that holds it
+};
+CallEpoch next_call_epoch(unsigned *ctr, hipStream_t st);      // slim_gemv_fused.hip
+
+__device__ __forceinline__ unsigned call_epoch(const CallEpoch &e)
+{
+    return e.where ? (__builtin_nontemporal_load(e.where) | 0x80000000u) : e.number;
+}
+
+constexpr int kScopeDevice = 16;      // cache policy of a buffer access: device scope (written through / read from memory)
+
+// A piece of T: {epoch, two dwords of four fp16 ranks, epoch ^ dword ^ dword}.  The reader accepts it only if
+// the first dword is this call's epoch and the last one is the checksum of the three before it, so a piece
+// whose dwords come from two different stores (should a 128-bit store ever become visible in parts) is
+// taken for "not there yet" and read again, unless the old and the new data have the same checksum --
+// which they do when they are the same data.  Only single dwords need to be atomic for that.
+__device__ __forceinline__ bool piece_valid(const uint4_t &pc, unsigned epoch)
+{
+    return pc[0] == epoch && pc[3] == (pc[0] ^ pc[1] ^ pc[2]);
+}
+__device__ __forceinline__ void store_piece(rsrc_t r, uint32_t off, unsigned epoch, uint2_t hb)
+{
+    typedef unsigned int store4_t __attribute__((__vector_size__(16)));
+    const store4_t piece = {epoch, hb[0], hb[1], epoch ^ hb[0] ^ hb[1]};
+    __builtin_amdgcn_raw_buffer_store_b128(piece, r, (int)off, 0, kScopeDevice);
+}
+__device__ __forceinline__ uint4_t load_piece(rsrc_t r, uint32_t off)
+{
+    return __builtin_bit_cast(uint4_t, __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, kScopeDevice));
+}
+
 // Geometry and launch of the one-launch decode path (slim_gemv_fused.hip).
 struct FusedPlan {
     bool ok;            // the layer and token count fit this path

@@ -273,6 +273,9 @@ int launch_gemm_sparse(const uint8_t *qvals, const uint8_t *meta, const float *s
 int launch_lowrank_decode(const half_t *X, int m, const half_t *R, const half_t *L, int n, int k, int rank, int rank_pad,
                           half_t *Y, int accumulate, float *T, void *T16, unsigned *ctrl, hipStream_t st);   // slim_gemv.hip
 
+int launch_gemm_mid(const slim_layer *layer, const half_t *X, int xf, const float *x_scale, int m, half_t *Y, void *T, size_t t_room,
+                    unsigned *ctrl, bool weight_term, int accumulate, hipStream_t st, bool *taken);   // slim_gemm_mid.hip
+
 }  // namespace slim
 
 using namespace slim;
@@ -313,6 +316,10 @@ static int linear_gemm(const slim_layer *layer_in, const void *X, int xf, const 
     float *P = reinterpret_cast<float *>(ws + p.part_off);
     const int rp = layer->rank_pad;
     const half_t *Xh = reinterpret_cast<const half_t *>(X);
+    bool taken = false;
+    const int mid = launch_gemm_mid(layer, Xh, xf, x_info, m, reinterpret_cast<half_t *>(Y), T, p.total - p.t_off,
+                                    reinterpret_cast<unsigned *>(ws + p.dec_off), true, 0, st, &taken);
+    if (taken) return mid;
     const half_t *Lh = q4 ? nullptr : reinterpret_cast<const half_t *>(layer->L);
     const half_t *Rh = q4 ? nullptr : reinterpret_cast<const half_t *>(layer->R);
     const half_t *Ls = reinterpret_cast<const half_t *>(layer->Ls), *Rs = reinterpret_cast<const half_t *>(layer->Rs);
@@ -366,6 +373,14 @@ extern "C" int slim_lowrank(const slim_half *X, int32_t m, const slim_half *R, c
 
     if ((uint64_t)shape.n * (uint64_t)rank_pad * 2 > 0xFFFFFFFFull) return SLIM_ERR_SHAPE;
     half_t *T = reinterpret_cast<half_t *>(ws + p.t_off);
+    slim_layer adapters{};
+    adapters.shape = shape;
+    adapters.L = L;
+    adapters.R = R;
+    adapters.rank_pad = rank_pad;
+    bool taken = false;
+    const int mid = launch_gemm_mid(&adapters, Xh, 0, nullptr, m, Yh, T, p.total - p.t_off, reinterpret_cast<unsigned *>(ws + p.dec_off), false, accumulate, st, &taken);
+    if (taken) return mid;
     const int rc = launch_t(Xh, m, Rh, shape.k, rank_pad, T, reinterpret_cast<float *>(ws + p.part_off), p.splits, st);
     if (rc != SLIM_OK) return rc;
     const int chunk = token_chunk(rank_pad);

@@ -1,0 +1,766 @@
+// slim_linear_gemm on few tokens: Y = scale * (X Wc^T) + T L^T where the 512 x 128 tiles of
+// slim_gemm_sparse.hip leave most of the chip idle.
+//
+// What bounds such a call is not a rate but launches (a dependent one costs 4 us) and the latency of
+// a workgroup's chain of loads, on the few compute units that have a tile.  So the tiles are
+// smaller, the inputs of a tile are divided among the eight wavefronts of its workgroup, X and the
+// weights go from memory to LDS without registers, a round of stages at a time and several rounds
+// ahead, and T = X R^T is made by other workgroups of the same launch meanwhile:
+//
+//   T role  (the first workgroups; they wait for nothing) tiles of 16 ranks x 16 tokens, the inputs divided
+//           among the wavefronts and added up in LDS: no partial sums in memory.  T leaves as 16-byte
+//           pieces that carry the number of the call (slim_decode.h), written through to memory.
+//   Y role  a tile of 32 RT RG rows x 32 NT tokens.  Wavefront (rg, kw) of the RG x KW = 8 owns RT row
+//           tiles and every KW-th stage of 128 inputs, then every KW-th unit of ranks, for which it
+//           re-reads its pieces of T until they carry this call's number; the KW partial tiles meet in LDS.
+//           Four more wavefronts (helpers) only bring X: loads return in order, so a wavefront that waited for its
+//           X (from the L2) would wait for all weights (from memory) it has asked for before.
+//
+// The two roles share a launch only if all its workgroups are resident at once (one workgroup per
+// compute unit), so that nothing that is waited for is queued behind something that waits; otherwise
+// they are two launches.  The wait is bounded either way, and one that gives up makes its outputs
+// NaN and sets the workspace's error word.
+//
+// X in LDS: a token's stage is one row without padding (the loads write LDS in lane order), so the
+// pieces of 16 bytes of a row are stored permuted by the token number: the sixteen lanes that read
+// together then hit all banks once.
+#include "slim_decode.h"
+#include "slim_mma.h"
+
+namespace slim {
+
+typedef int int4_t __attribute__((ext_vector_type(4)));
+typedef int int8v_t __attribute__((ext_vector_type(8)));
+
+struct MidArgs {
+    const uint8_t *qvals;
+    const uint8_t *meta;
+    const float *scale;
+    const half_t *X;      // [m][k] fp16, or (XF != 0) the same tensor as 8-bit codes
+    const float *x_scale; // XF != 0: the tensor's scale (device memory)
+    const half_t *R, *L;  // fp16 adapters in the adapter layout, or null with the 4-bit form:
+    const uint8_t *Rq, *Lq;
+    const half_t *Rs, *Ls;
+    uint4_t *T;           // pieces of T (mid_t_piece())
+    unsigned *err;        // set to 1 when a wait gave up
+    CallEpoch epoch;
+    half_t *Y;            // [m][n]
+    int n, k, rank, rank_pad, m;
+    int tiles_o;          // row tiles of the Y role
+    int n_t;              // workgroups in the T role, the first of the grid (a multiple of 8)
+    int t_tiles;          // tiles of T
+    int spin_limit;       // polls after which a wait gives up
+    int stages;           // stages of 128 inputs of the weight term (0: the adapter term alone)
+    int accumulate;       // add to what Y holds
+};
+
+constexpr int kMidWaves = 8, kMidHelpers = 4, kMidThreads = (kMidWaves + kMidHelpers) * kWave;
+constexpr uint32_t kPastEnd = 0xFFFFFFF0u;      // byte offset past the end of every buffer here
+
+// Eight 8-bit codes (two dwords) -> eight fp16 values, exactly (E4M3: XF 1, E5M2: XF 2).
+template <int XF>
+__device__ __forceinline__ half8_t codes8_to_half8(uint32_t lo, uint32_t hi)
+{
+    typedef float f2_t __attribute__((ext_vector_type(2)));
+    uint4_t out;
+#pragma unroll
+    for (int d = 0; d < 2; ++d) {
+        const int src = (int)(d ? hi : lo);
+        const f2_t p0 = XF == 1 ? __builtin_amdgcn_cvt_pk_f32_fp8(src, false) : __builtin_amdgcn_cvt_pk_f32_bf8(src, false);
+        const f2_t p1 = XF == 1 ? __builtin_amdgcn_cvt_pk_f32_fp8(src, true) : __builtin_amdgcn_cvt_pk_f32_bf8(src, true);
+        out[2 * d] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(p0[0], p0[1]));
+        out[2 * d + 1] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(p1[0], p1[1]));
+    }
+    return __builtin_bit_cast(half8_t, out);
+}
+
+// The adapter term runs in units of 32 ranks, two steps of V_MFMA_F32_32X32X16_F16 each.  Step s of unit u
+// multiplies on lane half h the ranks
+//   fp16 L   32 u + 16 s + 8 h + [0, 8): a wavefront's load of L is one contiguous KiB per step
+//   4-bit L  64 (u / 2) + 32 h + 16 (u % 2) + 8 s + [0, 8): 8 bytes of codes are both steps of a row
+// (of 4-bit L the last unit can lie past the padded rank in part: zeros on both sides).
+template <bool AQ>
+__host__ __device__ __forceinline__ int mid_units(int rank_pad) { return AQ ? 2 * ((rank_pad + 63) / 64) : rank_pad / 32; }
+template <bool AQ>
+__device__ __forceinline__ uint32_t mid_rank(uint32_t u, uint32_t s, uint32_t h)
+{
+    return AQ ? 64u * (u >> 1) + 32u * h + 16u * (u & 1u) + 8u * s : 32u * u + 16u * s + 8u * h;
+}
+// T as pieces {call number, four fp16 ranks, checksum}, ordered [32 tokens][unit][step][four ranks of the eight][h]
+// [token]: the B operand of a step is two contiguous KiB.  The piece of token t and ranks r .. r + 3 (r % 4 == 0):
+template <bool AQ>
+__device__ __forceinline__ uint32_t mid_t_piece(uint32_t t, uint32_t r, int rank_pad)
+{
+    const uint32_t u = AQ ? 2u * (r >> 6) + ((r >> 4) & 1u) : r >> 5;
+    const uint32_t st = AQ ? (r >> 3) & 1u : (r >> 4) & 1u, h = AQ ? (r >> 5) & 1u : (r >> 3) & 1u;
+    return ((t >> 5) * (uint32_t)mid_units<AQ>(rank_pad) + u) * 4096u + (2u * st + ((r >> 2) & 1u)) * 1024u + (32u * h + (t & 31u)) * 16u;
+}
+template <bool AQ>
+__host__ __device__ __forceinline__ uint32_t mid_t_bytes(int m, int rank_pad) { return (uint32_t)((m + 31) / 32 * mid_units<AQ>(rank_pad)) * 4096u; }
+
+// Tile j of a role whose workgroups are dealt to the dies in turn (index mod 8): the tiles of one row tile
+// run on one die, whose L2 then reads the row tile once.  A role has die_tiles() workgroups; false: no tile.
+__device__ __forceinline__ bool tile_on_die(int b, int tiles_o, int &ot, int &tt)
+{
+    const int per = (tiles_o + kDies - 1) / kDies, j = b / kDies;
+    ot = b % kDies + kDies * (j % per);
+    tt = j / per;
+    return ot < tiles_o;
+}
+static int die_tiles(int tiles_o, int tiles_t) { return (tiles_o + kDies - 1) / kDies * kDies * tiles_t; }
+
+// One load instruction of 64 x 16 bytes from a buffer (per-lane offset, which is range-checked, and a uniform
+// one, which is not) to 1 KiB of LDS at byte address lds_byte (uniform), in lane order.  The compiler does not
+// see the load: the caller waits for it.  DEV: device scope (from memory, not from this die's L2).
+template <bool DEV = false>
+__device__ __forceinline__ void load_to_lds(rsrc_t r, uint32_t lane_off, uint32_t uniform_off, uint32_t lds_byte)
+{
+    if constexpr (DEV)
+        asm volatile("s_mov_b32 m0, %3\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, %2 offen sc1 lds"
+                     :
+                     : "v"(lane_off), "s"(r), "s"(uniform_off), "s"(lds_byte)
+                     : "memory");
+    else
+        asm volatile("s_mov_b32 m0, %3\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, %2 offen lds"
+                     :
+                     : "v"(lane_off), "s"(r), "s"(uniform_off), "s"(lds_byte)
+                     : "memory");
+}
+
+// T tile of 16 ranks x 16 tokens.  A unit is 256 inputs: eight steps of V_MFMA_F32_16X16X32_F16, R from memory
+// into registers in operand order (runs of 256 bytes), X through LDS: in operand order neighbouring lanes are
+// different tokens, and such a load costs the address unit four times one that reads along the rows.
+// Wavefront w takes the units w, w + 12, ..., with 8 KiB of LDS of its own.
+// Which columns step t multiplies on lane quarter ly is free as long as R and X agree:
+//   fp16 R, fp16 X   32 t + 8 ly + [0, 8)
+//   fp16 R, 8-bit X  64 (t / 2) + 16 ly + 8 (t % 2) + [0, 8): two steps share one 16-byte load of codes
+//   4-bit R          64 ly + 8 t + [0, 8): the 64 columns of a lane are consecutive (32 bytes of codes, one scale)
+constexpr int kTUnitLds = 8192;
+template <int XF, bool AQ>
+__device__ __forceinline__ void t_tile(const MidArgs &a, int rt, int tt, char *lds_c, unsigned epoch)
+{
+    constexpr int TW = kMidWaves + kMidHelpers;
+    constexpr int ROWB = XF ? 256 : 512, PIECES = ROWB / 16, TPI = 64 / PIECES, NX = 16 / TPI;
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int lx = lane & 15, ly = lane >> 4;
+    const int units = (a.k + 255) / 256;
+    const uint32_t k = (uint32_t)a.k, xb = XF ? 1u : 2u;
+    const int tok = 16 * tt + lx;
+    const rsrc_t x_rs = make_rsrc(a.X, (uint32_t)a.m * k * xb);
+    const rsrc_t r_rs = AQ ? make_rsrc(a.Rq, (uint32_t)q4_code_bytes(a.rank, a.k)) : make_rsrc(a.R, (uint32_t)tl_bytes(a.rank_pad, a.k));
+    const rsrc_t s_rs = make_rsrc(AQ ? a.Rs : nullptr, AQ ? (uint32_t)q4_scale_bytes(a.rank, a.k) : 0u);
+    char *const xl = lds_c + wave * kTUnitLds;
+    const uint32_t xl0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)lds_c + (uint32_t)(wave * kTUnitLds);
+
+    auto column = [&](int u, int t) -> uint32_t {
+        if (AQ) return 256u * u + 64u * ly + 8u * t;
+        if (XF) return 256u * u + 64u * (t >> 1) + 16u * ly + 8u * (t & 1);
+        return 256u * u + 32u * t + 8u * ly;
+    };
+    float4_t acc0 = {0.f, 0.f, 0.f, 0.f}, acc1 = acc0;
+    __syncthreads();                            // the tile before this one is done with LDS
+    for (int u = wave; u < units; u += TW) {
+        // a token's 256 inputs are one row of LDS, its pieces of 16 bytes permuted by the token number
+#pragma unroll
+        for (int j = 0; j < NX; ++j) {
+            const int tj = TPI * j + lane / PIECES;
+            const uint32_t col = (uint32_t)((lane % PIECES) ^ tj) * (16u / xb);
+            const bool ok = 16 * tt + tj < a.m && 256u * u + col < k;
+            load_to_lds(x_rs, ok ? ((uint32_t)(16 * tt + tj) * k + 256u * u + col) * xb : kPastEnd, 0u, xl0 + (uint32_t)j * 1024u);
+        }
+        uint4_t rv[8];
+        half_t sc = (half_t)1.0f;
+        if constexpr (AQ) {
+            const bool ok = column(u, 0) < k;
+            const uint32_t base = ok ? q4_piece(16u * rt + lx, 4u * u + ly, q4_ctiles(a.k)) : kPastEnd;
+            rv[0] = load16(r_rs, base, 0);
+            rv[1] = load16(r_rs, ok ? base + 16u : kPastEnd, 0);
+            sc = load_half(s_rs, ok ? ((16u * rt + lx) * q4_groups(a.k) + 2u * u + (ly >> 1)) * 2u : kPastEnd, 0);
+        } else {
+#pragma unroll
+            for (int t = 0; t < 8; ++t) {
+                const uint32_t c = column(u, t);
+                rv[t] = load16(r_rs, c < k ? tl_piece(16u * rt + lx, c >> 3, k) : kPastEnd, 0);
+            }
+        }
+        asm volatile("s_waitcnt vmcnt(0)" : : : "memory");
+#pragma unroll
+        for (int t = 0; t < 8; ++t) {
+            const uint32_t c = column(0, t) * xb;               // byte of the row
+            const uint4_t xv = *reinterpret_cast<const uint4_t *>(xl + lx * ROWB + (((c >> 4) ^ (uint32_t)lx) << 4));
+            half8_t av, bv;
+            if constexpr (AQ)
+                av = codes_to_half8(rv[t >> 2][t & 3]) * sc;
+            else
+                av = __builtin_bit_cast(half8_t, rv[t]);
+            if constexpr (XF == 0)
+                bv = __builtin_bit_cast(half8_t, xv);
+            else
+                bv = codes8_to_half8<XF>(xv[2 * (t & 1)], xv[2 * (t & 1) + 1]);
+            if (t & 1)
+                acc1 = __builtin_amdgcn_mfma_f32_16x16x32_f16(av, bv, acc1, 0, 0, 0);
+            else
+                acc0 = __builtin_amdgcn_mfma_f32_16x16x32_f16(av, bv, acc0, 0, 0, 0);
+        }
+        asm volatile("s_waitcnt lgkmcnt(0)" : : : "memory");     // the row of LDS has been read
+    }
+    float *const red = reinterpret_cast<float *>(lds_c);
+    // lane holds token lx, ranks 16 rt + 4 ly .. + 3
+    float4_t acc = acc0 + acc1;
+    __syncthreads();
+    if (wave != 0) *reinterpret_cast<float4_t *>(red + ((wave - 1) * kWave + lane) * 4) = acc;
+    __syncthreads();
+    if (wave == 0) {
+#pragma unroll
+        for (int w = 0; w < kMidWaves + kMidHelpers - 1; ++w) acc += *reinterpret_cast<const float4_t *>(red + (w * kWave + lane) * 4);
+        if (XF) acc *= *a.x_scale;
+        const half4_t h = {(half_t)acc[0], (half_t)acc[1], (half_t)acc[2], (half_t)acc[3]};
+        store_piece(make_rsrc(a.T, mid_t_bytes<AQ>(a.m, a.rank_pad)), mid_t_piece<AQ>((uint32_t)tok, 16u * rt + 4u * ly, a.rank_pad),
+                    epoch, __builtin_bit_cast(uint2_t, h));
+    }
+}
+
+// Geometry of mid_kernel: the LDS of a round of X (shared) and of a round of weights (private to the wavefronts),
+// and how many rounds of each are there at a time.
+template <int NT_, int RT, int RG, int KW, int XF>
+struct MidLds {
+    static constexpr int ROWB = XF ? 128 : 256;                 // bytes of a token's stage
+    static constexpr int STAGE = NT_ * 32 * ROWB;               // bytes of a stage of X
+    static constexpr int XSLOT = KW * STAGE;
+    static constexpr int WBYTES = RT * 2048;                    // a wavefront's weights of a stage, or its rows of L of a unit of ranks
+    static constexpr int WSLOT = kMidWaves * WBYTES;
+    static constexpr int LDS = 160 * 1024;
+    static constexpr int XRING = 3 * XSLOT + 4 * WSLOT <= LDS ? 3 : 2;
+    static constexpr int WFIT = (LDS - XRING * XSLOT) / WSLOT;
+    static constexpr int WRING = WFIT > 8 ? 8 : WFIT;
+    // a round of the adapter term: UPR units of 32 ranks per wavefront of a row tile, as pieces (4 KiB per unit and 32 tokens)
+    // (XRING == 2: the helpers wait for every load anyway, and rounds may have different numbers of them)
+    static constexpr int UFIT = XSLOT / (KW * NT_ * 4096);
+    static constexpr int UPR = XRING == 2 && UFIT > WRING - 1 ? WRING - 1 : UFIT;
+    static constexpr int PARTS = (KW - 1) * RG * RT * NT_ * 4096;
+    static constexpr int TROLE = (kMidWaves + kMidHelpers) * kTUnitLds;
+    static constexpr int EITHER = PARTS > TROLE ? PARTS : TROLE;
+    static constexpr int ROUNDS = XRING * XSLOT + WRING * WSLOT;
+    static constexpr int BYTES = ROUNDS > EITHER ? ROUNDS : EITHER;
+    static_assert(RG * KW == kMidWaves, "eight working wavefronts");
+    static_assert(WRING >= 2 && BYTES <= LDS, "LDS of a compute unit");
+};
+
+template <int NT_, int RT, int RG, int KW, int XF, bool AQ>
+__global__ __launch_bounds__(kMidThreads, 3) void mid_kernel(MidArgs a)
+{
+    using G = MidLds<NT_, RT, RG, KW, XF>;
+    constexpr int ROWB = G::ROWB, STAGE = G::STAGE, XRING = G::XRING, WRING = G::WRING;
+    constexpr int TPI = 1024 / ROWB;                     // tokens per load instruction
+    constexpr int PIECES = ROWB / 16;
+    extern __shared__ __attribute__((aligned(16))) char lds_c[];
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int li = lane & 31, lb = lane >> 5;
+    const int rg = wave % RG, kw = wave / RG;
+    const unsigned epoch = a.rank_pad > 0 ? call_epoch(a.epoch) : 0u;
+    if ((int)blockIdx.x < a.n_t) {
+        for (int j = blockIdx.x; j < a.t_tiles; j += a.n_t) {
+            int rt, tr;
+            if (tile_on_die(j, a.rank_pad / 16, rt, tr)) t_tile<XF, AQ>(a, rt, tr, lds_c, epoch);
+        }
+        return;
+    }
+    int ot, tt;
+    if (!tile_on_die((int)blockIdx.x - a.n_t, a.tiles_o, ot, tt)) return;
+    const int o0 = (ot * RG + rg) * RT * 32;             // this wavefront's rows
+    const int t0 = tt * NT_ * 32;
+    const uint32_t k = (uint32_t)a.k, rp = (uint32_t)a.rank_pad;
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)lds_c;
+
+    constexpr int UPR = G::UPR;
+    const int units = mid_units<AQ>(a.rank_pad);         // of 32 ranks
+    const int rounds = (a.stages + KW - 1) / KW, t_rounds = (units + KW * UPR - 1) / (KW * UPR);
+    const rsrc_t dt = make_rsrc(a.T, mid_t_bytes<AQ>(a.m, a.rank_pad));
+    const uint32_t kt = k / 128;
+    const uint32_t xb = XF ? 1u : 2u;
+    if (wave >= kMidWaves) {
+        // ---- helpers: X -> LDS ----
+        // A round has KW * 32 NT / TPI load instructions, NX to a helper; instruction q moves the tokens
+        // TPI (q mod IPS) .. of stage q / IPS; lane -> (token, slot piece), source piece = slot piece ^ swizzle(token).
+        // Tokens past the last read as zeros; stages past the last, whose data nobody uses, repeat the last.
+        constexpr int IPS = NT_ * 32 / TPI, NX = KW * IPS / kMidHelpers;
+        static_assert(KW * IPS % kMidHelpers == 0 && IPS % kMidHelpers == 0, "every helper issues the same loads for every stage");
+        const int hw = wave - kMidWaves;
+        const rsrc_t dx = make_rsrc(a.X, (uint32_t)a.m * k * xb);
+        uint32_t xv[IPS / kMidHelpers];
+#pragma unroll
+        for (int j = 0; j < IPS / kMidHelpers; ++j) {
+            const int tok = TPI * (hw + kMidHelpers * j) + lane / PIECES;
+            const uint32_t piece = (uint32_t)((lane % PIECES) ^ (XF ? (tok >> 1) & 7 : tok & 15));
+            xv[j] = (uint32_t)(t0 + tok) * k * xb + piece * 16u;
+        }
+        // Rounds of the adapter term follow: the units of 32 ranks (u KW + kw) of this round, each 4 KiB of pieces per
+        // 32 tokens.  In the launch that makes T they are read from memory, not through the L2, and may come too early:
+        // the reader of a piece checks it.  Units past the last and tokens past the last tile read as zeros.
+        auto load_round = [&](int round, int slot) {
+            const uint32_t base = lds0 + (uint32_t)(slot * G::XSLOT + hw * 1024);
+            if (round < rounds || t_rounds == 0) {
+#pragma unroll
+                for (int q = 0; q < KW; ++q) {
+                    const int s = min(round * KW + q, a.stages - 1);
+#pragma unroll
+                    for (int j = 0; j < IPS / kMidHelpers; ++j)
+                        load_to_lds(dx, xv[j], (uint32_t)s * ROWB, base + (uint32_t)(q * STAGE + kMidHelpers * j * 1024));
+                }
+            } else {
+                // instruction (q, it, i): quarter hw of unit u, tokens 32 it .. 32 it + 31
+#pragma unroll
+                for (int q = 0; q < KW; ++q)
+#pragma unroll
+                    for (int i = 0; i < UPR; ++i) {
+                        const int u = ((round - rounds) * UPR + i) * KW + q;
+#pragma unroll
+                        for (int it = 0; it < NT_; ++it) {
+                            const uint32_t off = u < units ? (uint32_t)((t0 / 32 + it) * units + u) * 4096u + (uint32_t)(hw * 1024 + lane * 16) : kPastEnd;
+                            const uint32_t to = base + (uint32_t)((q * UPR + i) * NT_ + it) * 4096u;
+                            if (a.n_t > 0)
+                                load_to_lds<true>(dt, off, 0u, to);
+                            else
+                                load_to_lds(dt, off, 0u, to);
+                        }
+                    }
+            }
+        };
+        const int total = rounds + t_rounds;
+#pragma unroll
+        for (int r = 0; r < XRING - 1; ++r) load_round(r, r);
+        int slot = XRING - 1;
+        for (int r = 0; r < total; ++r) {
+            // round r is here when at most the loads of the XRING - 2 rounds after it are in flight; past the barrier
+            // every wavefront may read it, and the slot of round r - 1 is free
+            asm volatile("s_waitcnt vmcnt(%0)" : : "n"((XRING - 2) * NX) : "memory");
+            __builtin_amdgcn_s_barrier();
+            load_round(r + XRING - 1, slot);
+            slot = slot + 1 == XRING ? 0 : slot + 1;
+        }
+        asm volatile("s_waitcnt vmcnt(0)" : : : "memory");
+        __syncthreads();                 // the loads past the end have landed: LDS is free
+        __syncthreads();
+        return;
+    }
+
+    float16_t acc[RT][NT_];
+#pragma unroll
+    for (int i = 0; i < RT; ++i)
+#pragma unroll
+        for (int it = 0; it < NT_; ++it)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) acc[i][it][e] = 0.f;
+
+    const rsrc_t dl = AQ ? make_rsrc(a.Lq, (uint32_t)q4_code_bytes(a.n, a.rank)) : make_rsrc(a.L, (uint32_t)tl_bytes(a.n, a.rank_pad));
+    const rsrc_t dls = make_rsrc(AQ ? a.Ls : nullptr, AQ ? (uint32_t)q4_scale_bytes(a.n, a.rank) : 0u);
+    // 4-bit L, for a round of the adapter term: codes of both steps, scale
+    uint4_t lreg[UPR][RT];
+    auto load_l = [&](int t_round) {
+#pragma unroll
+        for (int q = 0; q < UPR; ++q) {
+            const int u = (t_round * UPR + q) * KW + kw;
+#pragma unroll
+            for (int i = 0; i < RT; ++i) {
+                {
+                    const uint32_t row = (uint32_t)(o0 + 32 * i + li), u64 = (uint32_t)u / 2u;
+                    const uint2_t c = load8(dl, u < units ? q4_piece(row, u64, q4_ctiles(a.rank)) + 16u * lb + 8u * (u & 1) : kPastEnd, 0);
+                    const half_t sc = load_half(dls, u < units ? (row * q4_groups(a.rank) + u64 / 2u) * 2u : kPastEnd, 0);
+                    lreg[q][i] = uint4_t{c[0], c[1], (uint32_t)__builtin_bit_cast(unsigned short, sc), 0u};
+                }
+            }
+        }
+    };
+    float4_t rscale[RT][4];                      // of the rows 32 i + 8 blk + 4 lb + [0, 4)
+    if (a.stages > 0) {
+        const rsrc_t rs = make_rsrc(a.scale, (uint32_t)a.n * 4u);
+#pragma unroll
+        for (int i = 0; i < RT; ++i)
+#pragma unroll
+            for (int blk = 0; blk < 4; ++blk)
+                rscale[i][blk] = __builtin_bit_cast(float4_t, load16(rs, (uint32_t)(o0 + 32 * i + 8 * blk + 4 * lb) * 4u, 0));
+    }
+    if (AQ && t_rounds > 0) load_l(0);
+    int slot = 0;                                // of the round that is due
+
+    // This wavefront's weights, round after round, then (fp16) its rows of L, unit after unit -> its own part of LDS,
+    // WRING - 1 slots ahead.  Row tiles past the last and units past the last read as zeros; every slot has the same
+    // number of loads, so the count of loads in flight says which slots have arrived.
+    constexpr int NW = 2 * RT;
+    const rsrc_t dq = make_rsrc(a.qvals, (uint32_t)pk_qbytes(a.n, a.k));
+    const rsrc_t dm = make_rsrc(a.meta, (uint32_t)pk_mbytes(a.n, a.k));
+    const uint32_t w_lds = lds0 + (uint32_t)(XRING * G::XSLOT + wave * G::WBYTES);
+    const int rt0 = o0 / 32;
+    auto load_w = [&](int r, int at) {
+        const uint32_t base = w_lds + (uint32_t)(at * G::WSLOT);
+        if (r < rounds) {
+            const int s = min(r * KW + kw, a.stages - 1);         // (nobody uses a stage past the last)
+#pragma unroll
+            for (int i = 0; i < RT; ++i) {
+                load_to_lds(dq, (uint32_t)(rt0 + i) * kt * 1024u + (uint32_t)lane * 16u, (uint32_t)s * 1024u, base + (uint32_t)i * 2048u);
+                if (lane < 32) load_to_lds(dm, (uint32_t)(rt0 + i) * kt * 512u + (uint32_t)lane * 16u, (uint32_t)s * 512u, base + (uint32_t)i * 2048u + 1024u);
+            }
+        } else {
+            const int u = (r - rounds) * KW + kw;
+#pragma unroll
+            for (int i = 0; i < RT; ++i)
+#pragma unroll
+                for (int j = 0; j < 2; ++j)
+                    load_to_lds(dl, !AQ && u < units ? ((uint32_t)(rt0 + i) * (rp / 16) + 2u * u + j) * 1024u + (uint32_t)lane * 16u : kPastEnd, 0u,
+                                base + (uint32_t)(i * 2048 + j * 1024));
+        }
+    };
+#pragma unroll
+    for (int r = 0; r < WRING - 1; ++r) load_w(r, r);
+    int wslot = 0;                               // of the weights that are due
+    if (a.stages > 0) {
+        // B fragments: token li of tile it
+        const int sw_read = XF ? (li >> 1) & 7 : li & 15;
+        const uint32_t rbase = (uint32_t)(kw * STAGE + li * ROWB);
+        const uint32_t rx = (uint32_t)(lb ^ sw_read) * 16u;
+        for (int r = 0; r < rounds; ++r) {
+            // this round's weights are here when at most the WRING - 2 rounds after it are in flight; X is, past the barrier
+            asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" : : "n"((WRING - 2) * NW) : "memory");
+            __builtin_amdgcn_s_barrier();
+            asm volatile("" : : : "memory");
+            load_w(r + WRING - 1, wslot == 0 ? WRING - 1 : wslot - 1);
+            __builtin_amdgcn_sched_barrier(0);
+            if (r * KW + kw < a.stages) {
+                const char *const bp = lds_c + slot * G::XSLOT + rbase;
+                const char *const wp = lds_c + XRING * G::XSLOT + wslot * G::WSLOT + wave * G::WBYTES;
+                uint4_t q[RT];
+                uint2_t mm[RT];
+#pragma unroll
+                for (int i = 0; i < RT; ++i) {
+                    q[i] = *reinterpret_cast<const uint4_t *>(wp + i * 2048 + lane * 16);
+                    mm[i] = *reinterpret_cast<const uint2_t *>(wp + i * 2048 + 1024 + lane * 8);
+                }
+                // the fragments of the next slice are read while the matrix instructions of this one run
+                if constexpr (XF == 0) {
+                    half16_t b[2][NT_];
+                    auto read_b = [&](int t) {
+#pragma unroll
+                        for (int it = 0; it < NT_; ++it) {
+                            const half8_t b1 = *reinterpret_cast<const half8_t *>(bp + (rx ^ (32u * t)) + it * 32 * ROWB);
+                            const half8_t b2 = *reinterpret_cast<const half8_t *>(bp + (rx ^ (32u * t) ^ 128u) + it * 32 * ROWB);
+                            b[t & 1][it] = __builtin_shufflevector(b1, b2, 0, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15);
+                        }
+                    };
+                    read_b(0);
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) {
+                        if (t + 1 < 4) read_b(t + 1);
+                        __builtin_amdgcn_sched_barrier(0);
+                        half8_t av[RT];
+#pragma unroll
+                        for (int i = 0; i < RT; ++i) av[i] = codes_to_half8(q[i][t]);
+#pragma unroll
+                        for (int it = 0; it < NT_; ++it)
+#pragma unroll
+                            for (int i = 0; i < RT; ++i) {
+                                if (t & 1)
+                                    acc[i][it] = __builtin_amdgcn_smfmac_f32_32x32x32_f16(av[i], b[t & 1][it], acc[i][it], (int)mm[i][t >> 1], 0, 1);
+                                else
+                                    acc[i][it] = __builtin_amdgcn_smfmac_f32_32x32x32_f16(av[i], b[t & 1][it], acc[i][it], (int)mm[i][t >> 1], 0, 0);
+                            }
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                } else {
+                    int8v_t b[2][NT_];
+                    auto read_b = [&](int u) {
+#pragma unroll
+                        for (int it = 0; it < NT_; ++it) {
+                            const uint4_t b1 = *reinterpret_cast<const uint4_t *>(bp + (rx ^ (32u * u)) + it * 32 * ROWB);
+                            const uint4_t b2 = *reinterpret_cast<const uint4_t *>(bp + (rx ^ (32u * u) ^ 64u) + it * 32 * ROWB);
+                            b[u][it] = int8v_t{(int)b1[0], (int)b1[1], (int)b1[2], (int)b1[3], (int)b2[0], (int)b2[1], (int)b2[2], (int)b2[3]};
+                        }
+                    };
+                    read_b(0);
+                    read_b(1);
+                    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                    for (int u = 0; u < 2; ++u) {
+                        int4_t av[RT];
+#pragma unroll
+                        for (int i = 0; i < RT; ++i) {
+                            const uint4_t h0 = __builtin_bit_cast(uint4_t, codes_to_half8(q[i][2 * u]));
+                            const uint4_t h1 = __builtin_bit_cast(uint4_t, codes_to_half8(q[i][2 * u + 1]));
+                            av[i] = int4_t{(int)__builtin_amdgcn_perm(h0[1], h0[0], 0x07050301u), (int)__builtin_amdgcn_perm(h0[3], h0[2], 0x07050301u),
+                                           (int)__builtin_amdgcn_perm(h1[1], h1[0], 0x07050301u), (int)__builtin_amdgcn_perm(h1[3], h1[2], 0x07050301u)};
+                        }
+#pragma unroll
+                        for (int it = 0; it < NT_; ++it)
+#pragma unroll
+                            for (int i = 0; i < RT; ++i) {
+                                if (XF == 1)
+                                    acc[i][it] = __builtin_amdgcn_smfmac_f32_32x32x64_bf8_fp8(av[i], b[u][it], acc[i][it], (int)mm[i][u], 0, 0);
+                                else
+                                    acc[i][it] = __builtin_amdgcn_smfmac_f32_32x32x64_bf8_bf8(av[i], b[u][it], acc[i][it], (int)mm[i][u], 0, 0);
+                            }
+                    }
+                }
+            }
+            slot = slot + 1 == XRING ? 0 : slot + 1;
+            wslot = wslot + 1 == WRING ? 0 : wslot + 1;
+        }
+    }
+    if (a.stages > 0) {
+        float xs = 1.0f;
+        if constexpr (XF != 0) xs = *a.x_scale;
+        // element 4 blk + e of a tile is row 8 blk + 4 lb + e
+#pragma unroll
+        for (int i = 0; i < RT; ++i)
+#pragma unroll
+            for (int blk = 0; blk < 4; ++blk)
+#pragma unroll
+                for (int it = 0; it < NT_; ++it)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) acc[i][it][4 * blk + e] *= rscale[i][blk][e] * xs;
+    }
+    if (t_rounds > 0) {
+        const int made = (a.m + 15) / 16 * 16;       // tokens of T that exist; the lanes of the others take anything
+        bool gave_up = false;
+        int spins = 0;
+        for (int tr = 0; tr < t_rounds; ++tr) {
+            // the UPR slots of this round
+            static_assert(WRING >= UPR + 1, "the ring holds a round of L");
+            asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" : : "n"((WRING - 1 - UPR) * NW) : "memory");
+            __builtin_amdgcn_s_barrier();
+            asm volatile("" : : : "memory");
+            const char *const pieces = lds_c + slot * G::XSLOT + kw * UPR * NT_ * 4096 + lane * 16;
+            half8_t av[UPR][2][RT], bv[UPR][2][NT_];
+#pragma unroll
+            for (int q = 0; q < UPR; ++q) {
+                const int u = (tr * UPR + q) * KW + kw;
+                uint4_t pc[2][NT_][2];
+#pragma unroll
+                for (int s = 0; s < 2; ++s)
+#pragma unroll
+                    for (int it = 0; it < NT_; ++it)
+#pragma unroll
+                        for (int j = 0; j < 2; ++j)
+                            pc[s][it][j] = *reinterpret_cast<const uint4_t *>(pieces + (q * NT_ + it) * 4096 + (2 * s + j) * 1024);
+                auto exists = [&](int s, int it) { return u < units && mid_rank<AQ>(u, s, lb) < rp && t0 + 32 * it + li < made; };
+                // a piece that is not this call's (it came through the L2 too early) is read again from memory
+                for (;;) {
+                    bool there = true;
+#pragma unroll
+                    for (int s = 0; s < 2; ++s)
+#pragma unroll
+                        for (int it = 0; it < NT_; ++it)
+#pragma unroll
+                            for (int j = 0; j < 2; ++j) there = there && (!exists(s, it) || piece_valid(pc[s][it][j], epoch));
+                    if (__all(there)) break;
+                    if (++spins >= a.spin_limit) {
+                        gave_up = true;
+                        break;
+                    }
+                    __builtin_amdgcn_s_sleep(4);
+#pragma unroll
+                    for (int s = 0; s < 2; ++s)
+#pragma unroll
+                        for (int it = 0; it < NT_; ++it)
+#pragma unroll
+                            for (int j = 0; j < 2; ++j)
+                                pc[s][it][j] = load_piece(dt, exists(s, it) ? mid_t_piece<AQ>((uint32_t)(t0 + 32 * it + li), mid_rank<AQ>(u, s, lb) + 4u * j, a.rank_pad) : kPastEnd);
+                }
+#pragma unroll
+                for (int s = 0; s < 2; ++s) {
+#pragma unroll
+                    for (int it = 0; it < NT_; ++it) {
+                        uint4_t v = {pc[s][it][0][1], pc[s][it][0][2], pc[s][it][1][1], pc[s][it][1][2]};
+                        if (AQ && mid_rank<AQ>(u, s, lb) >= rp) v = uint4_t{0u, 0u, 0u, 0u};
+                        if (gave_up) v = uint4_t{0x7E007E00u, 0x7E007E00u, 0x7E007E00u, 0x7E007E00u};    // NaN: must not pass for a result
+                        bv[q][s][it] = __builtin_bit_cast(half8_t, v);
+                    }
+#pragma unroll
+                    for (int i = 0; i < RT; ++i) {
+                        if constexpr (AQ)
+                            av[q][s][i] = codes_to_half8(lreg[q][i][s]) * __builtin_bit_cast(half_t, (unsigned short)lreg[q][i][2]);
+                        else
+                            av[q][s][i] = *reinterpret_cast<const half8_t *>(lds_c + XRING * G::XSLOT + wslot * G::WSLOT + wave * G::WBYTES +
+                                                                             i * 2048 + s * 1024 + lane * 16);
+                    }
+                }
+                wslot = wslot + 1 == WRING ? 0 : wslot + 1;
+            }
+            if (AQ) load_l(tr + 1);
+            asm volatile("s_waitcnt lgkmcnt(0)" : : : "memory");       // L has been read
+#pragma unroll
+            for (int q = 0; q < UPR; ++q) {
+                const int ahead = wslot + q + WRING - 1 - UPR;
+                load_w(rounds + tr * UPR + q + WRING - 1, ahead >= WRING ? ahead - WRING : ahead);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int q = 0; q < UPR; ++q)
+                if ((tr * UPR + q) * KW + kw < units) {
+#pragma unroll
+                    for (int s = 0; s < 2; ++s)
+#pragma unroll
+                        for (int i = 0; i < RT; ++i)
+#pragma unroll
+                            for (int it = 0; it < NT_; ++it)
+                                acc[i][it] = __builtin_amdgcn_mfma_f32_32x32x16_f16(av[q][s][i], bv[q][s][it], acc[i][it], 0, 0, 0);
+                }
+            slot = slot + 1 == XRING ? 0 : slot + 1;
+        }
+        if (gave_up && lane == 0) __hip_atomic_store(a.err, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+
+    // the KW partial tiles meet in LDS
+    float4_t *const red = reinterpret_cast<float4_t *>(lds_c);
+    asm volatile("s_waitcnt vmcnt(0)" : : : "memory");     // the loads past the end have landed
+    __syncthreads();                         // and X has been read
+    if (kw > 0) {
+#pragma unroll
+        for (int i = 0; i < RT; ++i)
+#pragma unroll
+            for (int it = 0; it < NT_; ++it)
+#pragma unroll
+                for (int blk = 0; blk < 4; ++blk)
+                    red[((((kw - 1) * RG + rg) * RT + i) * NT_ + it) * 256 + blk * 64 + lane] =
+                        float4_t{acc[i][it][4 * blk], acc[i][it][4 * blk + 1], acc[i][it][4 * blk + 2], acc[i][it][4 * blk + 3]};
+    }
+    __syncthreads();
+    if (kw > 0) return;
+    // store: lane holds token t0 + 32 it + li, rows 8 blk + 4 lb .. + 3 of tile i
+    const bool vec_ok = (a.n & 3) == 0;
+#pragma unroll
+    for (int it = 0; it < NT_; ++it) {
+        const int t = t0 + 32 * it + li;
+#pragma unroll
+        for (int i = 0; i < RT; ++i)
+#pragma unroll
+            for (int blk = 0; blk < 4; ++blk) {
+                float4_t v = {acc[i][it][4 * blk], acc[i][it][4 * blk + 1], acc[i][it][4 * blk + 2], acc[i][it][4 * blk + 3]};
+#pragma unroll
+                for (int w = 0; w < KW - 1; ++w) v += red[(((w * RG + rg) * RT + i) * NT_ + it) * 256 + blk * 64 + lane];
+                const int o = o0 + 32 * i + 8 * blk + 4 * lb;
+                if (t >= a.m || o >= a.n) continue;
+                half_t *y = a.Y + (size_t)t * a.n + o;
+                if (vec_ok) {
+                    if (a.accumulate) {
+                        const half4_t old = *reinterpret_cast<const half4_t *>(y);
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) v[e] += (float)old[e];
+                    }
+                    *reinterpret_cast<half4_t *>(y) = half4_t{(half_t)v[0], (half_t)v[1], (half_t)v[2], (half_t)v[3]};
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        if (o + e < a.n) y[e] = (half_t)(a.accumulate ? v[e] + (float)y[e] : v[e]);
+                }
+            }
+    }
+}
+
+template <int NT_, int RT, int RG, int KW, int XF, bool AQ>
+static int launch_mid(MidArgs a, bool wait_test, hipStream_t st)
+{
+    constexpr size_t lds = MidLds<NT_, RT, RG, KW, XF>::BYTES, lds_t = MidLds<NT_, RT, RG, KW, XF>::TROLE;
+    a.tiles_o = (a.n + 32 * RT * RG - 1) / (32 * RT * RG);
+    const int n_y = die_tiles(a.tiles_o, (a.m + 32 * NT_ - 1) / (32 * NT_));
+    a.t_tiles = die_tiles(a.rank_pad / 16, (a.m + 15) / 16);
+    // what the Y role leaves free of the workgroups that are resident at once is for the T role
+    const int spare = (device_info().cus - n_y) / kDies * kDies;
+    int n_t = a.t_tiles < spare ? a.t_tiles : (spare > 0 ? spare : 0);
+    const bool one_launch = n_t > 0 && (a.t_tiles + n_t - 1) / n_t <= 4;
+    if (wait_test) {
+        n_t = 0;                             // nobody makes T
+    } else if (a.t_tiles > 0 && !one_launch) {
+        MidArgs t = a;
+        t.n_t = a.t_tiles;
+        hipLaunchKernelGGL((mid_kernel<NT_, RT, RG, KW, XF, AQ>), dim3((unsigned)a.t_tiles), dim3(kMidThreads), lds_t, st, t);
+        n_t = 0;
+    }
+    a.n_t = n_t;
+    hipLaunchKernelGGL((mid_kernel<NT_, RT, RG, KW, XF, AQ>), dim3((unsigned)(n_t + n_y)), dim3(kMidThreads), lds, st, a);
+    return hip_status(hipGetLastError());
+}
+
+// The geometries, by growing tile: rows x tokens.
+constexpr int kMidTiles[4][2] = {{32, 32}, {64, 32}, {128, 32}, {128, 64}};
+
+// Which geometry, by the sizes alone (index into kMidTiles), or -1: the tiles of slim_gemm_sparse.hip.
+// The smallest tile that gives every compute unit at most one workgroup: a second workgroup on a unit doubles
+// the time of a call that is a chain of latencies, a smaller tile shortens the chain (4096 x 4096, r = 409, 64
+// tokens: 14.6 / 10.4 / 13.7 / 20.5 us with 256 / 128 / 64 / 32 workgroups' worth of tiles in that order, the 512 x 128
+// tiles 39.6).  Two workgroups per unit still pay on short rows, where the other path is all launches
+// (11008 x 2048 at 256 tokens 28.9 against 32.4 us; 28672 x 4096 at 128 tokens 50.3 against 47.1).
+// Above 512 tokens the workspace has no room for the pieces of T.
+static int mid_geometry(int n, int k, int m, int cus)
+{
+    if (m > 512) return -1;
+    auto workgroups = [&](int g) {
+        return die_tiles((n + kMidTiles[g][0] - 1) / kMidTiles[g][0], (m + kMidTiles[g][1] - 1) / kMidTiles[g][1]);
+    };
+    for (int g = 0; g < 4; ++g)
+        if (workgroups(g) <= cus) return g;
+    return k <= 2048 && workgroups(3) <= 2 * cus ? 3 : -1;
+}
+
+template <int XF, bool AQ>
+static int launch_mid_call(const MidArgs &a, int geometry, bool wait_test, hipStream_t st)
+{
+    switch (geometry) {
+        case 0: return launch_mid<1, 1, 1, 8, XF, AQ>(a, wait_test, st);
+        case 1: return launch_mid<1, 1, 2, 4, XF, AQ>(a, wait_test, st);
+        case 2: return launch_mid<1, 2, 2, 4, XF, AQ>(a, wait_test, st);
+        default: return launch_mid<2, 1, 4, 2, XF, AQ>(a, wait_test, st);
+    }
+}
+
+// The whole call (T and Y) if the sizes are this path's: *taken says so.  weight_term false: the adapter term alone
+// (slim_lowrank).  T: t_room bytes of the workspace, ctrl: its control words.
+int launch_gemm_mid(const slim_layer *layer, const half_t *X, int xf, const float *x_scale, int m, half_t *Y, void *T, size_t t_room,
+                    unsigned *ctrl, bool weight_term, int accumulate, hipStream_t st, bool *taken)
+{
+    *taken = false;
+    const slim_shape s = layer->shape;
+    const bool q4 = layer->adapter_bits == 4 && s.rank > 0;
+    const int geometry = mid_geometry(s.n, s.k, m, device_info().cus);
+    if (geometry < 0) return SLIM_OK;
+    // 32-bit offsets, tiles past the end included; room for the pieces of T
+    constexpr uint64_t kLimit = 0x80000000ull;
+    const uint64_t t_bytes = q4 ? mid_t_bytes<true>(m, layer->rank_pad) : mid_t_bytes<false>(m, layer->rank_pad);
+    if ((uint64_t)(m + 64) * s.k * 2 >= kLimit || (uint64_t)pk_qbytes(s.n + 128, s.k) >= kLimit ||
+        (uint64_t)tl_bytes(s.n + 128, layer->rank_pad) >= kLimit || (uint64_t)tl_bytes(layer->rank_pad, s.k) >= kLimit || t_bytes > t_room)
+        return SLIM_OK;
+    *taken = true;
+    MidArgs a{};
+    a.qvals = layer->qvals;
+    a.meta = layer->meta;
+    a.scale = layer->scale;
+    a.X = X;
+    a.x_scale = x_scale;
+    a.R = reinterpret_cast<const half_t *>(layer->R);
+    a.L = reinterpret_cast<const half_t *>(layer->L);
+    a.Rq = layer->Rq;
+    a.Lq = layer->Lq;
+    a.Rs = reinterpret_cast<const half_t *>(layer->Rs);
+    a.Ls = reinterpret_cast<const half_t *>(layer->Ls);
+    a.T = static_cast<uint4_t *>(T);
+    a.err = ctrl + 2;                        // read by slim_workspace_check
+    const bool wait_test = decode_path_override() == 3 && layer->rank_pad > 0;
+    if (layer->rank_pad > 0) a.epoch = next_call_epoch(ctrl + 3, st);
+    a.spin_limit = wait_test ? 256 : 1 << 16;
+    a.Y = Y;
+    a.n = s.n;
+    a.k = s.k;
+    a.rank = s.rank;
+    a.rank_pad = layer->rank_pad;
+    a.m = m;
+    a.stages = weight_term ? s.k / 128 : 0;
+    a.accumulate = accumulate;
+    if (q4) {
+        if (xf == 0) return launch_mid_call<0, true>(a, geometry, wait_test, st);
+        return xf == 1 ? launch_mid_call<1, true>(a, geometry, wait_test, st) : launch_mid_call<2, true>(a, geometry, wait_test, st);
+    }
+    if (xf == 0) return launch_mid_call<0, false>(a, geometry, wait_test, st);
+    return xf == 1 ? launch_mid_call<1, false>(a, geometry, wait_test, st) : launch_mid_call<2, false>(a, geometry, wait_test, st);
+}
+
+}  // namespace slim

@@ -50,7 +50,6 @@
 namespace slim {
 
 constexpr int kFusedMaxThreads = 1024;     // 8 working wavefronts + up to 8 helpers
-constexpr int kScopeDevice = 16;      // cache policy of a buffer access: device scope (written through / read from memory)
 constexpr int kMaxShares = 4;         // R role: at most this many shares of the inputs (planes of T)
 constexpr int kFusedWavesPerSimd = 4;   // the kernel is compiled for 128 registers: 16 wavefronts per compute unit
 constexpr int kSpinLimit = 1 << 16;
@@ -72,8 +71,7 @@ struct FusedArgs {
     half_t *Y;
     uint4_t *T;          // pieces {epoch, 4 ranks fp16, checksum} [kh][16][rank_pad / 4]: T is the sum of the planes
     unsigned *err;       // set to 1 when a wait gave up
-    unsigned epoch;      // this call's number (top bit clear, never 0), or
-    const unsigned *epoch_ptr;   // under stream capture: where a small kernel ahead of this one has put it (top bit set)
+    CallEpoch epoch;
     int n, k, rank_pad, m;
     int rank;            // true rank (rows of R, columns of L that exist in the 4-bit buffers)
     int kpad;            // k rounded up to 1024
@@ -89,30 +87,6 @@ struct FusedArgs {
                          // + 8 (test of the bounded wait): the helpers give up after kSpinLimitShort polls
 };
 
-// The number that tags this call's pieces of T.  A launch argument normally; a launch that is
-// being captured into a graph would replay with the same number and take the pieces of the
-// previous replay for its own, so there the number lives in the workspace and a one-thread
-// kernel ahead of this one advances it on every replay.  The top bit keeps the two kinds apart.
-__device__ __forceinline__ unsigned call_epoch(const FusedArgs &a)
-{
-    return a.epoch_ptr ? (__builtin_nontemporal_load(a.epoch_ptr) | 0x80000000u) : a.epoch;
-}
-
-__global__ void decode_epoch_bump_kernel(unsigned *ctr)
-{
-    const unsigned v = (*ctr + 1u) & 0x7FFFFFFFu;
-    *ctr = v ? v : 1u;
-}
-
-// A piece of T: {epoch, two dwords of four fp16 ranks, epoch ^ dword ^ dword}.  The reader accepts it only if
-// the first dword is this call's epoch and the last one is the checksum of the three before it, so a piece
-// whose dwords come from two different stores (should a 128-bit store ever become visible in parts) is
-// taken for "not there yet" and read again, unless the old and the new data have the same checksum --
-// which they do when they are the same data.  Only single dwords need to be atomic for that.
-__device__ __forceinline__ bool piece_valid(const uint4_t &pc, unsigned epoch)
-{
-    return pc[0] == epoch && pc[3] == (pc[0] ^ pc[1] ^ pc[2]);
-}
 constexpr unsigned short kHalfNaNBits = 0x7E00;
 #define kHalfNaN __builtin_bit_cast(half_t, kHalfNaNBits)
 
@@ -246,10 +220,7 @@ __device__ __forceinline__ void role_r(const FusedArgs &a, half_t *lds_h, int rb
         // one 16-byte store per lane, through to memory: the piece with its epoch
         const rsrc_t t_rs = make_rsrc(a.T, (uint32_t)a.kh * kMaxTokens * (rp / 4) * 16u);
         const uint32_t off = (((uint32_t)kh * kMaxTokens + lx) * (rp / 4) + 4 * rt + ly) * 16u;
-        typedef unsigned int store4_t __attribute__((__vector_size__(16)));
-        const unsigned ep = call_epoch(a);
-        const store4_t piece = {ep, hb[0], hb[1], ep ^ hb[0] ^ hb[1]};
-        __builtin_amdgcn_raw_buffer_store_b128(piece, t_rs, (int)off, 0, kScopeDevice);
+        store_piece(t_rs, off, call_epoch(a.epoch), hb);
     }
 }
 
@@ -448,7 +419,7 @@ __device__ __forceinline__ void role_y(const FusedArgs &a, half_t *lds, int yb, 
         int spins = 0;
         bool gave_up = false;
         const int spin_limit = (a.mode & 8) ? kSpinLimitShort : kSpinLimit;
-        const unsigned epoch = call_epoch(a);
+        const unsigned epoch = call_epoch(a.epoch);
         auto piece_off = [&](int pair, int share) {
             const int row = pair / qpr, q = pair - row * qpr;
             return pair < pairs ? (((uint32_t)share * kMaxTokens + row) * qpr + q) * 16u : kNowhere;
@@ -464,8 +435,7 @@ __device__ __forceinline__ void role_y(const FusedArgs &a, half_t *lds, int yb, 
                     for (int i = 0; i < PB; ++i)
 #pragma unroll
                         for (int h = 0; h < KH; ++h)
-                            pc[i * KH + h] = __builtin_bit_cast(
-                                uint4_t, __builtin_amdgcn_raw_buffer_load_b128(t_rs, (int)piece_off(p0 + i * hn, h), 0, kScopeDevice));
+                            pc[i * KH + h] = load_piece(t_rs, piece_off(p0 + i * hn, h));
                     all_there = true;
 #pragma unroll
                     for (int i = 0; i < PB; ++i)
@@ -785,7 +755,25 @@ FusedPlan plan_fused(int n, int k, int rank_pad, int m)
     return p;
 }
 
+__global__ void decode_epoch_bump_kernel(unsigned *ctr)
+{
+    const unsigned v = (*ctr + 1u) & 0x7FFFFFFFu;
+    *ctr = v ? v : 1u;
+}
+
 static std::atomic<unsigned> g_epoch{0};
+
+CallEpoch next_call_epoch(unsigned *ctr, hipStream_t st)
+{
+    unsigned e = ++g_epoch & 0x7FFFFFFFu;
+    if (e == 0) e = ++g_epoch & 0x7FFFFFFFu;      // a zero-filled workspace must not look valid: epoch 0 is never used
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &cap) == hipSuccess && cap == hipStreamCaptureStatusActive) {
+        hipLaunchKernelGGL(decode_epoch_bump_kernel, dim3(1), dim3(1), 0, st, ctr);
+        return CallEpoch{e, ctr};
+    }
+    return CallEpoch{e, nullptr};
+}
 
 // mode: 2 = one launch, 1 = the two roles as two launches.  lowrank: 0 = the layer; 1, 2 = the
 // low-rank term alone on the layer's fp16 adapters (its packed buffers are not read), 2 adds to Y.
@@ -806,15 +794,7 @@ int launch_decode_fused(const slim_layer *layer, const half_t *X, int m, half_t 
     a.Y = Y;
     a.T = static_cast<uint4_t *>(T);
     a.err = err;
-    unsigned e = ++g_epoch & 0x7FFFFFFFu;
-    if (e == 0) e = ++g_epoch & 0x7FFFFFFFu;      // a zero-filled workspace must not look valid: epoch 0 is never used
-    a.epoch = e;
-    a.epoch_ptr = nullptr;
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(st, &cap) == hipSuccess && cap == hipStreamCaptureStatusActive) {
-        hipLaunchKernelGGL(decode_epoch_bump_kernel, dim3(1), dim3(1), 0, st, epoch_ctr);
-        a.epoch_ptr = epoch_ctr;
-    }
+    a.epoch = next_call_epoch(epoch_ctr, st);
     a.n = layer->shape.n;
     a.k = layer->shape.k;
     a.rank_pad = layer->rank_pad;

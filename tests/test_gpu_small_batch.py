@@ -1,0 +1,131 @@
+"""slim_linear_gemm, slim_linear_gemm_fp8 and slim_lowrank on batches of 17 to 512 tokens (mid_kernel,
+csrc/slim_gemm_mid.hip) against the oracle, at the sizes where that path can go wrong: each of its four tile
+shapes with whole, ragged and partly empty tiles, T made in the same launch and in one of its own, one stage of
+inputs, stage counts that are no multiple of a round, ranks below and beyond whole rounds of the adapter term.
+The bounds are those of parity.py."""
+import pytest
+import torch
+
+from oracle import slim_oracle as O
+from paper_2410_09615_amd import binding as B
+from paper_2410_09615_amd import workloads as wl
+from parity import TOL_Y
+from test_gpu_parity import (CT_PREFILL, DEV, _assert_layer_close, _assert_lowrank_close, _forward_case, _fp8_forward_case,
+                             _gpu_layer, _shape)
+
+pytestmark = pytest.mark.gpu
+
+# tile rows x tokens: 32 x 32, 64 x 32, 128 x 32, 128 x 64 (the smallest that leaves every compute unit at most one)
+CASES = [
+    (512, 512, 51, 17), (33, 128, 1, 31), (32, 384, 31, 32), (1001, 640, 33, 70), (130, 2176, 97, 129), (700, 4096, 409, 33),
+    (4096, 256, 64, 64), (5000, 1408, 96, 40), (2049, 640, 200, 96), (1500, 1152, 150, 200),
+    (9001, 384, 65, 48), (11008, 640, 34, 33), (3000, 1280, 300, 160),
+    (28000, 256, 90, 40), (20003, 384, 130, 64), (4096, 512, 51, 512), (2050, 1152, 1100, 500),
+    (28672, 256, 60, 100), (700, 2048, 0, 40), (9001, 256, 0, 200),
+]
+
+
+@pytest.mark.parametrize("n,k,r,m", CASES)
+def test_small_batch(n, k, r, m):
+    assert _forward_case(_shape(n, k, r), m, B.slim_linear_gemm, seed=21) <= TOL_Y
+
+
+@pytest.mark.parametrize("n,k,r,m", [c for c in CASES if c[2] > 0])
+def test_small_batch_q4_adapters(n, k, r, m):
+    assert _forward_case(_shape(n, k, r), m, B.slim_linear_gemm, seed=22, bits=4) <= TOL_Y
+
+
+@pytest.mark.parametrize("bits", [16, 4])
+@pytest.mark.parametrize("gain", [1.0, 300.0])
+@pytest.mark.parametrize("n,k,r,m", [CASES[i] for i in (1, 3, 5, 7, 9, 10, 12, 13, 16, 17)])
+def test_small_batch_8_bit_inputs(n, k, r, m, gain, bits):
+    err, fmt = _fp8_forward_case(n, k, r, m, seed=23, x_gain=gain, bits=bits)
+    assert err <= TOL_Y and fmt == (1 if gain > 1 else 0)
+
+
+# (no rank of one here: its outputs reach below 2^-14, where rounding to fp16 errs by up to 2^-25 absolute, which the
+# element bound, relative to the value, does not cover)
+@pytest.mark.parametrize("accumulate", [False, True])
+@pytest.mark.parametrize("n,k,r,m", [(33, 128, 33, 17), (1001, 640, 33, 70), (5000, 1408, 96, 40), (9001, 384, 65, 48),
+                                     (20003, 384, 130, 64), (28672, 256, 60, 100)])
+def test_small_batch_adapter_term_alone(n, k, r, m, accumulate):
+    L, R = wl.make_adapters(n, k, r, 31, 32)
+    X = wl.make_activations(m, k, True, 33, 34)
+    Lp, Rp = B.slim_pack_adapters(L.to(DEV), R.to(DEV))
+    Y0 = Y0h = None
+    if accumulate:
+        Y0h = (torch.randn(m, n, generator=torch.Generator().manual_seed(9)) * 0.1).to(torch.float16)
+        Y0 = Y0h.to(DEV)
+    Y = B.slim_lowrank(X.to(DEV), Rp, Lp, n, r, Y=Y0, accumulate=accumulate)
+    torch.cuda.synchronize()
+    _assert_lowrank_close(Y, X, R, L, Y0=None if Y0h is None else Y0h.numpy())
+
+
+@pytest.mark.parametrize("bits", [16, 4])
+def test_tokens_do_not_leak_into_each_other(bits):
+    """Tokens that overflow share tiles, pieces of T and LDS rows with others, which still match the oracle."""
+    n, k, r, m = 384, 640, 90, 70
+    W, L, R, X = wl.make_layer(_shape(n, k, r), m, seed=24)
+    layer = B.compress(W.to(DEV), L.to(DEV), R.to(DEV), adapter_bits=bits)
+    if bits == 4:
+        L = torch.from_numpy(O.dequantize_adapter(*O.quantize_adapter(L.numpy())))
+        R = torch.from_numpy(O.dequantize_adapter(*O.quantize_adapter(R.numpy())))
+    bad = [0, 31, 32, 69]
+    good = [t for t in range(m) if t not in bad]
+    Xg = X.clone()
+    Xg[bad] = float("inf")
+    Y = B.slim_linear_gemm(layer, Xg.to(DEV))
+    torch.cuda.synchronize()
+    _assert_layer_close(Y[good], O.compress(W.numpy()), L.numpy(), R.numpy(), X[good], CT_PREFILL + (2 if bits == 4 else 0),
+                        "tokens beside infinite ones")
+
+
+def test_one_workspace_for_every_batch_and_path(decode_override):
+    """One workspace, sized for the largest call; batches of all paths in turn (decode, the tile shapes, the large
+    tiles), layers of two ranks: no piece of T of an earlier call may pass for this call's."""
+    shapes = [_shape(1000, 1152, 70), _shape(5000, 640, 33)]
+    data = [wl.make_layer(s, 600, seed=25 + i) for i, s in enumerate(shapes)]
+    layers = [_gpu_layer(W, L, R) for W, L, R, _ in data]
+    refs = [O.compress(W.numpy()) for W, _, _, _ in data]
+    ws = torch.zeros(max(B.slim_workspace_bytes(x, 600) for x in layers), dtype=torch.uint8, device=DEV)
+    for i, m in enumerate([64, 600, 64, 17, 300, 40, 600, 33, 512, 64, 64]):
+        for (W, L, R, X), layer, ref in zip(data, layers, refs):
+            Y = B.slim_linear_gemm(layer, X[:m].to(DEV), workspace=ws)
+            torch.cuda.synchronize()
+            _assert_layer_close(Y, ref, L.numpy(), R.numpy(), X[:m], CT_PREFILL, f"call {i} m={m}")
+    B.slim_workspace_check(ws)
+
+
+@pytest.mark.parametrize("bits", [16, 4])
+def test_a_wait_that_gives_up_is_loud(bits, decode_override):
+    """The bounded wait for T, forced from the host to run out (no workgroup makes T, 256 polls; every wavefront
+    ends normally): Y is NaN, slim_workspace_check reports it, and the next call on the workspace is correct."""
+    shape = _shape(640, 1024, 51)
+    W, L, R, X = wl.make_layer(shape, 48, seed=26)
+    layer = B.compress(W.to(DEV), L.to(DEV), R.to(DEV), adapter_bits=bits)
+    ws = B.alloc_workspace(layer, 48)
+    decode_override("wait_test")
+    Y = B.slim_linear_gemm(layer, X.to(DEV), workspace=ws)
+    torch.cuda.synchronize()
+    assert bool(torch.isnan(Y).all())
+    with pytest.raises(B.SlimError) as e:
+        B.slim_workspace_check(ws)
+    assert e.value.status == B.SLIM_ERR_WAIT
+    decode_override("auto")
+    Y = B.slim_linear_gemm(layer, X.to(DEV), workspace=ws)
+    Y2 = B.slim_linear_gemm(layer, X.to(DEV), workspace=B.alloc_workspace(layer, 48))
+    torch.cuda.synchronize()
+    assert torch.equal(Y, Y2) and bool(torch.isfinite(Y).all())
+    B.slim_workspace_check(ws)
+
+
+@pytest.mark.parametrize("stages", [1, 2, 3, 4, 5, 6, 7])
+@pytest.mark.parametrize("fp8", [False, True])
+def test_large_tiles_every_stage_count_modulo_six(stages, fp8):
+    """The main loops of the 512 x 128 tiles (above 512 tokens) are written out for six stages."""
+    n, k, r, m = 200, 128 * stages, 20, 530
+    if fp8:
+        err, _ = _fp8_forward_case(n, k, r, m, seed=stages)
+    else:
+        err = _forward_case(_shape(n, k, r), m, B.slim_linear_gemm, seed=stages)
+    assert err <= TOL_Y
