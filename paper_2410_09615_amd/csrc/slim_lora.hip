@@ -8,9 +8,7 @@
 // seeded random block of r columns.  The product Q Q^T S converges to the best rank-r
 // approximation of S (Eckart-Young); how far it is from it after `iters` rounds shows in the
 // captured energy ||Q^T S||_F^2 the call reports.  Everything is dense fp32 work on the matrix
-// cores (V_MFMA_F32_32X32X2_F32), all GEMM shapes through one kernel; orthonormalisation is
-// Cholesky QR in blocks of 64 columns (Gram matrix, then per block a small factor-and-invert
-// kernel and GEMMs for the panel, the trailing update and the application to the block).
+// cores; orthonormalisation is Cholesky QR (slim_lora_orth.hip).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -290,121 +288,10 @@ __global__ void lora_init_kernel(float *Z, int rows, int l, int r, uint32_t seed
     }
 }
 
-// ---- Cholesky QR in blocks of 64 columns ----
-// G = Lc Lc^T is factored block column by block column: the 64 x 64 diagonal block and its
-// inverse in one small workgroup (below), the panel under it and the trailing update as
-// GEMMs.  A pivot below 1e-9 of the largest diagonal entry of G marks a column that lies in
-// the span of the ones before it (or a padding column of zeros): it gets pivot 1 and a zero
-// column, so the orthonormalised block carries a (numerically) zero column there.
 constexpr int kMaxBlock = 1024;          // columns of the iteration block (rank_pad)
-constexpr int kCb = 64;                  // block width of the factorisation
 
-__global__ __launch_bounds__(1024) void lora_diagmax_kernel(const float *G, int l, float *out)
-{
-    __shared__ float red[16];
-    float mx = 0.f;
-    for (int i = threadIdx.x; i < l; i += blockDim.x) mx = fmaxf(mx, G[(size_t)i * l + i]);
-    mx = wave_max(mx);
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = mx;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        for (int w = 1; w < (int)blockDim.x / 64; ++w) mx = fmaxf(mx, red[w]);
-        *out = mx;
-    }
-}
-
-// Diagonal block at (j0, j0), width w <= 64: L11 replaces its lower triangle in G, and
-// X11 = L11^-1 (lower triangular, zeros above) goes to D[j0 .. j0 + w)[0 .. 64).
-// Column c of the factor and row c of the inverse are final after step c: the forward
-// substitution L X = I runs along with the factorisation (x starts as the identity).
-// The block lives in registers: 256 threads as a 16 x 16 grid, thread (ty, tx) owns the
-// elements (ty + 16 p, tx + 16 q) of a and of x.  A step needs column c of a and row c of x:
-// their owners publish them in LDS (two buffers in turn, one barrier per step), everybody
-// reads the four values of its rows and of its columns, and the update is 32 predicated
-// multiply-adds on registers.  Scaled column c and row c are final then and go to LDS
-// for the write-out at the end.
-__global__ __launch_bounds__(256) void lora_chol_diag_kernel(float *G, int l, int j0, int w, const float *gmax, float *D)
-{
-    __shared__ float col[2][kCb];        // column c of a, as it stands at step c (unscaled)
-    __shared__ float xrow[2][kCb];       // row c of x (unscaled)
-    __shared__ float lout[kCb][kCb + 1];
-    __shared__ float xout[kCb][kCb + 1];
-    const int tid = threadIdx.x, ty = tid >> 4, tx = tid & 15;
-    float av[4][4], xv[4][4];
-#pragma unroll
-    for (int p = 0; p < 4; ++p)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int i = ty + 16 * p, cc = tx + 16 * q;
-            av[p][q] = (i < w && cc < w) ? G[(size_t)(j0 + i) * l + j0 + cc] : 0.f;
-            xv[p][q] = i == cc ? 1.0f : 0.f;
-        }
-    for (int idx = tid; idx < kCb * kCb; idx += 256) {
-        lout[idx / kCb][idx % kCb] = 0.f;
-        xout[idx / kCb][idx % kCb] = 0.f;
-    }
-    const float floor_ = *gmax * 1e-9f;
-    for (int c = 0; c < w; ++c) {
-        const int b = c & 1, cq = c >> 4, cr = c & 15;
-        // publish: column c of a from the threads with tx == c mod 16, row c of x from those with ty == c mod 16
-        if (tx == cr) {
-#pragma unroll
-            for (int q = 0; q < 4; ++q)
-                if (q == cq) {
-#pragma unroll
-                    for (int p = 0; p < 4; ++p) col[b][ty + 16 * p] = av[p][q];
-                }
-        }
-        if (ty == cr) {
-#pragma unroll
-            for (int p = 0; p < 4; ++p)
-                if (p == cq) {
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) xrow[b][tx + 16 * q] = xv[p][q];
-                }
-        }
-        __syncthreads();
-        const float d = col[b][c];
-        const float pv = d > floor_ ? sqrtf(d) : 0.f;        // 0: a column in the span of the ones before it
-        const float inv = pv > 0.f ? 1.0f / pv : 0.f;
-        const float dinv = pv > 0.f ? 1.0f / pv : 1.0f;
-        float li[4], lc[4], xr[4];
-#pragma unroll
-        for (int p = 0; p < 4; ++p) li[p] = col[b][ty + 16 * p] * inv;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            lc[q] = col[b][tx + 16 * q] * inv;
-            xr[q] = xrow[b][tx + 16 * q] * dinv;
-        }
-#pragma unroll
-        for (int p = 0; p < 4; ++p)
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int i = ty + 16 * p, cc = tx + 16 * q;
-                if (i > c && cc > c && cc <= i) av[p][q] -= li[p] * lc[q];
-                if (i > c && cc <= c) xv[p][q] -= li[p] * xr[q];
-            }
-        // what is final now: column c of the factor (threads 0..63), row c of the inverse (64..127)
-        if (tid < kCb) {
-            if (tid > c)
-                lout[tid][c] = col[b][tid] * inv;
-            else if (tid == c)
-                lout[tid][c] = pv > 0.f ? pv : 1.0f;
-        } else if (tid < 2 * kCb) {
-            const int cc = tid - kCb;
-            if (cc <= c) xout[c][cc] = xrow[b][cc] * dinv;
-        }
-    }
-    __syncthreads();
-    for (int idx = tid; idx < w * w; idx += 256) {
-        const int i = idx / w, c = idx % w;
-        if (c <= i) G[(size_t)(j0 + i) * l + j0 + c] = lout[i][c];
-    }
-    for (int idx = tid; idx < w * kCb; idx += 256) {
-        const int i = idx / kCb, c = idx % kCb;
-        D[(size_t)(j0 + i) * kCb + c] = c < w ? xout[i][c] : 0.f;
-    }
-}
+size_t orth_floats(int l);                                                                           // slim_lora_orth.hip
+int launch_orth(const float *in, float *out, int rows, int l, float *ws, hipStream_t st);
 
 // ---- results: L fp16 [n][r] = Q[:, :r];  R fp16 [r][k] = R~[:r] / x;  sq[1] += ||R~[:r]||_F^2 ----
 __global__ void lora_out_l_kernel(const float *Q, int n, int l, int r, half_t *L)
@@ -449,7 +336,7 @@ __global__ void lora_report_kernel(const float *sq, float *diag)
 
 struct LoraPlan {
     int l;                      // columns of the iteration block: rank padded as the layer's adapters are
-    size_t x, S, Q, Y, Z, G, B, Rt, sq, total;      // byte offsets (B: the inverses of the diagonal blocks, [l][64])
+    size_t x, S, Q, Y, Z, G, O, Rt, sq, total;      // byte offsets (O: the orthonormalisation's own)
 };
 
 static size_t up256(size_t v) { return (v + 255) / 256 * 256; }
@@ -471,7 +358,7 @@ static LoraPlan plan_lora(int n, int k, int rank)
     p.Y = take(big * l);
     p.Z = take((size_t)k * l);
     p.G = take(l * l);
-    p.B = take(l * kCb);
+    p.O = take(orth_floats(p.l));
     p.Rt = take(l * k);
     p.sq = take(64);
     p.total = off;
@@ -510,7 +397,7 @@ extern "C" int slim_compute_adapters(const float *W, const uint8_t *qvals, const
     float *x = reinterpret_cast<float *>(ws + p.x), *S = reinterpret_cast<float *>(ws + p.S);
     float *Q = reinterpret_cast<float *>(ws + p.Q), *Y = reinterpret_cast<float *>(ws + p.Y);
     float *Z = reinterpret_cast<float *>(ws + p.Z), *G = reinterpret_cast<float *>(ws + p.G);
-    float *B = reinterpret_cast<float *>(ws + p.B), *Rt = reinterpret_cast<float *>(ws + p.Rt);
+    float *O = reinterpret_cast<float *>(ws + p.O), *Rt = reinterpret_cast<float *>(ws + p.Rt);
     float *sq = reinterpret_cast<float *>(ws + p.sq);
     const int l = p.l;
     const int q = iters == 0 ? 16 : iters;
@@ -532,31 +419,8 @@ extern "C" int slim_compute_adapters(const float *W, const uint8_t *qvals, const
     hipLaunchKernelGGL(lora_init_kernel, grid_for((size_t)k * l), dim3(256), 0, st, Z, k, l, r, seed);
     SLIM_TRY(launched());
 
-    // out = orth(in) for a block [rows][l] (in is overwritten): G = in^T in = Lc Lc^T, out = in Lc^-T
-    auto orth = [&](float *in, float *out, int rows) -> int {
-        int e = sgemm(true, false, in, l, in, l, G, l, l, l, rows, st);
-        if (e != SLIM_OK) return e;
-        hipLaunchKernelGGL(lora_diagmax_kernel, dim3(1), dim3(1024), 0, st, (const float *)G, l, sq + 4);
-        if ((e = launched()) != SLIM_OK) return e;
-        for (int j0 = 0; j0 < l; j0 += kCb) {
-            const int w = std::min(kCb, l - j0), below = l - j0 - w;
-            hipLaunchKernelGGL(lora_chol_diag_kernel, dim3(1), dim3(256), 0, st, G, l, j0, w, (const float *)(sq + 4), B);
-            if ((e = launched()) != SLIM_OK) return e;
-            float *panel = G + (size_t)(j0 + w) * l + j0;
-            // panel under the block: L21 = A21 L11^-T (in place: a workgroup has read its rows before it writes them)
-            if ((e = sgemm(false, true, panel, l, B + (size_t)j0 * kCb, kCb, panel, l, below, w, w, st)) != SLIM_OK) return e;
-            // what is left: A22 -= L21 L21^T
-            if ((e = sgemm(false, true, panel, l, panel, l, G + (size_t)(j0 + w) * l + j0 + w, l, below, below, w, st, -1.0f, 1)) != SLIM_OK)
-                return e;
-        }
-        // out = in Lc^-T by block columns: out_j = (in_j - out_{<j} Lc[j, <j]^T) X_jj^T
-        for (int j0 = 0; j0 < l; j0 += kCb) {
-            const int w = std::min(kCb, l - j0);
-            if ((e = sgemm(false, true, out, l, G + (size_t)j0 * l, l, in + j0, l, rows, w, j0, st, -1.0f, 1)) != SLIM_OK) return e;
-            if ((e = sgemm(false, true, in + j0, l, B + (size_t)j0 * kCb, kCb, out + j0, l, rows, w, w, st)) != SLIM_OK) return e;
-        }
-        return SLIM_OK;
-    };
+    // out = orth(in) for a block [rows][l]
+    auto orth = [&](const float *in, float *out, int rows) { return launch_orth(in, out, rows, l, O, st); };
 
     SLIM_TRY(sgemm(false, false, S, k, Z, l, Y, l, n, l, k, st));          // Y = S Z           [n][l]
     SLIM_TRY(orth(Y, Q, n));

@@ -1,0 +1,431 @@
+// out = orth(in) for a block in [rows][l] of fp32 columns, l <= 1024: Cholesky QR, the orthonormalisation of the
+// subspace iteration in slim_lora.hip.
+//
+//   G = in^T in = Lc Lc^T,  out = in Lc^-T     (columns in order: in = out Lc^T with a positive diagonal)
+//
+// The call is a chain (products, 64-column steps of the factorisation, products), so what bounds it is the
+// number of launches (4 us each) and the latency of the 64 x 64 diagonal blocks, not arithmetic:
+//   lora_gram_kernel    lower tiles of G, the rows divided among the workgroups, partial tiles to memory;
+//   lora_chol_kernel    one launch per step of 64 columns: every workgroup updates one tile of the trailing
+//                       matrix with the panel of the step before, which it scales itself (two products of
+//                       64^3 more, one launch less), and the workgroup of the diagonal tile then factors and
+//                       inverts it, in blocks of 16 that live in the registers of one wavefront;
+//   lora_apply_kernel   a workgroup carries 16 rows of `in` through all block columns, which stay in LDS:
+//                       out_J = (in_J - sum_{K<J} out_K L_JK^T) X_JJ^T, one launch for the whole block.
+// 4096 x 416: 11 launches (gram, 7 steps, apply) where separate panel, trailing and column products
+// took 38 and a 64-step one-workgroup factorisation (52 us) per 64 columns.
+//
+// A pivot below 1e-9 of the largest diagonal entry of G marks a column that lies in the span of the ones before it
+// (or a padding column of zeros): it gets pivot 1 and a zero column, so the block carries a (numerically)
+// zero column there.
+#include <utility>
+
+#include "slim_internal.h"
+
+namespace slim {
+
+typedef float float16v_t __attribute__((ext_vector_type(16)));
+
+constexpr int kOb = 64;                        // block of columns
+constexpr int kTileFloats = kOb * kOb;
+constexpr int kGramTiles = 640;                // partial tiles of G the workspace has room for
+
+// Tiles of 64 x 64 are stored in the operand order of V_MFMA_F32_16X16X4_F32, four of its steps at a time: the
+// element (n, k) at [n / 16][k / 16][(k % 16) / 4][n % 16][k % 4], so a wavefront's load of 16 rows x 16 columns
+// is one contiguous KiB, and the same tile serves as the A operand (rows m) and the B operand (columns n).
+__device__ __forceinline__ int op_at(int n, int k) { return ((n >> 4) * 4 + (k >> 4)) * 256 + ((k >> 2) & 3) * 64 + (n & 15) * 4 + (k & 3); }
+// tile (i, j), j <= i, of a lower triangle
+__device__ __host__ __forceinline__ int tri(int i, int j) { return i * (i + 1) / 2 + j; }
+
+// c += A B^T over 16 columns: a, b the operands of the lane (row or column lane % 16, columns 4 (lane / 16) .. + 3)
+__device__ __forceinline__ void mma16(float4_t a, float4_t b, float4_t &c)
+{
+#pragma unroll
+    for (int e = 0; e < 4; ++e) c = __builtin_amdgcn_mfma_f32_16x16x4f32(a[e], b[e], c, 0, 0, 0);
+}
+
+// Partial tile of G = Y^T Y: tile t = tri(i, j) over the rows z * zrows .. ; wavefront w takes a quarter of them.  Two
+// rows of Y are the operands of V_MFMA_F32_32X32X2_F32 as they lie in memory: no LDS on the way.
+__global__ __launch_bounds__(256) void lora_gram_kernel(const float *__restrict__ Y, int rows, int l, int zrows, int tiles,
+                                                        float *__restrict__ P)
+{
+    __shared__ __attribute__((aligned(16))) float red[kTileFloats];
+    const int lane = threadIdx.x & 63, r = lane & 31, h = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    int i = 0;
+    while (tri(i + 1, 0) <= (int)blockIdx.x) ++i;
+    const int j = (int)blockIdx.x - tri(i, 0);
+    const int per = zrows / 4;                  // even
+    const int k0 = (int)blockIdx.y * zrows + wave * per;
+    const int cnt = max(0, min(per, rows - k0));
+    // (a base of its own keeps the offsets in 32 bits for any number of rows; reads past the range are zeros)
+    const rsrc_t rs = make_rsrc(Y + (size_t)min(k0, rows) * l, (uint32_t)cnt * (uint32_t)l * 4u);
+    uint32_t ca[2], cb[2];
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+        const int na = kOb * i + 32 * b + r, nb = kOb * j + 32 * b + r;
+        ca[b] = na < l ? (uint32_t)(h * l + na) * 4u : 0xFFFFFF00u;
+        cb[b] = nb < l ? (uint32_t)(h * l + nb) * 4u : 0xFFFFFF00u;
+    }
+    float16v_t acc[2][2];
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) acc[a][b][e] = 0.f;
+    auto ld = [&](uint32_t c, uint32_t row) {
+        return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, c < 0xFFFFFF00u ? (int)(c + row * (uint32_t)l * 4u) : (int)c, 0, 0));
+    };
+    constexpr int U = 4;                        // pairs of rows per trip, the next trip's loads in flight
+    float av[U][2], bv[U][2];
+    auto load = [&](int k) {
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int b = 0; b < 2; ++b) {
+                av[u][b] = ld(ca[b], (uint32_t)(k + 2 * u));
+                bv[u][b] = ld(cb[b], (uint32_t)(k + 2 * u));
+            }
+    };
+    load(0);
+    for (int k = 0; k < cnt; k += 2 * U) {
+        float ac[U][2], bc[U][2];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int b = 0; b < 2; ++b) {
+                ac[u][b] = av[u][b];
+                bc[u][b] = bv[u][b];
+            }
+        load(k + 2 * U);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int a = 0; a < 2; ++a)
+#pragma unroll
+                for (int b = 0; b < 2; ++b) acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x2f32(ac[u][a], bc[u][b], acc[a][b], 0, 0, 0);
+    }
+    // register 4 q + e of a block: row 8 q + 4 h + e, column r
+    for (int w = 0; w < 4; ++w) {
+        if (wave == w) {
+#pragma unroll
+            for (int a = 0; a < 2; ++a)
+#pragma unroll
+                for (int b = 0; b < 2; ++b)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q)
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            float *p = red + op_at(32 * a + 8 * q + 4 * h + e, 32 * b + r);
+                            *p = w == 0 ? acc[a][b][4 * q + e] : *p + acc[a][b][4 * q + e];
+                        }
+        }
+        __syncthreads();
+    }
+    float4_t *const out = reinterpret_cast<float4_t *>(P + ((size_t)blockIdx.y * tiles + blockIdx.x) * kTileFloats);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) out[threadIdx.x + 256 * q] = reinterpret_cast<const float4_t *>(red)[threadIdx.x + 256 * q];
+}
+
+template <int N>
+__device__ __forceinline__ float row_lane(float v)       // lane N of the sixteen, to all of them
+{
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x150 + N, 0xF, 0xF, true));
+}
+template <int... Is, class F>
+__device__ __forceinline__ void for_each_impl(std::integer_sequence<int, Is...>, F &&f)
+{
+    (f(std::integral_constant<int, Is>{}), ...);
+}
+template <int N, class F>
+__device__ __forceinline__ void for_each(F &&f)
+{
+    for_each_impl(std::make_integer_sequence<int, N>{}, f);
+}
+
+// 16 x 16: lane i of sixteen holds row i; a: the symmetric block in, its Cholesky factor out (zeros above the
+// diagonal); x: the factor's inverse.  The steps broadcast across the sixteen lanes without LDS or barriers.
+__device__ __forceinline__ void factor16(float (&a)[16], float (&x)[16], int i, float floor_)
+{
+#pragma unroll
+    for (int c = 0; c < 16; ++c) x[c] = i == c ? 1.0f : 0.f;
+    for_each<16>([&](auto cc) {
+        constexpr int c = cc;
+        const float d = row_lane<c>(a[c]);
+        const bool ok = d > floor_;              // no: a column in the span of the ones before it
+        float q = __builtin_amdgcn_rsqf(ok ? d : 1.0f);
+        q = q * (1.5f - 0.5f * (ok ? d : 1.0f) * q * q);       // 1 / sqrt(d) to rounding
+        const float inv = ok ? q : 0.f;
+        const float li = a[c] * inv;
+        for_each<16>([&](auto jc) {
+            constexpr int j = jc;
+            if constexpr (j > c) a[j] -= li * row_lane<j>(li);
+        });
+        // row c of the inverse is final; the rows below subtract it
+        for_each<16>([&](auto jc) {
+            constexpr int j = jc;
+            if constexpr (j <= c) {
+                const float xs = ok ? x[j] * inv : x[j];
+                const float xc = row_lane<c>(xs);
+                x[j] = i > c ? x[j] - li * xc : (i == c ? xs : x[j]);
+            }
+        });
+        a[c] = i > c ? li : (i == c ? (ok ? d * inv : 1.0f) : 0.f);
+    });
+}
+
+// Step j: tiles (I, J), I >= J >= j, of the trailing matrix; column j - 1 of G holds A_{I, j-1}, D the inverse of
+// the last diagonal block, so the panel is L_{I, j-1} = A_{I, j-1} D^T.  Step 0 adds up the partial tiles instead.
+// The workgroups of column j write the panel to Lf; the one of tile (j, j) factors it and writes D[j].
+__global__ __launch_bounds__(256) void lora_chol_kernel(int j, int nb, int l, const float *__restrict__ P, int splits, int tiles,
+                                                        float *__restrict__ G, float *__restrict__ Lf, float *__restrict__ D, float *gmax)
+{
+    __shared__ __attribute__((aligned(16))) float T[kTileFloats], LI[kTileFloats], LJ[kTileFloats];
+    __shared__ float mx_s[4];
+    const int tid = threadIdx.x, lane = tid & 63, ln = lane & 15, mq = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    int I = 0;
+    while (tri(I + 1, 0) <= (int)blockIdx.x) ++I;
+    const int J = j + (int)blockIdx.x - tri(I, 0);
+    I += j;
+    float4_t *const T4 = reinterpret_cast<float4_t *>(T);
+    float *const Gt = G + (size_t)tri(I, J) * kTileFloats;
+    if (j == 0) {
+        const float4_t *p = reinterpret_cast<const float4_t *>(P + (size_t)tri(I, J) * kTileFloats);
+        float4_t s[4] = {};
+        for (int z = 0; z < splits; ++z)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) s[q] += p[(size_t)z * tiles * (kTileFloats / 4) + tid + 256 * q];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) T4[tid + 256 * q] = s[q];
+    } else {
+        const float4_t *const Ai = reinterpret_cast<const float4_t *>(G + (size_t)tri(I, j - 1) * kTileFloats);
+        const float4_t *const Aj = reinterpret_cast<const float4_t *>(G + (size_t)tri(J, j - 1) * kTileFloats);
+        const float4_t *const Dp = reinterpret_cast<const float4_t *>(D + (size_t)(j - 1) * kTileFloats);
+        float4_t g[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) g[q] = reinterpret_cast<const float4_t *>(Gt)[tid + 256 * q];
+        float4_t ai[4], aj[4];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            ai[t] = Ai[(wave * 4 + t) * 64 + lane];
+            aj[t] = Aj[(wave * 4 + t) * 64 + lane];
+        }
+        // 16 rows of both panels per wavefront
+#pragma unroll
+        for (int cb = 0; cb < 4; ++cb) {
+            float4_t ci = {0.f, 0.f, 0.f, 0.f}, cj = ci;
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                const float4_t d = Dp[(cb * 4 + t) * 64 + lane];
+                mma16(ai[t], d, ci);
+                mma16(aj[t], d, cj);
+            }
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                LI[op_at(16 * wave + 4 * mq + e, 16 * cb + ln)] = ci[e];
+                LJ[op_at(16 * wave + 4 * mq + e, 16 * cb + ln)] = cj[e];
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) T4[tid + 256 * q] = g[q];
+        __syncthreads();
+        if (J == j) {
+            float4_t *const out = reinterpret_cast<float4_t *>(Lf + (size_t)tri(I, j - 1) * kTileFloats);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) out[tid + 256 * q] = reinterpret_cast<const float4_t *>(LI)[tid + 256 * q];
+        }
+        float4_t a[4];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) a[t] = reinterpret_cast<const float4_t *>(LI)[(wave * 4 + t) * 64 + lane];
+#pragma unroll
+        for (int cb = 0; cb < 4; ++cb) {
+            float4_t c = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int t = 0; t < 4; ++t) mma16(a[t], reinterpret_cast<const float4_t *>(LJ)[(cb * 4 + t) * 64 + lane], c);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) T[op_at(16 * wave + 4 * mq + e, 16 * cb + ln)] -= c[e];
+        }
+    }
+    __syncthreads();
+    if (I != j || J != j) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) reinterpret_cast<float4_t *>(Gt)[tid + 256 * q] = T4[tid + 256 * q];
+        return;
+    }
+
+    // ---- the diagonal tile ----
+    float mx;
+    if (j == 0) {
+        mx = 0.f;
+        for (int c = tid; c < l; c += 256) {
+            float s = 0.f;
+            for (int z = 0; z < splits; ++z) s += P[((size_t)z * tiles + tri(c / kOb, c / kOb)) * kTileFloats + op_at(c % kOb, c % kOb)];
+            mx = fmaxf(mx, s);
+        }
+        mx = wave_max(mx);
+        if (lane == 0) mx_s[wave] = mx;
+        __syncthreads();
+        mx = fmaxf(fmaxf(mx_s[0], mx_s[1]), fmaxf(mx_s[2], mx_s[3]));
+        if (tid == 0) *gmax = mx;
+    } else {
+        mx = *gmax;
+    }
+    const float floor_ = mx * 1e-9f;
+    float *const X = LI;                         // the inverse, and
+    float *const XT = LJ;                        // the inverse transposed: block (c, r) holds block (r, c) of X
+    auto block = [](float *base, int bi, int bj) { return base + (bi * 4 + bj) * 256; };
+    auto operand = [&](const float *blk) { return reinterpret_cast<const float4_t *>(blk)[lane]; };
+    __shared__ __attribute__((aligned(16))) float M[3][256];
+    for (int idx = tid; idx < kTileFloats; idx += 256) X[idx] = 0.f;
+    __syncthreads();
+    for (int b = 0; b < 4; ++b) {
+        if (wave == 0) {
+            float a[16], x[16];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const float4_t v = reinterpret_cast<const float4_t *>(block(T, b, b))[q * 16 + ln];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) a[4 * q + e] = v[e];
+            }
+            factor16(a, x, ln, floor_);
+            if (lane < 16) {
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    reinterpret_cast<float4_t *>(block(X, b, b))[q * 16 + ln] = float4_t{x[4 * q], x[4 * q + 1], x[4 * q + 2], x[4 * q + 3]};
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) block(XT, b, b)[(ln >> 2) * 64 + (4 * q + e) * 4 + (ln & 3)] = x[4 * q + e];
+                }
+            }
+        }
+        __syncthreads();
+        // panel: block rows b + 1 .. 3, one per wavefront
+        if (wave > b) {
+            float4_t c = {0.f, 0.f, 0.f, 0.f};
+            mma16(operand(block(T, wave, b)), operand(block(X, b, b)), c);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) block(T, wave, b)[(ln >> 2) * 64 + (4 * mq + e) * 4 + (ln & 3)] = c[e];
+        }
+        __syncthreads();
+        if (wave > b) {
+            const float4_t a = operand(block(T, wave, b));
+            for (int k = b + 1; k <= wave; ++k) {
+                float4_t c = {0.f, 0.f, 0.f, 0.f};
+                mma16(a, operand(block(T, k, b)), c);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) block(T, wave, k)[(ln >> 2) * 64 + (4 * mq + e) * 4 + (ln & 3)] -= c[e];
+            }
+        }
+        __syncthreads();
+    }
+    // the inverse below its diagonal blocks: X_ij = -X_ii sum_{j <= k < i} L_ik X_kj, block row after block row
+    for (int i = 1; i < 4; ++i) {
+        if (wave < i) {
+            float4_t c = {0.f, 0.f, 0.f, 0.f};
+            for (int k = wave; k < i; ++k) mma16(operand(block(T, i, k)), operand(block(XT, wave, k)), c);
+            reinterpret_cast<float4_t *>(M[wave])[mq * 16 + ln] = c;          // transposed: operand order of its columns
+            asm volatile("s_waitcnt lgkmcnt(0)" : : : "memory");
+            float4_t y = {0.f, 0.f, 0.f, 0.f};
+            mma16(operand(block(X, i, i)), operand(M[wave]), y);
+            reinterpret_cast<float4_t *>(block(XT, wave, i))[mq * 16 + ln] = -y;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) block(X, i, wave)[(ln >> 2) * 64 + (4 * mq + e) * 4 + (ln & 3)] = -y[e];
+        }
+        __syncthreads();
+    }
+    float4_t *const out = reinterpret_cast<float4_t *>(D + (size_t)j * kTileFloats);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) out[tid + 256 * q] = reinterpret_cast<const float4_t *>(X)[tid + 256 * q];
+}
+
+// 16 rows of out = in Lc^-T, block column after block column; wavefront w computes the columns 16 w .. 16 w + 15 of each.
+__global__ __launch_bounds__(256) void lora_apply_kernel(const float *__restrict__ in, float *__restrict__ out, int rows, int l, int nb,
+                                                         const float *__restrict__ Lf, const float *__restrict__ D)
+{
+    extern __shared__ __attribute__((aligned(16))) float lds[];
+    const int ldo = nb * kOb + 4;
+    float *const O = lds;                        // [16][ldo]: the rows of out so far
+    float *const V = lds + 16 * ldo;             // [16][68]
+    const int lane = threadIdx.x & 63, ln = lane & 15, mq = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int r0 = blockIdx.x * 16;
+    for (int J = 0; J < nb; ++J) {
+        const int col = kOb * J + 16 * wave + ln;
+        float v[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int row = r0 + 4 * mq + e;
+            v[e] = row < rows && col < l ? in[(size_t)row * l + col] : 0.f;
+        }
+        const float4_t *const Dj = reinterpret_cast<const float4_t *>(D + (size_t)J * kTileFloats);
+        float4_t d[4];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) d[t] = Dj[(wave * 4 + t) * 64 + lane];
+        float4_t c0 = {0.f, 0.f, 0.f, 0.f}, c1 = c0;
+        const float4_t *const Lj = reinterpret_cast<const float4_t *>(Lf + (size_t)tri(J, 0) * kTileFloats);
+        float4_t b[4];
+        if (J > 0) {
+#pragma unroll
+            for (int t = 0; t < 4; ++t) b[t] = Lj[(wave * 4 + t) * 64 + lane];
+        }
+        for (int K = 0; K < J; ++K) {
+            float4_t bc[4];
+#pragma unroll
+            for (int t = 0; t < 4; ++t) bc[t] = b[t];
+            const int Kn = K + 1 < J ? K + 1 : K;
+#pragma unroll
+            for (int t = 0; t < 4; ++t) b[t] = Lj[(size_t)Kn * (kTileFloats / 4) + (wave * 4 + t) * 64 + lane];
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                const float4_t a = *reinterpret_cast<const float4_t *>(O + ln * ldo + kOb * K + 16 * t + 4 * mq);
+                mma16(a, bc[t], t & 1 ? c1 : c0);
+            }
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) V[(4 * mq + e) * 68 + 16 * wave + ln] = v[e] - (c0[e] + c1[e]);
+        __syncthreads();
+        float4_t y0 = {0.f, 0.f, 0.f, 0.f}, y1 = y0;
+#pragma unroll
+        for (int t = 0; t < 4; ++t) mma16(*reinterpret_cast<const float4_t *>(V + ln * 68 + 16 * t + 4 * mq), d[t], t & 1 ? y1 : y0);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int row = r0 + 4 * mq + e;
+            const float y = y0[e] + y1[e];
+            O[(4 * mq + e) * ldo + kOb * J + 16 * wave + ln] = y;
+            if (row < rows && col < l) out[(size_t)row * l + col] = y;
+        }
+        __syncthreads();
+    }
+}
+
+// Workspace of an orth(), in floats: partial tiles, tiles of G and of the factor, inverses of the diagonal blocks,
+// the largest diagonal entry.
+size_t orth_floats(int l)
+{
+    const size_t nb = (size_t)(l + kOb - 1) / kOb, t = nb * (nb + 1) / 2;
+    return (kGramTiles + 2 * t + nb) * kTileFloats + 64;
+}
+
+int launch_orth(const float *in, float *out, int rows, int l, float *ws, hipStream_t st)
+{
+    const int nb = (l + kOb - 1) / kOb, tiles = tri(nb, 0);
+    float *const P = ws, *const G = P + (size_t)kGramTiles * kTileFloats, *const Lf = G + (size_t)tiles * kTileFloats;
+    float *const D = Lf + (size_t)tiles * kTileFloats, *const gmax = D + (size_t)nb * kTileFloats;
+    // about two workgroups per compute unit, at least 64 rows each
+    int splits = kGramTiles / tiles;
+    if (splits > (rows + 63) / 64) splits = (rows + 63) / 64;
+    const int zrows = ((rows + splits - 1) / splits + 31) / 32 * 32;
+    splits = (rows + zrows - 1) / zrows;
+    hipLaunchKernelGGL(lora_gram_kernel, dim3((unsigned)tiles, (unsigned)splits), dim3(256), 0, st, in, rows, l, zrows, tiles, P);
+    for (int j = 0; j < nb; ++j)
+        hipLaunchKernelGGL(lora_chol_kernel, dim3((unsigned)tri(nb - j, 0)), dim3(256), 0, st, j, nb, l, (const float *)P, splits, tiles, G, Lf, D,
+                           gmax);
+    const size_t lds = (size_t)(16 * (nb * kOb + 4) + 16 * 68) * sizeof(float);
+    hipLaunchKernelGGL(lora_apply_kernel, dim3((unsigned)((rows + 15) / 16)), dim3(256), lds, st, in, out, rows, l, nb, (const float *)Lf,
+                       (const float *)D);
+    return hip_status(hipGetLastError());
+}
+
+}  // namespace slim
