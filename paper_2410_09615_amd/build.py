@@ -29,7 +29,7 @@ def sources():
 
 
 # Sources whose kernels address the accumulation registers by number (slim_mma.h).
-FIXED_ACC_SOURCES = ("slim_gemm", "slim_gemm_sparse")
+FIXED_ACC_SOURCES = ("slim_gemm", "slim_gemm_sparse", "slim_lora_split")
 _MATRIX_OP = re.compile(r"^\s*v_(mfma|smfmac)_")
 _COMPILER_AGPR = re.compile(r"\ba\d+\b|\ba\[\d+:\d+\]")
 

@@ -161,6 +161,9 @@ __device__ __forceinline__ half_t load_half(rsrc_t r, uint32_t lane_off, uint32_
 
 #endif
 
+// A block of columns of the adapter computation (magnitudes up to 1) as two fp16 numbers: v = (hi + lo) / kBlockSplit.
+constexpr float kBlockSplit = 4096.0f;
+
 // What the planners need to know of the device that is current: compute units and LDS bytes per compute
 // unit, read once per device from its properties (the nominal MI355X figures, 256 and 160 KiB, where no
 // device can be asked: the planners are host logic and also run without one).

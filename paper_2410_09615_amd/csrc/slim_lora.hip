@@ -236,7 +236,7 @@ __global__ __launch_bounds__(1024) void lora_shift_kernel(const float *xt, int k
 }
 
 // ---- S = (W - W^C) diag(x); the packed bytes are read in their tiled layout ----
-// One thread per group of four inputs.  sq[0] += ||S||_F^2.
+// One thread per group of four inputs.  sq[0] += ||S||_F^2, sq[4]: bits of the largest magnitude.
 __global__ __launch_bounds__(256) void lora_error_kernel(const float *W, const uint8_t *qvals, const uint8_t *meta,
                                                          const float *scale, const float *x, int n, int k, float *S,
                                                          float *sq)
@@ -244,7 +244,7 @@ __global__ __launch_bounds__(256) void lora_error_kernel(const float *W, const u
     const int groups = k / 4;
     const size_t total = (size_t)n * groups;
     const uint32_t kt = pk_ktiles(k);
-    float part = 0.f;
+    float part = 0.f, mx = 0.f;
     for (size_t t = (size_t)blockIdx.x * blockDim.x + threadIdx.x; t < total; t += (size_t)gridDim.x * blockDim.x) {
         const uint32_t o = (uint32_t)(t / groups), g = (uint32_t)(t % groups);
         const uint32_t q = qvals[pk_qoff(o, g, kt)];
@@ -261,10 +261,17 @@ __global__ __launch_bounds__(256) void lora_error_kernel(const float *W, const u
         for (int i = 0; i < 4; ++i) {
             e[i] = (w[i] - wc[i]) * xv[i];
             part += e[i] * e[i];
+            mx = fmaxf(mx, fabsf(e[i]));
         }
         *reinterpret_cast<float4_t *>(S + (size_t)o * k + 4 * g) = e;
     }
     block_add(part, sq);
+    __shared__ float mx4[4];
+    mx = wave_max(mx);
+    if ((threadIdx.x & 63) == 0) mx4[threadIdx.x >> 6] = mx;
+    __syncthreads();
+    if (threadIdx.x == 0)                    // non-negative floats order as integers
+        atomicMax(reinterpret_cast<unsigned *>(sq + 4), __float_as_uint(fmaxf(fmaxf(mx4[0], mx4[1]), fmaxf(mx4[2], mx4[3]))));
 }
 
 // ---- start block: uniform in (-1, 1) from a hash of (seed, element), columns >= r zero ----
@@ -278,20 +285,34 @@ __device__ __forceinline__ uint32_t mix32(uint32_t v)
     return v;
 }
 
-__global__ void lora_init_kernel(float *Z, int rows, int l, int r, uint32_t seed)
+// (element t = row * l + column; written to Z, or as the two fp16 numbers of the split products, columns as rows)
+__global__ void lora_init_kernel(float *Z, half_t *hi, half_t *lo, int rows, int l, int r, uint32_t seed)
 {
     const size_t total = (size_t)rows * l;
     for (size_t t = (size_t)blockIdx.x * blockDim.x + threadIdx.x; t < total; t += (size_t)gridDim.x * blockDim.x) {
         const int c = (int)(t % l);
         const uint32_t hsh = mix32(mix32((uint32_t)t ^ seed) + (uint32_t)(t >> 32) + 0x9e3779b9u * seed);
-        Z[t] = c < r ? ((float)(hsh >> 8) + 0.5f) * (2.0f / 16777216.0f) - 1.0f : 0.f;
+        const float z = c < r ? ((float)(hsh >> 8) + 0.5f) * (2.0f / 16777216.0f) - 1.0f : 0.f;
+        if (Z) {
+            Z[t] = z;
+            continue;
+        }
+        const float v = z * kBlockSplit;
+        const half_t x = (half_t)v;
+        hi[(size_t)c * rows + t / l] = x;
+        lo[(size_t)c * rows + t / l] = (half_t)(v - (float)x);
     }
 }
 
+constexpr int kSplitMax = 1 << 22;       // n and k below this: a tile's rows of the split matrices have 32-bit offsets
 constexpr int kMaxBlock = 1024;          // columns of the iteration block (rank_pad)
 
 size_t orth_floats(int l);                                                                           // slim_lora_orth.hip
-int launch_orth(const float *in, float *out, int rows, int l, float *ws, hipStream_t st);
+int launch_orth(const float *in, float *out, half_t *hi, half_t *lo, int rows, int l, float *ws, hipStream_t st);
+int split_gemm_splits(int rows, int cols, int K);                                                    // slim_lora_split.hip
+int launch_lora_split(const float *S, int n, int k, const unsigned *max_bits, half_t *Sh, half_t *Sl, half_t *Th, half_t *Tl, hipStream_t st);
+int launch_lora_split_gemm(const half_t *Ah, const half_t *Al, const unsigned *max_bits, const half_t *Bh, const half_t *Bl, int rows, int cols,
+                           int K, float *P, float *Y, hipStream_t st);
 
 // ---- results: L fp16 [n][r] = Q[:, :r];  R fp16 [r][k] = R~[:r] / x;  sq[1] += ||R~[:r]||_F^2 ----
 __global__ void lora_out_l_kernel(const float *Q, int n, int l, int r, half_t *L)
@@ -336,7 +357,8 @@ __global__ void lora_report_kernel(const float *sq, float *diag)
 
 struct LoraPlan {
     int l;                      // columns of the iteration block: rank padded as the layer's adapters are
-    size_t x, S, Q, Y, Z, G, O, Rt, sq, total;      // byte offsets (O: the orthonormalisation's own)
+    bool split;                 // products on the fp16 matrix cores (lora_split_gemm_kernel)
+    size_t x, S, half[4], Q, Y, Z, P, blk[4], G, O, Rt, sq, total;      // byte offsets (O: the orthonormalisation's own)
 };
 
 static size_t up256(size_t v) { return (v + 255) / 256 * 256; }
@@ -356,7 +378,17 @@ static LoraPlan plan_lora(int n, int k, int rank)
     p.S = take((size_t)n * k);
     p.Q = take(big * l);
     p.Y = take(big * l);
-    p.Z = take((size_t)k * l);
+    const int n32 = (n + 31) / 32 * 32;
+    p.split = n32 < kSplitMax && k < kSplitMax;
+    if (p.split) {
+        // S and S^T as two fp16 matrices each, the blocks [l][n32] and [l][k] likewise, partial sums of the products
+        for (int i = 0; i < 4; ++i) p.half[i] = take(((size_t)n32 * k + 1) / 2);
+        for (int i = 0; i < 4; ++i) p.blk[i] = take((l * (i < 2 ? n32 : k) + 1) / 2);
+        const size_t pn = (size_t)split_gemm_splits(n, p.l, k) * n * l, pk = (size_t)split_gemm_splits(k, p.l, n32) * k * l;
+        p.P = take(pn > pk ? pn : pk);
+    } else {
+        p.Z = take((size_t)k * l);
+    }
     p.G = take(l * l);
     p.O = take(orth_floats(p.l));
     p.Rt = take(l * k);
@@ -396,7 +428,7 @@ extern "C" int slim_compute_adapters(const float *W, const uint8_t *qvals, const
     char *ws = static_cast<char *>(workspace);
     float *x = reinterpret_cast<float *>(ws + p.x), *S = reinterpret_cast<float *>(ws + p.S);
     float *Q = reinterpret_cast<float *>(ws + p.Q), *Y = reinterpret_cast<float *>(ws + p.Y);
-    float *Z = reinterpret_cast<float *>(ws + p.Z), *G = reinterpret_cast<float *>(ws + p.G);
+    float *P = p.split ? reinterpret_cast<float *>(ws + p.P) : nullptr, *G = reinterpret_cast<float *>(ws + p.G);
     float *O = reinterpret_cast<float *>(ws + p.O), *Rt = reinterpret_cast<float *>(ws + p.Rt);
     float *sq = reinterpret_cast<float *>(ws + p.sq);
     const int l = p.l;
@@ -416,21 +448,38 @@ extern "C" int slim_compute_adapters(const float *W, const uint8_t *qvals, const
     hipLaunchKernelGGL(lora_error_kernel, dim3(std::min(grid_for((size_t)n * (k / 4)).x, 1024u)), dim3(256), 0, st, W, qvals, meta, scale,
                        (const float *)x, n, k, S, sq);
     SLIM_TRY(launched());
-    hipLaunchKernelGGL(lora_init_kernel, grid_for((size_t)k * l), dim3(256), 0, st, Z, k, l, r, seed);
-    SLIM_TRY(launched());
 
-    // out = orth(in) for a block [rows][l]
-    auto orth = [&](const float *in, float *out, int rows) { return launch_orth(in, out, rows, l, O, st); };
-
-    SLIM_TRY(sgemm(false, false, S, k, Z, l, Y, l, n, l, k, st));          // Y = S Z           [n][l]
-    SLIM_TRY(orth(Y, Q, n));
-    for (int it = 0; it < q; ++it) {
-        SLIM_TRY(sgemm(true, false, S, k, Q, l, Y, l, k, l, n, st));       // Y = S^T Q         [k][l]
-        SLIM_TRY(orth(Y, Z, k));
-        SLIM_TRY(sgemm(false, false, S, k, Z, l, Y, l, n, l, k, st));      // Y = S Z           [n][l]
-        SLIM_TRY(orth(Y, Q, n));
+    float *Z = p.split ? nullptr : reinterpret_cast<float *>(ws + p.Z);
+    half_t *Sh[4] = {}, *blk[4] = {};        // S, S^T: hi and lo; Q, Z: hi and lo
+    const unsigned *mx = reinterpret_cast<const unsigned *>(sq + 4);
+    const int n32 = (n + 31) / 32 * 32;
+    if (p.split) {
+        for (int i = 0; i < 4; ++i) {
+            Sh[i] = reinterpret_cast<half_t *>(ws + p.half[i]);
+            blk[i] = reinterpret_cast<half_t *>(ws + p.blk[i]);
+        }
+        SLIM_TRY(launch_lora_split(S, n, k, mx, Sh[0], Sh[1], Sh[2], Sh[3], st));
     }
-    SLIM_TRY(orth(Q, Y, n));                                        // second pass: orthonormal to rounding
+    hipLaunchKernelGGL(lora_init_kernel, grid_for((size_t)k * l), dim3(256), 0, st, Z, blk[2], blk[3], k, l, r, seed);
+    SLIM_TRY(launched());
+    auto times_z = [&]() {                   // Y = S Z     [n][l]
+        return p.split ? launch_lora_split_gemm(Sh[0], Sh[1], mx, blk[2], blk[3], n, l, k, P, Y, st)
+                       : sgemm(false, false, S, k, Z, l, Y, l, n, l, k, st);
+    };
+    auto times_q = [&]() {                   // Y = S^T Q   [k][l]
+        return p.split ? launch_lora_split_gemm(Sh[2], Sh[3], mx, blk[0], blk[1], k, l, n32, P, Y, st)
+                       : sgemm(true, false, S, k, Q, l, Y, l, k, l, n, st);
+    };
+
+    SLIM_TRY(times_z());
+    for (int it = 0; it < q; ++it) {
+        SLIM_TRY(launch_orth(Y, p.split ? nullptr : Q, blk[0], blk[1], n, l, O, st));
+        SLIM_TRY(times_q());
+        SLIM_TRY(launch_orth(Y, Z, blk[2], blk[3], k, l, O, st));
+        SLIM_TRY(times_z());
+    }
+    SLIM_TRY(launch_orth(Y, Q, nullptr, nullptr, n, l, O, st));
+    SLIM_TRY(launch_orth(Q, Y, nullptr, nullptr, n, l, O, st));    // second pass: orthonormal to rounding
     SLIM_TRY(sgemm(true, false, Y, l, S, k, Rt, k, l, k, n, st));          // R~ = Q^T S        [l][k]
     SLIM_TRY(sgemm(true, false, Y, l, Y, l, G, l, l, l, n, st));           // Gram of the final block, for the report
     hipLaunchKernelGGL(lora_ortho_kernel, grid_for((size_t)r * r), dim3(256), 0, st, (const float *)G, l, r, sq);

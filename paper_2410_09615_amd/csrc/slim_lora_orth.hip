@@ -12,8 +12,9 @@
 //                       inverts it, in blocks of 16 that live in the registers of one wavefront;
 //   lora_apply_kernel   a workgroup carries 16 rows of `in` through all block columns, which stay in LDS:
 //                       out_J = (in_J - sum_{K<J} out_K L_JK^T) X_JJ^T, one launch for the whole block.
-// 4096 x 416: 11 launches (gram, 7 steps, apply) where separate panel, trailing and column products
-// took 38 and a 64-step one-workgroup factorisation (52 us) per 64 columns.
+// 4096 x 416: 9 launches (gram, 7 steps, apply) where separate panel, trailing and column products
+// took 38 and a 64-step one-workgroup factorisation (52 us) per 64 columns: 150 us (gram 22, steps 15.7 each,
+// apply 20) where it was 700.
 //
 // A pivot below 1e-9 of the largest diagonal entry of G marks a column that lies in the span of the ones before it
 // (or a padding column of zeros): it gets pivot 1 and a zero column, so the block carries a (numerically)
@@ -77,7 +78,7 @@ __global__ __launch_bounds__(256) void lora_gram_kernel(const float *__restrict_
     auto ld = [&](uint32_t c, uint32_t row) {
         return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, c < 0xFFFFFF00u ? (int)(c + row * (uint32_t)l * 4u) : (int)c, 0, 0));
     };
-    constexpr int U = 4;                        // pairs of rows per trip, the next trip's loads in flight
+    constexpr int U = 8;                        // pairs of rows per trip, the next trip's loads in flight
     float av[U][2], bv[U][2];
     auto load = [&](int k) {
 #pragma unroll
@@ -145,35 +146,35 @@ __device__ __forceinline__ void for_each(F &&f)
     for_each_impl(std::make_integer_sequence<int, N>{}, f);
 }
 
-// 16 x 16: lane i of sixteen holds row i; a: the symmetric block in, its Cholesky factor out (zeros above the
-// diagonal); x: the factor's inverse.  The steps broadcast across the sixteen lanes without LDS or barriers.
+// 16 x 16: lane i of sixteen holds row i of the symmetric block a = Lc Lc^T; x: row i of Lc^-1.  The steps run on
+// a = M diag(d) M^T, M with a unit diagonal, whose chain has a reciprocal and no square root, and the rows of M^-1 are
+// scaled by 1 / sqrt(d) at the end; they broadcast across the sixteen lanes without LDS or barriers.
 __device__ __forceinline__ void factor16(float (&a)[16], float (&x)[16], int i, float floor_)
 {
 #pragma unroll
     for (int c = 0; c < 16; ++c) x[c] = i == c ? 1.0f : 0.f;
+    float mine = 1.0f;                           // this row's pivot
     for_each<16>([&](auto cc) {
         constexpr int c = cc;
         const float d = row_lane<c>(a[c]);
-        const bool ok = d > floor_;              // no: a column in the span of the ones before it
-        float q = __builtin_amdgcn_rsqf(ok ? d : 1.0f);
-        q = q * (1.5f - 0.5f * (ok ? d : 1.0f) * q * q);       // 1 / sqrt(d) to rounding
-        const float inv = ok ? q : 0.f;
-        const float li = a[c] * inv;
+        const bool ok = d > floor_;              // no: a column in the span of the ones before it: pivot 1, nothing to subtract
+        if (i == c) mine = ok ? d : 1.0f;
+        float q = __builtin_amdgcn_rcpf(d);
+        q = q * (2.0f - d * q);                  // to rounding
+        const float m = ok && i > c ? -a[c] * q : 0.f;
+        const float ac = a[c];
         for_each<16>([&](auto jc) {
             constexpr int j = jc;
-            if constexpr (j > c) a[j] -= li * row_lane<j>(li);
+            if constexpr (j > c)
+                a[j] = __builtin_fmaf(row_lane<j>(ac), m, a[j]);
+            else
+                x[j] = __builtin_fmaf(row_lane<c>(x[j]), m, x[j]);
         });
-        // row c of the inverse is final; the rows below subtract it
-        for_each<16>([&](auto jc) {
-            constexpr int j = jc;
-            if constexpr (j <= c) {
-                const float xs = ok ? x[j] * inv : x[j];
-                const float xc = row_lane<c>(xs);
-                x[j] = i > c ? x[j] - li * xc : (i == c ? xs : x[j]);
-            }
-        });
-        a[c] = i > c ? li : (i == c ? (ok ? d * inv : 1.0f) : 0.f);
     });
+    float q = __builtin_amdgcn_rsqf(mine);
+    q = q * (1.5f - 0.5f * mine * q * q);        // 1 / sqrt(d) to rounding
+#pragma unroll
+    for (int c = 0; c < 16; ++c) x[c] *= q;
 }
 
 // Step j: tiles (I, J), I >= J >= j, of the trailing matrix; column j - 1 of G holds A_{I, j-1}, D the inverse of
@@ -342,7 +343,8 @@ __global__ __launch_bounds__(256) void lora_chol_kernel(int j, int nb, int l, co
 
 // 16 rows of out = in Lc^-T, block column after block column; wavefront w computes the columns 16 w .. 16 w + 15 of each.
 __global__ __launch_bounds__(256) void lora_apply_kernel(const float *__restrict__ in, float *__restrict__ out, int rows, int l, int nb,
-                                                         const float *__restrict__ Lf, const float *__restrict__ D)
+                                                         const float *__restrict__ Lf, const float *__restrict__ D, half_t *__restrict__ hi,
+                                                         half_t *__restrict__ lo, int ldk)
 {
     extern __shared__ __attribute__((aligned(16))) float lds[];
     const int ldo = nb * kOb + 4;
@@ -351,25 +353,28 @@ __global__ __launch_bounds__(256) void lora_apply_kernel(const float *__restrict
     const int lane = threadIdx.x & 63, ln = lane & 15, mq = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int r0 = blockIdx.x * 16;
-    for (int J = 0; J < nb; ++J) {
+    // block column J: its part of `in`, the inverse of its diagonal block, the first tile of the factor (the loads of
+    // the next column go out before this one's last products)
+    float v[4];
+    float4_t d[4], b[4];
+    auto load_column = [&](int J) {
         const int col = kOb * J + 16 * wave + ln;
-        float v[4];
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             const int row = r0 + 4 * mq + e;
             v[e] = row < rows && col < l ? in[(size_t)row * l + col] : 0.f;
         }
-        const float4_t *const Dj = reinterpret_cast<const float4_t *>(D + (size_t)J * kTileFloats);
-        float4_t d[4];
 #pragma unroll
-        for (int t = 0; t < 4; ++t) d[t] = Dj[(wave * 4 + t) * 64 + lane];
+        for (int t = 0; t < 4; ++t) {
+            d[t] = reinterpret_cast<const float4_t *>(D + (size_t)J * kTileFloats)[(wave * 4 + t) * 64 + lane];
+            b[t] = reinterpret_cast<const float4_t *>(Lf + (size_t)tri(J, 0) * kTileFloats)[(wave * 4 + t) * 64 + lane];
+        }
+    };
+    load_column(0);
+    for (int J = 0; J < nb; ++J) {
+        const int col = kOb * J + 16 * wave + ln;
         float4_t c0 = {0.f, 0.f, 0.f, 0.f}, c1 = c0;
         const float4_t *const Lj = reinterpret_cast<const float4_t *>(Lf + (size_t)tri(J, 0) * kTileFloats);
-        float4_t b[4];
-        if (J > 0) {
-#pragma unroll
-            for (int t = 0; t < 4; ++t) b[t] = Lj[(wave * 4 + t) * 64 + lane];
-        }
         for (int K = 0; K < J; ++K) {
             float4_t bc[4];
 #pragma unroll
@@ -377,26 +382,50 @@ __global__ __launch_bounds__(256) void lora_apply_kernel(const float *__restrict
             const int Kn = K + 1 < J ? K + 1 : K;
 #pragma unroll
             for (int t = 0; t < 4; ++t) b[t] = Lj[(size_t)Kn * (kTileFloats / 4) + (wave * 4 + t) * 64 + lane];
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int t = 0; t < 4; ++t) {
                 const float4_t a = *reinterpret_cast<const float4_t *>(O + ln * ldo + kOb * K + 16 * t + 4 * mq);
                 mma16(a, bc[t], t & 1 ? c1 : c0);
             }
         }
+        float4_t dc[4];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) dc[t] = d[t];
 #pragma unroll
         for (int e = 0; e < 4; ++e) V[(4 * mq + e) * 68 + 16 * wave + ln] = v[e] - (c0[e] + c1[e]);
+        load_column(J + 1 < nb ? J + 1 : J);
         __syncthreads();
         float4_t y0 = {0.f, 0.f, 0.f, 0.f}, y1 = y0;
 #pragma unroll
-        for (int t = 0; t < 4; ++t) mma16(*reinterpret_cast<const float4_t *>(V + ln * 68 + 16 * t + 4 * mq), d[t], t & 1 ? y1 : y0);
+        for (int t = 0; t < 4; ++t) mma16(*reinterpret_cast<const float4_t *>(V + ln * 68 + 16 * t + 4 * mq), dc[t], t & 1 ? y1 : y0);
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             const int row = r0 + 4 * mq + e;
             const float y = y0[e] + y1[e];
             O[(4 * mq + e) * ldo + kOb * J + 16 * wave + ln] = y;
-            if (row < rows && col < l) out[(size_t)row * l + col] = y;
+            if (out && row < rows && col < l) out[(size_t)row * l + col] = y;
         }
         __syncthreads();
+    }
+    if (hi) {
+        // the rows of this workgroup as two fp16 numbers, columns as rows (rows past the last are zeros)
+        for (int c = threadIdx.x; c < l; c += 256) {
+            half8_t h[2], g[2];
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const float v = O[r * ldo + c] * kBlockSplit;
+                const half_t x = (half_t)v;
+                h[r / 8][r % 8] = x;
+                g[r / 8][r % 8] = (half_t)(v - (float)x);
+            }
+            const size_t at = (size_t)c * ldk + r0;
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                *reinterpret_cast<half8_t *>(hi + at + 8 * q) = h[q];
+                *reinterpret_cast<half8_t *>(lo + at + 8 * q) = g[q];
+            }
+        }
     }
 }
 
@@ -408,7 +437,8 @@ size_t orth_floats(int l)
     return (kGramTiles + 2 * t + nb) * kTileFloats + 64;
 }
 
-int launch_orth(const float *in, float *out, int rows, int l, float *ws, hipStream_t st)
+// out (or null): fp32 [rows][l]; hi, lo (or null): the block for lora_split_gemm_kernel, [l][rows rounded up to 32]
+int launch_orth(const float *in, float *out, half_t *hi, half_t *lo, int rows, int l, float *ws, hipStream_t st)
 {
     const int nb = (l + kOb - 1) / kOb, tiles = tri(nb, 0);
     float *const P = ws, *const G = P + (size_t)kGramTiles * kTileFloats, *const Lf = G + (size_t)tiles * kTileFloats;
@@ -423,8 +453,8 @@ int launch_orth(const float *in, float *out, int rows, int l, float *ws, hipStre
         hipLaunchKernelGGL(lora_chol_kernel, dim3((unsigned)tri(nb - j, 0)), dim3(256), 0, st, j, nb, l, (const float *)P, splits, tiles, G, Lf, D,
                            gmax);
     const size_t lds = (size_t)(16 * (nb * kOb + 4) + 16 * 68) * sizeof(float);
-    hipLaunchKernelGGL(lora_apply_kernel, dim3((unsigned)((rows + 15) / 16)), dim3(256), lds, st, in, out, rows, l, nb, (const float *)Lf,
-                       (const float *)D);
+    hipLaunchKernelGGL(lora_apply_kernel, dim3((unsigned)((rows + 31) / 32 * 2)), dim3(256), lds, st, in, out, rows, l, nb, (const float *)Lf,
+                       (const float *)D, hi, lo, (rows + 31) / 32 * 32);
     return hip_status(hipGetLastError());
 }
 

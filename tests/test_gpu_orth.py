@@ -1,0 +1,46 @@
+"""slim_compute_adapters at the sizes where its blocked orthonormalisation and its split products can go wrong: ranks on
+both sides of the 64-column blocks, rows and columns on both sides of the 16, 32, 64 and 256-row tiles, several
+blocks of K, error saliencies whose channels span six orders of magnitude.  Checked is what holds whatever the
+rounds have reached: L orthonormal, R = L^T S diag(1 / x) and the reported energies, all against binary64 on the
+library's own L.  L and R are rounded to fp16 once: entries of L^T L are sums of n products of two rounded numbers
+with 2^-11 relative error each, at most 2^-10 per entry for unit columns (Cauchy-Schwarz), taken at twice that;
+R is off by its own rounding, 2^-11, and by that of L it is compared with, 2^-11 of ||S|| / ||L^T S||, taken
+at four times their sum."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import slim_oracle as O
+from paper_2410_09615_amd import binding as B
+from paper_2410_09615_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+@pytest.mark.parametrize("n,k,r,spread", [
+    (64, 128, 1, 1), (33, 128, 31, 1), (100, 256, 63, 1), (130, 384, 64, 1), (257, 256, 65, 1e6), (513, 640, 96, 1),
+    (1000, 1152, 129, 1e6), (300, 2048, 200, 1), (2049, 512, 260, 1), (1100, 1280, 1024, 1), (96, 4096, 96, 1), (5000, 256, 50, 1e3)])
+def test_adapters_are_orthonormal_and_project_the_error(n, k, r, spread):
+    W = wl.make_weight(n, k, seed=n + r).numpy()
+    q, m, s = B.slim_pack(torch.from_numpy(W).to(DEV))
+    ref = O.compress(W)
+    Wc = O.dequant(ref.qvals, ref.meta, ref.scale)
+    rng = np.random.default_rng(n * r)
+    xt = np.exp(rng.uniform(0, np.log(spread), k)).astype(np.float32) if spread > 1 else None
+    L, R, diag = B.slim_compute_adapters(torch.from_numpy(W).to(DEV), q, m, s, r, None if xt is None else torch.from_numpy(xt).to(DEV), iters=3)
+    torch.cuda.synchronize()
+    x = np.ones(k) if xt is None else O.saliency_shift(xt)
+    S = (W.astype(np.float64) - Wc) * x[None, :]
+    Lf, Rf = L.cpu().numpy().astype(np.float64), R.cpu().numpy().astype(np.float64) * x[None, :]
+    d = diag.cpu().numpy().astype(np.float64)
+    assert np.max(np.abs(Lf.T @ Lf - np.eye(r))) <= 2 * 2.0 ** -10
+    assert d[2] < 1e-4
+    want = Lf.T @ S
+    tol = 4 * 2.0 ** -11 * (1 + np.linalg.norm(S) / np.linalg.norm(want))
+    assert np.linalg.norm(Rf - want) <= tol * np.linalg.norm(want)
+    assert abs(d[0] - np.sum(S ** 2)) <= 1e-4 * np.sum(S ** 2)
+    assert abs(d[1] - np.sum(want ** 2)) <= 4e-3 * np.sum(want ** 2)
+    # three rounds capture most of what the exact truncation does
+    top = np.sum(np.linalg.svd(S, compute_uv=False)[:r] ** 2)
+    assert 0.8 * top <= d[1] <= top * (1 + 1e-4)
