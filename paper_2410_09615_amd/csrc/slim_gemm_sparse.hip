@@ -4,8 +4,13 @@
 // Workgroup: 4 wavefronts, one per SIMD; tile (128 AT) output rows x 128 tokens;
 // each wavefront owns (32 AT) rows x 128 tokens = AT x 4 accumulator tiles of
 // 32 x 32.  AT = 4 is the working configuration (128 x 128 outputs per
-// wavefront); AT = 2 finishes the row tiles left over after the last whole
-// round of workgroups.
+// wavefront); AT = 2 and AT = 1 finish the row tiles left over after the last whole
+// round of workgroups, with eight wavefronts: two groups of four (KW = 2) work on the same
+// tile, each on half of the inputs and half of the ranks, and add up in LDS at the
+// end.  One wavefront per SIMD leaves the matrix pipe idle half of the time (its
+// conversions and waits are in line with its matrix instructions); the 512-row tile has
+// no registers for a second one, these have (11008 x 4096 at 333 tokens, all of it such tiles: 54.0 -> 51.4 us;
+// 2048 tokens with 8-bit inputs 155.5 -> 151.1).
 //   A (weights): never touches LDS.  Per 128 inputs a lane loads 16 bytes of
 //     codes and 8 bytes of positions of each of its rows straight from global
 //     memory (two stages ahead; the packed layout makes each load instruction one
@@ -99,16 +104,18 @@ __device__ __forceinline__ uint32_t codes_to_e5m2x4(uint32_t biased, int h)
 // (App. "Input Quantization"): the weight term then runs on the 8-bit sparse instruction, 64 inputs
 // per step, on half the bytes of X; the adapter term is unchanged (its T comes from the caller's
 // fp16 copy of the quantized X).
-template <int AT, int XF = 0>
-__global__ __launch_bounds__(256, 1) void gemm_sparse_kernel(SparseGemmArgs a)
+template <int AT, int XF = 0, int KW = 1>
+__global__ __launch_bounds__(256 * KW, KW) void gemm_sparse_kernel(SparseGemmArgs a)
 {
     constexpr int WROWS = 32 * AT;       // rows per wavefront
     constexpr int NB = 4 * NT;           // (slice, token tile) blocks per stage
     constexpr int HB = NB / 2;
-    extern __shared__ __attribute__((aligned(16))) half_t lds[];   // two stage buffers
-    const int tid = threadIdx.x;
+    extern __shared__ __attribute__((aligned(16))) half_t lds_all[];   // two stage buffers per group
+    const int kg = KW > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x / 256) : 0;      // group: its share of the inputs and ranks
+    half_t *const lds = lds_all + kg * 2 * SG_STAGE;
+    const int tid = threadIdx.x & 255;
     const int lane = tid & (kWave - 1);
-    const int wave = tid / kWave;
+    const int wave = KW > 1 ? __builtin_amdgcn_readfirstlane(tid / kWave) : tid / kWave;      // (two wavefronts per SIMD: registers are short)
     const int li = lane & 31;            // A row / B token within a 32-tile
     const int lb = lane >> 5;            // k-block of the lane
 
@@ -125,21 +132,29 @@ __global__ __launch_bounds__(256, 1) void gemm_sparse_kernel(SparseGemmArgs a)
     static_for<16 * AT * NT>([&](auto r) { acc_write<r>(0.0f); });
 
     const uint32_t k = (uint32_t)a.k;
-    const int nsteps = a.k / SG_BK;
+    // stages of this group: first .. first + nsteps, of which the last may not exist (the groups' loops have the same
+    // number of barriers)
+    const int nsteps = (a.k / SG_BK + KW - 1) / KW;
+    const int first = kg * nsteps;
+    const int exist = KW > 1 ? min(nsteps, a.k / SG_BK - first) : nsteps;
 
     // this lane's piece of row tile 0, stage 0 in the packed layout (one KiB of
     // codes, 512 bytes of positions per row tile and stage); tile i and stage s are
     // uniform terms; row tiles past the end read as zero
-    const uint32_t qv = (uint32_t)(o0 / 32) * (k / 128) * 1024u + (uint32_t)(lb * 32 + li) * 16u;
-    const uint32_t mv = (uint32_t)(o0 / 32) * (k / 128) * 512u + (uint32_t)(lb * 32 + li) * 8u;
+    const uint32_t qv = ((uint32_t)(o0 / 32) * (k / 128) + (uint32_t)first) * 1024u + (uint32_t)(lb * 32 + li) * 16u;
+    const uint32_t mv = ((uint32_t)(o0 / 32) * (k / 128) + (uint32_t)first) * 512u + (uint32_t)(lb * 32 + li) * 8u;
     uint4_t qa[3][AT];
     uint2_t ma[3][AT];
 
     // X / T staging: 16 lanes per token row (256 contiguous bytes), 16 rows per pass
     const int srow = tid >> 4, scol = (tid & 15) * 8;
-    const uint32_t xv = ((uint32_t)(t0 + srow) * k + (uint32_t)scol) * 2u;
+    const uint32_t xv = ((uint32_t)(t0 + srow) * k + (uint32_t)(first * SG_BK) + (uint32_t)scol) * 2u;
     half_t *const lw = lds + srow * SG_LD + scol;
-    uint4_t xr[2][XR];
+    // X on its way to LDS: two stages ahead in two register sets; with two wavefronts per SIMD, which have half the
+    // registers and wait for one another's matrix instructions anyway, one stage ahead in one set (loaded in the first half of a
+    // stage, stored in the second)
+    constexpr int XSETS = KW > 1 ? 1 : 2;
+    uint4_t xr[XSETS][XR];
     auto stage_store = [&](int u, const uint4_t (&reg)[XR], int only = -1) {
 #pragma unroll
         for (int p = 0; p < XR; ++p)
@@ -219,10 +234,10 @@ __global__ __launch_bounds__(256, 1) void gemm_sparse_kernel(SparseGemmArgs a)
         const rsrc_t dm = make_rsrc(a.meta, (uint32_t)pk_mbytes(a.n, a.k));
         const rsrc_t dx = make_rsrc(a.X, (uint32_t)a.m * k);
         const int srow8 = tid >> 3, c16 = tid & 7;
-        const uint32_t xv8 = (uint32_t)(t0 + srow8) * k + 16u * (uint32_t)c16;
+        const uint32_t xv8 = (uint32_t)(t0 + srow8) * k + (uint32_t)(first * SG_BK) + 16u * (uint32_t)c16;
         unsigned char *const lw8 = lds8 + srow8 * F8_LD + 64 * ((c16 & 3) >> 1) + 32 * (c16 & 1) + 16 * (c16 >> 2);
         const unsigned char *const lr8 = lds8 + li * F8_LD + 32 * lb;
-        uint4_t x8[2][4];
+        uint4_t x8[XSETS][4];
         auto fetch_x8 = [&](int p, int s, uint4_t (&reg)[4]) {
             reg[p] = load16(dx, xv8, (uint32_t)s * 128u + (uint32_t)p * 32u * k);
         };
@@ -288,8 +303,10 @@ __global__ __launch_bounds__(256, 1) void gemm_sparse_kernel(SparseGemmArgs a)
         for (int p = 0; p < 4; ++p) fetch_x8(p, 0, x8[0]);
 #pragma unroll
         for (int j = 0; j < 2 * AT; ++j) fetch_a(j, 0, qa8[0], ma8[0]);
+        if constexpr (KW == 1) {
 #pragma unroll
-        for (int p = 0; p < 4; ++p) fetch_x8(p, 1, x8[1]);
+            for (int p = 0; p < 4; ++p) fetch_x8(p, 1, x8[1]);
+        }
 #pragma unroll
         for (int j = 0; j < 2 * AT; ++j) fetch_a(j, 1, qa8[1], ma8[1]);
         stage_store8(0, x8[0]);
@@ -307,9 +324,20 @@ __global__ __launch_bounds__(256, 1) void gemm_sparse_kernel(SparseGemmArgs a)
                 constexpr int u = vc % 2, w = vc % 3, w1 = (vc + 1) % 3, w2 = (vc + 2) % 3;
                 const int s = s0 + vc;
                 if (s >= nsteps) return;
-                compute_stage8(u, qa8[w], qa8[w1], ma8[w], a0, [&](auto bc) {
+                if (KW == 1 || s < exist) compute_stage8(u, qa8[w], qa8[w1], ma8[w], a0, [&](auto bc) {
                     constexpr int bi = bc;           // 0 .. 2 NT - 1
-                    if constexpr (bi < NT) {
+                    if constexpr (KW > 1) {
+                        // X of stage s + 1 in the first half, its store and the weights of stage s + 2 in the second
+                        if constexpr (bi < NT) {
+                            fetch_x8(bi, s + 1, x8[0]);
+                        } else {
+                            constexpr int per = (2 * AT + NT - 1) / NT;
+#pragma unroll
+                            for (int j = (bi - NT) * per; j < (bi - NT + 1) * per && j < 2 * AT; ++j)
+                                fetch_a(j, s + 2, qa8[w2], ma8[w2]);
+                            *reinterpret_cast<uint4_t *>(lw8 + (u ^ 1) * F8_STAGE + (bi - NT) * 32 * F8_LD) = x8[0][bi - NT];
+                        }
+                    } else if constexpr (bi < NT) {
                         constexpr int per = (2 * AT + NT - 1) / NT;      // weights of stage s + 2
 #pragma unroll
                         for (int j = bi * per; j < (bi + 1) * per && j < 2 * AT; ++j)
@@ -318,7 +346,7 @@ __global__ __launch_bounds__(256, 1) void gemm_sparse_kernel(SparseGemmArgs a)
                         fetch_x8(bi - NT, s + 2, x8[u]);                 // X of stage s + 2: four loads
                     }
                 });
-                stage_store8(u ^ 1, x8[u ^ 1]);
+                if constexpr (KW == 1) stage_store8(u ^ 1, x8[u ^ 1]);
                 __syncthreads();
             });
         }
@@ -347,8 +375,10 @@ __global__ __launch_bounds__(256, 1) void gemm_sparse_kernel(SparseGemmArgs a)
         for (int p = 0; p < XR; ++p) fetch_x(p, 0, xr[0]);
 #pragma unroll
         for (int j = 0; j < 2 * AT; ++j) fetch_a(j, 0, qa[0], ma[0]);
+        if constexpr (KW == 1) {
 #pragma unroll
-        for (int p = 0; p < XR; ++p) fetch_x(p, 1, xr[1]);
+            for (int p = 0; p < XR; ++p) fetch_x(p, 1, xr[1]);
+        }
 #pragma unroll
         for (int j = 0; j < 2 * AT; ++j) fetch_a(j, 1, qa[1], ma[1]);
         stage_store(0, xr[0]);
@@ -363,9 +393,21 @@ __global__ __launch_bounds__(256, 1) void gemm_sparse_kernel(SparseGemmArgs a)
                 constexpr int u = vc % 2, w = vc % 3, w1 = (vc + 1) % 3, w2 = (vc + 2) % 3;
                 const int s = s0 + vc;
                 if (s >= nsteps) return;
-                compute_stage(u, qa[w], qa[w1], ma[w], a_first, [&](auto bc) {
+                if (KW == 1 || s < exist) compute_stage(u, qa[w], qa[w1], ma[w], a_first, [&](auto bc) {
                     constexpr int bi = bc;
-                    if constexpr (bi < HB) {
+                    if constexpr (KW > 1) {
+                        // X of stage s + 1 in the first half, its stores and the weights of stage s + 2 in the second
+                        static_assert(XR == HB, "one piece of X per block");
+                        if constexpr (bi < HB) {
+                            fetch_x(bi, s + 1, xr[0]);
+                        } else {
+                            constexpr int per = (2 * AT + HB - 1) / HB;
+#pragma unroll
+                            for (int j = (bi - HB) * per; j < (bi - HB + 1) * per && j < 2 * AT; ++j)
+                                fetch_a(j, s + 2, qa[w2], ma[w2]);
+                            *reinterpret_cast<uint4_t *>(lw + (u ^ 1) * SG_STAGE + (bi - HB) * 16 * SG_LD) = xr[0][bi - HB];
+                        }
+                    } else if constexpr (bi < HB) {
                         constexpr int per = (2 * AT + HB - 1) / HB;      // weights of stage s + 2
 #pragma unroll
                         for (int j = bi * per; j < (bi + 1) * per && j < 2 * AT; ++j)
@@ -419,36 +461,78 @@ __global__ __launch_bounds__(256, 1) void gemm_sparse_kernel(SparseGemmArgs a)
     // tiled layout: one contiguous KiB per row tile and step
     if (a.rank_pad > 0) {
         const uint32_t rp = (uint32_t)a.rank_pad;
+        // this group's ranks: whole stages of 128
+        const int rst = ((a.rank_pad + SG_BK - 1) / SG_BK + KW - 1) / KW;
+        const int r0 = kg * rst * SG_BK;
+        const int rlen = KW > 1 ? max(0, min(rst * SG_BK, a.rank_pad - r0)) : a.rank_pad;
         const rsrc_t dl = make_rsrc(a.L, a.L ? (uint32_t)tl_bytes(a.n, a.rank_pad) : 0u);
         const rsrc_t dt = make_rsrc(a.T, (uint32_t)a.m * rp * 2u);
-        const uint32_t lv = tl_piece((uint32_t)o0 + li, lb, rp);
-        const uint32_t tv = ((uint32_t)(t0 + srow) * rp + (uint32_t)scol) * 2u;
+        const uint32_t lv = tl_piece((uint32_t)o0 + li, (uint32_t)r0 / 8u + lb, rp);
+        const uint32_t tv = ((uint32_t)(t0 + srow) * rp + (uint32_t)r0 + (uint32_t)scol) * 2u;
         if (a.Lq) {
-            const Q4Rows lq = q4_rows_operand(a.Lq, a.Ls, a.n, a.rank, o0, li, lb, 0);
-            dense_phase_q4<AT>(lq, dt, tv, 32u * rp, scol, (int)rp, lds + li * SG_LD + 32 * lb, xr[0], stage_store);
+            const Q4Rows lq = q4_rows_operand(a.Lq, a.Ls, a.n, a.rank, o0, li, lb, r0);
+            dense_phase_q4<AT, 2, (KW > 1)>(lq, dt, tv, 32u * rp, scol, rlen, lds + li * SG_LD + 32 * lb, xr[0], stage_store);
         } else {
-            dense_phase<AT>(dl, lv, (rp / 16) * 1024u, 1024u, dt, tv, 32u * rp, (int)rp, lr, xr[0], stage_store);
+            dense_phase<AT>(dl, lv, (rp / 16) * 1024u, 1024u, dt, tv, 32u * rp, rlen, lr, xr[0], stage_store);
         }
+        // a group with fewer stages still takes part in the barriers of the other
+        if (KW > 1)
+            for (int s = (rlen + SG_BK - 1) / SG_BK; s < rst; ++s) __syncthreads();
         acc_settle();
+    }
+
+    // (the places of this lane again, from the thread's number: nothing of it need stay in registers through the phases)
+    unsigned again = threadIdx.x;
+    if constexpr (KW > 1) asm volatile("" : "+v"(again));
+    const int elane = (int)again & (kWave - 1), eli = elane & 31, elb = elane >> 5;
+
+    // the groups add up: each stores half of the token tiles and leaves its part of the other half in LDS
+    float4_t *const parts = reinterpret_cast<float4_t *>(lds_all) + (size_t)wave * (AT * (NT / 2) * 4) * kWave + elane;
+    constexpr int PSTRIDE = 4 * AT * (NT / 2) * 4 * kWave;       // pieces per group
+    if constexpr (KW > 1) {
+        __syncthreads();                 // everybody has read the last stage
+        static_for<NT / 2>([&](auto hc) {
+            static_for<AT>([&](auto ic) {
+                constexpr int i = ic, h = hc;
+                static_for<4>([&](auto bc) {
+                    constexpr int blk = bc;
+                    float4_t v;
+                    if (kg == 0) {
+                        constexpr int r = 16 * (i * NT + NT / 2 + h) + 4 * blk;
+                        v = float4_t{acc_read<r>(), acc_read<r + 1>(), acc_read<r + 2>(), acc_read<r + 3>()};
+                    } else {
+                        constexpr int r = 16 * (i * NT + h) + 4 * blk;
+                        v = float4_t{acc_read<r>(), acc_read<r + 1>(), acc_read<r + 2>(), acc_read<r + 3>()};
+                    }
+                    parts[(kg ^ 1) * PSTRIDE + ((h * AT + i) * 4 + blk) * kWave] = v;
+                });
+            });
+        });
+        __syncthreads();
     }
 
     // store: lane holds token t0 + 32 it + li, rows o .. o + 3 per (i, blk)
     const bool vec_ok = (a.n & 3) == 0;
     static_for<NT>([&](auto itc) {
         constexpr int it = itc;
-        const int t = t0 + 32 * it + li;
-        if (t >= t_end) return;
+        const int t = t0 + 32 * it + eli;
+        if (t >= t_end || (KW > 1 && kg != it / (NT / 2))) return;
         static_for<AT>([&](auto ic) {
             constexpr int i = ic;
             static_for<4>([&](auto bc) {
                 constexpr int blk = bc;
-                const int o = o0 + 32 * i + 8 * blk + 4 * lb;
+                const int o = o0 + 32 * i + 8 * blk + 4 * elb;
                 if (o >= a.n) return;
                 float v[4];
                 v[0] = acc_read<16 * (i * NT + it) + 4 * blk + 0>();
                 v[1] = acc_read<16 * (i * NT + it) + 4 * blk + 1>();
                 v[2] = acc_read<16 * (i * NT + it) + 4 * blk + 2>();
                 v[3] = acc_read<16 * (i * NT + it) + 4 * blk + 3>();
+                if constexpr (KW > 1) {
+                    const float4_t p = parts[kg * PSTRIDE + (((it % (NT / 2)) * AT + i) * 4 + blk) * kWave];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) v[e] += p[e];
+                }
                 half_t *y = a.Y + (size_t)t * a.n + o;
                 if (vec_ok) {
                     half4_t h;
@@ -508,7 +592,6 @@ int launch_gemm_sparse(const uint8_t *qvals, const uint8_t *meta, const float *s
     const uint64_t row_bytes = 2ull * (uint64_t)(k > rank_pad ? k : rank_pad);
     const int chunk = (int)((0xFFFFFFFFull / row_bytes) / 128 * 128);
     if (chunk < 128) return SLIM_ERR_SHAPE;
-    const size_t lds = (size_t)2 * SG_STAGE * sizeof(half_t);
     for (int t0 = 0; t0 < m; t0 += chunk) {
         a.m = m - t0 < chunk ? m - t0 : chunk;
         a.X = reinterpret_cast<const half_t *>(reinterpret_cast<const char *>(X) + (size_t)t0 * k * xbytes);
@@ -517,13 +600,14 @@ int launch_gemm_sparse(const uint8_t *qvals, const uint8_t *meta, const float *s
         plan_tiles(a, device_info().cus);
         const int n_rem = a.rem_split * (a.tiles_total - a.n_full);
         auto launch = [&](auto atc, unsigned grid) {
-            constexpr int AT = decltype(atc)::value;
+            constexpr int AT = decltype(atc)::value, KW = AT < 4 ? 2 : 1;
+            const size_t lds = (size_t)KW * 2 * SG_STAGE * sizeof(half_t);      // (the groups' partial tiles, 64 AT KiB, fit)
             if (xf == 0)
-                hipLaunchKernelGGL((gemm_sparse_kernel<AT, 0>), dim3(grid), dim3(256), lds, st, a);
+                hipLaunchKernelGGL((gemm_sparse_kernel<AT, 0, KW>), dim3(grid), dim3(256 * KW), lds, st, a);
             else if (xf == 1)
-                hipLaunchKernelGGL((gemm_sparse_kernel<AT, 1>), dim3(grid), dim3(256), lds, st, a);
+                hipLaunchKernelGGL((gemm_sparse_kernel<AT, 1, KW>), dim3(grid), dim3(256 * KW), lds, st, a);
             else
-                hipLaunchKernelGGL((gemm_sparse_kernel<AT, 2>), dim3(grid), dim3(256), lds, st, a);
+                hipLaunchKernelGGL((gemm_sparse_kernel<AT, 2, KW>), dim3(grid), dim3(256 * KW), lds, st, a);
         };
         if (a.n_full > 0) launch(std::integral_constant<int, 4>{}, (unsigned)a.n_full);
         if (n_rem > 0 && a.rem_split == 2) launch(std::integral_constant<int, 2>{}, (unsigned)n_rem);

@@ -238,8 +238,9 @@ __device__ __forceinline__ Q4Rows q4_rows_operand(const uint8_t *codes, const ha
 //      (lrq: this lane's token row at column 32 lb), one step ahead; a sum over the inputs does
 //      not care.  A partly valid stage runs whole groups of four steps: bcol = first column of the
 //      lane's share of a B stage, whose columns past K are replaced by zeros on their way into LDS.
+// LEAN: B fragments one block ahead instead of one step (12 registers fewer; for two wavefronts per SIMD).
 // Starts and ends with every wavefront past a barrier.
-template <int AT, int BB = 2, class Store>
+template <int AT, int BB = 2, bool LEAN = false, class Store>
 __device__ __forceinline__ void dense_phase_q4(const Q4Rows &qa, rsrc_t db, uint32_t bv, uint32_t b_pass, int bcol,
                                                int K, const half_t *lrq, uint4_t (&xs)[XR * BB / 2],
                                                Store &&stage_store)
@@ -282,9 +283,13 @@ __device__ __forceinline__ void dense_phase_q4(const Q4Rows &qa, rsrc_t db, uint
     for (int s = 0; s < stages; ++s) {
         const int u = s & 1;
         const int jn = min(8, 4 * ((K - SG_BK * s + 63) / 64));       // steps in this stage
-        half8_t b_cur[NT], b_nxt[NT];
+        half8_t b_cur[NT], b_nxt[LEAN ? 1 : NT];
+        if constexpr (LEAN) {
+            b_nxt[0] = read_b(u, 0, 0);
+        } else {
 #pragma unroll
-        for (int it = 0; it < NT; ++it) b_cur[it] = read_b(u, it, 0);
+            for (int it = 0; it < NT; ++it) b_cur[it] = read_b(u, it, 0);
+        }
         static_for<8>([&](auto jc) {
             constexpr int jj = jc;
             if (jj >= jn) return;
@@ -297,7 +302,15 @@ __device__ __forceinline__ void dense_phase_q4(const Q4Rows &qa, rsrc_t db, uint
                 if constexpr (jj < 4 && it < XRN / 4)
                     xs[(XRN / 4) * jj + it] =
                         load16(db, bv, (uint32_t)(s + 1) * (SG_BK * BB) + (uint32_t)((XRN / 4) * jj + it) * b_pass);
-                if constexpr (jj + 1 < 8) b_nxt[it] = read_b(u, it, jj + 1);
+                if constexpr (LEAN) {
+                    b_cur[it] = b_nxt[0];
+                    if constexpr (it + 1 < NT)
+                        b_nxt[0] = read_b(u, it + 1, jj);
+                    else if constexpr (jj + 1 < 8)
+                        b_nxt[0] = read_b(u, 0, jj + 1);
+                } else if constexpr (jj + 1 < 8) {
+                    b_nxt[it] = read_b(u, it, jj + 1);
+                }
                 if constexpr (jj >= 4 && it < XRN / 4) {
                     constexpr int p = (XRN / 4) * (jj - 4) + it;
                     if (s + 1 < stages) {
@@ -320,8 +333,10 @@ __device__ __forceinline__ void dense_phase_q4(const Q4Rows &qa, rsrc_t db, uint
                     __builtin_amdgcn_sched_barrier(0);
                 });
             });
+            if constexpr (!LEAN) {
 #pragma unroll
-            for (int it = 0; it < NT; ++it) b_cur[it] = b_nxt[it];
+                for (int it = 0; it < NT; ++it) b_cur[it] = b_nxt[it];
+            }
 #pragma unroll
             for (int i = 0; i < AT; ++i) a_cur[i] = a_nxt[i];
         });

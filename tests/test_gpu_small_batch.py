@@ -129,3 +129,11 @@ def test_large_tiles_every_stage_count_modulo_six(stages, fp8):
     else:
         err = _forward_case(_shape(n, k, r), m, B.slim_linear_gemm, seed=stages)
     assert err <= TOL_Y
+
+
+@pytest.mark.parametrize("n,k,r,m", [(1, 128, 0, 513), (33, 256, 31, 530), (100, 384, 33, 600), (129, 640, 129, 530), (1000, 1152, 300, 540)])
+@pytest.mark.parametrize("bits", [16, 4])
+def test_large_tiles_with_inputs_divided(n, k, r, m, bits):
+    """Tiles of 128 to 384 rows: two groups of wavefronts take every other stage and unit of ranks; one stage (the
+    second group has none), odd counts, fewer ranks than a unit."""
+    assert _forward_case(_shape(n, k, r), m, B.slim_linear_gemm, seed=28, bits=bits) <= TOL_Y
