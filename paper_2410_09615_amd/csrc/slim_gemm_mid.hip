@@ -41,7 +41,8 @@ struct MidArgs {
     const half_t *R, *L;  // fp16 adapters in the adapter layout, or null with the 4-bit form:
     const uint8_t *Rq, *Lq;
     const half_t *Rs, *Ls;
-    uint4_t *T;           // pieces of T (mid_t_piece())
+    uint4_t *T;           // pieces of T (mid_t_piece()), or null with
+    half_t *T_rows;       //   fp16 [m][rank_pad] (the T role alone)
     unsigned *err;        // set to 1 when a wait gave up
     CallEpoch epoch;
     half_t *Y;            // [m][n]
@@ -216,9 +217,253 @@ __device__ __forceinline__ void t_tile(const MidArgs &a, int rt, int tt, char *l
         for (int w = 0; w < kMidWaves + kMidHelpers - 1; ++w) acc += *reinterpret_cast<const float4_t *>(red + (w * kWave + lane) * 4);
         if (XF) acc *= *a.x_scale;
         const half4_t h = {(half_t)acc[0], (half_t)acc[1], (half_t)acc[2], (half_t)acc[3]};
+        if (a.T_rows) {
+            if (tok < a.m) *reinterpret_cast<half4_t *>(a.T_rows + (size_t)tok * a.rank_pad + 16 * rt + 4 * ly) = h;
+            return;
+        }
         store_piece(make_rsrc(a.T, mid_t_bytes<AQ>(a.m, a.rank_pad)), mid_t_piece<AQ>((uint32_t)tok, 16u * rt + 4u * ly, a.rank_pad),
                     epoch, __builtin_bit_cast(uint2_t, h));
     }
+}
+
+// ---- T = X R^T as a launch of its own: larger tiles, for batches that fill the chip with them ----
+// Tile of 32 RT ranks x 32 TT tokens per workgroup; the twelve wavefronts divide the inputs in units of 128 / TT, each the
+// whole tile on its units with V_MFMA_F32_32X32X16_F16 (R from memory into registers, X through 8 KiB of LDS
+// of its own, no barrier on the way), and add up in LDS.  What bounds it is the 64 bytes a compute unit
+// draws per clock from its L2: (32 RT + 32 TT) x 2 bytes of them per input, which is why the tile grows
+// with the batch.  A product split over workgroups instead, with fp32 partial sums in memory, took another
+// launch and 8 us to add them up.
+//   Whole calls, against that: 8192 x 8192 at 1000 tokens 125.0 -> 117.4 us, 11008 x 4096 at 333 tokens 55.2 -> 45.2.
+// Columns of a unit that step j multiplies on lane half h:
+//   fp16 R, fp16 X   16 j + 8 h + [0, 8)
+//   fp16 R, 8-bit X  32 (j / 2) + 16 h + 8 (j % 2) + [0, 8): two steps share one piece of codes
+//   4-bit R          64 (j / 4) + 32 h + 8 (j % 4) + [0, 8): four steps share one 16-byte load of codes, one scale
+struct TArgs {
+    const half_t *X;
+    const float *x_scale;
+    const half_t *R;
+    const uint8_t *Rq;
+    const half_t *Rs;
+    int k, rank, rank_pad, m;
+    int tiles_t, tiles_r;    // token tiles, rank tiles
+    half_t *T;               // fp16 [m][rank_pad], or
+    uint4_t *pieces;         // pieces of T (mid_t_piece()) with this call's number
+    bool q4_order;           //   in the order for 4-bit L
+    CallEpoch epoch;
+};
+
+template <int RT, int TT, int XF, bool AQ>
+__global__ __launch_bounds__(kMidThreads, 3) void t_product_kernel(TArgs a)
+{
+    constexpr int TW = kMidWaves + kMidHelpers;
+    constexpr int U = 128 / TT, STEPS = U / 16;          // inputs and steps of a unit
+    constexpr int ROWB = XF ? U : 2 * U;                 // bytes of a token's unit
+    constexpr int P = ROWB / 16, RPB = 16 / P;           // pieces of 16 bytes per row, rows per 256 bytes
+    constexpr int TPI = 64 / P, NX = 32 * TT / TPI;      // tokens per load instruction, instructions per unit
+    extern __shared__ __attribute__((aligned(16))) char lds_c[];
+    const int lane = threadIdx.x & (kWave - 1), li = lane & 31, lb = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    // the tiles of one token tile run on one die, whose L2 then reads X once (R, the smaller operand, is read by every die)
+    int rt, tt;
+    if (!tile_on_die((int)blockIdx.x, a.tiles_t, tt, rt)) return;
+    const int t0 = tt * 32 * TT, r0 = rt * 32 * RT;
+    const uint32_t k = (uint32_t)a.k, xb = XF ? 1u : 2u;
+    const rsrc_t x_rs = make_rsrc(a.X, (uint32_t)a.m * k * xb);
+    const rsrc_t r_rs = AQ ? make_rsrc(a.Rq, (uint32_t)q4_code_bytes(a.rank, a.k)) : make_rsrc(a.R, (uint32_t)tl_bytes(a.rank_pad, a.k));
+    const rsrc_t s_rs = make_rsrc(AQ ? a.Rs : nullptr, AQ ? (uint32_t)q4_scale_bytes(a.rank, a.k) : 0u);
+    const uint32_t x_lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)lds_c + (uint32_t)(wave * kTUnitLds);
+    const char *const xl = lds_c + wave * kTUnitLds + li * ROWB;
+    const int units = (a.k + U - 1) / U;                 // (k is a multiple of 128)
+    // loads of X: lane -> (token, slot piece), source piece = slot piece ^ swizzle(token)
+    const int stok = lane / P;
+    const uint32_t xoff = (uint32_t)(t0 + stok) * k * xb;
+    auto swz = [](int tok) { return (uint32_t)((tok / RPB) & (P - 1)); };
+    auto col = [&](int j) -> uint32_t {
+        if (AQ) return 64u * (j >> 2) + 32u * lb + 8u * (j & 3);
+        if (XF) return 32u * (j >> 1) + 16u * lb + 8u * (j & 1);
+        return 16u * j + 8u * lb;
+    };
+    float16_t acc[RT][TT];
+#pragma unroll
+    for (int i = 0; i < RT; ++i)
+#pragma unroll
+        for (int it = 0; it < TT; ++it)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) acc[i][it][e] = 0.f;
+    for (int u = wave; u < units; u += TW) {
+#pragma unroll
+        for (int q = 0; q < NX; ++q) {
+            const int tok = TPI * q + stok;
+            load_to_lds(x_rs, xoff + (uint32_t)(TPI * q) * k * xb + (((uint32_t)(lane % P) ^ swz(tok)) << 4), (uint32_t)(u * U) * xb, x_lds + (uint32_t)q * 1024u);
+        }
+        uint4_t rv[RT][AQ ? STEPS / 4 : STEPS];
+        half_t sc[RT];
+#pragma unroll
+        for (int i = 0; i < RT; ++i) {
+            const uint32_t row = (uint32_t)(r0 + 32 * i + li);
+            if constexpr (AQ) {
+#pragma unroll
+                for (int q = 0; q < STEPS / 4; ++q)
+                    rv[i][q] = load16(r_rs, q4_piece(row, (uint32_t)(u * U) / 64u + q, q4_ctiles(a.k)) + 16u * lb, 0);
+                sc[i] = load_half(s_rs, (row * q4_groups(a.k) + (uint32_t)(u * U) / 128u) * 2u, 0);
+            } else {
+#pragma unroll
+                for (int j = 0; j < STEPS; ++j) rv[i][j] = load16(r_rs, tl_piece(row, ((uint32_t)(u * U) + col(j)) >> 3, k), 0);
+            }
+        }
+        asm volatile("s_waitcnt vmcnt(0)" : : : "memory");
+#pragma unroll
+        for (int j = 0; j < STEPS; ++j) {
+            half8_t av[RT], bv[TT];
+            const uint32_t piece = XF ? col(j) >> 4 : col(j) >> 3;
+#pragma unroll
+            for (int it = 0; it < TT; ++it) {
+                const uint4_t v = *reinterpret_cast<const uint4_t *>(xl + it * 32 * ROWB + ((piece ^ swz(li)) << 4));
+                if constexpr (XF == 0)
+                    bv[it] = __builtin_bit_cast(half8_t, v);
+                else
+                    bv[it] = codes8_to_half8<XF>(v[2 * (j & 1)], v[2 * (j & 1) + 1]);
+            }
+#pragma unroll
+            for (int i = 0; i < RT; ++i) {
+                if constexpr (AQ)
+                    av[i] = codes_to_half8(rv[i][j >> 2][j & 3]) * sc[i];
+                else
+                    av[i] = __builtin_bit_cast(half8_t, rv[i][j]);
+            }
+#pragma unroll
+            for (int i = 0; i < RT; ++i)
+#pragma unroll
+                for (int it = 0; it < TT; ++it) acc[i][it] = __builtin_amdgcn_mfma_f32_32x32x16_f16(av[i], bv[it], acc[i][it], 0, 0, 0);
+        }
+        asm volatile("s_waitcnt lgkmcnt(0)" : : : "memory");     // the unit's LDS has been read
+    }
+    // add up: the upper six wavefronts to the lower six, then all of those by (tile, block of 8 rows)
+    constexpr int TILES = RT * TT, HALF = TW / 2;
+    float4_t *const red = reinterpret_cast<float4_t *>(lds_c);
+    auto put = [&](int w) {
+#pragma unroll
+        for (int x = 0; x < TILES; ++x)
+#pragma unroll
+            for (int b = 0; b < 4; ++b) {
+                const float16_t &v = acc[x / TT][x % TT];
+                red[((w * TILES + x) * 4 + b) * kWave + lane] = float4_t{v[4 * b], v[4 * b + 1], v[4 * b + 2], v[4 * b + 3]};
+            }
+    };
+    __syncthreads();
+    if (wave >= HALF) put(wave - HALF);
+    __syncthreads();
+    if (wave < HALF) {
+#pragma unroll
+        for (int x = 0; x < TILES; ++x)
+#pragma unroll
+            for (int b = 0; b < 4; ++b) {
+                const float4_t v = red[((wave * TILES + x) * 4 + b) * kWave + lane];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) acc[x / TT][x % TT][4 * b + e] += v[e];
+            }
+        put(wave);                               // (its own place, which only it has read)
+    }
+    __syncthreads();
+    const float xs = XF ? *a.x_scale : 1.0f;
+    const unsigned epoch = a.pieces ? call_epoch(a.epoch) : 0u;
+    for (int q = wave; q < 4 * TILES; q += TW) {
+        const int x = q >> 2, b = q & 3;
+        float4_t v = red[(x * 4 + b) * kWave + lane];
+#pragma unroll
+        for (int w = 1; w < HALF; ++w) v += red[((w * TILES + x) * 4 + b) * kWave + lane];
+        if (XF) v *= xs;
+        const half4_t h = {(half_t)v[0], (half_t)v[1], (half_t)v[2], (half_t)v[3]};
+        // lane holds token t, ranks r .. r + 3
+        const int t = t0 + 32 * (x % TT) + li, r = r0 + 32 * (x / TT) + 8 * b + 4 * lb;
+        if (r >= a.rank_pad) continue;
+        if (a.pieces) {
+            const rsrc_t p_rs = make_rsrc(a.pieces, a.q4_order ? mid_t_bytes<true>(a.m, a.rank_pad) : mid_t_bytes<false>(a.m, a.rank_pad));
+            const uint32_t off = a.q4_order ? mid_t_piece<true>((uint32_t)t, (uint32_t)r, a.rank_pad) : mid_t_piece<false>((uint32_t)t, (uint32_t)r, a.rank_pad);
+            store_piece(p_rs, t < (a.m + 31) / 32 * 32 ? off : kPastEnd, epoch, __builtin_bit_cast(uint2_t, h));
+        } else if (t < a.m) {
+            *reinterpret_cast<half4_t *>(a.T + (size_t)t * a.rank_pad + r) = h;
+        }
+    }
+}
+
+template <int RT, int TT>
+static void launch_t_tiles(TArgs a, int xf, hipStream_t st)
+{
+    a.tiles_t = (a.m + 32 * TT - 1) / (32 * TT);
+    a.tiles_r = (a.rank_pad + 32 * RT - 1) / (32 * RT);
+    const dim3 grid((unsigned)die_tiles(a.tiles_t, a.tiles_r)), blk(kMidThreads);
+    constexpr size_t lds = (size_t)(kMidWaves + kMidHelpers) * kTUnitLds;        // the partial tiles, 24 RT TT KiB, fit
+    static_assert((kMidWaves + kMidHelpers) / 2 * RT * TT * 4096 <= (kMidWaves + kMidHelpers) * kTUnitLds, "partial tiles");
+    if (a.Rq) {
+        if (xf == 0)
+            hipLaunchKernelGGL((t_product_kernel<RT, TT, 0, true>), grid, blk, lds, st, a);
+        else if (xf == 1)
+            hipLaunchKernelGGL((t_product_kernel<RT, TT, 1, true>), grid, blk, lds, st, a);
+        else
+            hipLaunchKernelGGL((t_product_kernel<RT, TT, 2, true>), grid, blk, lds, st, a);
+    } else {
+        if (xf == 0)
+            hipLaunchKernelGGL((t_product_kernel<RT, TT, 0, false>), grid, blk, lds, st, a);
+        else if (xf == 1)
+            hipLaunchKernelGGL((t_product_kernel<RT, TT, 1, false>), grid, blk, lds, st, a);
+        else
+            hipLaunchKernelGGL((t_product_kernel<RT, TT, 2, false>), grid, blk, lds, st, a);
+    }
+}
+
+static int t_shape(int rank_pad, int m);
+static void launch_t_role(const TArgs &a, int xf, hipStream_t st);
+static int launch_t_product_args(const TArgs &a, int xf, hipStream_t st)
+{
+    switch (t_shape(a.rank_pad, a.m)) {
+        case 3: launch_t_role(a, xf, st); break;
+        case 0: launch_t_tiles<1, 1>(a, xf, st); break;
+        case 1: launch_t_tiles<1, 2>(a, xf, st); break;
+        default: launch_t_tiles<2, 2>(a, xf, st); break;
+    }
+    return hip_status(hipGetLastError());
+}
+
+// T fp16 [m][rank_pad] = X R^T.  xf: 0 = X fp16; 1, 2 = X as E4M3 / E5M2 codes with the tensor's scale at x_scale.
+// R: fp16 in the adapter layout, or null with Rq / Rs: the 4-bit codes and scales of R [rank][k].  The caller keeps the
+// operands below 4 GiB each.
+int launch_t_product(const half_t *X, int xf, const float *x_scale, int m, int k, const half_t *R, const uint8_t *Rq, const half_t *Rs, int rank,
+                     int rank_pad, half_t *T, hipStream_t st)
+{
+    TArgs a{};
+    a.X = X;
+    a.x_scale = x_scale;
+    a.R = R;
+    a.Rq = R ? nullptr : Rq;
+    a.Rs = Rs;
+    a.k = k;
+    a.rank = rank;
+    a.rank_pad = rank_pad;
+    a.m = m;
+    a.T = T;
+    return launch_t_product_args(a, xf, st);
+}
+
+// 0, 1, 2: t_product_kernel's tiles of 32 x 32, 32 x 64, 64 x 64; 3: those of 16 x 16 of the T role above.
+// The smallest tile with which the product is one round of workgroups: a small tile shortens a workgroup's chain, a
+// second round doubles it (m = 333, rank 416, whole call on 11008 x 4096: 45.2 / 46.9 / 50.8 us with tiles of
+// 32 x 32, 32 x 64, 64 x 64; m = 700 with 8-bit inputs on 2100 x 4096: 43.9 / 40.6 / 45.6; m = 1000, rank 832
+// on 8192 x 8192: 137.8 / 126.5 / 117.4).
+static int t_shape(int rank_pad, int m)
+{
+    const long ranks32 = rank_pad / 32, tokens32 = (m + 31) / 32, cus = device_info().cus;
+    if (2 * ranks32 * ((m + 15) / 16) <= cus) return 3;
+    if (ranks32 * tokens32 <= cus) return 0;
+    return ranks32 * ((tokens32 + 1) / 2) <= cus ? 1 : 2;
+}
+
+// Whether t_product_kernel makes T for the large tiles, or the split product of slim_gemm.hip: up to two rounds of
+// its largest tile (m = 4096, rank 512, k = 5120: 181.5 against 184.0 us for the call; rank 832, k = 8192: 417
+// against 387).
+bool t_in_one_launch(int rank_pad, int m)
+{
+    return (long)((rank_pad + 63) / 64) * ((m + 63) / 64) <= 2L * device_info().cus;
 }
 
 // Geometry of mid_kernel: the LDS of a round of X (shared) and of a round of weights (private to the wavefronts),
@@ -259,7 +504,7 @@ __global__ __launch_bounds__(kMidThreads, 3) void mid_kernel(MidArgs a)
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int li = lane & 31, lb = lane >> 5;
     const int rg = wave % RG, kw = wave / RG;
-    const unsigned epoch = a.rank_pad > 0 ? call_epoch(a.epoch) : 0u;
+    const unsigned epoch = a.rank_pad > 0 && a.T ? call_epoch(a.epoch) : 0u;
     if ((int)blockIdx.x < a.n_t) {
         for (int j = blockIdx.x; j < a.t_tiles; j += a.n_t) {
             int rt, tr;
@@ -657,24 +902,81 @@ __global__ __launch_bounds__(kMidThreads, 3) void mid_kernel(MidArgs a)
     }
 }
 
+// The T role of mid_kernel in a launch of its own.
+template <int XF, bool AQ>
+static void launch_t_role_of(const TArgs &t, hipStream_t st)
+{
+    MidArgs a{};
+    a.X = t.X;
+    a.x_scale = t.x_scale;
+    a.R = t.R;
+    a.Rq = t.Rq;
+    a.Rs = t.Rs;
+    a.T = t.pieces;
+    a.T_rows = t.T;
+    a.epoch = t.epoch;
+    a.k = t.k;
+    a.rank = t.rank;
+    a.rank_pad = t.rank_pad;
+    a.m = t.m;
+    a.n_t = a.t_tiles = die_tiles(t.rank_pad / 16, (t.m + 15) / 16);
+    constexpr size_t lds = MidLds<1, 1, 1, 8, XF>::TROLE;
+    hipLaunchKernelGGL((mid_kernel<1, 1, 1, 8, XF, AQ>), dim3((unsigned)a.n_t), dim3(kMidThreads), lds, st, a);
+}
+static void launch_t_role(const TArgs &t, int xf, hipStream_t st)
+{
+    if (t.Rq) {
+        if (xf == 0)
+            launch_t_role_of<0, true>(t, st);
+        else if (xf == 1)
+            launch_t_role_of<1, true>(t, st);
+        else
+            launch_t_role_of<2, true>(t, st);
+    } else {
+        if (xf == 0)
+            launch_t_role_of<0, false>(t, st);
+        else if (xf == 1)
+            launch_t_role_of<1, false>(t, st);
+        else
+            launch_t_role_of<2, false>(t, st);
+    }
+}
+
+// Workgroups of the T role where both roles share a launch: what n_y workgroups of the Y role (one per compute unit)
+// leave free, if that makes T in at most `trips` tiles each; 0: T gets a launch of its own.
+static int t_workgroups(int t_tiles, int n_y, int cus, int trips)
+{
+    const int spare = (cus - n_y) / kDies * kDies;
+    const int n_t = t_tiles < spare ? t_tiles : spare;
+    return n_t > 0 && t_tiles <= trips * n_t ? n_t : 0;
+}
+
 template <int NT_, int RT, int RG, int KW, int XF, bool AQ>
 static int launch_mid(MidArgs a, bool wait_test, hipStream_t st)
 {
-    constexpr size_t lds = MidLds<NT_, RT, RG, KW, XF>::BYTES, lds_t = MidLds<NT_, RT, RG, KW, XF>::TROLE;
+    constexpr size_t lds = MidLds<NT_, RT, RG, KW, XF>::BYTES;
     a.tiles_o = (a.n + 32 * RT * RG - 1) / (32 * RT * RG);
     const int n_y = die_tiles(a.tiles_o, (a.m + 32 * NT_ - 1) / (32 * NT_));
     a.t_tiles = die_tiles(a.rank_pad / 16, (a.m + 15) / 16);
-    // what the Y role leaves free of the workgroups that are resident at once is for the T role
-    const int spare = (device_info().cus - n_y) / kDies * kDies;
-    int n_t = a.t_tiles < spare ? a.t_tiles : (spare > 0 ? spare : 0);
-    const bool one_launch = n_t > 0 && (a.t_tiles + n_t - 1) / n_t <= 4;
+    int n_t = t_workgroups(a.t_tiles, n_y, device_info().cus, 2);
     if (wait_test) {
         n_t = 0;                             // nobody makes T
-    } else if (a.t_tiles > 0 && !one_launch) {
-        MidArgs t = a;
-        t.n_t = a.t_tiles;
-        hipLaunchKernelGGL((mid_kernel<NT_, RT, RG, KW, XF, AQ>), dim3((unsigned)a.t_tiles), dim3(kMidThreads), lds_t, st, t);
-        n_t = 0;
+    } else if (a.t_tiles > 0 && n_t == 0) {
+        TArgs t{};
+        t.X = a.X;
+        t.x_scale = a.x_scale;
+        t.R = AQ ? nullptr : a.R;
+        t.Rq = AQ ? a.Rq : nullptr;
+        t.Rs = a.Rs;
+        t.k = a.k;
+        t.rank = a.rank;
+        t.rank_pad = a.rank_pad;
+        t.m = a.m;
+        t.pieces = a.T;
+        t.q4_order = AQ;
+        t.epoch = a.epoch;
+        const int rc = launch_t_product_args(t, XF, st);
+        if (rc != SLIM_OK) return rc;
     }
     a.n_t = n_t;
     hipLaunchKernelGGL((mid_kernel<NT_, RT, RG, KW, XF, AQ>), dim3((unsigned)(n_t + n_y)), dim3(kMidThreads), lds, st, a);
@@ -684,22 +986,35 @@ static int launch_mid(MidArgs a, bool wait_test, hipStream_t st)
 // The geometries, by growing tile: rows x tokens.
 constexpr int kMidTiles[4][2] = {{32, 32}, {64, 32}, {128, 32}, {128, 64}};
 
-// Which geometry, by the sizes alone (index into kMidTiles), or -1: the tiles of slim_gemm_sparse.hip.
-// The smallest tile that gives every compute unit at most one workgroup: a second workgroup on a unit doubles
-// the time of a call that is a chain of latencies, a smaller tile shortens the chain (4096 x 4096, r = 409, 64
-// tokens: 14.6 / 10.4 / 13.7 / 20.5 us with 256 / 128 / 64 / 32 workgroups' worth of tiles in that order, the 512 x 128
-// tiles 39.6).  Two workgroups per unit still pay on short rows, where the other path is all launches
-// (11008 x 2048 at 256 tokens 28.9 against 32.4 us; 28672 x 4096 at 128 tokens 50.3 against 47.1).
+// Which geometry, by the sizes alone (index into kMidTiles), or -1: the tiles of slim_gemm_sparse.hip (or, for the
+// adapter term alone, the dense product).
+// The smallest tile that gives every compute unit at most one workgroup and leaves room to make T in the same launch,
+// else the smallest that gives at most one: a second workgroup on a unit doubles the time of a call that is a
+// chain of latencies, a smaller tile shortens the chain.  4096 x 4096, r = 409: 64 tokens 14.6 / 10.4 / 13.7 / 20.5 us
+// (256 / 128 / 64 / 32 workgroups, in the order of kMidTiles; the 512 x 128 tiles 29), 128 tokens 23.2 / 16.8 /
+// 14.5 / 20.4 (31), 512 tokens 76 / 46 / 37 / 31 (36).  Where no tile fits, the large ones win: 11008 x 4096 at 256
+// tokens 36.6 against 49.7.
+// The adapter term alone has nothing to hide a chain of T behind: 4096 x 4096 at 128 tokens 15.7 / 12.5 / 15.2 / 20.1
+// against 14.1 of the dense product, 28672 x 4096 at 48 tokens 20.2 at best against 13.6.
 // Above 512 tokens the workspace has no room for the pieces of T.
-static int mid_geometry(int n, int k, int m, int cus)
+static int mid_geometry(int n, int rank_pad, int m, int cus, bool weight_term)
 {
     if (m > 512) return -1;
-    auto workgroups = [&](int g) {
-        return die_tiles((n + kMidTiles[g][0] - 1) / kMidTiles[g][0], (m + kMidTiles[g][1] - 1) / kMidTiles[g][1]);
-    };
-    for (int g = 0; g < 4; ++g)
-        if (workgroups(g) <= cus) return g;
-    return k <= 2048 && workgroups(3) <= 2 * cus ? 3 : -1;
+    const int t_tiles = die_tiles(rank_pad / 16, (m + 15) / 16);
+    int first = -1;
+    for (int g = 0; g < 4; ++g) {
+        const int n_y = die_tiles((n + kMidTiles[g][0] - 1) / kMidTiles[g][0], (m + kMidTiles[g][1] - 1) / kMidTiles[g][1]);
+        if (n_y > cus) continue;
+        if (t_tiles == 0) return g;
+        if (!weight_term) {
+            if (g < 3 && n < 16384) return g;
+            if (t_workgroups(t_tiles, n_y, cus, 1) > 0) return g;
+            continue;
+        }
+        if (t_workgroups(t_tiles, n_y, cus, 2) > 0) return g;
+        if (first < 0) first = g;
+    }
+    return first;
 }
 
 template <int XF, bool AQ>
@@ -721,7 +1036,7 @@ int launch_gemm_mid(const slim_layer *layer, const half_t *X, int xf, const floa
     *taken = false;
     const slim_shape s = layer->shape;
     const bool q4 = layer->adapter_bits == 4 && s.rank > 0;
-    const int geometry = mid_geometry(s.n, s.k, m, device_info().cus);
+    const int geometry = mid_geometry(s.n, layer->rank_pad, m, device_info().cus, weight_term);
     if (geometry < 0) return SLIM_OK;
     // 32-bit offsets, tiles past the end included; room for the pieces of T
     constexpr uint64_t kLimit = 0x80000000ull;

@@ -131,6 +131,25 @@ def test_large_tiles_every_stage_count_modulo_six(stages, fp8):
     assert err <= TOL_Y
 
 
+# T = X R^T in one launch: as fp16 rows for the 512 x 128 tiles (m > 512) and as pieces (n = 4096: no unit is left for the
+# T role), tiles of 16 x 16, 32 x 32, 32 x 64 and 64 x 64 in turn, the last tile of tokens and of ranks partly empty,
+# fewer units of inputs than wavefronts and more; the last case is the split product's.
+T_CASES = [(200, 384, 51, 530), (200, 1792, 200, 530), (200, 256, 510, 545), (200, 128, 992, 577), (200, 1664, 970, 530),
+           (4096, 640, 51, 500), (4096, 384, 200, 499), (4096, 256, 530, 481), (4096, 1664, 1100, 500),
+           (130, 128, 1024, 2100)]
+
+
+@pytest.mark.parametrize("kind", ["fp16", "q4", "fp8", "fp8_q4"])
+@pytest.mark.parametrize("n,k,r,m", T_CASES)
+def test_t_in_one_launch(n, k, r, m, kind):
+    bits = 4 if kind.endswith("q4") else 16
+    if kind.startswith("fp8"):
+        err, _ = _fp8_forward_case(n, k, r, m, seed=27, bits=bits)
+    else:
+        err = _forward_case(_shape(n, k, r), m, B.slim_linear_gemm, seed=27, bits=bits)
+    assert err <= TOL_Y
+
+
 @pytest.mark.parametrize("n,k,r,m", [(1, 128, 0, 513), (33, 256, 31, 530), (100, 384, 33, 600), (129, 640, 129, 530), (1000, 1152, 300, 540)])
 @pytest.mark.parametrize("bits", [16, 4])
 def test_large_tiles_with_inputs_divided(n, k, r, m, bits):
