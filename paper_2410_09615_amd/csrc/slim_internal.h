@@ -161,8 +161,10 @@ __device__ __forceinline__ half_t load_half(rsrc_t r, uint32_t lane_off, uint32_
 
 #endif
 
-// A block of columns of the adapter computation (magnitudes up to 1) as two fp16 numbers: v = (hi + lo) / kBlockSplit.
-constexpr float kBlockSplit = 4096.0f;
+// A block of columns of the adapter computation as two fp16 numbers: v = (hi + lo) / kBlockSplit, exact to 2^-22 of v or
+// 2^-31.  Columns are of unit length, but for what rounding leaves of dependent ones, which may be longer (some tens
+// with pivots near the floor of the factorisation): magnitudes beyond 1015 saturate.
+constexpr float kBlockSplit = 64.0f;
 
 // What the planners need to know of the device that is current: compute units and LDS bytes per compute
 // unit, read once per device from its properties (the nominal MI355X figures, 256 and 160 KiB, where no

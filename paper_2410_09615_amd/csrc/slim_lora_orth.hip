@@ -17,8 +17,9 @@
 // apply 20) where it was 700.
 //
 // A pivot below 1e-9 of the largest diagonal entry of G marks a column that lies in the span of the ones before it
-// (or a padding column of zeros): it gets pivot 1 and a zero column, so the block carries a (numerically)
-// zero column there.
+// (or a padding column of zeros): it gets pivot 1 and no column is subtracted for it, so the block carries what is
+// left of it, a (numerically) zero column if `in` is of order one.  (Where 1e-9 of that entry is more than 1, the pivot is
+// that: what is left stays within the range of the split into fp16 numbers.)
 #include <utility>
 
 #include "slim_internal.h"
@@ -149,7 +150,7 @@ __device__ __forceinline__ void for_each(F &&f)
 // 16 x 16: lane i of sixteen holds row i of the symmetric block a = Lc Lc^T; x: row i of Lc^-1.  The steps run on
 // a = M diag(d) M^T, M with a unit diagonal, whose chain has a reciprocal and no square root, and the rows of M^-1 are
 // scaled by 1 / sqrt(d) at the end; they broadcast across the sixteen lanes without LDS or barriers.
-__device__ __forceinline__ void factor16(float (&a)[16], float (&x)[16], int i, float floor_)
+__device__ __forceinline__ void factor16(float (&a)[16], float (&x)[16], int i, float floor_, float dead)
 {
 #pragma unroll
     for (int c = 0; c < 16; ++c) x[c] = i == c ? 1.0f : 0.f;
@@ -157,8 +158,8 @@ __device__ __forceinline__ void factor16(float (&a)[16], float (&x)[16], int i, 
     for_each<16>([&](auto cc) {
         constexpr int c = cc;
         const float d = row_lane<c>(a[c]);
-        const bool ok = d > floor_;              // no: a column in the span of the ones before it: pivot 1, nothing to subtract
-        if (i == c) mine = ok ? d : 1.0f;
+        const bool ok = d > floor_;              // no: a column in the span of the ones before it: pivot `dead`, nothing to subtract
+        if (i == c) mine = ok ? d : dead;
         float q = __builtin_amdgcn_rcpf(d);
         q = q * (2.0f - d * q);                  // to rounding
         const float m = ok && i > c ? -a[c] * q : 0.f;
@@ -291,7 +292,7 @@ __global__ __launch_bounds__(256) void lora_chol_kernel(int j, int nb, int l, co
 #pragma unroll
                 for (int e = 0; e < 4; ++e) a[4 * q + e] = v[e];
             }
-            factor16(a, x, ln, floor_);
+            factor16(a, x, ln, floor_, fmaxf(1.0f, floor_));
             if (lane < 16) {
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
@@ -414,7 +415,7 @@ __global__ __launch_bounds__(256) void lora_apply_kernel(const float *__restrict
             half8_t h[2], g[2];
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
-                const float v = O[r * ldo + c] * kBlockSplit;
+                const float s = O[r * ldo + c] * kBlockSplit, v = fabsf(s) > 65000.0f ? copysignf(65000.0f, s) : s;
                 const half_t x = (half_t)v;
                 h[r / 8][r % 8] = x;
                 g[r / 8][r % 8] = (half_t)(v - (float)x);

@@ -44,3 +44,29 @@ def test_adapters_are_orthonormal_and_project_the_error(n, k, r, spread):
     # three rounds capture most of what the exact truncation does
     top = np.sum(np.linalg.svd(S, compute_uv=False)[:r] ** 2)
     assert 0.8 * top <= d[1] <= top * (1 + 1e-4)
+
+
+@pytest.mark.parametrize("n,k,r", [(300, 384, 64), (1030, 512, 96), (64, 2048, 32)])
+@pytest.mark.parametrize("base", [1.0, 10.0, 100.0, 1e3, 1e5])
+def test_adapters_of_blocks_of_every_condition(n, k, r, base):
+    """r channels that span `base` in magnitude above a floor of the others: blocks that are only scaled between
+    products, that are orthonormalised each time, and both in turn.  Sixteen rounds converge ((1 / 25)^32), so L spans the r
+    leading directions of S up to its rounding: a column off by 2^-11 relative loses at most that part of its
+    direction, together 2^-11 of ||S||, taken twice.  (A block that spans more than 3e4 has columns below the floor of the
+    factorisation, which may stay zero: no unit columns are asked for at 1e5.)"""
+    W = wl.make_weight(n, k, seed=n + 7).numpy()
+    q, m, s = B.slim_pack(torch.from_numpy(W).to(DEV))
+    ref = O.compress(W)
+    Wc = O.dequant(ref.qvals, ref.meta, ref.scale)
+    rng = np.random.default_rng(n)
+    xt = np.full(k, 0.01, np.float32)
+    xt[rng.permutation(k)[:r]] = base ** (1 - np.arange(r) / r)
+    L, R, diag = B.slim_compute_adapters(torch.from_numpy(W).to(DEV), q, m, s, r, torch.from_numpy(xt).to(DEV))
+    torch.cuda.synchronize()
+    x = O.saliency_shift(xt)
+    S = (W.astype(np.float64) - Wc) * x[None, :]
+    Lo, _ = np.linalg.qr(L.cpu().numpy().astype(np.float64))
+    left = np.linalg.norm(S - Lo @ (Lo.T @ S))
+    best = np.sqrt(np.sum(np.linalg.svd(S, compute_uv=False)[r:] ** 2))
+    assert left <= best * (1 + 1e-3) + 2 * 2.0 ** -11 * np.linalg.norm(S)
+    assert base > 1e4 or diag.cpu()[2] < 1e-4
