@@ -308,11 +308,12 @@ constexpr int kSplitMax = 1 << 22;       // n and k below this: a tile's rows of
 constexpr int kMaxBlock = 1024;          // columns of the iteration block (rank_pad)
 
 size_t orth_floats(int l);                                                                           // slim_lora_orth.hip
-int launch_orth(const float *in, float *out, half_t *hi, half_t *lo, int rows, int l, float *ws, hipStream_t st);
+int launch_orth(const float *in, float *out, half_t *hi, half_t *lo, int rows, int l, float *ws, int round, hipStream_t st);
+unsigned *orth_column_max(float *ws, int l, int which);
 int split_gemm_splits(int rows, int cols, int K);                                                    // slim_lora_split.hip
 int launch_lora_split(const float *S, int n, int k, const unsigned *max_bits, half_t *Sh, half_t *Sl, half_t *Th, half_t *Tl, hipStream_t st);
 int launch_lora_split_gemm(const half_t *Ah, const half_t *Al, const unsigned *max_bits, const half_t *Bh, const half_t *Bl, int rows, int cols,
-                           int K, float *P, float *Y, hipStream_t st);
+                           int K, float *P, float *Y, unsigned *colmax, hipStream_t st);
 
 // ---- results: L fp16 [n][r] = Q[:, :r];  R fp16 [r][k] = R~[:r] / x;  sq[1] += ||R~[:r]||_F^2 ----
 __global__ void lora_out_l_kernel(const float *Q, int n, int l, int r, half_t *L)
@@ -462,24 +463,25 @@ extern "C" int slim_compute_adapters(const float *W, const uint8_t *qvals, const
     }
     hipLaunchKernelGGL(lora_init_kernel, grid_for((size_t)k * l), dim3(256), 0, st, Z, blk[2], blk[3], k, l, r, seed);
     SLIM_TRY(launched());
-    auto times_z = [&]() {                   // Y = S Z     [n][l]
-        return p.split ? launch_lora_split_gemm(Sh[0], Sh[1], mx, blk[2], blk[3], n, l, k, P, Y, st)
+    auto times_z = [&](int round) {          // Y = S Z     [n][l], for the first product of `round`
+        unsigned *const colmax = p.split && round > 0 && round < q ? orth_column_max(O, l, round & 1) : nullptr;
+        return p.split ? launch_lora_split_gemm(Sh[0], Sh[1], mx, blk[2], blk[3], n, l, k, P, Y, colmax, st)
                        : sgemm(false, false, S, k, Z, l, Y, l, n, l, k, st);
     };
     auto times_q = [&]() {                   // Y = S^T Q   [k][l]
-        return p.split ? launch_lora_split_gemm(Sh[2], Sh[3], mx, blk[0], blk[1], k, l, n32, P, Y, st)
+        return p.split ? launch_lora_split_gemm(Sh[2], Sh[3], mx, blk[0], blk[1], k, l, n32, P, Y, nullptr, st)
                        : sgemm(true, false, S, k, Q, l, Y, l, k, l, n, st);
     };
 
-    SLIM_TRY(times_z());
+    SLIM_TRY(times_z(0));
     for (int it = 0; it < q; ++it) {
-        SLIM_TRY(launch_orth(Y, p.split ? nullptr : Q, blk[0], blk[1], n, l, O, st));
+        SLIM_TRY(launch_orth(Y, p.split ? nullptr : Q, blk[0], blk[1], n, l, O, p.split ? it : -1, st));
         SLIM_TRY(times_q());
-        SLIM_TRY(launch_orth(Y, Z, blk[2], blk[3], k, l, O, st));
-        SLIM_TRY(times_z());
+        SLIM_TRY(launch_orth(Y, Z, blk[2], blk[3], k, l, O, -1, st));
+        SLIM_TRY(times_z(it + 1));
     }
-    SLIM_TRY(launch_orth(Y, Q, nullptr, nullptr, n, l, O, st));
-    SLIM_TRY(launch_orth(Q, Y, nullptr, nullptr, n, l, O, st));    // second pass: orthonormal to rounding
+    SLIM_TRY(launch_orth(Y, Q, nullptr, nullptr, n, l, O, -1, st));
+    SLIM_TRY(launch_orth(Q, Y, nullptr, nullptr, n, l, O, -1, st));    // second pass: orthonormal to rounding
     SLIM_TRY(sgemm(true, false, Y, l, S, k, Rt, k, l, k, n, st));          // R~ = Q^T S        [l][k]
     SLIM_TRY(sgemm(true, false, Y, l, Y, l, G, l, l, l, n, st));           // Gram of the final block, for the report
     hipLaunchKernelGGL(lora_ortho_kernel, grid_for((size_t)r * r), dim3(256), 0, st, (const float *)G, l, r, sq);

@@ -149,6 +149,35 @@ __global__ __launch_bounds__(256) void lora_split_reduce_kernel(const float4_t *
     }
 }
 
+// The same, a workgroup per 16 rows of cols4 float4s, with the bits of the columns' largest magnitudes (zero before).
+__global__ __launch_bounds__(256) void lora_split_reduce_max_kernel(const float4_t *__restrict__ P, int splits, int rows, int cols4,
+                                                                    float4_t *__restrict__ Y, unsigned *__restrict__ colmax)
+{
+    __shared__ uint4_t part[256];
+    const int rpp = 256 / cols4, row = threadIdx.x / cols4, col = threadIdx.x % cols4;
+    const size_t count4 = (size_t)rows * cols4;
+    const int end = min((int)blockIdx.x * 16 + 16, rows);
+    float4_t mx = {0.f, 0.f, 0.f, 0.f};
+    if (row < rpp)
+        for (int r = blockIdx.x * 16 + row; r < end; r += rpp) {
+            const size_t i = (size_t)r * cols4 + col;
+            float4_t s = P[i];
+            for (int z = 1; z < splits; ++z) s += P[(size_t)z * count4 + i];
+            Y[i] = s;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) mx[e] = fmaxf(mx[e], fabsf(s[e]));
+        }
+    part[threadIdx.x] = __builtin_bit_cast(uint4_t, mx);
+    __syncthreads();
+    if (row == 0) {
+        for (int q = 1; q < rpp; ++q)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) mx[e] = fmaxf(mx[e], __uint_as_float(part[q * cols4 + col][e]));
+#pragma unroll
+        for (int e = 0; e < 4; ++e) atomicMax(&colmax[4 * col + e], __float_as_uint(mx[e]));     // non-negative floats order as integers
+    }
+}
+
 // Split-K factor: enough workgroups for the chip, shares of at least 128 of K.
 int split_gemm_splits(int rows, int cols, int K)
 {
@@ -164,17 +193,21 @@ int launch_lora_split(const float *S, int n, int k, const unsigned *max_bits, ha
     return hip_status(hipGetLastError());
 }
 
-// Y [rows][cols] = A B^T (A scaled by split_scale(*max_bits), B by kBlockSplit); P: split_gemm_splits() x rows x cols floats
+// Y [rows][cols] = A B^T (A scaled by split_scale(*max_bits), B by kBlockSplit); P: split_gemm_splits() x rows x cols floats.
+// colmax (or null): zeros, which become the bits of the columns' largest magnitudes (cols <= 1024).
 int launch_lora_split_gemm(const half_t *Ah, const half_t *Al, const unsigned *max_bits, const half_t *Bh, const half_t *Bl, int rows, int cols,
-                           int K, float *P, float *Y, hipStream_t st)
+                           int K, float *P, float *Y, unsigned *colmax, hipStream_t st)
 {
     SplitGemmArgs a{Ah, Al, Bh, Bl, max_bits, nullptr, rows, cols, K, 0, (rows + 255) / 256};
     const int splits = split_gemm_splits(rows, cols, K);
-    a.P = splits > 1 ? P : Y;
+    a.P = splits > 1 || colmax ? P : Y;
     a.ks = ((K + 127) / 128 + splits - 1) / splits * 128;
     const size_t lds = (size_t)2 * SG_STAGE * sizeof(half_t);
     hipLaunchKernelGGL(lora_split_gemm_kernel, dim3((unsigned)(a.tiles_o * ((cols + 127) / 128)), (unsigned)splits), dim3(256), lds, st, a);
-    if (splits > 1) {
+    if (colmax) {
+        hipLaunchKernelGGL(lora_split_reduce_max_kernel, dim3((unsigned)((rows + 15) / 16)), dim3(256), 0, st, reinterpret_cast<const float4_t *>(P),
+                           splits, rows, cols / 4, reinterpret_cast<float4_t *>(Y), colmax);
+    } else if (splits > 1) {
         const size_t count4 = (size_t)rows * cols / 4;          // cols is a multiple of 32
         const unsigned grid = (unsigned)((count4 + 255) / 256 < 2048 ? (count4 + 255) / 256 : 2048);
         hipLaunchKernelGGL(lora_split_reduce_kernel, dim3(grid), dim3(256), 0, st, reinterpret_cast<const float4_t *>(P), splits, count4,
