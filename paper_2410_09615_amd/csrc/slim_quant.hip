@@ -14,6 +14,11 @@
 // Three passes over memory in all: max, histogram (both read W once, HBM-bound),
 // and the candidates, which only touch the histogram.  Everything stays on the
 // device; the error sums are fp64.
+//
+// The candidates are one launch: the fine samples around every coarse one are evaluated beside the coarse ones
+// (220 workgroups, at most one per compute unit, of which 31 count), and the workgroup that ends last picks.  What bounds it is
+// launches and latency, not work: with coarse, fine and pick as three launches (23 us on 20000 bins) the call on 11008 x 4096
+// took 128.7 us, with one 119.3 (the adds of the histograms, from another bin in every workgroup, included).
 #include "slim_internal.h"
 
 namespace slim {
@@ -21,23 +26,29 @@ namespace slim {
 constexpr int kCoarse = 10;
 constexpr int kFine = 21;
 constexpr int kMaxBins = 20000;
+constexpr int kCandidates = kCoarse * (1 + kFine);   // coarse ones, then the fine ones around each of them
 constexpr int kMaxBlocks = 1024;        // workgroups of the maximum pass (one partial maximum each)
 
-// workspace (32-bit words): [0] bits of M, [16 .. 77] errors (31 doubles from byte 64),
-// [128 .. 128 + B) counts, then kMaxBlocks per-workgroup maxima
+// workspace (32-bit words): [0] bits of M, [1] and every 14th after it to [113]: counts of candidates that have ended,
+// [128 .. 128 + B) counts, then kMaxBlocks per-workgroup maxima, over which (from the next 8-byte boundary) the
+// candidates' errors are written
 struct QuantWs {
-    unsigned *mbits;
-    double *err;
+    unsigned *mbits, *done;
     unsigned *counts;
+    float *bmax;
+    double *err;
 };
-__host__ __device__ inline QuantWs quant_ws(void *ws)
+__host__ __device__ inline QuantWs quant_ws(void *ws, int B)
 {
     QuantWs q;
     q.mbits = static_cast<unsigned *>(ws);
-    q.err = reinterpret_cast<double *>(static_cast<char *>(ws) + 64);
-    q.counts = static_cast<unsigned *>(ws) + 128;
+    q.done = q.mbits + 1;
+    q.counts = q.mbits + 128;
+    q.bmax = reinterpret_cast<float *>(q.counts + B);
+    q.err = reinterpret_cast<double *>(q.counts + (B + 1) / 2 * 2);
     return q;
 }
+static_assert(2 * kCandidates + 1 <= kMaxBlocks, "the errors fit where the maxima were");
 
 __host__ __device__ inline int quant_bins(long numel)
 {
@@ -88,18 +99,19 @@ __global__ __launch_bounds__(1024) void quant_hist_kernel(const float *__restric
         const float4 *W4 = reinterpret_cast<const float4 *>(W);
         const size_t stride = (size_t)gridDim.x * blockDim.x;
         size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x;
-        for (; i + stride < numel4; i += 2 * stride) {       // two loads in flight per lane
-            const float4 v = W4[i], u = W4[i + stride];
-            put(v.x);
-            put(v.y);
-            put(v.z);
-            put(v.w);
-            put(u.x);
-            put(u.y);
-            put(u.z);
-            put(u.w);
+        for (; i + 3 * stride < numel4; i += 4 * stride) {   // four loads in flight per lane
+            float4 v[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) v[q] = W4[i + q * stride];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                put(v[q].x);
+                put(v[q].y);
+                put(v[q].z);
+                put(v[q].w);
+            }
         }
-        if (i < numel4) {
+        for (; i < numel4; i += stride) {
             const float4 v = W4[i];
             put(v.x);
             put(v.y);
@@ -108,19 +120,37 @@ __global__ __launch_bounds__(1024) void quant_hist_kernel(const float *__restric
         }
     }
     __syncthreads();
-    for (int i = threadIdx.x; i < B; i += blockDim.x)
+    // every workgroup starts at another bin: adds to one address serialize at memory
+    const int first = (int)((size_t)blockIdx.x * B / gridDim.x) & ~(kWave - 1);
+    for (int j = threadIdx.x; j < B; j += blockDim.x) {
+        const int i = first + j < B ? first + j : first + j - B;
         if (hist[i]) atomicAdd(&counts[i], hist[i]);
+    }
 }
 
 // E(alpha) over the histogram: one workgroup, fp64
 __device__ __forceinline__ double quant_error_block(const unsigned *counts, int B, double M, double alpha, double *red)
 {
-    const double step = alpha / 7.0, width = M / B;
+    const double step = alpha / 7.0, width = M / B, inv_step = 1.0 / step;
     double e = 0.0;
-    for (int b = threadIdx.x; b < B; b += blockDim.x) {
-        const double x = ((double)b + 0.5) * width;
-        const double d = x <= alpha ? rint(x / step) * step - x : alpha - x;
-        e += (double)counts[b] * (d * d);
+    constexpr int N = 10;                        // counts in flight: they come from memory, where the adds put them
+    for (int b0 = threadIdx.x; b0 < B; b0 += N * blockDim.x) {
+        unsigned cnt[N];
+#pragma unroll
+        for (int i = 0; i < N; ++i) cnt[i] = b0 + i * (int)blockDim.x < B ? counts[b0 + i * blockDim.x] : 0u;
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            const double x = ((double)(b0 + i * (int)blockDim.x) + 0.5) * width;
+            double d = alpha - x;
+            if (x <= alpha) {
+                // rint(x / step) without the division wherever that cannot change it (see quant_rows_kernel)
+                const double q = x * inv_step;
+                double r = rint(q);
+                if (fabs(q - r) > 0.5 - 1e-9) r = rint(x / step);
+                d = r * step - x;
+            }
+            e += (double)cnt[i] * (d * d);
+        }
     }
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) e += __shfl_xor(e, off, kWave);
@@ -132,53 +162,59 @@ __device__ __forceinline__ double quant_error_block(const unsigned *counts, int 
     return t;
 }
 
-// candidates 0..9 coarse, 10..30 fine (the fine ones need the coarse errors: second launch)
+__device__ __forceinline__ double coarse_alpha(double M, int i) { return M / 10.0 * (i + 1); }
+__device__ __forceinline__ double fine_alpha(double M, int i, int f) { return M / 10.0 * (i + 1) + M / 10.0 * ((f - 10) / 10.0); }
+
+// Workgroup c evaluates candidate c: c < kCoarse coarse, else fine sample (c - kCoarse) % kFine around coarse candidate
+// (c - kCoarse) / kFine.  The last one to end picks: alpha* = first minimum over the coarse ones and the fine ones
+// around the best of them; scale_out[o] = alpha* / 7 for every row.
 __global__ __launch_bounds__(1024) void quant_eval_kernel(const unsigned *mbits, const unsigned *counts, int B, double *err,
-                                                          int first)
+                                                          unsigned *done, float *scale_out, int n, float *alpha_out)
 {
     __shared__ double red[16];
-    const int c = first + blockIdx.x;
+    __shared__ unsigned last;
+    const int c = blockIdx.x;
     const double M = (double)__uint_as_float(*mbits);
-    if (M == 0.0) return;
-    const double eta = M / 10.0;
-    double alpha;
-    if (c < kCoarse) {
-        alpha = eta * (c + 1);
-    } else {
-        int best = 0;
-        for (int i = 1; i < kCoarse; ++i)
-            if (err[i] < err[best]) best = i;
-        alpha = eta * (best + 1) + eta * ((c - kCoarse - 10) / 10.0);
-        if (!(alpha > 0.0 && alpha <= M)) {
-            if (threadIdx.x == 0) err[c] = __builtin_inf();
-            return;
-        }
+    const double alpha = c < kCoarse ? coarse_alpha(M, c) : fine_alpha(M, (c - kCoarse) / kFine, (c - kCoarse) % kFine);
+    double e = __builtin_inf();
+    if (M != 0.0 && (c < kCoarse || (alpha > 0.0 && alpha <= M))) e = quant_error_block(counts, B, M, alpha, red);
+    if (threadIdx.x == 0) {
+        // written through to memory, and there before the counts say so: one of eight, then the one of those (adds to one
+        // address serialize at memory)
+        __hip_atomic_store(err + c, e, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        asm volatile("s_waitcnt vmcnt(0)" : : : "memory");
+        const unsigned g = blockIdx.x % 8, of = (gridDim.x - g + 7) / 8;
+        last = 0u;
+        if (__hip_atomic_fetch_add(done + 14 * (g + 1), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == of - 1)
+            last = __hip_atomic_fetch_add(done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 7u;
     }
-    const double e = quant_error_block(counts, B, M, alpha, red);
-    if (threadIdx.x == 0) err[c] = e;
-}
-
-// alpha* = first minimum; scale_out[o] = alpha* / 7 for every row
-__global__ __launch_bounds__(256) void quant_pick_kernel(const unsigned *mbits, const double *err, float *scale_out, int n,
-                                                         float *alpha_out)
-{
-    const double M = (double)__uint_as_float(*mbits);
-    float alpha = 0.f, s = 1.f;
+    __syncthreads();
+    if (!last) return;
+    __shared__ double all[kCandidates];
+    if (threadIdx.x < kCandidates) all[threadIdx.x] = __hip_atomic_load(err + threadIdx.x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    float a = 0.f, s = 1.f;
     if (M > 0.0) {
-        const double eta = M / 10.0;
-        int best = 0;
+        int best = 0, pick = -1;
+        double low = all[0];
+#pragma unroll
         for (int i = 1; i < kCoarse; ++i)
-            if (err[i] < err[best]) best = i;
-        const double lo = eta * (best + 1);
-        int pick = best;
-        for (int c = kCoarse; c < kCoarse + kFine; ++c)
-            if (err[c] < err[pick]) pick = c;
-        const double a = pick < kCoarse ? eta * (pick + 1) : lo + eta * ((pick - kCoarse - 10) / 10.0);
-        alpha = (float)a;
-        s = alpha / 7.0f;
+            if (all[i] < low) {
+                low = all[i];
+                best = i;
+            }
+        const double *const fine = all + kCoarse + best * kFine;
+#pragma unroll
+        for (int f = 0; f < kFine; ++f)
+            if (fine[f] < low) {
+                low = fine[f];
+                pick = f;
+            }
+        a = (float)(pick < 0 ? coarse_alpha(M, best) : fine_alpha(M, best, pick));
+        s = a / 7.0f;
     }
-    for (int o = blockIdx.x * blockDim.x + threadIdx.x; o < n; o += gridDim.x * blockDim.x) scale_out[o] = s;
-    if (alpha_out && blockIdx.x == 0 && threadIdx.x == 0) *alpha_out = alpha;
+    for (int o = threadIdx.x; o < n; o += blockDim.x) scale_out[o] = s;
+    if (alpha_out && threadIdx.x == 0) *alpha_out = a;
 }
 
 // ---- the same search with one scale per output row: one workgroup per row, everything in LDS ----
@@ -303,23 +339,20 @@ extern "C" int slim_quant_search(const float *W, slim_shape shape, float *scale_
     const int B = quant_bins((long)numel);
     if (workspace_bytes < (size_t)(128 + B + kMaxBlocks) * 4) return SLIM_ERR_WORKSPACE;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    const QuantWs q = quant_ws(workspace);
+    const QuantWs q = quant_ws(workspace, B);
     const size_t numel4 = numel / 4;
     size_t g = (numel4 + 255) / 256;
     const unsigned grid_a = (unsigned)(g < (size_t)kMaxBlocks ? g : (size_t)kMaxBlocks);
-    float *bmax = reinterpret_cast<float *>(q.counts + B);
     g = (numel4 + 1023) / 1024;
     // every workgroup ends with one global add per non-empty bin of its own histogram: few workgroups
     // (one per compute unit; half of that below 2^25 elements, where those adds outweigh the reading)
     const size_t hcap = numel < ((size_t)1 << 25) ? 128 : 256;
     const unsigned grid_h = (unsigned)(g < hcap ? g : hcap);
-    hipLaunchKernelGGL(quant_absmax_kernel, dim3(grid_a), dim3(256), 0, st, W, numel4, bmax, q.mbits, 128 + B);
-    hipLaunchKernelGGL(quant_hist_kernel, dim3(grid_h), dim3(1024), (size_t)B * 4, st, W, numel4, B, bmax, (int)grid_a, q.mbits,
+    hipLaunchKernelGGL(quant_absmax_kernel, dim3(grid_a), dim3(256), 0, st, W, numel4, q.bmax, q.mbits, 128 + B);
+    hipLaunchKernelGGL(quant_hist_kernel, dim3(grid_h), dim3(1024), (size_t)B * 4, st, W, numel4, B, q.bmax, (int)grid_a, q.mbits,
                        q.counts);
-    hipLaunchKernelGGL(quant_eval_kernel, dim3(kCoarse), dim3(1024), 0, st, q.mbits, q.counts, B, q.err, 0);
-    hipLaunchKernelGGL(quant_eval_kernel, dim3(kFine), dim3(1024), 0, st, q.mbits, q.counts, B, q.err, kCoarse);
-    hipLaunchKernelGGL(quant_pick_kernel, dim3((unsigned)((shape.n + 255) / 256)), dim3(256), 0, st, q.mbits, q.err,
-                       scale_out, shape.n, alpha_out);
+    hipLaunchKernelGGL(quant_eval_kernel, dim3(kCandidates), dim3(1024), 0, st, q.mbits, q.counts, B, q.err, q.done, scale_out, shape.n,
+                       alpha_out);
     return hip_status(hipGetLastError());
 }
 
