@@ -102,7 +102,7 @@ __device__ __forceinline__ void mfma_fixed(half8_t av, half8_t bv)
 }
 
 // The order in which the prefill kernels hand output tiles (row tile x token tile) to workgroups.
-// These kernels are bound by the bytes their workgroups request from L2, and a die's L2 serves the
+// A die's L2 serves the
 // workgroups whose index is congruent to the die's modulo 8 (the dispatcher deals workgroups to the
 // dies in turn).  With tiles handed out in index order the 32 workgroups a die holds at a time are
 // scattered over the layer (8192 x 8192: 2 row tiles x 16 token tiles, 42 MB of distinct operands for
