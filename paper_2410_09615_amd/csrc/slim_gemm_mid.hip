@@ -412,11 +412,11 @@ static void launch_t_tiles(TArgs a, int xf, hipStream_t st)
     }
 }
 
-static int t_shape(int rank_pad, int m);
+static int t_shape(int rank_pad, int m, int k);
 static void launch_t_role(const TArgs &a, int xf, hipStream_t st);
 static int launch_t_product_args(const TArgs &a, int xf, hipStream_t st)
 {
-    switch (t_shape(a.rank_pad, a.m)) {
+    switch (t_shape(a.rank_pad, a.m, a.k)) {
         case 3: launch_t_role(a, xf, st); break;
         case 0: launch_t_tiles<1, 1>(a, xf, st); break;
         case 1: launch_t_tiles<1, 2>(a, xf, st); break;
@@ -450,20 +450,28 @@ int launch_t_product(const half_t *X, int xf, const float *x_scale, int m, int k
 // second round doubles it (m = 333, rank 416, whole call on 11008 x 4096: 45.2 / 46.9 / 50.8 us with tiles of
 // 32 x 32, 32 x 64, 64 x 64; m = 700 with 8-bit inputs on 2100 x 4096: 43.9 / 40.6 / 45.6; m = 1000, rank 832
 // on 8192 x 8192: 137.8 / 126.5 / 117.4).
-static int t_shape(int rank_pad, int m)
+// Beyond 4096 inputs 11/16 of a round, and the 16 x 16 tiles up to 512 tokens, because small tiles read both operands more
+// often and the chain hides it no longer (k = 11008, adapter term alone: 800 tokens, rank 64 in 200 tiles of 16 x 16 31.7 us,
+// in 50 of 32 x 32 21.6; rank 608, 300 tokens in 190 of 32 x 32 43.8, in 95 of 32 x 64 36.5; 512 tokens in 152 of
+// 32 x 64 37.4, in 80 of 64 x 64 45.2).
+static int t_shape(int rank_pad, int m, int k)
 {
-    const long ranks32 = rank_pad / 32, tokens32 = (m + 31) / 32, cus = device_info().cus;
-    if (2 * ranks32 * ((m + 15) / 16) <= cus) return 3;
-    if (ranks32 * tokens32 <= cus) return 0;
-    return ranks32 * ((tokens32 + 1) / 2) <= cus ? 1 : 2;
+    const long ranks32 = rank_pad / 32, tokens32 = (m + 31) / 32, cus = device_info().cus, most = k > 4096 ? cus * 11 / 16 : cus;
+    if (2 * ranks32 * ((m + 15) / 16) <= cus && (k <= 4096 || m <= 512)) return 3;
+    if (ranks32 * tokens32 <= most) return 0;
+    return ranks32 * ((tokens32 + 1) / 2) <= most ? 1 : 2;
 }
 
 // Whether t_product_kernel makes T for the large tiles, or the split product of slim_gemm.hip: up to two rounds of
-// its largest tile (m = 4096, rank 512, k = 5120: 181.5 against 184.0 us for the call; rank 832, k = 8192: 417
-// against 387).
-bool t_in_one_launch(int rank_pad, int m)
+// its largest tile, one beyond 4096 inputs (k = 11008, adapter term alone: rank 608 at 1500 tokens, 240 tiles, 58 against
+// 81 us; at 2500, 400 tiles, 91 against 84; k = 8192, rank 832 at 1500 tokens, 312 tiles, 111 against 100), and
+// where R, which every die reads, is beyond 16 MiB only with tiles of 16 x 16 (k = 11008, rank 1120: at 40 tokens 22.7
+// against 36.2, at 150 65 against 49).
+bool t_in_one_launch(int rank_pad, int m, int k)
 {
-    return (long)((rank_pad + 63) / 64) * ((m + 63) / 64) <= 2L * device_info().cus;
+    if ((long)rank_pad * k * 2 > (16L << 20)) return t_shape(rank_pad, m, k) == 3;
+    const long tiles = (long)((rank_pad + 63) / 64) * ((m + 63) / 64), cus = device_info().cus;
+    return tiles <= (k > 4096 ? cus : 2 * cus);
 }
 
 // Geometry of mid_kernel: the LDS of a round of X (shared) and of a round of weights (private to the wavefronts),
