@@ -17,8 +17,9 @@
 // apply 20) where it was 700.
 //
 // A pivot below 1e-9 of the largest diagonal entry of G marks a column that lies in the span of the ones before it
-// (or a padding column of zeros): it gets pivot 1 and no column is subtracted for it, so the block carries what is
-// left of it, a (numerically) zero column if `in` is of order one.  (Where 1e-9 of that entry is more than 1, the pivot is
+// (or a padding column of zeros): it gets pivot 1 and no column is subtracted for it, in the blocks that follow either,
+// so the block carries what is left of it, a (numerically) zero column if `in` is of order one.  (What is left of such
+// a column in G is rounding, 1e-7 of the largest entry: subtracted as a panel it takes the pivots of that size after it along.)  (Where 1e-9 of that entry is more than 1, the pivot is
 // that: what is left stays within the range of the split into fp16 numbers.)
 //
 // Every other block of the subspace iteration need not be orthonormal: two products in a row lose what one does, squared.
@@ -169,17 +170,22 @@ __device__ __forceinline__ void for_each(F &&f)
 // 16 x 16: lane i of sixteen holds row i of the symmetric block a = Lc Lc^T; x: row i of Lc^-1.  The steps run on
 // a = M diag(d) M^T, M with a unit diagonal, whose chain has a reciprocal and no square root, and the rows of M^-1 are
 // scaled by 1 / sqrt(d) at the end; they broadcast across the sixteen lanes without LDS or barriers.
-// pmax, pmin: the largest and the smallest pivot of a row so far, but for those of `dead`.
-__device__ __forceinline__ void factor16(float (&a)[16], float (&x)[16], int i, float floor_, float dead, float &pmax, float &pmin)
+// pmax, pmin: the largest and the smallest pivot of a row so far, but for those of `dead`.  Returns whether this row's
+// pivot is above the floor.
+__device__ __forceinline__ bool factor16(float (&a)[16], float (&x)[16], int i, float floor_, float dead, float &pmax, float &pmin)
 {
 #pragma unroll
     for (int c = 0; c < 16; ++c) x[c] = i == c ? 1.0f : 0.f;
     float mine = 1.0f;                           // this row's pivot
+    bool alive = false;
     for_each<16>([&](auto cc) {
         constexpr int c = cc;
         const float d = row_lane<c>(a[c]);
         const bool ok = d > floor_;              // no: a column in the span of the ones before it: pivot `dead`, nothing to subtract
-        if (i == c) mine = ok ? d : dead;
+        if (i == c) {
+            mine = ok ? d : dead;
+            alive = ok;
+        }
         pmax = ok ? fmaxf(pmax, d) : pmax;
         pmin = ok ? fminf(pmin, d) : pmin;
         float q = __builtin_amdgcn_rcpf(d);
@@ -198,13 +204,15 @@ __device__ __forceinline__ void factor16(float (&a)[16], float (&x)[16], int i, 
     q = q * (1.5f - 0.5f * mine * q * q);        // 1 / sqrt(d) to rounding
 #pragma unroll
     for (int c = 0; c < 16; ++c) x[c] *= q;
+    return alive;
 }
 
 // Step j: tiles (I, J), I >= J >= j, of the trailing matrix; column j - 1 of G holds A_{I, j-1}, D the inverse of
-// the last diagonal block, so the panel is L_{I, j-1} = A_{I, j-1} D^T.  Step 0 adds up the partial tiles instead.
-// The workgroups of column j write the panel to Lf; the one of tile (j, j) factors it and writes D[j].
+// the last diagonal block, its rows of pivots below the floor as zeros (Dp), so the panel is L_{I, j-1} = A_{I, j-1} D^T.
+// Step 0 adds up the partial tiles instead.  The workgroups of column j write the panel to Lf; the one of tile (j, j)
+// factors it and writes D[j], whole, and Dp[j].
 __global__ __launch_bounds__(256) void lora_chol_kernel(int j, int nb, int l, const float *__restrict__ P, int splits, int tiles,
-                                                        float *__restrict__ G, float *__restrict__ Lf, float *__restrict__ D, OrthWords *words,
+                                                        float *__restrict__ G, float *__restrict__ Lf, float *__restrict__ D, float *__restrict__ Dp, OrthWords *words,
                                                         const OrthWords *cond)
 {
     if (cond && !cond->need) return;
@@ -229,7 +237,7 @@ __global__ __launch_bounds__(256) void lora_chol_kernel(int j, int nb, int l, co
     } else {
         const float4_t *const Ai = reinterpret_cast<const float4_t *>(G + (size_t)tri(I, j - 1) * kTileFloats);
         const float4_t *const Aj = reinterpret_cast<const float4_t *>(G + (size_t)tri(J, j - 1) * kTileFloats);
-        const float4_t *const Dp = reinterpret_cast<const float4_t *>(D + (size_t)(j - 1) * kTileFloats);
+        const float4_t *const Dj = reinterpret_cast<const float4_t *>(Dp + (size_t)(j - 1) * kTileFloats);
         float4_t g[4];
 #pragma unroll
         for (int q = 0; q < 4; ++q) g[q] = reinterpret_cast<const float4_t *>(Gt)[tid + 256 * q];
@@ -245,7 +253,7 @@ __global__ __launch_bounds__(256) void lora_chol_kernel(int j, int nb, int l, co
             float4_t ci = {0.f, 0.f, 0.f, 0.f}, cj = ci;
 #pragma unroll
             for (int t = 0; t < 4; ++t) {
-                const float4_t d = Dp[(cb * 4 + t) * 64 + lane];
+                const float4_t d = Dj[(cb * 4 + t) * 64 + lane];
                 mma16(ai[t], d, ci);
                 mma16(aj[t], d, cj);
             }
@@ -306,6 +314,7 @@ __global__ __launch_bounds__(256) void lora_chol_kernel(int j, int nb, int l, co
     auto block = [](float *base, int bi, int bj) { return base + (bi * 4 + bj) * 256; };
     auto operand = [&](const float *blk) { return reinterpret_cast<const float4_t *>(blk)[lane]; };
     __shared__ __attribute__((aligned(16))) float M[3][256];
+    __shared__ int alive[kOb];                   // pivot above the floor
     for (int idx = tid; idx < kTileFloats; idx += 256) X[idx] = 0.f;
     __syncthreads();
     for (int b = 0; b < 4; ++b) {
@@ -317,8 +326,9 @@ __global__ __launch_bounds__(256) void lora_chol_kernel(int j, int nb, int l, co
 #pragma unroll
                 for (int e = 0; e < 4; ++e) a[4 * q + e] = v[e];
             }
-            factor16(a, x, ln, floor_, fmaxf(1.0f, floor_), pmax, pmin);
+            const bool ok = factor16(a, x, ln, floor_, fmaxf(1.0f, floor_), pmax, pmin);
             if (lane < 16) {
+                alive[16 * b + ln] = ok;
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
                     reinterpret_cast<float4_t *>(block(X, b, b))[q * 16 + ln] = float4_t{x[4 * q], x[4 * q + 1], x[4 * q + 2], x[4 * q + 3]};
@@ -333,7 +343,7 @@ __global__ __launch_bounds__(256) void lora_chol_kernel(int j, int nb, int l, co
             float4_t c = {0.f, 0.f, 0.f, 0.f};
             mma16(operand(block(T, wave, b)), operand(block(X, b, b)), c);
 #pragma unroll
-            for (int e = 0; e < 4; ++e) block(T, wave, b)[(ln >> 2) * 64 + (4 * mq + e) * 4 + (ln & 3)] = c[e];
+            for (int e = 0; e < 4; ++e) block(T, wave, b)[(ln >> 2) * 64 + (4 * mq + e) * 4 + (ln & 3)] = alive[16 * b + ln] ? c[e] : 0.f;
         }
         __syncthreads();
         if (wave > b) {
@@ -368,8 +378,13 @@ __global__ __launch_bounds__(256) void lora_chol_kernel(int j, int nb, int l, co
         words->need = pmax <= kSpread * pmin ? 0u : 1u;
     }
     float4_t *const out = reinterpret_cast<float4_t *>(D + (size_t)j * kTileFloats);
+    float4_t *const outp = reinterpret_cast<float4_t *>(Dp + (size_t)j * kTileFloats);
 #pragma unroll
-    for (int q = 0; q < 4; ++q) out[tid + 256 * q] = reinterpret_cast<const float4_t *>(X)[tid + 256 * q];
+    for (int q = 0; q < 4; ++q) {                // (piece tid + 256 q is of row 16 q + tid % 16)
+        const float4_t v = reinterpret_cast<const float4_t *>(X)[tid + 256 * q];
+        out[tid + 256 * q] = v;
+        outp[tid + 256 * q] = alive[16 * q + (tid & 15)] ? v : float4_t{0.f, 0.f, 0.f, 0.f};
+    }
 }
 
 // The power of two that brings a column whose largest magnitude has the bits `max_bits` below 1.
@@ -483,12 +498,12 @@ __global__ __launch_bounds__(256) void lora_apply_kernel(const float *__restrict
 }
 
 // Workspace of the orth()s of a call, in floats: partial tiles, tiles of G and of the factor, inverses of the diagonal
-// blocks, two sets of OrthWords, two rows of column maxima.
+// blocks (twice), two sets of OrthWords, two rows of column maxima.
 constexpr int kOrthWords = 64;
 size_t orth_floats(int l)
 {
     const size_t nb = (size_t)(l + kOb - 1) / kOb, t = nb * (nb + 1) / 2;
-    return (kGramTiles + 2 * t + nb) * kTileFloats + kOrthWords + 2 * (size_t)l;
+    return (kGramTiles + 2 * t + 2 * nb) * kTileFloats + kOrthWords + 2 * (size_t)l;
 }
 unsigned *orth_column_max(float *ws, int l, int which)
 {
@@ -503,8 +518,8 @@ int launch_orth(const float *in, float *out, half_t *hi, half_t *lo, int rows, i
 {
     const int nb = (l + kOb - 1) / kOb, tiles = tri(nb, 0);
     float *const P = ws, *const G = P + (size_t)kGramTiles * kTileFloats, *const Lf = G + (size_t)tiles * kTileFloats;
-    float *const D = Lf + (size_t)tiles * kTileFloats;
-    OrthWords *const both = reinterpret_cast<OrthWords *>(D + (size_t)nb * kTileFloats);
+    float *const D = Lf + (size_t)tiles * kTileFloats, *const Dp = D + (size_t)nb * kTileFloats;
+    OrthWords *const both = reinterpret_cast<OrthWords *>(Dp + (size_t)nb * kTileFloats);
     OrthWords *const words = both + (round < 0 ? 0 : 1);
     const OrthWords *const cond = round > 0 ? both : nullptr;
     const unsigned *const colmax = round > 0 ? orth_column_max(ws, l, round & 1) : nullptr;
@@ -517,7 +532,7 @@ int launch_orth(const float *in, float *out, half_t *hi, half_t *lo, int rows, i
     hipLaunchKernelGGL(lora_gram_kernel, dim3((unsigned)tiles, (unsigned)splits), dim3(256), 0, st, in, rows, l, zrows, tiles, P, cond);
     for (int j = 0; j < nb; ++j)
         hipLaunchKernelGGL(lora_chol_kernel, dim3((unsigned)tri(nb - j, 0)), dim3(256), 0, st, j, nb, l, (const float *)P, splits, tiles, G, Lf, D,
-                           words, cond);
+                           Dp, words, cond);
     const size_t lds = (size_t)(16 * (nb * kOb + 4) + 16 * 68) * sizeof(float);
     hipLaunchKernelGGL(lora_apply_kernel, dim3((unsigned)((rows + 31) / 32 * 2)), dim3(256), lds, st, in, out, rows, l, nb, (const float *)Lf,
                        (const float *)D, hi, lo, (rows + 31) / 32 * 32, cond, colmax, clear);
