@@ -307,7 +307,15 @@ __global__ __launch_bounds__(256) void lora_chol_kernel(int j, int nb, int l, co
     } else {
         mx = words->gmax;
     }
-    const float floor_ = mx * 1e-9f;
+    // Far from 1 the block is factored as 4^h G (exact): the reciprocals of factor16() know no subnormal numbers
+    int h = 0;
+    if (mx > 0.f && !(mx > 0x1p-60f && mx < 0x1p60f)) h = min(max(-(__builtin_amdgcn_frexp_expf(mx) / 2), -63), 63);
+    const float dead = ldexpf(fmaxf(1.0f, mx * 1e-9f), 2 * h), floor_ = ldexpf(mx, 2 * h) * 1e-9f;
+    if (h != 0)                                  // (a thread's own pieces)
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) T[4 * (tid + 256 * q) + e] = ldexpf(T[4 * (tid + 256 * q) + e], 2 * h);
     float pmax = j == 0 ? 0.f : words->pmax, pmin = j == 0 ? __builtin_inff() : words->pmin;     // (wavefront 0)
     float *const X = LI;                         // the inverse, and
     float *const XT = LJ;                        // the inverse transposed: block (c, r) holds block (r, c) of X
@@ -326,7 +334,7 @@ __global__ __launch_bounds__(256) void lora_chol_kernel(int j, int nb, int l, co
 #pragma unroll
                 for (int e = 0; e < 4; ++e) a[4 * q + e] = v[e];
             }
-            const bool ok = factor16(a, x, ln, floor_, fmaxf(1.0f, floor_), pmax, pmin);
+            const bool ok = factor16(a, x, ln, floor_, dead, pmax, pmin);
             if (lane < 16) {
                 alive[16 * b + ln] = ok;
 #pragma unroll
@@ -381,7 +389,10 @@ __global__ __launch_bounds__(256) void lora_chol_kernel(int j, int nb, int l, co
     float4_t *const outp = reinterpret_cast<float4_t *>(Dp + (size_t)j * kTileFloats);
 #pragma unroll
     for (int q = 0; q < 4; ++q) {                // (piece tid + 256 q is of row 16 q + tid % 16)
-        const float4_t v = reinterpret_cast<const float4_t *>(X)[tid + 256 * q];
+        float4_t v = reinterpret_cast<const float4_t *>(X)[tid + 256 * q];
+        if (h != 0)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] = ldexpf(v[e], h);
         out[tid + 256 * q] = v;
         outp[tid + 256 * q] = alive[16 * q + (tid & 15)] ? v : float4_t{0.f, 0.f, 0.f, 0.f};
     }

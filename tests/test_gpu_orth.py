@@ -94,3 +94,25 @@ def test_a_column_below_the_floor_takes_no_other_along(seed, gain):
     Lo, _ = np.linalg.qr(L.cpu().numpy().astype(np.float64))
     missing = int(np.sum(1 - np.sum((Lo.T @ lead) ** 2, axis=0) > 1e-3))
     assert missing <= 4
+
+
+@pytest.mark.parametrize("n,k,r", [(300, 384, 64), (1030, 512, 96)])
+def test_weights_whose_gram_matrices_are_subnormal(n, k, r):
+    """Weights of 2e-22: diagonal entries of the Gram matrix of S Q around 1e-41, where reciprocal instructions
+    return infinity.  S keeps 24 bits there, its Gram matrix 10 or more, so a block is orthonormal up to 2^-10 times
+    the condition of the block (below 4 for these weights) after one pass and the square of that after the second: entries of L^T L
+    stay within the 2^-9 that rounding L to fp16 is given above, and L captures as much as for the same weights times 1e20."""
+    W = wl.make_weight(n, k, seed=n).numpy().astype(np.float64)
+    left = []
+    for gain in (1.0, 1e-20):
+        Wg = (W * gain).astype(np.float32)
+        q, m, s = B.slim_pack(torch.from_numpy(Wg).to(DEV))
+        L, R, diag = B.slim_compute_adapters(torch.from_numpy(Wg).to(DEV), q, m, s, r)
+        torch.cuda.synchronize()
+        assert bool(torch.isfinite(L).all()) and bool(torch.isfinite(R).all()) and bool(torch.isfinite(diag).all())
+        Lf = L.cpu().numpy().astype(np.float64)
+        assert np.max(np.abs(Lf.T @ Lf - np.eye(r))) <= 2 * 2.0 ** -10
+        ref = O.compress(Wg)
+        S = (Wg.astype(np.float64) - O.dequant(ref.qvals, ref.meta, ref.scale)) / gain
+        left.append(np.linalg.norm(S - Lf @ (Lf.T @ S)))
+    assert abs(left[1] / left[0] - 1) <= 1e-3
