@@ -274,7 +274,9 @@ int slim_unpack(const uint8_t *qvals, const uint8_t *meta, slim_shape shape, int
  * token counts.  Two calls that overlap in time need two workspaces.
  * Diagnostics: the one-launch decode kernel, and slim_linear_gemm and slim_lowrank
  * on small batches (up to 512 tokens, where their tiles leave compute units free), wait,
- * inside the kernel, for their own T = X R^T; the wait is bounded.  Should it ever run out (it never should),
+ * inside the kernel, for their own T = X R^T; the wait is bounded.  The small-batch kernel makes T itself
+ * where the wait runs out (other work on the chip can hold its T back).  Should the decode kernel's wait ever run out
+ * (it never should), or T be missing even then,
  * the outputs that depend on the missing part are NaN -- a failed call cannot
  * pass for a result -- and word 2 of the workspace is set to 1.
  * slim_workspace_check reads that word back: it synchronizes `stream` (so it is
@@ -346,7 +348,9 @@ int slim_linear_gemv_static(const slim_layer *layer, const slim_half *X, int32_t
  *           fits, only the half of the kernel that waits for T is launched, with
  *           the wait cut to 256 polls, so it gives up (slim_linear_gemm on a small
  *           batch likewise): every wavefront still ends normally, Y is NaN and the workspace's error word is set
- *           (slim_workspace_check then reports SLIM_ERR_WAIT);
+ *           (slim_workspace_check then reports SLIM_ERR_WAIT).  With lds_kb != 0 slim_linear_gemm and
+ *           slim_lowrank on a small batch launch everything, but the workgroups meant to make T make nothing:
+ *           those that wait make it themselves, and Y is what it always is;
  *   lds_kb  0: plan with the device's LDS; 16..160: with at most this many KiB
  *           (X then streams through the LDS in chunks on small layers too).
  * Errors: SHAPE (a value outside these ranges).

@@ -17,9 +17,11 @@
 //           X (from the L2) would wait for all weights (from memory) it has asked for before.
 //
 // The two roles share a launch only if all its workgroups are resident at once (one workgroup per
-// compute unit), so that nothing that is waited for is queued behind something that waits; otherwise
-// they are two launches.  The wait is bounded either way, and one that gives up makes its outputs
-// NaN and sets the workspace's error word.
+// compute unit); otherwise they are two launches.  That T is made does not depend on it: other work on the chip (calls
+// on other streams, whose workgroups take whole compute units and wait likewise) can keep a T role from being dispatched
+// while the Y role already waits, in a circle if there are three such calls.  So the wait is short, and a workgroup whose wait
+// runs out makes T of its tokens itself and starts again: the same pieces, bit for bit, whoever stores them.
+// Should a piece still be missing then (it cannot be), the outputs are NaN and the workspace's error word is set.
 //
 // X in LDS: a token's stage is one row without padding (the loads write LDS in lane order), so the
 // pieces of 16 bytes of a row are stored permuted by the token number: the sixteen lanes that read
@@ -500,28 +502,19 @@ struct MidLds {
     static_assert(WRING >= 2 && BYTES <= LDS, "LDS of a compute unit");
 };
 
-template <int NT_, int RT, int RG, int KW, int XF, bool AQ>
-__global__ __launch_bounds__(kMidThreads, 3) void mid_kernel(MidArgs a)
+// The Y role.  SECOND: T of the tile's tokens has been made by this workgroup.  True: a wait for the T role ran out, and
+// nothing has been stored.
+template <int NT_, int RT, int RG, int KW, int XF, bool AQ, bool SECOND>
+__device__ __forceinline__ bool y_role(const MidArgs &a, int tid, int ot, int tt, char *lds_c, unsigned epoch)
 {
     using G = MidLds<NT_, RT, RG, KW, XF>;
     constexpr int ROWB = G::ROWB, STAGE = G::STAGE, XRING = G::XRING, WRING = G::WRING;
     constexpr int TPI = 1024 / ROWB;                     // tokens per load instruction
     constexpr int PIECES = ROWB / 16;
-    extern __shared__ __attribute__((aligned(16))) char lds_c[];
-    const int lane = threadIdx.x & (kWave - 1);
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int lane = tid & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
     const int li = lane & 31, lb = lane >> 5;
     const int rg = wave % RG, kw = wave / RG;
-    const unsigned epoch = a.rank_pad > 0 && a.T ? call_epoch(a.epoch) : 0u;
-    if ((int)blockIdx.x < a.n_t) {
-        for (int j = blockIdx.x; j < a.t_tiles; j += a.n_t) {
-            int rt, tr;
-            if (tile_on_die(j, a.rank_pad / 16, rt, tr)) t_tile<XF, AQ>(a, rt, tr, lds_c, epoch);
-        }
-        return;
-    }
-    int ot, tt;
-    if (!tile_on_die((int)blockIdx.x - a.n_t, a.tiles_o, ot, tt)) return;
     const int o0 = (ot * RG + rg) * RT * 32;             // this wavefront's rows
     const int t0 = tt * NT_ * 32;
     const uint32_t k = (uint32_t)a.k, rp = (uint32_t)a.rank_pad;
@@ -529,6 +522,16 @@ __global__ __launch_bounds__(kMidThreads, 3) void mid_kernel(MidArgs a)
 
     constexpr int UPR = G::UPR;
     const int units = mid_units<AQ>(a.rank_pad);         // of 32 ranks
+    // whether the wavefronts' waits ran out, behind the partial tiles
+    volatile int *const ran_out = reinterpret_cast<int *>(lds_c + G::PARTS);
+    static_assert(G::PARTS + kMidWaves * 4 <= G::BYTES, "LDS behind the partial tiles");
+    const bool may_help = !SECOND && a.n_t > 0 && a.rank_pad > 0;
+    auto any_ran_out = [&] {
+        int any = 0;
+#pragma unroll
+        for (int w = 0; w < kMidWaves; ++w) any |= ran_out[w];
+        return __builtin_amdgcn_readfirstlane(any) != 0;
+    };
     const int rounds = (a.stages + KW - 1) / KW, t_rounds = (units + KW * UPR - 1) / (KW * UPR);
     const rsrc_t dt = make_rsrc(a.T, mid_t_bytes<AQ>(a.m, a.rank_pad));
     const uint32_t kt = k / 128;
@@ -596,7 +599,7 @@ __global__ __launch_bounds__(kMidThreads, 3) void mid_kernel(MidArgs a)
         asm volatile("s_waitcnt vmcnt(0)" : : : "memory");
         __syncthreads();                 // the loads past the end have landed: LDS is free
         __syncthreads();
-        return;
+        return may_help && any_ran_out();
     }
 
     float16_t acc[RT][NT_];
@@ -772,9 +775,9 @@ __global__ __launch_bounds__(kMidThreads, 3) void mid_kernel(MidArgs a)
 #pragma unroll
                     for (int e = 0; e < 4; ++e) acc[i][it][4 * blk + e] *= rscale[i][blk][e] * xs;
     }
+    bool gave_up = false;
     if (t_rounds > 0) {
         const int made = (a.m + 15) / 16 * 16;       // tokens of T that exist; the lanes of the others take anything
-        bool gave_up = false;
         int spins = 0;
         for (int tr = 0; tr < t_rounds; ++tr) {
             // the UPR slots of this round
@@ -860,13 +863,14 @@ __global__ __launch_bounds__(kMidThreads, 3) void mid_kernel(MidArgs a)
                 }
             slot = slot + 1 == XRING ? 0 : slot + 1;
         }
-        if (gave_up && lane == 0) __hip_atomic_store(a.err, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (gave_up && !may_help && lane == 0) __hip_atomic_store(a.err, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
 
     // the KW partial tiles meet in LDS
     float4_t *const red = reinterpret_cast<float4_t *>(lds_c);
     asm volatile("s_waitcnt vmcnt(0)" : : : "memory");     // the loads past the end have landed
     __syncthreads();                         // and X has been read
+    if (may_help && lane == 0) ran_out[wave] = gave_up;
     if (kw > 0) {
 #pragma unroll
         for (int i = 0; i < RT; ++i)
@@ -878,7 +882,8 @@ __global__ __launch_bounds__(kMidThreads, 3) void mid_kernel(MidArgs a)
                         float4_t{acc[i][it][4 * blk], acc[i][it][4 * blk + 1], acc[i][it][4 * blk + 2], acc[i][it][4 * blk + 3]};
     }
     __syncthreads();
-    if (kw > 0) return;
+    if (may_help && any_ran_out()) return true;
+    if (kw > 0) return false;
     // store: lane holds token t0 + 32 it + li, rows 8 blk + 4 lb .. + 3 of tile i
     const bool vec_ok = (a.n & 3) == 0;
 #pragma unroll
@@ -908,6 +913,34 @@ __global__ __launch_bounds__(kMidThreads, 3) void mid_kernel(MidArgs a)
                 }
             }
     }
+    return false;
+}
+
+template <int NT_, int RT, int RG, int KW, int XF, bool AQ>
+__global__ __launch_bounds__(kMidThreads, 3) void mid_kernel(MidArgs a)
+{
+    extern __shared__ __attribute__((aligned(16))) char lds_c[];
+    const unsigned epoch = a.rank_pad > 0 && a.T ? call_epoch(a.epoch) : 0u;
+    if ((int)blockIdx.x < a.n_t) {
+        for (int j = blockIdx.x; j < a.t_tiles; j += a.n_t) {
+            int rt, tr;
+            if (tile_on_die(j, a.rank_pad / 16, rt, tr)) t_tile<XF, AQ>(a, rt, tr, lds_c, epoch);
+        }
+        return;
+    }
+    int ot, tt;
+    if (!tile_on_die((int)blockIdx.x - a.n_t, a.tiles_o, ot, tt)) return;
+    if (!y_role<NT_, RT, RG, KW, XF, AQ, false>(a, threadIdx.x, ot, tt, lds_c, epoch)) return;
+    for (int j = 0; j < a.rank_pad / 16 * 2 * NT_; ++j) {
+        const int tr = 2 * NT_ * tt + j % (2 * NT_);
+        if (16 * tr < a.m) t_tile<XF, AQ>(a, j / (2 * NT_), tr, lds_c, epoch);
+    }
+    asm volatile("s_waitcnt vmcnt(0)" : : : "memory");     // the pieces are in memory
+    __syncthreads();
+    // (a thread number the compiler knows nothing of: what it works out of it above would stay in registers until here)
+    unsigned tid = threadIdx.x;
+    asm volatile("" : "+v"(tid), "+s"(ot), "+s"(tt));
+    y_role<NT_, RT, RG, KW, XF, AQ, true>(a, (int)tid, ot, tt, lds_c, epoch);
 }
 
 // The T role of mid_kernel in a launch of its own.
@@ -950,6 +983,9 @@ static void launch_t_role(const TArgs &t, int xf, hipStream_t st)
     }
 }
 
+// Tests of the wait (slim_decode_override): nobody makes T, which ends in NaN, or the Y role has to make it.
+enum class WaitTest { none, fail, help };
+
 // Workgroups of the T role where both roles share a launch: what n_y workgroups of the Y role (one per compute unit)
 // leave free, if that makes T in at most `trips` tiles each; 0: T gets a launch of its own.
 static int t_workgroups(int t_tiles, int n_y, int cus, int trips)
@@ -960,15 +996,17 @@ static int t_workgroups(int t_tiles, int n_y, int cus, int trips)
 }
 
 template <int NT_, int RT, int RG, int KW, int XF, bool AQ>
-static int launch_mid(MidArgs a, bool wait_test, hipStream_t st)
+static int launch_mid(MidArgs a, WaitTest wait_test, hipStream_t st)
 {
     constexpr size_t lds = MidLds<NT_, RT, RG, KW, XF>::BYTES;
     a.tiles_o = (a.n + 32 * RT * RG - 1) / (32 * RT * RG);
     const int n_y = die_tiles(a.tiles_o, (a.m + 32 * NT_ - 1) / (32 * NT_));
     a.t_tiles = die_tiles(a.rank_pad / 16, (a.m + 15) / 16);
     int n_t = t_workgroups(a.t_tiles, n_y, device_info().cus, 2);
-    if (wait_test) {
+    if (wait_test == WaitTest::fail) {
         n_t = 0;                             // nobody makes T
+    } else if (wait_test == WaitTest::help && n_t > 0) {
+        a.t_tiles = 0;                       // the T role makes nothing
     } else if (a.t_tiles > 0 && n_t == 0) {
         TArgs t{};
         t.X = a.X;
@@ -1026,7 +1064,7 @@ static int mid_geometry(int n, int rank_pad, int m, int cus, bool weight_term)
 }
 
 template <int XF, bool AQ>
-static int launch_mid_call(const MidArgs &a, int geometry, bool wait_test, hipStream_t st)
+static int launch_mid_call(const MidArgs &a, int geometry, WaitTest wait_test, hipStream_t st)
 {
     switch (geometry) {
         case 0: return launch_mid<1, 1, 1, 8, XF, AQ>(a, wait_test, st);
@@ -1067,9 +1105,10 @@ int launch_gemm_mid(const slim_layer *layer, const half_t *X, int xf, const floa
     a.Ls = reinterpret_cast<const half_t *>(layer->Ls);
     a.T = static_cast<uint4_t *>(T);
     a.err = ctrl + 2;                        // read by slim_workspace_check
-    const bool wait_test = decode_path_override() == 3 && layer->rank_pad > 0;
+    const WaitTest wait_test = decode_path_override() != 3 || layer->rank_pad == 0 ? WaitTest::none : decode_lds_limit() == 0 ? WaitTest::fail : WaitTest::help;
     if (layer->rank_pad > 0) a.epoch = next_call_epoch(ctrl + 3, st);
-    a.spin_limit = wait_test ? 256 : 1 << 16;
+    // (a poll takes half a microsecond or more; T is there after a few where the T role runs)
+    a.spin_limit = wait_test != WaitTest::none ? 256 : 2048;
     a.Y = Y;
     a.n = s.n;
     a.k = s.k;

@@ -156,3 +156,64 @@ def test_large_tiles_with_inputs_divided(n, k, r, m, bits):
     """Tiles of 128 to 384 rows: two groups of wavefronts take every other stage and unit of ranks; one stage (the
     second group has none), odd counts, fewer ranks than a unit."""
     assert _forward_case(_shape(n, k, r), m, B.slim_linear_gemm, seed=28, bits=bits) <= TOL_Y
+
+
+# one launch for T and Y, with each of the four tile shapes (64 rows x 32 tokens with several tiles of tokens, and more ranks
+# than one round of the adapter term)
+HELP_CASES = [(512, 512, 51, 17), (33, 128, 33, 31), (700, 4096, 409, 33), (4096, 256, 64, 64), (5000, 1408, 96, 40),
+              (2049, 640, 200, 96), (9001, 384, 65, 48), (20003, 384, 130, 64)]
+
+
+@pytest.mark.parametrize("kind", ["fp16", "q4", "fp8", "fp8_q4"])
+@pytest.mark.parametrize("n,k,r,m", HELP_CASES)
+def test_a_workgroup_whose_wait_runs_out_makes_t_itself(n, k, r, m, kind, decode_override):
+    """The T role makes nothing (forced from the host), as if other work on the chip kept it from being dispatched: the waits run out
+    after 256 polls, and every workgroup makes T of its tokens and starts again.  The bounds are the usual ones."""
+    decode_override("wait_test", 16)
+    bits = 4 if kind.endswith("q4") else 16
+    if kind.startswith("fp8"):
+        err, _ = _fp8_forward_case(n, k, r, m, seed=29, bits=bits)
+    else:
+        err = _forward_case(_shape(n, k, r), m, B.slim_linear_gemm, seed=29, bits=bits)
+    assert err <= TOL_Y
+
+
+def test_a_forced_wait_leaves_the_same_bits_and_no_error(decode_override):
+    shape = _shape(5000, 1408, 96)
+    W, L, R, X = wl.make_layer(shape, 40, seed=30)
+    layer = _gpu_layer(W, L, R)
+    ws = B.alloc_workspace(layer, 40)
+    Y = B.slim_linear_gemm(layer, X.to(DEV), workspace=ws)
+    decode_override("wait_test", 16)
+    Y2 = B.slim_linear_gemm(layer, X.to(DEV), workspace=ws)
+    Z2 = B.slim_lowrank(X.to(DEV), layer.R, layer.L, 5000, 96, workspace=ws)
+    decode_override("auto")
+    Z = B.slim_lowrank(X.to(DEV), layer.R, layer.L, 5000, 96, workspace=ws)
+    torch.cuda.synchronize()
+    B.slim_workspace_check(ws)
+    assert torch.equal(Y, Y2) and torch.equal(Z, Z2)
+
+
+def test_overlapping_small_batch_calls():
+    """Small-batch calls on four streams at a time, each taking whole compute units and waiting for its own T, in a new
+    order each time: every result is the one of the call alone, and no wait was lost."""
+    m = 40
+    shapes = [(5000, 1408, 96), (9001, 384, 65), (4096, 1024, 102), (5000, 1408, 200)]
+    streams = [torch.cuda.Stream(device=DEV) for _ in shapes]
+    jobs = []
+    for i, (n, k, r) in enumerate(shapes):
+        W, L, R, X = wl.make_layer(_shape(n, k, r), m, seed=40 + i)
+        layer, Xd = _gpu_layer(W, L, R), X.to(DEV)
+        alone = B.slim_linear_gemm(layer, Xd)
+        jobs.append((layer, Xd, alone, B.alloc_workspace(layer, m), [torch.empty_like(alone) for _ in range(12)]))
+    torch.cuda.synchronize()
+    for call in range(12):
+        for i in range(len(jobs)):
+            j = (i + call) % len(jobs)
+            layer, Xd, _, ws, outs = jobs[j]
+            with torch.cuda.stream(streams[j]):
+                B.slim_linear_gemm(layer, Xd, Y=outs[call], workspace=ws)
+    torch.cuda.synchronize()
+    for layer, Xd, alone, ws, outs in jobs:
+        B.slim_workspace_check(ws)
+        assert all(torch.equal(alone, y) for y in outs)
