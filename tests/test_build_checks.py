@@ -27,3 +27,21 @@ def test_compiler_uses_of_accumulation_registers_are_found():
     parks there (a store index, once: an out-of-bounds store).  The build reads the device assembly and
     refuses such a library; here the reader itself, on a clean kernel and on one with three parked values."""
     assert compiler_agpr_uses(ASM) == {"_ZN4slim6parkedE": 3}
+
+
+def test_counts_that_hand_results_over_order_memory():
+    """A workgroup that learns from a count that others have ended reads what they stored: where the result of an
+    atomic add is compared, the add releases what came before it, and an acquire follows before anything is read."""
+    import glob
+    import os
+    import re
+    from paper_2410_09615_amd.build import CSRC
+    found = 0
+    for path in glob.glob(os.path.join(CSRC, "*.hip")) + glob.glob(os.path.join(CSRC, "*.h")):
+        with open(path) as fh:
+            text = fh.read()
+        for call in re.finditer(r"__hip_atomic_fetch_add\(((?:[^();]|\([^()]*\))*)\)\s*==", text):
+            found += 1
+            after = text[call.end():].split(";")[0]
+            assert "__ATOMIC_RELEASE" in call.group(1) and "fence(__ATOMIC_ACQUIRE" in after, (path, call.group(0))
+    assert found == 2
