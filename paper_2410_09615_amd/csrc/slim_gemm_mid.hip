@@ -122,12 +122,12 @@ __device__ __forceinline__ void load_to_lds(rsrc_t r, uint32_t lane_off, uint32_
         asm volatile("s_mov_b32 m0, %3\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, %2 offen sc1 lds"
                      :
                      : "v"(lane_off), "s"(r), "s"(uniform_off), "s"(lds_byte)
-                     : "memory");
+                     : "memory", "m0");
     else
         asm volatile("s_mov_b32 m0, %3\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, %2 offen lds"
                      :
                      : "v"(lane_off), "s"(r), "s"(uniform_off), "s"(lds_byte)
-                     : "memory");
+                     : "memory", "m0");
 }
 
 // T tile of 16 ranks x 16 tokens.  A unit is 256 inputs: eight steps of V_MFMA_F32_16X16X32_F16, R from memory

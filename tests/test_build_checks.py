@@ -45,3 +45,21 @@ def test_counts_that_hand_results_over_order_memory():
             after = text[call.end():].split(";")[0]
             assert "__ATOMIC_RELEASE" in call.group(1) and "fence(__ATOMIC_ACQUIRE" in after, (path, call.group(0))
     assert found == 2
+
+
+def test_asm_that_writes_m0_says_so():
+    """The compiler keeps values of its own in m0 (indexed registers, its own loads to LDS): asm that writes it
+    names it among what it clobbers."""
+    import glob
+    import os
+    import re
+    from paper_2410_09615_amd.build import CSRC
+    found = 0
+    for path in glob.glob(os.path.join(CSRC, "*.hip")) + glob.glob(os.path.join(CSRC, "*.h")):
+        with open(path) as fh:
+            text = fh.read()
+        for block in re.findall(r'asm volatile\(\s*"[^;]*;', text):
+            if re.search(r'"[^"]*\bs_mov_b32 m0\b', block):
+                found += 1
+                assert '"m0"' in block.split(":")[-1], (path, block)
+    assert found == 2
