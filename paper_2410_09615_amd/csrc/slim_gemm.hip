@@ -221,7 +221,7 @@ int gemm_t_splits(int32_t m, int32_t rank_pad, int32_t k)
 
 int launch_t_product(const half_t *X, int xf, const float *x_scale, int m, int k, const half_t *R, const uint8_t *Rq, const half_t *Rs, int rank,
                      int rank_pad, half_t *T, hipStream_t st);   // slim_gemm_mid.hip
-bool t_in_one_launch(int rank_pad, int m, int k);                      // slim_gemm_mid.hip
+int t_kind(int rank_pad, int m, int k, bool q4, bool split);           // slim_gemm_mid.hip
 
 // T fp16 [m][rank_pad] = X R^T.  xf: 0 = X fp16; 1, 2 = X as E4M3 / E5M2 codes (one byte per value) with the
 // tensor's scale at x_scale: T = scale * (value(X) R^T).
@@ -233,7 +233,7 @@ static int launch_t(const half_t *X, int m, const half_t *R, int k, int rank_pad
     if ((uint64_t)rank_pad * (uint64_t)k * 2 > 0xFFFFFFFFull) return SLIM_ERR_SHAPE;
     const int chunk = token_chunk(k);
     if (chunk < 128) return SLIM_ERR_SHAPE;
-    if (t_in_one_launch(rank_pad, m, k) && (uint64_t)(m + 64) * k * 2 < 0x80000000ull && (uint64_t)(rank_pad + 64) * k * 2 < 0x80000000ull)
+    if (t_kind(rank_pad, m, k, !R, true) != 4 && (uint64_t)(m + 64) * k * 2 < 0x80000000ull && (uint64_t)(rank_pad + 64) * k * 2 < 0x80000000ull)
         return launch_t_product(X, xf, x_scale, m, k, R, Rq, Rs, rank, rank_pad, T, st);
     DenseGemmArgs g{};
     g.A = R;

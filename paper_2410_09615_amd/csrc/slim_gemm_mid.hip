@@ -31,6 +31,8 @@
 
 namespace slim {
 
+int gemm_t_splits(int32_t m, int32_t rank_pad, int32_t k);   // slim_gemm.hip
+
 typedef int int4_t __attribute__((ext_vector_type(4)));
 typedef int int8v_t __attribute__((ext_vector_type(8)));
 
@@ -414,11 +416,58 @@ static void launch_t_tiles(TArgs a, int xf, hipStream_t st)
     }
 }
 
-static int t_shape(int rank_pad, int m, int k);
+// ---- which kernel makes T ----
+// 0, 1, 2: t_product_kernel with tiles of 32 x 32, 32 x 64, 64 x 64 (ranks x tokens); 3: the 16 x 16 tiles of the T role; 4: the
+// split product of slim_gemm.hip and the launch that adds it up.  The one whose estimated time is the shortest.  A kind
+// that deals its tiles to the dies takes as many rounds as its fullest die has tiles for its compute units (with 10 tiles of
+// tokens two dies have two, and 18 rank tiles make that 36 workgroups on 32 units: twice the time), and
+//   time = a + rounds (b + k / 1000 (c + d w)),   w = the share of that die's units with a tile in the first round;
+// the split product's is a + rounds c k / 1000 of a share + d per million partial sums.  The constants (us) are
+// fitted to 6048 measured products (ranks 32 to 1408, 17 to 4096 tokens, 512 to 28672 inputs, X in fp16 and 8 bits, R in
+// fp16 and 4 bits): off by 5 to 15 %, which makes the kind taken 1 % slower than the best one on average.  What is wrong
+// is rather the one launch (memory the dies share is in d only), so the split product is taken from 10 % more on: of those 6048,
+// the kind taken is slower than the split product by more than 3 % in 37, all but 13 by less than 8 %.
+//   8192 inputs, fp16 (us; kinds 0 to 4): rank 64 at 800 tokens 10.6 / 14.8 / 20.5 / 20.3 / 19.8, rank 512 at 1000 tokens
+//   27.0 / 20.6 / 25.8 / - / 24.9, rank 832 at 600 tokens 37.1 / 37.2 / 27.6 / - / 25.8, at 1000 tokens 49.2 / 37.5 / 27.8 / - / 33.7.
+struct TCost {
+    double a, b, c, d;
+};
+constexpr TCost kTCost[2][5] = {{{2.2, 1.1, 0.8, 0.5}, {2.0, 1.3, 1.2, 0.7}, {2.9, 1.4, 1.8, 1.1}, {1.9, 1.5, 0.3, 0.2}, {6.7, 0.0, 10.9, 2.2}},      // R in fp16
+                                {{1.9, 1.6, 0.9, 0.2}, {1.8, 1.8, 1.4, 0.3}, {2.3, 2.4, 2.1, 0.7}, {1.6, 2.1, 0.5, 0.2}, {7.1, 0.0, 16.0, 2.2}}};     // in 4 bits
+
+static double t_cost(int kind, int rank_pad, int m, int k, bool q4)
+{
+    const TCost &c = kTCost[q4][kind];
+    const int cus = device_info().cus;
+    if (kind == 4) {
+        const int splits = gemm_t_splits(m, rank_pad, k);
+        const long tiles = (long)((rank_pad + 255) / 256) * ((m + 127) / 128) * splits;
+        const double sums = splits > 1 ? (double)splits * m * rank_pad * 1e-6 : 0.0;
+        return 0.9 * (c.a + (double)((tiles + cus - 1) / cus) * c.c * k / splits * 1e-3 + c.d * sums);
+    }
+    // tiles along the side that is dealt to the dies, and along the other
+    constexpr int kSide[4][2] = {{32, 32}, {64, 32}, {64, 64}, {16, 16}};
+    const int dealt = kind == 3 ? rank_pad : m, other = kind == 3 ? m : rank_pad;
+    const long sides = (dealt + kSide[kind][0] - 1) / kSide[kind][0];
+    const long per_die = (sides + kDies - 1) / kDies * ((other + kSide[kind][1] - 1) / kSide[kind][1]);
+    const long units = cus / kDies > 0 ? cus / kDies : 1;
+    const double w = per_die < units ? (double)per_die / units : 1.0;
+    return c.a + (double)((per_die + units - 1) / units) * (c.b + k * 1e-3 * (c.c + c.d * w));
+}
+
+// `split`: the split product may be taken (it leaves T as rows, not as pieces)
+int t_kind(int rank_pad, int m, int k, bool q4, bool split)
+{
+    int best = 0;
+    for (int kind = 1; kind < (split ? 5 : 4); ++kind)
+        if (t_cost(kind, rank_pad, m, k, q4) < t_cost(best, rank_pad, m, k, q4)) best = kind;
+    return best;
+}
+
 static void launch_t_role(const TArgs &a, int xf, hipStream_t st);
 static int launch_t_product_args(const TArgs &a, int xf, hipStream_t st)
 {
-    switch (t_shape(a.rank_pad, a.m, a.k)) {
+    switch (t_kind(a.rank_pad, a.m, a.k, a.Rq != nullptr, false)) {
         case 3: launch_t_role(a, xf, st); break;
         case 0: launch_t_tiles<1, 1>(a, xf, st); break;
         case 1: launch_t_tiles<1, 2>(a, xf, st); break;
@@ -445,35 +494,6 @@ int launch_t_product(const half_t *X, int xf, const float *x_scale, int m, int k
     a.m = m;
     a.T = T;
     return launch_t_product_args(a, xf, st);
-}
-
-// 0, 1, 2: t_product_kernel's tiles of 32 x 32, 32 x 64, 64 x 64; 3: those of 16 x 16 of the T role above.
-// The smallest tile with which the product is one round of workgroups: a small tile shortens a workgroup's chain, a
-// second round doubles it (m = 333, rank 416, whole call on 11008 x 4096: 45.2 / 46.9 / 50.8 us with tiles of
-// 32 x 32, 32 x 64, 64 x 64; m = 700 with 8-bit inputs on 2100 x 4096: 43.9 / 40.6 / 45.6; m = 1000, rank 832
-// on 8192 x 8192: 137.8 / 126.5 / 117.4).
-// Beyond 4096 inputs 11/16 of a round, and the 16 x 16 tiles up to 512 tokens, because small tiles read both operands more
-// often and the chain hides it no longer (k = 11008, adapter term alone: 800 tokens, rank 64 in 200 tiles of 16 x 16 31.7 us,
-// in 50 of 32 x 32 21.6; rank 608, 300 tokens in 190 of 32 x 32 43.8, in 95 of 32 x 64 36.5; 512 tokens in 152 of
-// 32 x 64 37.4, in 80 of 64 x 64 45.2).
-static int t_shape(int rank_pad, int m, int k)
-{
-    const long ranks32 = rank_pad / 32, tokens32 = (m + 31) / 32, cus = device_info().cus, most = k > 4096 ? cus * 11 / 16 : cus;
-    if (2 * ranks32 * ((m + 15) / 16) <= cus && (k <= 4096 || m <= 512)) return 3;
-    if (ranks32 * tokens32 <= most) return 0;
-    return ranks32 * ((tokens32 + 1) / 2) <= most ? 1 : 2;
-}
-
-// Whether t_product_kernel makes T for the large tiles, or the split product of slim_gemm.hip: up to two rounds of
-// its largest tile, one beyond 4096 inputs (k = 11008, adapter term alone: rank 608 at 1500 tokens, 240 tiles, 58 against
-// 81 us; at 2500, 400 tiles, 91 against 84; k = 8192, rank 832 at 1500 tokens, 312 tiles, 111 against 100), and
-// where R, which every die reads, is beyond 16 MiB only with tiles of 16 x 16 (k = 11008, rank 1120: at 40 tokens 22.7
-// against 36.2, at 150 65 against 49).
-bool t_in_one_launch(int rank_pad, int m, int k)
-{
-    if ((long)rank_pad * k * 2 > (16L << 20)) return t_shape(rank_pad, m, k) == 3;
-    const long tiles = (long)((rank_pad + 63) / 64) * ((m + 63) / 64), cus = device_info().cus;
-    return tiles <= (k > 4096 ? cus : 2 * cus);
 }
 
 // Geometry of mid_kernel: the LDS of a round of X (shared) and of a round of weights (private to the wavefronts),

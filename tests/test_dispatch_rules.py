@@ -1,0 +1,49 @@
+"""Host logic: which kernel a call is sent to.  The times are measured ones (us, MI355X, products alone in a
+row), those of the sizes where one rule or another once chose badly; asked is that the kind chosen takes at most a tenth longer than
+the best of them, which is what the estimates behind the rule are good for.  (The rules ask the device for its
+compute units; without one they plan for 256.)"""
+import ctypes
+
+import pytest
+
+from paper_2410_09615_amd import binding as B
+
+
+def _t_kind(rank_pad, m, k, q4, split):
+    f = B.lib()._ZN4slim6t_kindEiiibb
+    f.argtypes = [ctypes.c_int] * 3 + [ctypes.c_bool] * 2
+    return f(rank_pad, m, k, q4, split)
+
+
+NO = float("inf")
+
+
+@pytest.mark.parametrize("q4,k,rank_pad,m,us", [
+    (False, 512, 64, 128, [4.4, 4.4, 5.5, 3.9, 11.2]),
+    (False, 2048, 32, 2048, [5.1, 6.5, 8.4, 16.2, 12.8]),
+    (False, 4096, 128, 1500, [8.0, 9.5, 12.9, 21.1, 17.6]),
+    (False, 8192, 64, 800, [10.6, 14.8, 20.5, 20.3, 19.8]),
+    (False, 8192, 416, 1000, [26.0, 20.2, 25.0, NO, 24.2]),
+    (False, 8192, 512, 800, [26.5, 20.4, 26.2, NO, 23.6]),
+    (False, 8192, 832, 512, [27.4, 21.8, 27.6, NO, 24.4]),
+    (False, 11008, 1120, 64, [35.7, 49.6, 33.5, 17.6, 23.4]),
+    (False, 13824, 128, 3000, [42.0, 31.5, 39.9, NO, 32.6]),
+    (False, 13824, 608, 600, [40.8, 59.1, 41.4, NO, 32.8]),
+    (False, 28672, 224, 2048, [78.3, 62.2, 74.6, NO, 52.1]),
+    (False, 28672, 1408, 48, [85.4, 107.4, 75.9, 41.1, 45.7]),
+    (True, 4096, 512, 2048, [28.6, 21.8, 17.9, NO, 28.2]),
+    (True, 8192, 832, 1000, [47.8, 37.8, 29.7, NO, 35.6]),
+    (True, 11008, 128, 2048, [18.4, 26.9, 39.5, NO, 34.7]),
+])
+def test_the_kind_of_t_product(q4, k, rank_pad, m, us):
+    assert us[_t_kind(rank_pad, m, k, q4, True)] <= 1.1 * min(us)
+    assert us[_t_kind(rank_pad, m, k, q4, False)] <= 1.1 * min(us[:4])
+
+
+def test_the_kind_of_t_product_is_always_one():
+    for k in (128, 4096, 28672):
+        for rank_pad in (32, 1024, 4096):
+            for m in (17, 1000, 100000):
+                for q4 in (False, True):
+                    assert 0 <= _t_kind(rank_pad, m, k, q4, True) <= 4
+                    assert 0 <= _t_kind(rank_pad, m, k, q4, False) <= 3

@@ -217,3 +217,20 @@ def test_overlapping_small_batch_calls():
     for layer, Xd, alone, ws, outs in jobs:
         B.slim_workspace_check(ws)
         assert all(torch.equal(alone, y) for y in outs)
+
+
+@pytest.mark.parametrize("kind", ["fp16", "q4", "fp8", "fp8_q4"])
+@pytest.mark.parametrize("n,k,r,m,t_kind", [
+    (28672, 256, 30, 256, (3, 0)), (200, 512, 51, 530, (0, 0)), (200, 1024, 200, 1100, (1, 1)), (200, 1152, 130, 2600, (1, 1)),
+    (200, 2048, 200, 4000, (2, 2)), (100, 128, 1024, 3000, (4, 4)), (60, 8192, 800, 1500, (4, 4))])
+def test_every_kind_of_t_product(n, k, r, m, t_kind, kind):
+    """T as rows for the large tiles by each of its kernels (the rule's choice is checked, so that a later rule does not
+    take the coverage away): token tiles that the dies do not divide evenly, the last tiles partly empty."""
+    from test_dispatch_rules import _t_kind
+    bits = 4 if kind.endswith("q4") else 16
+    assert _t_kind(B.slim_rank_pad(r), m, k, bits == 4, True) == t_kind[bits == 4]
+    if kind.startswith("fp8"):
+        err, _ = _fp8_forward_case(n, k, r, m, seed=31, bits=bits)
+    else:
+        err = _forward_case(_shape(n, k, r), m, B.slim_linear_gemm, seed=31, bits=bits)
+    assert err <= TOL_Y
