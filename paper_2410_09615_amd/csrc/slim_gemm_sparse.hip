@@ -10,7 +10,7 @@
 // end.  One wavefront per SIMD leaves the matrix pipe idle half of the time (its
 // conversions and waits are in line with its matrix instructions); the 512-row tile has
 // no registers for a second one, these have (11008 x 4096 at 333 tokens, all of it such tiles: 54.0 -> 51.4 us;
-// 2048 tokens with 8-bit inputs 155.5 -> 151.1).
+// 2048 tokens with 8-bit inputs 155.5 -> 151.1).  On short sums four wavefronts do it alone: see two_groups().
 //   A (weights): never touches LDS.  Per 128 inputs a lane loads 16 bytes of
 //     codes and 8 bytes of positions of each of its rows straight from global
 //     memory (two stages ahead; the packed layout makes each load instruction one
@@ -567,6 +567,16 @@ static void plan_tiles(SparseGemmArgs &a, int slots)
     a.per_die = slots % kDies == 0 ? slots / kDies : 0;
 }
 
+// Whether two groups of wavefronts share the tiles of fewer than 512 rows: from as many stages (of 128 inputs and of 128 ranks) on
+// as pay for the second group's start and for adding up.  Time with two groups over time with one, whole calls on
+// 512 to 28672 rows at 64 to 2048 tokens, without adapters and with rank 64:
+//   inputs            512    1024   1536   2048   4096   8192
+//   fp16 (AT = 1)     1.09   1.05   1.04   1.01   0.95   0.94
+//   8 bits (AT = 1)   1.04   0.98   0.93   0.90   0.84   0.78
+//   fp16 (AT = 2)     1.07   1.04   1.02   1.00   0.98   0.96
+//   8 bits (AT = 2)   1.07   1.02   0.99   0.98   0.92   0.88
+bool two_groups(int k, int rank_pad, bool fp8) { return (k + SG_BK - 1) / SG_BK + (rank_pad + SG_BK - 1) / SG_BK > (fp8 ? 10 : 18); }
+
 // Buffer offsets are 32 bits wide: the caller has checked that the weight and
 // adapter matrices stay below 4 GiB each; X, T and Y are walked in token chunks
 // that do.
@@ -599,8 +609,8 @@ int launch_gemm_sparse(const uint8_t *qvals, const uint8_t *meta, const float *s
         a.Y = Y + (size_t)t0 * n;
         plan_tiles(a, device_info().cus);
         const int n_rem = a.rem_split * (a.tiles_total - a.n_full);
-        auto launch = [&](auto atc, unsigned grid) {
-            constexpr int AT = decltype(atc)::value, KW = AT < 4 ? 2 : 1;
+        auto launch = [&](auto atc, auto kwc, unsigned grid) {
+            constexpr int AT = decltype(atc)::value, KW = decltype(kwc)::value;
             const size_t lds = (size_t)KW * 2 * SG_STAGE * sizeof(half_t);      // (the groups' partial tiles, 64 AT KiB, fit)
             if (xf == 0)
                 hipLaunchKernelGGL((gemm_sparse_kernel<AT, 0, KW>), dim3(grid), dim3(256 * KW), lds, st, a);
@@ -609,9 +619,21 @@ int launch_gemm_sparse(const uint8_t *qvals, const uint8_t *meta, const float *s
             else
                 hipLaunchKernelGGL((gemm_sparse_kernel<AT, 2, KW>), dim3(grid), dim3(256 * KW), lds, st, a);
         };
-        if (a.n_full > 0) launch(std::integral_constant<int, 4>{}, (unsigned)a.n_full);
-        if (n_rem > 0 && a.rem_split == 2) launch(std::integral_constant<int, 2>{}, (unsigned)n_rem);
-        if (n_rem > 0 && a.rem_split == 4) launch(std::integral_constant<int, 1>{}, (unsigned)n_rem);
+        using std::integral_constant;
+        const bool two = two_groups(k, rank_pad, xf != 0);
+        if (a.n_full > 0) launch(integral_constant<int, 4>{}, integral_constant<int, 1>{}, (unsigned)a.n_full);
+        if (n_rem > 0 && a.rem_split == 2) {
+            if (two)
+                launch(integral_constant<int, 2>{}, integral_constant<int, 2>{}, (unsigned)n_rem);
+            else
+                launch(integral_constant<int, 2>{}, integral_constant<int, 1>{}, (unsigned)n_rem);
+        }
+        if (n_rem > 0 && a.rem_split == 4) {
+            if (two)
+                launch(integral_constant<int, 1>{}, integral_constant<int, 2>{}, (unsigned)n_rem);
+            else
+                launch(integral_constant<int, 1>{}, integral_constant<int, 1>{}, (unsigned)n_rem);
+        }
     }
     return hip_status(hipGetLastError());
 }

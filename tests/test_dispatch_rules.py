@@ -48,3 +48,19 @@ def test_the_kind_of_t_product_is_always_one():
                 for q4 in (False, True):
                     assert 0 <= _t_kind(rank_pad, m, k, q4, True) <= 4
                     assert 0 <= _t_kind(rank_pad, m, k, q4, False) <= 3
+
+
+def _two_groups(k, rank_pad, fp8):
+    f = B.lib()._ZN4slim10two_groupsEiib
+    f.argtypes = [ctypes.c_int] * 2 + [ctypes.c_bool]
+    f.restype = ctypes.c_bool
+    return f(k, rank_pad, fp8)
+
+
+@pytest.mark.parametrize("fp8,k,rank_pad,ratio", [
+    (False, 128, 0, 1.12), (False, 512, 0, 1.09), (False, 1024, 0, 1.05), (False, 1024, 128, 1.05), (False, 2048, 64, 1.02),
+    (False, 4096, 0, 0.95), (False, 4096, 416, 0.94), (False, 8192, 832, 0.94), (False, 11008, 0, 0.94),
+    (True, 128, 0, 1.10), (True, 512, 64, 1.05), (True, 1536, 0, 0.96), (True, 2048, 64, 0.95), (True, 4096, 416, 0.88)])
+def test_two_groups_of_wavefronts_where_they_pay(fp8, k, rank_pad, ratio):
+    """ratio: time of a call with two groups over that with one, measured (mean of calls on 512 to 28672 rows)."""
+    assert _two_groups(k, rank_pad, fp8) == (ratio < 1.0)

@@ -348,8 +348,9 @@ def test_gemm_ragged_shapes(n, k, r, m):
 @pytest.mark.parametrize("stages", [1, 2, 3, 4, 5, 6, 7, 9, 12, 13])
 @pytest.mark.parametrize("fp8", [False, True])
 def test_gemm_every_stage_count_modulo_six(stages, fp8):
-    """The main loops are written out for six stages of 128 inputs (three register sets of weights, two of X):
-    every residue of the stage count, below and above one pass of the loop, on fp16 and on 8-bit inputs."""
+    """Every residue of the stage count modulo six, below and above six, on fp16 and on 8-bit inputs, at a size of the
+    small-batch kernel (rounds of eight wavefronts' stages; the main loops of the large tiles, written out for six stages, are in
+    test_gpu_small_batch.py)."""
     n, k, r, m = 200, 128 * stages, 20, 130
     if fp8:
         err, _ = _fp8_forward_case(n, k, r, m, seed=stages)

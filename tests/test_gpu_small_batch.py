@@ -3,6 +3,7 @@ csrc/slim_gemm_mid.hip) against the oracle, at the sizes where that path can go 
 shapes with whole, ragged and partly empty tiles, T made in the same launch and in one of its own, one stage of
 inputs, stage counts that are no multiple of a round, ranks below and beyond whole rounds of the adapter term.
 The bounds are those of parity.py."""
+import numpy as np
 import pytest
 import torch
 
@@ -122,7 +123,8 @@ def test_a_wait_that_gives_up_is_loud(bits, decode_override):
 @pytest.mark.parametrize("stages", [1, 2, 3, 4, 5, 6, 7])
 @pytest.mark.parametrize("fp8", [False, True])
 def test_large_tiles_every_stage_count_modulo_six(stages, fp8):
-    """The main loops of the 512 x 128 tiles (above 512 tokens) are written out for six stages."""
+    """Above 512 tokens the main loops are written out for six stages; here on tiles of 128 rows (test_large_tiles has the
+    taller ones)."""
     n, k, r, m = 200, 128 * stages, 20, 530
     if fp8:
         err, _ = _fp8_forward_case(n, k, r, m, seed=stages)
@@ -153,8 +155,7 @@ def test_t_in_one_launch(n, k, r, m, kind):
 @pytest.mark.parametrize("n,k,r,m", [(1, 128, 0, 513), (33, 256, 31, 530), (100, 384, 33, 600), (129, 640, 129, 530), (1000, 1152, 300, 540)])
 @pytest.mark.parametrize("bits", [16, 4])
 def test_large_tiles_with_inputs_divided(n, k, r, m, bits):
-    """Tiles of 128 to 384 rows: two groups of wavefronts take every other stage and unit of ranks; one stage (the
-    second group has none), odd counts, fewer ranks than a unit."""
+    """Tiles of 128 rows with few stages: one stage, odd counts, fewer ranks than a unit, no rows beyond the first."""
     assert _forward_case(_shape(n, k, r), m, B.slim_linear_gemm, seed=28, bits=bits) <= TOL_Y
 
 
@@ -233,4 +234,35 @@ def test_every_kind_of_t_product(n, k, r, m, t_kind, kind):
         err, _ = _fp8_forward_case(n, k, r, m, seed=31, bits=bits)
     else:
         err = _forward_case(_shape(n, k, r), m, B.slim_linear_gemm, seed=31, bits=bits)
+    assert err <= TOL_Y
+
+
+def _tile_height(n, m):
+    """Rows of a tile / 128 of slim_linear_gemm's large tiles, where one launch has them all."""
+    tiles, whole, _ = B.slim_gemm_tile_order(n, m)
+    assert whole in (0, tiles)
+    return 4 if whole else 2 if 4 * tiles > 256 else 1
+
+
+@pytest.mark.parametrize("kind", ["fp16", "q4", "fp8", "fp8_q4"])
+@pytest.mark.parametrize("groups,stages", [(1, s) for s in (1, 2, 3, 4, 5, 6, 7)] + [(2, s) for s in (18, 19, 21, 22, 23, 25, 27)])
+@pytest.mark.parametrize("height,n,m", [(4, 5120, 1663), (2, 5120, 870), (1, 200, 530)])
+def test_large_tiles(height, n, m, groups, stages, kind):
+    """The main loops of the tiles of 512, 256 and 128 rows, written out for six stages of 128 inputs, on stage counts of every
+    remainder, below and above one pass; on the lower two by one group of wavefronts and by two (with odd counts, where the second
+    group's last stage does not exist), whose share of the stages has every remainder modulo six too.  What
+    tile and how many groups a size gets is checked, so that a later rule does not take the coverage away."""
+    from test_dispatch_rules import _two_groups
+    k, r = 128 * stages, 20
+    assert _tile_height(n, m) == height
+    assert _two_groups(k, B.slim_rank_pad(r), False) == (groups == 2)
+    if kind.startswith("fp8") and groups == 2:
+        k -= 128 * 6                    # 8-bit inputs: two groups from ten stages on
+        assert _two_groups(k, B.slim_rank_pad(r), True)
+    rows = np.unique(np.r_[0, n - 1, np.random.default_rng(stages).integers(0, n, 40)])
+    bits = 4 if kind.endswith("q4") else 16
+    if kind.startswith("fp8"):
+        err, _ = _fp8_forward_case(n, k, r, m, seed=stages, bits=bits, rows=rows)
+    else:
+        err = _forward_case(_shape(n, k, r), m, B.slim_linear_gemm, seed=stages, bits=bits, rows=rows)
     assert err <= TOL_Y
