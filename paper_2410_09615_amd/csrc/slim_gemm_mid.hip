@@ -1065,11 +1065,9 @@ constexpr int kMidTiles[4][2] = {{32, 32}, {64, 32}, {128, 32}, {128, 64}};
 // 14.5 / 20.4 (31), 512 tokens 76 / 46 / 37 / 31 (36).  Where no tile fits, the large ones win: 11008 x 4096 at 256
 // tokens 36.6 against 49.7.
 // The adapter term alone has nothing to hide a chain of T behind: 4096 x 4096 at 128 tokens 15.7 / 12.5 / 15.2 / 20.1
-// against 14.1 of the dense product, 28672 x 4096 at 48 tokens 20.2 at best against 13.6; and where T in a launch of its
-// own takes longer than the split product, which leaves no pieces, nothing here makes up for it (8192 x 28672 at 192
-// tokens, rank 832: 66.7 against 60.3).
+// against 14.1 of the dense product, 28672 x 4096 at 48 tokens 20.2 at best against 13.6.
 // Above 512 tokens the workspace has no room for the pieces of T.
-int mid_geometry(int n, int k, int rank_pad, int m, int cus, bool weight_term)
+static int mid_geometry(int n, int rank_pad, int m, int cus, bool weight_term)
 {
     if (m > 512) return -1;
     const int t_tiles = die_tiles(rank_pad / 16, (m + 15) / 16);
@@ -1079,7 +1077,6 @@ int mid_geometry(int n, int k, int rank_pad, int m, int cus, bool weight_term)
         if (n_y > cus) continue;
         if (t_tiles == 0) return g;
         if (!weight_term) {
-            if (t_workgroups(t_tiles, n_y, cus, 2) == 0 && t_kind(rank_pad, m, k, false, true) == 4) continue;
             if (g < 3 && n < 16384) return g;
             if (t_workgroups(t_tiles, n_y, cus, 1) > 0) return g;
             continue;
@@ -1109,7 +1106,7 @@ int launch_gemm_mid(const slim_layer *layer, const half_t *X, int xf, const floa
     *taken = false;
     const slim_shape s = layer->shape;
     const bool q4 = layer->adapter_bits == 4 && s.rank > 0;
-    const int geometry = mid_geometry(s.n, s.k, layer->rank_pad, m, device_info().cus, weight_term);
+    const int geometry = mid_geometry(s.n, layer->rank_pad, m, device_info().cus, weight_term);
     if (geometry < 0) return SLIM_OK;
     // 32-bit offsets, tiles past the end included; room for the pieces of T
     constexpr uint64_t kLimit = 0x80000000ull;

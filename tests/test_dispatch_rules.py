@@ -64,12 +64,3 @@ def _two_groups(k, rank_pad, fp8):
 def test_two_groups_of_wavefronts_where_they_pay(fp8, k, rank_pad, ratio):
     """ratio: time of a call with two groups over that with one, measured (mean of calls on 512 to 28672 rows)."""
     assert _two_groups(k, rank_pad, fp8) == (ratio < 1.0)
-
-
-@pytest.mark.parametrize("n,k,rank_pad,m,small", [
-    (4096, 4096, 416, 128, True), (4096, 1024, 128, 48, True), (28672, 4096, 416, 48, False), (8192, 28672, 832, 192, False)])
-def test_the_adapter_term_alone_on_a_small_batch(n, k, rank_pad, m, small):
-    """Measured (us, small tiles / dense products): 12.5 / 14.1, 7.5 / 9.4, 20.2 / 13.6, 66.7 / 60.3."""
-    f = B.lib()._ZN4slim12mid_geometryEiiiiib
-    f.argtypes = [ctypes.c_int] * 5 + [ctypes.c_bool]
-    assert (f(n, k, rank_pad, m, 256, False) >= 0) == small
