@@ -422,12 +422,12 @@ static void launch_t_tiles(TArgs a, int xf, hipStream_t st)
 // that deals its tiles to the dies takes as many rounds as its fullest die has tiles for its compute units (with 10 tiles of
 // tokens two dies have two, and 18 rank tiles make that 36 workgroups on 32 units: twice the time), and
 //   time = a + rounds (b + k / 1000 (c + d w)),   w = the share of that die's units with a tile in the first round,
-// or, where the dies that have tiles all read R, what that takes at 7 TB/s together (8192 x 28672, rank 832, 48 MB, 200 tokens:
-// kind 0 55 us where the first estimate says 38, kind 4 49); the split product's is a + rounds c k / 1000 of a share + d per million partial sums.  The constants (us) are
+// or, where several dies read all of R, what that takes at 7 TB/s for all eight, three of them no faster (28672 inputs, rank 832,
+// 48 MB: kind 0 44 us at 64 tokens, 54 at 100, 55 at 200 and 256, where the first estimate says 38, and kind 4 47 to 50); the split product's is a + rounds c k / 1000 of a share + d per million partial sums.  The constants (us) are
 // fitted to 6048 measured products (ranks 32 to 1408, 17 to 4096 tokens, 512 to 28672 inputs, X in fp16 and 8 bits, R in
 // fp16 and 4 bits): off by 5 to 15 %, which makes the kind taken 1 % slower than the best one on average.  What is wrong
 // is rather the one launch (what else the dies share is in d only), so the split product is taken from 10 % more on: of those 6048,
-// the kind taken is slower than the split product by more than 3 % in 34, all but 11 by less than 8 %.
+// the kind taken is slower than the split product by more than 3 % in 31, all but 9 by less than 8 %.
 //   8192 inputs, fp16 (us; kinds 0 to 4): rank 64 at 800 tokens 10.6 / 14.8 / 20.5 / 20.3 / 19.8, rank 512 at 1000 tokens
 //   27.0 / 20.6 / 25.8 / - / 24.9, rank 832 at 600 tokens 37.1 / 37.2 / 27.6 / - / 25.8, at 1000 tokens 49.2 / 37.5 / 27.8 / - / 33.7.
 struct TCost {
@@ -455,7 +455,7 @@ static double t_cost(int kind, int rank_pad, int m, int k, bool q4)
     const double w = per_die < units ? (double)per_die / units : 1.0;
     const double t = c.a + (double)((per_die + units - 1) / units) * (c.b + k * 1e-3 * (c.c + c.d * w));
     if (kind == 3) return t;
-    const double r_us = c.a + (double)rank_pad * k * (q4 ? 0.53 : 2.0) * (sides < kDies ? sides : kDies) / 7e6;
+    const double r_us = c.a + (double)rank_pad * k * (q4 ? 0.53 : 2.0) * (sides > 2 ? kDies : sides) / 7e6;
     return r_us > t ? r_us : t;
 }
 

@@ -31,6 +31,8 @@ NO = float("inf")
     (False, 13824, 608, 600, [40.8, 59.1, 41.4, NO, 32.8]),
     (False, 28672, 224, 2048, [78.3, 62.2, 74.6, NO, 52.1]),
     (False, 28672, 832, 200, [54.9, 65.7, 80.2, 62.8, 48.7]),
+    (False, 28672, 832, 128, [53.9, 62.2, 76.9, 42.9, 48.6]),
+    (False, 28672, 832, 256, [55.4, 64.8, 79.8, NO, 50.3]),
     (False, 28672, 1408, 48, [85.4, 107.4, 75.9, 41.1, 45.7]),
     (True, 4096, 512, 2048, [28.6, 21.8, 17.9, NO, 28.2]),
     (True, 8192, 832, 1000, [47.8, 37.8, 29.7, NO, 35.6]),
