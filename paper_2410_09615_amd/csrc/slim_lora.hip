@@ -7,8 +7,10 @@
 // The truncated SVD is reached by subspace iteration: Q <- orth(S orth(S^T Q)), started from a
 // seeded random block of r columns.  The product Q Q^T S converges to the best rank-r
 // approximation of S (Eckart-Young); how far it is from it after `iters` rounds shows in the
-// captured energy ||Q^T S||_F^2 the call reports.  Everything is dense fp32 work on the matrix
-// cores; orthonormalisation is Cholesky QR (slim_lora_orth.hip).
+// captured energy ||Q^T S||_F^2 the call reports.  Orthonormalisation is Cholesky QR in fp32
+// (slim_lora_orth.hip), every other one of which is a scaling of the columns where that loses nothing; the
+// products of the iteration run on the fp16 matrix cores with both operands as two fp16 numbers (slim_lora_split.hip);
+// R~ and what is reported are fp32 products of the fp32 S.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -19,15 +21,13 @@ namespace slim {
 
 typedef float float16v_t __attribute__((ext_vector_type(16)));
 
-// ---- C = alpha op(A) op(B) + beta C, fp32, row-major, optional split over K with atomic adds ----
+// ---- C = op(A) B, fp32, row-major, optional split over K with atomic adds ----
 struct SgemmArgs {
     const float *A, *B;
     float *C;
     int M, N, K;          // C is [M][N]; K is the summed dimension
-    int lda, ldb, ldc;    // A is [M][K], or [K][M] when TA; B is [K][N], or [N][K] when TB
-    int kchunk;           // K values per grid.z slice (a multiple of 16); C is added to atomically when there are several
-    float alpha;
-    int beta;             // 0: C is overwritten (zeroed first when K is split), 1: added to
+    int lda, ldb;         // A is [M][K], or [K][M] when TA; B is [K][N]; C is contiguous
+    int kchunk;           // K values per grid.z slice (a multiple of 16); C (zeroed before) is added to atomically when there are several
 };
 
 constexpr int kGM = 128, kGN = 128, kGK = 16, kGLd = kGK + 4;      // LDS rows of 16 k-values, padded to 20 floats
@@ -37,7 +37,7 @@ constexpr int kGM = 128, kGN = 128, kGK = 16, kGLd = kGK + 4;      // LDS rows o
 // (r = lane % 32, h = lane / 32) of a block reads the four k-values 8 s + 4 h .. + 3 of
 // its row with one 128-bit read and feeds them to four instructions; A and B use the
 // same assignment of k-values to (lane half, instruction), so the sum is complete.
-template <bool TA, bool TB>
+template <bool TA>
 __global__ __launch_bounds__(256) void sgemm_kernel(SgemmArgs a)
 {
     __shared__ __attribute__((aligned(16))) float As[kGM * kGLd];
@@ -76,21 +76,11 @@ __global__ __launch_bounds__(256) void sgemm_kernel(SgemmArgs a)
                                                : float4_t{0.f, 0.f, 0.f, 0.f};
             }
         }
-        if constexpr (TB) {
-            // B [N][K]: as the untransposed A
 #pragma unroll
-            for (int i = 0; i < 2; ++i) {
-                const int col = n0 + (tid >> 2) + 64 * i, kk = k0 + (tid & 3) * 4;
-                rb[i] = (col < a.N && kk < ke) ? *reinterpret_cast<const float4_t *>(a.B + (size_t)col * a.ldb + kk)
-                                               : float4_t{0.f, 0.f, 0.f, 0.f};
-            }
-        } else {
-#pragma unroll
-            for (int i = 0; i < 2; ++i) {
-                const int kk = k0 + (tid >> 5) + 8 * i, col = n0 + (tid & 31) * 4;
-                rb[i] = (kk < ke && col < a.N) ? *reinterpret_cast<const float4_t *>(a.B + (size_t)kk * a.ldb + col)
-                                               : float4_t{0.f, 0.f, 0.f, 0.f};
-            }
+        for (int i = 0; i < 2; ++i) {
+            const int kk = k0 + (tid >> 5) + 8 * i, col = n0 + (tid & 31) * 4;
+            rb[i] = (kk < ke && col < a.N) ? *reinterpret_cast<const float4_t *>(a.B + (size_t)kk * a.ldb + col)
+                                           : float4_t{0.f, 0.f, 0.f, 0.f};
         }
     };
     auto store_slab = [&]() {
@@ -104,16 +94,10 @@ __global__ __launch_bounds__(256) void sgemm_kernel(SgemmArgs a)
 #pragma unroll
                 for (int e = 0; e < 4; ++e) As[((tid & 31) * 4 + e) * kGLd + (tid >> 5) + 8 * i] = ra[i][e];
         }
-        if constexpr (TB) {
 #pragma unroll
-            for (int i = 0; i < 2; ++i)
-                *reinterpret_cast<float4_t *>(Bs + ((tid >> 2) + 64 * i) * kGLd + (tid & 3) * 4) = rb[i];
-        } else {
+        for (int i = 0; i < 2; ++i)
 #pragma unroll
-            for (int i = 0; i < 2; ++i)
-#pragma unroll
-                for (int e = 0; e < 4; ++e) Bs[((tid & 31) * 4 + e) * kGLd + (tid >> 5) + 8 * i] = rb[i][e];
-        }
+            for (int e = 0; e < 4; ++e) Bs[((tid & 31) * 4 + e) * kGLd + (tid >> 5) + 8 * i] = rb[i][e];
     };
 
     // M and N are multiples of 4 wherever a 128-bit load straddles the edge (row counts
@@ -154,12 +138,11 @@ __global__ __launch_bounds__(256) void sgemm_kernel(SgemmArgs a)
                 for (int e = 0; e < 4; ++e) {
                     const int row = m0 + wm + 32 * i + 8 * b + 4 * h + e;
                     if (row >= a.M) continue;
-                    float *c = a.C + (size_t)row * a.ldc + col;
-                    const float v = a.alpha * acc[i][j][4 * b + e];
+                    float *c = a.C + (size_t)row * a.N + col;
                     if (add)
-                        atomicAdd(c, v);
+                        atomicAdd(c, acc[i][j][4 * b + e]);
                     else
-                        *c = a.beta ? *c + v : v;
+                        *c = acc[i][j][4 * b + e];
                 }
         }
 }
@@ -176,13 +159,11 @@ static int launch_fill(float *p, size_t count, float v, hipStream_t st)
     return hip_status(hipGetLastError());
 }
 
-// C = alpha op(A) op(B) + beta C.  Few tiles and a long K: K is split over grid.z and C
-// (zeroed first when beta = 0) is added to.
-static int sgemm(bool ta, bool tb, const float *A, int lda, const float *B, int ldb, float *C, int ldc, int M, int N, int K,
-                 hipStream_t st, float alpha = 1.0f, int beta = 0)
+// C = op(A) B.  Few tiles and a long K: K is split over grid.z and C (zeroed first) is added to.
+static int sgemm(bool ta, const float *A, int lda, const float *B, int ldb, float *C, int M, int N, int K, hipStream_t st)
 {
     if (M <= 0 || N <= 0 || K <= 0) return SLIM_OK;
-    SgemmArgs a{A, B, C, M, N, K, lda, ldb, ldc, 0, alpha, beta};
+    SgemmArgs a{A, B, C, M, N, K, lda, ldb, 0};
     const int tm = (M + kGM - 1) / kGM, tn = (N + kGN - 1) / kGN;
     int splits = 1;
     if (tm * tn < 512) splits = (512 + tm * tn - 1) / (tm * tn);
@@ -190,23 +171,15 @@ static int sgemm(bool ta, bool tb, const float *A, int lda, const float *B, int 
     if (splits > kslabs / 4) splits = kslabs / 4 > 0 ? kslabs / 4 : 1;      // at least 64 k-values per slice
     a.kchunk = (kslabs + splits - 1) / splits * kGK;
     splits = (K + a.kchunk - 1) / a.kchunk;
-    if (splits > 1 && !beta) {
-        if (ldc == N) {
-            const int rc = launch_fill(C, (size_t)M * N, 0.f, st);
-            if (rc != SLIM_OK) return rc;
-        } else {
-            return SLIM_ERR_SHAPE;      // not used: a C that is overwritten with K split is contiguous here
-        }
+    if (splits > 1) {
+        const int rc = launch_fill(C, (size_t)M * N, 0.f, st);
+        if (rc != SLIM_OK) return rc;
     }
     const dim3 grid(tn, tm, splits);
-    if (ta && !tb)
-        hipLaunchKernelGGL((sgemm_kernel<true, false>), grid, dim3(256), 0, st, a);
-    else if (!ta && tb)
-        hipLaunchKernelGGL((sgemm_kernel<false, true>), grid, dim3(256), 0, st, a);
-    else if (!ta && !tb)
-        hipLaunchKernelGGL((sgemm_kernel<false, false>), grid, dim3(256), 0, st, a);
+    if (ta)
+        hipLaunchKernelGGL((sgemm_kernel<true>), grid, dim3(256), 0, st, a);
     else
-        return SLIM_ERR_SHAPE;          // A^T B^T is not needed here
+        hipLaunchKernelGGL((sgemm_kernel<false>), grid, dim3(256), 0, st, a);
     return hip_status(hipGetLastError());
 }
 
@@ -466,11 +439,11 @@ extern "C" int slim_compute_adapters(const float *W, const uint8_t *qvals, const
     auto times_z = [&](int round) {          // Y = S Z     [n][l], for the first product of `round`
         unsigned *const colmax = p.split && round > 0 && round < q ? orth_column_max(O, l, round & 1) : nullptr;
         return p.split ? launch_lora_split_gemm(Sh[0], Sh[1], mx, blk[2], blk[3], n, l, k, P, Y, colmax, st)
-                       : sgemm(false, false, S, k, Z, l, Y, l, n, l, k, st);
+                       : sgemm(false, S, k, Z, l, Y, n, l, k, st);
     };
     auto times_q = [&]() {                   // Y = S^T Q   [k][l]
         return p.split ? launch_lora_split_gemm(Sh[2], Sh[3], mx, blk[0], blk[1], k, l, n32, P, Y, nullptr, st)
-                       : sgemm(true, false, S, k, Q, l, Y, l, k, l, n, st);
+                       : sgemm(true, S, k, Q, l, Y, k, l, n, st);
     };
 
     SLIM_TRY(times_z(0));
@@ -482,8 +455,8 @@ extern "C" int slim_compute_adapters(const float *W, const uint8_t *qvals, const
     }
     SLIM_TRY(launch_orth(Y, Q, nullptr, nullptr, n, l, O, -1, st));
     SLIM_TRY(launch_orth(Q, Y, nullptr, nullptr, n, l, O, -1, st));    // second pass: orthonormal to rounding
-    SLIM_TRY(sgemm(true, false, Y, l, S, k, Rt, k, l, k, n, st));          // R~ = Q^T S        [l][k]
-    SLIM_TRY(sgemm(true, false, Y, l, Y, l, G, l, l, l, n, st));           // Gram of the final block, for the report
+    SLIM_TRY(sgemm(true, Y, l, S, k, Rt, l, k, n, st));          // R~ = Q^T S        [l][k]
+    SLIM_TRY(sgemm(true, Y, l, Y, l, G, l, l, n, st));           // Gram of the final block, for the report
     hipLaunchKernelGGL(lora_ortho_kernel, grid_for((size_t)r * r), dim3(256), 0, st, (const float *)G, l, r, sq);
     SLIM_TRY(launched());
     hipLaunchKernelGGL(lora_out_l_kernel, grid_for((size_t)n * r), dim3(256), 0, st, (const float *)Y, n, l, r,
