@@ -101,7 +101,7 @@ extern "C" const char *slim_status_string(int status)
         case SLIM_ERR_ALIGN: return "a pointer is not 16-byte aligned";
         case SLIM_ERR_WORKSPACE: return "workspace is NULL or too small";
         case SLIM_ERR_HIP: return "a HIP runtime call failed";
-        case SLIM_ERR_WAIT: return "a decode call gave up waiting for its own intermediate result";
+        case SLIM_ERR_WAIT: return "a forward call gave up waiting for its own intermediate result";
         default: return "unknown status";
     }
 }

@@ -1,4 +1,5 @@
-// Device code shared by the decode kernels (slim_gemv.hip, slim_gemv_fused.hip).
+// Device code shared by the decode kernels (slim_gemv.hip, slim_gemv_fused.hip) and, for the pieces of T that travel
+// between workgroups, by the small-batch kernel (slim_gemm_mid.hip).
 #pragma once
 
 #include "slim_internal.h"

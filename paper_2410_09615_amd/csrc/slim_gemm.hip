@@ -1,10 +1,11 @@
 // slim_linear_gemm and slim_lowrank: prefill-shaped forward on the matrix cores.
 //
-// The dense products of the path, C[t][o] (+)= sum_k A[o][k] B[t][k] with fp16
-// operands and fp32 accumulation, all go through one kernel:
-//   T = X R^T        (A = R, B = X; split along k when there are few tiles),
-//   Y (+)= T L^T     (A = L, B = T; slim_lowrank with more than 16 tokens).
-// The quantized term and its adapter continuation are in slim_gemm_sparse.hip.
+// The dense products of large tiles, C[t][o] (+)= sum_k A[o][k] B[t][k] with fp16
+// operands and fp32 accumulation, through one kernel:
+//   T = X R^T        (A = R, B = X; split along k when there are few tiles), where t_kind() finds it the fastest,
+//   Y (+)= T L^T     (A = L, B = T; slim_lowrank above the small batches).
+// The other kernels of T and the small batches (17 to 512 tokens) are in slim_gemm_mid.hip, the quantized term of
+// the large tiles and its adapter continuation in slim_gemm_sparse.hip.
 #include "slim_mma.h"
 
 namespace slim {
