@@ -116,3 +116,42 @@ def test_weights_whose_gram_matrices_are_subnormal(n, k, r):
         S = (Wg.astype(np.float64) - O.dequant(ref.qvals, ref.meta, ref.scale)) / gain
         left.append(np.linalg.norm(S - Lf @ (Lf.T @ S)))
     assert abs(left[1] / left[0] - 1) <= 1e-3
+
+
+@pytest.mark.parametrize("n,k,r", [(513, 640, 64), (1000, 2048, 200)])
+def test_channels_far_below_the_largest(n, k, r):
+    """A saliency that spans 1e6: R of every single channel, the smallest included, is L^T S diag(1 / x) up to the rounding of R and
+    of the L it is compared with to fp16 (2^-11 of a column of R and of the whole of L, whose Frobenius norm is sqrt(r), times the
+    channel's norm; R down to 2^-25 absolute)."""
+    W = wl.make_weight(n, k, seed=n + 3).numpy()
+    q, m, s = B.slim_pack(torch.from_numpy(W).to(DEV))
+    ref = O.compress(W)
+    xt = np.exp(np.random.default_rng(n).uniform(0, np.log(1e6), k)).astype(np.float32)
+    L, R, _ = B.slim_compute_adapters(torch.from_numpy(W).to(DEV), q, m, s, r, torch.from_numpy(xt).to(DEV))
+    torch.cuda.synchronize()
+    E = W.astype(np.float64) - O.dequant(ref.qvals, ref.meta, ref.scale)
+    Lf, Rf = L.cpu().numpy().astype(np.float64), R.cpu().numpy().astype(np.float64)
+    want = Lf.T @ E
+    err = np.linalg.norm(Rf - want, axis=0)
+    u = 2.0 ** -11
+    assert np.all(err <= u * np.linalg.norm(want, axis=0) + u * np.sqrt(r) * np.linalg.norm(E, axis=0) + np.sqrt(r) * 2.0 ** -25)
+
+
+def test_more_rows_than_the_split_products_address():
+    """From 2^22 rows on the products of the rounds are fp32 ones and every block is orthonormalised (with 8 adapters of
+    128 channels, on the device throughout): L orthonormal, R = L^T S, the captured energy that of the exact truncation."""
+    n, k, r = 1 << 22, 128, 8
+    W = torch.randn(n, k, generator=torch.Generator(device=DEV).manual_seed(3), device=DEV) * 0.02
+    W[:, :r] *= (2.0 + torch.arange(r, device=DEV))[None, :]
+    q, m, s = B.slim_pack(W)
+    L, R, diag = B.slim_compute_adapters(W, q, m, s, r)
+    codes, _ = B.slim_unpack(q, m, n, k)
+    S = W.double() - codes.double() * s.double()[:, None]
+    Lf = L.double()
+    assert float((Lf.T @ Lf - torch.eye(r, device=DEV, dtype=torch.float64)).abs().max()) <= 2 * 2.0 ** -10
+    want = Lf.T @ S
+    assert float((R.double() - want).norm()) <= 4 * 2.0 ** -11 * (1 + float(S.norm() / want.norm())) * float(want.norm())
+    top = torch.linalg.eigvalsh((S.T @ S).cpu()).flip(0)
+    d = diag.cpu().double()
+    assert abs(float(d[0]) - float(top.sum())) <= 1e-3 * float(top.sum())
+    assert abs(float(d[1]) - float(top[:r].sum())) <= 3e-3 * float(top[:r].sum()) and d[2] < 1e-4

@@ -266,3 +266,42 @@ def test_large_tiles(height, n, m, groups, stages, kind):
     else:
         err = _forward_case(_shape(n, k, r), m, B.slim_linear_gemm, seed=stages, bits=bits, rows=rows)
     assert err <= TOL_Y
+
+
+@pytest.mark.parametrize("n,k,r,m", [(700, 1152, 70, 40), (4096, 640, 51, 500), (4096, 640, 200, 600)])
+def test_captured_calls_replay_correctly(n, k, r, m):
+    """slim_linear_gemm on fp16 and 4-bit adapters, slim_linear_gemm_fp8 and slim_lowrank captured into one graph, on
+    one workspace: T in the same launch, in one of its own (no unit left for the T role), and as rows.  Every replay gets
+    new inputs, with eager calls on the same workspace and a synchronization in between, and equals the eager results."""
+    W, L, R, X = wl.make_layer(_shape(n, k, r), m, seed=60)
+    layers = [B.compress(W.to(DEV), L.to(DEV), R.to(DEV), adapter_bits=bits) for bits in (16, 4)]
+    ws = torch.zeros(max(B.slim_workspace_bytes(x, m) for x in layers), dtype=torch.uint8, device=DEV)
+    Xd = X.to(DEV)
+    codes, info = torch.empty(m, k, dtype=torch.uint8, device=DEV), torch.empty(2, device=DEV)
+    qws = torch.empty(1024, dtype=torch.uint8, device=DEV)
+    out = [torch.empty(m, n, dtype=torch.float16, device=DEV) for _ in range(4)]
+
+    def calls(out, ws):
+        for i in (0, 1):
+            B.slim_linear_gemm(layers[i], Xd, Y=out[i], workspace=ws)
+        B.slim_input_quant_fp8(Xd, Xq=False, info=info, workspace=qws, codes=codes)
+        B.slim_linear_gemm_fp8(layers[1], codes, info, 0, Y=out[2], workspace=ws)
+        B.slim_lowrank(Xd, layers[0].R, layers[0].L, n, r, Y=out[3], workspace=ws)
+
+    calls(out, ws)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        calls(out, ws)
+    own = torch.zeros_like(ws)
+    for replay in range(4):
+        Xd.copy_(X.to(DEV).roll(replay, 0) * (1 + replay / 4))
+        graph.replay()
+        torch.cuda.synchronize()
+        got = [y.clone() for y in out]
+        want = [torch.empty_like(y) for y in out]
+        calls(want, own if replay % 2 else ws)
+        torch.cuda.synchronize()
+        for g, w in zip(got, want):
+            assert torch.equal(g, w)
+    B.slim_workspace_check(ws)
