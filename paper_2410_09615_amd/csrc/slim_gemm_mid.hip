@@ -426,14 +426,14 @@ static void launch_t_tiles(TArgs a, int xf, hipStream_t st)
 // 48 MB: kind 0 44 us at 64 tokens, 54 at 100, 55 at 200 and 256, where the first estimate says 38, and kind 4 47 to 50); the split product's is a + rounds c k / 1000 of a share + d per million partial sums.  The constants (us) are
 // fitted to 6048 measured products (ranks 32 to 1408, 17 to 4096 tokens, 512 to 28672 inputs, X in fp16 and 8 bits, R in
 // fp16 and 4 bits): off by 5 to 15 %, which makes the kind taken 1 % slower than the best one on average.  What is wrong
-// is rather the one launch (what else the dies share is in d only), so the split product is taken from 10 % more on: of those 6048,
-// the kind taken is slower than the split product by more than 3 % in 31, all but 9 by less than 8 %.
+// is rather the one launch (what else the dies share is in d only), so the split product is taken from 7 % more on: of those 6048,
+// the kind taken is slower than the split product by more than 3 % in 43, all but 15 by less than 8 %.
 //   8192 inputs, fp16 (us; kinds 0 to 4): rank 64 at 800 tokens 10.6 / 14.8 / 20.5 / 20.3 / 19.8, rank 512 at 1000 tokens
 //   27.0 / 20.6 / 25.8 / - / 24.9, rank 832 at 600 tokens 37.1 / 37.2 / 27.6 / - / 25.8, at 1000 tokens 49.2 / 37.5 / 27.8 / - / 33.7.
 struct TCost {
     double a, b, c, d;
 };
-constexpr TCost kTCost[2][5] = {{{2.2, 1.1, 0.8, 0.5}, {2.0, 1.3, 1.2, 0.7}, {2.9, 1.4, 1.8, 1.1}, {1.9, 1.5, 0.3, 0.2}, {6.7, 0.0, 10.9, 2.2}},      // R in fp16
+constexpr TCost kTCost[2][5] = {{{2.1, 1.1, 0.8, 0.5}, {2.0, 1.4, 1.2, 0.7}, {2.7, 1.6, 1.8, 1.0}, {1.9, 1.5, 0.3, 0.2}, {6.7, 0.0, 10.8, 2.2}},      // R in fp16
                                 {{1.9, 1.6, 0.9, 0.2}, {1.8, 1.8, 1.4, 0.3}, {2.3, 2.4, 2.1, 0.7}, {1.6, 2.1, 0.5, 0.2}, {7.1, 0.0, 16.0, 2.2}}};     // in 4 bits
 
 static double t_cost(int kind, int rank_pad, int m, int k, bool q4)
@@ -444,7 +444,7 @@ static double t_cost(int kind, int rank_pad, int m, int k, bool q4)
         const int splits = gemm_t_splits(m, rank_pad, k);
         const long tiles = (long)((rank_pad + 255) / 256) * ((m + 127) / 128) * splits;
         const double sums = splits > 1 ? (double)splits * m * rank_pad * 1e-6 : 0.0;
-        return 0.9 * (c.a + (double)((tiles + cus - 1) / cus) * c.c * k / splits * 1e-3 + c.d * sums);
+        return 0.93 * (c.a + (double)((tiles + cus - 1) / cus) * c.c * k / splits * 1e-3 + c.d * sums);
     }
     // tiles along the side that is dealt to the dies, and along the other
     constexpr int kSide[4][2] = {{32, 32}, {64, 32}, {64, 64}, {16, 16}};

@@ -27,6 +27,7 @@ NO = float("inf")
     (False, 8192, 512, 800, [26.5, 20.4, 26.2, NO, 23.6]),
     (False, 8192, 832, 512, [27.4, 21.8, 27.6, NO, 24.4]),
     (False, 11008, 1120, 64, [35.7, 49.6, 33.5, 17.6, 23.4]),
+    (False, 11008, 416, 2048, [64.7, 49.9, 33.3, NO, 38.7]),
     (False, 13824, 128, 3000, [42.0, 31.5, 39.9, NO, 32.6]),
     (False, 13824, 608, 600, [40.8, 59.1, 41.4, NO, 32.8]),
     (False, 28672, 224, 2048, [78.3, 62.2, 74.6, NO, 52.1]),

@@ -222,7 +222,7 @@ def test_overlapping_small_batch_calls():
 
 @pytest.mark.parametrize("kind", ["fp16", "q4", "fp8", "fp8_q4"])
 @pytest.mark.parametrize("n,k,r,m,t_kind", [
-    (28672, 256, 30, 256, (3, 0)), (200, 512, 51, 530, (0, 0)), (200, 1024, 200, 1100, (1, 1)), (200, 1152, 130, 2600, (1, 1)),
+    (28672, 1024, 60, 200, (3, 3)), (200, 512, 51, 530, (0, 0)), (200, 1024, 200, 1100, (1, 1)), (200, 1152, 130, 2600, (1, 1)),
     (200, 2048, 200, 4000, (2, 2)), (100, 128, 1024, 3000, (4, 4)), (60, 8192, 800, 1500, (4, 4))])
 def test_every_kind_of_t_product(n, k, r, m, t_kind, kind):
     """T as rows for the large tiles by each of its kernels (the rule's choice is checked, so that a later rule does not
