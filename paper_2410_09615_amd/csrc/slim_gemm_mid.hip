@@ -547,14 +547,13 @@ __device__ __forceinline__ bool y_role(const MidArgs &a, int tid, int ot, int tt
     constexpr int UPR = G::UPR;
     const int units = mid_units<AQ>(a.rank_pad);         // of 32 ranks
     // whether the wavefronts' waits ran out, behind the partial tiles
-    volatile int *const ran_out = reinterpret_cast<int *>(lds_c + G::PARTS);
-    static_assert(G::PARTS + kMidWaves * 4 <= G::BYTES, "LDS behind the partial tiles");
+    int *const ran_out = reinterpret_cast<int *>(lds_c + G::PARTS);
+    static_assert(kMidWaves == 8 && G::PARTS + kMidWaves * 4 <= G::BYTES, "LDS behind the partial tiles");
     const bool may_help = !SECOND && a.n_t > 0 && a.rank_pad > 0;
     auto any_ran_out = [&] {
-        int any = 0;
-#pragma unroll
-        for (int w = 0; w < kMidWaves; ++w) any |= ran_out[w];
-        return __builtin_amdgcn_readfirstlane(any) != 0;
+        const uint4_t lo = *reinterpret_cast<const uint4_t *>(ran_out), hi = *reinterpret_cast<const uint4_t *>(ran_out + 4);
+        const uint4_t any = lo | hi;
+        return __builtin_amdgcn_readfirstlane((int)(any[0] | any[1] | any[2] | any[3])) != 0;
     };
     const int rounds = (a.stages + KW - 1) / KW, t_rounds = (units + KW * UPR - 1) / (KW * UPR);
     const rsrc_t dt = make_rsrc(a.T, mid_t_bytes<AQ>(a.m, a.rank_pad));
