@@ -13,7 +13,7 @@
 //   lora_apply_kernel   a workgroup carries 16 rows of `in` through all block columns, which stay in LDS:
 //                       out_J = (in_J - sum_{K<J} out_K L_JK^T) X_JJ^T, one launch for the whole block.
 // 4096 x 416: 9 launches (gram, 7 steps, apply) where separate panel, trailing and column products
-// took 38 and a 64-step one-workgroup factorisation (52 us) per 64 columns: 150 us (gram 22, steps 15.7 each,
+// took 38 and a 64-step one-workgroup factorisation (52 us) per 64 columns: 160 us (gram 22, steps 17 each,
 // apply 20) where it was 700.
 //
 // A pivot below 1e-9 of the largest diagonal entry of G marks a column that lies in the span of the ones before it
@@ -30,7 +30,8 @@
 // 64 bits with and without, 16 rounds of 512 x 512 with 64 columns: random matrices 5.4e-7 and 5.6e-7, condition
 // numbers of the block 10 / 30 / 60 2.9e-7 / 2.5e-7 / 2.6e-7 and 2.9e-7 / 3.0e-7 / 2.7e-7; from 200 on, the
 // same; without the limit, one direction 10^4 times the others was lost.
-// Whole call, 4096 x 4096 with 409 columns: 8.34 -> 6.59 ms.
+// Whole call, 4096 x 4096 with 409 columns: 8.34 -> 6.59 ms (6.7 with panels that leave dependent columns out and pivots
+// of any magnitude).
 #include <utility>
 
 #include "slim_internal.h"
