@@ -165,6 +165,8 @@ __device__ __forceinline__ half_t load_half(rsrc_t r, uint32_t lane_off, uint32_
 // 2^-31.  Columns are of unit length, but for what rounding leaves of dependent ones, which may be longer (some tens
 // with pivots near the floor of the factorisation): magnitudes beyond 1015 saturate.
 constexpr float kBlockSplit = 64.0f;
+// The largest magnitudes of a block's columns are found in that many words each.
+constexpr int kColSlots = 32;
 
 // What the planners need to know of the device that is current: compute units and LDS bytes per compute
 // unit, read once per device from its properties (the nominal MI355X figures, 256 and 160 KiB, where no

@@ -406,8 +406,8 @@ __device__ __forceinline__ float column_scale(unsigned max_bits)
     return max_bits == 0u ? 1.0f : __uint_as_float((unsigned)max(253 - e, 1) << 23);
 }
 
-// With cond and no need to orthonormalise: 16 rows of out = `in` with scaled columns (colmax: the bits of their largest
-// magnitudes).  clear: words of the next block's column maxima, set to zero.
+// With cond and no need to orthonormalise: 16 rows of out = `in` with scaled columns (colmax: kColSlots rows of bits of their
+// largest magnitudes).  clear: those of the next block, set to zero.
 // 16 rows of out = in Lc^-T, block column after block column; wavefront w computes the columns 16 w .. 16 w + 15 of each.
 __global__ __launch_bounds__(256) void lora_apply_kernel(const float *__restrict__ in, float *__restrict__ out, int rows, int l, int nb,
                                                          const float *__restrict__ Lf, const float *__restrict__ D, half_t *__restrict__ hi,
@@ -420,18 +420,45 @@ __global__ __launch_bounds__(256) void lora_apply_kernel(const float *__restrict
     float *const V = lds + 16 * ldo;             // [16][68]
     const int lane = threadIdx.x & 63, ln = lane & 15, mq = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int r0 = blockIdx.x * 16;
-    if (clear && blockIdx.x == 0)
-        for (int c = threadIdx.x; c < l; c += 256) clear[c] = 0u;
-    const bool scale_only = cond && !cond->need;
-    if (scale_only) {
-        for (int c = threadIdx.x; c < l; c += 256) {
-            const float sc = column_scale(colmax[c]);
+    // neighbouring rows on one die (index mod 8): the lines of hi and lo, 64 rows each, leave its L2 whole (a block that is
+    // only scaled, 4096 x 416: 14 -> 7 us with this and without the way through LDS)
+    const int gx = (int)gridDim.x, bx = (int)blockIdx.x;
+    const int r0 = (gx % 8 == 0 ? bx % 8 * (gx / 8) + bx / 8 : bx) * 16;
+    // the sixteen rows of column c as two fp16 numbers, columns as rows
+    auto emit = [&](int c, const float (&v16)[16]) {
+        half8_t h[2], g[2];
 #pragma unroll
-            for (int r = 0; r < 16; ++r) O[r * ldo + c] = r0 + r < rows ? in[(size_t)(r0 + r) * l + c] * sc : 0.f;
+        for (int r = 0; r < 16; ++r) {
+            const float s = v16[r] * kBlockSplit, v = fabsf(s) > 65000.0f ? copysignf(65000.0f, s) : s;
+            const half_t x = (half_t)v;
+            h[r / 8][r % 8] = x;
+            g[r / 8][r % 8] = (half_t)(v - (float)x);
         }
-        __syncthreads();
-    } else {
+        const size_t at = (size_t)c * ldk + r0;
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            *reinterpret_cast<half8_t *>(hi + at + 8 * q) = h[q];
+            *reinterpret_cast<half8_t *>(lo + at + 8 * q) = g[q];
+        }
+    };
+    if (clear)
+        for (int q = blockIdx.x; q < kColSlots; q += gridDim.x)
+            for (int c = threadIdx.x; c < l; c += 256) clear[q * l + c] = 0u;
+    if (cond && !cond->need) {
+        for (int c = threadIdx.x; c < l; c += 256) {
+            float v16[16];
+#pragma unroll
+            for (int r = 0; r < 16; ++r) v16[r] = r0 + r < rows ? in[(size_t)(r0 + r) * l + c] : 0.f;
+            unsigned mx = 0u;
+#pragma unroll
+            for (int q = 0; q < kColSlots; ++q) mx = max(mx, colmax[q * l + c]);
+            const float sc = column_scale(mx);
+#pragma unroll
+            for (int r = 0; r < 16; ++r) v16[r] *= sc;
+            emit(c, v16);
+        }
+        return;
+    }
     // block column J: its part of `in`, the inverse of its diagonal block, the first tile of the factor (the loads of
     // the next column go out before this one's last products)
     float v[4];
@@ -487,39 +514,26 @@ __global__ __launch_bounds__(256) void lora_apply_kernel(const float *__restrict
         }
         __syncthreads();
     }
-    }
-    if (hi) {
-        // the rows of this workgroup as two fp16 numbers, columns as rows (rows past the last are zeros)
-        for (int c = threadIdx.x; c < l; c += 256) {
-            half8_t h[2], g[2];
+    if (hi)
+        for (int c = threadIdx.x; c < l; c += 256) {         // (rows past the last are zeros)
+            float v16[16];
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const float s = O[r * ldo + c] * kBlockSplit, v = fabsf(s) > 65000.0f ? copysignf(65000.0f, s) : s;
-                const half_t x = (half_t)v;
-                h[r / 8][r % 8] = x;
-                g[r / 8][r % 8] = (half_t)(v - (float)x);
-            }
-            const size_t at = (size_t)c * ldk + r0;
-#pragma unroll
-            for (int q = 0; q < 2; ++q) {
-                *reinterpret_cast<half8_t *>(hi + at + 8 * q) = h[q];
-                *reinterpret_cast<half8_t *>(lo + at + 8 * q) = g[q];
-            }
+            for (int r = 0; r < 16; ++r) v16[r] = O[r * ldo + c];
+            emit(c, v16);
         }
-    }
 }
 
 // Workspace of the orth()s of a call, in floats: partial tiles, tiles of G and of the factor, inverses of the diagonal
-// blocks (twice), two sets of OrthWords, two rows of column maxima.
+// blocks (twice), two sets of OrthWords, two times kColSlots rows of column maxima.
 constexpr int kOrthWords = 64;
 size_t orth_floats(int l)
 {
     const size_t nb = (size_t)(l + kOb - 1) / kOb, t = nb * (nb + 1) / 2;
-    return (kGramTiles + 2 * t + 2 * nb) * kTileFloats + kOrthWords + 2 * (size_t)l;
+    return (kGramTiles + 2 * t + 2 * nb) * kTileFloats + kOrthWords + 2 * (size_t)kColSlots * l;
 }
 unsigned *orth_column_max(float *ws, int l, int which)
 {
-    return reinterpret_cast<unsigned *>(ws + orth_floats(l) - (size_t)(2 - which) * l);
+    return reinterpret_cast<unsigned *>(ws + orth_floats(l) - (size_t)(2 - which) * kColSlots * l);
 }
 
 // out (or null): fp32 [rows][l]; hi, lo (or null): the block for lora_split_gemm_kernel, [l][rows rounded up to 32].

@@ -161,12 +161,14 @@ __global__ __launch_bounds__(256) void lora_split_reduce_kernel(const float4_t *
     }
 }
 
-// The same, a workgroup per 16 rows of cols4 float4s, with the bits of the columns' largest magnitudes (zero before).
-__global__ __launch_bounds__(256) void lora_split_reduce_max_kernel(const float4_t *__restrict__ P, int splits, int rows, int cols4,
+// The same, a workgroup per 16 rows of cols4 float4s, with the bits of the columns' largest magnitudes, in kColSlots rows of
+// 4 cols4 words (zero before), a workgroup's in row blockIdx mod kColSlots.  In one row the adds to a word were 256 in
+// turn, and 22 of 28 us (4096 x 416); now 8.
+__global__ __launch_bounds__(512) void lora_split_reduce_max_kernel(const float4_t *__restrict__ P, int splits, int rows, int cols4,
                                                                     float4_t *__restrict__ Y, unsigned *__restrict__ colmax)
 {
-    __shared__ uint4_t part[256];
-    const int rpp = 256 / cols4, row = threadIdx.x / cols4, col = threadIdx.x % cols4;
+    __shared__ uint4_t part[512];
+    const int rpp = 512 / cols4, row = threadIdx.x / cols4, col = threadIdx.x % cols4;
     const size_t count4 = (size_t)rows * cols4;
     const int end = min((int)blockIdx.x * 16 + 16, rows);
     float4_t mx = {0.f, 0.f, 0.f, 0.f};
@@ -185,8 +187,9 @@ __global__ __launch_bounds__(256) void lora_split_reduce_max_kernel(const float4
         for (int q = 1; q < rpp; ++q)
 #pragma unroll
             for (int e = 0; e < 4; ++e) mx[e] = fmaxf(mx[e], __uint_as_float(part[q * cols4 + col][e]));
+        unsigned *const to = colmax + (size_t)(blockIdx.x % kColSlots) * 4 * cols4 + 4 * col;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) atomicMax(&colmax[4 * col + e], __float_as_uint(mx[e]));     // non-negative floats order as integers
+        for (int e = 0; e < 4; ++e) atomicMax(&to[e], __float_as_uint(mx[e]));     // non-negative floats order as integers
     }
 }
 
@@ -206,7 +209,7 @@ int launch_lora_split(const float *S, int n, int k, const unsigned *max_bits, ha
 }
 
 // Y [rows][cols] = A B^T (A scaled by split_scale(*max_bits), B by kBlockSplit); P: split_gemm_splits() x rows x cols floats.
-// colmax (or null): zeros, which become the bits of the columns' largest magnitudes (cols <= 1024).
+// colmax (or null): kColSlots rows of zeros, which become bits of the columns' largest magnitudes (cols <= 1024).
 int launch_lora_split_gemm(const half_t *Ah, const half_t *Al, const unsigned *max_bits, const half_t *Bh, const half_t *Bl, int rows, int cols,
                            int K, float *P, float *Y, unsigned *colmax, hipStream_t st)
 {
@@ -217,7 +220,7 @@ int launch_lora_split_gemm(const half_t *Ah, const half_t *Al, const unsigned *m
     const size_t lds = (size_t)2 * SG_STAGE * sizeof(half_t);
     hipLaunchKernelGGL(lora_split_gemm_kernel, dim3((unsigned)(a.tiles_o * ((cols + 127) / 128)), (unsigned)splits), dim3(256), lds, st, a);
     if (colmax) {
-        hipLaunchKernelGGL(lora_split_reduce_max_kernel, dim3((unsigned)((rows + 15) / 16)), dim3(256), 0, st, reinterpret_cast<const float4_t *>(P),
+        hipLaunchKernelGGL(lora_split_reduce_max_kernel, dim3((unsigned)((rows + 15) / 16)), dim3(512), 0, st, reinterpret_cast<const float4_t *>(P),
                            splits, rows, cols / 4, reinterpret_cast<float4_t *>(Y), colmax);
     } else if (splits > 1) {
         const size_t count4 = (size_t)rows * cols / 4;          // cols is a multiple of 32
