@@ -212,8 +212,9 @@ int slim_quant_search_rows(const float *W, slim_shape shape, float *scale_out, f
  * lose bits.  Their error against 64 bits is below that of fp32 products (2.2e-7 against 5.8e-7 in the 2-norm at 4096 x
  * 4096, every row and column of the result included) for saliencies that span up to 1e3; beyond, it still is in the
  * 2-norm, but rows and columns of the result far below the largest are less exact (channels 1e6 below: 8e-6 against 7e-7).
- * The outer orth() of a round, but for the last one's, only scales its columns where the pivots of the inner
- * one span no more than 1e4: two products in a row lose nothing by it.
+ * orth() only scales columns where products in a row lose nothing by it: two, four or eight of them run between two
+ * blocks that are orthonormalised, by the pivots of the last one (two up to a span of 1e4, twice as many where its square is);
+ * the last block always is.
  * workspace: slim_adapters_workspace_bytes (HOST out-pointer; about 12 n k bytes -- S in fp32, S and its transpose as
  * two fp16 matrices -- plus 20 to 45 bytes per element of a block of max(n, k) x rank_pad), need not be zeroed.  Errors: NULL, SHAPE, ALIGN, WORKSPACE, HIP.
  */

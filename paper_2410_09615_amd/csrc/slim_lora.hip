@@ -8,7 +8,7 @@
 // seeded random block of r columns.  The product Q Q^T S converges to the best rank-r
 // approximation of S (Eckart-Young); how far it is from it after `iters` rounds shows in the
 // captured energy ||Q^T S||_F^2 the call reports.  Orthonormalisation is Cholesky QR in fp32
-// (slim_lora_orth.hip), every other one of which is a scaling of the columns where that loses nothing; the
+// (slim_lora_orth.hip), most of them a scaling of the columns where that loses nothing; the
 // products of the iteration run on the fp16 matrix cores with both operands as two fp16 numbers (slim_lora_split.hip);
 // R~ and what is reported are fp32 products of the fp32 S.
 #include <hip/hip_runtime.h>
@@ -281,7 +281,7 @@ constexpr int kSplitMax = 1 << 22;       // n and k below this: a tile's rows of
 constexpr int kMaxBlock = 1024;          // columns of the iteration block (rank_pad)
 
 size_t orth_floats(int l);                                                                           // slim_lora_orth.hip
-int launch_orth(const float *in, float *out, half_t *hi, half_t *lo, int rows, int l, float *ws, int round, hipStream_t st);
+int launch_orth(const float *in, float *out, half_t *hi, half_t *lo, int rows, int l, float *ws, int h, int last, hipStream_t st);
 unsigned *orth_column_max(float *ws, int l, int which);
 int split_gemm_splits(int rows, int cols, int K);                                                    // slim_lora_split.hip
 int launch_lora_split(const float *S, int n, int k, const unsigned *max_bits, half_t *Sh, half_t *Sl, half_t *Th, half_t *Tl, hipStream_t st);
@@ -436,25 +436,27 @@ extern "C" int slim_compute_adapters(const float *W, const uint8_t *qvals, const
     }
     hipLaunchKernelGGL(lora_init_kernel, grid_for((size_t)k * l), dim3(256), 0, st, Z, blk[2], blk[3], k, l, r, seed);
     SLIM_TRY(launched());
-    auto times_z = [&](int round) {          // Y = S Z     [n][l], for the first product of `round`
-        unsigned *const colmax = p.split && round > 0 && round < q ? orth_column_max(O, l, round & 1) : nullptr;
-        return p.split ? launch_lora_split_gemm(Sh[0], Sh[1], mx, blk[2], blk[3], n, l, k, P, Y, colmax, st)
+    const int last = 2 * q;                  // products with S^T and S, in turn, after the first
+    // (column maxima: for a block that may only be scaled)
+    auto colmax = [&](int h) { return h > 0 && h < last ? orth_column_max(O, l, h & 1) : nullptr; };
+    auto times_z = [&](int h) {              // Y = S Z     [n][l]
+        return p.split ? launch_lora_split_gemm(Sh[0], Sh[1], mx, blk[2], blk[3], n, l, k, P, Y, colmax(h), st)
                        : sgemm(false, S, k, Z, l, Y, n, l, k, st);
     };
-    auto times_q = [&]() {                   // Y = S^T Q   [k][l]
-        return p.split ? launch_lora_split_gemm(Sh[2], Sh[3], mx, blk[0], blk[1], k, l, n32, P, Y, nullptr, st)
+    auto times_q = [&](int h) {              // Y = S^T Q   [k][l]
+        return p.split ? launch_lora_split_gemm(Sh[2], Sh[3], mx, blk[0], blk[1], k, l, n32, P, Y, colmax(h), st)
                        : sgemm(true, S, k, Q, l, Y, k, l, n, st);
     };
 
     SLIM_TRY(times_z(0));
-    for (int it = 0; it < q; ++it) {
-        SLIM_TRY(launch_orth(Y, p.split ? nullptr : Q, blk[0], blk[1], n, l, O, p.split ? it : -1, st));
-        SLIM_TRY(times_q());
-        SLIM_TRY(launch_orth(Y, Z, blk[2], blk[3], k, l, O, -1, st));
-        SLIM_TRY(times_z(it + 1));
+    for (int h = 0; h < last; h += 2) {
+        SLIM_TRY(launch_orth(Y, p.split ? nullptr : Q, blk[0], blk[1], n, l, O, p.split ? h : -1, last, st));
+        SLIM_TRY(times_q(h + 1));
+        SLIM_TRY(launch_orth(Y, Z, blk[2], blk[3], k, l, O, p.split ? h + 1 : -1, last, st));
+        SLIM_TRY(times_z(h + 2));
     }
-    SLIM_TRY(launch_orth(Y, Q, nullptr, nullptr, n, l, O, -1, st));
-    SLIM_TRY(launch_orth(Q, Y, nullptr, nullptr, n, l, O, -1, st));    // second pass: orthonormal to rounding
+    SLIM_TRY(launch_orth(Y, Q, nullptr, nullptr, n, l, O, -1, last, st));
+    SLIM_TRY(launch_orth(Q, Y, nullptr, nullptr, n, l, O, -1, last, st));    // second pass: orthonormal to rounding
     SLIM_TRY(sgemm(true, Y, l, S, k, Rt, l, k, n, st));          // R~ = Q^T S        [l][k]
     SLIM_TRY(sgemm(true, Y, l, Y, l, G, l, l, n, st));           // Gram of the final block, for the report
     hipLaunchKernelGGL(lora_ortho_kernel, grid_for((size_t)r * r), dim3(256), 0, st, (const float *)G, l, r, sq);

@@ -22,16 +22,18 @@
 // a column in G is rounding, 1e-7 of the largest entry: subtracted as a panel it takes the pivots of that size after it along.)  (Where 1e-9 of that entry is more than 1, the pivot is
 // that: what is left stays within the range of the split into fp16 numbers.)
 //
-// Every other block of the subspace iteration need not be orthonormal: two products in a row lose what one does, squared.
-// Where the pivots of the last factorisation spread by no more than kSpread (a condition number of 100 for the
-// next product), scaling the columns to magnitudes up to 1 keeps two products within what fp32 Gram matrices
-// carry; beyond, the block is orthonormalised.  The decision is a word in memory that the kernels of the
-// conditional call read (all but the last then end at once): the host does not know it.  Errors against
-// 64 bits with and without, 16 rounds of 512 x 512 with 64 columns: random matrices 5.4e-7 and 5.6e-7, condition
-// numbers of the block 10 / 30 / 60 2.9e-7 / 2.5e-7 / 2.6e-7 and 2.9e-7 / 3.0e-7 / 2.7e-7; from 200 on, the
-// same; without the limit, one direction 10^4 times the others was lost.
-// Whole call, 4096 x 4096 with 409 columns: 8.34 -> 6.59 ms (6.7 with panels that leave dependent columns out and pivots
-// of any magnitude).
+// Not every block of the subspace iteration need be orthonormal: columns scaled to magnitudes up to 1 span the same, and
+// what the Gram matrix, the factorisation and the rounding of the products have to carry is the condition of the block, which
+// grows by that of S per product.  So several products follow on one another; how many is decided where the pivots are known, in
+// memory, and the kernels of a block that is only scaled return at once, but for the last (the host does not know).
+// The rule (next_run()): one product after the first block, two while the pivots of a block span at most kSpread (a
+// condition of 100), twice as many as before (up to kMaxRun) where their squares do.  Doubling to eight asks for 30: the
+// columns have separated by then, the pivots are squares of singular values whatever the number of products, and
+// rounding in the direction of the largest grows by their ratio with each product, 2e-7 * 5.5^8 = 0.2 of a column
+// at that limit.  A block whose pivots span more is followed by a quarter as many.
+// 16 rounds of a layer of 4096 x 4096 with 409 columns (singular values over a factor of 3): 12 blocks of 35 are orthonormalised,
+// where every other one was 19: 6.36 -> 4.69 ms for the call.  Residual, directions lost and orthonormality are those of every
+// other block on 150 spectra (saliencies that span 1 to 1e6 in several ways, 2 and 16 rounds).
 #include <utility>
 
 #include "slim_internal.h"
@@ -43,13 +45,23 @@ typedef float float16v_t __attribute__((ext_vector_type(16)));
 constexpr int kOb = 64;                        // block of columns
 constexpr int kTileFloats = kOb * kOb;
 constexpr int kGramTiles = 640;                // partial tiles of G the workspace has room for
-constexpr float kSpread = 1e4f;                // largest / smallest pivot up to which the next block is only scaled
+constexpr float kSpread = 1e4f;                // largest / smallest pivot up to which as many products as before may follow
+constexpr int kMaxRun = 8;                     // products between two blocks that are orthonormalised
 
 // Words of an orth() that its kernels share: the largest diagonal entry of G, the largest and the smallest pivot
-// so far, and whether the next block has to be orthonormalised.
+// so far, the product after which the next block has to be orthonormalised, and how many it is away.
 struct OrthWords {
     float gmax, pmax, pmin;
-    unsigned need;
+    int due, run;
+};
+// A conditional orth(): `h` products with S or S^T after the first block; the block is only scaled where h < in->due.
+// The words of the call before it are `in` (null: orthonormal whatever they say), its own are `out`; `last`: the products
+// after which a call that is not conditional follows.
+struct OrthStep {
+    const OrthWords *in;
+    OrthWords *out;
+    int h, last;
+    __device__ bool skip() const { return in && h < in->due; }
 };
 
 // Tiles of 64 x 64 are stored in the operand order of V_MFMA_F32_16X16X4_F32, four of its steps at a time: the
@@ -69,9 +81,9 @@ __device__ __forceinline__ void mma16(float4_t a, float4_t b, float4_t &c)
 // Partial tile of G = Y^T Y: tile t = tri(i, j) over the rows z * zrows .. ; wavefront w takes a quarter of them.  Two
 // rows of Y are the operands of V_MFMA_F32_32X32X2_F32 as they lie in memory: no LDS on the way.
 __global__ __launch_bounds__(256) void lora_gram_kernel(const float *__restrict__ Y, int rows, int l, int zrows, int tiles,
-                                                        float *__restrict__ P, const OrthWords *cond)
+                                                        float *__restrict__ P, OrthStep step)
 {
-    if (cond && !cond->need) return;
+    if (step.skip()) return;
     __shared__ __attribute__((aligned(16))) float red[kTileFloats];
     const int lane = threadIdx.x & 63, r = lane & 31, h = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -208,15 +220,28 @@ __device__ __forceinline__ bool factor16(float (&a)[16], float (&x)[16], int i, 
     return alive;
 }
 
+// How many products may follow before the next block that is orthonormalised, after one that took `done` of them to
+// pivots from pmin to pmax.
+__device__ __forceinline__ int next_run(int done, float pmax, float pmin)
+{
+    if (!(pmax <= kSpread * pmin)) return done >= 4 ? done / 4 : 1;
+    const float spread = pmax / pmin;
+    if (done == 0) return 1;
+    if (done == 1) return 2;
+    if (2 * done <= kMaxRun && spread <= (done == 2 ? 100.0f : 30.0f)) return 2 * done;
+    return done;
+}
+
 // Step j: tiles (I, J), I >= J >= j, of the trailing matrix; column j - 1 of G holds A_{I, j-1}, D the inverse of
 // the last diagonal block, its rows of pivots below the floor as zeros (Dp), so the panel is L_{I, j-1} = A_{I, j-1} D^T.
 // Step 0 adds up the partial tiles instead.  The workgroups of column j write the panel to Lf; the one of tile (j, j)
 // factors it and writes D[j], whole, and Dp[j].
 __global__ __launch_bounds__(256) void lora_chol_kernel(int j, int nb, int l, const float *__restrict__ P, int splits, int tiles,
-                                                        float *__restrict__ G, float *__restrict__ Lf, float *__restrict__ D, float *__restrict__ Dp, OrthWords *words,
-                                                        const OrthWords *cond)
+                                                        float *__restrict__ G, float *__restrict__ Lf, float *__restrict__ D, float *__restrict__ Dp,
+                                                        OrthStep step)
 {
-    if (cond && !cond->need) return;
+    if (step.skip()) return;
+    OrthWords *const words = step.out;
     __shared__ __attribute__((aligned(16))) float T[kTileFloats], LI[kTileFloats], LJ[kTileFloats];
     __shared__ float mx_s[4];
     const int tid = threadIdx.x, lane = tid & 63, ln = lane & 15, mq = lane >> 4;
@@ -384,7 +409,12 @@ __global__ __launch_bounds__(256) void lora_chol_kernel(int j, int nb, int l, co
     if (tid == 0) {                              // (every lane has seen every pivot)
         words->pmax = pmax;
         words->pmin = pmin;
-        words->need = pmax <= kSpread * pmin ? 0u : 1u;
+        if (j == nb - 1) {
+            const int done = step.in ? step.in->run : 0, run = next_run(done, pmax, pmin), end = step.h + run;
+            words->run = run;
+            // (a block that is due just before the last one is left to that)
+            words->due = step.last - end <= run / 4 ? step.last : end;
+        }
     }
     float4_t *const out = reinterpret_cast<float4_t *>(D + (size_t)j * kTileFloats);
     float4_t *const outp = reinterpret_cast<float4_t *>(Dp + (size_t)j * kTileFloats);
@@ -406,12 +436,12 @@ __device__ __forceinline__ float column_scale(unsigned max_bits)
     return max_bits == 0u ? 1.0f : __uint_as_float((unsigned)max(253 - e, 1) << 23);
 }
 
-// With cond and no need to orthonormalise: 16 rows of out = `in` with scaled columns (colmax: kColSlots rows of bits of their
+// Where the step skips the orthonormalisation: 16 rows of out = `in` with scaled columns (colmax: kColSlots rows of bits of their
 // largest magnitudes).  clear: those of the next block, set to zero.
 // 16 rows of out = in Lc^-T, block column after block column; wavefront w computes the columns 16 w .. 16 w + 15 of each.
 __global__ __launch_bounds__(256) void lora_apply_kernel(const float *__restrict__ in, float *__restrict__ out, int rows, int l, int nb,
                                                          const float *__restrict__ Lf, const float *__restrict__ D, half_t *__restrict__ hi,
-                                                         half_t *__restrict__ lo, int ldk, const OrthWords *cond,
+                                                         half_t *__restrict__ lo, int ldk, OrthStep step,
                                                          const unsigned *colmax, unsigned *clear)
 {
     extern __shared__ __attribute__((aligned(16))) float lds[];
@@ -444,7 +474,11 @@ __global__ __launch_bounds__(256) void lora_apply_kernel(const float *__restrict
     if (clear)
         for (int q = blockIdx.x; q < kColSlots; q += gridDim.x)
             for (int c = threadIdx.x; c < l; c += 256) clear[q * l + c] = 0u;
-    if (cond && !cond->need) {
+    if (step.skip()) {
+        if (blockIdx.x == 0 && threadIdx.x == 0) {
+            step.out->due = step.in->due;
+            step.out->run = step.in->run;
+        }
         for (int c = threadIdx.x; c < l; c += 256) {
             float v16[16];
 #pragma unroll
@@ -524,7 +558,7 @@ __global__ __launch_bounds__(256) void lora_apply_kernel(const float *__restrict
 }
 
 // Workspace of the orth()s of a call, in floats: partial tiles, tiles of G and of the factor, inverses of the diagonal
-// blocks (twice), two sets of OrthWords, two times kColSlots rows of column maxima.
+// blocks (twice), three sets of OrthWords, two times kColSlots rows of column maxima.
 constexpr int kOrthWords = 64;
 size_t orth_floats(int l)
 {
@@ -537,31 +571,31 @@ unsigned *orth_column_max(float *ws, int l, int which)
 }
 
 // out (or null): fp32 [rows][l]; hi, lo (or null): the block for lora_split_gemm_kernel, [l][rows rounded up to 32].
-// round < 0: always orthonormal, and the next conditional call goes by this one's pivots.  round >= 0: conditional (hi, lo only,
-// out = null) from round 1 on, where orth_column_max(round % 2) holds the column maxima of `in`; that of the
-// next round is cleared.
-int launch_orth(const float *in, float *out, half_t *hi, half_t *lo, int rows, int l, float *ws, int round, hipStream_t st)
+// h < 0: always orthonormal.  Else the block after h products, of `last`, in a call's sequence of them (hi, lo only, out = null):
+// orthonormal for h = 0, conditional from then on, where orth_column_max(h % 2) holds the column maxima of `in`; that of
+// the next block is cleared.
+int launch_orth(const float *in, float *out, half_t *hi, half_t *lo, int rows, int l, float *ws, int h, int last, hipStream_t st)
 {
     const int nb = (l + kOb - 1) / kOb, tiles = tri(nb, 0);
     float *const P = ws, *const G = P + (size_t)kGramTiles * kTileFloats, *const Lf = G + (size_t)tiles * kTileFloats;
     float *const D = Lf + (size_t)tiles * kTileFloats, *const Dp = D + (size_t)nb * kTileFloats;
-    OrthWords *const both = reinterpret_cast<OrthWords *>(Dp + (size_t)nb * kTileFloats);
-    OrthWords *const words = both + (round < 0 ? 0 : 1);
-    const OrthWords *const cond = round > 0 ? both : nullptr;
-    const unsigned *const colmax = round > 0 ? orth_column_max(ws, l, round & 1) : nullptr;
-    unsigned *const clear = round >= 0 ? orth_column_max(ws, l, (round + 1) & 1) : nullptr;
+    OrthWords *const words = reinterpret_cast<OrthWords *>(Dp + (size_t)nb * kTileFloats);
+    static_assert(3 * sizeof(OrthWords) <= kOrthWords * sizeof(float), "words of the orth()s");
+    const OrthStep step{h > 0 ? words + (h & 1) : nullptr, h < 0 ? words + 2 : words + ((h + 1) & 1), h, last};
+    const unsigned *const colmax = h > 0 ? orth_column_max(ws, l, h & 1) : nullptr;
+    unsigned *const clear = h >= 0 ? orth_column_max(ws, l, (h + 1) & 1) : nullptr;
     // about two workgroups per compute unit, at least 64 rows each
     int splits = kGramTiles / tiles;
     if (splits > (rows + 63) / 64) splits = (rows + 63) / 64;
     const int zrows = ((rows + splits - 1) / splits + 31) / 32 * 32;
     splits = (rows + zrows - 1) / zrows;
-    hipLaunchKernelGGL(lora_gram_kernel, dim3((unsigned)tiles, (unsigned)splits), dim3(256), 0, st, in, rows, l, zrows, tiles, P, cond);
+    hipLaunchKernelGGL(lora_gram_kernel, dim3((unsigned)tiles, (unsigned)splits), dim3(256), 0, st, in, rows, l, zrows, tiles, P, step);
     for (int j = 0; j < nb; ++j)
         hipLaunchKernelGGL(lora_chol_kernel, dim3((unsigned)tri(nb - j, 0)), dim3(256), 0, st, j, nb, l, (const float *)P, splits, tiles, G, Lf, D,
-                           Dp, words, cond);
+                           Dp, step);
     const size_t lds = (size_t)(16 * (nb * kOb + 4) + 16 * 68) * sizeof(float);
     hipLaunchKernelGGL(lora_apply_kernel, dim3((unsigned)((rows + 31) / 32 * 2)), dim3(256), lds, st, in, out, rows, l, nb, (const float *)Lf,
-                       (const float *)D, hi, lo, (rows + 31) / 32 * 32, cond, colmax, clear);
+                       (const float *)D, hi, lo, (rows + 31) / 32 * 32, step, colmax, clear);
     return hip_status(hipGetLastError());
 }
 

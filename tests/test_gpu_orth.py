@@ -72,6 +72,47 @@ def test_adapters_of_blocks_of_every_condition(n, k, r, base):
     assert base > 1e4 or diag.cpu()[2] < 1e-4
 
 
+def start_block(rows, cols, r, seed=1):
+    """The seeded start block: uniform in (-1, 1) from a hash of (seed, element), cols columns of which r are used."""
+    def mix(v):
+        v = v ^ (v >> np.uint32(16))
+        v = v * np.uint32(0x7feb352d)
+        v = v ^ (v >> np.uint32(15))
+        v = v * np.uint32(0x846ca68b)
+        return v ^ (v >> np.uint32(16))
+
+    t = np.arange(rows * cols, dtype=np.uint32)
+    h = mix(mix(t ^ np.uint32(seed)) + np.uint32((0x9e3779b9 * seed) & 0xFFFFFFFF))
+    z = ((h >> np.uint32(8)).astype(np.float64) + 0.5) * (2.0 / 16777216.0) - 1.0
+    return z.reshape(rows, cols)[:, :r]
+
+
+@pytest.mark.parametrize("n,k,r", [(257, 384, 40), (1030, 512, 96)])
+@pytest.mark.parametrize("base", [1.0, 30.0])
+@pytest.mark.parametrize("iters", [1, 2, 3, 4, 5, 6, 8, 11, 16])
+def test_rounds_without_orthonormalising_every_block(n, k, r, base, iters):
+    """Runs of one, two, four and eight products between two orthonormal blocks, and what is left of a run when the
+    rounds end: L spans what as many rounds with every block orthonormal reach in binary64 from the same start.
+    L is rounded to fp16: a column leaves that span by at most 2^-11; the rounding of the block's products and Gram matrices,
+    3e-7 times the condition of a block (at most 1e3 with eight products in a run), is below that: twice 2^-11 sqrt(r) for r columns."""
+    W = wl.make_weight(n, k, seed=n + 9).numpy()
+    q, m, s = B.slim_pack(torch.from_numpy(W).to(DEV))
+    ref = O.compress(W)
+    rng = np.random.default_rng(n)
+    xt = np.ones(k, np.float32)
+    xt[rng.permutation(k)[:r]] = base ** (1 - np.arange(r) / r)
+    L, _, diag = B.slim_compute_adapters(torch.from_numpy(W).to(DEV), q, m, s, r, torch.from_numpy(xt).to(DEV), iters=iters)
+    torch.cuda.synchronize()
+    S = (W.astype(np.float64) - O.dequant(ref.qvals, ref.meta, ref.scale)) * O.saliency_shift(xt)[None, :]
+    Q, _ = np.linalg.qr(S @ start_block(k, -(-r // 32) * 32, r))
+    for _ in range(iters):
+        Z, _ = np.linalg.qr(S.T @ Q)
+        Q, _ = np.linalg.qr(S @ Z)
+    Lf = L.cpu().numpy().astype(np.float64)
+    assert np.linalg.norm(Lf - Q @ (Q.T @ Lf)) <= 2 * 2.0 ** -11 * np.sqrt(r)
+    assert diag.cpu()[2] < 1e-4
+
+
 @pytest.mark.parametrize("seed,gain", [(0, 1.0), (1, 1.0), (2, 1.0), (1, 1e7)])
 def test_a_column_below_the_floor_takes_no_other_along(seed, gain):
     """102 channels that span 1e4 in magnitude: squared singular values down to 1e-8 of the largest, within ten times
