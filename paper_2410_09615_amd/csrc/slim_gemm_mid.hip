@@ -114,24 +114,6 @@ __device__ __forceinline__ bool tile_on_die(int b, int tiles_o, int &ot, int &tt
 }
 static int die_tiles(int tiles_o, int tiles_t) { return (tiles_o + kDies - 1) / kDies * kDies * tiles_t; }
 
-// One load instruction of 64 x 16 bytes from a buffer (per-lane offset, which is range-checked, and a uniform
-// one, which is not) to 1 KiB of LDS at byte address lds_byte (uniform), in lane order.  The compiler does not
-// see the load: the caller waits for it.  DEV: device scope (from memory, not from this die's L2).
-template <bool DEV = false>
-__device__ __forceinline__ void load_to_lds(rsrc_t r, uint32_t lane_off, uint32_t uniform_off, uint32_t lds_byte)
-{
-    if constexpr (DEV)
-        asm volatile("s_mov_b32 m0, %3\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, %2 offen sc1 lds"
-                     :
-                     : "v"(lane_off), "s"(r), "s"(uniform_off), "s"(lds_byte)
-                     : "memory", "m0");
-    else
-        asm volatile("s_mov_b32 m0, %3\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, %2 offen lds"
-                     :
-                     : "v"(lane_off), "s"(r), "s"(uniform_off), "s"(lds_byte)
-                     : "memory", "m0");
-}
-
 // T tile of 16 ranks x 16 tokens.  A unit is 256 inputs: eight steps of V_MFMA_F32_16X16X32_F16, R from memory
 // into registers in operand order (runs of 256 bytes), X through LDS: in operand order neighbouring lanes are
 // different tokens, and such a load costs the address unit four times one that reads along the rows.

@@ -12,11 +12,13 @@
 //          5 % of the channels 1e4 above the rest  1.4e-7 (1.4e-7)   2.4e-5 (4.1e-7)   1.8e-7 (1.7e-7)
 //   S^T Q  saliency of calibration inputs          1.2e-7 (3.0e-7)   2.5e-7 (6.8e-7)   2.5e-7 (4.9e-7)
 //          spanning 1e6, even in the logarithm     1.1e-7 (2.9e-7)   2.1e-7 (5.1e-7)   7.0e-6 (7.2e-7)
+// (The shares of K are added up in 64 bits and rounded once; acc + small is one rounding more per share than one accumulator for
+// all three products, added one after the other, would need: 2.22e-7 with that, 2.21e-7 like this, 2.23e-7 with shares added in fp32.)
 // The columns that lose in the third line are those of directions 1e4 below the leading ones: the error is of the direction of
 // the leading ones, which the orthonormalisation takes out.  Adapters of saliencies that span up to 1e8 capture what they did
 // with fp32 products, to the digits reported.
 // Three fp16 instructions do the work of eight fp32 ones that take twice the time each.  4096 x 4096 times 416 columns: 200 us with the fp32 instruction (70 TFLOP/s),
-// 58 us like this (52 and 6 to add the shares of K).
+// 54 us like this (46, and 8 to add the shares of K and find the columns' largest magnitudes).
 //   S is split once per call, into the operand order of the instruction, for S Z and for S^T Q;
 //   the blocks are split where they are written (lora_apply_kernel, lora_init_kernel), columns as rows.
 #include "slim_mma.h"
@@ -90,47 +92,133 @@ struct SplitGemmArgs {
     int tiles_o;                // row tiles of 256
 };
 
-// Workgroup: 4 wavefronts, tile 256 rows x 128 columns, each wavefront 64 x 128 on fixed accumulators; the k-loop is
-// dense_phase(), three times over the workgroup's share of K.
+// acc(i, it) += Ah_i Bh_it^T and small(i, it) += Al_i Bh_it^T + Ah_i Bl_it^T over K inputs (a multiple of 32), 16 per step of
+// V_MFMA_F32_32X32X16_F16, accumulators as in dense_phase() (slim_mma.h).  Both parts of both operands are at hand, so
+// each is fetched once for the three products.  Accumulator tiles 0 .. are acc, kSmall .. are small: what is of the
+// order of 2^-11 is added up by itself.
+//   A: from memory into registers, seven steps (of 24 matrix instructions) ahead in eight rotating sets;
+//   B: 128 columns x 128 inputs per stage and part in LDS, written by the loads themselves while the stage before it is
+//      multiplied.  A column's stage is a row of 256 bytes without padding, its pieces of 16 bytes permuted by the
+//      column number, so that the sixteen lanes that read together hit all banks once.
+constexpr int kSplitAT = 2, kSmall = kSplitAT * NT;
+constexpr uint32_t kSplitStage = 128 * SG_BK * 2;       // bytes of a stage of one part of B
+struct SplitOperands {
+    rsrc_t a[2], b[2];                // hi, lo
+    uint32_t av, a_tile, a_step;      // A: this lane's offset for row tile 0, step 0; bytes between row tiles, between steps
+    uint32_t bv, b_pass;              // B: this lane's offset for stage 0; bytes between the passes of 16 columns
+    uint32_t b_lds;                   // LDS address of this wavefront's part of pass 0 of buffer 0, hi
+};
+__device__ __forceinline__ void split_phase(const SplitOperands &o, int K, const char *lds_c, int li, int lb)
+{
+    constexpr int AT = kSplitAT;
+    const int nst = K / 16;
+    const int stages = (K + SG_BK - 1) / SG_BK;
+    // (everything in the lane's offset, which is range-checked)
+    auto fetch_b = [&](int s, int u, int q) {        // load q of a stage: pass q / 2 of part q % 2, to buffer u
+        load_to_lds(o.b[q & 1], o.bv + (uint32_t)s * (SG_BK * 2) + (uint32_t)(q >> 1) * o.b_pass, 0u,
+                    o.b_lds + (uint32_t)(2 * u + (q & 1)) * kSplitStage + (uint32_t)(q >> 1) * 4096u);
+    };
+    uint4_t la[8][AT][2];
+    // steps past the last read zeros (2^31 more than a lane's offset is past the end of every descriptor here), so that every
+    // stage is whole: with exits from the middle of a stage the compiler copies the sets, and waits for all of them
+    auto fetch_a = [&](int g, int i, int h) { return load16(o.a[h], o.av, g < nst ? (uint32_t)i * o.a_tile + (uint32_t)g * o.a_step : 0x80000000u); };
+    const char *const lr = lds_c + li * 256;
+    half8_t b[2][2];
+    auto read_b = [&](int u, int it, int j) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+            b[it & 1][h] = *reinterpret_cast<const half8_t *>(lr + (2 * u + h) * kSplitStage + it * 32 * 256 + (((2 * j + lb) ^ (li & 15)) << 4));
+    };
+#pragma unroll
+    for (int q = 0; q < 2 * XR; ++q) fetch_b(0, 0, q);
+#pragma unroll
+    for (int g = 0; g < 7; ++g)
+#pragma unroll
+        for (int i = 0; i < AT; ++i)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) la[g][i][h] = fetch_a(g, i, h);
+    asm volatile("s_waitcnt vmcnt(%0)" : : "n"(7 * AT * 2) : "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" : : : "memory");
+    for (int s = 0; s < stages; ++s) {
+        const int u = s & 1;
+        const int sn = min(s + 1, stages - 1);
+        read_b(u, 0, 0);
+        static_for<8>([&](auto jc) {
+            constexpr int j = jc;
+            const int g = 8 * s + j;
+            static_for<NT>([&](auto itc) {
+                constexpr int it = itc;
+                static_assert(NT == 2 * AT && 2 * XR == 4 * NT, "one load of A and, in half of the steps, one of B per block");
+                la[(j + 7) & 7][it / 2][it % 2] = fetch_a(g + 7, it / 2, it % 2);
+                if constexpr (j < 4) fetch_b(sn, u ^ 1, 4 * j + it);
+                if constexpr (it + 1 < NT)
+                    read_b(u, it + 1, j);
+                else if constexpr (j + 1 < 8)
+                    read_b(u, 0, j + 1);
+                __builtin_amdgcn_sched_barrier(0);
+                static_for<AT>([&](auto ic) {
+                    constexpr int i = ic;
+                    mfma_fixed<kSmall + i * NT + it>(__builtin_bit_cast(half8_t, la[j & 7][i][1]), b[it & 1][0]);
+                });
+                static_for<AT>([&](auto ic) {
+                    constexpr int i = ic;
+                    mfma_fixed<i * NT + it>(__builtin_bit_cast(half8_t, la[j & 7][i][0]), b[it & 1][0]);
+                });
+                static_for<AT>([&](auto ic) {
+                    constexpr int i = ic;
+                    mfma_fixed<kSmall + i * NT + it>(__builtin_bit_cast(half8_t, la[j & 7][i][0]), b[it & 1][1]);
+                });
+                __builtin_amdgcn_sched_barrier(0);
+            });
+        });
+        // the next stage's loads to LDS, the last of them ahead of the loads of A of four steps, have landed; this one has been read
+        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" : : "n"(4 * AT * 2) : "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" : : : "memory");
+    }
+    asm volatile("s_waitcnt vmcnt(0)" : : : "memory");   // what the last stage fetched for none after it
+}
+
+// Workgroup: 4 wavefronts, tile 256 rows x 128 columns, each wavefront 64 x 128 on fixed accumulators.  One wavefront per
+// SIMD, which its 24 matrix instructions per step of 16 inputs keep busy while the loads of the next are on their way:
+// 4096 x 4096 times 416 columns 46 us, of them 37 in the loop (matrix pipes busy 77 % of the time, at 1.75 GHz) and 5
+// to write four shares of K; the three products one after the other, with every operand fetched for each, took 51.
 __global__ __launch_bounds__(256, 1) void lora_split_gemm_kernel(SplitGemmArgs a)
 {
-    constexpr int AT = 2;
-    extern __shared__ __attribute__((aligned(16))) half_t lds[];   // two stage buffers
-    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave, li = lane & 31, lb = lane >> 5;
-    // the workgroups of a die (index mod 8) take neighbouring positions of the blocked order
-    const int gx = (int)gridDim.x;
-    const int q = gx % kDies == 0 ? ((int)blockIdx.x % kDies) * (gx / kDies) + (int)blockIdx.x / kDies : (int)blockIdx.x;
-    const int w = blocked_tile(q, a.tiles_o, gx / a.tiles_o);
-    const int o0 = (w % a.tiles_o) * 256 + wave * 64;
-    const int t0 = (w / a.tiles_o) * 128;
+    constexpr int AT = kSplitAT;
+    extern __shared__ __attribute__((aligned(16))) char lds_c[];   // two stage buffers of hi and lo
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), li = lane & 31, lb = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+    // the column tiles of a row tile on one die (index mod 8), whose L2 then reads the rows, most of what there is to read, once
+    const int gx = (int)gridDim.x, tiles_t = gx / a.tiles_o;
+    const int w = gx % kDies == 0 ? ((int)blockIdx.x % kDies) * (gx / kDies) + (int)blockIdx.x / kDies : (int)blockIdx.x;
+    const int ob = w / tiles_t * 256, o0 = ob + wave * 64;
+    const int t0 = w % tiles_t * 128;
     const int k0 = blockIdx.y * a.ks;
     const int klen = max(0, min(a.ks, a.K - k0));
 
-    acc_reserve<AT>();
-    static_for<16 * AT * NT>([&](auto r) { acc_write<r>(0.0f); });
+    acc_reserve<2 * AT>();
+    static_for<2 * 16 * AT * NT>([&](auto r) { acc_write<r>(0.0f); });
     const uint32_t K = (uint32_t)a.K;
-    const half_t *const lr = lds + li * SG_LD + 8 * lb;
-    const int srow = tid >> 4, scol = (tid & 15) * 8;
-    half_t *const lw = lds + srow * SG_LD + scol;
-    uint4_t xs[XR];
-    auto stage_store = [&](int u, const uint4_t (&reg)[XR], int only = -1) {
-#pragma unroll
-        for (int p = 0; p < XR; ++p)
-            if (only < 0 || only == p) *reinterpret_cast<uint4_t *>(lw + u * SG_STAGE + p * 16 * SG_LD) = reg[p];
-    };
     // descriptors of this tile's rows alone, so that the offsets stay in 32 bits whatever the matrices hold
-    const int ob = (w % a.tiles_o) * 256;
     const uint32_t bytes_a = (uint32_t)min(8, ((a.rows + 31) / 32 - ob / 32)) * (K / 16) * 1024u;
     const uint32_t bytes_b = (uint32_t)min(128, a.cols - t0) * K * 2u;
     const size_t at_a = (size_t)ob * K, at_b = (size_t)t0 * K;
-    const rsrc_t dah = make_rsrc(a.Ah + at_a, bytes_a), dal = make_rsrc(a.Al + at_a, bytes_a);
-    const rsrc_t dbh = make_rsrc(a.Bh + at_b, bytes_b), dbl = make_rsrc(a.Bl + at_b, bytes_b);
-    const uint32_t av = tl_piece((uint32_t)(wave * 64 + li), (uint32_t)k0 / 8 + lb, K);
-    const uint32_t bv = ((uint32_t)srow * K + (uint32_t)k0 + (uint32_t)scol) * 2u;
-    // smallest products first
-    dense_phase<AT>(dal, av, (K / 16) * 1024u, 1024u, dbh, bv, 32u * K, klen, lr, xs, stage_store);
-    dense_phase<AT>(dah, av, (K / 16) * 1024u, 1024u, dbl, bv, 32u * K, klen, lr, xs, stage_store);
-    dense_phase<AT>(dah, av, (K / 16) * 1024u, 1024u, dbh, bv, 32u * K, klen, lr, xs, stage_store);
+    SplitOperands op;
+    op.a[0] = make_rsrc(a.Ah + at_a, bytes_a);
+    op.a[1] = make_rsrc(a.Al + at_a, bytes_a);
+    op.b[0] = make_rsrc(a.Bh + at_b, bytes_b);
+    op.b[1] = make_rsrc(a.Bl + at_b, bytes_b);
+    op.av = tl_piece((uint32_t)(wave * 64 + li), (uint32_t)k0 / 8 + lb, K);
+    op.a_tile = (K / 16) * 1024u;
+    op.a_step = 1024u;
+    // a load instruction moves four columns: lane -> (column, slot of 16 bytes), source piece = slot ^ column
+    const uint32_t bc = (uint32_t)(4 * wave + (lane >> 4));
+    op.bv = (bc * K + (uint32_t)k0) * 2u + (((uint32_t)(lane & 15) ^ bc) << 4);
+    op.b_pass = 32u * K;
+    op.b_lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)lds_c + (uint32_t)wave * 1024u;
+    split_phase(op, klen, lds_c, li, lb);
     acc_settle();
     const float sc = 1.0f / (split_scale(*a.max_bits) * kBlockSplit);
     // lane holds column t0 + 32 it + li, rows o .. o + 3 per (i, blk)
@@ -144,20 +232,32 @@ __global__ __launch_bounds__(256, 1) void lora_split_gemm_kernel(SplitGemmArgs a
             static_for<16>([&](auto ec) {
                 constexpr int e = ec;
                 const int o = o0 + 32 * i + 8 * (e / 4) + 4 * lb + e % 4;
-                const float v = acc_read<16 * (i * NT + it) + e>();
-                if (o < a.rows) out[(size_t)o * a.cols + t] = v * sc;
+                const float v = acc_read<16 * (i * NT + it) + e>() + acc_read<16 * (kSmall + i * NT + it) + e>();
+                if (o < a.rows)        // (written through: 27 MB left in the L2s to the end of the kernel cost 2 us)
+                    __hip_atomic_store(&out[(size_t)o * a.cols + t], v * sc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             });
         });
     });
+}
+
+// sum_z P[z][i], rounded once
+__device__ __forceinline__ float4_t sum_shares(const float4_t *__restrict__ P, int splits, size_t count4, size_t i)
+{
+    const float4_t p = P[i];
+    double s[4] = {p[0], p[1], p[2], p[3]};
+    for (int z = 1; z < splits; ++z) {
+        const float4_t q = P[(size_t)z * count4 + i];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) s[e] += (double)q[e];
+    }
+    return float4_t{(float)s[0], (float)s[1], (float)s[2], (float)s[3]};
 }
 
 // Y[i] = sum_z P[z][i]
 __global__ __launch_bounds__(256) void lora_split_reduce_kernel(const float4_t *__restrict__ P, int splits, size_t count4, float4_t *__restrict__ Y)
 {
     for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < count4; i += (size_t)gridDim.x * blockDim.x) {
-        float4_t s = P[i];
-        for (int z = 1; z < splits; ++z) s += P[(size_t)z * count4 + i];
-        Y[i] = s;
+        Y[i] = sum_shares(P, splits, count4, i);
     }
 }
 
@@ -175,8 +275,7 @@ __global__ __launch_bounds__(512) void lora_split_reduce_max_kernel(const float4
     if (row < rpp)
         for (int r = blockIdx.x * 16 + row; r < end; r += rpp) {
             const size_t i = (size_t)r * cols4 + col;
-            float4_t s = P[i];
-            for (int z = 1; z < splits; ++z) s += P[(size_t)z * count4 + i];
+            const float4_t s = sum_shares(P, splits, count4, i);
             Y[i] = s;
 #pragma unroll
             for (int e = 0; e < 4; ++e) mx[e] = fmaxf(mx[e], fabsf(s[e]));
@@ -217,7 +316,7 @@ int launch_lora_split_gemm(const half_t *Ah, const half_t *Al, const unsigned *m
     const int splits = split_gemm_splits(rows, cols, K);
     a.P = splits > 1 || colmax ? P : Y;
     a.ks = ((K + 127) / 128 + splits - 1) / splits * 128;
-    const size_t lds = (size_t)2 * SG_STAGE * sizeof(half_t);
+    const size_t lds = (size_t)4 * kSplitStage;
     hipLaunchKernelGGL(lora_split_gemm_kernel, dim3((unsigned)(a.tiles_o * ((cols + 127) / 128)), (unsigned)splits), dim3(256), lds, st, a);
     if (colmax) {
         hipLaunchKernelGGL(lora_split_reduce_max_kernel, dim3((unsigned)((rows + 15) / 16)), dim3(512), 0, st, reinterpret_cast<const float4_t *>(P),

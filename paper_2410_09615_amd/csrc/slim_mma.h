@@ -28,6 +28,24 @@ __device__ __forceinline__ void static_for(F &&f)
     static_for_impl(std::make_integer_sequence<int, N>{}, f);
 }
 
+// One load instruction of 64 x 16 bytes from a buffer (per-lane offset, which is range-checked, and a uniform
+// one, which is not) to 1 KiB of LDS at byte address lds_byte (uniform), in lane order.  The compiler does not
+// see the load: the caller waits for it.  DEV: device scope (from memory, not from this die's L2).
+template <bool DEV = false>
+__device__ __forceinline__ void load_to_lds(rsrc_t r, uint32_t lane_off, uint32_t uniform_off, uint32_t lds_byte)
+{
+    if constexpr (DEV)
+        asm volatile("s_mov_b32 m0, %3\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, %2 offen sc1 lds"
+                     :
+                     : "v"(lane_off), "s"(r), "s"(uniform_off), "s"(lds_byte)
+                     : "memory", "m0");
+    else
+        asm volatile("s_mov_b32 m0, %3\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, %2 offen lds"
+                     :
+                     : "v"(lane_off), "s"(r), "s"(uniform_off), "s"(lds_byte)
+                     : "memory", "m0");
+}
+
 // Accumulators of a wavefront that owns 128 x 128 outputs: 256 registers, the
 // whole accumulation half of the register file, with everything else in the
 // ordinary half.  The compiler's allocator does not find this split (it spills),
