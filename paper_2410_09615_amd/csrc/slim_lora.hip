@@ -281,7 +281,9 @@ constexpr int kSplitMax = 1 << 22;       // n and k below this: a tile's rows of
 constexpr int kMaxBlock = 1024;          // columns of the iteration block (rank_pad)
 
 size_t orth_floats(int l);                                                                           // slim_lora_orth.hip
-int launch_orth(const float *in, float *out, half_t *hi, half_t *lo, int rows, int l, float *ws, int h, int last, hipStream_t st);
+size_t orth_hand_words();
+int launch_orth(const float *in, float *out, half_t *hi, half_t *lo, int rows, int l, float *ws, unsigned *hand, unsigned seq, int h, int last,
+                hipStream_t st);
 unsigned *orth_column_max(float *ws, int l, int which);
 int split_gemm_splits(int rows, int cols, int K);                                                    // slim_lora_split.hip
 int launch_lora_split(const float *S, int n, int k, const unsigned *max_bits, half_t *Sh, half_t *Sl, half_t *Th, half_t *Tl, hipStream_t st);
@@ -366,7 +368,7 @@ static LoraPlan plan_lora(int n, int k, int rank)
     p.G = take(l * l);
     p.O = take(orth_floats(p.l));
     p.Rt = take(l * k);
-    p.sq = take(64);
+    p.sq = take(64 + orth_hand_words());
     p.total = off;
     return p;
 }
@@ -416,7 +418,13 @@ extern "C" int slim_compute_adapters(const float *W, const uint8_t *qvals, const
     auto launched = [&]() { return hip_status(hipGetLastError()); };
     auto grid_for = [](size_t count) { return dim3((unsigned)std::min<size_t>((count + 255) / 256, 4096)); };
 
-    SLIM_TRY(launch_fill(sq, 64, 0.f, st));
+    // (the words that the orth()s' workgroups hand over by lie behind the sums)
+    unsigned *const hand = reinterpret_cast<unsigned *>(sq + 64);
+    unsigned orths = 0;
+    auto orth = [&](const float *in, float *out, half_t *hi, half_t *lo, int rows, int h, int last) {
+        return launch_orth(in, out, hi, lo, rows, p.l, O, hand, ++orths, h, last, st);
+    };
+    SLIM_TRY(launch_fill(sq, 64 + orth_hand_words(), 0.f, st));
     hipLaunchKernelGGL(lora_shift_kernel, dim3(1), dim3(1024), 0, st, x_tilde, k, x);
     SLIM_TRY(launched());
     hipLaunchKernelGGL(lora_error_kernel, dim3(std::min(grid_for((size_t)n * (k / 4)).x, 1024u)), dim3(256), 0, st, W, qvals, meta, scale,
@@ -450,13 +458,13 @@ extern "C" int slim_compute_adapters(const float *W, const uint8_t *qvals, const
 
     SLIM_TRY(times_z(0));
     for (int h = 0; h < last; h += 2) {
-        SLIM_TRY(launch_orth(Y, p.split ? nullptr : Q, blk[0], blk[1], n, l, O, p.split ? h : -1, last, st));
+        SLIM_TRY(orth(Y, p.split ? nullptr : Q, blk[0], blk[1], n, p.split ? h : -1, last));
         SLIM_TRY(times_q(h + 1));
-        SLIM_TRY(launch_orth(Y, Z, blk[2], blk[3], k, l, O, p.split ? h + 1 : -1, last, st));
+        SLIM_TRY(orth(Y, Z, blk[2], blk[3], k, p.split ? h + 1 : -1, last));
         SLIM_TRY(times_z(h + 2));
     }
-    SLIM_TRY(launch_orth(Y, Q, nullptr, nullptr, n, l, O, -1, last, st));
-    SLIM_TRY(launch_orth(Q, Y, nullptr, nullptr, n, l, O, -1, last, st));    // second pass: orthonormal to rounding
+    SLIM_TRY(orth(Y, Q, nullptr, nullptr, n, -1, last));
+    SLIM_TRY(orth(Q, Y, nullptr, nullptr, n, -1, last));    // second pass: orthonormal to rounding
     SLIM_TRY(sgemm(true, Y, l, S, k, Rt, l, k, n, st));          // R~ = Q^T S        [l][k]
     SLIM_TRY(sgemm(true, Y, l, Y, l, G, l, l, n, st));           // Gram of the final block, for the report
     hipLaunchKernelGGL(lora_ortho_kernel, grid_for((size_t)r * r), dim3(256), 0, st, (const float *)G, l, r, sq);

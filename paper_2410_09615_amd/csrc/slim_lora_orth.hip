@@ -6,15 +6,14 @@
 // The call is a chain (products, 64-column steps of the factorisation, products), so what bounds it is the
 // number of launches (4 us each) and the latency of the 64 x 64 diagonal blocks, not arithmetic:
 //   lora_gram_kernel    lower tiles of G, the rows divided among the workgroups, partial tiles to memory;
-//   lora_chol_kernel    one launch per step of 64 columns: every workgroup updates one tile of the trailing
-//                       matrix with the panel of the step before, which it scales itself (two products of
-//                       64^3 more, one launch less), and the workgroup of the diagonal tile then factors and
-//                       inverts it, in blocks of 16 that live in the registers of one wavefront;
+//   lora_chol_kernel    the factorisation, a workgroup per tile, which hand finished tiles to one another through
+//                       memory; the workgroup of a diagonal tile factors and inverts it, in blocks of 16 that live in the
+//                       registers of one wavefront;
 //   lora_apply_kernel   a workgroup carries 16 rows of `in` through all block columns, which stay in LDS:
 //                       out_J = (in_J - sum_{K<J} out_K L_JK^T) X_JJ^T, one launch for the whole block.
-// 4096 x 416: 9 launches (gram, 7 steps, apply) where separate panel, trailing and column products
-// took 38 and a 64-step one-workgroup factorisation (52 us) per 64 columns: 160 us (gram 22, steps 17 each,
-// apply 20) where it was 700.
+// 4096 x 416: 3 launches (gram 22 us, factorisation 128, apply 25) where a factorisation with one launch per 64 columns took
+// 148 us and seven launches of 4 us where the block is only scaled, and with separate panel, trailing and column products
+// and a 64-step one-workgroup diagonal 700.
 //
 // A pivot below 1e-9 of the largest diagonal entry of G marks a column that lies in the span of the ones before it
 // (or a padding column of zeros): it gets pivot 1 and no column is subtracted for it, in the blocks that follow either,
@@ -47,6 +46,7 @@ constexpr int kTileFloats = kOb * kOb;
 constexpr int kGramTiles = 640;                // partial tiles of G the workspace has room for
 constexpr float kSpread = 1e4f;                // largest / smallest pivot up to which as many products as before may follow
 constexpr int kMaxRun = 8;                     // products between two blocks that are orthonormalised
+constexpr int kMaxBlocks = 1024 / kOb, kMaxTri = kMaxBlocks * (kMaxBlocks + 1) / 2;      // blocks of columns, tiles of a lower triangle
 
 // Words of an orth() that its kernels share: the largest diagonal entry of G, the largest and the smallest pivot
 // so far, the product after which the next block has to be orthonormalised, and how many it is away.
@@ -232,87 +232,135 @@ __device__ __forceinline__ int next_run(int done, float pmax, float pmin)
     return done;
 }
 
-// Step j: tiles (I, J), I >= J >= j, of the trailing matrix; column j - 1 of G holds A_{I, j-1}, D the inverse of
-// the last diagonal block, its rows of pivots below the floor as zeros (Dp), so the panel is L_{I, j-1} = A_{I, j-1} D^T.
-// Step 0 adds up the partial tiles instead.  The workgroups of column j write the panel to Lf; the one of tile (j, j)
-// factors it and writes D[j], whole, and Dp[j].
-__global__ __launch_bounds__(256) void lora_chol_kernel(int j, int nb, int l, const float *__restrict__ P, int splits, int tiles,
-                                                        float *__restrict__ G, float *__restrict__ Lf, float *__restrict__ D, float *__restrict__ Dp,
-                                                        OrthStep step)
+// What the workgroups of a factorisation hand to one another: a tile of the factor (at tri(I, J)), the tile below a
+// diagonal one before it is scaled, the inverse of a diagonal tile.  A word each, in a line of its own, holds the number of the
+// orth() whose tile it is (kHandFailed: that of one whose wait ran out).
+enum { kHandL = 0, kHandA = kMaxTri, kHandD = kMaxTri + kMaxBlocks, kHandFailed = kMaxTri + 2 * kMaxBlocks, kHandWords };
+constexpr int kHandStride = 16;
+constexpr int kHandPolls = 1 << 20;            // half a microsecond or more each; a wait is over after some tens of them
+
+// Everything the workgroup has stored -> visible to who sees the word.
+__device__ __forceinline__ void hand_over(unsigned *hand, int what, unsigned seq)
+{
+    asm volatile("s_waitcnt vmcnt(0)" : : : "memory");
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+        __hip_atomic_store(hand + what * kHandStride, seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+}
+// One lane waits; false: the word has not come.
+__device__ __forceinline__ bool hand_taken(unsigned *hand, int what, unsigned seq)
+{
+    for (int polls = 0; __hip_atomic_load(hand + what * kHandStride, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != seq; ++polls) {
+        if (polls >= kHandPolls) return false;
+        __builtin_amdgcn_s_sleep(1);
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    return true;
+}
+
+// G = Lc Lc^T in one launch.  A workgroup has one tile (I, J), I >= J, column after column: it adds up the tile's partial
+// tiles, subtracts L_IK L_JK^T for the columns K < J as they come, and then either factors and inverts the diagonal tile (D[J]
+// whole, Dp[J] with the rows of pivots below the floor as zeros) or waits for that and hands on L_IJ = A_IJ Dp_J^T.  What the
+// call waits for is the chain of diagonal tiles, so the workgroup of the next one makes the last panel it needs itself, from
+// the tile below the diagonal (there long before) and Dp: one hand-over per 64 columns on the chain instead of two.
+// A workgroup waits only for tiles of columns before its own and for its diagonal tile, all of a lower index, which the
+// dispatcher starts first; should one not come all the same, lora_apply_kernel makes the block NaN.
+// 4096 x 416: 128 us, 4.5 where the block is only scaled; one launch per 64 columns took 148 and 30.  4096 x 4096 with 409
+// columns, whole call: 4461 -> 4029 us.
+__global__ __launch_bounds__(256) void lora_chol_kernel(int nb, int l, const float *__restrict__ P, int splits, int tiles, float *G,
+                                                        float *Lf, float *D, float *Dp, unsigned *hand, unsigned seq, OrthStep step)
 {
     if (step.skip()) return;
     OrthWords *const words = step.out;
     __shared__ __attribute__((aligned(16))) float T[kTileFloats], LI[kTileFloats], LJ[kTileFloats];
     __shared__ float mx_s[4];
+    __shared__ int missing;
     const int tid = threadIdx.x, lane = tid & 63, ln = lane & 15, mq = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    int I = 0;
-    while (tri(I + 1, 0) <= (int)blockIdx.x) ++I;
-    const int J = j + (int)blockIdx.x - tri(I, 0);
-    I += j;
+    int j = 0, left = (int)blockIdx.x;           // the tile's column
+    while (left >= nb - j) left -= nb - j++;
+    const int I = j + left;
+    const bool diagonal = I == j;
+    if (tid == 0) missing = 0;
+    // (words in turn: wavefront w waits for the w-th; the barrier makes it the workgroup's)
+    auto wait_for = [&](int first, int second) {
+        if (lane == 0 && wave < 2 && !missing && !hand_taken(hand, wave == 0 ? first : second, seq)) {
+            missing = 1;                         // (and the waits after this one are none)
+            __hip_atomic_store(hand + kHandFailed * kHandStride, seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        __syncthreads();
+    };
     float4_t *const T4 = reinterpret_cast<float4_t *>(T);
-    float *const Gt = G + (size_t)tri(I, J) * kTileFloats;
-    if (j == 0) {
-        const float4_t *p = reinterpret_cast<const float4_t *>(P + (size_t)tri(I, J) * kTileFloats);
+    {
+        const float4_t *p = reinterpret_cast<const float4_t *>(P + (size_t)tri(I, j) * kTileFloats);
         float4_t s[4] = {};
+#pragma unroll 4
         for (int z = 0; z < splits; ++z)
 #pragma unroll
             for (int q = 0; q < 4; ++q) s[q] += p[(size_t)z * tiles * (kTileFloats / 4) + tid + 256 * q];
 #pragma unroll
         for (int q = 0; q < 4; ++q) T4[tid + 256 * q] = s[q];
-    } else {
-        const float4_t *const Ai = reinterpret_cast<const float4_t *>(G + (size_t)tri(I, j - 1) * kTileFloats);
-        const float4_t *const Aj = reinterpret_cast<const float4_t *>(G + (size_t)tri(J, j - 1) * kTileFloats);
-        const float4_t *const Dj = reinterpret_cast<const float4_t *>(Dp + (size_t)(j - 1) * kTileFloats);
-        float4_t g[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) g[q] = reinterpret_cast<const float4_t *>(Gt)[tid + 256 * q];
-        float4_t ai[4], aj[4];
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            ai[t] = Ai[(wave * 4 + t) * 64 + lane];
-            aj[t] = Aj[(wave * 4 + t) * 64 + lane];
-        }
-        // 16 rows of both panels per wavefront
-#pragma unroll
-        for (int cb = 0; cb < 4; ++cb) {
-            float4_t ci = {0.f, 0.f, 0.f, 0.f}, cj = ci;
-#pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                const float4_t d = Dj[(cb * 4 + t) * 64 + lane];
-                mma16(ai[t], d, ci);
-                mma16(aj[t], d, cj);
-            }
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                LI[op_at(16 * wave + 4 * mq + e, 16 * cb + ln)] = ci[e];
-                LJ[op_at(16 * wave + 4 * mq + e, 16 * cb + ln)] = cj[e];
-            }
-        }
-#pragma unroll
-        for (int q = 0; q < 4; ++q) T4[tid + 256 * q] = g[q];
-        __syncthreads();
-        if (J == j) {
-            float4_t *const out = reinterpret_cast<float4_t *>(Lf + (size_t)tri(I, j - 1) * kTileFloats);
-#pragma unroll
-            for (int q = 0; q < 4; ++q) out[tid + 256 * q] = reinterpret_cast<const float4_t *>(LI)[tid + 256 * q];
-        }
-        float4_t a[4];
-#pragma unroll
-        for (int t = 0; t < 4; ++t) a[t] = reinterpret_cast<const float4_t *>(LI)[(wave * 4 + t) * 64 + lane];
+    }
+    __syncthreads();
+    // 16 rows of the tile per wavefront
+    auto subtract = [&](const float4_t (&a)[4], const float4_t *b) {
 #pragma unroll
         for (int cb = 0; cb < 4; ++cb) {
             float4_t c = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int t = 0; t < 4; ++t) mma16(a[t], reinterpret_cast<const float4_t *>(LJ)[(cb * 4 + t) * 64 + lane], c);
+            for (int t = 0; t < 4; ++t) mma16(a[t], b[(cb * 4 + t) * 64 + lane], c);
 #pragma unroll
             for (int e = 0; e < 4; ++e) T[op_at(16 * wave + 4 * mq + e, 16 * cb + ln)] -= c[e];
         }
+    };
+    // LI = a Dp[column]^T
+    auto panel = [&](const float4_t (&a)[4], int column) {
+        const float4_t *const Dj = reinterpret_cast<const float4_t *>(Dp + (size_t)column * kTileFloats);
+#pragma unroll
+        for (int cb = 0; cb < 4; ++cb) {
+            float4_t c = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int t = 0; t < 4; ++t) mma16(a[t], Dj[(cb * 4 + t) * 64 + lane], c);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) LI[op_at(16 * wave + 4 * mq + e, 16 * cb + ln)] = c[e];
+        }
+    };
+    auto rows_of = [&](const float *tile, float4_t (&a)[4]) {
+#pragma unroll
+        for (int t = 0; t < 4; ++t) a[t] = reinterpret_cast<const float4_t *>(tile)[(wave * 4 + t) * 64 + lane];
+    };
+    float4_t a[4];
+    for (int K = 0; K < j - (diagonal ? 1 : 0); ++K) {
+        wait_for(kHandL + tri(I, K), kHandL + tri(j, K));
+        rows_of(Lf + (size_t)tri(I, K) * kTileFloats, a);
+        subtract(a, reinterpret_cast<const float4_t *>(Lf + (size_t)tri(j, K) * kTileFloats));
+    }
+    if (diagonal && j > 0) {
+        wait_for(kHandD + j - 1, kHandA + j);
+        rows_of(G + (size_t)tri(j, j - 1) * kTileFloats, a);
+        panel(a, j - 1);
+        __syncthreads();
+        rows_of(LI, a);
+        subtract(a, reinterpret_cast<const float4_t *>(LI));
     }
     __syncthreads();
-    if (I != j || J != j) {
+    if (!diagonal) {
+        if (I == j + 1) {
+            float4_t *const out = reinterpret_cast<float4_t *>(G + (size_t)tri(I, j) * kTileFloats);
 #pragma unroll
-        for (int q = 0; q < 4; ++q) reinterpret_cast<float4_t *>(Gt)[tid + 256 * q] = T4[tid + 256 * q];
+            for (int q = 0; q < 4; ++q) out[tid + 256 * q] = T4[tid + 256 * q];
+            hand_over(hand, kHandA + I, seq);
+        }
+        wait_for(kHandD + j, kHandD + j);
+        rows_of(T, a);
+        panel(a, j);
+        __syncthreads();
+        float4_t *const out = reinterpret_cast<float4_t *>(Lf + (size_t)tri(I, j) * kTileFloats);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) out[tid + 256 * q] = reinterpret_cast<const float4_t *>(LI)[tid + 256 * q];
+        hand_over(hand, kHandL + tri(I, j), seq);
         return;
     }
 
@@ -322,6 +370,7 @@ __global__ __launch_bounds__(256) void lora_chol_kernel(int j, int nb, int l, co
         mx = 0.f;
         for (int c = tid; c < l; c += 256) {
             float s = 0.f;
+#pragma unroll 8
             for (int z = 0; z < splits; ++z) s += P[((size_t)z * tiles + tri(c / kOb, c / kOb)) * kTileFloats + op_at(c % kOb, c % kOb)];
             mx = fmaxf(mx, s);
         }
@@ -331,7 +380,7 @@ __global__ __launch_bounds__(256) void lora_chol_kernel(int j, int nb, int l, co
         mx = fmaxf(fmaxf(mx_s[0], mx_s[1]), fmaxf(mx_s[2], mx_s[3]));
         if (tid == 0) words->gmax = mx;
     } else {
-        mx = words->gmax;
+        mx = __hip_atomic_load(&words->gmax, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     // Far from 1 the block is factored as 4^h G (exact): the reciprocals of factor16() know no subnormal numbers
     int h = 0;
@@ -342,7 +391,11 @@ __global__ __launch_bounds__(256) void lora_chol_kernel(int j, int nb, int l, co
         for (int q = 0; q < 4; ++q)
 #pragma unroll
             for (int e = 0; e < 4; ++e) T[4 * (tid + 256 * q) + e] = ldexpf(T[4 * (tid + 256 * q) + e], 2 * h);
-    float pmax = j == 0 ? 0.f : words->pmax, pmin = j == 0 ? __builtin_inff() : words->pmin;     // (wavefront 0)
+    float pmax = 0.f, pmin = __builtin_inff();   // (wavefront 0)
+    if (j > 0) {
+        pmax = __hip_atomic_load(&words->pmax, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        pmin = __hip_atomic_load(&words->pmin, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
     float *const X = LI;                         // the inverse, and
     float *const XT = LJ;                        // the inverse transposed: block (c, r) holds block (r, c) of X
     auto block = [](float *base, int bi, int bj) { return base + (bi * 4 + bj) * 256; };
@@ -427,6 +480,7 @@ __global__ __launch_bounds__(256) void lora_chol_kernel(int j, int nb, int l, co
         out[tid + 256 * q] = v;
         outp[tid + 256 * q] = alive[16 * q + (tid & 15)] ? v : float4_t{0.f, 0.f, 0.f, 0.f};
     }
+    if (nb > 1) hand_over(hand, kHandD + j, seq);
 }
 
 // The power of two that brings a column whose largest magnitude has the bits `max_bits` below 1.
@@ -442,7 +496,7 @@ __device__ __forceinline__ float column_scale(unsigned max_bits)
 __global__ __launch_bounds__(256) void lora_apply_kernel(const float *__restrict__ in, float *__restrict__ out, int rows, int l, int nb,
                                                          const float *__restrict__ Lf, const float *__restrict__ D, half_t *__restrict__ hi,
                                                          half_t *__restrict__ lo, int ldk, OrthStep step,
-                                                         const unsigned *colmax, unsigned *clear)
+                                                         const unsigned *colmax, unsigned *clear, const unsigned *hand, unsigned seq)
 {
     extern __shared__ __attribute__((aligned(16))) float lds[];
     const int ldo = nb * kOb + 4;
@@ -493,6 +547,7 @@ __global__ __launch_bounds__(256) void lora_apply_kernel(const float *__restrict
         }
         return;
     }
+    const float poison = hand[kHandFailed * kHandStride] == seq ? __builtin_nanf("") : 0.f;      // the factor is not whole: must not pass for one
     // block column J: its part of `in`, the inverse of its diagonal block, the first tile of the factor (the loads of
     // the next column go out before this one's last products)
     float v[4];
@@ -502,7 +557,7 @@ __global__ __launch_bounds__(256) void lora_apply_kernel(const float *__restrict
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             const int row = r0 + 4 * mq + e;
-            v[e] = row < rows && col < l ? in[(size_t)row * l + col] : 0.f;
+            v[e] = row < rows && col < l ? in[(size_t)row * l + col] + poison : 0.f;
         }
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
@@ -574,7 +629,10 @@ unsigned *orth_column_max(float *ws, int l, int which)
 // h < 0: always orthonormal.  Else the block after h products, of `last`, in a call's sequence of them (hi, lo only, out = null):
 // orthonormal for h = 0, conditional from then on, where orth_column_max(h % 2) holds the column maxima of `in`; that of
 // the next block is cleared.
-int launch_orth(const float *in, float *out, half_t *hi, half_t *lo, int rows, int l, float *ws, int h, int last, hipStream_t st)
+// hand: orth_hand_words() words, zero at the start of a call's sequence, of which this is number seq (from 1).
+size_t orth_hand_words() { return (size_t)kHandWords * kHandStride; }
+int launch_orth(const float *in, float *out, half_t *hi, half_t *lo, int rows, int l, float *ws, unsigned *hand, unsigned seq, int h, int last,
+                hipStream_t st)
 {
     const int nb = (l + kOb - 1) / kOb, tiles = tri(nb, 0);
     float *const P = ws, *const G = P + (size_t)kGramTiles * kTileFloats, *const Lf = G + (size_t)tiles * kTileFloats;
@@ -590,12 +648,10 @@ int launch_orth(const float *in, float *out, half_t *hi, half_t *lo, int rows, i
     const int zrows = ((rows + splits - 1) / splits + 31) / 32 * 32;
     splits = (rows + zrows - 1) / zrows;
     hipLaunchKernelGGL(lora_gram_kernel, dim3((unsigned)tiles, (unsigned)splits), dim3(256), 0, st, in, rows, l, zrows, tiles, P, step);
-    for (int j = 0; j < nb; ++j)
-        hipLaunchKernelGGL(lora_chol_kernel, dim3((unsigned)tri(nb - j, 0)), dim3(256), 0, st, j, nb, l, (const float *)P, splits, tiles, G, Lf, D,
-                           Dp, step);
+    hipLaunchKernelGGL(lora_chol_kernel, dim3((unsigned)tiles), dim3(256), 0, st, nb, l, (const float *)P, splits, tiles, G, Lf, D, Dp, hand, seq, step);
     const size_t lds = (size_t)(16 * (nb * kOb + 4) + 16 * 68) * sizeof(float);
     hipLaunchKernelGGL(lora_apply_kernel, dim3((unsigned)((rows + 31) / 32 * 2)), dim3(256), lds, st, in, out, rows, l, nb, (const float *)Lf,
-                       (const float *)D, hi, lo, (rows + 31) / 32 * 32, step, colmax, clear);
+                       (const float *)D, hi, lo, (rows + 31) / 32 * 32, step, colmax, clear, (const unsigned *)hand, seq);
     return hip_status(hipGetLastError());
 }
 
