@@ -10,45 +10,46 @@ namespace slim {
 
 constexpr int kPackSlotsMax = 12;   // float4 groups a lane keeps at most: rows up to 4 * 1024 * 12 inputs stay in registers
 
-// Kept positions of one group: order by (|w| descending, position ascending),
-// take two, return them as i0 < i1 packed as i0 | (i1 << 2).
-__device__ __forceinline__ uint32_t keep_two(float a0, float a1, float a2, float a3)
+// The codes of a row divide by its scale s.  rint(w / s) is taken from w (1 / s) wherever that decides: the product is within
+// 2e-6 of the IEEE quotient for codes up to 8 in magnitude, so the two round to the same integer unless the product
+// lies within 4e-6 of a half; there, and where the reciprocal is not a normal number with room on both sides, it is divided.
+struct RowScale {
+    float s, inv;
+};
+__device__ __forceinline__ RowScale row_scale(float s)
 {
-    int first = 0;
-    float best = a0;
-    if (a1 > best) { best = a1; first = 1; }
-    if (a2 > best) { best = a2; first = 2; }
-    if (a3 > best) { best = a3; first = 3; }
-    int second = -1;
-    float sb = -1.0f;
-    if (first != 0 && a0 > sb) { sb = a0; second = 0; }
-    if (first != 1 && a1 > sb) { sb = a1; second = 1; }
-    if (first != 2 && a2 > sb) { sb = a2; second = 2; }
-    if (first != 3 && a3 > sb) { sb = a3; second = 3; }
-    int i0 = first < second ? first : second;
-    int i1 = first < second ? second : first;
-    return (uint32_t)i0 | ((uint32_t)i1 << 2);
+    return RowScale{s, s > 0x1p-100f && s < 0x1p100f ? 1.0f / s : __builtin_nanf("")};
 }
 
-__device__ __forceinline__ uint32_t quantize_code(float w, float s)
+// Encode one group: returns the qvals byte, *m4 the metadata nibble i0 | (i1 << 2).  The kept positions i0 < i1 are the first two in the
+// order (|w| sal descending, position ascending); sal: the saliency of the four inputs (all ones: the magnitude mask), the
+// products are single binary32 multiplications.  Six comparisons, whose combinations are scalar operations on the masks of a
+// wavefront, and selects.  The kernels here are as much bound by vector instructions as by memory: a chain of selections
+// with branches and two IEEE divisions were 150 per group, these are about 60 (11008 x 4096 with scales and saliency given
+// 39.5 -> 32.4 us, and that only with both of it: the tiles of pack_scaled_kernel alone 40.7).
+__device__ __forceinline__ uint32_t encode_group(float4 v, const RowScale &rs, uint32_t *m4, float4 sal = make_float4(1.f, 1.f, 1.f, 1.f))
 {
-    float q = rintf(w / s);               // IEEE division, round half to even
-    q = fminf(fmaxf(q, -8.0f), 7.0f);
-    return (uint32_t)(int)q & 0xFu;
-}
-
-// Encode one group: returns the qvals byte, *m4 the metadata nibble.  sal: the
-// saliency of the four inputs (all ones: the magnitude mask); the products are
-// single binary32 multiplications.
-__device__ __forceinline__ uint32_t encode_group(float4 v, float s, uint32_t *m4, float4 sal = make_float4(1.f, 1.f, 1.f, 1.f))
-{
-    uint32_t sel = keep_two(fabsf(v.x) * sal.x, fabsf(v.y) * sal.y, fabsf(v.z) * sal.z, fabsf(v.w) * sal.w);
-    uint32_t i0 = sel & 3u, i1 = sel >> 2;
-    float w[4] = {v.x, v.y, v.z, v.w};
-    float w0 = i0 == 0 ? w[0] : (i0 == 1 ? w[1] : w[2]);
-    float w1 = i1 == 1 ? w[1] : (i1 == 2 ? w[2] : w[3]);
-    *m4 = sel;
-    return quantize_code(w0, s) | (quantize_code(w1, s) << 4);
+    // (a NaN loses against everything, but for one in position 0, which nothing beats)
+    const float a0 = fabsf(v.x) * sal.x, a1 = fmaxf(fabsf(v.y) * sal.y, -1.0f), a2 = fmaxf(fabsf(v.z) * sal.z, -1.0f),
+                a3 = fmaxf(fabsf(v.w) * sal.w, -1.0f);
+    // the later one comes before the earlier one, a bit per lane
+    auto mask = [](bool b) { return __builtin_amdgcn_ballot_w64(b); };
+    const uint64_t b01 = mask(a1 > a0), b02 = mask(a2 > a0), b03 = mask(a3 > a0), b12 = mask(a2 > a1), b13 = mask(a3 > a1), b23 = mask(a3 > a2);
+    // kept: at most one of the other three comes before it
+    auto one_at_most = [](uint64_t x, uint64_t y, uint64_t z) { return __builtin_amdgcn_inverse_ballot_w64(~((x & y) | (z & (x | y)))); };
+    const bool k0 = one_at_most(b01, b02, b03), k1 = one_at_most(~b01, b12, b13), k2 = one_at_most(~b02, ~b12, b23),
+               k3 = one_at_most(~b03, ~b13, ~b23);
+    const float w0 = k0 ? v.x : (k1 ? v.y : v.z), w1 = k3 ? v.w : (k2 ? v.z : v.y);
+    *m4 = (k0 ? 0u : (k1 ? 1u : 2u)) | (k3 ? 12u : (k2 ? 8u : 4u));
+    float q0 = w0 * rs.inv, q1 = w1 * rs.inv;
+    float r0 = rintf(q0), r1 = rintf(q1);
+    if (!(fmaxf(fabsf(q0 - r0), fabsf(q1 - r1)) <= 0.499996f)) {
+        r0 = rintf(w0 / rs.s);                // IEEE division, round half to even
+        r1 = rintf(w1 / rs.s);
+    }
+    r0 = fminf(fmaxf(r0, -8.0f), 7.0f);
+    r1 = fminf(fmaxf(r1, -8.0f), 7.0f);
+    return ((uint32_t)(int)r0 & 0xFu) | (((uint32_t)(int)r1 & 0xFu) << 4);
 }
 
 // THREADS lanes per row; SLOTS = float4 groups of the row each lane keeps in
@@ -60,14 +61,13 @@ __device__ __forceinline__ uint32_t encode_group(float4 v, float s, uint32_t *m4
 // t writes group t + i THREADS of slot i, whose place in the packed layout is a
 // per-lane base plus a constant per slot.
 // EX: the variant behind slim_pack_ex: saliency [k] (or null) weighs the
-// magnitudes in the 2:4 choice, scale_in [n] (or null) replaces AbsMax / 7.
+// magnitudes in the 2:4 choice.
 template <int THREADS, int SLOTS, bool EX = false>
 __global__ __launch_bounds__(THREADS) void pack_kernel(const float *__restrict__ W, int n, int k,
                                                             uint8_t *__restrict__ qvals,
                                                             uint8_t *__restrict__ meta,
                                                             float *__restrict__ scale,
-                                                            const float *__restrict__ saliency = nullptr,
-                                                            const float *__restrict__ scale_in = nullptr)
+                                                            const float *__restrict__ saliency = nullptr)
 {
     __shared__ float wave_part[THREADS / kWave];
     const int ngroups = k / 4;
@@ -121,8 +121,8 @@ __global__ __launch_bounds__(THREADS) void pack_kernel(const float *__restrict__
         a = wave_part[0];
 #pragma unroll
         for (int w = 1; w < THREADS / kWave; ++w) a = fmaxf(a, wave_part[w]);
-        float s = (a == 0.0f) ? 1.0f : a / 7.0f;
-        if (EX && scale_in) s = scale_in[o];
+        const float s = (a == 0.0f) ? 1.0f : a / 7.0f;
+        const RowScale rs = row_scale(s);
         if (tid == 0) scale[o] = s;
 
         // Lanes g and g^1 hold the two groups of one position byte (the stride is
@@ -132,11 +132,11 @@ __global__ __launch_bounds__(THREADS) void pack_kernel(const float *__restrict__
             uint32_t q = 0, m4 = 0;
             if (g < ngroups) {
                 if (EX && saliency)
-                    q = encode_group(v, s, &m4, reinterpret_cast<const float4 *>(saliency)[g]);
+                    q = encode_group(v, rs, &m4, reinterpret_cast<const float4 *>(saliency)[g]);
                 else
-                    q = encode_group(v, s, &m4);
+                    q = encode_group(v, rs, &m4);
             }
-            const uint32_t other = __shfl_xor(m4, 1, kWave);
+            const uint32_t other = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)m4, 0xB1, 0xF, 0xF, true);     // of lane ^ 1
             if (g < gpad) {
                 ql[i * q_slot] = (uint8_t)q;
                 if ((g & 1) == 0) ml[i * m_slot] = (uint8_t)(m4 | (other << 4));
@@ -150,6 +150,65 @@ __global__ __launch_bounds__(THREADS) void pack_kernel(const float *__restrict__
                 const int g = g0 + tid;
                 emit(i, g, g < ngroups ? row[g] : make_float4(0.f, 0.f, 0.f, 0.f));
             }
+        }
+    }
+}
+
+// The same with the scales given (slim_pack_ex): nothing is to be known of a row, so a workgroup takes a tile of the packed layout
+// at a time, 32 rows x 128 inputs, four groups per lane, with the loads of its next tile under way.  Sixteen lanes read 256
+// contiguous bytes of a row, and a wavefront's codes of 4 rows are 64 contiguous bytes, a workgroup's whole lines: by rows
+// they were 16 bytes of a line that the workgroups of other rows filled up.  saliency: [k], or null.
+__global__ __launch_bounds__(256) void pack_scaled_kernel(const float *__restrict__ W, int n, int k, const float *__restrict__ saliency,
+                                                          const float *scale_in, uint8_t *__restrict__ qvals, uint8_t *__restrict__ meta,
+                                                          float *scale)
+{
+    const uint32_t kt = pk_ktiles(k), ngroups = (uint32_t)k / 4, tiles = (uint32_t)((n + 31) / 32) * kt;
+    const uint32_t r = threadIdx.x >> 4, c = threadIdx.x & 15;
+    struct Tile {
+        float4 w[2][2], sal[2];              // rows r and 16 + r, groups c and 16 + c
+        float s[2];
+        uint32_t rt, ct;
+    };
+    // (lanes of the padding load the last row and group)
+    auto load = [&](uint32_t u) {
+        Tile t;
+        t.rt = u / kt;
+        t.ct = u - t.rt * kt;
+        const uint32_t g0 = min(t.ct * 32 + c, ngroups - 1), g1 = min(t.ct * 32 + c + 16, ngroups - 1);
+        if (saliency) {
+            t.sal[0] = reinterpret_cast<const float4 *>(saliency)[g0];
+            t.sal[1] = reinterpret_cast<const float4 *>(saliency)[g1];
+        }
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const uint32_t o = min(t.rt * 32 + r + 16 * i, (uint32_t)n - 1);
+            const float4 *const row = reinterpret_cast<const float4 *>(W) + (size_t)o * ngroups;
+            t.s[i] = scale_in[o];
+            t.w[i][0] = row[g0];
+            t.w[i][1] = row[g1];
+        }
+        return t;
+    };
+    uint32_t u = blockIdx.x;
+    Tile next = load(u);
+    for (; u < tiles; u += gridDim.x) {
+        const Tile t = next;
+        next = load(min(u + gridDim.x, tiles - 1));
+        uint8_t *const qt = qvals + (size_t)u * 1024, *const mt = meta + (size_t)u * 512;
+        const uint32_t rows = (uint32_t)n - t.rt * 32;
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const uint32_t o = r + 16 * i;
+            const RowScale rs = row_scale(t.s[i]);
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                uint32_t m4 = 0, q = encode_group(t.w[i][h], rs, &m4, saliency ? t.sal[h] : make_float4(1.f, 1.f, 1.f, 1.f));
+                if (o >= rows || t.ct * 32 + c + 16 * h >= ngroups) q = m4 = 0;       // padding is zero bytes
+                const uint32_t other = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)m4, 0xB1, 0xF, 0xF, true);     // of lane ^ 1
+                qt[threadIdx.x + (h * 512 + i * 256)] = (uint8_t)q;
+                if ((c & 1) == 0) mt[threadIdx.x / 2 + (h * 256 + i * 128)] = (uint8_t)(m4 | (other << 4));
+            }
+            if (t.ct == 0 && c == 0 && o < rows) scale[t.rt * 32 + o] = t.s[i];
         }
     }
 }
@@ -224,7 +283,7 @@ using namespace slim;
 
 template <bool EX>
 static int launch_pack(const float *W, slim_shape shape, uint8_t *qvals, uint8_t *meta, float *scale,
-                       const float *saliency, const float *scale_in, hipStream_t st)
+                       const float *saliency, hipStream_t st)
 {
     const int npad = (shape.n + 31) / 32 * 32;      // the padding rows of the last tile get a workgroup too
     // lanes per row: enough that a lane keeps at most 4 groups, up to 1024
@@ -232,7 +291,7 @@ static int launch_pack(const float *W, slim_shape shape, uint8_t *qvals, uint8_t
     // (two rounds of resident workgroups at most; a workgroup walks the rows it owns)
 #define SLIM_PACK_LAUNCH(T, S)                                                                                    \
     hipLaunchKernelGGL((pack_kernel<T, S, EX>), dim3(pack_grid(npad, 256 * (4096 / T))), dim3(T), 0, st, W, shape.n, \
-                       shape.k, qvals, meta, scale, saliency, scale_in)
+                       shape.k, qvals, meta, scale, saliency)
     if (groups <= 256 * 2)
         SLIM_PACK_LAUNCH(256, 2);
     else if (groups <= 256 * 4)
@@ -257,7 +316,7 @@ extern "C" int slim_pack(const float *W, slim_shape shape, uint8_t *qvals, uint8
     if (!W || !qvals || !meta || !scale) return SLIM_ERR_NULL;
     if (shape.n < 1 || shape.k < 8 || shape.k % 8) return SLIM_ERR_SHAPE;
     if (!aligned16(W) || !aligned16(qvals) || !aligned16(meta) || !aligned16(scale)) return SLIM_ERR_ALIGN;
-    return launch_pack<false>(W, shape, qvals, meta, scale, nullptr, nullptr, static_cast<hipStream_t>(stream));
+    return launch_pack<false>(W, shape, qvals, meta, scale, nullptr, static_cast<hipStream_t>(stream));
 }
 
 extern "C" int slim_pack_ex(const float *W, slim_shape shape, const float *saliency, const float *scale_in,
@@ -268,7 +327,12 @@ extern "C" int slim_pack_ex(const float *W, slim_shape shape, const float *salie
     if (!aligned16(W) || !aligned16(qvals) || !aligned16(meta) || !aligned16(scale) || !aligned16(saliency) ||
         !aligned16(scale_in))
         return SLIM_ERR_ALIGN;
-    return launch_pack<true>(W, shape, qvals, meta, scale, saliency, scale_in, static_cast<hipStream_t>(stream));
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    if (!scale_in) return launch_pack<true>(W, shape, qvals, meta, scale, saliency, st);
+    const size_t tiles = (size_t)((shape.n + 31) / 32) * pk_ktiles(shape.k);
+    hipLaunchKernelGGL(pack_scaled_kernel, dim3((unsigned)(tiles < 2048 ? tiles : 2048)), dim3(256), 0, st, W, shape.n, shape.k, saliency, scale_in,
+                       qvals, meta, scale);
+    return hip_status(hipGetLastError());
 }
 
 extern "C" int slim_unpack(const uint8_t *qvals, const uint8_t *meta, slim_shape shape, int8_t *codes,
