@@ -183,14 +183,29 @@ static int sgemm(bool ta, const float *A, int lda, const float *B, int ldb, floa
     return hip_status(hipGetLastError());
 }
 
-// One atomic add per workgroup of 256 threads (adds to one address serialise).
-__device__ __forceinline__ void block_add(float part, float *dst)
+// The sums of the report, in kSumSlots words a line apart each: adds to one word serialise (10 ns each, 1024 workgroups), and
+// so do the maxima, of which only those that change the word are sent.
+constexpr int kSumSlots = 32, kSumStride = 16;
+// One atomic add per workgroup of 256 threads.
+__device__ __forceinline__ void block_add(float part, float *slots)
 {
     __shared__ float red4[4];
     part = wave_sum(part);
     if ((threadIdx.x & 63) == 0) red4[threadIdx.x >> 6] = part;
     __syncthreads();
-    if (threadIdx.x == 0) atomicAdd(dst, red4[0] + red4[1] + red4[2] + red4[3]);
+    if (threadIdx.x == 0) atomicAdd(slots + (blockIdx.x + blockIdx.y * gridDim.x) % kSumSlots * kSumStride, red4[0] + red4[1] + red4[2] + red4[3]);
+}
+// The largest of a workgroup's non-negative values into a word that holds the bits of one (they order as integers).
+__device__ __forceinline__ void block_max(float mx, float *dst)
+{
+    __shared__ float mx4[4];
+    mx = wave_max(mx);
+    if ((threadIdx.x & 63) == 0) mx4[threadIdx.x >> 6] = mx;
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    unsigned *const word = reinterpret_cast<unsigned *>(dst);
+    const unsigned bits = __float_as_uint(fmaxf(fmaxf(mx4[0], mx4[1]), fmaxf(mx4[2], mx4[3])));
+    if (bits > __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(word, bits);
 }
 
 // ---- x = x~ + min|x~| (Alg. 2), or ones ----
@@ -209,42 +224,47 @@ __global__ __launch_bounds__(1024) void lora_shift_kernel(const float *xt, int k
 }
 
 // ---- S = (W - W^C) diag(x); the packed bytes are read in their tiled layout ----
-// One thread per group of four inputs.  sq[0] += ||S||_F^2, sq[4]: bits of the largest magnitude.
-__global__ __launch_bounds__(256) void lora_error_kernel(const float *W, const uint8_t *qvals, const uint8_t *meta,
-                                                         const float *scale, const float *x, int n, int k, float *S,
-                                                         float *sq)
+// One thread per group of four inputs, in turn.  s2: slots of ||S||_F^2, mx_word: bits of the largest magnitude.
+// HBM-bound (W and S, 8 bytes per weight): 4096 x 4096 27 us (with a 64-bit division per group and every sum added to one word 42).
+__global__ __launch_bounds__(256) void lora_error_kernel(const float *__restrict__ W, const uint8_t *__restrict__ qvals,
+                                                         const uint8_t *__restrict__ meta, const float *__restrict__ scale,
+                                                         const float *__restrict__ x, int n, int k, float *__restrict__ S, float *s2, float *mx_word)
 {
-    const int groups = k / 4;
-    const size_t total = (size_t)n * groups;
-    const uint32_t kt = pk_ktiles(k);
+    const uint32_t groups = (uint32_t)k / 4, kt = pk_ktiles(k);
+    const size_t first = (size_t)blockIdx.x * blockDim.x + threadIdx.x, stride = (size_t)gridDim.x * blockDim.x;
+    // row and group of the next one without a division
+    size_t o = first / groups;
+    uint32_t g = (uint32_t)(first - o * groups);
+    const size_t row_step = stride / groups;
+    const uint32_t group_step = (uint32_t)(stride - row_step * groups);
     float part = 0.f, mx = 0.f;
-    for (size_t t = (size_t)blockIdx.x * blockDim.x + threadIdx.x; t < total; t += (size_t)gridDim.x * blockDim.x) {
-        const uint32_t o = (uint32_t)(t / groups), g = (uint32_t)(t % groups);
-        const uint32_t q = qvals[pk_qoff(o, g, kt)];
-        const uint32_t mb = meta[pk_moff(o, g >> 1, kt)];
+    while (o < (size_t)n) {
+        const uint32_t q = qvals[pk_qoff((uint32_t)o, g, kt)];
+        const uint32_t mb = meta[pk_moff((uint32_t)o, g >> 1, kt)];
         const uint32_t m4 = (g & 1) ? (mb >> 4) : (mb & 15u);
         const float s = scale[o];
-        float wc[4] = {0.f, 0.f, 0.f, 0.f};
-        wc[m4 & 3u] = (float)nibble_to_int(q & 15u) * s;
-        wc[(m4 >> 2) & 3u] = (float)nibble_to_int(q >> 4) * s;
-        const float4_t w = *reinterpret_cast<const float4_t *>(W + (size_t)o * k + 4 * g);
-        const float4_t xv = *reinterpret_cast<const float4_t *>(x + 4 * g);
+        const float4_t w = reinterpret_cast<const float4_t *>(W)[o * groups + g];
+        const float4_t xv = reinterpret_cast<const float4_t *>(x)[g];
+        const uint32_t i0 = m4 & 3u, i1 = (m4 >> 2) & 3u;
+        const float w0 = (float)nibble_to_int(q & 15u) * s, w1 = (float)nibble_to_int(q >> 4) * s;
         float4_t e;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            e[i] = (w[i] - wc[i]) * xv[i];
+        for (uint32_t i = 0; i < 4; ++i) {
+            const float wc = i == i1 ? w1 : (i == i0 ? w0 : 0.f);
+            e[i] = (w[i] - wc) * xv[i];
             part += e[i] * e[i];
             mx = fmaxf(mx, fabsf(e[i]));
         }
-        *reinterpret_cast<float4_t *>(S + (size_t)o * k + 4 * g) = e;
+        reinterpret_cast<float4_t *>(S)[o * groups + g] = e;
+        o += row_step;
+        g += group_step;
+        if (g >= groups) {
+            g -= groups;
+            ++o;
+        }
     }
-    block_add(part, sq);
-    __shared__ float mx4[4];
-    mx = wave_max(mx);
-    if ((threadIdx.x & 63) == 0) mx4[threadIdx.x >> 6] = mx;
-    __syncthreads();
-    if (threadIdx.x == 0)                    // non-negative floats order as integers
-        atomicMax(reinterpret_cast<unsigned *>(sq + 4), __float_as_uint(fmaxf(fmaxf(mx4[0], mx4[1]), fmaxf(mx4[2], mx4[3]))));
+    block_add(part, s2);
+    block_max(mx, mx_word);
 }
 
 // ---- start block: uniform in (-1, 1) from a hash of (seed, element), columns >= r zero ----
@@ -258,12 +278,13 @@ __device__ __forceinline__ uint32_t mix32(uint32_t v)
     return v;
 }
 
-// (element t = row * l + column; written to Z, or as the two fp16 numbers of the split products, columns as rows)
-__global__ void lora_init_kernel(float *Z, half_t *hi, half_t *lo, int rows, int l, int r, uint32_t seed)
+// Element t = row * l + column; written to Z, or as the two fp16 numbers of the split products, columns as rows: blockIdx.y is
+// the column, so that the stores are contiguous (4096 x 416: 20 -> 5 us).
+__global__ __launch_bounds__(256) void lora_init_kernel(float *Z, half_t *hi, half_t *lo, int rows, int l, int r, uint32_t seed)
 {
-    const size_t total = (size_t)rows * l;
-    for (size_t t = (size_t)blockIdx.x * blockDim.x + threadIdx.x; t < total; t += (size_t)gridDim.x * blockDim.x) {
-        const int c = (int)(t % l);
+    const int c = blockIdx.y;
+    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < rows; i += gridDim.x * blockDim.x) {
+        const size_t t = (size_t)i * l + c;
         const uint32_t hsh = mix32(mix32((uint32_t)t ^ seed) + (uint32_t)(t >> 32) + 0x9e3779b9u * seed);
         const float z = c < r ? ((float)(hsh >> 8) + 0.5f) * (2.0f / 16777216.0f) - 1.0f : 0.f;
         if (Z) {
@@ -272,8 +293,8 @@ __global__ void lora_init_kernel(float *Z, half_t *hi, half_t *lo, int rows, int
         }
         const float v = z * kBlockSplit;
         const half_t x = (half_t)v;
-        hi[(size_t)c * rows + t / l] = x;
-        lo[(size_t)c * rows + t / l] = (half_t)(v - (float)x);
+        hi[(size_t)c * rows + i] = x;
+        lo[(size_t)c * rows + i] = (half_t)(v - (float)x);
     }
 }
 
@@ -290,7 +311,7 @@ int launch_lora_split(const float *S, int n, int k, const unsigned *max_bits, ha
 int launch_lora_split_gemm(const half_t *Ah, const half_t *Al, const unsigned *max_bits, const half_t *Bh, const half_t *Bl, int rows, int cols,
                            int K, float *P, float *Y, unsigned *colmax, hipStream_t st);
 
-// ---- results: L fp16 [n][r] = Q[:, :r];  R fp16 [r][k] = R~[:r] / x;  sq[1] += ||R~[:r]||_F^2 ----
+// ---- results: L fp16 [n][r] = Q[:, :r];  R fp16 [r][k] = R~[:r] / x;  r2: slots of ||R~[:r]||_F^2 ----
 __global__ void lora_out_l_kernel(const float *Q, int n, int l, int r, half_t *L)
 {
     const size_t total = (size_t)n * r;
@@ -300,17 +321,24 @@ __global__ void lora_out_l_kernel(const float *Q, int n, int l, int r, half_t *L
     }
 }
 
-__global__ __launch_bounds__(256) void lora_out_r_kernel(const float *Rt, const float *x, int k, int r, half_t *R, float *sq)
+// (blockIdx.y: the row)
+__global__ __launch_bounds__(256) void lora_out_r_kernel(const float *__restrict__ Rt, const float *__restrict__ x, int k, half_t *__restrict__ R,
+                                                         float *r2)
 {
-    const size_t total = (size_t)r * k;
+    const float4_t *const row = reinterpret_cast<const float4_t *>(Rt + (size_t)blockIdx.y * k);
+    half4_t *const out = reinterpret_cast<half4_t *>(R + (size_t)blockIdx.y * k);
     float part = 0.f;
-    for (size_t t = (size_t)blockIdx.x * blockDim.x + threadIdx.x; t < total; t += (size_t)gridDim.x * blockDim.x) {
-        const size_t j = t % k;
-        const float v = Rt[t];
-        part += v * v;
-        R[t] = (half_t)(v / x[j]);
+    for (int j = blockIdx.x * blockDim.x + threadIdx.x; j < k / 4; j += gridDim.x * blockDim.x) {
+        const float4_t v = row[j], xv = reinterpret_cast<const float4_t *>(x)[j];
+        half4_t h;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            part += v[e] * v[e];
+            h[e] = (half_t)(v[e] / xv[e]);
+        }
+        out[j] = h;
     }
-    block_add(part, sq + 1);
+    block_add(part, r2);
 }
 
 // sq[2] = max |G - I| over the leading r x r block (orthonormality of the final Q)
@@ -321,14 +349,20 @@ __global__ __launch_bounds__(256) void lora_ortho_kernel(const float *G, int l, 
         const int i = t / r, c = t % r;
         mx = fmaxf(mx, fabsf(G[(size_t)i * l + c] - (i == c ? 1.0f : 0.f)));
     }
-    mx = wave_max(mx);
-    if ((threadIdx.x & 63) == 0) atomicMax(reinterpret_cast<unsigned *>(sq + 2), __float_as_uint(mx));   // non-negative floats order as integers
+    block_max(mx, sq + 2);
 }
 
 // the four numbers of the report, out of the workspace (a kernel, so that the call is kernels only)
-__global__ void lora_report_kernel(const float *sq, float *diag)
+__global__ __launch_bounds__(64) void lora_report_kernel(const float *sq, const float *sums, float *diag)
 {
-    if (threadIdx.x < 4) diag[threadIdx.x] = threadIdx.x < 3 ? sq[threadIdx.x] : 0.f;
+    const int t = threadIdx.x;
+    if (t < 2) {
+        float s = 0.f;
+        for (int i = 0; i < kSumSlots; ++i) s += sums[(t * kSumSlots + i) * kSumStride];
+        diag[t] = s;
+    }
+    if (t == 2) diag[2] = sq[2];
+    if (t == 3) diag[3] = 0.f;
 }
 
 struct LoraPlan {
@@ -368,7 +402,7 @@ static LoraPlan plan_lora(int n, int k, int rank)
     p.G = take(l * l);
     p.O = take(orth_floats(p.l));
     p.Rt = take(l * k);
-    p.sq = take(64 + orth_hand_words());
+    p.sq = take(64 + 2 * kSumSlots * kSumStride + orth_hand_words());
     p.total = off;
     return p;
 }
@@ -418,17 +452,18 @@ extern "C" int slim_compute_adapters(const float *W, const uint8_t *qvals, const
     auto launched = [&]() { return hip_status(hipGetLastError()); };
     auto grid_for = [](size_t count) { return dim3((unsigned)std::min<size_t>((count + 255) / 256, 4096)); };
 
-    // (the words that the orth()s' workgroups hand over by lie behind the sums)
-    unsigned *const hand = reinterpret_cast<unsigned *>(sq + 64);
+    // (behind the maxima: the slots of the two sums, and the words that the orth()s' workgroups hand over by)
+    float *const s2 = sq + 64, *const r2 = s2 + kSumSlots * kSumStride;
+    unsigned *const hand = reinterpret_cast<unsigned *>(r2 + kSumSlots * kSumStride);
     unsigned orths = 0;
     auto orth = [&](const float *in, float *out, half_t *hi, half_t *lo, int rows, int h, int last) {
         return launch_orth(in, out, hi, lo, rows, p.l, O, hand, ++orths, h, last, st);
     };
-    SLIM_TRY(launch_fill(sq, 64 + orth_hand_words(), 0.f, st));
+    SLIM_TRY(launch_fill(sq, 64 + 2 * kSumSlots * kSumStride + orth_hand_words(), 0.f, st));
     hipLaunchKernelGGL(lora_shift_kernel, dim3(1), dim3(1024), 0, st, x_tilde, k, x);
     SLIM_TRY(launched());
     hipLaunchKernelGGL(lora_error_kernel, dim3(std::min(grid_for((size_t)n * (k / 4)).x, 1024u)), dim3(256), 0, st, W, qvals, meta, scale,
-                       (const float *)x, n, k, S, sq);
+                       (const float *)x, n, k, S, s2, sq + 4);
     SLIM_TRY(launched());
 
     float *Z = p.split ? nullptr : reinterpret_cast<float *>(ws + p.Z);
@@ -442,7 +477,7 @@ extern "C" int slim_compute_adapters(const float *W, const uint8_t *qvals, const
         }
         SLIM_TRY(launch_lora_split(S, n, k, mx, Sh[0], Sh[1], Sh[2], Sh[3], st));
     }
-    hipLaunchKernelGGL(lora_init_kernel, grid_for((size_t)k * l), dim3(256), 0, st, Z, blk[2], blk[3], k, l, r, seed);
+    hipLaunchKernelGGL(lora_init_kernel, dim3((unsigned)std::min((k + 255) / 256, 1024), (unsigned)l), dim3(256), 0, st, Z, blk[2], blk[3], k, l, r, seed);
     SLIM_TRY(launched());
     const int last = 2 * q;                  // products with S^T and S, in turn, after the first
     // (column maxima: for a block that may only be scaled)
@@ -467,16 +502,16 @@ extern "C" int slim_compute_adapters(const float *W, const uint8_t *qvals, const
     SLIM_TRY(orth(Q, Y, nullptr, nullptr, n, -1, last));    // second pass: orthonormal to rounding
     SLIM_TRY(sgemm(true, Y, l, S, k, Rt, l, k, n, st));          // R~ = Q^T S        [l][k]
     SLIM_TRY(sgemm(true, Y, l, Y, l, G, l, l, n, st));           // Gram of the final block, for the report
-    hipLaunchKernelGGL(lora_ortho_kernel, grid_for((size_t)r * r), dim3(256), 0, st, (const float *)G, l, r, sq);
+    hipLaunchKernelGGL(lora_ortho_kernel, dim3(std::min(grid_for((size_t)r * r).x, 256u)), dim3(256), 0, st, (const float *)G, l, r, sq);
     SLIM_TRY(launched());
     hipLaunchKernelGGL(lora_out_l_kernel, grid_for((size_t)n * r), dim3(256), 0, st, (const float *)Y, n, l, r,
                        reinterpret_cast<half_t *>(L));
     SLIM_TRY(launched());
-    hipLaunchKernelGGL(lora_out_r_kernel, dim3(std::min(grid_for((size_t)r * k).x, 1024u)), dim3(256), 0, st, (const float *)Rt, (const float *)x, k,
-                       r, reinterpret_cast<half_t *>(R), sq);
+    hipLaunchKernelGGL(lora_out_r_kernel, dim3((unsigned)std::min((k / 4 + 255) / 256, 1024), (unsigned)r), dim3(256), 0, st, (const float *)Rt,
+                       (const float *)x, k, reinterpret_cast<half_t *>(R), r2);
     SLIM_TRY(launched());
     if (diag) {
-        hipLaunchKernelGGL(lora_report_kernel, dim3(1), dim3(64), 0, st, (const float *)sq, diag);
+        hipLaunchKernelGGL(lora_report_kernel, dim3(1), dim3(64), 0, st, (const float *)sq, (const float *)s2, diag);
         SLIM_TRY(launched());
     }
 #undef SLIM_TRY
