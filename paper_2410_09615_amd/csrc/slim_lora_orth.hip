@@ -11,7 +11,7 @@
 //                       registers of one wavefront;
 //   lora_apply_kernel   a workgroup carries 16 rows of `in` through all block columns, which stay in LDS:
 //                       out_J = (in_J - sum_{K<J} out_K L_JK^T) X_JJ^T, one launch for the whole block.
-// 4096 x 416: 3 launches (gram 22 us, factorisation 128, apply 25) where a factorisation with one launch per 64 columns took
+// 4096 x 416: 3 launches (gram 22 us, factorisation 94, apply 25) where a factorisation with one launch per 64 columns took
 // 148 us and seven launches of 4 us where the block is only scaled, and with separate panel, trailing and column products
 // and a 64-step one-workgroup diagonal 700.
 //
@@ -48,10 +48,9 @@ constexpr float kSpread = 1e4f;                // largest / smallest pivot up to
 constexpr int kMaxRun = 8;                     // products between two blocks that are orthonormalised
 constexpr int kMaxBlocks = 1024 / kOb, kMaxTri = kMaxBlocks * (kMaxBlocks + 1) / 2;      // blocks of columns, tiles of a lower triangle
 
-// Words of an orth() that its kernels share: the largest diagonal entry of G, the largest and the smallest pivot
-// so far, the product after which the next block has to be orthonormalised, and how many it is away.
+// Words of an orth() that its kernels and the next orth() read: the product after which the next block has to be
+// orthonormalised, and how many it is away.
 struct OrthWords {
-    float gmax, pmax, pmin;
     int due, run;
 };
 // A conditional orth(): `h` products with S or S^T after the first block; the block is only scaled where h < in->due.
@@ -180,43 +179,50 @@ __device__ __forceinline__ void for_each(F &&f)
     for_each_impl(std::make_integer_sequence<int, N>{}, f);
 }
 
-// 16 x 16: lane i of sixteen holds row i of the symmetric block a = Lc Lc^T; x: row i of Lc^-1.  The steps run on
-// a = M diag(d) M^T, M with a unit diagonal, whose chain has a reciprocal and no square root, and the rows of M^-1 are
-// scaled by 1 / sqrt(d) at the end; they broadcast across the sixteen lanes without LDS or barriers.
-// pmax, pmin: the largest and the smallest pivot of a row so far, but for those of `dead`.  Returns whether this row's
-// pivot is above the floor.
-__device__ __forceinline__ bool factor16(float (&a)[16], float (&x)[16], int i, float floor_, float dead, float &pmax, float &pmin)
+// The value that lane i % 16 of the G-th sixteen lanes holds, to lane i of all four.
+template <int G>
+__device__ __forceinline__ float from_group(float v)
 {
-#pragma unroll
-    for (int c = 0; c < 16; ++c) x[c] = i == c ? 1.0f : 0.f;
-    float mine = 1.0f;                           // this row's pivot
-    bool alive = false;
+    const unsigned b = __builtin_bit_cast(unsigned, v);
+    const auto p = __builtin_amdgcn_permlane16_swap(b, b, false, false);        // groups 0, 0, 2, 2 and 1, 1, 3, 3
+    const unsigned h = p[G & 1];
+    const auto q = __builtin_amdgcn_permlane32_swap(h, h, false, false);
+    return __builtin_bit_cast(float, (unsigned)q[G >> 1]);
+}
+
+// 16 x 16: lane i of group g (sixteen lanes) holds row i, columns 4 g .. 4 g + 3, of the symmetric block a = Lc Lc^T; on
+// return those of Lc^-1.  The steps run on a = M diag(d) M^T, M with a unit diagonal, whose chain has a reciprocal and no square
+// root, and the rows of M^-1 are scaled by 1 / sqrt(d) at the end.  Step c adds m_i = -a_ic / d_c times row c to the rows i
+// below it: to the columns of a after c, to those of M^-1 before it, and column c becomes that of M^-1, so that one register
+// holds a column of the one and then of the other.  Broadcasts are between lanes, without LDS or barriers.  (With a row
+// of both in each of sixteen lanes the 64 x 64 block took 13 us instead of 9: twice the instructions per step.)
+// pmax, pmin: the largest and the smallest pivot of this lane's rows so far, but for those of `dead`.  Returns whether this row's
+// pivot is above the floor.
+__device__ __forceinline__ bool factor16(float4_t &w, int i, int g, float floor_, float dead, float &pmax, float &pmin)
+{
+    float d_i = 1.0f;                            // this row's pivot
     for_each<16>([&](auto cc) {
         constexpr int c = cc;
-        const float d = row_lane<c>(a[c]);
-        const bool ok = d > floor_;              // no: a column in the span of the ones before it: pivot `dead`, nothing to subtract
-        if (i == c) {
-            mine = ok ? d : dead;
-            alive = ok;
-        }
-        pmax = ok ? fmaxf(pmax, d) : pmax;
-        pmin = ok ? fminf(pmin, d) : pmin;
+        const float col = from_group<c / 4>(w[c % 4]);
+        const float d = row_lane<c>(col);
+        d_i = i == c ? d : d_i;
         float q = __builtin_amdgcn_rcpf(d);
         q = q * (2.0f - d * q);                  // to rounding
-        const float m = ok && i > c ? -a[c] * q : 0.f;
-        const float ac = a[c];
-        for_each<16>([&](auto jc) {
-            constexpr int j = jc;
-            if constexpr (j > c)
-                a[j] = __builtin_fmaf(row_lane<j>(ac), m, a[j]);
-            else
-                x[j] = __builtin_fmaf(row_lane<c>(x[j]), m, x[j]);
-        });
-    });
-    float q = __builtin_amdgcn_rsqf(mine);
-    q = q * (1.5f - 0.5f * mine * q * q);        // 1 / sqrt(d) to rounding
+        const float m = d > floor_ && i > c ? -col * q : 0.f;    // (d below: a column in the span of the ones before it: nothing to subtract)
 #pragma unroll
-    for (int c = 0; c < 16; ++c) x[c] *= q;
+        for (int e = 0; e < 4; ++e) {
+            const float s = __builtin_fmaf(row_lane<c>(w[e]), m, w[e]);
+            w[e] = e == c % 4 && g == c / 4 ? (i == c ? 1.0f : m) : s;
+        }
+    });
+    const bool alive = d_i > floor_;
+    pmax = alive ? fmaxf(pmax, d_i) : pmax;
+    pmin = alive ? fminf(pmin, d_i) : pmin;
+    const float p = alive ? d_i : dead;
+    float q = __builtin_amdgcn_rsqf(p);
+    q = q * (1.5f - 0.5f * p * q * q);           // 1 / sqrt(d) to rounding
+#pragma unroll
+    for (int e = 0; e < 4; ++e) w[e] *= q;
     return alive;
 }
 
@@ -232,10 +238,10 @@ __device__ __forceinline__ int next_run(int done, float pmax, float pmin)
     return done;
 }
 
-// What the workgroups of a factorisation hand to one another: a tile of the factor (at tri(I, J)), the tile below a
-// diagonal one before it is scaled, the inverse of a diagonal tile.  A word each, in a line of its own, holds the number of the
-// orth() whose tile it is (kHandFailed: that of one whose wait ran out).
-enum { kHandL = 0, kHandA = kMaxTri, kHandD = kMaxTri + kMaxBlocks, kHandFailed = kMaxTri + 2 * kMaxBlocks, kHandWords };
+// What the workgroups of a factorisation hand to one another: a tile of the factor (at tri(I, J)), a diagonal tile and the
+// one to its left before the last column is subtracted, the inverse of a diagonal tile.  A word each, in a line of its own,
+// holds the number of the orth() whose tile it is (kHandFailed: that of one whose wait ran out).
+enum { kHandL = 0, kHandT = kMaxTri, kHandA = kHandT + kMaxBlocks, kHandD = kHandA + kMaxBlocks, kHandFailed = kHandD + kMaxBlocks, kHandWords };
 constexpr int kHandStride = 16;
 constexpr int kHandPolls = 1 << 20;            // half a microsecond or more each; a wait is over after some tens of them
 
@@ -244,7 +250,7 @@ __device__ __forceinline__ void hand_over(unsigned *hand, int what, unsigned seq
 {
     asm volatile("s_waitcnt vmcnt(0)" : : : "memory");
     __syncthreads();
-    if (threadIdx.x == 0) {
+    if (threadIdx.x == 192) {                    // (not of the wavefront that factors)
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
         __hip_atomic_store(hand + what * kHandStride, seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
@@ -260,20 +266,21 @@ __device__ __forceinline__ bool hand_taken(unsigned *hand, int what, unsigned se
     return true;
 }
 
-// G = Lc Lc^T in one launch.  A workgroup has one tile (I, J), I >= J, column after column: it adds up the tile's partial
-// tiles, subtracts L_IK L_JK^T for the columns K < J as they come, and then either factors and inverts the diagonal tile (D[J]
-// whole, Dp[J] with the rows of pivots below the floor as zeros) or waits for that and hands on L_IJ = A_IJ Dp_J^T.  What the
-// call waits for is the chain of diagonal tiles, so the workgroup of the next one makes the last panel it needs itself, from
-// the tile below the diagonal (there long before) and Dp: one hand-over per 64 columns on the chain instead of two.
-// A workgroup waits only for tiles of columns before its own and for its diagonal tile, all of a lower index, which the
-// dispatcher starts first; should one not come all the same, lora_apply_kernel makes the block NaN.
-// 4096 x 416: 128 us, 4.5 where the block is only scaled; one launch per 64 columns took 148 and 30.  4096 x 4096 with 409
-// columns, whole call: 4461 -> 4029 us.
+// G = Lc Lc^T in one launch.  What it waits for is the chain of diagonal tiles, so workgroup 0 factors and inverts all of
+// them, one after the other (D[J] whole, Dp[J] with the rows of pivots below the floor as zeros), and nothing on that chain
+// goes through memory but what the others have ready: the tiles (J, J) and (J, J - 1) with the columns before J - 1
+// subtracted.  The panel between those and the column J - 1 it makes itself, from the inverse it has in LDS.  Every other
+// workgroup has a tile (I, J), I >= J, column after column: it adds up the tile's partial tiles, subtracts L_IK L_JK^T for the
+// columns before its own as they come, and hands the tile to workgroup 0 or waits for D[J] and hands on L_IJ = A_IJ Dp_J^T.
+// A workgroup waits for workgroup 0 and for tiles of columns before its own, of a lower index, and workgroup 0 for tiles whose
+// workgroups wait for it in no more than it has handed on: with workgroups started in the order of their index there is always
+// one that runs.  A wait is bounded all the same; should a tile not come, lora_apply_kernel makes the block NaN.
+// 4096 x 416: 94 us, 4.5 where the block is only scaled; one launch per 64 columns took 148 and 30.  (With a diagonal tile's
+// inverse handed through memory to the workgroup of the next one: 4 us more.)
 __global__ __launch_bounds__(256) void lora_chol_kernel(int nb, int l, const float *__restrict__ P, int splits, int tiles, float *G,
                                                         float *Lf, float *D, float *Dp, unsigned *hand, unsigned seq, OrthStep step)
 {
     if (step.skip()) return;
-    OrthWords *const words = step.out;
     __shared__ __attribute__((aligned(16))) float T[kTileFloats], LI[kTileFloats], LJ[kTileFloats];
     __shared__ float mx_s[4];
     __shared__ int missing;
@@ -282,7 +289,6 @@ __global__ __launch_bounds__(256) void lora_chol_kernel(int nb, int l, const flo
     int j = 0, left = (int)blockIdx.x;           // the tile's column
     while (left >= nb - j) left -= nb - j++;
     const int I = j + left;
-    const bool diagonal = I == j;
     if (tid == 0) missing = 0;
     // (words in turn: wavefront w waits for the w-th; the barrier makes it the workgroup's)
     auto wait_for = [&](int first, int second) {
@@ -315,172 +321,157 @@ __global__ __launch_bounds__(256) void lora_chol_kernel(int nb, int l, const flo
             for (int e = 0; e < 4; ++e) T[op_at(16 * wave + 4 * mq + e, 16 * cb + ln)] -= c[e];
         }
     };
-    // LI = a Dp[column]^T
-    auto panel = [&](const float4_t (&a)[4], int column) {
-        const float4_t *const Dj = reinterpret_cast<const float4_t *>(Dp + (size_t)column * kTileFloats);
+    // to = a d^T
+    auto panel = [&](const float4_t (&a)[4], const float4_t *d, float *to) {
 #pragma unroll
         for (int cb = 0; cb < 4; ++cb) {
             float4_t c = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int t = 0; t < 4; ++t) mma16(a[t], Dj[(cb * 4 + t) * 64 + lane], c);
+            for (int t = 0; t < 4; ++t) mma16(a[t], d[(cb * 4 + t) * 64 + lane], c);
 #pragma unroll
-            for (int e = 0; e < 4; ++e) LI[op_at(16 * wave + 4 * mq + e, 16 * cb + ln)] = c[e];
+            for (int e = 0; e < 4; ++e) to[op_at(16 * wave + 4 * mq + e, 16 * cb + ln)] = c[e];
         }
     };
     auto rows_of = [&](const float *tile, float4_t (&a)[4]) {
 #pragma unroll
         for (int t = 0; t < 4; ++t) a[t] = reinterpret_cast<const float4_t *>(tile)[(wave * 4 + t) * 64 + lane];
     };
-    float4_t a[4];
-    for (int K = 0; K < j - (diagonal ? 1 : 0); ++K) {
-        wait_for(kHandL + tri(I, K), kHandL + tri(j, K));
-        rows_of(Lf + (size_t)tri(I, K) * kTileFloats, a);
-        subtract(a, reinterpret_cast<const float4_t *>(Lf + (size_t)tri(j, K) * kTileFloats));
-    }
-    if (diagonal && j > 0) {
-        wait_for(kHandD + j - 1, kHandA + j);
-        rows_of(G + (size_t)tri(j, j - 1) * kTileFloats, a);
-        panel(a, j - 1);
-        __syncthreads();
-        rows_of(LI, a);
-        subtract(a, reinterpret_cast<const float4_t *>(LI));
-    }
-    __syncthreads();
-    if (!diagonal) {
-        if (I == j + 1) {
-            float4_t *const out = reinterpret_cast<float4_t *>(G + (size_t)tri(I, j) * kTileFloats);
+    auto store_tile = [&](float *to, const float *tile) {
 #pragma unroll
-            for (int q = 0; q < 4; ++q) out[tid + 256 * q] = T4[tid + 256 * q];
-            hand_over(hand, kHandA + I, seq);
+        for (int q = 0; q < 4; ++q) reinterpret_cast<float4_t *>(to)[tid + 256 * q] = reinterpret_cast<const float4_t *>(tile)[tid + 256 * q];
+    };
+    float4_t a[4];
+    if (blockIdx.x > 0) {
+        for (int K = 0; K < (I == j ? j - 1 : j); ++K) {
+            wait_for(kHandL + tri(I, K), kHandL + tri(j, K));
+            rows_of(Lf + (size_t)tri(I, K) * kTileFloats, a);
+            subtract(a, reinterpret_cast<const float4_t *>(Lf + (size_t)tri(j, K) * kTileFloats));
+        }
+        __syncthreads();
+        if (I <= j + 1) {
+            store_tile(G + (size_t)tri(I, j) * kTileFloats, T);
+            hand_over(hand, (I == j ? kHandT : kHandA) + I, seq);
+            if (I == j) return;
         }
         wait_for(kHandD + j, kHandD + j);
         rows_of(T, a);
-        panel(a, j);
+        panel(a, reinterpret_cast<const float4_t *>(Dp + (size_t)j * kTileFloats), LI);
         __syncthreads();
-        float4_t *const out = reinterpret_cast<float4_t *>(Lf + (size_t)tri(I, j) * kTileFloats);
-#pragma unroll
-        for (int q = 0; q < 4; ++q) out[tid + 256 * q] = reinterpret_cast<const float4_t *>(LI)[tid + 256 * q];
+        store_tile(Lf + (size_t)tri(I, j) * kTileFloats, LI);
         hand_over(hand, kHandL + tri(I, j), seq);
         return;
     }
 
-    // ---- the diagonal tile ----
-    float mx;
-    if (j == 0) {
-        mx = 0.f;
-        for (int c = tid; c < l; c += 256) {
-            float s = 0.f;
+    // ---- the diagonal tiles ----
+    float mx = 0.f;                              // the largest diagonal entry of G
+    for (int c = tid; c < l; c += 256) {
+        float s = 0.f;
 #pragma unroll 8
-            for (int z = 0; z < splits; ++z) s += P[((size_t)z * tiles + tri(c / kOb, c / kOb)) * kTileFloats + op_at(c % kOb, c % kOb)];
-            mx = fmaxf(mx, s);
-        }
-        mx = wave_max(mx);
-        if (lane == 0) mx_s[wave] = mx;
-        __syncthreads();
-        mx = fmaxf(fmaxf(mx_s[0], mx_s[1]), fmaxf(mx_s[2], mx_s[3]));
-        if (tid == 0) words->gmax = mx;
-    } else {
-        mx = __hip_atomic_load(&words->gmax, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        for (int z = 0; z < splits; ++z) s += P[((size_t)z * tiles + tri(c / kOb, c / kOb)) * kTileFloats + op_at(c % kOb, c % kOb)];
+        mx = fmaxf(mx, s);
     }
+    mx = wave_max(mx);
+    if (lane == 0) mx_s[wave] = mx;
+    __syncthreads();
+    mx = fmaxf(fmaxf(mx_s[0], mx_s[1]), fmaxf(mx_s[2], mx_s[3]));
     // Far from 1 the block is factored as 4^h G (exact): the reciprocals of factor16() know no subnormal numbers
     int h = 0;
     if (mx > 0.f && !(mx > 0x1p-60f && mx < 0x1p60f)) h = min(max(-(__builtin_amdgcn_frexp_expf(mx) / 2), -63), 63);
     const float dead = ldexpf(fmaxf(1.0f, mx * 1e-9f), 2 * h), floor_ = ldexpf(mx, 2 * h) * 1e-9f;
-    if (h != 0)                                  // (a thread's own pieces)
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) T[4 * (tid + 256 * q) + e] = ldexpf(T[4 * (tid + 256 * q) + e], 2 * h);
-    float pmax = 0.f, pmin = __builtin_inff();   // (wavefront 0)
-    if (j > 0) {
-        pmax = __hip_atomic_load(&words->pmax, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        pmin = __hip_atomic_load(&words->pmin, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
+    float pmax = 0.f, pmin = __builtin_inff();   // (of the rows of a lane of wavefront 0)
     float *const X = LI;                         // the inverse, and
     float *const XT = LJ;                        // the inverse transposed: block (c, r) holds block (r, c) of X
     auto block = [](float *base, int bi, int bj) { return base + (bi * 4 + bj) * 256; };
     auto operand = [&](const float *blk) { return reinterpret_cast<const float4_t *>(blk)[lane]; };
     __shared__ __attribute__((aligned(16))) float M[3][256];
     __shared__ int alive[kOb];                   // pivot above the floor
-    for (int idx = tid; idx < kTileFloats; idx += 256) X[idx] = 0.f;
-    __syncthreads();
-    for (int b = 0; b < 4; ++b) {
-        if (wave == 0) {
-            float a[16], x[16];
+    for (j = 0; j < nb; ++j) {
+        if (j > 0) {
+            wait_for(kHandT + j, kHandA + j);
+            rows_of(G + (size_t)tri(j, j - 1) * kTileFloats, a);
+            store_tile(T, G + (size_t)tri(j, j) * kTileFloats);
+            panel(a, reinterpret_cast<const float4_t *>(X), XT);
+            __syncthreads();
+            rows_of(XT, a);
+            subtract(a, reinterpret_cast<const float4_t *>(XT));
+            __syncthreads();
+        }
+        if (h != 0)                                  // (a thread's own pieces)
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const float4_t v = reinterpret_cast<const float4_t *>(block(T, b, b))[q * 16 + ln];
+            for (int q = 0; q < 4; ++q)
 #pragma unroll
-                for (int e = 0; e < 4; ++e) a[4 * q + e] = v[e];
+                for (int e = 0; e < 4; ++e) T[4 * (tid + 256 * q) + e] = ldexpf(T[4 * (tid + 256 * q) + e], 2 * h);
+        for (int idx = tid; idx < kTileFloats; idx += 256) X[idx] = 0.f;
+        __syncthreads();
+        for (int b = 0; b < 4; ++b) {
+            if (wave == 0) {
+                float4_t w = operand(block(T, b, b));
+                const bool ok = factor16(w, ln, mq, floor_, dead, pmax, pmin);
+                if (lane < 16) alive[16 * b + ln] = ok;
+                reinterpret_cast<float4_t *>(block(X, b, b))[lane] = w;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) block(XT, b, b)[(ln >> 2) * 64 + (4 * mq + e) * 4 + (ln & 3)] = w[e];
             }
-            const bool ok = factor16(a, x, ln, floor_, dead, pmax, pmin);
-            if (lane < 16) {
-                alive[16 * b + ln] = ok;
+            __syncthreads();
+            // panel: block rows b + 1 .. 3, one per wavefront
+            if (wave > b) {
+                float4_t c = {0.f, 0.f, 0.f, 0.f};
+                mma16(operand(block(T, wave, b)), operand(block(X, b, b)), c);
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    reinterpret_cast<float4_t *>(block(X, b, b))[q * 16 + ln] = float4_t{x[4 * q], x[4 * q + 1], x[4 * q + 2], x[4 * q + 3]};
+                for (int e = 0; e < 4; ++e) block(T, wave, b)[(ln >> 2) * 64 + (4 * mq + e) * 4 + (ln & 3)] = alive[16 * b + ln] ? c[e] : 0.f;
+            }
+            __syncthreads();
+            if (wave > b) {
+                const float4_t a = operand(block(T, wave, b));
+                for (int k = b + 1; k <= wave; ++k) {
+                    float4_t c = {0.f, 0.f, 0.f, 0.f};
+                    mma16(a, operand(block(T, k, b)), c);
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) block(XT, b, b)[(ln >> 2) * 64 + (4 * q + e) * 4 + (ln & 3)] = x[4 * q + e];
+                    for (int e = 0; e < 4; ++e) block(T, wave, k)[(ln >> 2) * 64 + (4 * mq + e) * 4 + (ln & 3)] -= c[e];
                 }
             }
+            __syncthreads();
         }
-        __syncthreads();
-        // panel: block rows b + 1 .. 3, one per wavefront
-        if (wave > b) {
-            float4_t c = {0.f, 0.f, 0.f, 0.f};
-            mma16(operand(block(T, wave, b)), operand(block(X, b, b)), c);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) block(T, wave, b)[(ln >> 2) * 64 + (4 * mq + e) * 4 + (ln & 3)] = alive[16 * b + ln] ? c[e] : 0.f;
-        }
-        __syncthreads();
-        if (wave > b) {
-            const float4_t a = operand(block(T, wave, b));
-            for (int k = b + 1; k <= wave; ++k) {
+        // the inverse below its diagonal blocks: X_ij = -X_ii sum_{j <= k < i} L_ik X_kj, block row after block row
+        for (int i = 1; i < 4; ++i) {
+            if (wave < i) {
                 float4_t c = {0.f, 0.f, 0.f, 0.f};
-                mma16(a, operand(block(T, k, b)), c);
+                for (int k = wave; k < i; ++k) mma16(operand(block(T, i, k)), operand(block(XT, wave, k)), c);
+                reinterpret_cast<float4_t *>(M[wave])[mq * 16 + ln] = c;          // transposed: operand order of its columns
+                asm volatile("s_waitcnt lgkmcnt(0)" : : : "memory");
+                float4_t y = {0.f, 0.f, 0.f, 0.f};
+                mma16(operand(block(X, i, i)), operand(M[wave]), y);
+                reinterpret_cast<float4_t *>(block(XT, wave, i))[mq * 16 + ln] = -y;
 #pragma unroll
-                for (int e = 0; e < 4; ++e) block(T, wave, k)[(ln >> 2) * 64 + (4 * mq + e) * 4 + (ln & 3)] -= c[e];
+                for (int e = 0; e < 4; ++e) block(X, i, wave)[(ln >> 2) * 64 + (4 * mq + e) * 4 + (ln & 3)] = -y[e];
             }
+            __syncthreads();
         }
-        __syncthreads();
-    }
-    // the inverse below its diagonal blocks: X_ij = -X_ii sum_{j <= k < i} L_ik X_kj, block row after block row
-    for (int i = 1; i < 4; ++i) {
-        if (wave < i) {
-            float4_t c = {0.f, 0.f, 0.f, 0.f};
-            for (int k = wave; k < i; ++k) mma16(operand(block(T, i, k)), operand(block(XT, wave, k)), c);
-            reinterpret_cast<float4_t *>(M[wave])[mq * 16 + ln] = c;          // transposed: operand order of its columns
-            asm volatile("s_waitcnt lgkmcnt(0)" : : : "memory");
-            float4_t y = {0.f, 0.f, 0.f, 0.f};
-            mma16(operand(block(X, i, i)), operand(M[wave]), y);
-            reinterpret_cast<float4_t *>(block(XT, wave, i))[mq * 16 + ln] = -y;
+        // both forms to memory; the second stays in X
+        float4_t *const out = reinterpret_cast<float4_t *>(D + (size_t)j * kTileFloats);
+        float4_t *const outp = reinterpret_cast<float4_t *>(Dp + (size_t)j * kTileFloats);
 #pragma unroll
-            for (int e = 0; e < 4; ++e) block(X, i, wave)[(ln >> 2) * 64 + (4 * mq + e) * 4 + (ln & 3)] = -y[e];
+        for (int q = 0; q < 4; ++q) {            // (piece tid + 256 q is of row 16 q + tid % 16)
+            float4_t v = reinterpret_cast<const float4_t *>(X)[tid + 256 * q];
+            if (h != 0)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[e] = ldexpf(v[e], h);
+            out[tid + 256 * q] = v;
+            if (!alive[16 * q + (tid & 15)]) v = float4_t{0.f, 0.f, 0.f, 0.f};
+            outp[tid + 256 * q] = v;
+            reinterpret_cast<float4_t *>(X)[tid + 256 * q] = v;
         }
-        __syncthreads();
+        if (j + 1 < nb) hand_over(hand, kHandD + j, seq);
     }
-    if (tid == 0) {                              // (every lane has seen every pivot)
-        words->pmax = pmax;
-        words->pmin = pmin;
-        if (j == nb - 1) {
-            const int done = step.in ? step.in->run : 0, run = next_run(done, pmax, pmin), end = step.h + run;
-            words->run = run;
-            // (a block that is due just before the last one is left to that)
-            words->due = step.last - end <= run / 4 ? step.last : end;
-        }
+    if (wave != 0) return;
+    pmax = wave_max(pmax);
+    pmin = -wave_max(-pmin);
+    if (tid == 0) {
+        const int done = step.in ? step.in->run : 0, run = next_run(done, pmax, pmin), end = step.h + run;
+        step.out->run = run;
+        // (a block that is due just before the last one is left to that)
+        step.out->due = step.last - end <= run / 4 ? step.last : end;
     }
-    float4_t *const out = reinterpret_cast<float4_t *>(D + (size_t)j * kTileFloats);
-    float4_t *const outp = reinterpret_cast<float4_t *>(Dp + (size_t)j * kTileFloats);
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {                // (piece tid + 256 q is of row 16 q + tid % 16)
-        float4_t v = reinterpret_cast<const float4_t *>(X)[tid + 256 * q];
-        if (h != 0)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) v[e] = ldexpf(v[e], h);
-        out[tid + 256 * q] = v;
-        outp[tid + 256 * q] = alive[16 * q + (tid & 15)] ? v : float4_t{0.f, 0.f, 0.f, 0.f};
-    }
-    if (nb > 1) hand_over(hand, kHandD + j, seq);
 }
 
 // The power of two that brings a column whose largest magnitude has the bits `max_bits` below 1.
