@@ -55,3 +55,23 @@ def test_calls_in_turn_on_one_workspace():
         a = np.float32(alpha.cpu().numpy()[0])
         assert O.quant_search_accepts(W, a)
         assert np.all(scale.cpu().numpy() == np.float32(a / np.float32(7.0)))
+
+
+@pytest.mark.parametrize("n,k", [(3, 8), (5, 520), (2, 512992), (2, 513000), (2, 520000)])
+@pytest.mark.parametrize("dist", ["normal", "student_t", "one_value"])
+def test_rows_with_and_without_a_table_of_bins(n, k, dist):
+    """Rows of 512 bins, whose centres and counts are tabulated, and of more (from 513000 inputs on); most bins empty, all but one."""
+    rng = np.random.default_rng(k)
+    if dist == "normal":
+        W = rng.standard_normal((n, k)).astype(np.float32) * 0.02
+    elif dist == "student_t":
+        W = rng.standard_t(2, (n, k)).astype(np.float32)
+    else:
+        W = np.full((n, k), 0.5, np.float32)
+    W[n - 1] *= np.float32(1e-3)
+    scale, alpha = B.slim_quant_search_rows(torch.from_numpy(W).to(DEV))
+    torch.cuda.synchronize()
+    a = alpha.cpu().numpy().reshape(-1)
+    for i in range(n):
+        assert O.quant_search_accepts(W[i:i + 1], a[i])
+    assert np.array_equal(scale.cpu().numpy(), (a / np.float32(7.0)).astype(np.float32))
