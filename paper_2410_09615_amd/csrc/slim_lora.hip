@@ -30,18 +30,21 @@ struct SgemmArgs {
     int kchunk;           // K values per grid.z slice (a multiple of 16); C (zeroed before) is added to atomically when there are several
 };
 
-constexpr int kGM = 128, kGN = 128, kGK = 16, kGLd = kGK + 4;      // LDS rows of 16 k-values, padded to 20 floats
+constexpr int kGM = 128, kGN = 128, kGK = 16, kGLd = kGM + 8;      // LDS: a k-value is one row of 128 values, padded to 136 floats
 
 // Workgroup of 4 wavefronts, tile 128 x 128, each wavefront 64 x 64 = 2 x 2 matrix
-// instruction blocks.  Both operand tiles sit in LDS as [row or column][k]: lane
-// (r = lane % 32, h = lane / 32) of a block reads the four k-values 8 s + 4 h .. + 3 of
-// its row with one 128-bit read and feeds them to four instructions; A and B use the
-// same assignment of k-values to (lane half, instruction), so the sum is complete.
+// instruction blocks.  Both operand tiles sit in LDS as [k][row or column], as B and a transposed A come from memory, so that
+// they are stored by 128 bits; lane (r = lane % 32, h = lane / 32) of a block reads the k-values 8 s + 4 h .. + 3 of
+// its row, 32 neighbouring words per half of the lanes, four rows apart in different banks (hence the padding), and feeds
+// them to four instructions; A and B use the same assignment of k-values to (lane half, instruction), so the sum is complete.
+// (As [row][k] with one 128-bit read for the four they were stored word by word, eight lanes to a bank: 416 x 4096 over
+// 4096 218 us, now 156; its adds are no part of that: shares side by side instead of one sum took as long.)
 template <bool TA>
 __global__ __launch_bounds__(256) void sgemm_kernel(SgemmArgs a)
 {
-    __shared__ __attribute__((aligned(16))) float As[kGM * kGLd];
-    __shared__ __attribute__((aligned(16))) float Bs[kGN * kGLd];
+    static_assert(kGM == kGN, "one row length");
+    __shared__ __attribute__((aligned(16))) float As[kGK * kGLd];
+    __shared__ __attribute__((aligned(16))) float Bs[kGK * kGLd];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int m0 = blockIdx.y * kGM, n0 = blockIdx.x * kGN;
     const int kb = blockIdx.z * a.kchunk, ke = min(a.K, kb + a.kchunk);
@@ -84,20 +87,16 @@ __global__ __launch_bounds__(256) void sgemm_kernel(SgemmArgs a)
         }
     };
     auto store_slab = [&]() {
-        if constexpr (!TA) {
 #pragma unroll
-            for (int i = 0; i < 2; ++i)
-                *reinterpret_cast<float4_t *>(As + ((tid >> 2) + 64 * i) * kGLd + (tid & 3) * 4) = ra[i];
-        } else {
+        for (int i = 0; i < 2; ++i) {
+            if constexpr (!TA) {
 #pragma unroll
-            for (int i = 0; i < 2; ++i)
-#pragma unroll
-                for (int e = 0; e < 4; ++e) As[((tid & 31) * 4 + e) * kGLd + (tid >> 5) + 8 * i] = ra[i][e];
+                for (int e = 0; e < 4; ++e) As[((tid & 3) * 4 + e) * kGLd + (tid >> 2) + 64 * i] = ra[i][e];
+            } else {
+                *reinterpret_cast<float4_t *>(As + ((tid >> 5) + 8 * i) * kGLd + (tid & 31) * 4) = ra[i];
+            }
+            *reinterpret_cast<float4_t *>(Bs + ((tid >> 5) + 8 * i) * kGLd + (tid & 31) * 4) = rb[i];
         }
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) Bs[((tid & 31) * 4 + e) * kGLd + (tid >> 5) + 8 * i] = rb[i][e];
     };
 
     // M and N are multiples of 4 wherever a 128-bit load straddles the edge (row counts
@@ -112,9 +111,12 @@ __global__ __launch_bounds__(256) void sgemm_kernel(SgemmArgs a)
         for (int s = 0; s < 2; ++s) {
             float4_t av[2], bv[2];
 #pragma unroll
-            for (int i = 0; i < 2; ++i) av[i] = *reinterpret_cast<const float4_t *>(As + (wm + 32 * i + r) * kGLd + 8 * s + 4 * h);
+            for (int i = 0; i < 2; ++i)
 #pragma unroll
-            for (int j = 0; j < 2; ++j) bv[j] = *reinterpret_cast<const float4_t *>(Bs + (wn + 32 * j + r) * kGLd + 8 * s + 4 * h);
+                for (int e = 0; e < 4; ++e) {
+                    av[i][e] = As[(8 * s + 4 * h + e) * kGLd + wm + 32 * i + r];
+                    bv[i][e] = Bs[(8 * s + 4 * h + e) * kGLd + wn + 32 * i + r];
+                }
 #pragma unroll
             for (int e = 0; e < 4; ++e)
 #pragma unroll
