@@ -217,6 +217,7 @@ int slim_quant_search_rows(const float *W, slim_shape shape, float *scale_out, f
  * the last block always is.
  * workspace: slim_adapters_workspace_bytes (HOST out-pointer; about 12 n k bytes -- S in fp32, S and its transpose as
  * two fp16 matrices -- plus 20 to 45 bytes per element of a block of max(n, k) x rank_pad), need not be zeroed.  Errors: NULL, SHAPE, ALIGN, WORKSPACE, HIP.
+ * The workgroups of a factorisation hand tiles to one another; those waits are bounded, and should one run out, L and R are NaN.
  */
 int slim_adapters_workspace_bytes(slim_shape shape, size_t *bytes);
 int slim_compute_adapters(const float *W, const uint8_t *qvals, const uint8_t *meta, const float *scale,
@@ -358,7 +359,8 @@ int slim_linear_gemv_static(const slim_layer *layer, const slim_half *X, int32_t
  *           batch likewise): every wavefront still ends normally, Y is NaN and the workspace's error word is set
  *           (slim_workspace_check then reports SLIM_ERR_WAIT).  With lds_kb != 0 slim_linear_gemm and
  *           slim_lowrank on a small batch launch everything, but the workgroups meant to make T make nothing:
- *           those that wait make it themselves, and Y is what it always is;
+ *           those that wait make it themselves, and Y is what it always is.  slim_compute_adapters on more than 64
+ *           columns (rank_pad) launches only the workgroup of each factorisation that waits for the others: L and R are NaN;
  *   lds_kb  0: plan with the device's LDS; 16..160: with at most this many KiB
  *           (X then streams through the LDS in chunks on small layers too).
  * Errors: SHAPE (a value outside these ranges).

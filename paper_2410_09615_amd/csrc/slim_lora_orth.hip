@@ -243,7 +243,8 @@ __device__ __forceinline__ int next_run(int done, float pmax, float pmin)
 // holds the number of the orth() whose tile it is (kHandFailed: that of one whose wait ran out).
 enum { kHandL = 0, kHandT = kMaxTri, kHandA = kHandT + kMaxBlocks, kHandD = kHandA + kMaxBlocks, kHandFailed = kHandD + kMaxBlocks, kHandWords };
 constexpr int kHandStride = 16;
-constexpr int kHandPolls = 1 << 20;            // half a microsecond or more each; a wait is over after some tens of them
+constexpr int kHandPolls = 1 << 24;            // half a microsecond or more each; a wait is over after some tens of them, or when other
+                                               // work on the chip has let the rest of the launch start
 
 // Everything the workgroup has stored -> visible to who sees the word.
 __device__ __forceinline__ void hand_over(unsigned *hand, int what, unsigned seq)
@@ -256,10 +257,10 @@ __device__ __forceinline__ void hand_over(unsigned *hand, int what, unsigned seq
     }
 }
 // One lane waits; false: the word has not come.
-__device__ __forceinline__ bool hand_taken(unsigned *hand, int what, unsigned seq)
+__device__ __forceinline__ bool hand_taken(unsigned *hand, int what, unsigned seq, int limit)
 {
     for (int polls = 0; __hip_atomic_load(hand + what * kHandStride, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != seq; ++polls) {
-        if (polls >= kHandPolls) return false;
+        if (polls >= limit) return false;
         __builtin_amdgcn_s_sleep(1);
     }
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
@@ -278,7 +279,7 @@ __device__ __forceinline__ bool hand_taken(unsigned *hand, int what, unsigned se
 // 4096 x 416: 94 us, 4.5 where the block is only scaled; one launch per 64 columns took 148 and 30.  (With a diagonal tile's
 // inverse handed through memory to the workgroup of the next one: 4 us more.)
 __global__ __launch_bounds__(256) void lora_chol_kernel(int nb, int l, const float *__restrict__ P, int splits, int tiles, float *G,
-                                                        float *Lf, float *D, float *Dp, unsigned *hand, unsigned seq, OrthStep step)
+                                                        float *Lf, float *D, float *Dp, unsigned *hand, unsigned seq, int polls, OrthStep step)
 {
     if (step.skip()) return;
     __shared__ __attribute__((aligned(16))) float T[kTileFloats], LI[kTileFloats], LJ[kTileFloats];
@@ -292,7 +293,7 @@ __global__ __launch_bounds__(256) void lora_chol_kernel(int nb, int l, const flo
     if (tid == 0) missing = 0;
     // (words in turn: wavefront w waits for the w-th; the barrier makes it the workgroup's)
     auto wait_for = [&](int first, int second) {
-        if (lane == 0 && wave < 2 && !missing && !hand_taken(hand, wave == 0 ? first : second, seq)) {
+        if (lane == 0 && wave < 2 && !missing && !hand_taken(hand, wave == 0 ? first : second, seq, polls)) {
             missing = 1;                         // (and the waits after this one are none)
             __hip_atomic_store(hand + kHandFailed * kHandStride, seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
@@ -639,7 +640,9 @@ int launch_orth(const float *in, float *out, half_t *hi, half_t *lo, int rows, i
     const int zrows = ((rows + splits - 1) / splits + 31) / 32 * 32;
     splits = (rows + zrows - 1) / zrows;
     hipLaunchKernelGGL(lora_gram_kernel, dim3((unsigned)tiles, (unsigned)splits), dim3(256), 0, st, in, rows, l, zrows, tiles, P, step);
-    hipLaunchKernelGGL(lora_chol_kernel, dim3((unsigned)tiles), dim3(256), 0, st, nb, l, (const float *)P, splits, tiles, G, Lf, D, Dp, hand, seq, step);
+    const bool wait_test = decode_path_override() == 3;      // (slim_decode_override: only the workgroup that waits for the others)
+    hipLaunchKernelGGL(lora_chol_kernel, dim3((unsigned)(wait_test ? 1 : tiles)), dim3(256), 0, st, nb, l, (const float *)P, splits, tiles, G, Lf, D, Dp,
+                       hand, seq, wait_test ? 256 : kHandPolls, step);
     const size_t lds = (size_t)(16 * (nb * kOb + 4) + 16 * 68) * sizeof(float);
     hipLaunchKernelGGL(lora_apply_kernel, dim3((unsigned)((rows + 31) / 32 * 2)), dim3(256), lds, st, in, out, rows, l, nb, (const float *)Lf,
                        (const float *)D, hi, lo, (rows + 31) / 32 * 32, step, colmax, clear, (const unsigned *)hand, seq);
