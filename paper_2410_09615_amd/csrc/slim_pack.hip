@@ -26,7 +26,7 @@ __device__ __forceinline__ RowScale row_scale(float s)
 // products are single binary32 multiplications.  Six comparisons, whose combinations are scalar operations on the masks of a
 // wavefront, and selects.  The kernels here are as much bound by vector instructions as by memory: a chain of selections
 // with branches and two IEEE divisions were 150 per group, these are about 60 (11008 x 4096 with scales and saliency given
-// 39.5 -> 32.4 us, and that only with both of it: the tiles of pack_scaled_kernel alone 40.7).
+// 38 -> 30 us, and that only with both of it: pack_scaled_kernel with the chain took as long as the rows did).
 __device__ __forceinline__ uint32_t encode_group(float4 v, const RowScale &rs, uint32_t *m4, float4 sal = make_float4(1.f, 1.f, 1.f, 1.f))
 {
     // (a NaN loses against everything, but for one in position 0, which nothing beats)
@@ -41,7 +41,7 @@ __device__ __forceinline__ uint32_t encode_group(float4 v, const RowScale &rs, u
                k3 = one_at_most(~b03, ~b13, ~b23);
     const float w0 = k0 ? v.x : (k1 ? v.y : v.z), w1 = k3 ? v.w : (k2 ? v.z : v.y);
     *m4 = (k0 ? 0u : (k1 ? 1u : 2u)) | (k3 ? 12u : (k2 ? 8u : 4u));
-    float q0 = w0 * rs.inv, q1 = w1 * rs.inv;
+    const float q0 = w0 * rs.inv, q1 = w1 * rs.inv;
     float r0 = rintf(q0), r1 = rintf(q1);
     if (!(fmaxf(fabsf(q0 - r0), fabsf(q1 - r1)) <= 0.499996f)) {
         r0 = rintf(w0 / rs.s);                // IEEE division, round half to even
@@ -56,8 +56,7 @@ __device__ __forceinline__ uint32_t encode_group(float4 v, const RowScale &rs, u
 // registers (the row has at most 4 THREADS SLOTS inputs); 0 = rows of any
 // length, read twice.  Few slots per lane keep the register count low enough
 // for eight wavefronts per SIMD, which is what hides the load latency here.
-// The kernel is as much bound by its vector ALU work (top-2 selection, two IEEE
-// divisions per group) as by memory, so the stores stay plain byte stores: lane
+// The kernel is as much bound by its vector ALU work as by memory, so the stores stay plain byte stores: lane
 // t writes group t + i THREADS of slot i, whose place in the packed layout is a
 // per-lane base plus a constant per slot.
 // EX: the variant behind slim_pack_ex: saliency [k] (or null) weighs the
@@ -83,15 +82,16 @@ __global__ __launch_bounds__(THREADS) void pack_kernel(const float *__restrict__
     const int rows_per_die = ((npad / 32 + 7) / 8) * 32;
     const int o_end = min(npad, (die + 1) * rows_per_die);
     for (int o = die * rows_per_die + local; o < o_end; o += per_die) {
-        // this lane's byte of slot 0 in the packed layout (group tid, position byte tid / 2)
-        uint8_t *const ql = qvals + pk_qoff(o, tid, kt);
-        uint8_t *const ml = meta + pk_moff(o, tid >> 1, kt);
+        // the row in the packed layout, and this lane's byte of a slot in it (group tid, position byte tid / 2): one address
+        // in scalar registers and one offset, where an address per slot took the registers of the second workgroup of a unit
+        uint8_t *const qrow = qvals + pk_qoff(o, 0, kt), *const mrow = meta + pk_moff(o, 0, kt);
+        const uint32_t ql = (uint32_t)pk_qoff(0, tid, kt), ml = (uint32_t)pk_moff(0, tid >> 1, kt);
         constexpr size_t q_slot = (size_t)(THREADS / 32) * 1024, m_slot = (size_t)(THREADS / 32) * 512;
         if (o >= n) {
             // padding row of the last row tile: zero bytes
             for (int g = tid, i = 0; g < gpad; g += THREADS, ++i) {
-                ql[i * q_slot] = 0;
-                if ((g & 1) == 0) ml[i * m_slot] = 0;
+                (qrow + i * q_slot)[ql] = 0;
+                if ((g & 1) == 0) (mrow + i * m_slot)[ml] = 0;
             }
             continue;
         }
@@ -138,8 +138,8 @@ __global__ __launch_bounds__(THREADS) void pack_kernel(const float *__restrict__
             }
             const uint32_t other = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)m4, 0xB1, 0xF, 0xF, true);     // of lane ^ 1
             if (g < gpad) {
-                ql[i * q_slot] = (uint8_t)q;
-                if ((g & 1) == 0) ml[i * m_slot] = (uint8_t)(m4 | (other << 4));
+                (qrow + i * q_slot)[ql] = (uint8_t)q;
+                if ((g & 1) == 0) (mrow + i * m_slot)[ml] = (uint8_t)(m4 | (other << 4));
             }
         };
         if (CACHED) {
@@ -154,62 +154,55 @@ __global__ __launch_bounds__(THREADS) void pack_kernel(const float *__restrict__
     }
 }
 
-// The same with the scales given (slim_pack_ex): nothing is to be known of a row, so a workgroup takes a tile of the packed layout
-// at a time, 32 rows x 128 inputs, four groups per lane, with the loads of its next tile under way.  Sixteen lanes read 256
-// contiguous bytes of a row, and a wavefront's codes of 4 rows are 64 contiguous bytes, a workgroup's whole lines: by rows
-// they were 16 bytes of a line that the workgroups of other rows filled up.  saliency: [k], or null.
+// The same with the scales given (slim_pack_ex): nothing is to be known of a row, so a workgroup takes half a tile of the packed
+// layout, 16 rows x 128 inputs, two groups per lane, at a time, with the loads of its next one under way.  Sixteen lanes read
+// 256 contiguous bytes of a row, and a workgroup's codes are two runs of 256 bytes: by rows they were 16 bytes of a line that
+// the workgroups of other rows filled up.  16384 workgroups: 11008 x 4096 29.9 us, 16115 x 7296 94.7 (2048: 31.2 and 103.7; whole
+// tiles 29.2 and 95.1, on 4096 x 4096 13.5 instead of 12.9; quarters 33 and 107).  saliency: [k], or null.
+constexpr int kPackScaledGrid = 16384;
 __global__ __launch_bounds__(256) void pack_scaled_kernel(const float *__restrict__ W, int n, int k, const float *__restrict__ saliency,
                                                           const float *scale_in, uint8_t *__restrict__ qvals, uint8_t *__restrict__ meta,
                                                           float *scale)
 {
-    const uint32_t kt = pk_ktiles(k), ngroups = (uint32_t)k / 4, tiles = (uint32_t)((n + 31) / 32) * kt;
+    const uint32_t kt = pk_ktiles(k), ngroups = (uint32_t)k / 4, parts = (uint32_t)((n + 31) / 32) * kt * 2;
     const uint32_t r = threadIdx.x >> 4, c = threadIdx.x & 15;
-    struct Tile {
-        float4 w[2][2], sal[2];              // rows r and 16 + r, groups c and 16 + c
-        float s[2];
-        uint32_t rt, ct;
+    struct Part {
+        float4 w[2], sal[2];
+        float s;
+        uint32_t row, col;                   // of the lane's first group
     };
     // (lanes of the padding load the last row and group)
     auto load = [&](uint32_t u) {
-        Tile t;
-        t.rt = u / kt;
-        t.ct = u - t.rt * kt;
-        const uint32_t g0 = min(t.ct * 32 + c, ngroups - 1), g1 = min(t.ct * 32 + c + 16, ngroups - 1);
-        if (saliency) {
-            t.sal[0] = reinterpret_cast<const float4 *>(saliency)[g0];
-            t.sal[1] = reinterpret_cast<const float4 *>(saliency)[g1];
-        }
+        Part t;
+        const uint32_t tile = u / 2, rt = tile / kt;
+        t.row = rt * 32 + (u & 1) * 16 + r;
+        t.col = (tile - rt * kt) * 32 + c;
+        if (saliency)
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            const uint32_t o = min(t.rt * 32 + r + 16 * i, (uint32_t)n - 1);
-            const float4 *const row = reinterpret_cast<const float4 *>(W) + (size_t)o * ngroups;
-            t.s[i] = scale_in[o];
-            t.w[i][0] = row[g0];
-            t.w[i][1] = row[g1];
-        }
+            for (int h = 0; h < 2; ++h) t.sal[h] = reinterpret_cast<const float4 *>(saliency)[min(t.col + 16 * h, ngroups - 1)];
+        const uint32_t o = min(t.row, (uint32_t)n - 1);
+        const float4 *const row = reinterpret_cast<const float4 *>(W) + (size_t)o * ngroups;
+        t.s = scale_in[o];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) t.w[h] = row[min(t.col + 16 * h, ngroups - 1)];
         return t;
     };
     uint32_t u = blockIdx.x;
-    Tile next = load(u);
-    for (; u < tiles; u += gridDim.x) {
-        const Tile t = next;
-        next = load(min(u + gridDim.x, tiles - 1));
-        uint8_t *const qt = qvals + (size_t)u * 1024, *const mt = meta + (size_t)u * 512;
-        const uint32_t rows = (uint32_t)n - t.rt * 32;
+    Part next = load(u);
+    for (; u < parts; u += gridDim.x) {
+        const Part t = next;
+        next = load(min(u + gridDim.x, parts - 1));
+        uint8_t *const qt = qvals + (size_t)(u / 2) * 1024 + (u & 1) * 256, *const mt = meta + (size_t)(u / 2) * 512 + (u & 1) * 128;
+        const RowScale rs = row_scale(t.s);
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            const uint32_t o = r + 16 * i;
-            const RowScale rs = row_scale(t.s[i]);
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                uint32_t m4 = 0, q = encode_group(t.w[i][h], rs, &m4, saliency ? t.sal[h] : make_float4(1.f, 1.f, 1.f, 1.f));
-                if (o >= rows || t.ct * 32 + c + 16 * h >= ngroups) q = m4 = 0;       // padding is zero bytes
-                const uint32_t other = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)m4, 0xB1, 0xF, 0xF, true);     // of lane ^ 1
-                qt[threadIdx.x + (h * 512 + i * 256)] = (uint8_t)q;
-                if ((c & 1) == 0) mt[threadIdx.x / 2 + (h * 256 + i * 128)] = (uint8_t)(m4 | (other << 4));
-            }
-            if (t.ct == 0 && c == 0 && o < rows) scale[t.rt * 32 + o] = t.s[i];
+        for (int h = 0; h < 2; ++h) {
+            uint32_t m4 = 0, q = encode_group(t.w[h], rs, &m4, saliency ? t.sal[h] : make_float4(1.f, 1.f, 1.f, 1.f));
+            if (t.row >= (uint32_t)n || t.col + 16 * h >= ngroups) q = m4 = 0;           // padding is zero bytes
+            const uint32_t other = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)m4, 0xB1, 0xF, 0xF, true);     // of lane ^ 1
+            qt[threadIdx.x + h * 512] = (uint8_t)q;
+            if ((c & 1) == 0) mt[threadIdx.x / 2 + h * 256] = (uint8_t)(m4 | (other << 4));
         }
+        if (t.col == 0 && t.row < (uint32_t)n) scale[t.row] = t.s;
     }
 }
 
@@ -286,7 +279,7 @@ static int launch_pack(const float *W, slim_shape shape, uint8_t *qvals, uint8_t
                        const float *saliency, hipStream_t st)
 {
     const int npad = (shape.n + 31) / 32 * 32;      // the padding rows of the last tile get a workgroup too
-    // lanes per row: enough that a lane keeps at most 4 groups, up to 1024
+    // lanes per row: enough that a lane keeps at most 4 groups, 8 from 512 lanes on
     const int groups = shape.k / 4;
     // (two rounds of resident workgroups at most; a workgroup walks the rows it owns)
 #define SLIM_PACK_LAUNCH(T, S)                                                                                    \
@@ -298,13 +291,13 @@ static int launch_pack(const float *W, slim_shape shape, uint8_t *qvals, uint8_t
         SLIM_PACK_LAUNCH(256, 4);
     else if (groups <= 512 * 4)
         SLIM_PACK_LAUNCH(512, 4);
-    else if (groups <= 1024 * 4)
-        SLIM_PACK_LAUNCH(1024, 4);
+    else if (groups <= 512 * 8)              // (1024 lanes with four groups each: 4096 x 11008 48 and 45 us, with and without saliency, these 42 and 34)
+        SLIM_PACK_LAUNCH(512, 8);
     else if (groups <= 1024 * 8)
         SLIM_PACK_LAUNCH(1024, 8);
-    else if (groups <= 1024 * kPackSlotsMax)
+    else if (groups <= 1024 * kPackSlotsMax && !EX)
         SLIM_PACK_LAUNCH(1024, kPackSlotsMax);
-    else
+    else                                     // (with saliency, twelve slots do not fit the registers: 1024 x 40960 63 us, read twice 53)
         SLIM_PACK_LAUNCH(1024, 0);
 #undef SLIM_PACK_LAUNCH
     return hip_status(hipGetLastError());
@@ -330,8 +323,7 @@ extern "C" int slim_pack_ex(const float *W, slim_shape shape, const float *salie
     hipStream_t st = static_cast<hipStream_t>(stream);
     if (!scale_in) return launch_pack<true>(W, shape, qvals, meta, scale, saliency, st);
     const size_t tiles = (size_t)((shape.n + 31) / 32) * pk_ktiles(shape.k);
-    hipLaunchKernelGGL(pack_scaled_kernel, dim3((unsigned)(tiles < 2048 ? tiles : 2048)), dim3(256), 0, st, W, shape.n, shape.k, saliency, scale_in,
-                       qvals, meta, scale);
+    hipLaunchKernelGGL(pack_scaled_kernel, dim3((unsigned)(2 * tiles < kPackScaledGrid ? 2 * tiles : kPackScaledGrid)), dim3(256), 0, st, W, shape.n, shape.k, saliency, scale_in, qvals, meta, scale);
     return hip_status(hipGetLastError());
 }
 
