@@ -7,8 +7,8 @@
 // number of launches (4 us each) and the latency of the 64 x 64 diagonal blocks, not arithmetic:
 //   lora_gram_kernel    lower tiles of G, the rows divided among the workgroups, partial tiles to memory;
 //   lora_chol_kernel    the factorisation, a workgroup per tile, which hand finished tiles to one another through
-//                       memory; the workgroup of a diagonal tile factors and inverts it, in blocks of 16 that live in the
-//                       registers of one wavefront;
+//                       memory; one of them factors and inverts the diagonal tiles, in blocks of 16 that live in the
+//                       registers of a wavefront;
 //   lora_apply_kernel   a workgroup carries 16 rows of `in` through all block columns, which stay in LDS:
 //                       out_J = (in_J - sum_{K<J} out_K L_JK^T) X_JJ^T, one launch for the whole block.
 // 4096 x 416: 3 launches (gram 22 us, factorisation 94, apply 25) where a factorisation with one launch per 64 columns took
@@ -30,7 +30,7 @@
 // columns have separated by then, the pivots are squares of singular values whatever the number of products, and
 // rounding in the direction of the largest grows by their ratio with each product, 2e-7 * 5.5^8 = 0.2 of a column
 // at that limit.  A block whose pivots span more is followed by a quarter as many.
-// 16 rounds of a layer of 4096 x 4096 with 409 columns (singular values over a factor of 3): 12 blocks of 35 are orthonormalised,
+// 16 rounds of a layer of 4096 x 4096 with 409 columns (singular values over a factor of 3): 9 blocks of 34 are orthonormalised,
 // where every other one was 19: 6.36 -> 4.69 ms for the call.  Residual, directions lost and orthonormality are those of every
 // other block on 150 spectra (saliencies that span 1 to 1e6 in several ways, 2 and 16 rounds).
 #include <utility>
