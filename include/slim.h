@@ -205,7 +205,7 @@ int slim_quant_search_rows(const float *W, slim_shape shape, float *scale_out, f
  *                sums use atomic adds, so results differ in the last bits from call to call;
  *   diag         (may be NULL) four floats out: ||S||_F^2, the captured part
  *                ||L^T S||_F^2 (the exact truncation captures the sum of the rank
- *                largest squared singular values), max |L^T L - I|, 0.
+ *                largest squared singular values), max |L^T L - I| (infinite if L is not finite), 0.
  * Arithmetic: S, the Gram matrices, the orthonormalisations, L, R and what diag reports are fp32.  The products
  * with S in the rounds run on the fp16 matrix cores, both operands as two fp16 numbers each and the sums in fp32: S up to
  * 2^-23 of an element or 2^-39 of the largest one, whichever is more, so elements 2^17 below the largest and smaller
@@ -218,6 +218,7 @@ int slim_quant_search_rows(const float *W, slim_shape shape, float *scale_out, f
  * workspace: slim_adapters_workspace_bytes (HOST out-pointer; about 12 n k bytes -- S in fp32, S and its transpose as
  * two fp16 matrices -- plus 20 to 45 bytes per element of a block of max(n, k) x rank_pad), need not be zeroed.  Errors: NULL, SHAPE, ALIGN, WORKSPACE, HIP.
  * The workgroups of a factorisation hand tiles to one another; those waits are bounded, and should one run out, L and R are NaN.
+ * The call has returned SLIM_OK by then and there is no error word: diag[2] is infinite, which is how a caller detects it.
  */
 int slim_adapters_workspace_bytes(slim_shape shape, size_t *bytes);
 int slim_compute_adapters(const float *W, const uint8_t *qvals, const uint8_t *meta, const float *scale,

@@ -409,6 +409,8 @@ def compress_dense(W: torch.Tensor, rank: int, x_tilde: torch.Tensor | None = No
     scales (AbsMax per row, or slim_quant_search ("tensor") / slim_quant_search_rows ("rows")), 2:4 mask (by magnitude,
     or weighted by `saliency`) and codes (slim_pack / slim_pack_ex), adapters of `rank` (slim_compute_adapters:
     SLiM-LoRA with x_tilde, Naive-LoRA without; rank 0: none), their layout (fp16, or 4-bit groups of 128).
+    Nothing is read back: adapters that are not finite (weights that are not; a factorisation whose wait ran out) show as NaN in L,
+    R and every output of the layer, and as an infinite diag[2] of slim_compute_adapters.
     Returns the SlimLayer, or (SlimLayer, L fp16 [n][rank], R fp16 [rank][k]) with return_adapters."""
     if scale_search == "absmax":
         scale_in = None

@@ -343,13 +343,15 @@ __global__ __launch_bounds__(256) void lora_out_r_kernel(const float *__restrict
     block_add(part, r2);
 }
 
-// sq[2] = max |G - I| over the leading r x r block (orthonormality of the final Q)
+// sq[2] = max |G - I| over the leading r x r block (orthonormality of the final Q), infinite where an entry is a NaN, which the
+// maxima on the way to the report would drop
 __global__ __launch_bounds__(256) void lora_ortho_kernel(const float *G, int l, int r, float *sq)
 {
     float mx = 0.f;
     for (int t = blockIdx.x * blockDim.x + threadIdx.x; t < r * r; t += gridDim.x * blockDim.x) {
         const int i = t / r, c = t % r;
-        mx = fmaxf(mx, fabsf(G[(size_t)i * l + c] - (i == c ? 1.0f : 0.f)));
+        const float d = fabsf(G[(size_t)i * l + c] - (i == c ? 1.0f : 0.f));
+        mx = fmaxf(mx, d == d ? d : __builtin_inff());
     }
     block_max(mx, sq + 2);
 }

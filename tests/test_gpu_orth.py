@@ -215,3 +215,23 @@ def test_a_factorisation_whose_wait_runs_out_is_nan():
     assert bool(torch.isnan(L).all()) and bool(torch.isnan(R).all())
     again = B.slim_compute_adapters(W, q, m, s, r, iters=2)[0]
     assert float((again.float() - want.float()).norm()) <= 2.0 ** -8 * float(want.float().norm())
+
+
+@pytest.mark.parametrize("why", ["wait", "weight"])
+def test_adapters_that_are_not_finite_do_not_report_as_orthonormal(why):
+    """The maximum of |L^T L - I| is over NaNs: reported is an infinity, not the maximum of what is left."""
+    n, k, r = 300, 384, 130
+    W = wl.make_weight(n, k, seed=n).to(DEV)
+    q, m, s = B.slim_pack(W)
+    if why == "weight":
+        W[17, 5] = float("nan")
+        L, _, diag = B.slim_compute_adapters(W, q, m, s, r, iters=2)
+    else:
+        try:
+            assert B.lib().slim_decode_override(3, 0) == 0
+            L, _, diag = B.slim_compute_adapters(W, q, m, s, r, iters=2)
+            torch.cuda.synchronize()
+        finally:
+            assert B.lib().slim_decode_override(-1, 0) == 0
+    assert bool(torch.isnan(L).any())
+    assert float(diag[2]) == float("inf")
