@@ -59,8 +59,8 @@ __device__ __forceinline__ uint32_t encode_group(float4 v, const RowScale &rs, u
 // The kernel is as much bound by its vector ALU work as by memory, so the stores stay plain byte stores: lane
 // t writes group t + i THREADS of slot i, whose place in the packed layout is a
 // per-lane base plus a constant per slot.
-// EX: the variant behind slim_pack_ex: saliency [k] (or null) weighs the
-// magnitudes in the 2:4 choice.
+// EX: the variant behind slim_pack_ex: saliency [k] weighs the magnitudes in the
+// 2:4 choice.
 template <int THREADS, int SLOTS, bool EX = false>
 __global__ __launch_bounds__(THREADS) void pack_kernel(const float *__restrict__ W, int n, int k,
                                                             uint8_t *__restrict__ qvals,
@@ -97,6 +97,11 @@ __global__ __launch_bounds__(THREADS) void pack_kernel(const float *__restrict__
         }
         const float4 *row = reinterpret_cast<const float4 *>(W + (size_t)o * k);
         constexpr bool CACHED = SLOTS > 0;
+        // Not kept: four groups at a time, because a wait for a load is also one for the stores before it, and a group's work is
+        // short (one at a time, 2048 x 60000 177 and 183 us, without and with saliency, this 153 and 161; 33 x 131072 119 and 125,
+        // this 85 and 91; with loads that leave the L2 first 193 and 218, what the second pass reads there)
+        constexpr int AHEAD = 4;
+        auto weights = [&](int g) { return row[min(g, ngroups - 1)]; };
         float4 cache[CACHED ? SLOTS : 1];
         float a = 0.0f;
         if (CACHED) {
@@ -109,9 +114,12 @@ __global__ __launch_bounds__(THREADS) void pack_kernel(const float *__restrict__
                 a = fmaxf(a, fmaxf(fmaxf(fabsf(v.x), fabsf(v.y)), fmaxf(fabsf(v.z), fabsf(v.w))));
             }
         } else {
-            for (int g = tid; g < ngroups; g += THREADS) {
-                float4 v = row[g];
-                a = fmaxf(a, fmaxf(fmaxf(fabsf(v.x), fabsf(v.y)), fmaxf(fabsf(v.z), fabsf(v.w))));
+            for (int g0 = 0; g0 < ngroups; g0 += 4 * THREADS) {
+                float4 v[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) v[u] = weights(g0 + u * THREADS + tid);
+#pragma unroll
+                for (int u = 0; u < 4; ++u) a = fmaxf(a, fmaxf(fmaxf(fabsf(v[u].x), fabsf(v[u].y)), fmaxf(fabsf(v[u].z), fabsf(v[u].w))));
             }
         }
         a = wave_max(a);
@@ -128,11 +136,11 @@ __global__ __launch_bounds__(THREADS) void pack_kernel(const float *__restrict__
         // Lanes g and g^1 hold the two groups of one position byte (the stride is
         // even, so both are active together).  Groups past the end of the row
         // (padding of the last tile) are zero bytes.
-        auto emit = [&](int i, int g, float4 v) {
+        auto emit = [&](int i, int g, float4 v, auto sal_of) {
             uint32_t q = 0, m4 = 0;
             if (g < ngroups) {
-                if (EX && saliency)
-                    q = encode_group(v, rs, &m4, reinterpret_cast<const float4 *>(saliency)[g]);
+                if (EX)
+                    q = encode_group(v, rs, &m4, sal_of(g));
                 else
                     q = encode_group(v, rs, &m4);
             }
@@ -144,11 +152,19 @@ __global__ __launch_bounds__(THREADS) void pack_kernel(const float *__restrict__
         };
         if (CACHED) {
 #pragma unroll
-            for (int i = 0; i < SLOTS; ++i) emit(i, tid + i * THREADS, cache[i]);
+            for (int i = 0; i < SLOTS; ++i) emit(i, tid + i * THREADS, cache[i], [&](int g) { return reinterpret_cast<const float4 *>(saliency)[g]; });
         } else {
-            for (int g0 = 0, i = 0; g0 < gpad; g0 += THREADS, ++i) {
-                const int g = g0 + tid;
-                emit(i, g, g < ngroups ? row[g] : make_float4(0.f, 0.f, 0.f, 0.f));
+            // (from the end of the row, whose last part is what the first pass left in the L2)
+            for (int i = ((gpad + THREADS - 1) / THREADS - 1) / AHEAD * AHEAD; i >= 0; i -= AHEAD) {
+                const int g0 = i * THREADS;
+                float4 v[AHEAD], sal[AHEAD];
+#pragma unroll
+                for (int u = 0; u < AHEAD; ++u) {
+                    v[u] = weights(g0 + u * THREADS + tid);
+                    if (EX) sal[u] = reinterpret_cast<const float4 *>(saliency)[min(g0 + u * THREADS + tid, ngroups - 1)];
+                }
+#pragma unroll
+                for (int u = 0; u < AHEAD; ++u) emit(i + u, g0 + u * THREADS + tid, v[u], [&](int) { return sal[u]; });
             }
         }
     }
@@ -321,6 +337,7 @@ extern "C" int slim_pack_ex(const float *W, slim_shape shape, const float *salie
         !aligned16(scale_in))
         return SLIM_ERR_ALIGN;
     hipStream_t st = static_cast<hipStream_t>(stream);
+    if (!scale_in && !saliency) return launch_pack<false>(W, shape, qvals, meta, scale, nullptr, st);
     if (!scale_in) return launch_pack<true>(W, shape, qvals, meta, scale, saliency, st);
     const size_t tiles = (size_t)((shape.n + 31) / 32) * pk_ktiles(shape.k);
     hipLaunchKernelGGL(pack_scaled_kernel, dim3((unsigned)(2 * tiles < kPackScaledGrid ? 2 * tiles : kPackScaledGrid)), dim3(256), 0, st, W, shape.n, shape.k, saliency, scale_in, qvals, meta, scale);

@@ -36,6 +36,15 @@ def test_row_lengths(n, k):
             check(W, sal if use_sal else None, given if use_scale else None)
 
 
+@pytest.mark.parametrize("n,k", [(2, 53256), (33, 57352), (1, 65536), (2, 36864)])
+def test_row_lengths_that_are_read_twice(n, k):
+    """Four groups per lane at a time, from the end: every remainder of the number of trips."""
+    rng = np.random.default_rng(k + 1)
+    W = rng.standard_normal((n, k)).astype(np.float32)
+    check(W, None, None)
+    check(W, rng.uniform(0.1, 3.0, k).astype(np.float32), None)
+
+
 @pytest.mark.parametrize("scale", [0.5, 0.1, 1 / 7.0, 3.3333333, 1e-30, 1e-40, 1e36])
 def test_quotients_next_to_a_half(scale):
     """Products of the scale with every half from -9.5 to 8.5, and the four numbers on both sides of each."""
