@@ -311,9 +311,9 @@ static int launch_pack(const float *W, slim_shape shape, uint8_t *qvals, uint8_t
         SLIM_PACK_LAUNCH(512, 8);
     else if (groups <= 1024 * 8)
         SLIM_PACK_LAUNCH(1024, 8);
-    else if (groups <= 1024 * kPackSlotsMax && !EX)
+    else if (groups <= 1024 * kPackSlotsMax)     // (read twice instead, with saliency: 1024 x 32776 42 -> 45 us, up to 49152 the same)
         SLIM_PACK_LAUNCH(1024, kPackSlotsMax);
-    else                                     // (with saliency, twelve slots do not fit the registers: 1024 x 40960 63 us, read twice 53)
+    else
         SLIM_PACK_LAUNCH(1024, 0);
 #undef SLIM_PACK_LAUNCH
     return hip_status(hipGetLastError());
