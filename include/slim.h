@@ -212,9 +212,11 @@ int slim_quant_search_rows(const float *W, slim_shape shape, float *scale_out, f
  * lose bits.  Their error against 64 bits is below that of fp32 products (2.2e-7 against 5.8e-7 in the 2-norm at 4096 x
  * 4096, every row and column of the result included) for saliencies that span up to 1e3; beyond, it still is in the
  * 2-norm, but rows and columns of the result far below the largest are less exact (channels 1e6 below: 8e-6 against 7e-7).
- * orth() only scales columns where products in a row lose nothing by it: two, four or eight of them run between two
- * blocks that are orthonormalised, by the pivots of the last one (two up to a span of 1e4, twice as many where its square is);
- * the last block always is.
+ * Between two blocks that are orthonormalised up to eight products may run whose columns are only scaled, as many as
+ * the pivots of the last such block allow (two up to a span of 1e4, from the seventh product on four up to 1e3 and eight
+ * up to 30); the last block always is orthonormalised, with no more than four before it.  Before L is rounded to fp16 its span
+ * is as near the exact iterate's as with two in a row at most up to a factor of 1.5, and as with every block orthonormal
+ * up to one of about 3 (replayed on the CPU: 2e-6 to 2e-5 in the 2-norm, where fp16 rounds at 5e-4).
  * workspace: slim_adapters_workspace_bytes (HOST out-pointer; about 12 n k bytes -- S in fp32, S and its transpose as
  * two fp16 matrices -- plus 20 to 45 bytes per element of a block of max(n, k) x rank_pad), need not be zeroed.  Errors: NULL, SHAPE, ALIGN, WORKSPACE, HIP.
  * The workgroups of a factorisation hand tiles to one another; those waits are bounded, and should one run out, L and R are NaN.

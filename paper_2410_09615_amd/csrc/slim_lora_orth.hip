@@ -25,14 +25,18 @@
 // what the Gram matrix, the factorisation and the rounding of the products have to carry is the condition of the block, which
 // grows by that of S per product.  So several products follow on one another; how many is decided where the pivots are known, in
 // memory, and the kernels of a block that is only scaled return at once, but for the last (the host does not know).
-// The rule (next_run()): one product after the first block, two while the pivots of a block span at most kSpread (a
-// condition of 100), twice as many as before (up to kMaxRun) where their squares do.  Doubling to eight asks for 30: the
-// columns have separated by then, the pivots are squares of singular values whatever the number of products, and
-// rounding in the direction of the largest grows by their ratio with each product, 2e-7 * 5.5^8 = 0.2 of a column
-// at that limit.  A block whose pivots span more is followed by a quarter as many.
-// 16 rounds of a layer of 4096 x 4096 with 409 columns (singular values over a factor of 3): 9 blocks of 34 are orthonormalised,
-// where every other one was 19: 6.36 -> 4.69 ms for the call.  Residual, directions lost and orthonormality are those of every
-// other block on 150 spectra (saliencies that span 1 to 1e6 in several ways, 2 and 16 rounds).
+// The rule (orth_run()): one product after the first block, then two while the pivots of a block span at most kSpread (a
+// condition of 100), then twice as many as before, up to kMaxRun, while their span allows that many: rounding in the
+// direction of the largest singular value grows by its ratio to the smallest with each product, and 2e-7 (of a column) times that
+// ratio to the power of the run has to stay below 0.2, which is 1e3 for the span, the ratio's square, at four products and 30 at
+// eight; beginning with four asks for 100.  A span above kSpread is followed by a quarter as many.
+// That is so where the columns have separated.  Before, they hold a part of the direction of the largest by themselves, and what
+// they lose beside it is not only in that direction: with four products in a row from the third on, L was up to 110 times further
+// from the span of the exact iterate (one singular value 10 times the others, 6 rounds: 9e-4 of a column, where L in fp16 is
+// rounded at 5e-4).  So four begin with the seventh product, and the last run has no more than four (orth_due()), after which
+// L is as near as with two products at most in a row, up to a factor of 1.5 (tests/test_orth_rule.py).
+// 16 rounds of a layer of 4096 x 4096 with 409 columns (singular values over a factor of 3): 11 blocks of 34 are orthonormalised,
+// where every other one was 19 (127 us more for each than for one that is only scaled).
 #include <utility>
 
 #include "slim_internal.h"
@@ -45,7 +49,9 @@ constexpr int kOb = 64;                        // block of columns
 constexpr int kTileFloats = kOb * kOb;
 constexpr int kGramTiles = 640;                // partial tiles of G the workspace has room for
 constexpr float kSpread = 1e4f;                // largest / smallest pivot up to which as many products as before may follow
-constexpr int kMaxRun = 8;                     // products between two blocks that are orthonormalised
+constexpr int kMaxRun = 8;                     // products between two blocks that are orthonormalised, at most
+constexpr int kLastRun = 4;                    // before the last of them, at most
+constexpr int kSeparated = 7;                  // products before more than two in a row
 constexpr int kMaxBlocks = 1024 / kOb, kMaxTri = kMaxBlocks * (kMaxBlocks + 1) / 2;      // blocks of columns, tiles of a lower triangle
 
 // Words of an orth() that its kernels and the next orth() read: the product after which the next block has to be
@@ -226,16 +232,25 @@ __device__ __forceinline__ bool factor16(float4_t &w, int i, int g, float floor_
     return alive;
 }
 
-// How many products may follow before the next block that is orthonormalised, after one that took `done` of them to
-// pivots from pmin to pmax.
-__device__ __forceinline__ int next_run(int done, float pmax, float pmin)
+// How many products may follow before the next block that is orthonormalised, after the one `h` products into the iteration that
+// took `done` of them (0, or a power of two up to kMaxRun) to pivots from pmin to pmax.
+__host__ __device__ int orth_run(int done, int h, float pmax, float pmin)
 {
     if (!(pmax <= kSpread * pmin)) return done >= 4 ? done / 4 : 1;
+    if (done < 2) return done + 1;
+    if (h < kSeparated) return 2;
     const float spread = pmax / pmin;
-    if (done == 0) return 1;
-    if (done == 1) return 2;
-    if (2 * done <= kMaxRun && spread <= (done == 2 ? 100.0f : 30.0f)) return 2 * done;
-    return done;
+    int run = 2 * done < kMaxRun ? 2 * done : kMaxRun;
+    if (run == 8 && !(spread <= 30.0f)) run = 4;
+    if (run == 4 && !(spread <= (done == 2 ? 100.0f : 1e3f))) run = 2;
+    return run;
+}
+// The product after which the next block is orthonormalised, where `run` may follow the one after h of them: the last run begins at
+// last - kLastRun or later.
+__host__ __device__ int orth_due(int h, int run, int last)
+{
+    const int end = h + run < last ? h + run : last;
+    return h < last - kLastRun && end > last - kLastRun ? last - kLastRun : end;
 }
 
 // What the workgroups of a factorisation hand to one another: a tile of the factor (at tri(I, J)), a diagonal tile and the
@@ -468,10 +483,9 @@ __global__ __launch_bounds__(256) void lora_chol_kernel(int nb, int l, const flo
     pmax = wave_max(pmax);
     pmin = -wave_max(-pmin);
     if (tid == 0) {
-        const int done = step.in ? step.in->run : 0, run = next_run(done, pmax, pmin), end = step.h + run;
+        const int run = orth_run(step.in ? step.in->run : 0, step.h, pmax, pmin);
         step.out->run = run;
-        // (a block that is due just before the last one is left to that)
-        step.out->due = step.last - end <= run / 4 ? step.last : end;
+        step.out->due = orth_due(step.h, run, step.last);
     }
 }
 

@@ -93,8 +93,8 @@ def start_block(rows, cols, r, seed=1):
 def test_rounds_without_orthonormalising_every_block(n, k, r, base, iters):
     """Runs of one, two, four and eight products between two orthonormal blocks, and what is left of a run when the
     rounds end: L spans what as many rounds with every block orthonormal reach in binary64 from the same start.
-    L is rounded to fp16: a column leaves that span by at most 2^-11; the rounding of the block's products and Gram matrices,
-    3e-7 times the condition of a block (at most 1e3 with eight products in a run), is below that: twice 2^-11 sqrt(r) for r columns."""
+    L is rounded to fp16: a column leaves that span by at most 2^-11; the rounding of the block's products and Gram matrices
+    (below 3e-5 for the whole block in the replay of test_orth_rule.py) is below that: twice 2^-11 sqrt(r) for r columns."""
     W = wl.make_weight(n, k, seed=n + 9).numpy()
     q, m, s = B.slim_pack(torch.from_numpy(W).to(DEV))
     ref = O.compress(W)
