@@ -363,7 +363,8 @@ int slim_linear_gemv_static(const slim_layer *layer, const slim_half *X, int32_t
  *           (slim_workspace_check then reports SLIM_ERR_WAIT).  With lds_kb != 0 slim_linear_gemm and
  *           slim_lowrank on a small batch launch everything, but the workgroups meant to make T make nothing:
  *           those that wait make it themselves, and Y is what it always is.  slim_compute_adapters on more than 64
- *           columns (rank_pad) launches only the workgroup of each factorisation that waits for the others: L and R are NaN;
+ *           columns (rank_pad), called by the thread that has set this and by no other, launches only the workgroup of
+ *           each factorisation that waits for the others: L and R are NaN and diag[2] is infinite;
  *   lds_kb  0: plan with the device's LDS; 16..160: with at most this many KiB
  *           (X then streams through the LDS in chunks on small layers too).
  * Errors: SHAPE (a value outside these ranges).

@@ -42,6 +42,9 @@ DeviceInfo device_info()
 static std::atomic<int> g_decode_path{-1};
 static std::atomic<int> g_decode_lds_kb{0};
 int decode_path_override() { return g_decode_path.load(std::memory_order_relaxed); }
+// (the thread that has set path 3 asked for it itself)
+static thread_local bool t_wait_test = false;
+bool adapters_wait_test() { return t_wait_test && decode_path_override() == 3; }
 size_t decode_lds_limit() { return (size_t)g_decode_lds_kb.load(std::memory_order_relaxed) * 1024; }
 
 int gemm_t_splits(int32_t m, int32_t rank_pad, int32_t k);   // slim_gemm.hip
@@ -110,6 +113,7 @@ extern "C" int slim_decode_override(int32_t path, int32_t lds_kb)
 {
     if (path < -1 || path > 3) return SLIM_ERR_SHAPE;
     if (lds_kb != 0 && (lds_kb < 16 || lds_kb > 160)) return SLIM_ERR_SHAPE;
+    t_wait_test = path == 3;
     g_decode_path.store(path, std::memory_order_relaxed);
     g_decode_lds_kb.store(lds_kb, std::memory_order_relaxed);
     return SLIM_OK;

@@ -178,7 +178,8 @@ struct DeviceInfo {
 DeviceInfo device_info();
 
 // Process-wide test and measurement control of the decode geometry (slim_decode_override).
-int decode_path_override();      // -1: automatic, 0: two-launch kernels, 1: the roles as two launches, 2: one launch
+int decode_path_override();      // -1: automatic, 0: two-launch kernels, 1: the roles as two launches, 2: one launch, 3: a test of the bounded waits
+bool adapters_wait_test();       // 3, set by the calling thread: slim_compute_adapters tests its wait too
 size_t decode_lds_limit();       // 0: the device's LDS; else bytes the one-launch geometry may plan with
 
 // Device address of the library's own scratch array on the current device (slim_gemv.hip).

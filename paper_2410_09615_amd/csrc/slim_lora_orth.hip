@@ -654,7 +654,7 @@ int launch_orth(const float *in, float *out, half_t *hi, half_t *lo, int rows, i
     const int zrows = ((rows + splits - 1) / splits + 31) / 32 * 32;
     splits = (rows + zrows - 1) / zrows;
     hipLaunchKernelGGL(lora_gram_kernel, dim3((unsigned)tiles, (unsigned)splits), dim3(256), 0, st, in, rows, l, zrows, tiles, P, step);
-    const bool wait_test = decode_path_override() == 3;      // (slim_decode_override: only the workgroup that waits for the others)
+    const bool wait_test = adapters_wait_test();     // (slim_decode_override: only the workgroup that waits for the others)
     hipLaunchKernelGGL(lora_chol_kernel, dim3((unsigned)(wait_test ? 1 : tiles)), dim3(256), 0, st, nb, l, (const float *)P, splits, tiles, G, Lf, D, Dp,
                        hand, seq, wait_test ? 256 : kHandPolls, step);
     const size_t lds = (size_t)(16 * (nb * kOb + 4) + 16 * 68) * sizeof(float);

@@ -175,6 +175,34 @@ def test_decode_plan_of_the_configured_shapes(decode_override):
         assert p["path"] == 2 and p["chunks"] > 1 and p["lds_bytes"] <= lds_kb * 1024, (n, k, r, m, lds_kb)
 
 
+def test_the_wait_test_of_the_adapters_is_the_threads_own(decode_override):
+    """While one thread tests a wait (path 3), slim_compute_adapters called by another computes as always."""
+    import threading
+    f = B.lib()._ZN4slim18adapters_wait_testEv
+    f.argtypes, f.restype = [], ctypes.c_bool
+    seen = []
+
+    def other(path):
+        if path:
+            B.slim_decode_override(path)
+        seen.append(f())
+
+    def in_thread(path):
+        t = threading.Thread(target=other, args=(path,))
+        t.start()
+        t.join()
+
+    assert not f()
+    decode_override("wait_test")
+    assert f()
+    in_thread(None)
+    in_thread("auto")
+    assert not f()                        # (the other thread has ended the test)
+    in_thread("wait_test")
+    decode_override("auto")
+    assert seen == [False, False, True] and not f()
+
+
 def test_static_scratch_call_validates_on_the_host():
     """slim_linear_gemv_static checks arguments and the size of its own scratch array before anything
     touches a device."""
