@@ -48,7 +48,7 @@ typedef float float16v_t __attribute__((ext_vector_type(16)));
 constexpr int kOb = 64;                        // block of columns
 constexpr int kTileFloats = kOb * kOb;
 constexpr int kGramTiles = 640;                // partial tiles of G the workspace has room for
-constexpr float kSpread = 1e4f;                // largest / smallest pivot up to which as many products as before may follow
+constexpr float kSpread = 1e4f;                // largest / smallest pivot up to which more than one product may follow
 constexpr int kMaxRun = 8;                     // products between two blocks that are orthonormalised, at most
 constexpr int kLastRun = 4;                    // before the last of them, at most
 constexpr int kSeparated = 7;                  // products before more than two in a row

@@ -18,7 +18,7 @@
 // the leading ones, which the orthonormalisation takes out.  Adapters of saliencies that span up to 1e8 capture what they did
 // with fp32 products, to the digits reported.
 // Three fp16 instructions do the work of eight fp32 ones that take twice the time each.  4096 x 4096 times 416 columns: 200 us with the fp32 instruction (70 TFLOP/s),
-// 54 us like this (46, and 8 to add the shares of K and find the columns' largest magnitudes).
+// 53 us like this (44, and 9 to add the shares of K and find the columns' largest magnitudes).
 //   S is split once per call, into the operand order of the instruction, for S Z and for S^T Q;
 //   the blocks are split where they are written (lora_apply_kernel, lora_init_kernel), columns as rows.
 #include "slim_mma.h"
@@ -182,7 +182,7 @@ __device__ __forceinline__ void split_phase(const SplitOperands &o, int K, const
 
 // Workgroup: 4 wavefronts, tile 256 rows x 128 columns, each wavefront 64 x 128 on fixed accumulators.  One wavefront per
 // SIMD, which its 24 matrix instructions per step of 16 inputs keep busy while the loads of the next are on their way:
-// 4096 x 4096 times 416 columns 46 us, of them 37 in the loop (matrix pipes busy 77 % of the time, at 1.75 GHz) and 5
+// 4096 x 4096 times 416 columns 44 to 46 us, of them 37 in the loop (matrix pipes busy 77 % of the time, at 1.75 GHz) and 5
 // to write four shares of K; the three products one after the other, with every operand fetched for each, took 51.
 __global__ __launch_bounds__(256, 1) void lora_split_gemm_kernel(SplitGemmArgs a)
 {
