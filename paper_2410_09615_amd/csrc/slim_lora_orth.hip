@@ -3,17 +3,16 @@
 //
 //   G = in^T in = Lc Lc^T,  out = in Lc^-T     (columns in order: in = out Lc^T with a positive diagonal)
 //
-// The call is a chain (products, 64-column steps of the factorisation, products), so what bounds it is the
-// number of launches (4 us each) and the latency of the 64 x 64 diagonal blocks, not arithmetic:
-//   lora_gram_kernel    lower tiles of G, the rows divided among the workgroups, partial tiles to memory;
-//   lora_chol_kernel    the factorisation, a workgroup per tile, which hand finished tiles to one another through
-//                       memory; one of them factors and inverts the diagonal tiles, in blocks of 16 that live in the
-//                       registers of a wavefront;
+// The call is a chain (products, 16-column steps of the factorisation, products), so what bounds it is the
+// number of launches (4 us each) and the latency of the diagonal blocks, not arithmetic:
+//   lora_factor_kernel  lower tiles of G, the rows divided among workgroups; then the factorisation: a workgroup that factors and
+//                       inverts the diagonal tiles, in blocks of 16 that live in the registers of a wavefront, and workgroups for the
+//                       other tiles, in strips of 16 rows, which hand what they make to one another through memory;
 //   lora_apply_kernel   a workgroup carries 16 rows of `in` through all block columns, which stay in LDS:
 //                       out_J = (in_J - sum_{K<J} out_K L_JK^T) X_JJ^T, one launch for the whole block.
-// 4096 x 416: 3 launches (gram 22 us, factorisation 94, apply 25) where a factorisation with one launch per 64 columns took
-// 148 us and seven launches of 4 us where the block is only scaled, and with separate panel, trailing and column products
-// and a 64-step one-workgroup diagonal 700.
+// 4096 x 416: 90 us (G 15, the diagonal tiles 7.3 each, apply 20).  With G in a launch of its own and a workgroup per tile that hands it on
+// with release and acquire 141 (22, 12.1, 25), with one launch per 64 columns 200, and with separate panel, trailing and column
+// products and a 64-step one-workgroup diagonal 700.
 //
 // A pivot below 1e-9 of the largest diagonal entry of G marks a column that lies in the span of the ones before it
 // (or a padding column of zeros): it gets pivot 1 and no column is subtracted for it, in the blocks that follow either,
@@ -36,7 +35,7 @@
 // rounded at 5e-4).  So four begin with the seventh product, and the last run has no more than four (orth_due()), after which
 // L is as near as with two products at most in a row, up to a factor of 1.5 (tests/test_orth_rule.py).
 // 16 rounds of a layer of 4096 x 4096 with 409 columns (singular values over a factor of 3): 11 blocks of 34 are orthonormalised,
-// where every other one was 19 (127 us more for each than for one that is only scaled).
+// where every other one was 19 (80 us more for each than for one that is only scaled).
 #include <utility>
 
 #include "slim_internal.h"
@@ -47,11 +46,11 @@ typedef float float16v_t __attribute__((ext_vector_type(16)));
 
 constexpr int kOb = 64;                        // block of columns
 constexpr int kTileFloats = kOb * kOb;
-constexpr int kGramTiles = 640;                // partial tiles of G the workspace has room for
 constexpr float kSpread = 1e4f;                // largest / smallest pivot up to which more than one product may follow
 constexpr int kMaxRun = 8;                     // products between two blocks that are orthonormalised, at most
 constexpr int kLastRun = 4;                    // before the last of them, at most
 constexpr int kSeparated = 7;                  // products before more than two in a row
+constexpr int kDies = 8;
 constexpr int kMaxBlocks = 1024 / kOb, kMaxTri = kMaxBlocks * (kMaxBlocks + 1) / 2;      // blocks of columns, tiles of a lower triangle
 
 // Words of an orth() that its kernels and the next orth() read: the product after which the next block has to be
@@ -83,92 +82,6 @@ __device__ __forceinline__ void mma16(float4_t a, float4_t b, float4_t &c)
     for (int e = 0; e < 4; ++e) c = __builtin_amdgcn_mfma_f32_16x16x4f32(a[e], b[e], c, 0, 0, 0);
 }
 
-// Partial tile of G = Y^T Y: tile t = tri(i, j) over the rows z * zrows .. ; wavefront w takes a quarter of them.  Two
-// rows of Y are the operands of V_MFMA_F32_32X32X2_F32 as they lie in memory: no LDS on the way.
-__global__ __launch_bounds__(256) void lora_gram_kernel(const float *__restrict__ Y, int rows, int l, int zrows, int tiles,
-                                                        float *__restrict__ P, OrthStep step)
-{
-    if (step.skip()) return;
-    __shared__ __attribute__((aligned(16))) float red[kTileFloats];
-    const int lane = threadIdx.x & 63, r = lane & 31, h = lane >> 5;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    int i = 0;
-    while (tri(i + 1, 0) <= (int)blockIdx.x) ++i;
-    const int j = (int)blockIdx.x - tri(i, 0);
-    const int per = zrows / 4;                  // even
-    const int k0 = (int)blockIdx.y * zrows + wave * per;
-    const int cnt = max(0, min(per, rows - k0));
-    // (a base of its own keeps the offsets in 32 bits for any number of rows; reads past the range are zeros)
-    const rsrc_t rs = make_rsrc(Y + (size_t)min(k0, rows) * l, (uint32_t)cnt * (uint32_t)l * 4u);
-    uint32_t ca[2], cb[2];
-#pragma unroll
-    for (int b = 0; b < 2; ++b) {
-        const int na = kOb * i + 32 * b + r, nb = kOb * j + 32 * b + r;
-        ca[b] = na < l ? (uint32_t)(h * l + na) * 4u : 0xFFFFFF00u;
-        cb[b] = nb < l ? (uint32_t)(h * l + nb) * 4u : 0xFFFFFF00u;
-    }
-    float16v_t acc[2][2];
-#pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int b = 0; b < 2; ++b)
-#pragma unroll
-            for (int e = 0; e < 16; ++e) acc[a][b][e] = 0.f;
-    auto ld = [&](uint32_t c, uint32_t row) {
-        return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, c < 0xFFFFFF00u ? (int)(c + row * (uint32_t)l * 4u) : (int)c, 0, 0));
-    };
-    constexpr int U = 8;                        // pairs of rows per trip, the next trip's loads in flight
-    float av[U][2], bv[U][2];
-    auto load = [&](int k) {
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-#pragma unroll
-            for (int b = 0; b < 2; ++b) {
-                av[u][b] = ld(ca[b], (uint32_t)(k + 2 * u));
-                bv[u][b] = ld(cb[b], (uint32_t)(k + 2 * u));
-            }
-    };
-    load(0);
-    for (int k = 0; k < cnt; k += 2 * U) {
-        float ac[U][2], bc[U][2];
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-#pragma unroll
-            for (int b = 0; b < 2; ++b) {
-                ac[u][b] = av[u][b];
-                bc[u][b] = bv[u][b];
-            }
-        load(k + 2 * U);
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-#pragma unroll
-            for (int a = 0; a < 2; ++a)
-#pragma unroll
-                for (int b = 0; b < 2; ++b) acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x2f32(ac[u][a], bc[u][b], acc[a][b], 0, 0, 0);
-    }
-    // register 4 q + e of a block: row 8 q + 4 h + e, column r
-    for (int w = 0; w < 4; ++w) {
-        if (wave == w) {
-#pragma unroll
-            for (int a = 0; a < 2; ++a)
-#pragma unroll
-                for (int b = 0; b < 2; ++b)
-#pragma unroll
-                    for (int q = 0; q < 4; ++q)
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) {
-                            float *p = red + op_at(32 * a + 8 * q + 4 * h + e, 32 * b + r);
-                            *p = w == 0 ? acc[a][b][4 * q + e] : *p + acc[a][b][4 * q + e];
-                        }
-        }
-        __syncthreads();
-    }
-    float4_t *const out = reinterpret_cast<float4_t *>(P + ((size_t)blockIdx.y * tiles + blockIdx.x) * kTileFloats);
-#pragma unroll
-    for (int q = 0; q < 4; ++q) out[threadIdx.x + 256 * q] = reinterpret_cast<const float4_t *>(red)[threadIdx.x + 256 * q];
-}
-
 template <int N>
 __device__ __forceinline__ float row_lane(float v)       // lane N of the sixteen, to all of them
 {
@@ -185,41 +98,90 @@ __device__ __forceinline__ void for_each(F &&f)
     for_each_impl(std::make_integer_sequence<int, N>{}, f);
 }
 
-// The value that lane i % 16 of the G-th sixteen lanes holds, to lane i of all four.
+// What lane i % 16 of the G-th sixteen lanes holds, to lane i of all four: four registers side by side, in asm because a swap has to
+// come two wait states after what it moves, which the other registers' instructions are (an s_nop is 9 cycles, an instruction 5).
 template <int G>
-__device__ __forceinline__ float from_group(float v)
+__device__ __forceinline__ void from_group(const float4_t &w, float (&out)[4])
 {
-    const unsigned b = __builtin_bit_cast(unsigned, v);
-    const auto p = __builtin_amdgcn_permlane16_swap(b, b, false, false);        // groups 0, 0, 2, 2 and 1, 1, 3, 3
-    const unsigned h = p[G & 1];
-    const auto q = __builtin_amdgcn_permlane32_swap(h, h, false, false);
-    return __builtin_bit_cast(float, (unsigned)q[G >> 1]);
+    float t[4];
+    asm volatile("v_mov_b32 %0, %8\n\tv_mov_b32 %4, %8\n\tv_mov_b32 %1, %9\n\tv_mov_b32 %5, %9\n\t"
+                 "v_mov_b32 %2, %10\n\tv_mov_b32 %6, %10\n\tv_mov_b32 %3, %11\n\tv_mov_b32 %7, %11\n\t"
+                 "v_permlane16_swap_b32 %0, %4\n\tv_permlane16_swap_b32 %1, %5\n\ts_nop 0\n\t"
+                 "v_permlane16_swap_b32 %2, %6\n\tv_permlane16_swap_b32 %3, %7"          // groups 0, 0, 2, 2 and 1, 1, 3, 3
+                 : "=&v"(t[0]), "=&v"(t[1]), "=&v"(t[2]), "=&v"(t[3]), "=&v"(out[0]), "=&v"(out[1]), "=&v"(out[2]), "=&v"(out[3])
+                 : "v"(w[0]), "v"(w[1]), "v"(w[2]), "v"(w[3]));
+#define SLIM_MOVES(to, from) "v_mov_b32 %" #to ", %" #from "\n\t"
+    if constexpr (G & 1)
+        asm volatile("s_nop 1\n\t" SLIM_MOVES(0, 4) SLIM_MOVES(1, 5) SLIM_MOVES(2, 6) SLIM_MOVES(3, 7)
+                     "v_permlane32_swap_b32 %0, %4\n\tv_permlane32_swap_b32 %1, %5\n\ts_nop 0\n\tv_permlane32_swap_b32 %2, %6\n\tv_permlane32_swap_b32 %3, %7\n\ts_nop 1"
+                     : "+v"(t[0]), "+v"(t[1]), "+v"(t[2]), "+v"(t[3]), "+v"(out[0]), "+v"(out[1]), "+v"(out[2]), "+v"(out[3]));
+    else
+        asm volatile("s_nop 1\n\t" SLIM_MOVES(4, 0) SLIM_MOVES(5, 1) SLIM_MOVES(6, 2) SLIM_MOVES(7, 3)
+                     "v_permlane32_swap_b32 %0, %4\n\tv_permlane32_swap_b32 %1, %5\n\ts_nop 0\n\tv_permlane32_swap_b32 %2, %6\n\tv_permlane32_swap_b32 %3, %7\n\ts_nop 1"
+                     : "+v"(t[0]), "+v"(t[1]), "+v"(t[2]), "+v"(t[3]), "+v"(out[0]), "+v"(out[1]), "+v"(out[2]), "+v"(out[3]));
+#undef SLIM_MOVES
+    if constexpr (G < 2)                         // (lower halves in both of t, upper in both of out)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) out[e] = t[e];
+}
+
+// Step C of factor16(): w[f] += m times w[f] of lane C of the sixteen, for the registers of w and for those of c4 that are still
+// ahead (FIRST on); then the pivot of the next step, d = c4[FIRST] of its lane or the floor, and its reciprocal q, behind which the last
+// of w hide.  The broadcast rides on the multiply-add.  Outside the compiler's hazard bookkeeping: two wait states between a
+// write and a read by another lane (w[FIRST - 1], written last before a step, comes last; an s_nop is 9 cycles, an instruction 5), one
+// behind a reciprocal.
+template <int C, int FIRST>
+__device__ __forceinline__ void factor_step(float4_t &w, float (&c4)[4], float m, float floor_, float &d, float &q)
+{
+#define SLIM_ROW(x) "v_fmac_f32_dpp " x ", " x ", %10 row_newbcast:%12 row_mask:0xf bank_mask:0xf\n\t"
+#define SLIM_NEXT(x) "v_max_f32_dpp %8, " x ", %11 row_newbcast:%13 row_mask:0xf bank_mask:0xf\n\tv_rcp_f32 %9, %8\n\t"
+#define SLIM_REGS "+v"(w[0]), "+v"(w[1]), "+v"(w[2]), "+v"(w[3]), "+v"(c4[0]), "+v"(c4[1]), "+v"(c4[2]), "+v"(c4[3]), "=&v"(d), "=&v"(q) \
+                  : "v"(m), "v"(floor_), "n"(C), "n"((C + 1) % 16)
+    if constexpr (FIRST == 1)
+        asm volatile(SLIM_ROW("%5") SLIM_ROW("%6") SLIM_ROW("%7") SLIM_NEXT("%5") SLIM_ROW("%1") SLIM_ROW("%2") SLIM_ROW("%3") SLIM_ROW("%0") : SLIM_REGS);
+    else if constexpr (FIRST == 2)
+        asm volatile(SLIM_ROW("%6") SLIM_ROW("%7") SLIM_ROW("%2") SLIM_NEXT("%6") SLIM_ROW("%3") SLIM_ROW("%0") SLIM_ROW("%1") : SLIM_REGS);
+    else if constexpr (FIRST == 3)
+        asm volatile(SLIM_ROW("%7") SLIM_ROW("%3") SLIM_ROW("%0") SLIM_NEXT("%7") SLIM_ROW("%1") SLIM_ROW("%2") : SLIM_REGS);
+    else
+        asm volatile(SLIM_ROW("%0") SLIM_ROW("%1") SLIM_ROW("%2") SLIM_ROW("%3") : SLIM_REGS);
+#undef SLIM_ROW
+#undef SLIM_NEXT
+#undef SLIM_REGS
 }
 
 // 16 x 16: lane i of group g (sixteen lanes) holds row i, columns 4 g .. 4 g + 3, of the symmetric block a = Lc Lc^T; on
 // return those of Lc^-1.  The steps run on a = M diag(d) M^T, M with a unit diagonal, whose chain has a reciprocal and no square
 // root, and the rows of M^-1 are scaled by 1 / sqrt(d) at the end.  Step c adds m_i = -a_ic / d_c times row c to the rows i
 // below it: to the columns of a after c, to those of M^-1 before it, and column c becomes that of M^-1, so that one register
-// holds a column of the one and then of the other.  Broadcasts are between lanes, without LDS or barriers.  (With a row
-// of both in each of sixteen lanes the 64 x 64 block took 13 us instead of 9: twice the instructions per step.)
+// holds a column of the one and then of the other.  Every group works on a copy of the four columns in turn, so that what the
+// steps wait for is the pivot's broadcast, its reciprocal and one multiply-add, in registers; no LDS, no barriers.
+// A lone wavefront issues an instruction in 5 cycles whether or not it waits for the one before, so instructions are what counts, and
+// those that select by a comparison count threefold (the mask has to be waited for): rows and pivots that take no part are
+// multiplied by zero instead.  0.9 us a block; with each column fetched from its group by itself, moves for the broadcasts and selections
+// 1.15.
 // pmax, pmin: the largest and the smallest pivot of this lane's rows so far, but for those of `dead`.  Returns whether this row's
-// pivot is above the floor.
+// pivot is above the floor (2^-120 or more).
 __device__ __forceinline__ bool factor16(float4_t &w, int i, int g, float floor_, float dead, float &pmax, float &pmin)
 {
     float d_i = 1.0f;                            // this row's pivot
-    for_each<16>([&](auto cc) {
-        constexpr int c = cc;
-        const float col = from_group<c / 4>(w[c % 4]);
-        const float d = row_lane<c>(col);
-        d_i = i == c ? d : d_i;
-        float q = __builtin_amdgcn_rcpf(d);
-        q = q * (2.0f - d * q);                  // to rounding
-        const float m = d > floor_ && i > c ? -col * q : 0.f;    // (d below: a column in the span of the ones before it: nothing to subtract)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const float s = __builtin_fmaf(row_lane<c>(w[e]), m, w[e]);
-            w[e] = e == c % 4 && g == c / 4 ? (i == c ? 1.0f : m) : s;
-        }
+    for_each<4>([&](auto pc) {
+        constexpr int p = pc;
+        float c4[4];
+        from_group<p>(w, c4);
+        float d = fmaxf(row_lane<4 * p>(c4[0]), floor_), q = __builtin_amdgcn_rcpf(d);
+        for_each<4>([&](auto ec) {
+            constexpr int e = ec, c = 4 * p + e;
+            const float below = i > c ? -1.0f : 0.f;
+            // (d at the floor: a column in the span of the ones before it, nothing to subtract)
+            const float above = __builtin_amdgcn_fmed3f((d - floor_) * 0x1p127f, 0.f, 1.f);
+            const float col = c4[e] * below * above;
+            q = q * (2.0f - d * q);              // to rounding
+            w[e] = g == p ? (i == c ? 1.0f : 0.f) : w[e];
+            factor_step<c, e + 1>(w, c4, col * q, floor_, d, q);
+        });
+        const float mine = (i & 2) ? ((i & 1) ? c4[3] : c4[2]) : ((i & 1) ? c4[1] : c4[0]);
+        d_i = i / 4 == p ? mine : d_i;           // (a pivot stays where it was used)
     });
     const bool alive = d_i > floor_;
     pmax = alive ? fmaxf(pmax, d_i) : pmax;
@@ -253,240 +215,571 @@ __host__ __device__ int orth_due(int h, int run, int last)
     return h < last - kLastRun && end > last - kLastRun ? last - kLastRun : end;
 }
 
-// What the workgroups of a factorisation hand to one another: a tile of the factor (at tri(I, J)), a diagonal tile and the
-// one to its left before the last column is subtracted, the inverse of a diagonal tile.  A word each, in a line of its own,
-// holds the number of the orth() whose tile it is (kHandFailed: that of one whose wait ran out).
-enum { kHandL = 0, kHandT = kMaxTri, kHandA = kHandT + kMaxBlocks, kHandD = kHandA + kMaxBlocks, kHandFailed = kHandD + kMaxBlocks, kHandWords };
-constexpr int kHandStride = 16;
+// ---- G = Y^T Y = Lc Lc^T in one launch ----
+// Three kinds of workgroups, in the order of their index:
+//   gram units   a tile of 64 x 64 of G over a range of rows each; they wait for nothing;
+//   the chain    one workgroup, which factors and inverts the diagonal tiles one after the other;
+//   strips       16 rows of a tile below the diagonal (or of a diagonal tile, for the chain) each.
+// What bounds the launch is the chain: 64 columns at a time, each of which needs what the one before it left.  So the chain's
+// workgroup does nothing but what the next 16 columns wait for, and everything else is done beside it: by its other wavefronts
+// while one factors 16 columns, and by the strips.
+// What one workgroup makes for others goes through memory: stored past the L2 (device scope), waited for, and then named by words
+// that hold the number of the orth(), which the readers poll.  They read it past their L2 as well, so there are no fences (write-back and
+// invalidation of an L2 are over a microsecond each).
+// A workgroup waits for workgroups of a lower index, and the chain for strips that wait for it in no more than it has
+// handed on: with workgroups started in the order of their index there is always one that runs.  A wait is bounded all the
+// same; should something not come, lora_apply_kernel makes the block NaN.
+constexpr int kGramUnits = 256;                // partial tiles, at most
+constexpr int kStripGroups = 112;              // workgroups of strips, at most (a call on each of four hardware queues has room for them)
+struct FactorArgs {
+    const float *Y;
+    int rows, l, nb, tiles;
+    int splits, zrows;                         // ranges of rows, rows in each
+    int strips;                                // workgroups of strips
+    float *ws;                                 // orth_floats() (offsets: FactorPlaces)
+    unsigned *hand;
+    unsigned seq;
+    int polls;
+    OrthStep step;
+};
+// Byte offsets in the workspace of an orth(): partial tiles, their diagonals, tiles (of the lower triangle) on their way to the chain, tiles
+// of the factor, inverses of the diagonal tiles.
+struct FactorPlaces {
+    uint32_t P, diag, G, Lf, D, end;
+    __host__ __device__ explicit FactorPlaces(int nb)
+    {
+        const uint32_t t = (uint32_t)tri(nb, 0), b = kTileFloats * 4;
+        P = 0;
+        diag = kGramUnits * b;
+        G = diag + kGramUnits * kOb * 4;
+        Lf = G + t * b;
+        D = Lf + t * b;
+        end = D + (uint32_t)nb * b;
+    }
+};
+// The words: one per gram unit; then four per strip (one of each wavefront), those of the strips of a tile together: of a tile of the factor
+// (at tri(I, J)), of a diagonal tile and of the one to its left before the last columns are subtracted, and four of the inverse of a
+// diagonal tile; last the number of an orth() in which a wait ran out.
+enum { kHandGram = 0, kHandL = kGramUnits, kHandT = kHandL + 16 * kMaxTri, kHandA = kHandT + 16 * kMaxBlocks, kHandD = kHandA + 16 * kMaxBlocks,
+       kHandFailed = kHandD + 16 * kMaxBlocks, kHandWords = kHandFailed + 16 };
 constexpr int kHandPolls = 1 << 24;            // half a microsecond or more each; a wait is over after some tens of them, or when other
                                                // work on the chip has let the rest of the launch start
+constexpr int kDevice = 16;                    // cache policy of a buffer access: device scope (written through / read from memory)
 
-// Everything the workgroup has stored -> visible to who sees the word.
-__device__ __forceinline__ void hand_over(unsigned *hand, int what, unsigned seq)
+__device__ __forceinline__ float4_t load_dev(rsrc_t r, uint32_t off)
+{
+    return __builtin_bit_cast(float4_t, __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, kDevice));
+}
+__device__ __forceinline__ void store_dev(rsrc_t r, uint32_t off, float4_t v)
+{
+    typedef unsigned int store4_t __attribute__((__vector_size__(16)));
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(store4_t, v), r, (int)off, 0, kDevice);
+}
+// What this wavefront has stored is in memory -> its word, or words.
+template <int N = 1>
+__device__ __forceinline__ void hand_over(const FactorArgs &a, int word, int lane)
 {
     asm volatile("s_waitcnt vmcnt(0)" : : : "memory");
-    __syncthreads();
-    if (threadIdx.x == 192) {                    // (not of the wavefront that factors)
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-        __hip_atomic_store(hand + what * kHandStride, seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
+    if (lane < N) __hip_atomic_store(a.hand + word + lane, a.seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-// One lane waits; false: the word has not come.
-__device__ __forceinline__ bool hand_taken(unsigned *hand, int what, unsigned seq, int limit)
+// A wavefront's waits: each lane for four words from `word` on (a multiple of 4; or for none, with a negative number).  `lost`: a
+// wait has run out, and those after it are none.
+__device__ __forceinline__ bool words_there(const FactorArgs &a, rsrc_t hand, int word)
 {
-    for (int polls = 0; __hip_atomic_load(hand + what * kHandStride, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != seq; ++polls) {
-        if (polls >= limit) return false;
-        __builtin_amdgcn_s_sleep(1);
+    const uint4_t v = __builtin_bit_cast(uint4_t, __builtin_amdgcn_raw_buffer_load_b128(hand, word < 0 ? 0 : 4 * word, 0, kDevice));
+    return __all(word < 0 || (v[0] == a.seq && v[1] == a.seq && v[2] == a.seq && v[3] == a.seq));
+}
+__device__ __forceinline__ void wait_words(const FactorArgs &a, rsrc_t hand, int word, bool &lost)
+{
+    for (int polls = 0; !lost; ++polls) {
+        if (words_there(a, hand, word)) break;
+        if (polls >= a.polls) {
+            lost = true;
+            __hip_atomic_store(a.hand + kHandFailed, a.seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        if (polls > 32) __builtin_amdgcn_s_sleep(1);
+        asm volatile("" : : : "memory");
     }
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-    return true;
+    asm volatile("" : : : "memory");
+}
+// The same for `count` gram units, lanes and turns; unit(i): which.
+template <class F>
+__device__ __forceinline__ void wait_gram(const FactorArgs &a, rsrc_t hand, int count, int lane, bool &lost, F &&unit)
+{
+    for (int i = lane; i - lane < count; i += kWave)
+        for (int polls = 0; !lost; ++polls) {
+            const unsigned v = __builtin_amdgcn_raw_buffer_load_b32(hand, i < count ? 4 * (kHandGram + unit(i)) : 0, 0, kDevice);
+            if (__all(i >= count || v == a.seq)) break;
+            if (polls >= a.polls) {
+                lost = true;
+                __hip_atomic_store(a.hand + kHandFailed, a.seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+            __builtin_amdgcn_s_sleep(1);
+            asm volatile("" : : : "memory");
+        }
+    asm volatile("" : : : "memory");
 }
 
-// G = Lc Lc^T in one launch.  What it waits for is the chain of diagonal tiles, so workgroup 0 factors and inverts all of
-// them, one after the other (D[J] whole, Dp[J] with the rows of pivots below the floor as zeros), and nothing on that chain
-// goes through memory but what the others have ready: the tiles (J, J) and (J, J - 1) with the columns before J - 1
-// subtracted.  The panel between those and the column J - 1 it makes itself, from the inverse it has in LDS.  Every other
-// workgroup has a tile (I, J), I >= J, column after column: it adds up the tile's partial tiles, subtracts L_IK L_JK^T for the
-// columns before its own as they come, and hands the tile to workgroup 0 or waits for D[J] and hands on L_IJ = A_IJ Dp_J^T.
-// A workgroup waits for workgroup 0 and for tiles of columns before its own, of a lower index, and workgroup 0 for tiles whose
-// workgroups wait for it in no more than it has handed on: with workgroups started in the order of their index there is always
-// one that runs.  A wait is bounded all the same; should a tile not come, lora_apply_kernel makes the block NaN.
-// 4096 x 416: 94 us, 4.5 where the block is only scaled; one launch per 64 columns took 148 and 30.  (With a diagonal tile's
-// inverse handed through memory to the workgroup of the next one: 4 us more.)
-__global__ __launch_bounds__(256) void lora_chol_kernel(int nb, int l, const float *__restrict__ P, int splits, int tiles, float *G,
-                                                        float *Lf, float *D, float *Dp, unsigned *hand, unsigned seq, int polls, OrthStep step)
+// Partial tile of G: tile t = tri(i, j) over the rows z * zrows .. ; wavefront w takes a quarter of them.  Two
+// rows of Y are the operands of V_MFMA_F32_32X32X2_F32 as they lie in memory, two neighbouring columns a lane: no LDS on the way.  What bounds
+// it is how much is in flight (64 KB per compute unit at 2 us): a register is loaded again as soon as it has been used.  The wavefronts
+// then add up a quarter of the tile each; columns of the tile are rows of the instruction's result, so that a lane holds four next to one
+// another, as the operand order has them.
+__device__ __forceinline__ void gram_unit(const FactorArgs &a, int tile, int z, rsrc_t ws, float4_t *red)
 {
-    if (step.skip()) return;
-    __shared__ __attribute__((aligned(16))) float T[kTileFloats], LI[kTileFloats], LJ[kTileFloats];
-    __shared__ float mx_s[4];
-    __shared__ int missing;
+    const int lane = threadIdx.x & 63, r = lane & 31, h = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int l = a.l;
+    int i = 0;
+    while (tri(i + 1, 0) <= tile) ++i;
+    const int j = tile - tri(i, 0);
+    const int per = a.zrows / 4;                // even
+    const int k0 = z * a.zrows + wave * per;
+    const int cnt = max(0, min(per, a.rows - k0));
+    // (a base of its own keeps the offsets in 32 bits for any number of rows; reads past the range are zeros)
+    const rsrc_t rs = make_rsrc(a.Y + (size_t)min(k0, a.rows) * l, (uint32_t)cnt * (uint32_t)l * 4u);
+    const int na = kOb * i + 2 * r, nb = kOb * j + 2 * r;         // (l is even)
+    const uint32_t ca = (uint32_t)(h * l + na) * 4u, cb = (uint32_t)(h * l + nb) * 4u;
+    float16v_t acc[4];                           // rows 2 x + n / 2, columns 2 y + n % 2 of the tile (x: column, y: row of the instruction's result)
+#pragma unroll
+    for (int n = 0; n < 4; ++n)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[n][e] = 0.f;
+    auto ld = [&](bool ok, uint32_t c, uint32_t row) { return load8(rs, ok ? c + row * (uint32_t)l * 4u : 0xFFFFFF00u, 0u); };
+    constexpr int U = 16;                       // pairs of rows in flight
+    uint2_t av[U], bv[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        av[u] = ld(na < l, ca, (uint32_t)(2 * u));
+        bv[u] = ld(nb < l, cb, (uint32_t)(2 * u));
+    }
+    for (int k = 0; k < cnt; k += 2 * U)
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            float av2[2], bv2[2];
+#pragma unroll
+            for (int b = 0; b < 2; ++b) {
+                const uint32_t x = av[u][b], y = bv[u][b];
+                av2[b] = __builtin_bit_cast(float, x);
+                bv2[b] = __builtin_bit_cast(float, y);
+            }
+#pragma unroll
+            for (int n = 0; n < 4; ++n) acc[n] = __builtin_amdgcn_mfma_f32_32x32x2f32(bv2[n % 2], av2[n / 2], acc[n], 0, 0, 0);
+            av[u] = ld(na < l, ca, (uint32_t)(k + 2 * (U + u)));
+            bv[u] = ld(nb < l, cb, (uint32_t)(k + 2 * (U + u)));
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    // register 4 q + e of acc[n], row 8 q + 4 h + e of the result.  Wavefront w adds up those with q = w: the others leave their part of
+    // them (q, slot of three) in LDS
+    auto slot = [](int q, int w) { return (3 * q + (w < q ? w : w - 1)) * 4 * kWave; };
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+        if (q != wave)
+#pragma unroll
+            for (int n = 0; n < 4; ++n)
+                red[slot(q, wave) + n * kWave + lane] = float4_t{acc[n][4 * q], acc[n][4 * q + 1], acc[n][4 * q + 2], acc[n][4 * q + 3]};
+    __syncthreads();
+    float4_t sum[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+        if (q == wave)
+#pragma unroll
+            for (int n = 0; n < 4; ++n) sum[n] = float4_t{acc[n][4 * q], acc[n][4 * q + 1], acc[n][4 * q + 2], acc[n][4 * q + 3]};
+#pragma unroll
+    for (int w = 0; w < 4; ++w)
+        if (w != wave)
+#pragma unroll
+            for (int n = 0; n < 4; ++n) sum[n] += red[slot(wave, w) + n * kWave + lane];
+    // lane: rows 2 r + p, columns 16 wave + 8 h + 4 f .. + 3
+    const FactorPlaces at(a.nb);
+    const uint32_t to = at.P + (uint32_t)(z * a.tiles + tile) * (kTileFloats * 4);
+#pragma unroll
+    for (int p = 0; p < 2; ++p)
+#pragma unroll
+        for (int f = 0; f < 2; ++f) {
+            const float4_t v = {sum[2 * p][2 * f], sum[2 * p + 1][2 * f], sum[2 * p][2 * f + 1], sum[2 * p + 1][2 * f + 1]};
+            const int row = 2 * r + p, col = 16 * wave + 8 * h + 4 * f;
+            store_dev(ws, to + 4u * (uint32_t)op_at(row, col), v);
+            if (i == j && row / 4 == col / 4) {  // (this lane's entry of the diagonal)
+                const float d = (row & 2) ? ((row & 1) ? v[3] : v[2]) : ((row & 1) ? v[1] : v[0]);
+                __hip_atomic_store(a.ws + at.diag / 4 + (size_t)z * a.nb * kOb + kOb * i + row, d, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+        }
+    asm volatile("s_waitcnt vmcnt(0)" : : : "memory");
+    __syncthreads();
+    if (threadIdx.x == 0) __hip_atomic_store(a.hand + kHandGram + tile * a.splits + z, a.seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// a b^T of 16 x 16 blocks in operand order, added to c in the same order
+__device__ __forceinline__ void mul16(float4_t a, float4_t b, float4_t &c) { mma16(b, a, c); }
+
+// Blocks (q, w) .. (q, w + N - 1) of a tile, lane by lane: the sums of its partial tiles.
+template <int N>
+__device__ __forceinline__ void gram_blocks(const FactorArgs &a, rsrc_t ws, int tile, int q, int w, int lane, float4_t (&s)[N])
+{
+    constexpr int U = N > 1 ? 4 : 8;            // shares in flight
+    const uint32_t from = FactorPlaces(a.nb).P + (uint32_t)tile * (kTileFloats * 4) + (uint32_t)((q * 4 + w) * 64 + lane) * 16u;
+    const uint32_t step = (uint32_t)a.tiles * (kTileFloats * 4);
+#pragma unroll
+    for (int n = 0; n < N; ++n) s[n] = float4_t{0.f, 0.f, 0.f, 0.f};
+    for (int z = 0; z < a.splits; z += U) {
+        float4_t v[U][N];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int n = 0; n < N; ++n) v[u][n] = load_dev(ws, z + u < a.splits ? from + (uint32_t)(z + u) * step + 1024u * n : 0xFFFFFFF0u);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int n = 0; n < N; ++n) s[n] += v[u][n];
+    }
+}
+
+// Strips g, g + strips, ... in the order (column, row tile, strip): wavefront w makes the 16 columns 16 w .. of 16 rows of the tile (I, j).
+// It adds up the partial tiles, subtracts L_IK L_jK^T for the columns K before its own as they come, and hands the strip to the chain or waits
+// for the inverse of the diagonal tile and hands on L_Ij = A_Ij X_j^T.
+__device__ __forceinline__ void strip_role(const FactorArgs &a, int g, rsrc_t ws, rsrc_t hand, float4_t *sh)
+{
+    const int lane = threadIdx.x & 63, mq = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const FactorPlaces at(a.nb);
+    auto block = [&](uint32_t region, int tile, int q, int t) { return region + (uint32_t)tile * (kTileFloats * 4) + (uint32_t)((q * 4 + t) * 64 + lane) * 16u; };
+    bool lost = false;
+    for (int task = 4 + g; task < 4 * a.tiles; task += a.strips) {
+        int j = 0, left = task >> 2;
+        while (left >= a.nb - j) left -= a.nb - j++;
+        const int I = j + left, q = task & 3;
+        wait_gram(a, hand, a.splits, lane, lost, [&](int i) { return tri(I, j) * a.splits + i; });
+        float4_t sum[1], s0 = {0.f, 0.f, 0.f, 0.f}, s1 = s0;
+        gram_blocks(a, ws, tri(I, j), q, wave, lane, sum);
+        float4_t c = sum[0];
+        for (int K = 0; K < (I == j ? j - 1 : j); ++K) {
+            wait_words(a, hand, lane == 0 ? kHandL + 16 * tri(I, K) + 4 * q : lane == 1 ? kHandL + 16 * tri(j, K) + 4 * wave : -1, lost);
+            float4_t x[4], y[4];
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                x[t] = load_dev(ws, block(at.Lf, tri(I, K), q, t));
+                y[t] = load_dev(ws, block(at.Lf, tri(j, K), wave, t));
+            }
+#pragma unroll
+            for (int t = 0; t < 4; ++t) mul16(x[t], y[t], t & 1 ? s1 : s0);
+        }
+        c -= s0 + s1;
+        if (I <= j + 1) {
+            store_dev(ws, block(at.G, tri(I, j), q, wave), c);
+            hand_over(a, (I == j ? kHandT : kHandA) + 16 * I + 4 * q + wave, lane);
+            if (I == j) continue;
+        }
+        sh[wave * 64 + lane] = c;
+        __syncthreads();
+        wait_words(a, hand, lane == 0 ? kHandD + 16 * j : -1, lost);
+        float4_t x[4];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) x[t] = t <= wave ? load_dev(ws, block(at.D, j, wave, t)) : float4_t{0.f, 0.f, 0.f, 0.f};
+        const float4_t alive = load_dev(ws, at.D + (uint32_t)j * (kTileFloats * 4) + 1024u + (uint32_t)(16 * wave + 4 * mq) * 4u);
+        float4_t y0 = {0.f, 0.f, 0.f, 0.f}, y1 = y0;
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+            if (t <= wave) mul16(sh[t * 64 + lane], x[t], t & 1 ? y1 : y0);
+        float4_t y = y0 + y1;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) y[e] = alive[e] != 0.f ? y[e] : 0.f;
+        store_dev(ws, block(at.Lf, tri(I, j), q, wave), y);
+        hand_over(a, kHandL + 16 * tri(I, j) + 4 * q + wave, lane);
+        __syncthreads();                         // sh has been read
+    }
+}
+
+// LDS of the chain, in 16 x 16 blocks in operand order.
+struct ChainLds {
+    float4_t T[10][64];                          // the diagonal tile, block (i, k) at tri(i, k), as far as it is worked on
+    float4_t L[6][64];                           // its factor, below the diagonal: (i, k) at tri(i - 1, k)
+    float4_t X0[2][64];                          // its inverse: block (0, 0), of this tile and of the one before it,
+    float4_t X[9][64];                           //   and the others, (i, k) at tri(i, k) - 1
+    float4_t XT[6][64];                          // the blocks (i, k) of the inverse, i < 3, transposed
+    float4_t P[16][64];                          // the panel between the tile before and this one
+    float4_t next[3][64];                        // for wavefront 0, of the next tile: block (0, 0), and (0, 0) and (0, 1) of the tile to its left;
+    int have;                                    //   whether they are there
+    float alive[2][kOb];                         // whether a pivot is above the floor: of this tile, of the one before it
+    float mx[4];
+};
+
+// The diagonal tiles.  Wavefront 0 factors blocks of 16; wavefront w > 0 owns row w of the blocks of a tile and brings it up to date
+// meanwhile, one step behind.  What wavefront 0 needs next it works out itself, the others in registers of their own again: barriers
+// are only between the steps.  A tile is 7.3 us: 0.9 to factor each of its four blocks and 0.2 to 0.4 around that, 1.4 for the panel between the tile
+// before and this one, 0.6 to end the inverse, and, about as long on the whole, what passes between the inverse of a tile and what
+// the tile after next needs of the strips (two hand-overs of 2.5 us): both would have to be shorter.
+__device__ __forceinline__ void chain_role(const FactorArgs &a, rsrc_t ws, rsrc_t hand, ChainLds &s)
+{
     const int tid = threadIdx.x, lane = tid & 63, ln = lane & 15, mq = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    int j = 0, left = (int)blockIdx.x;           // the tile's column
-    while (left >= nb - j) left -= nb - j++;
-    const int I = j + left;
-    if (tid == 0) missing = 0;
-    // (words in turn: wavefront w waits for the w-th; the barrier makes it the workgroup's)
-    auto wait_for = [&](int first, int second) {
-        if (lane == 0 && wave < 2 && !missing && !hand_taken(hand, wave == 0 ? first : second, seq, polls)) {
-            missing = 1;                         // (and the waits after this one are none)
-            __hip_atomic_store(hand + kHandFailed * kHandStride, seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
-        __syncthreads();
-    };
-    float4_t *const T4 = reinterpret_cast<float4_t *>(T);
-    {
-        const float4_t *p = reinterpret_cast<const float4_t *>(P + (size_t)tri(I, j) * kTileFloats);
-        float4_t s[4] = {};
-#pragma unroll 4
-        for (int z = 0; z < splits; ++z)
-#pragma unroll
-            for (int q = 0; q < 4; ++q) s[q] += p[(size_t)z * tiles * (kTileFloats / 4) + tid + 256 * q];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) T4[tid + 256 * q] = s[q];
-    }
-    __syncthreads();
-    // 16 rows of the tile per wavefront
-    auto subtract = [&](const float4_t (&a)[4], const float4_t *b) {
-#pragma unroll
-        for (int cb = 0; cb < 4; ++cb) {
-            float4_t c = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int t = 0; t < 4; ++t) mma16(a[t], b[(cb * 4 + t) * 64 + lane], c);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) T[op_at(16 * wave + 4 * mq + e, 16 * cb + ln)] -= c[e];
-        }
-    };
-    // to = a d^T
-    auto panel = [&](const float4_t (&a)[4], const float4_t *d, float *to) {
-#pragma unroll
-        for (int cb = 0; cb < 4; ++cb) {
-            float4_t c = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int t = 0; t < 4; ++t) mma16(a[t], d[(cb * 4 + t) * 64 + lane], c);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) to[op_at(16 * wave + 4 * mq + e, 16 * cb + ln)] = c[e];
-        }
-    };
-    auto rows_of = [&](const float *tile, float4_t (&a)[4]) {
-#pragma unroll
-        for (int t = 0; t < 4; ++t) a[t] = reinterpret_cast<const float4_t *>(tile)[(wave * 4 + t) * 64 + lane];
-    };
-    auto store_tile = [&](float *to, const float *tile) {
-#pragma unroll
-        for (int q = 0; q < 4; ++q) reinterpret_cast<float4_t *>(to)[tid + 256 * q] = reinterpret_cast<const float4_t *>(tile)[tid + 256 * q];
-    };
-    float4_t a[4];
-    if (blockIdx.x > 0) {
-        for (int K = 0; K < (I == j ? j - 1 : j); ++K) {
-            wait_for(kHandL + tri(I, K), kHandL + tri(j, K));
-            rows_of(Lf + (size_t)tri(I, K) * kTileFloats, a);
-            subtract(a, reinterpret_cast<const float4_t *>(Lf + (size_t)tri(j, K) * kTileFloats));
-        }
-        __syncthreads();
-        if (I <= j + 1) {
-            store_tile(G + (size_t)tri(I, j) * kTileFloats, T);
-            hand_over(hand, (I == j ? kHandT : kHandA) + I, seq);
-            if (I == j) return;
-        }
-        wait_for(kHandD + j, kHandD + j);
-        rows_of(T, a);
-        panel(a, reinterpret_cast<const float4_t *>(Dp + (size_t)j * kTileFloats), LI);
-        __syncthreads();
-        store_tile(Lf + (size_t)tri(I, j) * kTileFloats, LI);
-        hand_over(hand, kHandL + tri(I, j), seq);
-        return;
-    }
-
-    // ---- the diagonal tiles ----
+    const FactorPlaces at(a.nb);
+    auto block = [&](uint32_t region, int tile, int q, int t) { return region + (uint32_t)tile * (kTileFloats * 4) + (uint32_t)((q * 4 + t) * 64 + lane) * 16u; };
+    const float4_t zero = {0.f, 0.f, 0.f, 0.f};
+    bool lost = false;
+    // row `wave` of the first tile
+    float4_t to[3], td;                          // blocks (wave, k), k < wave, and (wave, wave)
+    wait_gram(a, hand, a.nb * a.splits, lane, lost, [&](int i) { return tri(i / a.splits, i / a.splits) * a.splits + i % a.splits; });
     float mx = 0.f;                              // the largest diagonal entry of G
-    for (int c = tid; c < l; c += 256) {
-        float s = 0.f;
+    for (int c = 4 * tid; c < a.nb * kOb; c += 4 * 256) {
+        float4_t d = zero;
 #pragma unroll 8
-        for (int z = 0; z < splits; ++z) s += P[((size_t)z * tiles + tri(c / kOb, c / kOb)) * kTileFloats + op_at(c % kOb, c % kOb)];
-        mx = fmaxf(mx, s);
+        for (int z = 0; z < a.splits; ++z) d += load_dev(ws, at.diag + (uint32_t)(z * a.nb * kOb + c) * 4u);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) mx = fmaxf(mx, d[e]);
+    }
+    {
+        float4_t row[4];
+        gram_blocks(a, ws, 0, wave, 0, lane, row);
+#pragma unroll
+        for (int k = 0; k < 3; ++k) to[k] = row[k];
+        td = wave == 0 ? row[0] : wave == 1 ? row[1] : wave == 2 ? row[2] : row[3];
     }
     mx = wave_max(mx);
-    if (lane == 0) mx_s[wave] = mx;
+    if (lane == 0) s.mx[wave] = mx;
     __syncthreads();
-    mx = fmaxf(fmaxf(mx_s[0], mx_s[1]), fmaxf(mx_s[2], mx_s[3]));
+    mx = fmaxf(fmaxf(s.mx[0], s.mx[1]), fmaxf(s.mx[2], s.mx[3]));
     // Far from 1 the block is factored as 4^h G (exact): the reciprocals of factor16() know no subnormal numbers
     int h = 0;
     if (mx > 0.f && !(mx > 0x1p-60f && mx < 0x1p60f)) h = min(max(-(__builtin_amdgcn_frexp_expf(mx) / 2), -63), 63);
-    const float dead = ldexpf(fmaxf(1.0f, mx * 1e-9f), 2 * h), floor_ = ldexpf(mx, 2 * h) * 1e-9f;
+    const float dead = ldexpf(fmaxf(1.0f, mx * 1e-9f), 2 * h), floor_ = fmaxf(ldexpf(mx, 2 * h) * 1e-9f, 0x1p-120f);
     float pmax = 0.f, pmin = __builtin_inff();   // (of the rows of a lane of wavefront 0)
-    float *const X = LI;                         // the inverse, and
-    float *const XT = LJ;                        // the inverse transposed: block (c, r) holds block (r, c) of X
-    auto block = [](float *base, int bi, int bj) { return base + (bi * 4 + bj) * 256; };
-    auto operand = [&](const float *blk) { return reinterpret_cast<const float4_t *>(blk)[lane]; };
-    __shared__ __attribute__((aligned(16))) float M[3][256];
-    __shared__ int alive[kOb];                   // pivot above the floor
-    for (j = 0; j < nb; ++j) {
+    auto scaled = [&](float4_t v, int by) {
+        if (h != 0)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] = ldexpf(v[e], by);
+        return v;
+    };
+    // columns of dead pivots as zeros (lane: columns 4 mq .. of block k)
+    auto living = [&](float4_t v, int which, int k) {
+        const float4_t f = reinterpret_cast<const float4_t *>(s.alive[which])[4 * k + mq];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = f[e] != 0.f ? v[e] : 0.f;
+        return v;
+    };
+    // what tile j needs: row `wave` of it, rows 0 (the blocks up to `wave`) and `wave` of the tile to its left; wavefront 1 looks out for
+    // wavefront 0 too
+    float4_t a0[4], aw[4], t00 = zero;
+    bool there = false;
+    auto words_of = [&](int j) {
+        const int t = kHandT + 16 * j, l = kHandA + 16 * j;
+        return lane == 0 ? t + 4 * wave : lane == 1 ? l : lane == 2 ? l + 4 * wave : lane == 3 && wave == 1 ? t : -1;
+    };
+    auto load_tile = [&](int j) {
+#pragma unroll
+        for (int t = 0; t < 4; ++t) a0[t] = wave < 3 && (t < 2 || wave > 0) ? load_dev(ws, block(at.G, tri(j, j - 1), 0, t)) : zero;
+#pragma unroll
+        for (int t = 0; t < 4; ++t) aw[t] = wave > 0 ? load_dev(ws, block(at.G, tri(j, j - 1), wave, t)) : zero;
+#pragma unroll
+        for (int k = 0; k < 3; ++k) to[k] = k < wave ? load_dev(ws, block(at.G, tri(j, j), wave, k)) : zero;
+        td = load_dev(ws, block(at.G, tri(j, j), wave, wave));
+        if (wave == 1) t00 = load_dev(ws, block(at.G, tri(j, j), 0, 0));
+    };
+    for (int j = 0; j < a.nb; ++j) {
+        const int cur = j & 1, prev = cur ^ 1;
+        auto X = [&](int which, int i, int k) { return i == 0 ? s.X0[which][lane] : s.X[tri(i, k) - 1][lane]; };
+        float4_t pw[4] = {zero, zero, zero, zero};       // row `wave` of the panel
+        float4_t p0, p1;
+        auto panel_diagonal = [&] {
+            p0 = p1 = zero;
+#pragma unroll
+            for (int t = 0; t < 4; ++t) mul16(pw[t], pw[t], t & 1 ? p1 : p0);
+            td -= p0 + p1;
+        };
         if (j > 0) {
-            wait_for(kHandT + j, kHandA + j);
-            rows_of(G + (size_t)tri(j, j - 1) * kTileFloats, a);
-            store_tile(T, G + (size_t)tri(j, j) * kTileFloats);
-            panel(a, reinterpret_cast<const float4_t *>(X), XT);
-            __syncthreads();
-            rows_of(XT, a);
-            subtract(a, reinterpret_cast<const float4_t *>(XT));
-            __syncthreads();
-        }
-        if (h != 0)                                  // (a thread's own pieces)
+            if (wave == 0 && s.have) {
+                td = s.next[0][lane];
+                a0[0] = s.next[1][lane];
+                a0[1] = s.next[2][lane];
+            } else if (!there) {
+                wait_words(a, hand, words_of(j), lost);
+                load_tile(j);
+            }
+            // block (0, wave) of the panel
+            // (wavefront 3 is busy handing over)
+            auto panel_block = [&](int c) {
+                p0 = p1 = zero;
 #pragma unroll
-            for (int q = 0; q < 4; ++q)
-#pragma unroll
-                for (int e = 0; e < 4; ++e) T[4 * (tid + 256 * q) + e] = ldexpf(T[4 * (tid + 256 * q) + e], 2 * h);
-        for (int idx = tid; idx < kTileFloats; idx += 256) X[idx] = 0.f;
-        __syncthreads();
-        for (int b = 0; b < 4; ++b) {
+                for (int t = 0; t < 4; ++t)
+                    if (t <= c) mul16(scaled(a0[t], 2 * h), X(prev, c, t), t & 1 ? p1 : p0);
+                s.P[c][lane] = living(p0 + p1, prev, c);
+            };
             if (wave == 0) {
-                float4_t w = operand(block(T, b, b));
-                const bool ok = factor16(w, ln, mq, floor_, dead, pmax, pmin);
-                if (lane < 16) alive[16 * b + ln] = ok;
-                reinterpret_cast<float4_t *>(block(X, b, b))[lane] = w;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) block(XT, b, b)[(ln >> 2) * 64 + (4 * mq + e) * 4 + (ln & 3)] = w[e];
+                panel_block(0);
+                panel_block(1);
+            } else if (wave < 3) {
+                panel_block(wave == 1 ? 3 : 2);
             }
             __syncthreads();
-            // panel: block rows b + 1 .. 3, one per wavefront
-            if (wave > b) {
-                float4_t c = {0.f, 0.f, 0.f, 0.f};
-                mma16(operand(block(T, wave, b)), operand(block(X, b, b)), c);
+            td = scaled(td, 2 * h);
+            if (wave > 0) {
 #pragma unroll
-                for (int e = 0; e < 4; ++e) block(T, wave, b)[(ln >> 2) * 64 + (4 * mq + e) * 4 + (ln & 3)] = alive[16 * b + ln] ? c[e] : 0.f;
-            }
-            __syncthreads();
-            if (wave > b) {
-                const float4_t a = operand(block(T, wave, b));
-                for (int k = b + 1; k <= wave; ++k) {
-                    float4_t c = {0.f, 0.f, 0.f, 0.f};
-                    mma16(a, operand(block(T, k, b)), c);
+                for (int t = 0; t < 4; ++t) aw[t] = scaled(aw[t], 2 * h);
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) block(T, wave, k)[(ln >> 2) * 64 + (4 * mq + e) * 4 + (ln & 3)] -= c[e];
+                for (int c = 0; c < 4; ++c) {
+                    p0 = p1 = zero;
+#pragma unroll
+                    for (int t = 0; t <= c; ++t) mul16(aw[t], X(prev, c, t), t & 1 ? p1 : p0);
+                    pw[c] = living(p0 + p1, prev, c);
+                    s.P[4 * wave + c][lane] = pw[c];
                 }
+                p0 = p1 = zero;
+#pragma unroll
+                for (int t = 0; t < 4; ++t) mul16(pw[t], s.P[t][lane], t & 1 ? p1 : p0);
+                to[0] = scaled(to[0], 2 * h) - (p0 + p1);
+                if (wave == 1) panel_diagonal();         // (the others' have time until the next step)
+            } else {
+                p0 = p1 = zero;
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    const float4_t p = s.P[t][lane];
+                    mul16(p, p, t & 1 ? p1 : p0);
+                }
+                td -= p0 + p1;
+            }
+        } else {
+            to[0] = scaled(to[0], 2 * h);
+            td = scaled(td, 2 * h);
+        }
+        // (the columns between are brought up to date when their turn comes)
+        to[1] = scaled(to[1], 2 * h);
+        to[2] = scaled(to[2], 2 * h);
+        if (wave > 0) {
+            s.T[tri(wave, 0)][lane] = to[0];
+            if (wave == 1) s.T[tri(1, 1)][lane] = td;
+        }
+        // wavefront 0: block (b, b)
+        auto factor = [&](int b, float4_t w) {
+            const bool ok = factor16(w, ln, mq, floor_, dead, pmax, pmin);
+            if (lane < 16) s.alive[cur][16 * b + ln] = ok ? 1.f : 0.f;
+            if (b == 0)
+                s.X0[cur][lane] = w;
+            else
+                s.X[tri(b, b) - 1][lane] = w;
+            if (b < 3) {
+                float *const xt = reinterpret_cast<float *>(s.XT[tri(b, b)]);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) xt[(ln >> 2) * 64 + (4 * mq + e) * 4 + (ln & 3)] = w[e];
+            }
+        };
+        // block (i, k) of the inverse, -X_ii sum_{k <= m < i} L_im X_mk
+        auto inverse = [&](int i, int k) {
+            float4_t m0 = zero, m1 = zero, y = zero;
+            for (int m = k; m < i; ++m) mul16(s.XT[tri(m, k)][lane], s.L[tri(i - 1, m)][lane], (m - k) & 1 ? m1 : m0);
+            m0 += m1;                            // transposed
+            const float4_t x = X(cur, i, i);
+            mul16(x, m0, y);
+            s.X[tri(i, k) - 1][lane] = -y;
+            if (i < 3) {
+                y = zero;
+                mul16(m0, x, y);
+                s.XT[tri(i, k)][lane] = -y;
+            }
+        };
+        if (wave == 0) factor(0, td);
+        __syncthreads();
+        there = false;
+        for_each<3>([&](auto bc) {
+            constexpr int b = bc + 1;
+            if constexpr (b == 3)
+                if (wave > 0 && j + 1 < a.nb) {
+                    // what the next tile needs, if it is ready: (the registers of this one are free)
+                    there = words_there(a, hand, words_of(j + 1)) || words_there(a, hand, words_of(j + 1));
+                    if (there) load_tile(j + 1);
+                }
+            if (wave == 0 || wave >= b) {
+                const float4_t x = X(cur, b - 1, b - 1);
+                float4_t lb = zero;
+                if (wave != b) {
+                    mul16(s.T[tri(b, b - 1)][lane], x, lb);
+                    lb = living(lb, cur, b - 1);
+                }
+                if (wave == 0) {
+                    float4_t c = zero;
+                    mul16(lb, lb, c);
+                    factor(b, s.T[tri(b, b)][lane] - c);
+                } else {
+                    float4_t lw = zero, c = zero;
+                    mul16(s.T[tri(wave, b - 1)][lane], x, lw);
+                    lw = living(lw, cur, b - 1);
+                    s.L[tri(wave - 1, b - 1)][lane] = lw;
+                    if (wave > b) {
+                        if (b == 1) panel_diagonal();
+                        mul16(lw, lw, c);
+                        td -= c;
+                        s.T[tri(wave, wave)][lane] = td;
+                        if constexpr (b < 3) {
+                            // column b of this row
+                            float4_t c0 = zero, c1 = zero;
+                            if (j > 0)
+#pragma unroll
+                                for (int t = 0; t < 4; ++t) mul16(pw[t], s.P[4 * b + t][lane], t & 1 ? c1 : c0);
+                            for (int k = 0; k < b - 1; ++k) mul16(s.L[tri(wave - 1, k)][lane], s.L[tri(b - 1, k)][lane], c0);
+                            mul16(lw, lb, c1);
+                            s.T[tri(wave, b)][lane] = to[b] - (c0 + c1);
+                        }
+                    }
+                }
+            } else if (b == 2) {
+                inverse(1, 0);                   // (wavefront 1)
+            } else if (b == 3) {
+                inverse(2, wave == 1 ? 1 : 0);   // (wavefronts 1 and 2)
             }
             __syncthreads();
-        }
-        // the inverse below its diagonal blocks: X_ij = -X_ii sum_{j <= k < i} L_ik X_kj, block row after block row
-        for (int i = 1; i < 4; ++i) {
-            if (wave < i) {
-                float4_t c = {0.f, 0.f, 0.f, 0.f};
-                for (int k = wave; k < i; ++k) mma16(operand(block(T, i, k)), operand(block(XT, wave, k)), c);
-                reinterpret_cast<float4_t *>(M[wave])[mq * 16 + ln] = c;          // transposed: operand order of its columns
-                asm volatile("s_waitcnt lgkmcnt(0)" : : : "memory");
-                float4_t y = {0.f, 0.f, 0.f, 0.f};
-                mma16(operand(block(X, i, i)), operand(M[wave]), y);
-                reinterpret_cast<float4_t *>(block(XT, wave, i))[mq * 16 + ln] = -y;
+        });
+        const uint32_t out = at.D + (uint32_t)j * (kTileFloats * 4);
+        auto publish = [&](int i) {
 #pragma unroll
-                for (int e = 0; e < 4; ++e) block(X, i, wave)[(ln >> 2) * 64 + (4 * mq + e) * 4 + (ln & 3)] = -y[e];
+            for (int k = 0; k < 4; ++k)
+                if (k <= i) store_dev(ws, out + (uint32_t)((i * 4 + k) * 64 + lane) * 16u, scaled(X(cur, i, k), h));
+        };
+        if (wave < 3) {
+            inverse(3, wave);
+        } else {
+            publish(0);
+            publish(1);
+            publish(2);
+        }
+        if (wave == 1) {
+            if (there) {
+                s.next[0][lane] = t00;
+                s.next[1][lane] = a0[0];
+                s.next[2][lane] = a0[1];
             }
-            __syncthreads();
+            if (lane == 0) s.have = there;
         }
-        // both forms to memory; the second stays in X
-        float4_t *const out = reinterpret_cast<float4_t *>(D + (size_t)j * kTileFloats);
-        float4_t *const outp = reinterpret_cast<float4_t *>(Dp + (size_t)j * kTileFloats);
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {            // (piece tid + 256 q is of row 16 q + tid % 16)
-            float4_t v = reinterpret_cast<const float4_t *>(X)[tid + 256 * q];
-            if (h != 0)
-#pragma unroll
-                for (int e = 0; e < 4; ++e) v[e] = ldexpf(v[e], h);
-            out[tid + 256 * q] = v;
-            if (!alive[16 * q + (tid & 15)]) v = float4_t{0.f, 0.f, 0.f, 0.f};
-            outp[tid + 256 * q] = v;
-            reinterpret_cast<float4_t *>(X)[tid + 256 * q] = v;
+        __syncthreads();
+        // the rest of the inverse to memory, and the living pivots
+        if (wave == 3) {
+            publish(3);
+            if (lane < 16) store_dev(ws, out + 1024u + (uint32_t)lane * 16u, reinterpret_cast<const float4_t *>(s.alive[cur])[lane]);
+            hand_over<4>(a, kHandD + 16 * j, lane);
         }
-        if (j + 1 < nb) hand_over(hand, kHandD + j, seq);
     }
     if (wave != 0) return;
     pmax = wave_max(pmax);
     pmin = -wave_max(-pmin);
     if (tid == 0) {
-        const int run = orth_run(step.in ? step.in->run : 0, step.h, pmax, pmin);
-        step.out->run = run;
-        step.out->due = orth_due(step.h, run, step.last);
+        const int run = orth_run(a.step.in ? a.step.in->run : 0, a.step.h, pmax, pmin);
+        a.step.out->run = run;
+        a.step.out->due = orth_due(a.step.h, run, a.step.last);
     }
+}
+
+__global__ __launch_bounds__(256, 2) void lora_factor_kernel(FactorArgs a)
+{
+    if (a.step.skip()) return;
+    __shared__ __attribute__((aligned(16))) ChainLds s;
+    static_assert(sizeof(ChainLds) >= 12 * 4 * kWave * 16, "LDS of a gram unit");
+    const rsrc_t ws = make_rsrc(a.ws, FactorPlaces(a.nb).end), hand = make_rsrc(a.hand, kHandWords * 4u);
+    const int units = a.tiles * a.splits, b = (int)blockIdx.x;
+    if (b < units)
+        gram_unit(a, b / a.splits, b % a.splits, ws, reinterpret_cast<float4_t *>(&s));       // (a range of rows on one die, where their number is a multiple of 8)
+    else if (b == units)
+        chain_role(a, ws, hand, s);
+    else
+        strip_role(a, b - units - 1, ws, hand, s.P[0]);
 }
 
 // The power of two that brings a column whose largest magnitude has the bits `max_bits` below 1.
@@ -553,7 +846,7 @@ __global__ __launch_bounds__(256) void lora_apply_kernel(const float *__restrict
         }
         return;
     }
-    const float poison = hand[kHandFailed * kHandStride] == seq ? __builtin_nanf("") : 0.f;      // the factor is not whole: must not pass for one
+    const float poison = hand[kHandFailed] == seq ? __builtin_nanf("") : 0.f;      // the factor is not whole: must not pass for one
     // block column J: its part of `in`, the inverse of its diagonal block, the first tile of the factor (the loads of
     // the next column go out before this one's last products)
     float v[4];
@@ -567,7 +860,7 @@ __global__ __launch_bounds__(256) void lora_apply_kernel(const float *__restrict
         }
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
-            d[t] = reinterpret_cast<const float4_t *>(D + (size_t)J * kTileFloats)[(wave * 4 + t) * 64 + lane];
+            d[t] = t <= wave ? reinterpret_cast<const float4_t *>(D + (size_t)J * kTileFloats)[(wave * 4 + t) * 64 + lane] : float4_t{0.f, 0.f, 0.f, 0.f};
             b[t] = reinterpret_cast<const float4_t *>(Lf + (size_t)tri(J, 0) * kTileFloats)[(wave * 4 + t) * 64 + lane];
         }
     };
@@ -618,14 +911,10 @@ __global__ __launch_bounds__(256) void lora_apply_kernel(const float *__restrict
         }
 }
 
-// Workspace of the orth()s of a call, in floats: partial tiles, tiles of G and of the factor, inverses of the diagonal
-// blocks (twice), three sets of OrthWords, two times kColSlots rows of column maxima.
+// Workspace of the orth()s of a call, in floats: what the workgroups of a factorisation hand on, three sets of OrthWords, two times
+// kColSlots rows of column maxima.
 constexpr int kOrthWords = 64;
-size_t orth_floats(int l)
-{
-    const size_t nb = (size_t)(l + kOb - 1) / kOb, t = nb * (nb + 1) / 2;
-    return (kGramTiles + 2 * t + 2 * nb) * kTileFloats + kOrthWords + 2 * (size_t)kColSlots * l;
-}
+size_t orth_floats(int l) { return FactorPlaces((l + kOb - 1) / kOb).end / 4 + kOrthWords + 2 * (size_t)kColSlots * l; }
 unsigned *orth_column_max(float *ws, int l, int which)
 {
     return reinterpret_cast<unsigned *>(ws + orth_floats(l) - (size_t)(2 - which) * kColSlots * l);
@@ -636,30 +925,41 @@ unsigned *orth_column_max(float *ws, int l, int which)
 // orthonormal for h = 0, conditional from then on, where orth_column_max(h % 2) holds the column maxima of `in`; that of
 // the next block is cleared.
 // hand: orth_hand_words() words, zero at the start of a call's sequence, of which this is number seq (from 1).
-size_t orth_hand_words() { return (size_t)kHandWords * kHandStride; }
+size_t orth_hand_words() { return kHandWords; }
 int launch_orth(const float *in, float *out, half_t *hi, half_t *lo, int rows, int l, float *ws, unsigned *hand, unsigned seq, int h, int last,
                 hipStream_t st)
 {
     const int nb = (l + kOb - 1) / kOb, tiles = tri(nb, 0);
-    float *const P = ws, *const G = P + (size_t)kGramTiles * kTileFloats, *const Lf = G + (size_t)tiles * kTileFloats;
-    float *const D = Lf + (size_t)tiles * kTileFloats, *const Dp = D + (size_t)nb * kTileFloats;
-    OrthWords *const words = reinterpret_cast<OrthWords *>(Dp + (size_t)nb * kTileFloats);
+    const FactorPlaces at(nb);
+    OrthWords *const words = reinterpret_cast<OrthWords *>(ws + at.end / 4);
     static_assert(3 * sizeof(OrthWords) <= kOrthWords * sizeof(float), "words of the orth()s");
     const OrthStep step{h > 0 ? words + (h & 1) : nullptr, h < 0 ? words + 2 : words + ((h + 1) & 1), h, last};
     const unsigned *const colmax = h > 0 ? orth_column_max(ws, l, h & 1) : nullptr;
     unsigned *const clear = h >= 0 ? orth_column_max(ws, l, (h + 1) & 1) : nullptr;
-    // about two workgroups per compute unit, at least 64 rows each
-    int splits = kGramTiles / tiles;
+    FactorArgs f{};
+    f.Y = in;
+    f.rows = rows;
+    f.l = l;
+    f.nb = nb;
+    f.tiles = tiles;
+    f.ws = ws;
+    f.hand = hand;
+    f.seq = seq;
+    f.step = step;
+    // a workgroup per compute unit, at least 64 rows each
+    int splits = kGramUnits / tiles;
     if (splits > (rows + 63) / 64) splits = (rows + 63) / 64;
-    const int zrows = ((rows + splits - 1) / splits + 31) / 32 * 32;
-    splits = (rows + zrows - 1) / zrows;
-    hipLaunchKernelGGL(lora_gram_kernel, dim3((unsigned)tiles, (unsigned)splits), dim3(256), 0, st, in, rows, l, zrows, tiles, P, step);
+    if (splits > kDies) splits = splits / kDies * kDies;
+    f.zrows = ((rows + splits - 1) / splits + 31) / 32 * 32;
+    f.splits = (rows + f.zrows - 1) / f.zrows;
     const bool wait_test = adapters_wait_test();     // (slim_decode_override: only the workgroup that waits for the others)
-    hipLaunchKernelGGL(lora_chol_kernel, dim3((unsigned)(wait_test ? 1 : tiles)), dim3(256), 0, st, nb, l, (const float *)P, splits, tiles, G, Lf, D, Dp,
-                       hand, seq, wait_test ? 256 : kHandPolls, step);
+    f.strips = wait_test ? 0 : 4 * (tiles - 1) < kStripGroups ? 4 * (tiles - 1) : kStripGroups;
+    f.polls = wait_test ? 256 : kHandPolls;
+    hipLaunchKernelGGL(lora_factor_kernel, dim3((unsigned)(tiles * f.splits + 1 + f.strips)), dim3(256), 0, st, f);
     const size_t lds = (size_t)(16 * (nb * kOb + 4) + 16 * 68) * sizeof(float);
-    hipLaunchKernelGGL(lora_apply_kernel, dim3((unsigned)((rows + 31) / 32 * 2)), dim3(256), lds, st, in, out, rows, l, nb, (const float *)Lf,
-                       (const float *)D, hi, lo, (rows + 31) / 32 * 32, step, colmax, clear, (const unsigned *)hand, seq);
+    hipLaunchKernelGGL(lora_apply_kernel, dim3((unsigned)((rows + 31) / 32 * 2)), dim3(256), lds, st, in, out, rows, l, nb,
+                       (const float *)(ws + at.Lf / 4), (const float *)(ws + at.D / 4), hi, lo, (rows + 31) / 32 * 32, step, colmax, clear,
+                       (const unsigned *)hand, seq);
     return hip_status(hipGetLastError());
 }
 

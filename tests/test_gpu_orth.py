@@ -72,6 +72,13 @@ def test_adapters_of_blocks_of_every_condition(n, k, r, base):
     assert base > 1e4 or diag.cpu()[2] < 1e-4
 
 
+@pytest.mark.parametrize("n,k,r", [(40, 512, 40), (200, 256, 128), (610, 640, 193), (4100, 640, 448), (700, 640, 470), (1100, 1152, 705)])
+def test_factorisations_of_every_number_of_tiles(n, k, r):
+    """One tile and several, as many strips as workgroups for them and more, row counts that divide into none of the ranges:
+    what holds above, after a round whose blocks are all orthonormalised."""
+    test_adapters_are_orthonormal_and_project_the_error(n, k, r, 1)
+
+
 def start_block(rows, cols, r, seed=1):
     """The seeded start block: uniform in (-1, 1) from a hash of (seed, element), cols columns of which r are used."""
     def mix(v):
