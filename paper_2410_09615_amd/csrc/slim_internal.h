@@ -185,6 +185,13 @@ size_t decode_lds_limit();       // 0: the device's LDS; else bytes the one-laun
 // Device address of the library's own scratch array on the current device (slim_gemv.hip).
 int scratch_of_current_device(void **out);
 
+#ifdef __HIPCC__
+// The power of two in a channel's x (at least 2^-126, at most 2^126), and its reciprocal.
+__device__ __forceinline__ uint32_t channel_exponent_bits(float x) { return min(max(__float_as_uint(x) & 0x7F800000u, 0x00800000u), 0x7E800000u); }
+__device__ __forceinline__ float channel_exponent(float x) { return __uint_as_float(channel_exponent_bits(x)); }
+__device__ __forceinline__ float channel_rescale(float x) { return __uint_as_float(0x7F000000u - channel_exponent_bits(x)); }
+#endif
+
 inline bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
 inline int hip_status(hipError_t e) { return e == hipSuccess ? SLIM_OK : SLIM_ERR_HIP; }

@@ -170,7 +170,7 @@ static int sgemm(bool ta, const float *A, int lda, const float *B, int ldb, floa
     int splits = 1;
     if (tm * tn < 512) splits = (512 + tm * tn - 1) / (tm * tn);
     const int kslabs = (K + kGK - 1) / kGK;
-    if (splits > kslabs / 4) splits = kslabs / 4 > 0 ? kslabs / 4 : 1;      // at least 64 k-values per slice
+    if (splits > kslabs / 16) splits = kslabs / 16 > 0 ? kslabs / 16 : 1;   // at least 256 k-values per slice (416 x 416 over 4096: with 64 K_SG us)
     a.kchunk = (kslabs + splits - 1) / splits * kGK;
     splits = (K + a.kchunk - 1) / a.kchunk;
     if (splits > 1) {
@@ -226,11 +226,12 @@ __global__ __launch_bounds__(1024) void lora_shift_kernel(const float *xt, int k
 }
 
 // ---- S = (W - W^C) diag(x); the packed bytes are read in their tiled layout ----
-// One thread per group of four inputs, in turn.  s2: slots of ||S||_F^2, mx_word: bits of the largest magnitude.
+// One thread per group of four inputs, in turn.  s2: slots of ||S||_F^2, mx_words: bits of the largest magnitude, and of the
+// largest with each channel scaled by the power of two of its x (channel_exponent()).
 // HBM-bound (W and S, 8 bytes per weight): 4096 x 4096 27 us (with a 64-bit division per group and every sum added to one word 42).
 __global__ __launch_bounds__(256) void lora_error_kernel(const float *__restrict__ W, const uint8_t *__restrict__ qvals,
                                                          const uint8_t *__restrict__ meta, const float *__restrict__ scale,
-                                                         const float *__restrict__ x, int n, int k, float *__restrict__ S, float *s2, float *mx_word)
+                                                         const float *__restrict__ x, int n, int k, float *__restrict__ S, float *s2, float *mx_words)
 {
     const uint32_t groups = (uint32_t)k / 4, kt = pk_ktiles(k);
     const size_t first = (size_t)blockIdx.x * blockDim.x + threadIdx.x, stride = (size_t)gridDim.x * blockDim.x;
@@ -239,7 +240,7 @@ __global__ __launch_bounds__(256) void lora_error_kernel(const float *__restrict
     uint32_t g = (uint32_t)(first - o * groups);
     const size_t row_step = stride / groups;
     const uint32_t group_step = (uint32_t)(stride - row_step * groups);
-    float part = 0.f, mx = 0.f;
+    float part = 0.f, mx = 0.f, mx_scaled = 0.f;
     while (o < (size_t)n) {
         const uint32_t q = qvals[pk_qoff((uint32_t)o, g, kt)];
         const uint32_t mb = meta[pk_moff((uint32_t)o, g >> 1, kt)];
@@ -256,6 +257,7 @@ __global__ __launch_bounds__(256) void lora_error_kernel(const float *__restrict
             e[i] = (w[i] - wc) * xv[i];
             part += e[i] * e[i];
             mx = fmaxf(mx, fabsf(e[i]));
+            mx_scaled = fmaxf(mx_scaled, fabsf(e[i]) * channel_rescale(xv[i]));
         }
         reinterpret_cast<float4_t *>(S)[o * groups + g] = e;
         o += row_step;
@@ -266,7 +268,9 @@ __global__ __launch_bounds__(256) void lora_error_kernel(const float *__restrict
         }
     }
     block_add(part, s2);
-    block_max(mx, mx_word);
+    block_max(mx, mx_words);
+    __syncthreads();
+    block_max(mx_scaled, mx_words + 1);
 }
 
 // ---- start block: uniform in (-1, 1) from a hash of (seed, element), columns >= r zero ----
@@ -309,9 +313,9 @@ int launch_orth(const float *in, float *out, half_t *hi, half_t *lo, int rows, i
                 hipStream_t st);
 unsigned *orth_column_max(float *ws, int l, int which);
 int split_gemm_splits(int rows, int cols, int K);                                                    // slim_lora_split.hip
-int launch_lora_split(const float *S, int n, int k, const unsigned *max_bits, half_t *Sh, half_t *Sl, half_t *Th, half_t *Tl, hipStream_t st);
-int launch_lora_split_gemm(const half_t *Ah, const half_t *Al, const unsigned *max_bits, const half_t *Bh, const half_t *Bl, int rows, int cols,
-                           int K, float *P, float *Y, unsigned *colmax, hipStream_t st);
+int launch_lora_split(const float *S, const float *x, int n, int k, const unsigned *max_bits, half_t *Sh, half_t *Sl, half_t *Th, half_t *Tl, hipStream_t st);
+int launch_lora_split_gemm(const half_t *Ah, const half_t *Al, const unsigned *max_bits, const float *x, const half_t *Bh, const half_t *Bl, int rows,
+                           int cols, int K, float *P, float *Y, unsigned *colmax, hipStream_t st);
 
 // ---- results: L fp16 [n][r] = Q[:, :r];  R fp16 [r][k] = R~[:r] / x;  r2: slots of ||R~[:r]||_F^2 ----
 __global__ void lora_out_l_kernel(const float *Q, int n, int l, int r, half_t *L)
@@ -323,22 +327,30 @@ __global__ void lora_out_l_kernel(const float *Q, int n, int l, int r, half_t *L
     }
 }
 
-// (blockIdx.y: the row)
-__global__ __launch_bounds__(256) void lora_out_r_kernel(const float *__restrict__ Rt, const float *__restrict__ x, int k, half_t *__restrict__ R,
-                                                         float *r2)
+// Rt: [k][l], R~ transposed.  A workgroup turns 64 channels x 64 columns.
+__global__ __launch_bounds__(256) void lora_out_r_kernel(const float *__restrict__ Rt, const float *__restrict__ x, int k, int l, int r,
+                                                         half_t *__restrict__ R, float *r2)
 {
-    const float4_t *const row = reinterpret_cast<const float4_t *>(Rt + (size_t)blockIdx.y * k);
-    half4_t *const out = reinterpret_cast<half4_t *>(R + (size_t)blockIdx.y * k);
+    __shared__ float t[64][65];
+    const int j0 = blockIdx.x * 64, c0 = blockIdx.y * 64;        // (k is a multiple of 64, l of 32)
     float part = 0.f;
-    for (int j = blockIdx.x * blockDim.x + threadIdx.x; j < k / 4; j += gridDim.x * blockDim.x) {
-        const float4_t v = row[j], xv = reinterpret_cast<const float4_t *>(x)[j];
-        half4_t h;
+    for (int q = threadIdx.x; q < 64 * 16; q += 256) {
+        const int j = q >> 4, c = (q & 15) * 4;
+        float4_t v = {0.f, 0.f, 0.f, 0.f};
+        if (c0 + c < l) v = *reinterpret_cast<const float4_t *>(Rt + (size_t)(j0 + j) * l + c0 + c);
+        const float xj = x[j0 + j];
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            part += v[e] * v[e];
-            h[e] = (half_t)(v[e] / xv[e]);
+            if (c0 + c + e < r) part += v[e] * v[e];
+            t[j][c + e] = v[e] / xj;
         }
-        out[j] = h;
+    }
+    __syncthreads();
+    for (int q = threadIdx.x; q < 64 * 16; q += 256) {
+        const int c = q >> 4, j = (q & 15) * 4;
+        if (c0 + c < r)
+            *reinterpret_cast<half4_t *>(R + (size_t)(c0 + c) * k + j0 + j) =
+                half4_t{(half_t)t[j][c], (half_t)t[j + 1][c], (half_t)t[j + 2][c], (half_t)t[j + 3][c]};
     }
     block_add(part, r2);
 }
@@ -479,7 +491,7 @@ extern "C" int slim_compute_adapters(const float *W, const uint8_t *qvals, const
             Sh[i] = reinterpret_cast<half_t *>(ws + p.half[i]);
             blk[i] = reinterpret_cast<half_t *>(ws + p.blk[i]);
         }
-        SLIM_TRY(launch_lora_split(S, n, k, mx, Sh[0], Sh[1], Sh[2], Sh[3], st));
+        SLIM_TRY(launch_lora_split(S, x, n, k, mx, Sh[0], Sh[1], Sh[2], Sh[3], st));
     }
     hipLaunchKernelGGL(lora_init_kernel, dim3((unsigned)std::min((k + 255) / 256, 1024), (unsigned)l), dim3(256), 0, st, Z, blk[2], blk[3], k, l, r, seed);
     SLIM_TRY(launched());
@@ -487,13 +499,13 @@ extern "C" int slim_compute_adapters(const float *W, const uint8_t *qvals, const
     // (column maxima: for a block that may only be scaled)
     auto colmax = [&](int h) { return h > 0 && h < last ? orth_column_max(O, l, h & 1) : nullptr; };
     auto times_z = [&](int h) {              // Y = S Z     [n][l]
-        return p.split ? launch_lora_split_gemm(Sh[0], Sh[1], mx, blk[2], blk[3], n, l, k, P, Y, colmax(h), st)
+        return p.split ? launch_lora_split_gemm(Sh[0], Sh[1], mx, nullptr, blk[2], blk[3], n, l, k, P, Y, colmax(h), st)
                        : sgemm(false, S, k, Z, l, Y, n, l, k, st);
     };
-    auto times_q = [&](int h) {              // Y = S^T Q   [k][l]
-        return p.split ? launch_lora_split_gemm(Sh[2], Sh[3], mx, blk[0], blk[1], k, l, n32, P, Y, colmax(h), st)
-                       : sgemm(true, S, k, Q, l, Y, k, l, n, st);
+    auto times = [&](const float *q, float *to, unsigned *cm) {          // S^T q     [k][l]
+        return p.split ? launch_lora_split_gemm(Sh[2], Sh[3], mx + 1, x, blk[0], blk[1], k, l, n32, P, to, cm, st) : sgemm(true, S, k, q, l, to, k, l, n, st);
     };
+    auto times_q = [&](int h) { return times(Q, Y, colmax(h)); };        // Y = S^T Q
 
     SLIM_TRY(times_z(0));
     for (int h = 0; h < last; h += 2) {
@@ -503,16 +515,16 @@ extern "C" int slim_compute_adapters(const float *W, const uint8_t *qvals, const
         SLIM_TRY(times_z(h + 2));
     }
     SLIM_TRY(orth(Y, Q, nullptr, nullptr, n, -1, last));
-    SLIM_TRY(orth(Q, Y, nullptr, nullptr, n, -1, last));    // second pass: orthonormal to rounding
-    SLIM_TRY(sgemm(true, Y, l, S, k, Rt, l, k, n, st));          // R~ = Q^T S        [l][k]
+    SLIM_TRY(orth(Q, Y, blk[0], blk[1], n, -1, last));      // second pass: orthonormal to rounding
+    SLIM_TRY(times(Y, Rt, nullptr));         // R~ = Q^T S, transposed
     SLIM_TRY(sgemm(true, Y, l, Y, l, G, l, l, n, st));           // Gram of the final block, for the report
     hipLaunchKernelGGL(lora_ortho_kernel, dim3(std::min(grid_for((size_t)r * r).x, 256u)), dim3(256), 0, st, (const float *)G, l, r, sq);
     SLIM_TRY(launched());
     hipLaunchKernelGGL(lora_out_l_kernel, grid_for((size_t)n * r), dim3(256), 0, st, (const float *)Y, n, l, r,
                        reinterpret_cast<half_t *>(L));
     SLIM_TRY(launched());
-    hipLaunchKernelGGL(lora_out_r_kernel, dim3((unsigned)std::min((k / 4 + 255) / 256, 1024), (unsigned)r), dim3(256), 0, st, (const float *)Rt,
-                       (const float *)x, k, reinterpret_cast<half_t *>(R), r2);
+    hipLaunchKernelGGL(lora_out_r_kernel, dim3((unsigned)(k / 64), (unsigned)((r + 63) / 64)), dim3(256), 0, st, (const float *)Rt, (const float *)x, k, l, r,
+                       reinterpret_cast<half_t *>(R), r2);
     SLIM_TRY(launched());
     if (diag) {
         hipLaunchKernelGGL(lora_report_kernel, dim3(1), dim3(64), 0, st, (const float *)sq, (const float *)s2, diag);

@@ -32,21 +32,21 @@ __device__ __forceinline__ float split_scale(unsigned max_bits)
     return max_bits == 0u ? 1.0f : exp2f((float)min(13 - e, 126));
 }
 
-// S [n][k] -> hi and lo in the adapter layout (tiles of 32 rows x 16 columns), for S (rows n) and S^T (rows k,
-// n padded to 32 columns).  A workgroup moves 64 x 64.
-__global__ __launch_bounds__(256) void lora_split_kernel(const float *__restrict__ S, int n, int k, const unsigned *max_bits,
+// S [n][k] -> hi and lo in the adapter layout (tiles of 32 rows x 16 columns), for S (rows n) and S^T (rows k, each scaled by
+// the power of two of its channel's x; n padded to 32 columns).  max_bits: largest magnitudes of S, and of S so scaled.  A workgroup moves 64 x 64.
+__global__ __launch_bounds__(256) void lora_split_kernel(const float *__restrict__ S, const float *__restrict__ x, int n, int k, const unsigned *max_bits,
                                                          half_t *__restrict__ Sh, half_t *__restrict__ Sl, half_t *__restrict__ Th,
                                                          half_t *__restrict__ Tl)
 {
     __shared__ float t[64][65];
     const int i0 = blockIdx.y * 64, j0 = blockIdx.x * 64, tid = threadIdx.x;
-    const float sc = split_scale(*max_bits);
+    const float sc = split_scale(max_bits[0]), sct = split_scale(max_bits[1]);
     for (int q = tid; q < 64 * 16; q += 256) {
         const int r = q >> 4, c = (q & 15) * 4;
         float4_t v = {0.f, 0.f, 0.f, 0.f};
         if (i0 + r < n) v = *reinterpret_cast<const float4_t *>(S + (size_t)(i0 + r) * k + j0 + c);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) t[r][c + e] = v[e] * sc;
+        for (int e = 0; e < 4; ++e) t[r][c + e] = v[e];
     }
     __syncthreads();
     const int n32 = (n + 31) / 32 * 32;
@@ -72,12 +72,13 @@ __global__ __launch_bounds__(256) void lora_split_kernel(const float *__restrict
         float v[8];
         if (i0 + a < n32) {
 #pragma unroll
-            for (int e = 0; e < 8; ++e) v[e] = t[a][b + e];
+            for (int e = 0; e < 8; ++e) v[e] = t[a][b + e] * sc;
             put(Sh, Sl, piece(i0 + a, (j0 + b) / 8, k), v);
         }
         if (i0 + b < n32) {
+            const float xa = channel_rescale(x[j0 + a]);
 #pragma unroll
-            for (int e = 0; e < 8; ++e) v[e] = t[b + e][a];
+            for (int e = 0; e < 8; ++e) v[e] = t[b + e][a] * xa * sct;
             put(Th, Tl, piece(j0 + a, (i0 + b) / 8, n32), v);
         }
     }
@@ -261,10 +262,11 @@ __global__ __launch_bounds__(256) void lora_split_reduce_kernel(const float4_t *
     }
 }
 
-// The same, a workgroup per 16 rows of cols4 float4s, with the bits of the columns' largest magnitudes, in kColSlots rows of
+// The same, a workgroup per 16 rows of cols4 float4s; x (or null): times the powers of two of the rows' channels; colmax (or null): the
+// bits of the columns' largest magnitudes, in kColSlots rows of
 // 4 cols4 words (zero before), a workgroup's in row blockIdx mod kColSlots.  In one row the adds to a word were 256 in
 // turn, and 22 of 28 us (4096 x 416); now 8.
-__global__ __launch_bounds__(512) void lora_split_reduce_max_kernel(const float4_t *__restrict__ P, int splits, int rows, int cols4,
+__global__ __launch_bounds__(512) void lora_split_reduce_max_kernel(const float4_t *__restrict__ P, const float *__restrict__ x, int splits, int rows, int cols4,
                                                                     float4_t *__restrict__ Y, unsigned *__restrict__ colmax)
 {
     __shared__ uint4_t part[512];
@@ -275,11 +277,12 @@ __global__ __launch_bounds__(512) void lora_split_reduce_max_kernel(const float4
     if (row < rpp)
         for (int r = blockIdx.x * 16 + row; r < end; r += rpp) {
             const size_t i = (size_t)r * cols4 + col;
-            const float4_t s = sum_shares(P, splits, count4, i);
+            const float4_t s = sum_shares(P, splits, count4, i) * (x ? channel_exponent(x[r]) : 1.0f);
             Y[i] = s;
 #pragma unroll
             for (int e = 0; e < 4; ++e) mx[e] = fmaxf(mx[e], fabsf(s[e]));
         }
+    if (!colmax) return;
     part[threadIdx.x] = __builtin_bit_cast(uint4_t, mx);
     __syncthreads();
     if (row == 0) {
@@ -301,26 +304,26 @@ int split_gemm_splits(int rows, int cols, int K)
     return s;
 }
 
-int launch_lora_split(const float *S, int n, int k, const unsigned *max_bits, half_t *Sh, half_t *Sl, half_t *Th, half_t *Tl, hipStream_t st)
+int launch_lora_split(const float *S, const float *x, int n, int k, const unsigned *max_bits, half_t *Sh, half_t *Sl, half_t *Th, half_t *Tl, hipStream_t st)
 {
-    hipLaunchKernelGGL(lora_split_kernel, dim3((unsigned)(k / 64), (unsigned)((n + 63) / 64)), dim3(256), 0, st, S, n, k, max_bits, Sh, Sl, Th, Tl);
+    hipLaunchKernelGGL(lora_split_kernel, dim3((unsigned)(k / 64), (unsigned)((n + 63) / 64)), dim3(256), 0, st, S, x, n, k, max_bits, Sh, Sl, Th, Tl);
     return hip_status(hipGetLastError());
 }
 
-// Y [rows][cols] = A B^T (A scaled by split_scale(*max_bits), B by kBlockSplit); P: split_gemm_splits() x rows x cols floats.
+// Y [rows][cols] = A B^T (A scaled by split_scale(*max_bits), and its rows by the powers of two of x, or null; B by kBlockSplit; cols <= 1024); P: split_gemm_splits() x rows x cols floats.
 // colmax (or null): kColSlots rows of zeros, which become bits of the columns' largest magnitudes (cols <= 1024).
-int launch_lora_split_gemm(const half_t *Ah, const half_t *Al, const unsigned *max_bits, const half_t *Bh, const half_t *Bl, int rows, int cols,
-                           int K, float *P, float *Y, unsigned *colmax, hipStream_t st)
+int launch_lora_split_gemm(const half_t *Ah, const half_t *Al, const unsigned *max_bits, const float *x, const half_t *Bh, const half_t *Bl, int rows,
+                           int cols, int K, float *P, float *Y, unsigned *colmax, hipStream_t st)
 {
     SplitGemmArgs a{Ah, Al, Bh, Bl, max_bits, nullptr, rows, cols, K, 0, (rows + 255) / 256};
     const int splits = split_gemm_splits(rows, cols, K);
-    a.P = splits > 1 || colmax ? P : Y;
+    a.P = splits > 1 || colmax || x ? P : Y;
     a.ks = ((K + 127) / 128 + splits - 1) / splits * 128;
     const size_t lds = (size_t)4 * kSplitStage;
     hipLaunchKernelGGL(lora_split_gemm_kernel, dim3((unsigned)(a.tiles_o * ((cols + 127) / 128)), (unsigned)splits), dim3(256), lds, st, a);
-    if (colmax) {
+    if (colmax || x) {
         hipLaunchKernelGGL(lora_split_reduce_max_kernel, dim3((unsigned)((rows + 15) / 16)), dim3(512), 0, st, reinterpret_cast<const float4_t *>(P),
-                           splits, rows, cols / 4, reinterpret_cast<float4_t *>(Y), colmax);
+                           x, splits, rows, cols / 4, reinterpret_cast<float4_t *>(Y), colmax);
     } else if (splits > 1) {
         const size_t count4 = (size_t)rows * cols / 4;          // cols is a multiple of 32
         const unsigned grid = (unsigned)((count4 + 255) / 256 < 2048 ? (count4 + 255) / 256 : 2048);
