@@ -9,8 +9,8 @@
 // approximation of S (Eckart-Young); how far it is from it after `iters` rounds shows in the
 // captured energy ||Q^T S||_F^2 the call reports.  Orthonormalisation is Cholesky QR in fp32
 // (slim_lora_orth.hip), most of them a scaling of the columns where that loses nothing; the
-// products of the iteration run on the fp16 matrix cores with both operands as two fp16 numbers (slim_lora_split.hip);
-// R~ and what is reported are fp32 products of the fp32 S.
+// products of the iteration, and that for R~, run on the fp16 matrix cores with both operands as two fp16 numbers
+// (slim_lora_split.hip: nearer to the exact product than the fp32 instruction); the Gram matrix of the report is an fp32 product.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -38,7 +38,7 @@ constexpr int kGM = 128, kGN = 128, kGK = 16, kGLd = kGM + 8;      // LDS: a k-v
 // its row, 32 neighbouring words per half of the lanes, four rows apart in different banks (hence the padding), and feeds
 // them to four instructions; A and B use the same assignment of k-values to (lane half, instruction), so the sum is complete.
 // (As [row][k] with one 128-bit read for the four they were stored word by word, eight lanes to a bank: 416 x 4096 over
-// 4096 218 us, now 156; its adds are no part of that: shares side by side instead of one sum took as long.)
+// 4096 218 us, now 156, which the products of slim_lora_split.hip do in 50.)
 template <bool TA>
 __global__ __launch_bounds__(256) void sgemm_kernel(SgemmArgs a)
 {
@@ -170,7 +170,7 @@ static int sgemm(bool ta, const float *A, int lda, const float *B, int ldb, floa
     int splits = 1;
     if (tm * tn < 512) splits = (512 + tm * tn - 1) / (tm * tn);
     const int kslabs = (K + kGK - 1) / kGK;
-    if (splits > kslabs / 16) splits = kslabs / 16 > 0 ? kslabs / 16 : 1;   // at least 256 k-values per slice (416 x 416 over 4096: with 64 K_SG us)
+    if (splits > kslabs / 16) splits = kslabs / 16 > 0 ? kslabs / 16 : 1;   // at least 256 k-values per slice (416 x 416 over 4096: with 64 37 us, now 32)
     a.kchunk = (kslabs + splits - 1) / splits * kGK;
     splits = (K + a.kchunk - 1) / a.kchunk;
     if (splits > 1) {

@@ -2,7 +2,7 @@
 // split into two fp16 numbers, v = (hi + lo) 2^-e, and
 //   S Z = Sh Zh + Sl Zh + Sh Zl     (what is left out, Sl Zl, is 2^-22 of a product)
 // is added up in fp32 by V_MFMA_F32_32X32X16_F16.  hi + lo is v up to 2^-23 of v while lo is a normal number; e is one for all
-// of S (and one for all of a block), so elements of S below 2^-17 of the largest, and of a block below 2^-8, are off by 2^-39 of the
+// of S, one for a channel of S^T and one for all of a block, so elements of S (of a channel of S^T) below 2^-17 of the largest, and of a block below 2^-8, are off by 2^-39 of the
 // largest and by 2^-31 instead.  fp16 products are exact in fp32, and a sum of sixteen of them is rounded less often than
 // with the fp32 instruction, which adds up two at a time, so the result is nearer to the exact one.  Measured against
 // 64 bits (2-norm of the product, largest of a column and of a row, each relative; in brackets the fp32 instruction),
@@ -11,7 +11,7 @@
 //          spanning 1e6, even in the logarithm     2.3e-7 (4.2e-7)   2.6e-7 (5.2e-7)   2.9e-7 (5.5e-7)
 //          5 % of the channels 1e4 above the rest  1.4e-7 (1.4e-7)   2.4e-5 (4.1e-7)   1.8e-7 (1.7e-7)
 //   S^T Q  saliency of calibration inputs          1.2e-7 (3.0e-7)   2.5e-7 (6.8e-7)   2.5e-7 (4.9e-7)
-//          spanning 1e6, even in the logarithm     1.1e-7 (2.9e-7)   2.1e-7 (5.1e-7)   7.0e-6 (7.2e-7)
+//          spanning 1e6, even in the logarithm     1.1e-7 (2.9e-7)   2.0e-7 (5.1e-7)   2.7e-7 (7.2e-7)
 // (The shares of K are added up in 64 bits and rounded once; acc + small is one rounding more per share than one accumulator for
 // all three products, added one after the other, would need: 2.22e-7 with that, 2.21e-7 like this, 2.23e-7 with shares added in fp32.)
 // The columns that lose in the third line are those of directions 1e4 below the leading ones: the error is of the direction of
