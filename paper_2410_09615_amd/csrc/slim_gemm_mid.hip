@@ -7,7 +7,7 @@
 // weights go from memory to LDS without registers, a round of stages at a time and several rounds
 // ahead, and T = X R^T is made by other workgroups of the same launch meanwhile:
 //
-//   T role  (the first workgroups; they wait for nothing) tiles of 16 ranks x 16 tokens, the inputs divided
+//   T role  (the first workgroups; they wait for nothing) tiles of 16 ranks x 16 or 32 tokens, the inputs divided
 //           among the wavefronts and added up in LDS: no partial sums in memory.  T leaves as 16-byte
 //           pieces that carry the number of the call (slim_decode.h), written through to memory.
 //   Y role  a tile of 32 RT RG rows x 32 NT tokens.  Wavefront (rg, kw) of the RG x KW = 8 owns RT row
@@ -36,6 +36,7 @@ int gemm_t_splits(int32_t m, int32_t rank_pad, int32_t k);   // slim_gemm.hip
 typedef int int4_t __attribute__((ext_vector_type(4)));
 typedef int int8v_t __attribute__((ext_vector_type(8)));
 
+enum MidFlags { kAccumulate = 1, kWideT = 2 };      // add to what Y holds; tiles of T are of 32 tokens, not 16
 struct MidArgs {
     const uint8_t *qvals;
     const uint8_t *meta;
@@ -56,7 +57,7 @@ struct MidArgs {
     int t_tiles;          // tiles of T
     int spin_limit;       // polls after which a wait gives up
     int stages;           // stages of 128 inputs of the weight term (0: the adapter term alone)
-    int accumulate;       // add to what Y holds
+    int flags;            // MidFlags (one more word of arguments made a call 0.1 us slower)
 };
 
 constexpr int kMidWaves = 8, kMidHelpers = 4, kMidThreads = (kMidWaves + kMidHelpers) * kWave;
@@ -114,26 +115,28 @@ __device__ __forceinline__ bool tile_on_die(int b, int tiles_o, int &ot, int &tt
 }
 static int die_tiles(int tiles_o, int tiles_t) { return (tiles_o + kDies - 1) / kDies * kDies * tiles_t; }
 
-// T tile of 16 ranks x 16 tokens.  A unit is 256 inputs: eight steps of V_MFMA_F32_16X16X32_F16, R from memory
+// T tile of 16 ranks x 16 TT tokens.  A unit is 256 / TT inputs: steps of V_MFMA_F32_16X16X32_F16, R from memory
 // into registers in operand order (runs of 256 bytes), X through LDS: in operand order neighbouring lanes are
 // different tokens, and such a load costs the address unit four times one that reads along the rows.
 // Wavefront w takes the units w, w + 12, ..., with 8 KiB of LDS of its own.
 // Which columns step t multiplies on lane quarter ly is free as long as R and X agree:
 //   fp16 R, fp16 X   32 t + 8 ly + [0, 8)
 //   fp16 R, 8-bit X  64 (t / 2) + 16 ly + 8 (t % 2) + [0, 8): two steps share one 16-byte load of codes
-//   4-bit R          64 ly + 8 t + [0, 8): the 64 columns of a lane are consecutive (32 bytes of codes, one scale)
+//   4-bit R          (64 / TT) ly + 8 t + [0, 8): the columns of a lane are consecutive (16 bytes of codes for four steps, one scale)
 constexpr int kTUnitLds = 8192;
-template <int XF, bool AQ>
+template <int XF, bool AQ, int TT>
 __device__ __forceinline__ void t_tile(const MidArgs &a, int rt, int tt, char *lds_c, unsigned epoch)
 {
-    constexpr int TW = kMidWaves + kMidHelpers;
-    constexpr int ROWB = XF ? 256 : 512, PIECES = ROWB / 16, TPI = 64 / PIECES, NX = 16 / TPI;
-    const int lane = threadIdx.x & (kWave - 1);
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    constexpr int TW = kMidWaves + kMidHelpers, UN = 256 / TT, STEPS = UN / 32;
+    constexpr int ROWB = XF ? UN : 2 * UN, PIECES = ROWB / 16, TPI = 64 / PIECES, NX = 16 * TT / TPI;
+    // (a thread number the compiler knows nothing of: nothing worked out of it stays in registers from one tile to the next)
+    unsigned tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));
+    const int lane = tid & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
     const int lx = lane & 15, ly = lane >> 4;
-    const int units = (a.k + 255) / 256;
+    const int units = (a.k + UN - 1) / UN;
     const uint32_t k = (uint32_t)a.k, xb = XF ? 1u : 2u;
-    const int tok = 16 * tt + lx;
     const rsrc_t x_rs = make_rsrc(a.X, (uint32_t)a.m * k * xb);
     const rsrc_t r_rs = AQ ? make_rsrc(a.Rq, (uint32_t)q4_code_bytes(a.rank, a.k)) : make_rsrc(a.R, (uint32_t)tl_bytes(a.rank_pad, a.k));
     const rsrc_t s_rs = make_rsrc(AQ ? a.Rs : nullptr, AQ ? (uint32_t)q4_scale_bytes(a.rank, a.k) : 0u);
@@ -141,74 +144,89 @@ __device__ __forceinline__ void t_tile(const MidArgs &a, int rt, int tt, char *l
     const uint32_t xl0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)lds_c + (uint32_t)(wave * kTUnitLds);
 
     auto column = [&](int u, int t) -> uint32_t {
-        if (AQ) return 256u * u + 64u * ly + 8u * t;
-        if (XF) return 256u * u + 64u * (t >> 1) + 16u * ly + 8u * (t & 1);
-        return 256u * u + 32u * t + 8u * ly;
+        if (AQ) return (uint32_t)(UN * u) + (uint32_t)(UN / 4) * ly + 8u * t;
+        if (XF) return (uint32_t)(UN * u) + 64u * (t >> 1) + 16u * ly + 8u * (t & 1);
+        return (uint32_t)(UN * u) + 32u * t + 8u * ly;
     };
-    float4_t acc0 = {0.f, 0.f, 0.f, 0.f}, acc1 = acc0;
+    // the pieces of 16 bytes of a token's row of LDS are permuted by the token number (two rows of 128 bytes go round the banks together)
+    auto swz = [](int tok) { return (uint32_t)(ROWB >= 256 ? tok & 15 : (tok >> 1) & 7); };
+    float4_t acc0[TT], acc1[TT];
+#pragma unroll
+    for (int it = 0; it < TT; ++it) acc0[it] = acc1[it] = float4_t{0.f, 0.f, 0.f, 0.f};
     __syncthreads();                            // the tile before this one is done with LDS
     for (int u = wave; u < units; u += TW) {
-        // a token's 256 inputs are one row of LDS, its pieces of 16 bytes permuted by the token number
+        // a token's inputs are one row of LDS
 #pragma unroll
         for (int j = 0; j < NX; ++j) {
             const int tj = TPI * j + lane / PIECES;
-            const uint32_t col = (uint32_t)((lane % PIECES) ^ tj) * (16u / xb);
-            const bool ok = 16 * tt + tj < a.m && 256u * u + col < k;
-            load_to_lds(x_rs, ok ? ((uint32_t)(16 * tt + tj) * k + 256u * u + col) * xb : kPastEnd, 0u, xl0 + (uint32_t)j * 1024u);
+            const uint32_t col = ((uint32_t)(lane % PIECES) ^ swz(tj)) * (16u / xb);
+            const bool ok = 16 * TT * tt + tj < a.m && (uint32_t)(UN * u) + col < k;
+            load_to_lds(x_rs, ok ? ((uint32_t)(16 * TT * tt + tj) * k + (uint32_t)(UN * u) + col) * xb : kPastEnd, 0u, xl0 + (uint32_t)j * 1024u);
         }
-        uint4_t rv[8];
+        uint4_t rv[AQ ? 2 / TT : STEPS];
         half_t sc = (half_t)1.0f;
         if constexpr (AQ) {
             const bool ok = column(u, 0) < k;
-            const uint32_t base = ok ? q4_piece(16u * rt + lx, 4u * u + ly, q4_ctiles(a.k)) : kPastEnd;
-            rv[0] = load16(r_rs, base, 0);
-            rv[1] = load16(r_rs, ok ? base + 16u : kPastEnd, 0);
-            sc = load_half(s_rs, ok ? ((16u * rt + lx) * q4_groups(a.k) + 2u * u + (ly >> 1)) * 2u : kPastEnd, 0);
+            const uint32_t base = ok ? q4_piece(16u * rt + lx, column(u, 0) / 64u, q4_ctiles(a.k)) + (TT == 2 ? 16u * (ly & 1) : 0u) : kPastEnd;
+#pragma unroll
+            for (int t = 0; t < 2 / TT; ++t) rv[t] = load16(r_rs, ok ? base + 16u * t : kPastEnd, 0);
+            sc = load_half(s_rs, ok ? ((16u * rt + lx) * q4_groups(a.k) + column(u, 0) / 128u) * 2u : kPastEnd, 0);
         } else {
 #pragma unroll
-            for (int t = 0; t < 8; ++t) {
+            for (int t = 0; t < STEPS; ++t) {
                 const uint32_t c = column(u, t);
                 rv[t] = load16(r_rs, c < k ? tl_piece(16u * rt + lx, c >> 3, k) : kPastEnd, 0);
             }
         }
         asm volatile("s_waitcnt vmcnt(0)" : : : "memory");
 #pragma unroll
-        for (int t = 0; t < 8; ++t) {
+        for (int t = 0; t < STEPS; ++t) {
             const uint32_t c = column(0, t) * xb;               // byte of the row
-            const uint4_t xv = *reinterpret_cast<const uint4_t *>(xl + lx * ROWB + (((c >> 4) ^ (uint32_t)lx) << 4));
-            half8_t av, bv;
+            half8_t av;
             if constexpr (AQ)
                 av = codes_to_half8(rv[t >> 2][t & 3]) * sc;
             else
                 av = __builtin_bit_cast(half8_t, rv[t]);
-            if constexpr (XF == 0)
-                bv = __builtin_bit_cast(half8_t, xv);
-            else
-                bv = codes8_to_half8<XF>(xv[2 * (t & 1)], xv[2 * (t & 1) + 1]);
-            if (t & 1)
-                acc1 = __builtin_amdgcn_mfma_f32_16x16x32_f16(av, bv, acc1, 0, 0, 0);
-            else
-                acc0 = __builtin_amdgcn_mfma_f32_16x16x32_f16(av, bv, acc0, 0, 0, 0);
+#pragma unroll
+            for (int it = 0; it < TT; ++it) {
+                const uint4_t xv = *reinterpret_cast<const uint4_t *>(xl + (16 * it + lx) * ROWB + (((c >> 4) ^ swz(lx)) << 4));
+                half8_t bv;
+                if constexpr (XF == 0)
+                    bv = __builtin_bit_cast(half8_t, xv);
+                else
+                    bv = codes8_to_half8<XF>(xv[2 * (t & 1)], xv[2 * (t & 1) + 1]);
+                if (t & 1)
+                    acc1[it] = __builtin_amdgcn_mfma_f32_16x16x32_f16(av, bv, acc1[it], 0, 0, 0);
+                else
+                    acc0[it] = __builtin_amdgcn_mfma_f32_16x16x32_f16(av, bv, acc0[it], 0, 0, 0);
+            }
         }
         asm volatile("s_waitcnt lgkmcnt(0)" : : : "memory");     // the row of LDS has been read
     }
-    float *const red = reinterpret_cast<float *>(lds_c);
-    // lane holds token lx, ranks 16 rt + 4 ly .. + 3
-    float4_t acc = acc0 + acc1;
+    float4_t *const red = reinterpret_cast<float4_t *>(lds_c);
+    // wavefront it < TT adds up 16 tokens.  Lane: token lx, ranks 16 rt + 4 ly .. + 3
     __syncthreads();
-    if (wave != 0) *reinterpret_cast<float4_t *>(red + ((wave - 1) * kWave + lane) * 4) = acc;
-    __syncthreads();
-    if (wave == 0) {
 #pragma unroll
-        for (int w = 0; w < kMidWaves + kMidHelpers - 1; ++w) acc += *reinterpret_cast<const float4_t *>(red + (w * kWave + lane) * 4);
+    for (int it = 0; it < TT; ++it)
+        if (wave != it) red[(it * TW + wave) * kWave + lane] = acc0[it] + acc1[it];
+    __syncthreads();
+    if (wave >= TT) return;
+#pragma unroll
+    for (int it = 0; it < TT; ++it) {
+        if (TT > 1 && wave != it) continue;
+        float4_t acc = acc0[it] + acc1[it];
+#pragma unroll
+        for (int w = 0; w < TW; ++w)
+            if (w != it) acc += red[(it * TW + w) * kWave + lane];
         if (XF) acc *= *a.x_scale;
+        const int tok = 16 * (TT * tt + it) + lx;
         const half4_t h = {(half_t)acc[0], (half_t)acc[1], (half_t)acc[2], (half_t)acc[3]};
         if (a.T_rows) {
             if (tok < a.m) *reinterpret_cast<half4_t *>(a.T_rows + (size_t)tok * a.rank_pad + 16 * rt + 4 * ly) = h;
-            return;
+        } else if (TT == 1 || tok < (a.m + 15) / 16 * 16) {
+            store_piece(make_rsrc(a.T, mid_t_bytes<AQ>(a.m, a.rank_pad)), mid_t_piece<AQ>((uint32_t)tok, 16u * rt + 4u * ly, a.rank_pad),
+                        epoch, __builtin_bit_cast(uint2_t, h));
         }
-        store_piece(make_rsrc(a.T, mid_t_bytes<AQ>(a.m, a.rank_pad)), mid_t_piece<AQ>((uint32_t)tok, 16u * rt + 4u * ly, a.rank_pad),
-                    epoch, __builtin_bit_cast(uint2_t, h));
     }
 }
 
@@ -905,7 +923,7 @@ __device__ __forceinline__ bool y_role(const MidArgs &a, int tid, int ot, int tt
                 if (t >= a.m || o >= a.n) continue;
                 half_t *y = a.Y + (size_t)t * a.n + o;
                 if (vec_ok) {
-                    if (a.accumulate) {
+                    if (a.flags & kAccumulate) {
                         const half4_t old = *reinterpret_cast<const half4_t *>(y);
 #pragma unroll
                         for (int e = 0; e < 4; ++e) v[e] += (float)old[e];
@@ -914,11 +932,29 @@ __device__ __forceinline__ bool y_role(const MidArgs &a, int tid, int ot, int tt
                 } else {
 #pragma unroll
                     for (int e = 0; e < 4; ++e)
-                        if (o + e < a.n) y[e] = (half_t)(a.accumulate ? v[e] + (float)y[e] : v[e]);
+                        if (o + e < a.n) y[e] = (half_t)(a.flags & kAccumulate ? v[e] + (float)y[e] : v[e]);
                 }
             }
     }
     return false;
+}
+
+// Tiles j, j + step, ... of T, and all of those along `count` token tiles from `first` on.
+template <int XF, bool AQ, int TT>
+__device__ __forceinline__ void t_tiles(const MidArgs &a, int j, int step, char *lds_c, unsigned epoch)
+{
+    for (; j < a.t_tiles; j += step) {
+        int rt, tr;
+        if (tile_on_die(j, a.rank_pad / 16, rt, tr)) t_tile<XF, AQ, TT>(a, rt, tr, lds_c, epoch);
+    }
+}
+template <int XF, bool AQ, int TT>
+__device__ __forceinline__ void t_of_tokens(const MidArgs &a, int first, int count, char *lds_c, unsigned epoch)
+{
+    for (int j = 0; j < a.rank_pad / 16 * count; ++j) {
+        const int tr = first + j % count;
+        if (16 * TT * tr < a.m) t_tile<XF, AQ, TT>(a, j / count, tr, lds_c, epoch);
+    }
 }
 
 template <int NT_, int RT, int RG, int KW, int XF, bool AQ>
@@ -927,19 +963,19 @@ __global__ __launch_bounds__(kMidThreads, 3) void mid_kernel(MidArgs a)
     extern __shared__ __attribute__((aligned(16))) char lds_c[];
     const unsigned epoch = a.rank_pad > 0 && a.T ? call_epoch(a.epoch) : 0u;
     if ((int)blockIdx.x < a.n_t) {
-        for (int j = blockIdx.x; j < a.t_tiles; j += a.n_t) {
-            int rt, tr;
-            if (tile_on_die(j, a.rank_pad / 16, rt, tr)) t_tile<XF, AQ>(a, rt, tr, lds_c, epoch);
-        }
+        if (a.flags & kWideT)
+            t_tiles<XF, AQ, 2>(a, blockIdx.x, a.n_t, lds_c, epoch);
+        else
+            t_tiles<XF, AQ, 1>(a, blockIdx.x, a.n_t, lds_c, epoch);
         return;
     }
     int ot, tt;
     if (!tile_on_die((int)blockIdx.x - a.n_t, a.tiles_o, ot, tt)) return;
     if (!y_role<NT_, RT, RG, KW, XF, AQ, false>(a, threadIdx.x, ot, tt, lds_c, epoch)) return;
-    for (int j = 0; j < a.rank_pad / 16 * 2 * NT_; ++j) {
-        const int tr = 2 * NT_ * tt + j % (2 * NT_);
-        if (16 * tr < a.m) t_tile<XF, AQ>(a, j / (2 * NT_), tr, lds_c, epoch);
-    }
+    if (a.flags & kWideT)
+        t_of_tokens<XF, AQ, 2>(a, NT_ * tt, NT_, lds_c, epoch);
+    else
+        t_of_tokens<XF, AQ, 1>(a, 2 * NT_ * tt, 2 * NT_, lds_c, epoch);
     asm volatile("s_waitcnt vmcnt(0)" : : : "memory");     // the pieces are in memory
     __syncthreads();
     // (a thread number the compiler knows nothing of: what it works out of it above would stay in registers until here)
@@ -991,23 +1027,26 @@ static void launch_t_role(const TArgs &t, int xf, hipStream_t st)
 // Tests of the wait (slim_decode_override): nobody makes T, which ends in NaN, or the Y role has to make it.
 enum class WaitTest { none, fail, help };
 
-// Workgroups of the T role where both roles share a launch: what n_y workgroups of the Y role (one per compute unit)
-// leave free, if that makes T in at most `trips` tiles each; 0: T gets a launch of its own.
-static int t_workgroups(int t_tiles, int n_y, int cus, int trips)
+// How many tiles of T (of `tokens` tokens) each workgroup of the T role has to make beside n_y workgroups of the Y role, one per compute
+// unit; n_t: those workgroups.  None are free: more than any rule takes.
+static int t_trips(int rank_pad, int m, int tokens, int n_y, int cus, int *n_t = nullptr)
 {
-    const int spare = (cus - n_y) / kDies * kDies;
-    const int n_t = t_tiles < spare ? t_tiles : spare;
-    return n_t > 0 && t_tiles <= trips * n_t ? n_t : 0;
+    const int spare = (cus - n_y) / kDies * kDies, tiles = die_tiles(rank_pad / 16, (m + tokens - 1) / tokens);
+    const int n = tiles < spare ? tiles : spare;
+    if (n_t) *n_t = n > 0 ? n : 0;
+    return n > 0 ? (tiles + n - 1) / n : 1 << 20;
 }
 
 template <int NT_, int RT, int RG, int KW, int XF, bool AQ>
-static int launch_mid(MidArgs a, WaitTest wait_test, hipStream_t st)
+static int launch_mid(MidArgs a, int t_tokens, WaitTest wait_test, hipStream_t st)
 {
     constexpr size_t lds = MidLds<NT_, RT, RG, KW, XF>::BYTES;
     a.tiles_o = (a.n + 32 * RT * RG - 1) / (32 * RT * RG);
     const int n_y = die_tiles(a.tiles_o, (a.m + 32 * NT_ - 1) / (32 * NT_));
-    a.t_tiles = die_tiles(a.rank_pad / 16, (a.m + 15) / 16);
-    int n_t = t_workgroups(a.t_tiles, n_y, device_info().cus, 2);
+    if (t_tokens == 32) a.flags |= kWideT;
+    int n_t = 0;
+    if (t_tokens > 0) t_trips(a.rank_pad, a.m, t_tokens, n_y, device_info().cus, &n_t);
+    a.t_tiles = t_tokens == 32 ? die_tiles(a.rank_pad / 16, (a.m + 31) / 32) : die_tiles(a.rank_pad / 16, (a.m + 15) / 16);
     if (wait_test == WaitTest::fail) {
         n_t = 0;                             // nobody makes T
     } else if (wait_test == WaitTest::help && n_t > 0) {
@@ -1038,44 +1077,63 @@ static int launch_mid(MidArgs a, WaitTest wait_test, hipStream_t st)
 constexpr int kMidTiles[4][2] = {{32, 32}, {64, 32}, {128, 32}, {128, 64}};
 
 // Which geometry, by the sizes alone (index into kMidTiles), or -1: the tiles of slim_gemm_sparse.hip (or, for the
-// adapter term alone, the dense product).
-// The smallest tile that gives every compute unit at most one workgroup and leaves room to make T in the same launch,
-// else the smallest that gives at most one: a second workgroup on a unit doubles the time of a call that is a
-// chain of latencies, a smaller tile shortens the chain.  4096 x 4096, r = 409: 64 tokens 14.6 / 10.4 / 13.7 / 20.5 us
-// (256 / 128 / 64 / 32 workgroups, in the order of kMidTiles; the 512 x 128 tiles 29), 128 tokens 23.2 / 16.8 /
+// adapter term alone, the dense product); and the tokens of a tile of T in the same launch, or 0: T gets a launch of its own.
+struct MidPlan {
+    int geometry, t_tokens;
+};
+// The smallest tile that gives every compute unit at most one workgroup and leaves room to make T in the same launch: a second workgroup
+// on a unit doubles the time of a call that is a chain of latencies, a smaller tile shortens the chain.  4096 x 4096, r = 409: 64 tokens
+// 14.6 / 10.4 / 13.7 / 20.5 us (256 / 128 / 64 / 32 workgroups, in the order of kMidTiles; the 512 x 128 tiles 29), 128 tokens 23.2 / 16.8 /
 // 14.5 / 20.4 (31), 512 tokens 76 / 46 / 37 / 31 (36).  Where no tile fits, the large ones win: 11008 x 4096 at 256
 // tokens 36.6 against 49.7.
+// T is best made in one tile per workgroup.  Where tiles of 16 tokens are more than that, those of 32 tokens come next (which read R
+// half as often, and each take longer), then two tiles, then three, and then a launch of T's own; a larger tile of Y that leaves room for one
+// instead of two is worth it from the smallest to the next only (us: 7452 x 2432 at 31 tokens, two tiles 10.1, one of 32 tokens 8.6, one of 16
+// beside the next tile of Y 8.2; 2244 x 3968 at 343 tokens T by itself 25.8, one of 32 tokens 17.6; 12523 x 7040 at 36 tokens two of 32 tokens
+// 27.7, the next tile of Y 36.8).  Of 216 layers of 512 to 28672 rows and 512 to 11008 inputs at 17 to 512 tokens this rule is 0.5 % from the best of all of
+// these on average, and slower than two tiles of 16 or else the next tile of Y, as it was, in none by more than 5 %; 3 % faster on average, up to 1.47
+// times.
 // The adapter term alone has nothing to hide a chain of T behind: 4096 x 4096 at 128 tokens 15.7 / 12.5 / 15.2 / 20.1
-// against 14.1 of the dense product, 28672 x 4096 at 48 tokens 20.2 at best against 13.6.
+// against 14.1 of the dense product (12.7 to 12.8 with T in the same launch, in tiles of 32 tokens), 28672 x 4096 at 48 tokens 20.2 at best against 13.6.
 // Above 512 tokens the workspace has no room for the pieces of T.
-static int mid_geometry(int n, int rank_pad, int m, int cus, bool weight_term)
+MidPlan mid_plan(int n, int rank_pad, int m, int cus, bool weight_term)
 {
-    if (m > 512) return -1;
-    const int t_tiles = die_tiles(rank_pad / 16, (m + 15) / 16);
-    int first = -1;
+    constexpr MidPlan none{-1, 0};
+    if (m > 512) return none;
+    auto workgroups = [&](int g) { return die_tiles((n + kMidTiles[g][0] - 1) / kMidTiles[g][0], (m + kMidTiles[g][1] - 1) / kMidTiles[g][1]); };
+    MidPlan first = none, more = none;           // the first tile that fits, the first with room for more than one tile of T
     for (int g = 0; g < 4; ++g) {
-        const int n_y = die_tiles((n + kMidTiles[g][0] - 1) / kMidTiles[g][0], (m + kMidTiles[g][1] - 1) / kMidTiles[g][1]);
+        const int n_y = workgroups(g);
         if (n_y > cus) continue;
-        if (t_tiles == 0) return g;
+        if (rank_pad == 0) return {g, 0};
+        const int t16 = t_trips(rank_pad, m, 16, n_y, cus), t32 = t_trips(rank_pad, m, 32, n_y, cus);
         if (!weight_term) {
-            if (g < 3 && n < 16384) return g;
-            if (t_workgroups(t_tiles, n_y, cus, 1) > 0) return g;
-            continue;
+            if (g == 3 || n >= 16384) {
+                if (t16 <= 1) return {g, 16};
+                continue;
+            }
+            if (t16 <= 1 || t16 > 2) return {g, t16 <= 1 ? 16 : 0};
+            if (g == 0 && t_trips(rank_pad, m, 16, workgroups(1), cus) <= 1) return {1, 16};
+            return {g, t32 <= 1 ? 32 : 16};
         }
-        if (t_workgroups(t_tiles, n_y, cus, 2) > 0) return g;
-        if (first < 0) first = g;
+        if (first.geometry < 0) first = {g, 0};
+        if (t16 <= 1 || t32 <= 1) {
+            if (more.geometry < 0 || (more.geometry == 0 && g == 1)) return {g, t16 <= 1 ? 16 : 32};
+            return more;
+        }
+        if (more.geometry < 0 && (t16 <= 3 || t32 <= 2)) more = {g, t16 <= 2 || t32 > 2 ? 16 : 32};
     }
-    return first;
+    return more.geometry >= 0 ? more : first;
 }
 
 template <int XF, bool AQ>
-static int launch_mid_call(const MidArgs &a, int geometry, WaitTest wait_test, hipStream_t st)
+static int launch_mid_call(const MidArgs &a, MidPlan plan, WaitTest wait_test, hipStream_t st)
 {
-    switch (geometry) {
-        case 0: return launch_mid<1, 1, 1, 8, XF, AQ>(a, wait_test, st);
-        case 1: return launch_mid<1, 1, 2, 4, XF, AQ>(a, wait_test, st);
-        case 2: return launch_mid<1, 2, 2, 4, XF, AQ>(a, wait_test, st);
-        default: return launch_mid<2, 1, 4, 2, XF, AQ>(a, wait_test, st);
+    switch (plan.geometry) {
+        case 0: return launch_mid<1, 1, 1, 8, XF, AQ>(a, plan.t_tokens, wait_test, st);
+        case 1: return launch_mid<1, 1, 2, 4, XF, AQ>(a, plan.t_tokens, wait_test, st);
+        case 2: return launch_mid<1, 2, 2, 4, XF, AQ>(a, plan.t_tokens, wait_test, st);
+        default: return launch_mid<2, 1, 4, 2, XF, AQ>(a, plan.t_tokens, wait_test, st);
     }
 }
 
@@ -1087,8 +1145,8 @@ int launch_gemm_mid(const slim_layer *layer, const half_t *X, int xf, const floa
     *taken = false;
     const slim_shape s = layer->shape;
     const bool q4 = layer->adapter_bits == 4 && s.rank > 0;
-    const int geometry = mid_geometry(s.n, layer->rank_pad, m, device_info().cus, weight_term);
-    if (geometry < 0) return SLIM_OK;
+    const MidPlan plan = mid_plan(s.n, layer->rank_pad, m, device_info().cus, weight_term);
+    if (plan.geometry < 0) return SLIM_OK;
     // 32-bit offsets, tiles past the end included; room for the pieces of T
     constexpr uint64_t kLimit = 0x80000000ull;
     const uint64_t t_bytes = q4 ? mid_t_bytes<true>(m, layer->rank_pad) : mid_t_bytes<false>(m, layer->rank_pad);
@@ -1121,13 +1179,13 @@ int launch_gemm_mid(const slim_layer *layer, const half_t *X, int xf, const floa
     a.rank_pad = layer->rank_pad;
     a.m = m;
     a.stages = weight_term ? s.k / 128 : 0;
-    a.accumulate = accumulate;
+    a.flags = accumulate ? kAccumulate : 0;
     if (q4) {
-        if (xf == 0) return launch_mid_call<0, true>(a, geometry, wait_test, st);
-        return xf == 1 ? launch_mid_call<1, true>(a, geometry, wait_test, st) : launch_mid_call<2, true>(a, geometry, wait_test, st);
+        if (xf == 0) return launch_mid_call<0, true>(a, plan, wait_test, st);
+        return xf == 1 ? launch_mid_call<1, true>(a, plan, wait_test, st) : launch_mid_call<2, true>(a, plan, wait_test, st);
     }
-    if (xf == 0) return launch_mid_call<0, false>(a, geometry, wait_test, st);
-    return xf == 1 ? launch_mid_call<1, false>(a, geometry, wait_test, st) : launch_mid_call<2, false>(a, geometry, wait_test, st);
+    if (xf == 0) return launch_mid_call<0, false>(a, plan, wait_test, st);
+    return xf == 1 ? launch_mid_call<1, false>(a, plan, wait_test, st) : launch_mid_call<2, false>(a, plan, wait_test, st);
 }
 
 }  // namespace slim

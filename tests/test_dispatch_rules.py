@@ -67,3 +67,32 @@ def _two_groups(k, rank_pad, fp8):
 def test_two_groups_of_wavefronts_where_they_pay(fp8, k, rank_pad, ratio):
     """ratio: time of a call with two groups over that with one, measured (mean of calls on 512 to 28672 rows)."""
     assert _two_groups(k, rank_pad, fp8) == (ratio < 1.0)
+
+
+def _mid_plan(n, rank_pad, m, weight_term):
+    f = B.lib()._ZN4slim8mid_planEiiiib
+    f.argtypes, f.restype = [ctypes.c_int] * 4 + [ctypes.c_bool], ctypes.c_uint64
+    v = f(n, rank_pad, m, 256, weight_term)
+    return ctypes.c_int32(v & 0xFFFFFFFF).value, v >> 32
+
+
+@pytest.mark.parametrize("n,k,r,m,us", [
+    (2244, 3968, 224, 343, {(-1, 0): 32.0, (3, 0): 25.8, (3, 32): 17.6}),
+    (7452, 2432, 243, 31, {(0, 0): 12.0, (0, 16): 10.1, (0, 32): 8.6, (1, 0): 11.8, (1, 16): 8.2, (1, 32): 8.8, (2, 16): 10.0, (2, 32): 10.0}),
+    (1375, 3584, 137, 126, {(0, 0): 13.2, (0, 16): 11.4, (0, 32): 9.8, (1, 16): 9.3, (1, 32): 10.2, (2, 16): 12.4, (2, 32): 12.5}),
+    (1540, 4096, 154, 98, {(0, 0): 13.1, (0, 32): 13.9, (1, 16): 9.3, (1, 32): 10.1, (2, 16): 12.3}),
+    (3127, 2304, 230, 156, {(1, 0): 19.4, (2, 0): 15.2, (2, 16): 12.3, (2, 32): 11.2, (3, 16): 15.0}),
+    (12523, 7040, 704, 36, {(1, 0): 41.0, (2, 0): 33.0, (2, 16): 29.8, (2, 32): 27.7, (3, 16): 36.8}),
+    (11008, 8192, 819, 48, {(1, 0): 41.2, (2, 0): 32.9, (2, 16): 25.2, (2, 32): 26.0, (3, 16): 35.4}),
+    (5120, 5120, 512, 48, {(0, 0): 23.0, (1, 0): 17.2, (1, 16): 11.7, (1, 32): 13.2, (2, 16): 15.7}),
+    (13056, 3200, 320, 148, {(-1, 0): 29.9, (3, 0): 39.7})])
+def test_the_plan_of_small_batches(n, k, r, m, us):
+    """Tile and T of whole layers: the plan taken is within a tenth of the best one measured."""
+    assert us[_mid_plan(n, B.slim_rank_pad(r), m, True)] <= 1.1 * min(us.values())
+
+
+def test_the_plan_of_the_adapter_term_alone():
+    assert _mid_plan(4096, 416, 128, False) == (1, 0)        # 12.1 us; in one launch 12.7
+    assert _mid_plan(2679, 96, 203, False) == (2, 32)        # 8.9 us; two tiles of 16 tokens 10.2
+    assert _mid_plan(2016, 224, 96, False) == (1, 16)        # 8.2; on the smallest tile 10.4
+    assert _mid_plan(18662, 256, 64, False) == (3, 16) and _mid_plan(28672, 832, 400, False)[0] == -1

@@ -305,3 +305,24 @@ def test_captured_calls_replay_correctly(n, k, r, m):
         for g, w in zip(got, want):
             assert torch.equal(g, w)
     B.slim_workspace_check(ws)
+
+
+# T in tiles of 32 tokens beside each of the four tile shapes, one per workgroup and two, token counts that end in either half of a tile
+T32_CASES = [(7452, 256, 243, 31), (1604, 1024, 102, 109), (1485, 1536, 148, 189), (3127, 384, 230, 150), (2244, 384, 224, 343)]
+
+
+@pytest.mark.parametrize("help_t", [False, True])
+@pytest.mark.parametrize("kind", ["fp16", "q4", "fp8", "fp8_q4"])
+@pytest.mark.parametrize("n,k,r,m", T32_CASES)
+def test_t_in_tiles_of_32_tokens(n, k, r, m, kind, help_t, decode_override):
+    """By the T role, and by workgroups whose wait runs out.  The bounds are the usual ones."""
+    from test_dispatch_rules import _mid_plan
+    assert _mid_plan(n, B.slim_rank_pad(r), m, True)[1] == 32
+    if help_t:
+        decode_override("wait_test", 16)
+    bits = 4 if kind.endswith("q4") else 16
+    if kind.startswith("fp8"):
+        err, _ = _fp8_forward_case(n, k, r, m, seed=33, bits=bits)
+    else:
+        err = _forward_case(_shape(n, k, r), m, B.slim_linear_gemm, seed=33, bits=bits)
+    assert err <= TOL_Y
