@@ -47,7 +47,15 @@ static thread_local bool t_wait_test = false;
 bool adapters_wait_test() { return t_wait_test && decode_path_override() == 3; }
 size_t decode_lds_limit() { return (size_t)g_decode_lds_kb.load(std::memory_order_relaxed) * 1024; }
 
-int gemm_t_splits(int32_t m, int32_t rank_pad, int32_t k);   // slim_gemm.hip
+// The most ranges of inputs that T = X R^T is split into, for which a workspace has room: enough that 256 ranks x 128 tokens each make
+// 192 workgroups, of at least 512 inputs.
+int gemm_t_splits(int32_t m, int32_t rank_pad, int32_t k)
+{
+    const long tiles = (long)((rank_pad + 255) / 256) * ((m + 127) / 128);
+    int s = 1;
+    while (tiles * s < 192 && s < 8 && k / (2 * s) >= 512) s *= 2;
+    return s;
+}
 
 WorkspacePlan plan_workspace(int32_t n, int32_t k, int32_t rank_pad, int32_t m, bool q4)
 {

@@ -31,7 +31,7 @@
 
 namespace slim {
 
-int gemm_t_splits(int32_t m, int32_t rank_pad, int32_t k);   // slim_gemm.hip
+int gemm_t_splits(int32_t m, int32_t rank_pad, int32_t k);   // slim_api.hip
 
 typedef int int4_t __attribute__((ext_vector_type(4)));
 typedef int int8v_t __attribute__((ext_vector_type(8)));
@@ -235,9 +235,8 @@ __device__ __forceinline__ void t_tile(const MidArgs &a, int rt, int tt, char *l
 // whole tile on its units with V_MFMA_F32_32X32X16_F16 (R from memory into registers, X through 8 KiB of LDS
 // of its own, no barrier on the way), and add up in LDS.  What bounds it is the 64 bytes a compute unit
 // draws per clock from its L2: (32 RT + 32 TT) x 2 bytes of them per input, which is why the tile grows
-// with the batch.  A product split over workgroups instead, with fp32 partial sums in memory, took another
-// launch and 8 us to add them up.
-//   Whole calls, against that: 8192 x 8192 at 1000 tokens 125.0 -> 117.4 us, 11008 x 4096 at 333 tokens 55.2 -> 45.2.
+// with the batch.
+//   Whole calls, against a product split over workgroups (256 x 128): 8192 x 8192 at 1000 tokens 125.0 -> 117.4 us, 11008 x 4096 at 333 tokens 55.2 -> 45.2.
 // Columns of a unit that step j multiplies on lane half h:
 //   fp16 R, fp16 X   16 j + 8 h + [0, 8)
 //   fp16 R, 8-bit X  32 (j / 2) + 16 h + 8 (j % 2) + [0, 8): two steps share one piece of codes
@@ -416,36 +415,346 @@ static void launch_t_tiles(TArgs a, int xf, hipStream_t st)
     }
 }
 
+// ---- the same in tiles of 128 ranks x 128 tokens, the inputs split over workgroups where there are few ----
+// What bounds the tiles above on many tokens is what they draw from the L2 (64 x 64: 21 TB/s over the chip); these draw half of that.
+//   X and R come by direct-to-LDS loads, a stage of 64 inputs at a time, three stages ahead in a ring of four.  The eight wavefronts are four groups, each
+// on one of the four steps of a stage, and a wavefront has 128 ranks x 64 tokens (4 x 2 tiles of V_MFMA_F32_32X32X16_F16): six operands read from LDS
+// for eight products.  They read one stage ahead, and the loads stand between the products: issued together before them they kept
+// the matrix core waiting for a place in the load queue.  The groups add up in LDS at the end.
+//   A stage takes 0.34 us on a part of the chip, 0.47 on all of it (LDS 0.29, products 0.21).  Neither the reads one stage ahead (64.8 -> 61.3 us at
+// 4096 x 832 x 8192) nor fewer reads (60.3) changed much; conversion of 4-bit codes adds 0.2 us.
+//   A die works on one range of the inputs (or several dies on the same), so that all dies together read X and R little more than once.  The partial sums
+// cost their way through memory and a launch that adds them up: 8 us at two ranges of 2048 x 416, 13 at four of 1000 x 832.
+//   tokens x ranks x inputs, us: this / split product with 256 x 128 tiles, before / 64 x 64 tiles:
+//   4096 x 832 x 8192 60 / 72 / 103, 2048 x 1120 x 5120 35 / 50 / 52, with 8-bit X (k 4096) 29 / 42 / 40, 4-bit R (4096 x 832 x 8192) 79 / 86 / 116;
+//   over 500 drawn products (128 to 4096 tokens, ranks 32 to 1400, 512 to 28672 inputs) the kind now taken is 8 % faster on average than the one launch with
+//   fp16 R, up to 2.5 times, and 2 % in 4 bits.
+// Columns of a stage that step j (of four) multiplies on lane half h
+//   fp16 R, fp16 X   16 j + 8 h + [0, 8)
+//   fp16 R, 8-bit X  32 (j / 2) + 16 h + 8 (j % 2) + [0, 8)
+//   4-bit R          32 h + 8 j + [0, 8)
+constexpr int kBigStage = 64, kBigRing = 4, kBigWaves = 8;
+constexpr int kBigRange = 32768;     // inputs whose 4-bit scales fit in LDS beside the ring
+struct TBigArgs {
+    TArgs t;
+    int splits, ks;          // ranges of the inputs (1, 2, 4 or 8), inputs in each (a multiple of 128)
+    int per;                 // tiles of a die
+    float *P;                // splits > 1: fp32 [splits][m][rank_pad]
+};
+template <int XF, bool AQ>
+__global__ __launch_bounds__(kBigWaves * kWave, 2) void t_big_kernel(TBigArgs b)
+{
+    const TArgs &a = b.t;
+    constexpr int XROW = XF ? 64 : 128, PIECES = XROW / 16, TPI = 64 / PIECES;        // bytes of a token's stage, pieces of it, tokens per load
+    constexpr int XBYTES = 128 * XROW, RBYTES = AQ ? 4096 : 16384, SLOT = XBYTES + RBYTES;
+    constexpr int NX = XBYTES / 1024, NR = RBYTES / 1024, NL = (NX + NR) / kBigWaves;  // loads of a stage; per wavefront
+    constexpr int LEFT = (NX + NR) % kBigWaves;                                       // (4-bit R and 16-bit X: the first wavefronts have one more)
+    extern __shared__ __attribute__((aligned(16))) char lds_c[];
+    const int lane = threadIdx.x & (kWave - 1), li = lane & 31, lb = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int group = wave >> 1, th = wave & 1;             // this wavefront's step of a stage, its half of the tokens
+    const int die = (int)blockIdx.x % kDies, share = kDies / b.splits, z = die / share;
+    const int tile = (die % share) * b.per + (int)blockIdx.x / kDies;
+    if (tile >= a.tiles_t * a.tiles_r) return;
+    const int r0 = tile % a.tiles_r * 128, t0 = tile / a.tiles_r * 128;
+    const uint32_t k = (uint32_t)a.k, xb = XF ? 1u : 2u;
+    int k0 = z * b.ks;
+    const int k_end = min(a.k, k0 + b.ks);
+    int stages = 0;                                         // of the part of the range that starts at k0
+    const rsrc_t x_rs = make_rsrc(a.X, (uint32_t)a.m * k * xb);
+    const rsrc_t r_rs = AQ ? make_rsrc(a.Rq, (uint32_t)q4_code_bytes(a.rank, a.k)) : make_rsrc(a.R, (uint32_t)tl_bytes(a.rank_pad, a.k));
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)lds_c;
+    auto swz = [](int tok) { return (uint32_t)(XF ? (tok >> 2) & 3 : (tok >> 1) & 7); };
+    const uint32_t ct = q4_ctiles(a.k);
+    // load i of this wavefront's NL of stage s, to its place in the ring (the last stage again past the end; nobody uses it)
+    auto load = [&](int s, auto ic) {
+        constexpr int i = ic;
+        const uint32_t to = lds0 + (uint32_t)(s % kBigRing) * SLOT + (uint32_t)wave * 1024u, c0 = (uint32_t)(k0 + min(s, stages - 1) * kBigStage);
+        if constexpr (i < NX / kBigWaves) {
+            const int tok = TPI * (kBigWaves * i + wave) + lane / PIECES;
+            load_to_lds(x_rs, (uint32_t)(t0 + tok) * k * xb + (((uint32_t)(lane % PIECES) ^ swz(tok)) << 4), c0 * xb, to + (uint32_t)i * 8192u);
+        } else if constexpr (AQ) {
+            if (wave < LEFT) {
+                const uint32_t row = (uint32_t)(r0 + 32 * wave + li);
+                load_to_lds(r_rs, q4_piece(row, 0, ct) + 16u * lb, (c0 >> 8) * 2048u + ((c0 >> 6) & 3u) * 32u, to + XBYTES);
+            }
+        } else {
+            constexpr int j = i - NX / kBigWaves;
+            const uint32_t p = (uint32_t)(kBigWaves * j + wave);     // row tile p / 4, columns 16 (p % 4) .. of the stage
+            load_to_lds(r_rs, ((uint32_t)(r0 / 32) + p / 4) * (k >> 4) * 1024u + (uint32_t)lane * 16u, ((c0 >> 4) + p % 4) * 1024u,
+                        to + XBYTES + (uint32_t)j * 8192u);
+        }
+    };
+    auto load_stage = [&](int s) { static_for<NL + (LEFT > 0)>([&](auto ic) { load(s, ic); }); };
+    half_t *const scales = reinterpret_cast<half_t *>(lds_c + kBigRing * SLOT);       // 4-bit R: [group of 128][row]
+    float16_t acc[4][2];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int it = 0; it < 2; ++it)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) acc[i][it][e] = 0.f;
+    // what a wavefront multiplies of a stage: one step of its two tiles of X and four of R
+    using XPart = std::conditional_t<XF != 0, uint2_t, uint4_t>;
+    using RPart = std::conditional_t<AQ, uint32_t, uint4_t>;
+    struct Part {
+        XPart x[2];
+        RPart r[4];
+    };
+    // every wavefront's loads of stage s are here when at most the two after it are in flight; past the barrier all may read it, and the place of the
+    // one before, whose reads have ended, is free
+    auto arrive = [&]() {
+        if (LEFT > 0 && wave < LEFT)
+            asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" : : "n"((kBigRing - 2) * (NL + 1)) : "memory");
+        else
+            asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" : : "n"((kBigRing - 2) * NL) : "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" : : : "memory");
+    };
+    auto read = [&](Part &f, int s) {
+        const char *const xs = lds_c + (s % kBigRing) * SLOT, *const rs = xs + XBYTES;
+#pragma unroll
+        for (int it = 0; it < 2; ++it) {
+            const int tok = 64 * th + 32 * it + li;
+            const uint32_t piece = XF ? (AQ ? 2u * lb + group / 2 : 2u * (group / 2) + lb) : (AQ ? 4u * lb + group : 2u * group + lb);
+            f.x[it] = *reinterpret_cast<const XPart *>(xs + tok * XROW + ((piece ^ swz(tok)) << 4) + (XF ? 8 * (group % 2) : 0));
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            f.r[i] = *reinterpret_cast<const RPart *>(AQ ? rs + i * 1024 + lane * 16 + 4 * group
+                                                         : rs + i * 4096 + (XF ? (2 * (group / 2) + lb) * 1024 + (32 * (group % 2) + li) * 16
+                                                                               : group * 1024 + lane * 16));
+    };
+    half_t sc[4] = {};
+    // the loads of stage `next` between the products, so that a full load queue does not keep the matrix core waiting
+    auto multiply = [&](const Part &f, int next) {
+        half8_t bv[2];
+#pragma unroll
+        for (int it = 0; it < 2; ++it) {
+            if constexpr (XF == 0)
+                bv[it] = __builtin_bit_cast(half8_t, f.x[it]);
+            else
+                bv[it] = codes8_to_half8<XF>(f.x[it][0], f.x[it][1]);
+        }
+        // (4-bit R: the conversion of the next row tile's codes, 17 vector instructions, beside this one's products)
+        auto row_tile = [&](int i) {
+            if constexpr (AQ)
+                return codes_to_half8(f.r[i]) * sc[i];
+            else
+                return __builtin_bit_cast(half8_t, f.r[i]);
+        };
+        half8_t av = row_tile(0);
+        if constexpr (AQ) __builtin_amdgcn_sched_barrier(0);
+        static_for<4>([&](auto ic) {
+            constexpr int i = ic;
+            half8_t next_av = av;
+            if constexpr (i < 3) next_av = row_tile(i + 1);
+#pragma unroll
+            for (int it = 0; it < 2; ++it) acc[i][it] = __builtin_amdgcn_mfma_f32_32x32x16_f16(av, bv[it], acc[i][it], 0, 0, 0);
+            if constexpr (AQ && i < 3) {
+                __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);
+                __builtin_amdgcn_sched_group_barrier(0x2, 8, 0);
+                __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);
+                __builtin_amdgcn_sched_group_barrier(0x2, 9, 0);
+            }
+            av = next_av;
+            __builtin_amdgcn_sched_barrier(0);
+            if constexpr (i < NL + (LEFT > 0)) load(next, ic);
+            __builtin_amdgcn_sched_barrier(0);
+        });
+    };
+    for (; k0 < k_end; k0 += kBigRange) {
+        // (more than one part only with 4-bit R: without it a range has one)
+        const int klen = AQ ? min(kBigRange, k_end - k0) : k_end - k0;
+        stages = klen / kBigStage;
+        if constexpr (AQ) {
+            const rsrc_t s_rs = make_rsrc(a.Rs, (uint32_t)q4_scale_bytes(a.rank, a.k));
+            for (int i = threadIdx.x; i < klen; i += kBigWaves * kWave)
+                scales[i] = load_half(s_rs, ((uint32_t)(r0 + i % 128) * q4_groups(a.k) + (uint32_t)(k0 / 128 + i / 128)) * 2u, 0);
+        }
+        asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" : : : "memory");
+#pragma unroll
+        for (int s = 0; s < kBigRing - 1; ++s) load_stage(s);
+        arrive();
+        Part f0, f1;
+        read(f0, 0);
+        load_stage(kBigRing - 1);
+        for (int s = 0; s < stages; s += 2) {
+            if constexpr (AQ)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) sc[i] = scales[s / 2 * 128 + 32 * i + li];
+            arrive();
+            read(f1, s + 1);
+            multiply(f0, s + kBigRing);
+            arrive();
+            read(f0, s + 2);
+            multiply(f1, s + 1 + kBigRing);
+        }
+        // the loads past the end have landed and every wavefront has read what it reads
+        asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" : : : "memory");
+        __syncthreads();
+        if constexpr (!AQ) break;
+    }
+    // the groups add up: group g stores row tile g, 32 tokens at a time, with what the three others have left in LDS
+    float4_t *const red = reinterpret_cast<float4_t *>(lds_c) + th * 12 * 256 + lane;       // [th][row tile][of three][4][lane]
+    const float xscale = XF ? *a.x_scale : 1.0f;
+#pragma unroll
+    for (int it = 0; it < 2; ++it) {
+        if (it) __syncthreads();
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            if (i != group)
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    red[(3 * i + ((group - i) & 3) - 1) * 256 + q * kWave] = float4_t{acc[i][it][4 * q], acc[i][it][4 * q + 1], acc[i][it][4 * q + 2], acc[i][it][4 * q + 3]};
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            if (i == group)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    float4_t v = {acc[i][it][4 * q], acc[i][it][4 * q + 1], acc[i][it][4 * q + 2], acc[i][it][4 * q + 3]};
+#pragma unroll
+                    for (int o = 0; o < 3; ++o) v += red[(3 * i + o) * 256 + q * kWave];
+                    if (XF) v *= xscale;
+                    // lane holds token t, ranks r .. r + 3
+                    const int t = t0 + 64 * th + 32 * it + li, r = r0 + 32 * i + 8 * q + 4 * lb;
+                    if (t >= a.m || r >= a.rank_pad) continue;
+                    if (b.splits > 1)
+                        *reinterpret_cast<float4_t *>(b.P + ((size_t)z * a.m + t) * a.rank_pad + r) = v;
+                    else
+                        *reinterpret_cast<half4_t *>(a.T + (size_t)t * a.rank_pad + r) = half4_t{(half_t)v[0], (half_t)v[1], (half_t)v[2], (half_t)v[3]};
+                }
+    }
+}
+
+// T[i] = fp16(sum_z P[z][i]), four at a time
+template <int S>
+__global__ __launch_bounds__(256) void t_sum_kernel(const float4_t *__restrict__ P, size_t count, half4_t *__restrict__ T)
+{
+    const size_t i = blockIdx.x * (size_t)256 + threadIdx.x;
+    if (i >= count) return;
+    float4_t v[S];
+#pragma unroll
+    for (int z = 0; z < S; ++z) v[z] = P[(size_t)z * count + i];
+#pragma unroll
+    for (int z = 1; z < S; ++z) v[0] += v[z];
+    T[i] = half4_t{(half_t)v[0][0], (half_t)v[0][1], (half_t)v[0][2], (half_t)v[0][3]};
+}
+
+static void launch_t_big(const TArgs &t, int xf, int splits, float *P, hipStream_t st)
+{
+    TBigArgs b{};
+    b.t = t;
+    b.t.tiles_t = (t.m + 127) / 128;
+    b.t.tiles_r = (t.rank_pad + 127) / 128;
+    b.splits = splits;
+    b.ks = (t.k / 128 + splits - 1) / splits * 128;
+    b.P = P;
+    const int share = kDies / splits, tiles = b.t.tiles_t * b.t.tiles_r;
+    b.per = (tiles + share - 1) / share;
+    const dim3 grid((unsigned)(kDies * b.per)), blk(kBigWaves * kWave);
+    // the ring and the scales of a range, and not less than what the groups leave at the end
+    auto bytes = [&](int x, int r) {
+        const int range = b.ks < kBigRange ? b.ks : kBigRange;
+        const size_t v = (size_t)kBigRing * (128 * (x ? 64 : 128) + (r ? 4096 : 16384)) + (r ? 2 * (size_t)range : 0);
+        return v > 98304 ? v : (size_t)98304;
+    };
+    if (t.Rq) {
+        if (xf == 0)
+            hipLaunchKernelGGL((t_big_kernel<0, true>), grid, blk, bytes(0, 1), st, b);
+        else if (xf == 1)
+            hipLaunchKernelGGL((t_big_kernel<1, true>), grid, blk, bytes(1, 1), st, b);
+        else
+            hipLaunchKernelGGL((t_big_kernel<2, true>), grid, blk, bytes(2, 1), st, b);
+    } else {
+        if (xf == 0)
+            hipLaunchKernelGGL((t_big_kernel<0, false>), grid, blk, bytes(0, 0), st, b);
+        else if (xf == 1)
+            hipLaunchKernelGGL((t_big_kernel<1, false>), grid, blk, bytes(1, 0), st, b);
+        else
+            hipLaunchKernelGGL((t_big_kernel<2, false>), grid, blk, bytes(2, 0), st, b);
+    }
+    if (splits > 1) {
+        const size_t count = (size_t)t.m * t.rank_pad / 4;
+        const dim3 sums((unsigned)((count + 255) / 256));
+        const float4_t *p = reinterpret_cast<const float4_t *>(P);
+        half4_t *out = reinterpret_cast<half4_t *>(t.T);
+        if (splits == 2)
+            hipLaunchKernelGGL(t_sum_kernel<2>, sums, dim3(256), 0, st, p, count, out);
+        else if (splits == 4)
+            hipLaunchKernelGGL(t_sum_kernel<4>, sums, dim3(256), 0, st, p, count, out);
+        else
+            hipLaunchKernelGGL(t_sum_kernel<8>, sums, dim3(256), 0, st, p, count, out);
+    }
+}
+
+// As launch_t_product(), in tiles of 128 x 128 with the inputs in `splits` (1, 2, 4, 8) ranges; P: fp32 [splits][m][rank_pad] where that is
+// more than one.  The caller keeps X and R below 4 GiB each.
+int launch_t_split(const half_t *X, int xf, const float *x_scale, int m, int k, const half_t *R, const uint8_t *Rq, const half_t *Rs, int rank,
+                   int rank_pad, half_t *T, float *P, int splits, hipStream_t st)
+{
+    TArgs a{};
+    a.X = X;
+    a.x_scale = x_scale;
+    a.R = R;
+    a.Rq = R ? nullptr : Rq;
+    a.Rs = Rs;
+    a.k = k;
+    a.rank = rank;
+    a.rank_pad = rank_pad;
+    a.m = m;
+    a.T = T;
+    launch_t_big(a, xf, splits, P, st);
+    return hip_status(hipGetLastError());
+}
+
 // ---- which kernel makes T ----
-// 0, 1, 2: t_product_kernel with tiles of 32 x 32, 32 x 64, 64 x 64 (ranks x tokens); 3: the 16 x 16 tiles of the T role; 4: the
-// split product of slim_gemm.hip and the launch that adds it up.  The one whose estimated time is the shortest.  A kind
+// 0, 1, 2: t_product_kernel with tiles of 32 x 32, 32 x 64, 64 x 64 (ranks x tokens); 3: the 16 x 16 tiles of the T role; 4:
+// t_big_kernel, the inputs in t_splits() ranges.  The one whose estimated time is the shortest.  A kind
 // that deals its tiles to the dies takes as many rounds as its fullest die has tiles for its compute units (with 10 tiles of
 // tokens two dies have two, and 18 rank tiles make that 36 workgroups on 32 units: twice the time), and
 //   time = a + rounds (b + k / 1000 (c + d w)),   w = the share of that die's units with a tile in the first round,
 // or, where several dies read all of R, what that takes at 7 TB/s for all eight, three of them no faster (28672 inputs, rank 832,
-// 48 MB: kind 0 44 us at 64 tokens, 54 at 100, 55 at 200 and 256, where the first estimate says 38, and kind 4 47 to 50); the split product's is a + rounds c k / 1000 of a share + d per million partial sums.  The constants (us) are
+// 48 MB: kind 0 44 us at 64 tokens, 54 at 100, 55 at 200 and 256, where the first estimate says 38).  For kind 4, k is that of a range, the dies of one
+// range share the tiles, and several ranges add e + f per million partial sums.  The constants (us) are
 // fitted to 6048 measured products (ranks 32 to 1408, 17 to 4096 tokens, 512 to 28672 inputs, X in fp16 and 8 bits, R in
-// fp16 and 4 bits): off by 5 to 15 %, which makes the kind taken 1 % slower than the best one on average.  What is wrong
-// is rather the one launch (what else the dies share is in d only), so the split product is taken from 7 % more on: of those 6048,
-// the kind taken is slower than the split product by more than 3 % in 43, all but 15 by less than 8 %.
-//   8192 inputs, fp16 (us; kinds 0 to 4): rank 64 at 800 tokens 10.6 / 14.8 / 20.5 / 20.3 / 19.8, rank 512 at 1000 tokens
-//   27.0 / 20.6 / 25.8 / - / 24.9, rank 832 at 600 tokens 37.1 / 37.2 / 27.6 / - / 25.8, at 1000 tokens 49.2 / 37.5 / 27.8 / - / 33.7.
+// fp16 and 4 bits; kind 4: 500, at every number of ranges): off by 5 to 15 %, 4 % for kind 4, which makes the kind taken 1 % slower than the best one on
+// average.  Those of kind 4 with fp16 R are a tenth above the fit: where both are about as fast the one launch is taken, which needs no memory
+// for partial sums.  Up to 128 tokens, one tile of them, it was not measured and is not taken.
+//   8192 inputs, fp16 (us; kinds 0 to 3): rank 64 at 800 tokens 10.6 / 14.8 / 20.5 / 20.3, rank 512 at 1000 tokens
+//   27.0 / 20.6 / 25.8 / -, rank 832 at 600 tokens 37.1 / 37.2 / 27.6 / -, at 1000 tokens 49.2 / 37.5 / 27.8 / - (kind 4 there 25 to 26).
 struct TCost {
-    double a, b, c, d;
+    double a, b, c, d, e, f;
 };
-constexpr TCost kTCost[2][5] = {{{2.1, 1.1, 0.8, 0.5}, {2.0, 1.4, 1.2, 0.7}, {2.7, 1.6, 1.8, 1.0}, {1.9, 1.5, 0.3, 0.2}, {6.7, 0.0, 10.8, 2.2}},      // R in fp16
-                                {{1.9, 1.6, 0.9, 0.2}, {1.8, 1.8, 1.4, 0.3}, {2.3, 2.4, 2.1, 0.7}, {1.6, 2.1, 0.5, 0.2}, {7.1, 0.0, 16.0, 2.2}}};     // in 4 bits
+constexpr TCost kTCost[2][5] = {{{2.1, 1.1, 0.8, 0.5}, {2.0, 1.4, 1.2, 0.7}, {2.7, 1.6, 1.8, 1.0}, {1.9, 1.5, 0.3, 0.2}, {4.7, 1.7, 4.9, 1.5, 2.0, 2.2}},      // R in fp16
+                                {{1.9, 1.6, 0.9, 0.2}, {1.8, 1.8, 1.4, 0.3}, {2.3, 2.4, 2.1, 0.7}, {1.6, 2.1, 0.5, 0.2}, {5.5, 0.2, 8.3, 0.75, 1.8, 2.0}}};   // in 4 bits
+
+static double t_big_cost(int splits, int rank_pad, int m, int k, bool q4)
+{
+    const TCost &c = kTCost[q4][4];
+    const int cus = device_info().cus, share = kDies / splits;
+    const long tiles = (long)((rank_pad + 127) / 128) * ((m + 127) / 128), per_die = (tiles + share - 1) / share;
+    const long units = cus / kDies > 0 ? cus / kDies : 1;
+    const double w = per_die < units ? (double)per_die / units : 1.0;
+    const double t = c.a + (double)((per_die + units - 1) / units) * (c.b + (k / 128 + splits - 1) / splits * 0.128 * (c.c + c.d * w));
+    return splits > 1 ? t + c.e + c.f * splits * m * rank_pad * 1e-6 : t;
+}
+
+// The ranges of the inputs, up to those that the workspace has room for.
+int t_splits(int rank_pad, int m, int k, bool q4)
+{
+    int best = 1;
+    for (int s = 2; s <= gemm_t_splits(m, rank_pad, k); s *= 2)
+        if (t_big_cost(s, rank_pad, m, k, q4) < t_big_cost(best, rank_pad, m, k, q4)) best = s;
+    return best;
+}
 
 static double t_cost(int kind, int rank_pad, int m, int k, bool q4)
 {
+    if (kind == 4) return t_big_cost(t_splits(rank_pad, m, k, q4), rank_pad, m, k, q4);
     const TCost &c = kTCost[q4][kind];
     const int cus = device_info().cus;
-    if (kind == 4) {
-        const int splits = gemm_t_splits(m, rank_pad, k);
-        const long tiles = (long)((rank_pad + 255) / 256) * ((m + 127) / 128) * splits;
-        const double sums = splits > 1 ? (double)splits * m * rank_pad * 1e-6 : 0.0;
-        return 0.93 * (c.a + (double)((tiles + cus - 1) / cus) * c.c * k / splits * 1e-3 + c.d * sums);
-    }
     // tiles along the side that is dealt to the dies, and along the other
     constexpr int kSide[4][2] = {{32, 32}, {64, 32}, {64, 64}, {16, 16}};
     const int dealt = kind == 3 ? rank_pad : m, other = kind == 3 ? m : rank_pad;
@@ -459,11 +768,11 @@ static double t_cost(int kind, int rank_pad, int m, int k, bool q4)
     return r_us > t ? r_us : t;
 }
 
-// `split`: the split product may be taken (it leaves T as rows, not as pieces)
+// `split`: kind 4 may be taken (it leaves T as rows, not as pieces)
 int t_kind(int rank_pad, int m, int k, bool q4, bool split)
 {
     int best = 0;
-    for (int kind = 1; kind < (split ? 5 : 4); ++kind)
+    for (int kind = 1; kind < (split && m > 128 ? 5 : 4); ++kind)
         if (t_cost(kind, rank_pad, m, k, q4) < t_cost(best, rank_pad, m, k, q4)) best = kind;
     return best;
 }

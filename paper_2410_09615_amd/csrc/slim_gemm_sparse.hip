@@ -471,7 +471,7 @@ __global__ __launch_bounds__(256 * KW, KW) void gemm_sparse_kernel(SparseGemmArg
         const uint32_t tv = ((uint32_t)(t0 + srow) * rp + (uint32_t)r0 + (uint32_t)scol) * 2u;
         if (a.Lq) {
             const Q4Rows lq = q4_rows_operand(a.Lq, a.Ls, a.n, a.rank, o0, li, lb, r0);
-            dense_phase_q4<AT, 2, (KW > 1)>(lq, dt, tv, 32u * rp, scol, rlen, lds + li * SG_LD + 32 * lb, xr[0], stage_store);
+            dense_phase_q4<AT, (KW > 1)>(lq, dt, tv, 32u * rp, scol, rlen, lds + li * SG_LD + 32 * lb, xr[0], stage_store);
         } else {
             dense_phase<AT>(dl, lv, (rp / 16) * 1024u, 1024u, dt, tv, 32u * rp, rlen, lr, xr[0], stage_store);
         }

@@ -206,7 +206,7 @@ struct WorkspacePlan {
     size_t acc_off, acc_bytes;    // decode: partial quantized term, fp32 [slots][m][n]
     size_t part_off, part_bytes;  // gemm: split-K partials of T, fp32 [splits][m][rank_pad]
     size_t exp_off, exp_bytes;    // 4-bit adapters expanded to fp16 (adapter layout): L then R
-    int splits;                   // split-K factor of the T product
+    int splits;                   // ranges of inputs that part_bytes has room for
     size_t total;
 };
 

@@ -150,25 +150,23 @@ __host__ __device__ __forceinline__ int blocked_tile(int q, int tiles_o, int til
 //      a_step: bytes between steps), fetched three steps ahead into four rotating sets;
 //   B: 128 tokens x 128 inputs per stage staged through the LDS buffers like X
 //      (db, bv: this lane's staging offset for stage 0; b_pass: bytes between
-//      the passes of 16-byte loads; a stage is 128 BB bytes further), next stage's
-//      loads issued during steps 0-3 of the current one.  BB = 2: B is fp16, eight
-//      loads per lane and stage; BB = 1: B is 8-bit codes, four loads, which
-//      stage_store(buffer, registers, piece: one of them, or all with -1) expands to fp16 on their way into LDS.
+//      the passes of 16-byte loads; a stage is 256 bytes further), next stage's
+//      loads issued during steps 0-3 of the current one, eight per lane and stage, which
+//      stage_store(buffer, registers, piece: one of them, or all with -1) puts into LDS.
 // Loads past the end stay inside the descriptors or read as zero and are not
 // used; issuing them anyway keeps one path through the loop body.
 // Starts and ends with every wavefront past a barrier.
-template <int AT, int BB = 2, class Store>
+template <int AT, class Store>
 __device__ __forceinline__ void dense_phase(rsrc_t da, uint32_t av, uint32_t a_tile, uint32_t a_step, rsrc_t db,
                                             uint32_t bv,
-                                            uint32_t b_pass, int K, const half_t *lr, uint4_t (&xs)[XR * BB / 2],
+                                            uint32_t b_pass, int K, const half_t *lr, uint4_t (&xs)[XR],
                                             Store &&stage_store)
 {
-    constexpr int XRN = XR * BB / 2;              // 16-byte loads of a stage per lane
     const int nst = K / 16;                       // steps
     const int stages = (K + SG_BK - 1) / SG_BK;
     uint4_t la[4][AT];
 #pragma unroll
-    for (int p = 0; p < XRN; ++p) xs[p] = load16(db, bv, (uint32_t)p * b_pass);
+    for (int p = 0; p < XR; ++p) xs[p] = load16(db, bv, (uint32_t)p * b_pass);
 #pragma unroll
     for (int g = 0; g < 3; ++g)
 #pragma unroll
@@ -190,15 +188,15 @@ __device__ __forceinline__ void dense_phase(rsrc_t da, uint32_t av, uint32_t a_t
                 constexpr int it = itc;
                 if constexpr (it < AT)
                     la[(j + 3) & 3][it] = load16(da, av, (uint32_t)it * a_tile + (uint32_t)(g + 3) * a_step);
-                if constexpr (j < 4 && it < XRN / 4)
-                    xs[(XRN / 4) * j + it] =
-                        load16(db, bv, (uint32_t)(s + 1) * (SG_BK * BB) + (uint32_t)((XRN / 4) * j + it) * b_pass);
+                if constexpr (j < 4 && it < XR / 4)
+                    xs[(XR / 4) * j + it] =
+                        load16(db, bv, (uint32_t)(s + 1) * (SG_BK * 2) + (uint32_t)((XR / 4) * j + it) * b_pass);
                 if constexpr (j + 1 < 8)
                     b_nxt[it] = *reinterpret_cast<const half8_t *>(lr + u * SG_STAGE + it * 32 * SG_LD + 16 * (j + 1));
                 // the next stage's B, loaded four steps ago, goes into the other buffer (nobody reads it during
                 // this stage) piece by piece, not in the stage's tail
-                if constexpr (j >= 4 && it < XRN / 4)
-                    if (s + 1 < stages) stage_store(u ^ 1, xs, (XRN / 4) * (j - 4) + it);
+                if constexpr (j >= 4 && it < XR / 4)
+                    if (s + 1 < stages) stage_store(u ^ 1, xs, (XR / 4) * (j - 4) + it);
                 __builtin_amdgcn_sched_barrier(0);
                 static_for<AT>([&](auto ic) {
                     constexpr int i = ic;
@@ -258,12 +256,11 @@ __device__ __forceinline__ Q4Rows q4_rows_operand(const uint8_t *codes, const ha
 //      lane's share of a B stage, whose columns past K are replaced by zeros on their way into LDS.
 // LEAN: B fragments one block ahead instead of one step (12 registers fewer; for two wavefronts per SIMD).
 // Starts and ends with every wavefront past a barrier.
-template <int AT, int BB = 2, bool LEAN = false, class Store>
+template <int AT, bool LEAN, class Store>
 __device__ __forceinline__ void dense_phase_q4(const Q4Rows &qa, rsrc_t db, uint32_t bv, uint32_t b_pass, int bcol,
-                                               int K, const half_t *lrq, uint4_t (&xs)[XR * BB / 2],
+                                               int K, const half_t *lrq, uint4_t (&xs)[XR],
                                                Store &&stage_store)
 {
-    constexpr int XRN = XR * BB / 2;
     static_assert(AT <= NT, "one load per block refills a half stage");
     const int stages = (K + SG_BK - 1) / SG_BK;
     uint4_t cq[2][AT];             // [half of the stage][row tile]
@@ -278,14 +275,14 @@ __device__ __forceinline__ void dense_phase_q4(const Q4Rows &qa, rsrc_t db, uint
     auto zero_tail = [&](int s) {
         if (SG_BK * s + bcol >= K) {
 #pragma unroll
-            for (int p = 0; p < XRN; ++p) xs[p] = uint4_t{0u, 0u, 0u, 0u};
+            for (int p = 0; p < XR; ++p) xs[p] = uint4_t{0u, 0u, 0u, 0u};
         }
     };
     auto read_b = [&](int u, int it, int jj) {
         return *reinterpret_cast<const half8_t *>(lrq + u * SG_STAGE + it * 32 * SG_LD + 64 * (jj >> 2) + 8 * (jj & 3));
     };
 #pragma unroll
-    for (int p = 0; p < XRN; ++p) xs[p] = load16(db, bv, (uint32_t)p * b_pass);
+    for (int p = 0; p < XR; ++p) xs[p] = load16(db, bv, (uint32_t)p * b_pass);
 #pragma unroll
     for (int i = 0; i < AT; ++i) {
         fetch_codes(0, i, 0);
@@ -317,9 +314,9 @@ __device__ __forceinline__ void dense_phase_q4(const Q4Rows &qa, rsrc_t db, uint
                 if constexpr (jj == 2 && it < AT) fetch_scale(it, s + 1, sc_nxt);
                 if constexpr (jj == 3 && it < AT) fetch_codes(0, it, s + 1);
                 if constexpr (jj == 7 && it < AT) fetch_codes(1, it, s + 1);
-                if constexpr (jj < 4 && it < XRN / 4)
-                    xs[(XRN / 4) * jj + it] =
-                        load16(db, bv, (uint32_t)(s + 1) * (SG_BK * BB) + (uint32_t)((XRN / 4) * jj + it) * b_pass);
+                if constexpr (jj < 4 && it < XR / 4)
+                    xs[(XR / 4) * jj + it] =
+                        load16(db, bv, (uint32_t)(s + 1) * (SG_BK * 2) + (uint32_t)((XR / 4) * jj + it) * b_pass);
                 if constexpr (LEAN) {
                     b_cur[it] = b_nxt[0];
                     if constexpr (it + 1 < NT)
@@ -329,8 +326,8 @@ __device__ __forceinline__ void dense_phase_q4(const Q4Rows &qa, rsrc_t db, uint
                 } else if constexpr (jj + 1 < 8) {
                     b_nxt[it] = read_b(u, it, jj + 1);
                 }
-                if constexpr (jj >= 4 && it < XRN / 4) {
-                    constexpr int p = (XRN / 4) * (jj - 4) + it;
+                if constexpr (jj >= 4 && it < XR / 4) {
+                    constexpr int p = (XR / 4) * (jj - 4) + it;
                     if (s + 1 < stages) {
                         if (SG_BK * (s + 1) + bcol >= K) xs[p] = uint4_t{0u, 0u, 0u, 0u};
                         stage_store(u ^ 1, xs, p);

@@ -3,6 +3,8 @@ csrc/slim_gemm_mid.hip) against the oracle, at the sizes where that path can go 
 shapes with whole, ragged and partly empty tiles, T made in the same launch and in one of its own, one stage of
 inputs, stage counts that are no multiple of a round, ranks below and beyond whole rounds of the adapter term.
 The bounds are those of parity.py."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -235,6 +237,48 @@ def test_every_kind_of_t_product(n, k, r, m, t_kind, kind):
     else:
         err = _forward_case(_shape(n, k, r), m, B.slim_linear_gemm, seed=31, bits=bits)
     assert err <= TOL_Y
+
+
+@pytest.mark.parametrize("bits,xf", [(16, 0), (16, 1), (16, 2), (4, 0), (4, 1), (4, 2)])
+@pytest.mark.parametrize("m,r,k,splits", [
+    (1, 1, 128, 1), (127, 32, 256, 2), (128, 128, 384, 4), (129, 129, 640, 8), (260, 150, 1152, 2), (1100, 300, 512, 1), (1025, 33, 2048, 8),
+    (130, 40, 33024, 1)])
+def test_t_in_tiles_of_128(m, r, k, splits, bits, xf):
+    """The tiles of 128 ranks x 128 tokens alone: one and several tiles, their remainders on both sides, ranges of the inputs that are uneven
+    (five groups of 128 on two and eight) or empty, and more inputs than the 4-bit scales in LDS hold.  T is a sum in fp32, rounded to fp16 once."""
+    g = torch.Generator().manual_seed(k + m)
+    Rw = torch.randn(r, k, generator=g).half() * 0.05
+    L = torch.zeros(8, r, dtype=torch.half)
+    rp = B.slim_rank_pad(r)
+    if bits == 4:
+        q = B.slim_pack_adapters_q4(L.to(DEV), Rw.to(DEV))
+        Rq, Rs, R = q[2], q[3], None
+        codes, scales = B.slim_unpack_adapters_q4(Rq, Rs, r, k)
+        R64 = (codes.half().cpu() * scales.half().cpu().repeat_interleave(128, 1)[:, :k]).double()
+    else:
+        R, Rq, Rs, R64 = B.slim_pack_adapters(L.to(DEV), Rw.to(DEV))[1], None, None, Rw.double()
+    if xf:
+        f8 = torch.float8_e4m3fn if xf == 1 else torch.float8_e5m2
+        Xc = torch.randn(m, k, generator=g).to(f8)
+        X64, X, scale = Xc.double(), Xc.view(torch.uint8).to(DEV), torch.tensor([0.625], device=DEV)
+    else:
+        Xh = torch.randn(m, k, generator=g).half()
+        X64, X, scale = Xh.double(), Xh.to(DEV), torch.tensor([1.0], device=DEV)
+    T = torch.full((m, rp), float("nan"), dtype=torch.half, device=DEV)
+    P = torch.full((splits * m * rp,), float("nan"), device=DEV)
+    vp, i32 = ctypes.c_void_p, ctypes.c_int
+    f = B.lib()._ZN4slim14launch_t_splitEPKDF16_iPKfiiS1_PKhS1_iiPDF16_PfiP12ihipStream_t
+    f.argtypes = [vp, i32, vp, i32, i32, vp, vp, vp, i32, i32, vp, vp, i32, vp]
+    ptr = lambda t: None if t is None else t.data_ptr()
+    assert f(ptr(X), xf, ptr(scale), m, k, ptr(R), ptr(Rq), ptr(Rs), r, rp, ptr(T), ptr(P), splits, torch.cuda.current_stream().cuda_stream) == 0
+    s = float(scale)
+    ref, size = s * (X64 @ R64.T), s * (X64.abs() @ R64.abs().T)
+    # fp32: a rounding for each of at most k / 16 + 16 partial sums, of at most `size`; fp16: half a unit of the result
+    bound = (k / 16 + 16) * 2.0 ** -24 * size
+    bound = bound + 2.0 ** -11 * (ref.abs() + bound) + 2.0 ** -25
+    got = T.double().cpu()
+    assert bool(((got[:, :r] - ref).abs() <= bound).all())
+    assert bool((got[:, r:] == 0).all())
 
 
 def _tile_height(n, m):
