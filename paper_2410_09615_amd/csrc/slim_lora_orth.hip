@@ -792,6 +792,8 @@ __device__ __forceinline__ float column_scale(unsigned max_bits)
 // Where the step skips the orthonormalisation: 16 rows of out = `in` with scaled columns (colmax: kColSlots rows of bits of their
 // largest magnitudes).  clear: those of the next block, set to zero.
 // 16 rows of out = in Lc^-T, block column after block column; wavefront w computes the columns 16 w .. 16 w + 15 of each.
+// It is a chain of latencies (matrix cores 6.5 us of the 20).  The two fp16 numbers go out from the registers that hold a block column, and the wavefronts meet
+// before they need one another's columns, not after each block column: 1.2 us less than with the whole rows converted from LDS at the end.
 __global__ __launch_bounds__(256) void lora_apply_kernel(const float *__restrict__ in, float *__restrict__ out, int rows, int l, int nb,
                                                          const float *__restrict__ Lf, const float *__restrict__ D, half_t *__restrict__ hi,
                                                          half_t *__restrict__ lo, int ldk, OrthStep step,
@@ -807,21 +809,23 @@ __global__ __launch_bounds__(256) void lora_apply_kernel(const float *__restrict
     // only scaled, 4096 x 416: 14 -> 7 us with this and without the way through LDS)
     const int gx = (int)gridDim.x, bx = (int)blockIdx.x;
     const int r0 = (gx % 8 == 0 ? bx % 8 * (gx / 8) + bx / 8 : bx) * 16;
-    // the sixteen rows of column c as two fp16 numbers, columns as rows
-    auto emit = [&](int c, const float (&v16)[16]) {
-        half8_t h[2], g[2];
+    // N rows of column c from `row` on as two fp16 numbers, columns as rows
+    auto emit = [&](int c, int row, const auto &v16) {
+        constexpr int N = sizeof(v16) / sizeof(v16[0]), Q = N < 8 ? N : 8;
+        typedef half_t piece_t __attribute__((ext_vector_type(Q)));
+        const size_t at = (size_t)c * ldk + row;
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const float s = v16[r] * kBlockSplit, v = fabsf(s) > 65000.0f ? copysignf(65000.0f, s) : s;
-            const half_t x = (half_t)v;
-            h[r / 8][r % 8] = x;
-            g[r / 8][r % 8] = (half_t)(v - (float)x);
-        }
-        const size_t at = (size_t)c * ldk + r0;
+        for (int q = 0; q < N / Q; ++q) {
+            piece_t h, g;
 #pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            *reinterpret_cast<half8_t *>(hi + at + 8 * q) = h[q];
-            *reinterpret_cast<half8_t *>(lo + at + 8 * q) = g[q];
+            for (int r = 0; r < Q; ++r) {
+                const float s = v16[Q * q + r] * kBlockSplit, v = fabsf(s) > 65000.0f ? copysignf(65000.0f, s) : s;
+                const half_t x = (half_t)v;
+                h[r] = x;
+                g[r] = (half_t)(v - (float)x);
+            }
+            *reinterpret_cast<piece_t *>(hi + at + Q * q) = h;
+            *reinterpret_cast<piece_t *>(lo + at + Q * q) = g;
         }
     };
     if (clear)
@@ -842,7 +846,7 @@ __global__ __launch_bounds__(256) void lora_apply_kernel(const float *__restrict
             const float sc = column_scale(mx);
 #pragma unroll
             for (int r = 0; r < 16; ++r) v16[r] *= sc;
-            emit(c, v16);
+            emit(c, r0, v16);
         }
         return;
     }
@@ -877,6 +881,7 @@ __global__ __launch_bounds__(256) void lora_apply_kernel(const float *__restrict
 #pragma unroll
             for (int t = 0; t < 4; ++t) b[t] = Lj[(size_t)Kn * (kTileFloats / 4) + (wave * 4 + t) * 64 + lane];
             __builtin_amdgcn_sched_barrier(0);
+            if (K == J - 1) __syncthreads();     // (the other wavefronts' columns of the block column before this one)
 #pragma unroll
             for (int t = 0; t < 4; ++t) {
                 const float4_t a = *reinterpret_cast<const float4_t *>(O + ln * ldo + kOb * K + 16 * t + 4 * mq);
@@ -893,22 +898,16 @@ __global__ __launch_bounds__(256) void lora_apply_kernel(const float *__restrict
         float4_t y0 = {0.f, 0.f, 0.f, 0.f}, y1 = y0;
 #pragma unroll
         for (int t = 0; t < 4; ++t) mma16(*reinterpret_cast<const float4_t *>(V + ln * 68 + 16 * t + 4 * mq), dc[t], t & 1 ? y1 : y0);
+        float y[4];
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             const int row = r0 + 4 * mq + e;
-            const float y = y0[e] + y1[e];
-            O[(4 * mq + e) * ldo + kOb * J + 16 * wave + ln] = y;
-            if (out && row < rows && col < l) out[(size_t)row * l + col] = y;
+            y[e] = y0[e] + y1[e];
+            O[(4 * mq + e) * ldo + kOb * J + 16 * wave + ln] = y[e];
+            if (out && row < rows && col < l) out[(size_t)row * l + col] = y[e];
         }
-        __syncthreads();
+        if (hi && col < l) emit(col, r0 + 4 * mq, y);         // (rows past the last are zeros)
     }
-    if (hi)
-        for (int c = threadIdx.x; c < l; c += 256) {         // (rows past the last are zeros)
-            float v16[16];
-#pragma unroll
-            for (int r = 0; r < 16; ++r) v16[r] = O[r * ldo + c];
-            emit(c, v16);
-        }
 }
 
 // Workspace of the orth()s of a call, in floats: what the workgroups of a factorisation hand on, three sets of OrthWords, two times
