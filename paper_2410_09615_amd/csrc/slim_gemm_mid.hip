@@ -124,14 +124,14 @@ static int die_tiles(int tiles_o, int tiles_t) { return (tiles_o + kDies - 1) / 
 //   fp16 R, 8-bit X  64 (t / 2) + 16 ly + 8 (t % 2) + [0, 8): two steps share one 16-byte load of codes
 //   4-bit R          (64 / TT) ly + 8 t + [0, 8): the columns of a lane are consecutive (16 bytes of codes for four steps, one scale)
 constexpr int kTUnitLds = 8192;
-template <int XF, bool AQ, int TT>
+template <int XF, bool AQ, int TT, bool HIDE>
 __device__ __forceinline__ void t_tile(const MidArgs &a, int rt, int tt, char *lds_c, unsigned epoch)
 {
     constexpr int TW = kMidWaves + kMidHelpers, UN = 256 / TT, STEPS = UN / 32;
     constexpr int ROWB = XF ? UN : 2 * UN, PIECES = ROWB / 16, TPI = 64 / PIECES, NX = 16 * TT / TPI;
-    // (a thread number the compiler knows nothing of: nothing worked out of it stays in registers from one tile to the next)
+    // (HIDE: a thread number the compiler knows nothing of, so that nothing worked out of it stays in registers from one tile to the next)
     unsigned tid = threadIdx.x;
-    asm volatile("" : "+v"(tid));
+    if constexpr (HIDE) asm volatile("" : "+v"(tid));
     const int lane = tid & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
     const int lx = lane & 15, ly = lane >> 4;
@@ -1249,20 +1249,20 @@ __device__ __forceinline__ bool y_role(const MidArgs &a, int tid, int ot, int tt
 }
 
 // Tiles j, j + step, ... of T, and all of those along `count` token tiles from `first` on.
-template <int XF, bool AQ, int TT>
+template <int XF, bool AQ, int TT, bool HIDE>
 __device__ __forceinline__ void t_tiles(const MidArgs &a, int j, int step, char *lds_c, unsigned epoch)
 {
     for (; j < a.t_tiles; j += step) {
         int rt, tr;
-        if (tile_on_die(j, a.rank_pad / 16, rt, tr)) t_tile<XF, AQ, TT>(a, rt, tr, lds_c, epoch);
+        if (tile_on_die(j, a.rank_pad / 16, rt, tr)) t_tile<XF, AQ, TT, HIDE>(a, rt, tr, lds_c, epoch);
     }
 }
-template <int XF, bool AQ, int TT>
+template <int XF, bool AQ, int TT, bool HIDE>
 __device__ __forceinline__ void t_of_tokens(const MidArgs &a, int first, int count, char *lds_c, unsigned epoch)
 {
     for (int j = 0; j < a.rank_pad / 16 * count; ++j) {
         const int tr = first + j % count;
-        if (16 * TT * tr < a.m) t_tile<XF, AQ, TT>(a, j / count, tr, lds_c, epoch);
+        if (16 * TT * tr < a.m) t_tile<XF, AQ, TT, HIDE>(a, j / count, tr, lds_c, epoch);
     }
 }
 
@@ -1270,21 +1270,24 @@ template <int NT_, int RT, int RG, int KW, int XF, bool AQ>
 __global__ __launch_bounds__(kMidThreads, 3) void mid_kernel(MidArgs a)
 {
     extern __shared__ __attribute__((aligned(16))) char lds_c[];
+    // beside tiles of 128 x 64 the codes' tiles of T of 16 tokens are faster with what they work out kept from one to the next (18688 x 9984 at 38 tokens,
+    // two tiles each, 47.8 -> 45.5 us), beside those of 64 x 32 slower (12572 x 4992 at 20 tokens 13.65 -> 13.85), as with fp16 R
+    constexpr bool HIDE = !(AQ && NT_ == 2);
     const unsigned epoch = a.rank_pad > 0 && a.T ? call_epoch(a.epoch) : 0u;
     if ((int)blockIdx.x < a.n_t) {
         if (a.flags & kWideT)
-            t_tiles<XF, AQ, 2>(a, blockIdx.x, a.n_t, lds_c, epoch);
+            t_tiles<XF, AQ, 2, true>(a, blockIdx.x, a.n_t, lds_c, epoch);
         else
-            t_tiles<XF, AQ, 1>(a, blockIdx.x, a.n_t, lds_c, epoch);
+            t_tiles<XF, AQ, 1, HIDE>(a, blockIdx.x, a.n_t, lds_c, epoch);
         return;
     }
     int ot, tt;
     if (!tile_on_die((int)blockIdx.x - a.n_t, a.tiles_o, ot, tt)) return;
     if (!y_role<NT_, RT, RG, KW, XF, AQ, false>(a, threadIdx.x, ot, tt, lds_c, epoch)) return;
     if (a.flags & kWideT)
-        t_of_tokens<XF, AQ, 2>(a, NT_ * tt, NT_, lds_c, epoch);
+        t_of_tokens<XF, AQ, 2, true>(a, NT_ * tt, NT_, lds_c, epoch);
     else
-        t_of_tokens<XF, AQ, 1>(a, 2 * NT_ * tt, 2 * NT_, lds_c, epoch);
+        t_of_tokens<XF, AQ, 1, HIDE>(a, 2 * NT_ * tt, 2 * NT_, lds_c, epoch);
     asm volatile("s_waitcnt vmcnt(0)" : : : "memory");     // the pieces are in memory
     __syncthreads();
     // (a thread number the compiler knows nothing of: what it works out of it above would stay in registers until here)
@@ -1399,7 +1402,9 @@ struct MidPlan {
 // half as often, and each take longer), then two tiles, then three, and then a launch of T's own; a larger tile of Y that leaves room for one
 // instead of two is worth it from the smallest to the next only (us: 7452 x 2432 at 31 tokens, two tiles 10.1, one of 32 tokens 8.6, one of 16
 // beside the next tile of Y 8.2; 2244 x 3968 at 343 tokens T by itself 25.8, one of 32 tokens 17.6; 12523 x 7040 at 36 tokens two of 32 tokens
-// 27.7, the next tile of Y 36.8).  Of 216 layers of 512 to 28672 rows and 512 to 11008 inputs at 17 to 512 tokens this rule is 0.5 % from the best of all of
+// 27.7, the next tile of Y 36.8).  Not so where few workgroups have a second tile, at most a quarter, and the ranks are many: most of the ranks' work on Y
+// is done while those few are made (12572 x 4992, rank 499, at 20 tokens 64 tiles on 56 workgroups 13.3 against 14.0 us, 12572 x 3072 10.6 against 11.8; 104 tiles on 56,
+// 12572 x 8192, 25.0 against 21.8; below rank 384 tiles of 32 tokens were 5 to 24 % faster there, above it no more than 1 %).  Of 216 layers of 512 to 28672 rows and 512 to 11008 inputs at 17 to 512 tokens this rule is 0.5 % from the best of all of
 // these on average, and slower than two tiles of 16 or else the next tile of Y, as it was, in none by more than 5 %; 3 % faster on average, up to 1.47
 // times.
 // The adapter term alone has nothing to hide a chain of T behind: 4096 x 4096 at 128 tokens 15.7 / 12.5 / 15.2 / 20.1
@@ -1415,7 +1420,8 @@ MidPlan mid_plan(int n, int rank_pad, int m, int cus, bool weight_term)
         const int n_y = workgroups(g);
         if (n_y > cus) continue;
         if (rank_pad == 0) return {g, 0};
-        const int t16 = t_trips(rank_pad, m, 16, n_y, cus), t32 = t_trips(rank_pad, m, 32, n_y, cus);
+        int n16 = 0;
+        const int t16 = t_trips(rank_pad, m, 16, n_y, cus, &n16), t32 = t_trips(rank_pad, m, 32, n_y, cus);
         if (!weight_term) {
             if (g == 3 || n >= 16384) {
                 if (t16 <= 1) return {g, 16};
@@ -1427,8 +1433,9 @@ MidPlan mid_plan(int n, int rank_pad, int m, int cus, bool weight_term)
         }
         if (first.geometry < 0) first = {g, 0};
         if (t16 <= 1 || t32 <= 1) {
-            if (more.geometry < 0 || (more.geometry == 0 && g == 1)) return {g, t16 <= 1 ? 16 : 32};
-            return more;
+            if (more.geometry >= 0 && !(more.geometry == 0 && g == 1)) return more;
+            const bool few = t16 == 2 && rank_pad >= 384 && die_tiles(rank_pad / 16, (m + 15) / 16) - n16 <= n16 / 4;
+            return {g, t16 <= 1 || few ? 16 : 32};
         }
         if (more.geometry < 0 && (t16 <= 3 || t32 <= 2)) more = {g, t16 <= 2 || t32 > 2 ? 16 : 32};
     }

@@ -85,7 +85,9 @@ def _mid_plan(n, rank_pad, m, weight_term):
     (12523, 7040, 704, 36, {(1, 0): 41.0, (2, 0): 33.0, (2, 16): 29.8, (2, 32): 27.7, (3, 16): 36.8}),
     (11008, 8192, 819, 48, {(1, 0): 41.2, (2, 0): 32.9, (2, 16): 25.2, (2, 32): 26.0, (3, 16): 35.4}),
     (5120, 5120, 512, 48, {(0, 0): 23.0, (1, 0): 17.2, (1, 16): 11.7, (1, 32): 13.2, (2, 16): 15.7}),
-    (13056, 3200, 320, 148, {(-1, 0): 29.9, (3, 0): 39.7})])
+    (13056, 3200, 320, 148, {(-1, 0): 29.9, (3, 0): 39.7}),
+    (12572, 3072, 499, 20, {(1, 16): 10.6, (1, 32): 11.8}),
+    (12572, 8192, 819, 20, {(1, 16): 25.0, (1, 32): 21.8})])
 def test_the_plan_of_small_batches(n, k, r, m, us):
     """Tile and T of whole layers: the plan taken is within a tenth of the best one measured."""
     assert us[_mid_plan(n, B.slim_rank_pad(r), m, True)] <= 1.1 * min(us.values())
