@@ -218,7 +218,7 @@ int slim_quant_search_rows(const float *W, slim_shape shape, float *scale_out, f
  * is as near the exact iterate's as with two in a row at most up to a factor of 1.5, and as with every block orthonormal
  * up to one of about 3 (replayed on the CPU: 2e-6 to 2e-5 in the 2-norm, where fp16 rounds at 5e-4).
  * workspace: slim_adapters_workspace_bytes (HOST out-pointer; about 12 n k bytes -- S in fp32, S and its transpose as
- * two fp16 matrices -- plus 20 to 45 bytes per element of a block of max(n, k) x rank_pad), need not be zeroed.  Errors: NULL, SHAPE, ALIGN, WORKSPACE, HIP.
+ * two fp16 matrices -- plus 19 to 50 bytes per element of a block of max(n, k) x rank_pad, on small layers a few MB more), need not be zeroed.  Errors: NULL, SHAPE, ALIGN, WORKSPACE, HIP.
  * The workgroups of a factorisation hand tiles to one another; those waits are bounded, and should one run out, L and R are NaN.
  * The call has returned SLIM_OK by then and there is no error word: diag[2] is infinite, which is how a caller detects it.
  */
