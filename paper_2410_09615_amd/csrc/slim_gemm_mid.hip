@@ -1404,7 +1404,7 @@ struct MidPlan {
 // beside the next tile of Y 8.2; 2244 x 3968 at 343 tokens T by itself 25.8, one of 32 tokens 17.6; 12523 x 7040 at 36 tokens two of 32 tokens
 // 27.7, the next tile of Y 36.8).  Not so where few workgroups have a second tile, at most a quarter, and the ranks are many: most of the ranks' work on Y
 // is done while those few are made (12572 x 4992, rank 499, at 20 tokens 64 tiles on 56 workgroups 13.3 against 14.0 us, 12572 x 3072 10.6 against 11.8; 104 tiles on 56,
-// 12572 x 8192, 25.0 against 21.8; below rank 384 tiles of 32 tokens were 5 to 24 % faster there, above it no more than 1 %).  Of 216 layers of 512 to 28672 rows and 512 to 11008 inputs at 17 to 512 tokens this rule is 0.5 % from the best of all of
+// 12572 x 8192, 25.0 against 21.8; 2688 x 4736 with 4-bit adapters, rank 268, at 79 tokens 12.8 against 13.0; below rank 256, and beside tiles of 32 rows, those of 32 tokens were 5 to 24 % faster).  Of 216 layers of 512 to 28672 rows and 512 to 11008 inputs at 17 to 512 tokens this rule is 0.5 % from the best of all of
 // these on average, and slower than two tiles of 16 or else the next tile of Y, as it was, in none by more than 5 %; 3 % faster on average, up to 1.47
 // times.
 // The adapter term alone has nothing to hide a chain of T behind: 4096 x 4096 at 128 tokens 15.7 / 12.5 / 15.2 / 20.1
@@ -1434,7 +1434,7 @@ MidPlan mid_plan(int n, int rank_pad, int m, int cus, bool weight_term)
         if (first.geometry < 0) first = {g, 0};
         if (t16 <= 1 || t32 <= 1) {
             if (more.geometry >= 0 && !(more.geometry == 0 && g == 1)) return more;
-            const bool few = t16 == 2 && rank_pad >= 384 && die_tiles(rank_pad / 16, (m + 15) / 16) - n16 <= n16 / 4;
+            const bool few = t16 == 2 && g > 0 && rank_pad >= 256 && die_tiles(rank_pad / 16, (m + 15) / 16) - n16 <= n16 / 4;
             return {g, t16 <= 1 || few ? 16 : 32};
         }
         if (more.geometry < 0 && (t16 <= 3 || t32 <= 2)) more = {g, t16 <= 2 || t32 > 2 ? 16 : 32};
