@@ -451,7 +451,7 @@ __device__ __forceinline__ void strip_role(const FactorArgs &a, int g, rsrc_t ws
         while (left >= a.nb - j) left -= a.nb - j++;
         const int I = j + left, q = task & 3;
         wait_gram(a, hand, a.splits, lane, lost, [&](int i) { return tri(I, j) * a.splits + i; });
-        float4_t sum[1], s0 = {0.f, 0.f, 0.f, 0.f}, s1 = s0;
+        float4_t sum[1];
         gram_blocks(a, ws, tri(I, j), q, wave, lane, sum);
         float4_t c = sum[0];
         for (int K = 0; K < (I == j ? j - 1 : j); ++K) {
@@ -462,10 +462,12 @@ __device__ __forceinline__ void strip_role(const FactorArgs &a, int g, rsrc_t ws
                 x[t] = load_dev(ws, block(at.Lf, tri(I, K), q, t));
                 y[t] = load_dev(ws, block(at.Lf, tri(j, K), wave, t));
             }
+            // (one column at a time: what is left of c grows smaller, and its rounding with it, where the sum of all columns would grow)
+            float4_t s0 = {0.f, 0.f, 0.f, 0.f}, s1 = s0;
 #pragma unroll
             for (int t = 0; t < 4; ++t) mul16(x[t], y[t], t & 1 ? s1 : s0);
+            c -= s0 + s1;
         }
-        c -= s0 + s1;
         if (I <= j + 1) {
             store_dev(ws, block(at.G, tri(I, j), q, wave), c);
             hand_over(a, (I == j ? kHandT : kHandA) + 16 * I + 4 * q + wave, lane);
@@ -712,9 +714,12 @@ __device__ __forceinline__ void chain_role(const FactorArgs &a, rsrc_t ws, rsrc_
                         if constexpr (b < 3) {
                             // column b of this row
                             float4_t c0 = zero, c1 = zero;
-                            if (j > 0)
+                            if (j > 0) {
 #pragma unroll
                                 for (int t = 0; t < 4; ++t) mul16(pw[t], s.P[4 * b + t][lane], t & 1 ? c1 : c0);
+                                to[b] -= c0 + c1;
+                                c0 = c1 = zero;
+                            }
                             for (int k = 0; k < b - 1; ++k) mul16(s.L[tri(wave - 1, k)][lane], s.L[tri(b - 1, k)][lane], c0);
                             mul16(lw, lb, c1);
                             s.T[tri(wave, b)][lane] = to[b] - (c0 + c1);

@@ -6,6 +6,8 @@ library's own L.  L and R are rounded to fp16 once: entries of L^T L are sums of
 with 2^-11 relative error each, at most 2^-10 per entry for unit columns (Cauchy-Schwarz), taken at twice that;
 R is off by its own rounding, 2^-11, and by that of L it is compared with, 2^-11 of ||S|| / ||L^T S||, taken
 at four times their sum."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -77,6 +79,36 @@ def test_factorisations_of_every_number_of_tiles(n, k, r):
     """One tile and several, as many strips as workgroups for them and more, row counts that divide into none of the ranges:
     what holds above, after a round whose blocks are all orthonormalised."""
     test_adapters_are_orthonormal_and_project_the_error(n, k, r, 1)
+
+
+def _orth(Y):
+    """One orthonormalisation by the library: out with in = out Lc^T."""
+    rows, l = Y.shape
+    vp, i32 = ctypes.c_void_p, ctypes.c_int
+    floats, words, launch = B.lib()._ZN4slim11orth_floatsEi, B.lib()._ZN4slim15orth_hand_wordsEv, \
+        B.lib()._ZN4slim11launch_orthEPKfPfPDF16_S3_iiS2_PjjiiP12ihipStream_t
+    floats.argtypes, floats.restype, words.restype = [i32], ctypes.c_size_t, ctypes.c_size_t
+    launch.argtypes = [vp, vp, vp, vp, i32, i32, vp, vp, ctypes.c_uint, i32, i32, vp]
+    out, ws, hand = torch.empty_like(Y), torch.empty(floats(l), device=DEV), torch.zeros(words(), dtype=torch.int32, device=DEV)
+    assert launch(Y.data_ptr(), out.data_ptr(), None, None, rows, l, ws.data_ptr(), hand.data_ptr(), 1, -1, 2,
+                  torch.cuda.current_stream().cuda_stream) == 0
+    torch.cuda.synchronize()
+    return out
+
+
+@pytest.mark.parametrize("rows,l", [(4096, 640), (2048, 768)])
+def test_a_factorisation_is_as_near_as_the_hosts(rows, l):
+    """One block of columns that have a direction in common, so that most of a Gram matrix is subtracted again: no further from binary64
+    than the same steps (Gram matrix, Cholesky factor, triangular solution) of the host's library in binary32."""
+    g = torch.Generator().manual_seed(rows + l)
+    Y = torch.randn(rows, l, generator=g)
+    Y = Y @ (torch.randn(l, l, generator=g) * 0.3 / l ** 0.5 + torch.eye(l)) + 0.5
+
+    def host(A):
+        return torch.linalg.solve_triangular(torch.linalg.cholesky(A.T @ A), A.T.contiguous(), upper=False).T.double()
+
+    exact = host(Y.double())
+    assert float((_orth(Y.to(DEV)).cpu().double() - exact).norm()) <= float((host(Y) - exact).norm())
 
 
 def start_block(rows, cols, r, seed=1):
