@@ -229,7 +229,8 @@ __host__ __device__ int orth_due(int h, int run, int last)
 // A workgroup waits for workgroups of a lower index, and the chain for strips that wait for it in no more than it has
 // handed on: with workgroups started in the order of their index there is always one that runs.  A wait is bounded all the
 // same; should something not come, lora_apply_kernel makes the block NaN.
-constexpr int kGramUnits = 256;                // partial tiles, at most
+constexpr int kGramUnits = 640;                // partial tiles, at most
+constexpr int kGramRun = 256;                  // rows added up by themselves
 constexpr int kStripGroups = 112;              // workgroups of strips, at most (a call on each of four hardware queues has room for them)
 struct FactorArgs {
     const float *Y;
@@ -346,29 +347,59 @@ __device__ __forceinline__ void gram_unit(const FactorArgs &a, int tile, int z, 
 #pragma unroll
         for (int e = 0; e < 16; ++e) acc[n][e] = 0.f;
     auto ld = [&](bool ok, uint32_t c, uint32_t row) { return load8(rs, ok ? c + row * (uint32_t)l * 4u : 0xFFFFFF00u, 0u); };
+    // What kGramRun rows add up to goes to LDS (there are no registers left), to what came before: a sum is rounded once for every pair of rows,
+    // at the size it has by then.
+    float4_t *const before = red + wave * 16 * kWave + lane;
+    bool any = false;
+    auto add_before = [&] {
+#pragma unroll
+        for (int n = 0; n < 4; ++n)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const float4_t v = before[(4 * n + q) * kWave];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) acc[n][4 * q + e] += v[e];
+            }
+    };
     constexpr int U = 16;                       // pairs of rows in flight
+    static_assert(kGramRun % (2 * U) == 0, "whole trips");
     uint2_t av[U], bv[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
         av[u] = ld(na < l, ca, (uint32_t)(2 * u));
         bv[u] = ld(nb < l, cb, (uint32_t)(2 * u));
     }
-    for (int k = 0; k < cnt; k += 2 * U)
+    for (int k = 0; k < cnt;) {
+        for (const int end = min(cnt, k + kGramRun); k < end; k += 2 * U)
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            float av2[2], bv2[2];
+            for (int u = 0; u < U; ++u) {
+                float av2[2], bv2[2];
 #pragma unroll
-            for (int b = 0; b < 2; ++b) {
-                const uint32_t x = av[u][b], y = bv[u][b];
-                av2[b] = __builtin_bit_cast(float, x);
-                bv2[b] = __builtin_bit_cast(float, y);
+                for (int b = 0; b < 2; ++b) {
+                    const uint32_t x = av[u][b], y = bv[u][b];
+                    av2[b] = __builtin_bit_cast(float, x);
+                    bv2[b] = __builtin_bit_cast(float, y);
+                }
+#pragma unroll
+                for (int n = 0; n < 4; ++n) acc[n] = __builtin_amdgcn_mfma_f32_32x32x2f32(bv2[n % 2], av2[n / 2], acc[n], 0, 0, 0);
+                av[u] = ld(na < l, ca, (uint32_t)(k + 2 * (U + u)));
+                bv[u] = ld(nb < l, cb, (uint32_t)(k + 2 * (U + u)));
+                __builtin_amdgcn_sched_barrier(0);
             }
+        if (k >= cnt) break;
+        if (any) add_before();
+        any = true;
 #pragma unroll
-            for (int n = 0; n < 4; ++n) acc[n] = __builtin_amdgcn_mfma_f32_32x32x2f32(bv2[n % 2], av2[n / 2], acc[n], 0, 0, 0);
-            av[u] = ld(na < l, ca, (uint32_t)(k + 2 * (U + u)));
-            bv[u] = ld(nb < l, cb, (uint32_t)(k + 2 * (U + u)));
-            __builtin_amdgcn_sched_barrier(0);
-        }
+        for (int n = 0; n < 4; ++n)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                before[(4 * n + q) * kWave] = float4_t{acc[n][4 * q], acc[n][4 * q + 1], acc[n][4 * q + 2], acc[n][4 * q + 3]};
+#pragma unroll
+                for (int e = 0; e < 4; ++e) acc[n][4 * q + e] = 0.f;
+            }
+    }
+    if (any) add_before();
+    if (per > kGramRun) __syncthreads();         // (LDS is used again)
     // register 4 q + e of acc[n], row 8 q + 4 h + e of the result.  Wavefront w adds up those with q = w: the others leave their part of
     // them (q, slot of three) in LDS
     auto slot = [](int q, int w) { return (3 * q + (w < q ? w : w - 1)) * 4 * kWave; };
@@ -775,12 +806,13 @@ __device__ __forceinline__ void chain_role(const FactorArgs &a, rsrc_t ws, rsrc_
 __global__ __launch_bounds__(256, 2) void lora_factor_kernel(FactorArgs a)
 {
     if (a.step.skip()) return;
-    __shared__ __attribute__((aligned(16))) ChainLds s;
-    static_assert(sizeof(ChainLds) >= 12 * 4 * kWave * 16, "LDS of a gram unit");
+    __shared__ float4_t lds[4 * 16 * kWave];                 // (of a gram unit: the registers of its wavefronts)
+    static_assert(sizeof(ChainLds) <= sizeof(lds), "LDS of the chain");
+    ChainLds &s = *reinterpret_cast<ChainLds *>(lds);
     const rsrc_t ws = make_rsrc(a.ws, FactorPlaces(a.nb).end), hand = make_rsrc(a.hand, kHandWords * 4u);
     const int units = a.tiles * a.splits, b = (int)blockIdx.x;
     if (b < units)
-        gram_unit(a, b / a.splits, b % a.splits, ws, reinterpret_cast<float4_t *>(&s));       // (a range of rows on one die, where their number is a multiple of 8)
+        gram_unit(a, b / a.splits, b % a.splits, ws, lds);       // (a range of rows on one die, where their number is a multiple of 8)
     else if (b == units)
         chain_role(a, ws, hand, s);
     else
@@ -915,6 +947,23 @@ __global__ __launch_bounds__(256) void lora_apply_kernel(const float *__restrict
     }
 }
 
+// Into how many ranges of rows the units of a tile of G go, and how many rows each has.  A workgroup per compute unit, at least 64 rows each, and no
+// more than kGramRange as long as there is room: the matrix cores' work decides then, which 136 units (1024 columns) would leave to half of the chip, and
+// the bytes of a quarter of a range (a wavefront's part) have to have 32-bit offsets.
+// us and relative error of a block, in brackets with a workgroup per compute unit at any number of rows and no kGramRun: 28672 x 832 556, 6.7e-7 (596, 1.9e-6),
+// 28672 x 1024 806, 7.4e-7 (954, 3.9e-6), 4096 x 1024 265, 1.0e-6 (266, 2.2e-6).
+constexpr int kGramRange = 4096;
+int gram_ranges(int rows, int l, int *rows_each)
+{
+    const int nb = (l + kOb - 1) / kOb, tiles = tri(nb, 0);
+    int n = 256 / tiles;
+    if (n > (rows + 63) / 64) n = (rows + 63) / 64;
+    if (((long)rows + n - 1) / n > kGramRange) n = (int)min((long)kGramUnits / tiles, ((long)rows + kGramRange - 1) / kGramRange);
+    if (n > kDies) n = n / kDies * kDies;
+    *rows_each = (int)((((long)rows + n - 1) / n + 31) / 32 * 32);
+    return (int)(((long)rows + *rows_each - 1) / *rows_each);
+}
+
 // Workspace of the orth()s of a call, in floats: what the workgroups of a factorisation hand on, three sets of OrthWords, two times
 // kColSlots rows of column maxima.
 constexpr int kOrthWords = 64;
@@ -950,12 +999,7 @@ int launch_orth(const float *in, float *out, half_t *hi, half_t *lo, int rows, i
     f.hand = hand;
     f.seq = seq;
     f.step = step;
-    // a workgroup per compute unit, at least 64 rows each
-    int splits = kGramUnits / tiles;
-    if (splits > (rows + 63) / 64) splits = (rows + 63) / 64;
-    if (splits > kDies) splits = splits / kDies * kDies;
-    f.zrows = ((rows + splits - 1) / splits + 31) / 32 * 32;
-    f.splits = (rows + f.zrows - 1) / f.zrows;
+    f.splits = gram_ranges(rows, l, &f.zrows);
     const bool wait_test = adapters_wait_test();     // (slim_decode_override: only the workgroup that waits for the others)
     f.strips = wait_test ? 0 : 4 * (tiles - 1) < kStripGroups ? 4 * (tiles - 1) : kStripGroups;
     f.polls = wait_test ? 256 : kHandPolls;

@@ -96,7 +96,7 @@ def _orth(Y):
     return out
 
 
-@pytest.mark.parametrize("rows,l", [(4096, 640), (2048, 768)])
+@pytest.mark.parametrize("rows,l", [(4096, 640), (2048, 768), (4096, 1024), (28672, 1024), (33000, 832)])
 def test_a_factorisation_is_as_near_as_the_hosts(rows, l):
     """One block of columns that have a direction in common, so that most of a Gram matrix is subtracted again: no further from binary64
     than the same steps (Gram matrix, Cholesky factor, triangular solution) of the host's library in binary32."""

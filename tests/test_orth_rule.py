@@ -52,6 +52,22 @@ def test_the_last_run_is_short(run, last):
         assert sum(steps) == last and steps[0] == min(first, last - 4 if last > 4 else last)
 
 
+@pytest.mark.parametrize("l", [32, 64, 96, 256, 416, 640, 832, 992, 1024])
+@pytest.mark.parametrize("rows", [1, 31, 64, 65, 1000, 4096, 4097, 28672, 28673, 100000, (1 << 22) - 32, 1 << 22, (1 << 22) + 1, (1 << 24) - 4096])
+def test_ranges_of_rows_of_a_gram_matrix(rows, l):
+    """They are the rows, fit the workspace's partial tiles, and a wavefront's quarter of one, with the rows it reads ahead, has 32-bit
+    offsets in bytes; none is much longer than 4096 rows while there is room for more."""
+    f, each = B.lib()._ZN4slim11gram_rangesEiiPi, ctypes.c_int()
+    f.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_void_p]
+    n, nb = f(rows, l, ctypes.byref(each)), -(-l // 64)
+    tiles = nb * (nb + 1) // 2
+    assert (n - 1) * each.value < rows <= n * each.value and each.value % 32 == 0
+    assert 1 <= n and n * tiles <= 640
+    assert (each.value // 4 + 64) * l * 4 < 1 << 32
+    most = 640 // tiles if 640 // tiles <= 8 else 640 // tiles // 8 * 8
+    assert each.value <= 4096 * 9 // 8 + 32 or n == most          # (more than eight ranges are a multiple of eight)
+
+
 def _orth(Y):
     """Cholesky QR in binary32, columns in order: (block, largest pivot, smallest pivot)."""
     A = (Y.T @ Y).astype(np.float32)
