@@ -226,17 +226,16 @@ __host__ __device__ int orth_due(int h, int run, int last)
 // What one workgroup makes for others goes through memory: stored past the L2 (device scope), waited for, and then named by words
 // that hold the number of the orth(), which the readers poll.  They read it past their L2 as well, so there are no fences (write-back and
 // invalidation of an L2 are over a microsecond each).
-// A workgroup waits for workgroups of a lower index, and the chain for strips that wait for it in no more than it has
-// handed on: with workgroups started in the order of their index there is always one that runs.  A wait is bounded all the
-// same; should something not come, lora_apply_kernel makes the block NaN.
+// A gram unit waits for nothing, a strip for strips of a lower index and for diagonal tiles, and a diagonal tile of column j for strips that come
+// before all strips that wait for it: with workgroups started in the order of their index, room for the chain and one strip is enough.
+// A workgroup that made several strips, one after the other, would wait with its second for strips of a higher index, whose workgroups may not have
+// room to start.  A wait is bounded all the same; should something not come, lora_apply_kernel makes the block NaN.
 constexpr int kGramUnits = 640;                // partial tiles, at most
 constexpr int kGramRun = 256;                  // rows added up by themselves
-constexpr int kStripGroups = 112;              // workgroups of strips, at most (a call on each of four hardware queues has room for them)
 struct FactorArgs {
     const float *Y;
     int rows, l, nb, tiles;
     int splits, zrows;                         // ranges of rows, rows in each
-    int strips;                                // workgroups of strips
     float *ws;                                 // orth_floats() (offsets: FactorPlaces)
     unsigned *hand;
     unsigned seq;
@@ -467,61 +466,67 @@ __device__ __forceinline__ void gram_blocks(const FactorArgs &a, rsrc_t ws, int 
     }
 }
 
-// Strips g, g + strips, ... in the order (column, row tile, strip): wavefront w makes the 16 columns 16 w .. of 16 rows of the tile (I, j).
+// The strips in the order (column j, row tile I, sixteen rows q), but for those of the first diagonal tile, which is the chain's alone.
+__host__ __device__ void strip_at(int strip, int nb, int *I, int *j, int *q)
+{
+    int c = 0, left = strip / 4 + 1;
+    while (left >= nb - c) left -= nb - c++;
+    *I = c + left;
+    *j = c;
+    *q = strip % 4;
+}
+
+// Wavefront w makes the 16 columns 16 w .. of 16 rows of the tile (I, j).
 // It adds up the partial tiles, subtracts L_IK L_jK^T for the columns K before its own as they come, and hands the strip to the chain or waits
 // for the inverse of the diagonal tile and hands on L_Ij = A_Ij X_j^T.
-__device__ __forceinline__ void strip_role(const FactorArgs &a, int g, rsrc_t ws, rsrc_t hand, float4_t *sh)
+__device__ __forceinline__ void strip_role(const FactorArgs &a, int strip, rsrc_t ws, rsrc_t hand, float4_t *sh)
 {
     const int lane = threadIdx.x & 63, mq = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const FactorPlaces at(a.nb);
     auto block = [&](uint32_t region, int tile, int q, int t) { return region + (uint32_t)tile * (kTileFloats * 4) + (uint32_t)((q * 4 + t) * 64 + lane) * 16u; };
     bool lost = false;
-    for (int task = 4 + g; task < 4 * a.tiles; task += a.strips) {
-        int j = 0, left = task >> 2;
-        while (left >= a.nb - j) left -= a.nb - j++;
-        const int I = j + left, q = task & 3;
-        wait_gram(a, hand, a.splits, lane, lost, [&](int i) { return tri(I, j) * a.splits + i; });
-        float4_t sum[1];
-        gram_blocks(a, ws, tri(I, j), q, wave, lane, sum);
-        float4_t c = sum[0];
-        for (int K = 0; K < (I == j ? j - 1 : j); ++K) {
-            wait_words(a, hand, lane == 0 ? kHandL + 16 * tri(I, K) + 4 * q : lane == 1 ? kHandL + 16 * tri(j, K) + 4 * wave : -1, lost);
-            float4_t x[4], y[4];
+    int I, j, q;
+    strip_at(strip, a.nb, &I, &j, &q);
+    wait_gram(a, hand, a.splits, lane, lost, [&](int i) { return tri(I, j) * a.splits + i; });
+    float4_t sum[1];
+    gram_blocks(a, ws, tri(I, j), q, wave, lane, sum);
+    float4_t c = sum[0];
+    for (int K = 0; K < (I == j ? j - 1 : j); ++K) {
+        wait_words(a, hand, lane == 0 ? kHandL + 16 * tri(I, K) + 4 * q : lane == 1 ? kHandL + 16 * tri(j, K) + 4 * wave : -1, lost);
+        float4_t x[4], y[4];
 #pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                x[t] = load_dev(ws, block(at.Lf, tri(I, K), q, t));
-                y[t] = load_dev(ws, block(at.Lf, tri(j, K), wave, t));
-            }
-            // (one column at a time: what is left of c grows smaller, and its rounding with it, where the sum of all columns would grow)
-            float4_t s0 = {0.f, 0.f, 0.f, 0.f}, s1 = s0;
-#pragma unroll
-            for (int t = 0; t < 4; ++t) mul16(x[t], y[t], t & 1 ? s1 : s0);
-            c -= s0 + s1;
+        for (int t = 0; t < 4; ++t) {
+            x[t] = load_dev(ws, block(at.Lf, tri(I, K), q, t));
+            y[t] = load_dev(ws, block(at.Lf, tri(j, K), wave, t));
         }
-        if (I <= j + 1) {
-            store_dev(ws, block(at.G, tri(I, j), q, wave), c);
-            hand_over(a, (I == j ? kHandT : kHandA) + 16 * I + 4 * q + wave, lane);
-            if (I == j) continue;
-        }
-        sh[wave * 64 + lane] = c;
-        __syncthreads();
-        wait_words(a, hand, lane == 0 ? kHandD + 16 * j : -1, lost);
-        float4_t x[4];
+        // (one column at a time: what is left of c grows smaller, and its rounding with it, where the sum of all columns would grow)
+        float4_t s0 = {0.f, 0.f, 0.f, 0.f}, s1 = s0;
 #pragma unroll
-        for (int t = 0; t < 4; ++t) x[t] = t <= wave ? load_dev(ws, block(at.D, j, wave, t)) : float4_t{0.f, 0.f, 0.f, 0.f};
-        const float4_t alive = load_dev(ws, at.D + (uint32_t)j * (kTileFloats * 4) + 1024u + (uint32_t)(16 * wave + 4 * mq) * 4u);
-        float4_t y0 = {0.f, 0.f, 0.f, 0.f}, y1 = y0;
-#pragma unroll
-        for (int t = 0; t < 4; ++t)
-            if (t <= wave) mul16(sh[t * 64 + lane], x[t], t & 1 ? y1 : y0);
-        float4_t y = y0 + y1;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) y[e] = alive[e] != 0.f ? y[e] : 0.f;
-        store_dev(ws, block(at.Lf, tri(I, j), q, wave), y);
-        hand_over(a, kHandL + 16 * tri(I, j) + 4 * q + wave, lane);
-        __syncthreads();                         // sh has been read
+        for (int t = 0; t < 4; ++t) mul16(x[t], y[t], t & 1 ? s1 : s0);
+        c -= s0 + s1;
     }
+    if (I <= j + 1) {
+        store_dev(ws, block(at.G, tri(I, j), q, wave), c);
+        hand_over(a, (I == j ? kHandT : kHandA) + 16 * I + 4 * q + wave, lane);
+        if (I == j) return;
+    }
+    sh[wave * 64 + lane] = c;
+    __syncthreads();
+    wait_words(a, hand, lane == 0 ? kHandD + 16 * j : -1, lost);
+    float4_t x[4];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) x[t] = t <= wave ? load_dev(ws, block(at.D, j, wave, t)) : float4_t{0.f, 0.f, 0.f, 0.f};
+    const float4_t alive = load_dev(ws, at.D + (uint32_t)j * (kTileFloats * 4) + 1024u + (uint32_t)(16 * wave + 4 * mq) * 4u);
+    float4_t y0 = {0.f, 0.f, 0.f, 0.f}, y1 = y0;
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+        if (t <= wave) mul16(sh[t * 64 + lane], x[t], t & 1 ? y1 : y0);
+    float4_t y = y0 + y1;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) y[e] = alive[e] != 0.f ? y[e] : 0.f;
+    store_dev(ws, block(at.Lf, tri(I, j), q, wave), y);
+    hand_over(a, kHandL + 16 * tri(I, j) + 4 * q + wave, lane);
 }
 
 // LDS of the chain, in 16 x 16 blocks in operand order.
@@ -1001,9 +1006,8 @@ int launch_orth(const float *in, float *out, half_t *hi, half_t *lo, int rows, i
     f.step = step;
     f.splits = gram_ranges(rows, l, &f.zrows);
     const bool wait_test = adapters_wait_test();     // (slim_decode_override: only the workgroup that waits for the others)
-    f.strips = wait_test ? 0 : 4 * (tiles - 1) < kStripGroups ? 4 * (tiles - 1) : kStripGroups;
     f.polls = wait_test ? 256 : kHandPolls;
-    hipLaunchKernelGGL(lora_factor_kernel, dim3((unsigned)(tiles * f.splits + 1 + f.strips)), dim3(256), 0, st, f);
+    hipLaunchKernelGGL(lora_factor_kernel, dim3((unsigned)(tiles * f.splits + 1 + (wait_test ? 0 : 4 * (tiles - 1)))), dim3(256), 0, st, f);
     const size_t lds = (size_t)(16 * (nb * kOb + 4) + 16 * 68) * sizeof(float);
     hipLaunchKernelGGL(lora_apply_kernel, dim3((unsigned)((rows + 31) / 32 * 2)), dim3(256), lds, st, in, out, rows, l, nb,
                        (const float *)(ws + at.Lf / 4), (const float *)(ws + at.D / 4), hi, lo, (rows + 31) / 32 * 32, step, colmax, clear,

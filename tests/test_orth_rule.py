@@ -68,6 +68,40 @@ def test_ranges_of_rows_of_a_gram_matrix(rows, l):
     assert each.value <= 4096 * 9 // 8 + 32 or n == most          # (more than eight ranges are a multiple of eight)
 
 
+@pytest.mark.parametrize("nb", range(1, 17))
+@pytest.mark.parametrize("room", [1, 2, 57])
+def test_a_factorisation_ends_with_room_for_few_workgroups(nb, room):
+    """A workgroup per strip, started in the order of their index as those before them end, beside the one of the diagonal tiles: with room
+    for a single strip all of them end.  What waits for what is replayed from the order in which the library has the strips."""
+    f, out = B.lib()._ZN4slim8strip_atEiiPiS0_S0_, [ctypes.c_int() for _ in range(3)]
+    f.argtypes, f.restype = [ctypes.c_int] * 2 + [ctypes.c_void_p] * 3, None
+    strips = []
+    for i in range(4 * (nb * (nb + 1) // 2 - 1)):
+        f(i, nb, *[ctypes.byref(v) for v in out])
+        strips.append(tuple(v.value for v in out))
+    assert sorted(strips) == sorted((I, j, q) for I in range(nb) for j in range(I + 1) for q in range(4) if I > 0)
+    handed, factor, diagonal = set(), set(), 0        # strips handed to the chain, strips of the factor, diagonal tiles that are done
+
+    def ends(I, j, q):
+        columns = range(j - 1 if I == j else j)
+        if not all((I, K, q) in factor and all((j, K, w) in factor for w in range(4)) for K in columns):
+            return False
+        if I <= j + 1:
+            handed.add((I, j, q))
+        if I > j and diagonal > j:
+            factor.add((I, j, q))
+        return I == j or diagonal > j
+
+    waiting, running = list(strips), []
+    while waiting or running or diagonal < nb:
+        before = len(handed), len(factor), diagonal, len(waiting)
+        while diagonal < nb and all(diagonal == 0 or ((diagonal, diagonal, q) in handed and (diagonal, diagonal - 1, q) in handed) for q in range(4)):
+            diagonal += 1
+        running += [waiting.pop(0) for _ in range(min(room - len(running), len(waiting)))]
+        running = [s for s in running if not ends(*s)]
+        assert (len(handed), len(factor), diagonal, len(waiting)) != before, "nothing that runs can go on"
+
+
 def _orth(Y):
     """Cholesky QR in binary32, columns in order: (block, largest pivot, smallest pivot)."""
     A = (Y.T @ Y).astype(np.float32)
