@@ -125,26 +125,29 @@ __device__ __forceinline__ void from_group(const float4_t &w, float (&out)[4])
         for (int e = 0; e < 4; ++e) out[e] = t[e];
 }
 
-// Step C of factor16(): w[f] += m times w[f] of lane C of the sixteen, for the registers of w and for those of c4 that are still
-// ahead (FIRST on); then the pivot of the next step, d = c4[FIRST] of its lane or the floor, and its reciprocal q, behind which the last
-// of w hide.  The broadcast rides on the multiply-add.  Outside the compiler's hazard bookkeeping: two wait states between a
-// write and a read by another lane (w[FIRST - 1], written last before a step, comes last; an s_nop is 9 cycles, an instruction 5), one
-// behind a reciprocal.
+// Step C of factor16(): w[f] += m times w[f] of lane C of the sixteen, m = col above / d, for the registers of w and for those of c4
+// that are still ahead (FIRST on); then the pivot of the next step, d = c4[FIRST] of its lane or the floor, and its reciprocal q, behind
+// which the last of w hide.  The broadcast rides on the multiply-add.  Outside the compiler's hazard bookkeeping: two wait states between a
+// write and a read by another lane, one behind a reciprocal.  The four instructions of m come first in the same asm, so that a register the
+// compiler writes or copies right before it is not read by another lane too early (an s_nop would be 9 cycles, an instruction is 5).
 template <int C, int FIRST>
-__device__ __forceinline__ void factor_step(float4_t &w, float (&c4)[4], float m, float floor_, float &d, float &q)
+__device__ __forceinline__ void factor_step(float4_t &w, float (&c4)[4], float col, float above, float floor_, float &d, float &q)
 {
-#define SLIM_ROW(x) "v_fmac_f32_dpp " x ", " x ", %10 row_newbcast:%12 row_mask:0xf bank_mask:0xf\n\t"
-#define SLIM_NEXT(x) "v_max_f32_dpp %8, " x ", %11 row_newbcast:%13 row_mask:0xf bank_mask:0xf\n\tv_rcp_f32 %9, %8\n\t"
-#define SLIM_REGS "+v"(w[0]), "+v"(w[1]), "+v"(w[2]), "+v"(w[3]), "+v"(c4[0]), "+v"(c4[1]), "+v"(c4[2]), "+v"(c4[3]), "=&v"(d), "=&v"(q) \
-                  : "v"(m), "v"(floor_), "n"(C), "n"((C + 1) % 16)
+    float m, t;
+#define SLIM_M "v_mul_f32 %10, %12, %13\n\tv_fma_f32 %11, -%8, %9, 2.0\n\tv_mul_f32 %11, %9, %11\n\tv_mul_f32 %10, %11, %10\n\t"      // (q to rounding)
+#define SLIM_ROW(x) "v_fmac_f32_dpp " x ", " x ", %10 row_newbcast:%15 row_mask:0xf bank_mask:0xf\n\t"
+#define SLIM_NEXT(x) "v_max_f32_dpp %8, " x ", %14 row_newbcast:%16 row_mask:0xf bank_mask:0xf\n\tv_rcp_f32 %9, %8\n\t"
+#define SLIM_REGS "+v"(w[0]), "+v"(w[1]), "+v"(w[2]), "+v"(w[3]), "+v"(c4[0]), "+v"(c4[1]), "+v"(c4[2]), "+v"(c4[3]), "+v"(d), "+v"(q), \
+                  "=&v"(m), "=&v"(t) : "v"(col), "v"(above), "v"(floor_), "n"(C), "n"((C + 1) % 16)
     if constexpr (FIRST == 1)
-        asm volatile(SLIM_ROW("%5") SLIM_ROW("%6") SLIM_ROW("%7") SLIM_NEXT("%5") SLIM_ROW("%1") SLIM_ROW("%2") SLIM_ROW("%3") SLIM_ROW("%0") : SLIM_REGS);
+        asm volatile(SLIM_M SLIM_ROW("%5") SLIM_ROW("%6") SLIM_ROW("%7") SLIM_NEXT("%5") SLIM_ROW("%1") SLIM_ROW("%2") SLIM_ROW("%3") SLIM_ROW("%0") : SLIM_REGS);
     else if constexpr (FIRST == 2)
-        asm volatile(SLIM_ROW("%6") SLIM_ROW("%7") SLIM_ROW("%2") SLIM_NEXT("%6") SLIM_ROW("%3") SLIM_ROW("%0") SLIM_ROW("%1") : SLIM_REGS);
+        asm volatile(SLIM_M SLIM_ROW("%6") SLIM_ROW("%7") SLIM_ROW("%2") SLIM_NEXT("%6") SLIM_ROW("%3") SLIM_ROW("%0") SLIM_ROW("%1") : SLIM_REGS);
     else if constexpr (FIRST == 3)
-        asm volatile(SLIM_ROW("%7") SLIM_ROW("%3") SLIM_ROW("%0") SLIM_NEXT("%7") SLIM_ROW("%1") SLIM_ROW("%2") : SLIM_REGS);
+        asm volatile(SLIM_M SLIM_ROW("%7") SLIM_ROW("%3") SLIM_ROW("%0") SLIM_NEXT("%7") SLIM_ROW("%1") SLIM_ROW("%2") : SLIM_REGS);
     else
-        asm volatile(SLIM_ROW("%0") SLIM_ROW("%1") SLIM_ROW("%2") SLIM_ROW("%3") : SLIM_REGS);
+        asm volatile(SLIM_M SLIM_ROW("%0") SLIM_ROW("%1") SLIM_ROW("%2") SLIM_ROW("%3") : SLIM_REGS);
+#undef SLIM_M
 #undef SLIM_ROW
 #undef SLIM_NEXT
 #undef SLIM_REGS
@@ -175,10 +178,9 @@ __device__ __forceinline__ bool factor16(float4_t &w, int i, int g, float floor_
             const float below = i > c ? -1.0f : 0.f;
             // (d at the floor: a column in the span of the ones before it, nothing to subtract)
             const float above = __builtin_amdgcn_fmed3f((d - floor_) * 0x1p127f, 0.f, 1.f);
-            const float col = c4[e] * below * above;
-            q = q * (2.0f - d * q);              // to rounding
+            const float col = c4[e] * below;
             w[e] = g == p ? (i == c ? 1.0f : 0.f) : w[e];
-            factor_step<c, e + 1>(w, c4, col * q, floor_, d, q);
+            factor_step<c, e + 1>(w, c4, col, above, floor_, d, q);
         });
         const float mine = (i & 2) ? ((i & 1) ? c4[3] : c4[2]) : ((i & 1) ? c4[1] : c4[0]);
         d_i = i / 4 == p ? mine : d_i;           // (a pivot stays where it was used)

@@ -1,5 +1,5 @@
 """The build's own check of the prefill kernels' register use (host logic, no GPU)."""
-from paper_2410_09615_amd.build import compiler_agpr_uses
+from paper_2410_09615_amd.build import compiler_agpr_uses, lane_reads_too_early
 
 ASM = """\t.text
 _ZN4slim5cleanE:
@@ -27,6 +27,46 @@ def test_compiler_uses_of_accumulation_registers_are_found():
     parks there (a store index, once: an out-of-bounds store).  The build reads the device assembly and
     refuses such a library; here the reader itself, on a clean kernel and on one with three parked values."""
     assert compiler_agpr_uses(ASM) == {"_ZN4slim6parkedE": 3}
+
+
+LANES = """_ZN4slim5cleanE:
+\tv_mov_b32_e32 v9, v64
+\tv_mov_b32_e32 v3, v7
+\t;;#ASMSTART
+\tv_mul_f32 v4, v5, v6
+\tv_mul_f32 v5, v4, v6
+\tv_fmac_f32_dpp v9, v9, v4 row_newbcast:0 row_mask:0xf bank_mask:0xf
+\tv_fmac_f32_dpp v8, v8, v4 row_newbcast:0 row_mask:0xf bank_mask:0xf
+\tv_permlane16_swap_b32 v2, v3
+\ts_nop 1
+\tv_permlane32_swap_b32 v2, v3
+\t;;#ASMEND
+\ts_nop 1
+\tv_mov_b32_dpp v7, v2 row_newbcast:0 row_mask:0xf bank_mask:0xf bound_ctrl:1
+\ts_endpgm
+_ZN4slim4copyE:
+\tv_mov_b32_e32 v9, v64
+\t;;#ASMSTART
+\ts_nop 0
+\tv_fmac_f32_dpp v9, v9, v7 row_newbcast:0 row_mask:0xf bank_mask:0xf
+\tv_fmac_f32_dpp v8, v8, v7 row_newbcast:0 row_mask:0xf bank_mask:0xf
+\t;;#ASMEND
+\tv_mov_b32_dpp v7, v8 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf
+\ts_endpgm
+_ZN4slim5startE:
+\ts_nop 7
+\t;;#ASMSTART
+\tv_fmac_f32_dpp v53, v53, v7 row_newbcast:1 row_mask:0xf bank_mask:0xf
+\t;;#ASMEND
+\ts_endpgm
+"""
+
+
+def test_reads_of_other_lanes_right_after_a_write_are_found():
+    """A register that another lane reads has to have been written two wait states before, and asm cannot know what the compiler
+    places before it: a copy right before a block that begins with such a read, the read itself, and one right behind the
+    block are found, in a kernel each; blocks that begin with two other instructions are not."""
+    assert lane_reads_too_early(LANES) == {"_ZN4slim4copyE": 2, "_ZN4slim5startE": 1}
 
 
 def test_counts_that_hand_results_over_order_memory():
