@@ -161,8 +161,10 @@ __device__ __forceinline__ half_t load_half(rsrc_t r, uint32_t lane_off, uint32_
 
 #endif
 
-// A block of columns of the adapter computation as two fp16 numbers: v = (hi + lo) / kBlockSplit, exact to 2^-22 of v or
-// 2^-31.  Columns are of unit length, but for what rounding leaves of dependent ones, which may be longer (some tens
+// A value of the adapter computation as two fp16 numbers, hi + lo / kLowSplit: lo, 2^11 below hi or less, is scaled by that, so that it is a normal number
+// wherever hi is (unscaled it was subnormal, and lost bits, from 2^-3 on down).
+constexpr float kLowSplit = 2048.0f;
+// A block of columns so: v = (hi + lo / kLowSplit) / kBlockSplit, exact to 2^-22 of v or 2^-42.  Columns are of unit length, but for what rounding leaves of dependent ones, which may be longer (some tens
 // with pivots near the floor of the factorisation): magnitudes beyond 1015 saturate.
 constexpr float kBlockSplit = 64.0f;
 // The largest magnitudes of a block's columns are found in that many words each.

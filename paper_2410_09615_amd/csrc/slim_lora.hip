@@ -300,7 +300,7 @@ __global__ __launch_bounds__(256) void lora_init_kernel(float *Z, half_t *hi, ha
         const float v = z * kBlockSplit;
         const half_t x = (half_t)v;
         hi[(size_t)c * rows + i] = x;
-        lo[(size_t)c * rows + i] = (half_t)(v - (float)x);
+        lo[(size_t)c * rows + i] = (half_t)((v - (float)x) * kLowSplit);
     }
 }
 

@@ -866,7 +866,7 @@ __global__ __launch_bounds__(256) void lora_apply_kernel(const float *__restrict
                 const float s = v16[Q * q + r] * kBlockSplit, v = fabsf(s) > 65000.0f ? copysignf(65000.0f, s) : s;
                 const half_t x = (half_t)v;
                 h[r] = x;
-                g[r] = (half_t)(v - (float)x);
+                g[r] = (half_t)((v - (float)x) * kLowSplit);
             }
             *reinterpret_cast<piece_t *>(hi + at + Q * q) = h;
             *reinterpret_cast<piece_t *>(lo + at + Q * q) = g;

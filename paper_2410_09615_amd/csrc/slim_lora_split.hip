@@ -1,9 +1,9 @@
 // Products of the error saliency S (fp32) with a block of columns (fp32) on the fp16 matrix cores: both operands are
-// split into two fp16 numbers, v = (hi + lo) 2^-e, and
-//   S Z = Sh Zh + Sl Zh + Sh Zl     (what is left out, Sl Zl, is 2^-22 of a product)
-// is added up in fp32 by V_MFMA_F32_32X32X16_F16.  hi + lo is v up to 2^-23 of v while lo is a normal number; e is one for all
-// of S, one for a channel of S^T and one for all of a block, so elements of S (of a channel of S^T) below 2^-17 of the largest, and of a block below 2^-8, are off by 2^-39 of the
-// largest and by 2^-31 instead.  fp16 products are exact in fp32, and a sum of sixteen of them is rounded less often than
+// split into two fp16 numbers, v = (hi + 2^-11 lo) 2^-e, and
+//   S Z = Sh Zh + 2^-11 (Sl Zh + Sh Zl)     (what is left out, 2^-22 Sl Zl, is 2^-22 of a product)
+// is added up in fp32 by V_MFMA_F32_32X32X16_F16, the second sum by itself.  hi + 2^-11 lo is v up to 2^-22 of v while hi is a normal number; e is one for all
+// of S, one for a channel of S^T and one for all of a block, so elements of S (of a channel of S^T) below 2^-27 of the largest, and of a block below 2^-20, are off by 2^-49 of the
+// largest and by 2^-42 instead.  fp16 products are exact in fp32, and a sum of sixteen of them is rounded less often than
 // with the fp32 instruction, which adds up two at a time, so the result is nearer to the exact one.  Measured against
 // 64 bits (2-norm of the product, largest of a column and of a row, each relative; in brackets the fp32 instruction),
 // 4096 x 4096 times 416 leading singular vectors:
@@ -59,7 +59,7 @@ __global__ __launch_bounds__(256) void lora_split_kernel(const float *__restrict
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
             h[e] = (half_t)v[e];
-            l[e] = (half_t)(v[e] - (float)h[e]);
+            l[e] = (half_t)((v[e] - (float)h[e]) * kLowSplit);
         }
         *reinterpret_cast<half8_t *>(reinterpret_cast<char *>(hi) + off) = h;
         *reinterpret_cast<half8_t *>(reinterpret_cast<char *>(lo) + off) = l;
@@ -233,7 +233,7 @@ __global__ __launch_bounds__(256, 1) void lora_split_gemm_kernel(SplitGemmArgs a
             static_for<16>([&](auto ec) {
                 constexpr int e = ec;
                 const int o = o0 + 32 * i + 8 * (e / 4) + 4 * lb + e % 4;
-                const float v = acc_read<16 * (i * NT + it) + e>() + acc_read<16 * (kSmall + i * NT + it) + e>();
+                const float v = acc_read<16 * (i * NT + it) + e>() + acc_read<16 * (kSmall + i * NT + it) + e>() * (1.0f / kLowSplit);
                 if (o < a.rows)        // (written through: 27 MB left in the L2s to the end of the kernel cost 2 us)
                     __hip_atomic_store(&out[(size_t)o * a.cols + t], v * sc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             });
