@@ -169,6 +169,8 @@ constexpr float kLowSplit = 2048.0f;
 constexpr float kBlockSplit = 64.0f;
 // The largest magnitudes of a block's columns are found in that many words each.
 constexpr int kColSlots = 32;
+// Those of the channels of S in so many.
+constexpr int kChannelSlots = 8;
 
 // What the planners need to know of the device that is current: compute units and LDS bytes per compute
 // unit, read once per device from its properties (the nominal MI355X figures, 256 and 160 KiB, where no
@@ -186,13 +188,6 @@ size_t decode_lds_limit();       // 0: the device's LDS; else bytes the one-laun
 
 // Device address of the library's own scratch array on the current device (slim_gemv.hip).
 int scratch_of_current_device(void **out);
-
-#ifdef __HIPCC__
-// The power of two in a channel's x (at least 2^-126, at most 2^126), and its reciprocal.
-__device__ __forceinline__ uint32_t channel_exponent_bits(float x) { return min(max(__float_as_uint(x) & 0x7F800000u, 0x00800000u), 0x7E800000u); }
-__device__ __forceinline__ float channel_exponent(float x) { return __uint_as_float(channel_exponent_bits(x)); }
-__device__ __forceinline__ float channel_rescale(float x) { return __uint_as_float(0x7F000000u - channel_exponent_bits(x)); }
-#endif
 
 inline bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 

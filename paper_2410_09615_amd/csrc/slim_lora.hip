@@ -10,7 +10,7 @@
 // captured energy ||Q^T S||_F^2 the call reports.  Orthonormalisation is Cholesky QR in fp32
 // (slim_lora_orth.hip), most of them a scaling of the columns where that loses nothing; the
 // products of the iteration, and that for R~, run on the fp16 matrix cores with both operands as two fp16 numbers
-// (slim_lora_split.hip: nearer to the exact product than the fp32 instruction); the Gram matrix of the report is an fp32 product.
+// (slim_lora_split.hip: as near to the exact product as fp32); the Gram matrix of the report is an fp32 product.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -226,28 +226,28 @@ __global__ __launch_bounds__(1024) void lora_shift_kernel(const float *xt, int k
 }
 
 // ---- S = (W - W^C) diag(x); the packed bytes are read in their tiled layout ----
-// One thread per group of four inputs, in turn.  s2: slots of ||S||_F^2, mx_words: bits of the largest magnitude, and of the
-// largest with each channel scaled by the power of two of its x (channel_exponent()).
-// HBM-bound (W and S, 8 bytes per weight): 4096 x 4096 27 us (with a 64-bit division per group and every sum added to one word 42).
-__global__ __launch_bounds__(256) void lora_error_kernel(const float *__restrict__ W, const uint8_t *__restrict__ qvals,
-                                                         const uint8_t *__restrict__ meta, const float *__restrict__ scale,
-                                                         const float *__restrict__ x, int n, int k, float *__restrict__ S, float *s2, float *mx_words)
+// A workgroup has the 32 groups of four inputs of a column tile and every eighth of its rows in turn, so that a thread keeps the maxima of its four
+// channels in registers.  s2: slots of ||S||_F^2, mx_word: bits of the largest magnitude, channel_max: kChannelSlots rows of bits of the channels' largest.
+// HBM-bound (W and S, 8 bytes per weight): 4096 x 4096 26 us (27 with a thread per group of any column and no channels' maxima).
+constexpr int kErrorRows = 8;
+__global__ __launch_bounds__(32 * kErrorRows) void lora_error_kernel(const float *__restrict__ W, const uint8_t *__restrict__ qvals,
+                                                                     const uint8_t *__restrict__ meta, const float *__restrict__ scale,
+                                                                     const float *__restrict__ x, int n, int k, int rows, float *__restrict__ S,
+                                                                     float *s2, float *mx_word, unsigned *channel_max)
 {
-    const uint32_t groups = (uint32_t)k / 4, kt = pk_ktiles(k);
-    const size_t first = (size_t)blockIdx.x * blockDim.x + threadIdx.x, stride = (size_t)gridDim.x * blockDim.x;
-    // row and group of the next one without a division
-    size_t o = first / groups;
-    uint32_t g = (uint32_t)(first - o * groups);
-    const size_t row_step = stride / groups;
-    const uint32_t group_step = (uint32_t)(stride - row_step * groups);
-    float part = 0.f, mx = 0.f, mx_scaled = 0.f;
-    while (o < (size_t)n) {
+    __shared__ float4_t red[kErrorRows][32];
+    const uint32_t groups = (uint32_t)k / 4, kt = pk_ktiles(k), g = 32 * blockIdx.x + threadIdx.x % 32;
+    const int first = (int)blockIdx.y * rows + (int)threadIdx.x / 32, end = min(n, (int)blockIdx.y * rows + rows);
+    const float4_t xv = reinterpret_cast<const float4_t *>(x)[g];
+    float part = 0.f;
+    float4_t mx = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 4
+    for (int o = first; o < end; o += kErrorRows) {
         const uint32_t q = qvals[pk_qoff((uint32_t)o, g, kt)];
         const uint32_t mb = meta[pk_moff((uint32_t)o, g >> 1, kt)];
         const uint32_t m4 = (g & 1) ? (mb >> 4) : (mb & 15u);
         const float s = scale[o];
-        const float4_t w = reinterpret_cast<const float4_t *>(W)[o * groups + g];
-        const float4_t xv = reinterpret_cast<const float4_t *>(x)[g];
+        const float4_t w = reinterpret_cast<const float4_t *>(W)[(size_t)o * groups + g];
         const uint32_t i0 = m4 & 3u, i1 = (m4 >> 2) & 3u;
         const float w0 = (float)nibble_to_int(q & 15u) * s, w1 = (float)nibble_to_int(q >> 4) * s;
         float4_t e;
@@ -256,21 +256,20 @@ __global__ __launch_bounds__(256) void lora_error_kernel(const float *__restrict
             const float wc = i == i1 ? w1 : (i == i0 ? w0 : 0.f);
             e[i] = (w[i] - wc) * xv[i];
             part += e[i] * e[i];
-            mx = fmaxf(mx, fabsf(e[i]));
-            mx_scaled = fmaxf(mx_scaled, fabsf(e[i]) * channel_rescale(xv[i]));
+            mx[i] = fmaxf(mx[i], fabsf(e[i]));
         }
-        reinterpret_cast<float4_t *>(S)[o * groups + g] = e;
-        o += row_step;
-        g += group_step;
-        if (g >= groups) {
-            g -= groups;
-            ++o;
-        }
+        reinterpret_cast<float4_t *>(S)[(size_t)o * groups + g] = e;
     }
     block_add(part, s2);
-    block_max(mx, mx_words);
+    red[threadIdx.x / 32][threadIdx.x % 32] = mx;
+    block_max(fmaxf(fmaxf(mx[0], mx[1]), fmaxf(mx[2], mx[3])), mx_word);
     __syncthreads();
-    block_max(mx_scaled, mx_words + 1);
+    if (threadIdx.x >= 128) return;
+    const float *const column = reinterpret_cast<const float *>(red) + threadIdx.x;
+    float c = 0.f;
+#pragma unroll
+    for (int i = 0; i < kErrorRows; ++i) c = fmaxf(c, column[128 * i]);
+    atomicMax(channel_max + (size_t)(blockIdx.y % kChannelSlots) * k + 128 * blockIdx.x + threadIdx.x, __float_as_uint(c));
 }
 
 // ---- start block: uniform in (-1, 1) from a hash of (seed, element), columns >= r zero ----
@@ -313,8 +312,9 @@ int launch_orth(const float *in, float *out, half_t *hi, half_t *lo, int rows, i
                 hipStream_t st);
 unsigned *orth_column_max(float *ws, int l, int which);
 int split_gemm_splits(int rows, int cols, int K);                                                    // slim_lora_split.hip
-int launch_lora_split(const float *S, const float *x, int n, int k, const unsigned *max_bits, half_t *Sh, half_t *Sl, half_t *Th, half_t *Tl, hipStream_t st);
-int launch_lora_split_gemm(const half_t *Ah, const half_t *Al, const unsigned *max_bits, const float *x, const half_t *Bh, const half_t *Bl, int rows,
+int launch_lora_split(const float *S, int n, int k, const unsigned *max_bits, const unsigned *channel_max, half_t *Sh, half_t *Sl, half_t *Th, half_t *Tl,
+                      float *channel_factor, hipStream_t st);
+int launch_lora_split_gemm(const half_t *Ah, const half_t *Al, const unsigned *max_bits, const float *row_factor, const half_t *Bh, const half_t *Bl, int rows,
                            int cols, int K, float *P, float *Y, unsigned *colmax, hipStream_t st);
 
 // ---- results: L fp16 [n][r] = Q[:, :r];  R fp16 [r][k] = R~[:r] / x;  r2: slots of ||R~[:r]||_F^2 ----
@@ -381,10 +381,13 @@ __global__ __launch_bounds__(64) void lora_report_kernel(const float *sq, const 
     if (t == 3) diag[3] = 0.f;
 }
 
+// Words that a call clears: maxima, slots of the two sums, the words that the orth()s' workgroups hand over by, the channels' maxima.
+static size_t lora_cleared(int k) { return 64 + 2 * kSumSlots * kSumStride + orth_hand_words() + (size_t)kChannelSlots * k; }
+
 struct LoraPlan {
     int l;                      // columns of the iteration block: rank padded as the layer's adapters are
     bool split;                 // products on the fp16 matrix cores (lora_split_gemm_kernel)
-    size_t x, S, half[4], Q, Y, Z, P, blk[4], G, O, Rt, sq, total;      // byte offsets (O: the orthonormalisation's own)
+    size_t x, S, half[4], Q, Y, Z, P, blk[4], G, O, Rt, factor, sq, total;      // byte offsets (O: the orthonormalisation's own)
 };
 
 static size_t up256(size_t v) { return (v + 255) / 256 * 256; }
@@ -418,7 +421,8 @@ static LoraPlan plan_lora(int n, int k, int rank)
     p.G = take(l * l);
     p.O = take(orth_floats(p.l));
     p.Rt = take(l * k);
-    p.sq = take(64 + 2 * kSumSlots * kSumStride + orth_hand_words());
+    p.factor = take(k);
+    p.sq = take(lora_cleared(k));
     p.total = off;
     return p;
 }
@@ -456,7 +460,7 @@ extern "C" int slim_compute_adapters(const float *W, const uint8_t *qvals, const
     float *Q = reinterpret_cast<float *>(ws + p.Q), *Y = reinterpret_cast<float *>(ws + p.Y);
     float *P = p.split ? reinterpret_cast<float *>(ws + p.P) : nullptr, *G = reinterpret_cast<float *>(ws + p.G);
     float *O = reinterpret_cast<float *>(ws + p.O), *Rt = reinterpret_cast<float *>(ws + p.Rt);
-    float *sq = reinterpret_cast<float *>(ws + p.sq);
+    float *sq = reinterpret_cast<float *>(ws + p.sq), *factor = reinterpret_cast<float *>(ws + p.factor);
     const int l = p.l;
     const int q = iters == 0 ? 16 : iters;
     int rc;
@@ -468,18 +472,22 @@ extern "C" int slim_compute_adapters(const float *W, const uint8_t *qvals, const
     auto launched = [&]() { return hip_status(hipGetLastError()); };
     auto grid_for = [](size_t count) { return dim3((unsigned)std::min<size_t>((count + 255) / 256, 4096)); };
 
-    // (behind the maxima: the slots of the two sums, and the words that the orth()s' workgroups hand over by)
+    // (in the order of lora_cleared())
     float *const s2 = sq + 64, *const r2 = s2 + kSumSlots * kSumStride;
     unsigned *const hand = reinterpret_cast<unsigned *>(r2 + kSumSlots * kSumStride);
+    unsigned *const channel_max = hand + orth_hand_words();
     unsigned orths = 0;
     auto orth = [&](const float *in, float *out, half_t *hi, half_t *lo, int rows, int h, int last) {
         return launch_orth(in, out, hi, lo, rows, p.l, O, hand, ++orths, h, last, st);
     };
-    SLIM_TRY(launch_fill(sq, 64 + 2 * kSumSlots * kSumStride + orth_hand_words(), 0.f, st));
+    SLIM_TRY(launch_fill(sq, lora_cleared(k), 0.f, st));
     hipLaunchKernelGGL(lora_shift_kernel, dim3(1), dim3(1024), 0, st, x_tilde, k, x);
     SLIM_TRY(launched());
-    hipLaunchKernelGGL(lora_error_kernel, dim3(std::min(grid_for((size_t)n * (k / 4)).x, 1024u)), dim3(256), 0, st, W, qvals, meta, scale,
-                       (const float *)x, n, k, S, s2, sq + 4);
+    // about 1024 workgroups
+    const int column_tiles = k / 128, passes = (n + kErrorRows - 1) / kErrorRows, chunks = std::min(passes, (1023 + column_tiles) / column_tiles);
+    const int rows = (passes + chunks - 1) / chunks * kErrorRows;
+    hipLaunchKernelGGL(lora_error_kernel, dim3((unsigned)column_tiles, (unsigned)((n + rows - 1) / rows)), dim3(32 * kErrorRows), 0, st, W, qvals, meta, scale,
+                       (const float *)x, n, k, rows, S, s2, sq + 4, channel_max);
     SLIM_TRY(launched());
 
     float *Z = p.split ? nullptr : reinterpret_cast<float *>(ws + p.Z);
@@ -491,7 +499,7 @@ extern "C" int slim_compute_adapters(const float *W, const uint8_t *qvals, const
             Sh[i] = reinterpret_cast<half_t *>(ws + p.half[i]);
             blk[i] = reinterpret_cast<half_t *>(ws + p.blk[i]);
         }
-        SLIM_TRY(launch_lora_split(S, x, n, k, mx, Sh[0], Sh[1], Sh[2], Sh[3], st));
+        SLIM_TRY(launch_lora_split(S, n, k, mx, channel_max, Sh[0], Sh[1], Sh[2], Sh[3], factor, st));
     }
     hipLaunchKernelGGL(lora_init_kernel, dim3((unsigned)std::min((k + 255) / 256, 1024), (unsigned)l), dim3(256), 0, st, Z, blk[2], blk[3], k, l, r, seed);
     SLIM_TRY(launched());
@@ -503,7 +511,7 @@ extern "C" int slim_compute_adapters(const float *W, const uint8_t *qvals, const
                        : sgemm(false, S, k, Z, l, Y, n, l, k, st);
     };
     auto times = [&](const float *q, float *to, unsigned *cm) {          // S^T q     [k][l]
-        return p.split ? launch_lora_split_gemm(Sh[2], Sh[3], mx + 1, x, blk[0], blk[1], k, l, n32, P, to, cm, st) : sgemm(true, S, k, q, l, to, k, l, n, st);
+        return p.split ? launch_lora_split_gemm(Sh[2], Sh[3], nullptr, factor, blk[0], blk[1], k, l, n32, P, to, cm, st) : sgemm(true, S, k, q, l, to, k, l, n, st);
     };
     auto times_q = [&](int h) { return times(Q, Y, colmax(h)); };        // Y = S^T Q
 

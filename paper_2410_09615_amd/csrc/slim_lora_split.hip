@@ -4,19 +4,20 @@
 // is added up in fp32 by V_MFMA_F32_32X32X16_F16, the second sum by itself.  hi + 2^-11 lo is v up to 2^-22 of v while hi is a normal number; e is one for all
 // of S, one for a channel of S^T and one for all of a block, so elements of S (of a channel of S^T) below 2^-27 of the largest, and of a block below 2^-20, are off by 2^-49 of the
 // largest and by 2^-42 instead.  fp16 products are exact in fp32, and a sum of sixteen of them is rounded less often than
-// with the fp32 instruction, which adds up two at a time, so the result is nearer to the exact one.  Measured against
-// 64 bits (2-norm of the product, largest of a column and of a row, each relative; in brackets the fp32 instruction),
-// 4096 x 4096 times 416 leading singular vectors:
-//   S Z    saliency of calibration inputs          2.2e-7 (5.5e-7)   2.7e-7 (7.3e-7)   4.1e-7 (1.1e-6)
-//          spanning 1e6, even in the logarithm     2.3e-7 (4.2e-7)   2.6e-7 (5.2e-7)   2.9e-7 (5.5e-7)
-//          5 % of the channels 1e4 above the rest  1.4e-7 (1.4e-7)   2.4e-5 (4.1e-7)   1.8e-7 (1.7e-7)
-//   S^T Q  saliency of calibration inputs          1.2e-7 (3.0e-7)   2.5e-7 (6.8e-7)   2.5e-7 (4.9e-7)
-//          spanning 1e6, even in the logarithm     1.1e-7 (2.9e-7)   2.0e-7 (5.1e-7)   2.7e-7 (7.2e-7)
-// (The shares of K are added up in 64 bits and rounded once; acc + small is one rounding more per share than one accumulator for
-// all three products, added one after the other, would need: 2.22e-7 with that, 2.21e-7 like this, 2.23e-7 with shares added in fp32.)
-// The columns that lose in the third line are those of directions 1e4 below the leading ones: the error is of the direction of
-// the leading ones, which the orthonormalisation takes out.  Adapters of saliencies that span up to 1e8 capture what they did
-// with fp32 products, to the digits reported.
+// with the fp32 instruction, which adds up two at a time.  Measured against 64 bits (2-norm of the product, largest of a column and of a row, each
+// relative; in brackets a product in fp32 by the host's library, in blocks), 4096 x 4096 times 409 leading singular vectors:
+//   S Z    saliency of calibration inputs          2.0e-7 (2.5e-7)   2.6e-7 (3.1e-7)   3.4e-7 (4.3e-7)
+//          saliency spanning 1e6                   2.3e-7 (2.0e-7)   2.7e-7 (2.6e-7)   2.9e-7 (2.5e-7)
+//          5 % of the channels 1e4 above the rest  1.5e-7 (1.2e-7)   1.9e-7 (1.8e-7)   1.8e-7 (1.5e-7)
+//          rows of W spanning 1e6                  1.1e-7 (1.2e-7)   2.0e-7 (2.2e-7)   2.7e-7 (3.1e-7)
+//          rows of W spanning 1e9                  1.1e-7 (1.2e-7)   2.5e-7 (2.9e-7)   4.7e-6 (3.1e-7)
+//   S^T Q  saliency of calibration inputs          1.1e-7 (1.3e-7)   2.6e-7 (3.0e-7)   1.8e-7 (2.1e-7)
+//          saliency spanning 1e6                   1.1e-7 (1.2e-7)   1.9e-7 (2.2e-7)   2.7e-7 (3.1e-7)
+//          spanning 1e9, weights of channels 1 / that   1.4e-7 (1.6e-7)   1.6e-7 (1.8e-7)   1.8e-7 (2.1e-7)
+//          rows of W spanning 1e6                  2.3e-7 (2.1e-7)   2.7e-7 (2.5e-7)   2.8e-7 (2.5e-7)
+// (With lo unscaled a row of S Z was off by 9e-6 and 8e-3 where the rows of W span 1e6 and 1e9, a column by 1.2e-5 where 5 % of the channels are 1e4 above
+// the rest; with a channel of S^T scaled by its saliency instead of its own maximum S^T Q was off by 4.7e-4 in the last line but one.)
+// The shares of K are added up in 64 bits and rounded once.
 // Three fp16 instructions do the work of eight fp32 ones that take twice the time each.  4096 x 4096 times 416 columns: 200 us with the fp32 instruction (70 TFLOP/s),
 // 53 us like this (44, and 9 to add the shares of K and find the columns' largest magnitudes).
 //   S is split once per call, into the operand order of the instruction, for S Z and for S^T Q;
@@ -32,15 +33,23 @@ __device__ __forceinline__ float split_scale(unsigned max_bits)
     return max_bits == 0u ? 1.0f : exp2f((float)min(13 - e, 126));
 }
 
-// S [n][k] -> hi and lo in the adapter layout (tiles of 32 rows x 16 columns), for S (rows n) and S^T (rows k, each scaled by
-// the power of two of its channel's x; n padded to 32 columns).  max_bits: largest magnitudes of S, and of S so scaled.  A workgroup moves 64 x 64.
-__global__ __launch_bounds__(256) void lora_split_kernel(const float *__restrict__ S, const float *__restrict__ x, int n, int k, const unsigned *max_bits,
-                                                         half_t *__restrict__ Sh, half_t *__restrict__ Sl, half_t *__restrict__ Th,
-                                                         half_t *__restrict__ Tl)
+// S [n][k] -> hi and lo in the adapter layout (tiles of 32 rows x 16 columns), for S (rows n) and S^T (rows k, each scaled by its own largest
+// magnitude; n padded to 32 columns).  max_bits: the largest magnitude of S; channel_max: kChannelSlots rows of the channels';
+// channel_factor: the reciprocals of their scales.  A workgroup moves 64 x 64.
+__global__ __launch_bounds__(256) void lora_split_kernel(const float *__restrict__ S, int n, int k, const unsigned *max_bits,
+                                                         const unsigned *__restrict__ channel_max, half_t *__restrict__ Sh, half_t *__restrict__ Sl,
+                                                         half_t *__restrict__ Th, half_t *__restrict__ Tl, float *__restrict__ channel_factor)
 {
-    __shared__ float t[64][65];
+    __shared__ float t[64][65], channel_scale[64];
     const int i0 = blockIdx.y * 64, j0 = blockIdx.x * 64, tid = threadIdx.x;
-    const float sc = split_scale(max_bits[0]), sct = split_scale(max_bits[1]);
+    const float sc = split_scale(*max_bits);
+    if (tid < 64) {
+        unsigned mx = 0u;
+#pragma unroll
+        for (int q = 0; q < kChannelSlots; ++q) mx = max(mx, channel_max[(size_t)q * k + j0 + tid]);
+        channel_scale[tid] = split_scale(mx);
+        if (i0 == 0) channel_factor[j0 + tid] = 1.0f / split_scale(mx);
+    }
     for (int q = tid; q < 64 * 16; q += 256) {
         const int r = q >> 4, c = (q & 15) * 4;
         float4_t v = {0.f, 0.f, 0.f, 0.f};
@@ -76,9 +85,9 @@ __global__ __launch_bounds__(256) void lora_split_kernel(const float *__restrict
             put(Sh, Sl, piece(i0 + a, (j0 + b) / 8, k), v);
         }
         if (i0 + b < n32) {
-            const float xa = channel_rescale(x[j0 + a]);
+            const float sca = channel_scale[a];
 #pragma unroll
-            for (int e = 0; e < 8; ++e) v[e] = t[b + e][a] * xa * sct;
+            for (int e = 0; e < 8; ++e) v[e] = t[b + e][a] * sca;
             put(Th, Tl, piece(j0 + a, (i0 + b) / 8, n32), v);
         }
     }
@@ -87,7 +96,7 @@ __global__ __launch_bounds__(256) void lora_split_kernel(const float *__restrict
 struct SplitGemmArgs {
     const half_t *Ah, *Al;      // [rows][K] in the adapter layout
     const half_t *Bh, *Bl;      // [cols][K]
-    const unsigned *max_bits;   // largest magnitude of what Ah + Al was split from
+    const unsigned *max_bits;   // largest magnitude of what Ah + Al was split from, or null: rows with scales of their own
     float *P;                   // [splits][rows][cols]
     int rows, cols, K, ks;      // K a multiple of 32, ks (inputs per split) of 128
     int tiles_o;                // row tiles of 256
@@ -221,7 +230,7 @@ __global__ __launch_bounds__(256, 1) void lora_split_gemm_kernel(SplitGemmArgs a
     op.b_lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)lds_c + (uint32_t)wave * 1024u;
     split_phase(op, klen, lds_c, li, lb);
     acc_settle();
-    const float sc = 1.0f / (split_scale(*a.max_bits) * kBlockSplit);
+    const float sc = 1.0f / ((a.max_bits ? split_scale(*a.max_bits) : 1.0f) * kBlockSplit);
     // lane holds column t0 + 32 it + li, rows o .. o + 3 per (i, blk)
     float *const out = a.P + (size_t)blockIdx.y * a.rows * a.cols;
     static_for<NT>([&](auto itc) {
@@ -262,11 +271,11 @@ __global__ __launch_bounds__(256) void lora_split_reduce_kernel(const float4_t *
     }
 }
 
-// The same, a workgroup per 16 rows of cols4 float4s; x (or null): times the powers of two of the rows' channels; colmax (or null): the
+// The same, a workgroup per 16 rows of cols4 float4s; row_factor (or null): of each row; colmax (or null): the
 // bits of the columns' largest magnitudes, in kColSlots rows of
 // 4 cols4 words (zero before), a workgroup's in row blockIdx mod kColSlots.  In one row the adds to a word were 256 in
 // turn, and 22 of 28 us (4096 x 416); now 8.
-__global__ __launch_bounds__(512) void lora_split_reduce_max_kernel(const float4_t *__restrict__ P, const float *__restrict__ x, int splits, int rows, int cols4,
+__global__ __launch_bounds__(512) void lora_split_reduce_max_kernel(const float4_t *__restrict__ P, const float *__restrict__ row_factor, int splits, int rows, int cols4,
                                                                     float4_t *__restrict__ Y, unsigned *__restrict__ colmax)
 {
     __shared__ uint4_t part[512];
@@ -277,7 +286,7 @@ __global__ __launch_bounds__(512) void lora_split_reduce_max_kernel(const float4
     if (row < rpp)
         for (int r = blockIdx.x * 16 + row; r < end; r += rpp) {
             const size_t i = (size_t)r * cols4 + col;
-            const float4_t s = sum_shares(P, splits, count4, i) * (x ? channel_exponent(x[r]) : 1.0f);
+            const float4_t s = sum_shares(P, splits, count4, i) * (row_factor ? row_factor[r] : 1.0f);
             Y[i] = s;
 #pragma unroll
             for (int e = 0; e < 4; ++e) mx[e] = fmaxf(mx[e], fabsf(s[e]));
@@ -304,26 +313,29 @@ int split_gemm_splits(int rows, int cols, int K)
     return s;
 }
 
-int launch_lora_split(const float *S, const float *x, int n, int k, const unsigned *max_bits, half_t *Sh, half_t *Sl, half_t *Th, half_t *Tl, hipStream_t st)
+int launch_lora_split(const float *S, int n, int k, const unsigned *max_bits, const unsigned *channel_max, half_t *Sh, half_t *Sl, half_t *Th, half_t *Tl,
+                      float *channel_factor, hipStream_t st)
 {
-    hipLaunchKernelGGL(lora_split_kernel, dim3((unsigned)(k / 64), (unsigned)((n + 63) / 64)), dim3(256), 0, st, S, x, n, k, max_bits, Sh, Sl, Th, Tl);
+    hipLaunchKernelGGL(lora_split_kernel, dim3((unsigned)(k / 64), (unsigned)((n + 63) / 64)), dim3(256), 0, st, S, n, k, max_bits,
+                       channel_max, Sh, Sl, Th, Tl, channel_factor);
     return hip_status(hipGetLastError());
 }
 
-// Y [rows][cols] = A B^T (A scaled by split_scale(*max_bits), and its rows by the powers of two of x, or null; B by kBlockSplit; cols <= 1024); P: split_gemm_splits() x rows x cols floats.
+// Y [rows][cols] = A B^T (A scaled by split_scale(*max_bits), or with max_bits null a row by the reciprocal of its row_factor; B by kBlockSplit; cols <= 1024).
+// P: split_gemm_splits() x rows x cols floats.
 // colmax (or null): kColSlots rows of zeros, which become bits of the columns' largest magnitudes (cols <= 1024).
-int launch_lora_split_gemm(const half_t *Ah, const half_t *Al, const unsigned *max_bits, const float *x, const half_t *Bh, const half_t *Bl, int rows,
+int launch_lora_split_gemm(const half_t *Ah, const half_t *Al, const unsigned *max_bits, const float *row_factor, const half_t *Bh, const half_t *Bl, int rows,
                            int cols, int K, float *P, float *Y, unsigned *colmax, hipStream_t st)
 {
     SplitGemmArgs a{Ah, Al, Bh, Bl, max_bits, nullptr, rows, cols, K, 0, (rows + 255) / 256};
     const int splits = split_gemm_splits(rows, cols, K);
-    a.P = splits > 1 || colmax || x ? P : Y;
+    a.P = splits > 1 || colmax || row_factor ? P : Y;
     a.ks = ((K + 127) / 128 + splits - 1) / splits * 128;
     const size_t lds = (size_t)4 * kSplitStage;
     hipLaunchKernelGGL(lora_split_gemm_kernel, dim3((unsigned)(a.tiles_o * ((cols + 127) / 128)), (unsigned)splits), dim3(256), lds, st, a);
-    if (colmax || x) {
+    if (colmax || row_factor) {
         hipLaunchKernelGGL(lora_split_reduce_max_kernel, dim3((unsigned)((rows + 15) / 16)), dim3(512), 0, st, reinterpret_cast<const float4_t *>(P),
-                           x, splits, rows, cols / 4, reinterpret_cast<float4_t *>(Y), colmax);
+                           row_factor, splits, rows, cols / 4, reinterpret_cast<float4_t *>(Y), colmax);
     } else if (splits > 1) {
         const size_t count4 = (size_t)rows * cols / 4;          // cols is a multiple of 32
         const unsigned grid = (unsigned)((count4 + 255) / 256 < 2048 ? (count4 + 255) / 256 : 2048);
