@@ -36,7 +36,6 @@ int gemm_t_splits(int32_t m, int32_t rank_pad, int32_t k);   // slim_api.hip
 typedef int int4_t __attribute__((ext_vector_type(4)));
 typedef int int8v_t __attribute__((ext_vector_type(8)));
 
-enum MidFlags { kAccumulate = 1, kWideT = 2 };      // add to what Y holds; tiles of T are of 32 tokens, not 16
 struct MidArgs {
     const uint8_t *qvals;
     const uint8_t *meta;
@@ -57,7 +56,7 @@ struct MidArgs {
     int t_tiles;          // tiles of T
     int spin_limit;       // polls after which a wait gives up
     int stages;           // stages of 128 inputs of the weight term (0: the adapter term alone)
-    int flags;            // MidFlags (one more word of arguments made a call 0.1 us slower)
+    int accumulate;       // add to what Y holds
 };
 
 constexpr int kMidWaves = 8, kMidHelpers = 4, kMidThreads = (kMidWaves + kMidHelpers) * kWave;
@@ -167,10 +166,10 @@ __device__ __forceinline__ void t_tile(const MidArgs &a, int rt, int tt, char *l
         half_t sc = (half_t)1.0f;
         if constexpr (AQ) {
             const bool ok = column(u, 0) < k;
-            const uint32_t base = ok ? q4_piece(16u * rt + lx, column(u, 0) / 64u, q4_ctiles(a.k)) + (TT == 2 ? 16u * (ly & 1) : 0u) : kPastEnd;
+            const uint32_t base = ok ? q4_piece(16u * rt + lx, (uint32_t)(UN / 64) * u + ly / TT, q4_ctiles(a.k)) + (TT == 2 ? 16u * (ly & 1) : 0u) : kPastEnd;
 #pragma unroll
             for (int t = 0; t < 2 / TT; ++t) rv[t] = load16(r_rs, ok ? base + 16u * t : kPastEnd, 0);
-            sc = load_half(s_rs, ok ? ((16u * rt + lx) * q4_groups(a.k) + column(u, 0) / 128u) * 2u : kPastEnd, 0);
+            sc = load_half(s_rs, ok ? ((16u * rt + lx) * q4_groups(a.k) + (uint32_t)(UN / 128) * u + ly / (2 * TT)) * 2u : kPastEnd, 0);
         } else {
 #pragma unroll
             for (int t = 0; t < STEPS; ++t) {
@@ -1232,7 +1231,7 @@ __device__ __forceinline__ bool y_role(const MidArgs &a, int tid, int ot, int tt
                 if (t >= a.m || o >= a.n) continue;
                 half_t *y = a.Y + (size_t)t * a.n + o;
                 if (vec_ok) {
-                    if (a.flags & kAccumulate) {
+                    if (a.accumulate) {
                         const half4_t old = *reinterpret_cast<const half4_t *>(y);
 #pragma unroll
                         for (int e = 0; e < 4; ++e) v[e] += (float)old[e];
@@ -1241,7 +1240,7 @@ __device__ __forceinline__ bool y_role(const MidArgs &a, int tid, int ot, int tt
                 } else {
 #pragma unroll
                     for (int e = 0; e < 4; ++e)
-                        if (o + e < a.n) y[e] = (half_t)(a.flags & kAccumulate ? v[e] + (float)y[e] : v[e]);
+                        if (o + e < a.n) y[e] = (half_t)(a.accumulate ? v[e] + (float)y[e] : v[e]);
                 }
             }
     }
@@ -1266,28 +1265,22 @@ __device__ __forceinline__ void t_of_tokens(const MidArgs &a, int first, int cou
     }
 }
 
-template <int NT_, int RT, int RG, int KW, int XF, bool AQ>
+// TT: a tile of T is of 16 TT tokens.
+template <int NT_, int RT, int RG, int KW, int XF, bool AQ, int TT>
 __global__ __launch_bounds__(kMidThreads, 3) void mid_kernel(MidArgs a)
 {
     extern __shared__ __attribute__((aligned(16))) char lds_c[];
-    // beside tiles of 128 x 64 the codes' tiles of T of 16 tokens are faster with what they work out kept from one to the next (18688 x 9984 at 38 tokens,
-    // two tiles each, 47.8 -> 45.5 us), beside those of 64 x 32 slower (12572 x 4992 at 20 tokens 13.65 -> 13.85), as with fp16 R
-    constexpr bool HIDE = !(AQ && NT_ == 2);
+    // with tiles of T of 16 tokens: beside tiles of 32 rows 1 to 2 % faster, with 8-bit X and 4-bit adapters 7 % (and up to 6 beside 64 rows), elsewhere up to 8 % slower
+    constexpr bool HIDE = TT == 2 || RG == 1 || (XF != 0 && AQ && RT == 1 && RG == 2);
     const unsigned epoch = a.rank_pad > 0 && a.T ? call_epoch(a.epoch) : 0u;
     if ((int)blockIdx.x < a.n_t) {
-        if (a.flags & kWideT)
-            t_tiles<XF, AQ, 2, true>(a, blockIdx.x, a.n_t, lds_c, epoch);
-        else
-            t_tiles<XF, AQ, 1, HIDE>(a, blockIdx.x, a.n_t, lds_c, epoch);
+        t_tiles<XF, AQ, TT, HIDE>(a, blockIdx.x, a.n_t, lds_c, epoch);
         return;
     }
     int ot, tt;
     if (!tile_on_die((int)blockIdx.x - a.n_t, a.tiles_o, ot, tt)) return;
     if (!y_role<NT_, RT, RG, KW, XF, AQ, false>(a, threadIdx.x, ot, tt, lds_c, epoch)) return;
-    if (a.flags & kWideT)
-        t_of_tokens<XF, AQ, 2, true>(a, NT_ * tt, NT_, lds_c, epoch);
-    else
-        t_of_tokens<XF, AQ, 1, HIDE>(a, 2 * NT_ * tt, 2 * NT_, lds_c, epoch);
+    t_of_tokens<XF, AQ, TT, HIDE>(a, 2 / TT * NT_ * tt, 2 / TT * NT_, lds_c, epoch);
     asm volatile("s_waitcnt vmcnt(0)" : : : "memory");     // the pieces are in memory
     __syncthreads();
     // (a thread number the compiler knows nothing of: what it works out of it above would stay in registers until here)
@@ -1315,7 +1308,7 @@ static void launch_t_role_of(const TArgs &t, hipStream_t st)
     a.m = t.m;
     a.n_t = a.t_tiles = die_tiles(t.rank_pad / 16, (t.m + 15) / 16);
     constexpr size_t lds = MidLds<1, 1, 1, 8, XF>::TROLE;
-    hipLaunchKernelGGL((mid_kernel<1, 1, 1, 8, XF, AQ>), dim3((unsigned)a.n_t), dim3(kMidThreads), lds, st, a);
+    hipLaunchKernelGGL((mid_kernel<1, 1, 1, 8, XF, AQ, 1>), dim3((unsigned)a.n_t), dim3(kMidThreads), lds, st, a);
 }
 static void launch_t_role(const TArgs &t, int xf, hipStream_t st)
 {
@@ -1349,16 +1342,15 @@ static int t_trips(int rank_pad, int m, int tokens, int n_y, int cus, int *n_t =
     return n > 0 ? (tiles + n - 1) / n : 1 << 20;
 }
 
-template <int NT_, int RT, int RG, int KW, int XF, bool AQ>
-static int launch_mid(MidArgs a, int t_tokens, WaitTest wait_test, hipStream_t st)
+template <int NT_, int RT, int RG, int KW, int XF, bool AQ, int TT>
+static int launch_mid_tiles(MidArgs a, int t_tokens, WaitTest wait_test, hipStream_t st)
 {
     constexpr size_t lds = MidLds<NT_, RT, RG, KW, XF>::BYTES;
     a.tiles_o = (a.n + 32 * RT * RG - 1) / (32 * RT * RG);
     const int n_y = die_tiles(a.tiles_o, (a.m + 32 * NT_ - 1) / (32 * NT_));
-    if (t_tokens == 32) a.flags |= kWideT;
     int n_t = 0;
     if (t_tokens > 0) t_trips(a.rank_pad, a.m, t_tokens, n_y, device_info().cus, &n_t);
-    a.t_tiles = t_tokens == 32 ? die_tiles(a.rank_pad / 16, (a.m + 31) / 32) : die_tiles(a.rank_pad / 16, (a.m + 15) / 16);
+    a.t_tiles = die_tiles(a.rank_pad / 16, (a.m + 16 * TT - 1) / (16 * TT));
     if (wait_test == WaitTest::fail) {
         n_t = 0;                             // nobody makes T
     } else if (wait_test == WaitTest::help && n_t > 0) {
@@ -1381,8 +1373,16 @@ static int launch_mid(MidArgs a, int t_tokens, WaitTest wait_test, hipStream_t s
         if (rc != SLIM_OK) return rc;
     }
     a.n_t = n_t;
-    hipLaunchKernelGGL((mid_kernel<NT_, RT, RG, KW, XF, AQ>), dim3((unsigned)(n_t + n_y)), dim3(kMidThreads), lds, st, a);
+    hipLaunchKernelGGL((mid_kernel<NT_, RT, RG, KW, XF, AQ, TT>), dim3((unsigned)(n_t + n_y)), dim3(kMidThreads), lds, st, a);
     return hip_status(hipGetLastError());
+}
+
+// A kernel for each of the two tiles of T: one with both had twice the scalar registers to spill (<1, 1, 2, 4, 0, true> 43 instead of 23).
+template <int NT_, int RT, int RG, int KW, int XF, bool AQ>
+static int launch_mid(const MidArgs &a, int t_tokens, WaitTest wait_test, hipStream_t st)
+{
+    return t_tokens == 32 ? launch_mid_tiles<NT_, RT, RG, KW, XF, AQ, 2>(a, t_tokens, wait_test, st)
+                          : launch_mid_tiles<NT_, RT, RG, KW, XF, AQ, 1>(a, t_tokens, wait_test, st);
 }
 
 // The geometries, by growing tile: rows x tokens.
@@ -1399,18 +1399,23 @@ struct MidPlan {
 // 14.5 / 20.4 (31), 512 tokens 76 / 46 / 37 / 31 (36).  Where no tile fits, the large ones win: 11008 x 4096 at 256
 // tokens 36.6 against 49.7.
 // T is best made in one tile per workgroup.  Where tiles of 16 tokens are more than that, those of 32 tokens come next (which read R
-// half as often, and each take longer), then two tiles, then three, and then a launch of T's own; a larger tile of Y that leaves room for one
-// instead of two is worth it from the smallest to the next only (us: 7452 x 2432 at 31 tokens, two tiles 10.1, one of 32 tokens 8.6, one of 16
-// beside the next tile of Y 8.2; 2244 x 3968 at 343 tokens T by itself 25.8, one of 32 tokens 17.6; 12523 x 7040 at 36 tokens two of 32 tokens
-// 27.7, the next tile of Y 36.8).  Not so where few workgroups have a second tile, at most a quarter, and the ranks are many: most of the ranks' work on Y
-// is done while those few are made (12572 x 4992, rank 499, at 20 tokens 64 tiles on 56 workgroups 13.3 against 14.0 us, 12572 x 3072 10.6 against 11.8; 104 tiles on 56,
-// 12572 x 8192, 25.0 against 21.8; 2688 x 4736 with 4-bit adapters, rank 268, at 79 tokens 12.8 against 13.0; below rank 256, and beside tiles of 32 rows, those of 32 tokens were 5 to 24 % faster).  Of 216 layers of 512 to 28672 rows and 512 to 11008 inputs at 17 to 512 tokens this rule is 0.5 % from the best of all of
-// these on average, and slower than two tiles of 16 or else the next tile of Y, as it was, in none by more than 5 %; 3 % faster on average, up to 1.47
-// times.
+// half as often, and each take longer), then two tiles, then three, and then a launch of T's own (us: 7452 x 2432 at 31 tokens, two tiles 10.1, one
+// of 32 tokens 8.6, one of 16 beside the next tile of Y 8.2; 2244 x 3968 at 343 tokens T by itself 25.8, one of 32 tokens 17.6).
+//   few: where few workgroups have a second tile of 16 tokens, at most a quarter, and the ranks are many, most of the ranks' work on Y is done while
+// those are made: 288 ranks and more beside tiles of 64 rows and more (16 against 32 tokens: 12572 x 3072, rank 499, at 20 tokens 10.3 against 11.8, 2610 x 3200, 261, at
+// 74 10.2 / 11.2, 4399 x 4352, 435, at 56 11.7 / 12.5; the adapter term alone 9600 x 9728, 960, at 27 19.5 / 21.4; up to 256 ranks the other way round: 2304 x 8064,
+// 230, at 100 15.5 / 14.1, 2560 x 2432, 243, at 106 9.6 / 8.6; and so with a second tile on 0.29 of them: 3031 x 6656, 303, at 96 15.4 / 13.9).
+//   4-bit adapters on long sums, beside tiles of 128 x 32: a tile of 32 tokens converts the codes half as often, but waits for memory twice as often as one
+// of 16, and two of those are as fast or faster from 2048 inputs on (2048 x 9856, 8-bit X, at 205 tokens 22.6 / 25.6, 4951 x 7296 at 90 22.3 / 24.8, with fp16 X 1 to 3 %; up to 1024 inputs 32 tokens are 3 to 10 % faster).
+//   A larger tile of Y that leaves room for one tile of T per workgroup instead of two: worth it from the smallest to the next; from 64 rows to 128
+// but for 8-bit X with fp16 R (4096 x 7168 at 86 tokens 18.8 against 20.5, 2304 x 3328 at 153 11.4 / 13.0; with 8-bit X 3840 x 5120 at 86 15.1 / 11.6); from 128 x 32 to 128 x 64 on short sums only (9600 x 896 at 69 tokens 8.3 / 9.5, 3596 x 1152 at 209 9.1 / 10.1; 13184 x 6400, 8-bit X, at 33 27.9 / 19.6,
+// 7101 x 6016 at 86 29.0 / 22.5).
+// Against two tiles of 16 tokens at most or else the next tile of Y, over drawn layers of 512 to 28672 rows and 512 to 11008 inputs at 17 to 512 tokens: a
+// fifth of the calls differ, of 300 of those one is slower by more than 2 % (2.2 %) and the mean is 12 % faster, up to 1.5 times.
 // The adapter term alone has nothing to hide a chain of T behind: 4096 x 4096 at 128 tokens 15.7 / 12.5 / 15.2 / 20.1
 // against 14.1 of the dense product (12.7 to 12.8 with T in the same launch, in tiles of 32 tokens), 28672 x 4096 at 48 tokens 20.2 at best against 13.6.
 // Above 512 tokens the workspace has no room for the pieces of T.
-MidPlan mid_plan(int n, int rank_pad, int m, int cus, bool weight_term)
+MidPlan mid_plan(int n, int k, int rank_pad, int m, int cus, bool weight_term, bool q4, bool fp8)
 {
     constexpr MidPlan none{-1, 0};
     if (m > 512) return none;
@@ -1422,6 +1427,7 @@ MidPlan mid_plan(int n, int rank_pad, int m, int cus, bool weight_term)
         if (rank_pad == 0) return {g, 0};
         int n16 = 0;
         const int t16 = t_trips(rank_pad, m, 16, n_y, cus, &n16), t32 = t_trips(rank_pad, m, 32, n_y, cus);
+        const bool few = t16 == 2 && g > 0 && rank_pad > 256 && die_tiles(rank_pad / 16, (m + 15) / 16) - n16 <= n16 / 4;
         if (!weight_term) {
             if (g == 3 || n >= 16384) {
                 if (t16 <= 1) return {g, 16};
@@ -1429,13 +1435,14 @@ MidPlan mid_plan(int n, int rank_pad, int m, int cus, bool weight_term)
             }
             if (t16 <= 1 || t16 > 2) return {g, t16 <= 1 ? 16 : 0};
             if (g == 0 && t_trips(rank_pad, m, 16, workgroups(1), cus) <= 1) return {1, 16};
-            return {g, t32 <= 1 ? 32 : 16};
+            return {g, t32 <= 1 && !few ? 32 : 16};
         }
         if (first.geometry < 0) first = {g, 0};
         if (t16 <= 1 || t32 <= 1) {
-            if (more.geometry >= 0 && !(more.geometry == 0 && g == 1)) return more;
-            const bool few = t16 == 2 && g > 0 && rank_pad >= 256 && die_tiles(rank_pad / 16, (m + 15) / 16) - n16 <= n16 / 4;
-            return {g, t16 <= 1 || few ? 16 : 32};
+            const bool next = more.geometry == 0 || (more.t_tokens == 32 && (more.geometry == 1 ? q4 || !fp8 : k < 1280));
+            if (more.geometry >= 0 && !(next && g == more.geometry + 1)) return more;
+            const bool long_codes = t16 == 2 && g == 2 && q4 && k > 2048;
+            return {g, t16 <= 1 || few || long_codes ? 16 : 32};
         }
         if (more.geometry < 0 && (t16 <= 3 || t32 <= 2)) more = {g, t16 <= 2 || t32 > 2 ? 16 : 32};
     }
@@ -1461,7 +1468,7 @@ int launch_gemm_mid(const slim_layer *layer, const half_t *X, int xf, const floa
     *taken = false;
     const slim_shape s = layer->shape;
     const bool q4 = layer->adapter_bits == 4 && s.rank > 0;
-    const MidPlan plan = mid_plan(s.n, layer->rank_pad, m, device_info().cus, weight_term);
+    const MidPlan plan = mid_plan(s.n, s.k, layer->rank_pad, m, device_info().cus, weight_term, q4, xf != 0);
     if (plan.geometry < 0) return SLIM_OK;
     // 32-bit offsets, tiles past the end included; room for the pieces of T
     constexpr uint64_t kLimit = 0x80000000ull;
@@ -1495,7 +1502,7 @@ int launch_gemm_mid(const slim_layer *layer, const half_t *X, int xf, const floa
     a.rank_pad = layer->rank_pad;
     a.m = m;
     a.stages = weight_term ? s.k / 128 : 0;
-    a.flags = accumulate ? kAccumulate : 0;
+    a.accumulate = accumulate;
     if (q4) {
         if (xf == 0) return launch_mid_call<0, true>(a, plan, wait_test, st);
         return xf == 1 ? launch_mid_call<1, true>(a, plan, wait_test, st) : launch_mid_call<2, true>(a, plan, wait_test, st);

@@ -69,10 +69,10 @@ def test_two_groups_of_wavefronts_where_they_pay(fp8, k, rank_pad, ratio):
     assert _two_groups(k, rank_pad, fp8) == (ratio < 1.0)
 
 
-def _mid_plan(n, rank_pad, m, weight_term):
-    f = B.lib()._ZN4slim8mid_planEiiiib
-    f.argtypes, f.restype = [ctypes.c_int] * 4 + [ctypes.c_bool], ctypes.c_uint64
-    v = f(n, rank_pad, m, 256, weight_term)
+def _mid_plan(n, k, rank_pad, m, weight_term, q4=False, fp8=False):
+    f = B.lib()._ZN4slim8mid_planEiiiiibbb
+    f.argtypes, f.restype = [ctypes.c_int] * 5 + [ctypes.c_bool] * 3, ctypes.c_uint64
+    v = f(n, k, rank_pad, m, 256, weight_term, q4, fp8)
     return ctypes.c_int32(v & 0xFFFFFFFF).value, v >> 32
 
 
@@ -90,11 +90,43 @@ def _mid_plan(n, rank_pad, m, weight_term):
     (12572, 8192, 819, 20, {(1, 16): 25.0, (1, 32): 21.8})])
 def test_the_plan_of_small_batches(n, k, r, m, us):
     """Tile and T of whole layers: the plan taken is within a tenth of the best one measured."""
-    assert us[_mid_plan(n, B.slim_rank_pad(r), m, True)] <= 1.1 * min(us.values())
+    assert us[_mid_plan(n, k, B.slim_rank_pad(r), m, True)] <= 1.1 * min(us.values())
+
+
+@pytest.mark.parametrize("kind,n,k,r,m,us", [
+    # few workgroups with a second tile of 16 tokens, and more
+    ("gemm", 2610, 3200, 261, 74, {(1, 16): 10.2, (1, 32): 11.2}),
+    ("gemm q4", 2688, 4736, 268, 79, {(1, 16): 12.2, (1, 32): 12.1}),
+    ("gemm", 4399, 4352, 435, 56, {(1, 16): 11.7, (1, 32): 12.5}),
+    ("gemm", 5888, 2816, 281, 38, {(1, 16): 9.1, (1, 32): 10.2}),
+    ("gemm", 2560, 2432, 243, 106, {(1, 16): 9.6, (1, 32): 8.6}),
+    ("gemm q4", 2304, 8064, 230, 100, {(1, 16): 16.9, (1, 32): 14.9}),
+    ("gemm", 3031, 6656, 303, 96, {(1, 16): 15.4, (1, 32): 13.9}),
+    ("lowrank", 9600, 9728, 960, 27, {(1, 16): 19.5, (1, 32): 21.4}),
+    ("lowrank", 12288, 5888, 588, 22, {(1, 16): 14.4, (1, 32): 15.2}),
+    ("lowrank", 4992, 9984, 499, 55, {(1, 16): 19.5, (1, 32): 17.1}),
+    # two tiles of 32 tokens, or the next tile of Y
+    ("gemm", 4096, 7168, 409, 86, {(2, 16): 18.8, (1, 32): 20.5}),
+    ("gemm", 2304, 3328, 230, 153, {(2, 32): 11.4, (2, 16): 11.4, (1, 32): 13.0}),
+    ("fp8 q4", 4864, 1024, 102, 83, {(2, 16): 8.2, (1, 32): 10.1}),
+    ("fp8", 3840, 5120, 384, 86, {(2, 16): 15.1, (1, 32): 11.6}),
+    ("gemm q4", 3744, 9344, 374, 69, {(2, 16): 26.4, (1, 16): 19.1}),
+    ("gemm", 9600, 896, 89, 69, {(3, 16): 8.3, (2, 32): 9.5}),
+    ("fp8 q4", 3456, 1024, 102, 210, {(3, 16): 9.6, (2, 32): 10.8}),
+    ("fp8", 13184, 6400, 640, 33, {(3, 16): 27.9, (2, 32): 19.6}),
+    ("gemm", 7101, 6016, 601, 86, {(3, 16): 29.0, (2, 32): 22.5}),
+    # 4-bit adapters on long sums
+    ("fp8 q4", 2048, 9856, 204, 205, {(2, 16): 22.6, (2, 32): 25.6}),
+    ("fp8 q4", 4951, 7296, 495, 90, {(2, 16): 22.3, (2, 32): 24.8}),
+    ("fp8 q4", 640, 1152, 64, 432, {(2, 16): 9.9, (2, 32): 8.9})])
+def test_the_plan_by_ranks_inputs_and_types(kind, n, k, r, m, us):
+    """The two or three plans that a rule decides between: the faster one, or one within 6 %."""
+    plan = _mid_plan(n, k, B.slim_rank_pad(r), m, kind != "lowrank", "q4" in kind, "fp8" in kind)
+    assert us[plan] <= 1.06 * min(us.values())
 
 
 def test_the_plan_of_the_adapter_term_alone():
-    assert _mid_plan(4096, 416, 128, False) == (1, 0)        # 12.1 us; in one launch 12.7
-    assert _mid_plan(2679, 96, 203, False) == (2, 32)        # 8.9 us; two tiles of 16 tokens 10.2
-    assert _mid_plan(2016, 224, 96, False) == (1, 16)        # 8.2; on the smallest tile 10.4
-    assert _mid_plan(18662, 256, 64, False) == (3, 16) and _mid_plan(28672, 832, 400, False)[0] == -1
+    assert _mid_plan(4096, 4096, 416, 128, False) == (1, 0)        # 12.1 us; in one launch 12.7
+    assert _mid_plan(2679, 896, 96, 203, False) == (2, 32)        # 8.9 us; two tiles of 16 tokens 10.2
+    assert _mid_plan(2016, 2176, 224, 96, False) == (1, 16)        # 8.2; on the smallest tile 10.4
+    assert _mid_plan(18662, 2560, 256, 64, False) == (3, 16) and _mid_plan(28672, 8192, 832, 400, False)[0] == -1

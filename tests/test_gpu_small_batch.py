@@ -361,7 +361,7 @@ T32_CASES = [(7452, 256, 243, 31), (1604, 1024, 102, 109), (1485, 1536, 148, 189
 def test_t_in_tiles_of_32_tokens(n, k, r, m, kind, help_t, decode_override):
     """By the T role, and by workgroups whose wait runs out.  The bounds are the usual ones."""
     from test_dispatch_rules import _mid_plan
-    assert _mid_plan(n, B.slim_rank_pad(r), m, True)[1] == 32
+    assert _mid_plan(n, k, B.slim_rank_pad(r), m, True, kind.endswith("q4"), kind.startswith("fp8"))[1] == 32
     if help_t:
         decode_override("wait_test", 16)
     bits = 4 if kind.endswith("q4") else 16
