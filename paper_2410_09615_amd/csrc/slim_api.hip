@@ -48,7 +48,7 @@ bool adapters_wait_test() { return t_wait_test && decode_path_override() == 3; }
 size_t decode_lds_limit() { return (size_t)g_decode_lds_kb.load(std::memory_order_relaxed) * 1024; }
 
 // The most ranges of inputs that T = X R^T is split into, for which a workspace has room: enough that 256 ranks x 128 tokens each make
-// 192 workgroups, of at least 512 inputs.
+// 192 workgroups, of at least 512 inputs.  With tiles of 128 x 128 the best number was this or less wherever that was measured (t_splits(), slim_gemm_mid.hip).
 int gemm_t_splits(int32_t m, int32_t rank_pad, int32_t k)
 {
     const long tiles = (long)((rank_pad + 255) / 256) * ((m + 127) / 128);

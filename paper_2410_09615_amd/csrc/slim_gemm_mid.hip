@@ -720,7 +720,9 @@ int launch_t_split(const half_t *X, int xf, const float *x_scale, int m, int k, 
 // fitted to 6048 measured products (ranks 32 to 1408, 17 to 4096 tokens, 512 to 28672 inputs, X in fp16 and 8 bits, R in
 // fp16 and 4 bits; kind 4: 500, at every number of ranges): off by 5 to 15 %, 4 % for kind 4, which makes the kind taken 1 % slower than the best one on
 // average.  Those of kind 4 with fp16 R are a tenth above the fit: where both are about as fast the one launch is taken, which needs no memory
-// for partial sums.  Up to 128 tokens, one tile of them, it was not measured and is not taken.
+// for partial sums (4096 x 416 x 4096 29.7 / 24.8, 8192 inputs, rank 832, 512 tokens 21.2 / 18.6).  Up to 128 tokens, one tile of them, kind 4 is not taken: the one launch is the faster
+// there as long as a workgroup of it has one tile (rank 416 at 128 tokens, 8192 inputs 7.9 / 13.5, 28672 inputs 21.7 / 25.0), and where it has more (28672 inputs, rank 832, 100
+// tokens 39 / 25) the calls are those of layers with too many rows for the small batches' tiles.
 //   8192 inputs, fp16 (us; kinds 0 to 3): rank 64 at 800 tokens 10.6 / 14.8 / 20.5 / 20.3, rank 512 at 1000 tokens
 //   27.0 / 20.6 / 25.8 / -, rank 832 at 600 tokens 37.1 / 37.2 / 27.6 / -, at 1000 tokens 49.2 / 37.5 / 27.8 / - (kind 4 there 25 to 26).
 struct TCost {
