@@ -111,6 +111,59 @@ def test_a_factorisation_is_as_near_as_the_hosts(rows, l):
     assert float((_orth(Y.to(DEV)).cpu().double() - exact).norm()) <= float((host(Y) - exact).norm())
 
 
+@pytest.mark.parametrize("rows,l", [(300, 192), (1000, 224), (1030, 448), (900, 640)])
+@pytest.mark.parametrize("gain", [0, -50, 45])
+def test_columns_below_the_floor_among_three_tiles_and_more(rows, l, gain):
+    """Columns 1e-6 of the others in every tile of 64, the last tile's end zeros: their pivots are below the floor (1e-12 of the largest), and the
+    other columns are as near to the exact ones of the block without them as the host's library in binary32 (taken twice: l columns, of which fewer
+    count).  A block times a power of two, beyond 2^60 in its Gram matrix factored as 4^h times it: the same columns to the bit."""
+    g = torch.Generator().manual_seed(rows + l)
+    Y = torch.randn(rows, l, generator=g)
+    Y = Y @ (torch.randn(l, l, generator=g) * 0.3 / l ** 0.5 + torch.eye(l)) + 0.2
+    dead = sorted({c for t in range(0, l, 64) for c in (t + 3, t + 17, t + 40) if c < l} | set(range(l - 9, l)))
+    live = [c for c in range(l) if c not in dead]
+    Y[:, dead] *= 1e-6
+    Y[:, l - 9:] = 0
+
+    def host(A):
+        return torch.linalg.solve_triangular(torch.linalg.cholesky(A.T @ A), A.T.contiguous(), upper=False).T.double()
+
+    plain = _orth(Y.to(DEV)).cpu()
+    exact = host(Y[:, live].double())
+    assert float((plain[:, live].double() - exact).norm()) <= 2 * float((host(Y[:, live]) - exact).norm())
+    if gain:
+        assert torch.equal(_orth(torch.ldexp(Y, torch.tensor(gain)).to(DEV)).cpu()[:, live], plain[:, live])
+
+
+def test_calls_on_several_streams_at_once():
+    """Workgroups of a factorisation wait for one another: three calls on streams of their own, beside small batches on a fourth, end with what
+    each of them gives alone (no sum of L and R depends on the order of additions)."""
+    shapes = [(1100, 1152, 705), (700, 1280, 470), (1500, 1536, 1024)]
+    packed = []
+    for n, k, r in shapes:
+        W = wl.make_weight(n, k, seed=n).to(DEV)
+        packed.append((W, *B.slim_pack(W), r))
+    n, k, r, m = 2048, 2048, 204, 40
+    layer = B.compress(wl.make_weight(n, k, seed=3).to(DEV), *(a.to(DEV) for a in wl.make_adapters(n, k, r)))
+    X, ws = wl.make_activations(m, k).to(DEV), B.alloc_workspace(layer, m)
+    alone = [B.slim_compute_adapters(*p, iters=4) for p in packed]
+    want = B.slim_linear_gemm(layer, X, workspace=ws).clone()
+    torch.cuda.synchronize()
+    streams, got, ys = [torch.cuda.Stream() for _ in range(4)], [None] * 3, []
+    for _ in range(3):
+        for i, p in enumerate(packed):
+            with torch.cuda.stream(streams[i]):
+                got[i] = B.slim_compute_adapters(*p, iters=4)
+        with torch.cuda.stream(streams[3]):
+            ys += [B.slim_linear_gemm(layer, X, workspace=ws) for _ in range(20)]
+    torch.cuda.synchronize()
+    for a, b in zip(alone, got):
+        assert torch.equal(a[0], b[0]) and torch.equal(a[1], b[1])
+        assert bool(torch.isfinite(b[2]).all()) and float(b[2][2]) < 1e-4
+    assert all(torch.equal(y, want) for y in ys)
+    B.slim_workspace_check(ws)
+
+
 def start_block(rows, cols, r, seed=1):
     """The seeded start block: uniform in (-1, 1) from a hash of (seed, element), cols columns of which r are used."""
     def mix(v):
