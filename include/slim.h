@@ -206,19 +206,22 @@ int slim_quant_search_rows(const float *W, slim_shape shape, float *scale_out, f
  *   diag         (may be NULL) four floats out: ||S||_F^2, the captured part
  *                ||L^T S||_F^2 (the exact truncation captures the sum of the rank
  *                largest squared singular values), max |L^T L - I| (infinite if L is not finite), 0.
- * Arithmetic: S, the Gram matrices, the orthonormalisations, L, R and what diag reports are fp32.  The products
- * with S in the rounds run on the fp16 matrix cores, both operands as two fp16 numbers each and the sums in fp32: S up to
- * 2^-23 of an element or 2^-39 of the largest one, whichever is more, so elements 2^17 below the largest and smaller
- * lose bits.  Their error against 64 bits is below that of fp32 products (2.2e-7 against 5.8e-7 in the 2-norm at 4096 x
- * 4096, every row and column of the result included) for saliencies that span up to 1e3; beyond, it still is in the
- * 2-norm, but rows and columns of the result far below the largest are less exact (channels 1e6 below: 8e-6 against 7e-7).
+ * Arithmetic: S, the Gram matrices, the orthonormalisations and what diag reports are fp32.  The products with S,
+ * those of the rounds and the R~ = L^T S that R is made of, run on the fp16 matrix cores, both operands as two fp16 numbers
+ * each and the sums in fp32: a block's entries up to 2^-22 of an entry or 2^-42; S, where it is multiplied by a block of inputs, up to
+ * 2^-22 of an element or 2^-49 of the largest of S, whichever is more; S transposed (R~ too) up to 2^-22 of an element or 2^-49 of the
+ * largest of its channel.  Against 64 bits they are as near as fp32 products (4096 x 4096, 2-norm, largest of a column and of a
+ * row: 1e-7 to 4e-7) for saliencies, channels of the weights and rows of the weights that span 1e6; with rows over 1e9
+ * a row of the result is off by 5e-6.  (From 2^22 rows or inputs on they are fp32 products.)
  * Between two blocks that are orthonormalised up to eight products may run whose columns are only scaled, as many as
  * the pivots of the last such block allow (two up to a span of 1e4, from the seventh product on four up to 1e3 and eight
  * up to 30); the last block always is orthonormalised, with no more than four before it.  Before L is rounded to fp16 its span
  * is as near the exact iterate's as with two in a row at most up to a factor of 1.5, and as with every block orthonormal
  * up to one of about 3 (replayed on the CPU: 2e-6 to 2e-5 in the 2-norm, where fp16 rounds at 5e-4).
- * workspace: slim_adapters_workspace_bytes (HOST out-pointer; about 12 n k bytes -- S in fp32, S and its transpose as
- * two fp16 matrices -- plus 19 to 50 bytes per element of a block of max(n, k) x rank_pad, on small layers a few MB more), need not be zeroed.  Errors: NULL, SHAPE, ALIGN, WORKSPACE, HIP.
+ * workspace: slim_adapters_workspace_bytes (HOST out-pointer), need not be zeroed: 12 n k bytes (S in fp32, S and its transpose as
+ * two fp16 matrices each), at most 84 bytes per element of a block of max(n, k) x rank_pad (20 for the blocks themselves, 4 for each of up to 16
+ * shares that a product is added up from; 19 in all at 28672 x 8192, rank 820) and at most 16 MB (n counts in whole 32s).
+ * Errors: NULL, SHAPE, ALIGN, WORKSPACE, HIP.
  * The workgroups of a factorisation hand tiles to one another; those waits are bounded, and should one run out, L and R are NaN.
  * The call has returned SLIM_OK by then and there is no error word: diag[2] is infinite, which is how a caller detects it.
  */

@@ -833,10 +833,10 @@ __device__ __forceinline__ float column_scale(unsigned max_bits)
     return max_bits == 0u ? 1.0f : __uint_as_float((unsigned)max(253 - e, 1) << 23);
 }
 
+// 16 rows of out = in Lc^-T, block column after block column; wavefront w computes the columns 16 w .. 16 w + 15 of each.
 // Where the step skips the orthonormalisation: 16 rows of out = `in` with scaled columns (colmax: kColSlots rows of bits of their
 // largest magnitudes).  clear: those of the next block, set to zero.
-// 16 rows of out = in Lc^-T, block column after block column; wavefront w computes the columns 16 w .. 16 w + 15 of each.
-// It is a chain of latencies (matrix cores 6.5 us of the 20).  The two fp16 numbers go out from the registers that hold a block column, and the wavefronts meet
+// The orthonormalisation is a chain of latencies (matrix cores 6.5 us of the 20).  The two fp16 numbers go out from the registers that hold a block column, and the wavefronts meet
 // before they need one another's columns, not after each block column: 1.2 us less than with the whole rows converted from LDS at the end.
 __global__ __launch_bounds__(256) void lora_apply_kernel(const float *__restrict__ in, float *__restrict__ out, int rows, int l, int nb,
                                                          const float *__restrict__ Lf, const float *__restrict__ D, half_t *__restrict__ hi,

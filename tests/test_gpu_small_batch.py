@@ -137,7 +137,7 @@ def test_large_tiles_every_stage_count_modulo_six(stages, fp8):
 
 # T = X R^T in one launch: as fp16 rows for the 512 x 128 tiles (m > 512) and as pieces (n = 4096: no unit is left for the
 # T role), tiles of 16 x 16, 32 x 32, 32 x 64 and 64 x 64 in turn, the last tile of tokens and of ranks partly empty,
-# fewer units of inputs than wavefronts and more; the last case is the split product's.
+# fewer units of inputs than wavefronts and more; the last case is of the tiles of 128 x 128.
 T_CASES = [(200, 384, 51, 530), (200, 1792, 200, 530), (200, 256, 510, 545), (200, 128, 992, 577), (200, 1664, 970, 530),
            (4096, 640, 51, 500), (4096, 384, 200, 499), (4096, 256, 530, 481), (4096, 1664, 1100, 500),
            (130, 128, 1024, 2100)]

@@ -109,6 +109,17 @@ def test_missing_library_fails_loudly(monkeypatch):
         B.lib()
 
 
+@pytest.mark.parametrize("n", [1, 33, 1000, 4096, 28672, (1 << 22) + 1])
+@pytest.mark.parametrize("k", [128, 1152, 4096, 8192])
+def test_adapter_workspace_is_what_the_header_says(n, k):
+    for r in (1, 32, 100, 225, 410, 820, 1024):
+        if r > min(n, k):
+            continue
+        out, n32 = ctypes.c_size_t(), -(-n // 32) * 32
+        assert B.lib().slim_adapters_workspace_bytes(B.slim_shape(n, k, r), out) == 0
+        assert out.value <= 12 * n32 * k + 84 * max(n32, k) * B.slim_rank_pad(r) + (16 << 20)
+
+
 def test_adapter_computation_workspace_query_and_validation():
     lib = B.lib()
     out = ctypes.c_size_t()
