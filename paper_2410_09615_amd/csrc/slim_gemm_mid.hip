@@ -1272,8 +1272,9 @@ template <int NT_, int RT, int RG, int KW, int XF, bool AQ, int TT>
 __global__ __launch_bounds__(kMidThreads, 3) void mid_kernel(MidArgs a)
 {
     extern __shared__ __attribute__((aligned(16))) char lds_c[];
-    // with tiles of T of 16 tokens: beside tiles of 32 rows 1 to 2 % faster, with 8-bit X and 4-bit adapters 7 % (and up to 6 beside 64 rows), elsewhere up to 8 % slower
-    constexpr bool HIDE = TT == 2 || RG == 1 || (XF != 0 && AQ && RT == 1 && RG == 2);
+    // with tiles of T of 16 tokens: beside tiles of 32 and 64 rows 1 to 2 % faster, with 8-bit X and 4-bit adapters up to 8 %, but 5 % slower beside 64 rows with fp16 X and
+    // 4-bit adapters, and beside larger tiles 1 to 5 % slower
+    constexpr bool HIDE = TT == 2 || RG == 1 || (RT == 1 && RG == 2 && (XF != 0 || !AQ));
     const unsigned epoch = a.rank_pad > 0 && a.T ? call_epoch(a.epoch) : 0u;
     if ((int)blockIdx.x < a.n_t) {
         t_tiles<XF, AQ, TT, HIDE>(a, blockIdx.x, a.n_t, lds_c, epoch);
